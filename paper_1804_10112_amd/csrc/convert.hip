@@ -1,6 +1,7 @@
 // COO -> CSR (paper Section 5.4, Figure 14) on gfx950.
 //
-//   1. reorder (Section 4.3 "reordering"): a stable least-significant-digit
+//   1. reorder (Section 4.3 "reordering"): up to 2^26 records by sample sort
+//      (sample_sort.hip, which also assembles pos); beyond, a stable least-significant-digit
 //      radix sort of the (row, col, value) records, 8 bits per pass, over the
 //      significant bits of the column (ROW_COL order only) and then of the row.
 //      Every pass is histogram -> exclusive scan -> stable scatter; the records
@@ -178,7 +179,16 @@ static SortPlan plan(const spt_tensor* A, int32_t order) {
   return P;
 }
 
+// sample sort (sample_sort.hip): up to 2^26 records
+bool sample_sort_applies(int64_t n);
+size_t sample_sort_workspace(int dtype, int64_t n);
+template <typename VT>
+spt_status sample_sort_convert(int64_t n, int64_t nrows, int64_t ncols, bool by_col, const int32_t* row,
+                               const int32_t* col, const VT* vals, int32_t* pos_out, int32_t* crd_out,
+                               VT* vals_out, void* ws, size_t ws_bytes, hipStream_t s);
+
 size_t coo_to_csr_workspace(const spt_tensor* A) {
+  if (sample_sort_applies(A->nvals)) return sample_sort_workspace(A->dtype, A->nvals);
   return std::max(plan(A, SPT_ORDER_ROW_COL).total, plan(A, SPT_ORDER_ROW_STABLE).total);
 }
 
@@ -190,10 +200,9 @@ static spt_status convert_typed(const spt_tensor* A, int32_t order, int32_t* pos
   if (nnz64 + kSortTile >= INT32_MAX || N + 1 >= INT32_MAX)
     return fail(SPT_ERR_UNSUPPORTED, "coo_to_csr: more than 2^31 entries or rows");
   const int nnz = (int)nnz64;
-  const SortPlan P = plan(A, order);
-  if (!ws || ws_bytes < P.total)
-    return fail(SPT_ERR_WORKSPACE, "coo_to_csr: workspace of %zu bytes needed, %zu given", P.total,
-                ws_bytes);
+  const size_t need = coo_to_csr_workspace(A);
+  if (!ws || ws_bytes < need)
+    return fail(SPT_ERR_WORKSPACE, "coo_to_csr: workspace of %zu bytes needed, %zu given", need, ws_bytes);
   const int32_t* row = A->level[0].crd;
   const int32_t* col = A->level[1].crd;
   const VT* vals = static_cast<const VT*>(A->vals);
@@ -205,18 +214,6 @@ static spt_status convert_typed(const spt_tensor* A, int32_t order, int32_t* pos
     return SPT_OK;
   }
 
-  Workspace W(ws, ws_bytes);
-  int32_t* srow[2];
-  int32_t* scol[2];
-  VT* sval[2];
-  for (int b = 0; b < 2; ++b) {
-    srow[b] = W.take<int32_t>(nnz);
-    scol[b] = W.take<int32_t>(nnz);
-    sval[b] = W.take<VT>(nnz);
-  }
-  int32_t* hist = W.take<int32_t>((size_t)kRadix * P.ntiles);
-  int32_t* scan_tmp = reinterpret_cast<int32_t*>(W.take<char>(P.scan_bytes));
-
   const bool sorted_in = (A->level[0].flags & SPT_ORDERED) &&
                          (order == SPT_ORDER_ROW_STABLE || (A->level[1].flags & SPT_ORDERED));
   const int32_t* sorted_rows = row;
@@ -225,7 +222,22 @@ static spt_status convert_typed(const spt_tensor* A, int32_t order, int32_t* pos
     hipLaunchKernelGGL(copy_entries_kernel<VT>, dim3(egrid), dim3(kBlock), 0, s, nnz, col, vals,
                        crd_out, vals_out);
     SPT_CHECK_LAUNCH("copy_entries");
+  } else if (sample_sort_applies(nnz64)) {
+    return sample_sort_convert<VT>(nnz64, N, A->level[1].N, order == SPT_ORDER_ROW_COL, row, col, vals, pos_out,
+                                   crd_out, vals_out, ws, ws_bytes, s);
   } else {
+    const SortPlan P = plan(A, order);
+    Workspace W(ws, ws_bytes);
+    int32_t* srow[2];
+    int32_t* scol[2];
+    VT* sval[2];
+    for (int b = 0; b < 2; ++b) {
+      srow[b] = W.take<int32_t>(nnz);
+      scol[b] = W.take<int32_t>(nnz);
+      sval[b] = W.take<VT>(nnz);
+    }
+    int32_t* hist = W.take<int32_t>((size_t)kRadix * P.ntiles);
+    int32_t* scan_tmp = reinterpret_cast<int32_t*>(W.take<char>(P.scan_bytes));
     const int npass = P.passes_col + P.passes_row;
     const int32_t *rin = row, *cin = col;
     const VT* vin = vals;

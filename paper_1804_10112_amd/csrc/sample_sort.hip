@@ -1,0 +1,958 @@
+// COO -> CSR by sample sort (paper Section 4.3 reordering + Section 5.4), gfx950.
+//
+// A radix sort of (row, column) keys moves every record once per 8 bits of key, six times for
+// 22-bit rows and columns, and starts four kernels each time. Here the key range is cut at
+// splitters drawn from the input itself, so that every piece holds about the same number of
+// records however skewed the rows are, and pieces that fit the LDS of one workgroup are finished
+// there:
+//   up to kSelectMax records          one launch: workgroup j sorts a sample of the keys, picks
+//                                     the records between its two splitters out of the whole
+//                                     input (which stays in L2) and sorts them;
+//   up to kTwoLevelMin                one stable partition into up to 256 buckets, then the same
+//                                     selection inside each bucket;
+//   beyond                            two stable partitions, then one workgroup per bucket.
+// A partition is count -> exclusive scan -> stable scatter, as a radix pass, with the digit found
+// by bisection among the splitters instead of taken from the key bits. The count kernel notes
+// each record's digit in one byte for the scatter.
+// Equal keys: splitters are (key, position) pairs, so that even a million copies of one
+// coordinate spread over the buckets, and inside a bucket records carry their number in input
+// order: the result is that of a stable sort.
+// pos (Table 3: running sum of the row counts) falls out of the last step: the workgroup of the
+// keys between splitters of rows a and b stores pos[a+1 .. b].
+// A bucket that the sample got wrong (more records than fit LDS; its chance is below 1e-4 per
+// call for any input that does not know the sampling positions) is ranked by counting, slowly
+// but correctly.
+//
+// Measured against the six radix passes it replaces (fp64): 60M records with power-law rows
+// 3.09 -> 1.80 ms (splitters 35 + 87 us, classify 2 x 150, scans 4 x 9, partitions 427 + 441,
+// finish 505); 50 000 records 171 -> 21 us. The partitions write 256 x 2 interleaved streams and
+// are bound by how the memory system takes them: with twice the waves per compute unit (512
+// threads, half the registers) they are slower (474 us), with tiles of 8192 too (515 us). The
+// finishing kernel is bound by vector instructions.
+#include <algorithm>
+
+#include "blocksort.hpp"
+#include "common.hpp"
+#include "radix.hpp"
+#include "rows.hpp"
+#include "scan.hpp"
+#include "wavescan.hpp"
+
+namespace spt {
+
+constexpr int kFin = 256;           // threads of a workgroup that finishes a bucket of its own
+constexpr int kSel = 1024;          // threads of a workgroup that selects its records first
+constexpr int kCap = 4096;          // records either can sort in LDS
+constexpr int kStaged = 2048;       // records whose keys and values also pass through LDS (own bucket)
+constexpr int kTile = 4096;         // records per tile of a partition
+constexpr int kPart = 256;          // threads that scatter a tile
+constexpr int kPartWaves = kPart / kWave;
+constexpr int kPartIPT = kTile / kPart;
+constexpr int kGroup = 4;           // consecutive tiles that one workgroup classifies
+constexpr int kLiBits = 12;         // bits of a record's number inside its bucket; the rest of a word: its key, coarsely
+constexpr int kMaxSamples = 4096;   // numbered by kLiBits bits, too
+constexpr int kSelTarget1 = 384;    // records per workgroup: selected out of the whole (small) input,
+constexpr int kSelTarget2 = 1024;   // selected out of a bucket,
+constexpr int kDirTarget = 1408;    // of a bucket of its own
+constexpr int64_t kSelectMax = 128 * 1024;  // every workgroup reads all rows: 512 KB from L2
+constexpr int64_t kTwoLevelMin = 4 << 20;   // 256 buckets of 16K records, each read by 16 workgroups
+constexpr int64_t kSampleSortMax = int64_t(1) << 26;  // 256 x 256 buckets of kDirTarget and the sample's spread
+constexpr int kSegMax = 256;        // buckets of a partition
+
+// Position of sample t of S out of m records: one in every m / S, at a place of the stretch that
+// differs from stretch to stretch.
+template <int S>
+__device__ __forceinline__ int sample_pos(int t, int m) {
+  static_assert(S <= kMaxSamples, "");
+  const uint32_t jitter = (static_cast<uint32_t>(t) * 2654435769u) >> 16;
+  return static_cast<int>((((static_cast<uint64_t>(t) << 16) | jitter) * static_cast<uint64_t>(m) / S) >> 16);
+}
+
+// How a record's key is put together: K = row << cb | col; what the order compares is K
+// (row, then column) or the row alone (kshift = cb: rows stable).
+struct KeyForm {
+  int cb;      // bits of a column
+  int kshift;  // 0: order by (row, col); cb: by row
+  __device__ __forceinline__ int row_of(uint64_t ckey) const {
+    return static_cast<int>(kshift ? ckey : ckey >> cb);
+  }
+  __device__ __forceinline__ int col_of(uint64_t K) const { return static_cast<int>(K & ((uint64_t{1} << cb) - 1)); }
+};
+
+// The records of one level: the caller's row and column arrays, or packed keys of a partition.
+struct RcSource {
+  const int32_t* __restrict__ row;
+  const int32_t* __restrict__ col;
+  __device__ __forceinline__ uint64_t key(int p, const KeyForm& f) const {
+    return (static_cast<uint64_t>(static_cast<uint32_t>(row[p])) << f.cb) | static_cast<uint32_t>(col[p]);
+  }
+  __device__ __forceinline__ uint64_t key_stream(int p, const KeyForm& f) const {
+    return (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_nontemporal_load(row + p))) << f.cb) |
+           static_cast<uint32_t>(__builtin_nontemporal_load(col + p));
+  }
+  // selection reads the row first and the column only where it decides
+  typedef int32_t Coarse;
+  static constexpr int kUnroll = 16;
+  __device__ __forceinline__ Coarse coarse(int p) const { return row[p]; }
+  __device__ __forceinline__ int coarse_row(Coarse c, const KeyForm&) const { return c; }
+  __device__ __forceinline__ uint64_t fine(Coarse c, int p, const KeyForm& f) const {
+    return (static_cast<uint64_t>(static_cast<uint32_t>(c)) << f.cb) | static_cast<uint32_t>(col[p]);
+  }
+};
+struct KSource {
+  const uint64_t* __restrict__ k;
+  __device__ __forceinline__ uint64_t key(int p, const KeyForm&) const { return k[p]; }
+  __device__ __forceinline__ uint64_t key_stream(int p, const KeyForm&) const { return __builtin_nontemporal_load(k + p); }
+  typedef uint64_t Coarse;
+  static constexpr int kUnroll = 8;
+  __device__ __forceinline__ Coarse coarse(int p) const { return k[p]; }
+  __device__ __forceinline__ int coarse_row(Coarse c, const KeyForm& f) const { return static_cast<int>(c >> f.cb); }
+  __device__ __forceinline__ uint64_t fine(Coarse c, int, const KeyForm&) const { return c; }
+};
+
+// A cut of the order: everything from (key, pos) on.
+struct Cut {
+  uint64_t key;
+  int pos;
+  __device__ __forceinline__ bool at_or_before(uint64_t k, int p) const {
+    return key < k || (key == k && pos <= p);
+  }
+};
+
+// ---- segments of the second level -----------------------------------------------------------
+struct Tables {
+  int32_t* seg_start;  // [nseg + 1] first record of each bucket of level 1
+  int32_t* seg_tile;   // [nseg + 1] tiles before the segment
+  int32_t* seg_group;  // [nseg + 1] groups of kGroup tiles before the segment
+  int32_t* seg_bucket; // [nseg + 1] final buckets before the segment
+  int32_t* group_seg;  // segment of each group
+  int32_t* tile_seg;   // segment of each tile
+  int32_t* bucket_seg; // segment of each final bucket
+};
+
+__device__ __forceinline__ int tiles_in(int m) { return (m + kTile - 1) / kTile; }
+__device__ __forceinline__ int final_buckets(int m, int target) {
+  return max(1, min(kSegMax, (m + target - 1) / target));
+}
+
+// ---- sorting a few thousand records in one workgroup ------------------------------------------
+// Orders n records (numbered as in the input) by key.
+// A record travels through the sort as one 32-bit word: 20 bits of its key's place between the
+// bounds `base` and `base` + 2^(20 + shift), 12 bits of its number in input order; where that many
+// bits do not tell two neighbours apart, a record counts the keys of its stretch that come before
+// it (`key_at` gives the whole key of a record). Mostly such stretches are two or three records long.
+// Bound by vector instructions (110 of 225 per record in the finishing kernel are the network).
+// Left out after measuring: dealing the words to 1024 equal bins of the key range and ranking
+// inside the bins (631 instead of 503 us for 60M records with power-law rows: long and short rows
+// in one bucket crowd the bins).
+// words: NT * E words of LDS; ord: n half-words, the records in order.
+template <int NT, int E, class KA>
+__device__ __forceinline__ void sort_records(uint32_t* words, uint16_t* ord, int n, uint64_t base, int shift,
+                                             const KA& key_at) {
+  const int tid = threadIdx.x;
+  uint32_t v[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int li = e * NT + tid;
+    v[e] = ~0u;
+    if (li < n) v[e] = (static_cast<uint32_t>((key_at(li) - base) >> shift) << kLiBits) | li;
+  }
+  block_sort_u32<NT, E>(v, words);
+  constexpr uint32_t kLi = (1 << kLiBits) - 1;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int i = e * NT + tid;
+    if (i < n) {
+      const uint32_t w = words[i], q = w >> kLiBits;
+      const int li = w & kLi;
+      int at = i;
+      if (shift > 0 && ((i > 0 && words[i - 1] >> kLiBits == q) || (i + 1 < n && words[i + 1] >> kLiBits == q))) {
+        const uint64_t key = key_at(li);
+        int g = i;
+        while (g > 0 && words[g - 1] >> kLiBits == q) --g;
+        at = g;
+        for (; g < n && words[g] >> kLiBits == q; ++g) {
+          const int other = words[g] & kLi;
+          const uint64_t k = key_at(other);
+          at += (k < key || (k == key && other < li)) ? 1 : 0;
+        }
+      }
+      ord[at] = static_cast<uint16_t>(li);
+    }
+  }
+  __syncthreads();
+}
+
+// The number of low key bits that 20 bits cannot hold between two bounds.
+__device__ __forceinline__ int coarse_shift(uint64_t lo, uint64_t hi) {
+  const int bits = 64 - __clzll(static_cast<long long>((hi - lo) | 1));
+  return max(0, bits - (32 - kLiBits));
+}
+
+// ---- splitters ------------------------------------------------------------------------------
+// Sorts S = 1024 * E sampled keys of segment blockIdx.x and takes every (S / nb)th as a splitter.
+// LEVEL2: the segment is a bucket of level 1 (bounds from that level's scanned counts `off1`),
+// nb follows from its size, and the workgroup fills in its rows of the segment tables.
+template <int E, class SRC, bool LEVEL2>
+__global__ __launch_bounds__(1024) void splitters_kernel(const SRC src, const KeyForm f, int n, int nrows, int nb_fixed,
+                                                         const int32_t* __restrict__ off1, int ntiles1, int nseg,
+                                                         const Tables T, const uint64_t* __restrict__ skey1,
+                                                         uint64_t* __restrict__ skey,
+                                                         int32_t* __restrict__ spos) {
+  constexpr int S = 1024 * E;
+  __shared__ uint64_t s_key[S];
+  __shared__ __attribute__((aligned(16))) uint32_t words[S];
+  __shared__ uint16_t ord[S];
+  __shared__ int s_sum[4];
+  const int tid = threadIdx.x;
+  const int seg = blockIdx.x;
+  int begin = 0, m = n, nb = nb_fixed;
+  if (LEVEL2) {
+    if (tid < 4) s_sum[tid] = 0;
+    __syncthreads();
+    begin = off1[static_cast<int64_t>(seg) * ntiles1];
+    m = (seg + 1 < kRadix ? off1[static_cast<int64_t>(seg + 1) * ntiles1] : n) - begin;
+    nb = final_buckets(m, kDirTarget);
+    if (tid < seg) {  // what the segments before this one take of each table
+      const int b = off1[static_cast<int64_t>(tid) * ntiles1], e = off1[static_cast<int64_t>(tid + 1) * ntiles1];
+      const int nt = tiles_in(e - b);
+      atomicAdd(&s_sum[0], nt);
+      atomicAdd(&s_sum[1], (nt + kGroup - 1) / kGroup);
+      atomicAdd(&s_sum[2], final_buckets(e - b, kDirTarget));
+    }
+    __syncthreads();
+    const int nt = tiles_in(m), ng = (nt + kGroup - 1) / kGroup;
+    const int t0 = s_sum[0], g0 = s_sum[1], b0 = s_sum[2];
+    if (tid == 0) {
+      T.seg_start[seg] = begin;
+      T.seg_tile[seg] = t0;
+      T.seg_group[seg] = g0;
+      T.seg_bucket[seg] = b0;
+      if (seg == nseg - 1) {
+        T.seg_start[nseg] = begin + m;
+        T.seg_tile[nseg] = t0 + nt;
+        T.seg_group[nseg] = g0 + ng;
+        T.seg_bucket[nseg] = b0 + nb;
+      }
+    }
+    for (int q = tid; q < nt; q += 1024) T.tile_seg[t0 + q] = seg;
+    for (int q = tid; q < ng; q += 1024) T.group_seg[g0 + q] = seg;
+    for (int q = tid; q < nb; q += 1024) T.bucket_seg[b0 + q] = seg;
+  }
+  if (m == 0) return;  // uniform; one empty bucket, no splitter
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int t = e * 1024 + tid;
+    s_key[t] = src.key(begin + sample_pos<S>(t, m), f) >> f.kshift;
+  }
+  __syncthreads();
+  const uint64_t lo = LEVEL2 && seg > 0 ? skey1[seg] : 0;
+  const uint64_t hi = LEVEL2 && seg + 1 < nseg ? skey1[seg + 1] : static_cast<uint64_t>(nrows) << (f.cb - f.kshift);
+  sort_records<1024, E>(words, ord, S, lo, coarse_shift(lo, hi), [&](int t) { return s_key[t]; });
+  if (tid < kSegMax) {
+    uint64_t key = ~uint64_t{0};  // unused splitters lie beyond every key
+    int pos = INT32_MAX;
+    if (tid > 0 && tid < nb) {
+      const int t = ord[static_cast<int>((static_cast<int64_t>(tid) * S) / nb)];
+      key = s_key[t];
+      pos = begin + sample_pos<S>(t, m);
+    }
+    skey[seg * kSegMax + tid] = key;
+    spos[seg * kSegMax + tid] = pos;
+  }
+}
+
+// ---- partition ------------------------------------------------------------------------------
+// Splitters 1 .. 255 of a segment in LDS: whole, and as the first 31 bits of the segment's key
+// range, on which the bisection runs (half the LDS traffic, 32-bit compares). A record whose
+// bits equal a splitter's is placed by the whole keys. The bisection's tree is stored level by
+// level (children of node i: 2i and 2i + 1): the nodes of one level lie side by side, so that the
+// lanes of a wave, scattered over a level, meet few bank conflicts. Stored in key order, the
+// nodes of a level share a bank: 190 us for 60M records, two thirds of it conflicts.
+struct SplitterTable {
+  uint64_t key[kSegMax];
+  int32_t pos[kSegMax];
+  uint32_t coarse[kSegMax];
+  uint32_t tree[kSegMax];
+};
+__device__ __forceinline__ uint32_t coarse_key(uint64_t k, uint64_t base, int shift) {
+  const uint64_t r = k < base ? 0 : ((k - base) >> shift) + 1;  // monotone, whatever the range
+  return r > 0xFFFFFFFEu ? 0xFFFFFFFEu : static_cast<uint32_t>(r);
+}
+// Bucket of a record: the number of splitters at or before it.
+__device__ __forceinline__ int bucket_of(const SplitterTable& t, uint64_t k, int p, uint64_t base, int shift) {
+  const uint32_t c = coarse_key(k, base, shift);
+  int node = 1;
+#pragma unroll
+  for (int level = 0; level < kRadixBits; ++level) node = 2 * node + (t.tree[node] <= c ? 1 : 0);
+  int d = node - kSegMax;
+  if (__any(t.coarse[d] == c && d > 0)) {
+    d = 0;
+#pragma unroll
+    for (int step = kSegMax / 2; step > 0; step >>= 1) {
+      const uint64_t q = t.key[d + step];
+      bool le = q < k;
+      if (q == k) le = t.pos[d + step] <= p;
+      d += le ? step : 0;
+    }
+  }
+  return d;
+}
+
+// hist[base + d * nt + i] = records of tile i of the segment whose bucket is d, and each record's
+// bucket as one byte in dig. A workgroup takes up to `group` consecutive tiles of one segment
+// and stores each bucket's counts of them side by side (digit-major for the scan).
+template <class SRC, bool LEVEL2>
+__global__ __launch_bounds__(kBlock) void classify_kernel(const SRC src, const KeyForm f, int n, int group,
+                                                          int nseg, const Tables T,
+                                                          const uint64_t* __restrict__ skey,
+                                                          const int32_t* __restrict__ spos,
+                                                          uint8_t* __restrict__ dig, int32_t* __restrict__ hist) {
+  __shared__ SplitterTable t;
+  __shared__ int s_cnt[kGroup][kRadix];
+  const int tid = threadIdx.x, lane = lane_id();
+  int seg = 0, begin = 0, end = n, tile0, ntiles;
+  int64_t base = 0;
+  const int g = xcd_contiguous_block_id();
+  if (LEVEL2) {
+    if (g >= T.seg_group[nseg]) return;
+    seg = T.group_seg[g];
+    begin = T.seg_start[seg];
+    end = T.seg_start[seg + 1];
+    ntiles = T.seg_tile[seg + 1] - T.seg_tile[seg];
+    tile0 = (g - T.seg_group[seg]) * group;
+    base = static_cast<int64_t>(T.seg_tile[seg]) * kRadix;
+  } else {
+    ntiles = tiles_in(n);
+    tile0 = g * group;
+  }
+  t.key[tid] = skey[seg * kSegMax + tid];
+  t.pos[tid] = spos[seg * kSegMax + tid];
+  for (int q = tid; q < group * kRadix; q += kBlock) (&s_cnt[0][0])[q] = 0;
+  __syncthreads();
+  // range of the splitters: key[1] .. the last that is not unused
+  const uint64_t kbase = t.key[1];
+  uint64_t klast = kbase;
+#pragma unroll
+  for (int step = kSegMax / 2, d = 0; step > 0; step >>= 1)
+    if (t.key[d + step] != ~uint64_t{0}) d += step, klast = t.key[d];
+  const uint64_t range = klast - kbase;
+  const int shift = range >> 31 ? 33 - __clzll(static_cast<long long>(range)) : 0;
+  t.coarse[tid] = tid == 0 ? 0 : t.key[tid] == ~uint64_t{0} ? ~0u : coarse_key(t.key[tid], kbase, shift);
+  __syncthreads();
+  if (tid > 0) {  // node tid of the tree: which splitter
+    const int level = 31 - __clz(tid);
+    t.tree[tid] = t.coarse[((tid - (1 << level)) * 2 + 1) << (kRadixBits - 1 - level)];
+  }
+  __syncthreads();
+  const int nt = min(group, ntiles - tile0);
+  constexpr int kAhead = 8;  // keys in flight per thread, across tiles
+  uint64_t ahead[kAhead];
+#pragma unroll
+  for (int k = 0; k < kAhead; ++k)
+    ahead[k] = src.key_stream(min(begin + tile0 * kTile + k * kBlock + tid, end - 1), f) >> f.kshift;
+  for (int q = 0; q < nt; ++q) {
+    const int first = begin + (tile0 + q) * kTile;
+    int* cnt = s_cnt[q];
+#pragma unroll
+    for (int k = 0; k < (kTile / kBlock); ++k) {
+      const int p = first + k * kBlock + tid;
+      const uint64_t key = ahead[k % kAhead];
+      ahead[k % kAhead] = src.key_stream(min(p + kAhead * kBlock, end - 1), f) >> f.kshift;
+      const int d = bucket_of(t, key, p, kbase, shift);
+      if (p - lane + kWave <= end) {  // the whole wave
+        // ordered input: a wave's records share a bucket, and adds to one counter are serialised
+        if (__all(d == __builtin_amdgcn_readfirstlane(d))) {
+          if (lane == 0) atomicAdd(&cnt[d], kWave);
+        } else {
+          atomicAdd(&cnt[d], 1);
+        }
+        dig[p] = static_cast<uint8_t>(d);
+      } else if (p < end) {
+        atomicAdd(&cnt[d], 1);
+        dig[p] = static_cast<uint8_t>(d);
+      }
+    }
+  }
+  __syncthreads();
+  int32_t* out = hist + base + static_cast<int64_t>(tid) * ntiles + tile0;
+  for (int q = 0; q < nt; ++q) out[q] = s_cnt[q][tid];
+}
+
+// Stable scatter of one tile by the noted buckets; ranks as in the radix scatter: a ballot match
+// inside the wave plus per-wave counters, then the tile is put in bucket order in LDS so that
+// consecutive lanes store to consecutive addresses.
+template <typename VT, class SRC, bool LEVEL2>
+__global__ __launch_bounds__(kPart) void partition_kernel(const SRC src, const VT* __restrict__ val_in,
+                                                           const KeyForm f, int n, int nseg, const Tables T,
+                                                           const uint8_t* __restrict__ dig,
+                                                           const int32_t* __restrict__ off,
+                                                           uint64_t* __restrict__ key_out,
+                                                           VT* __restrict__ val_out) {
+  __shared__ int s_cnt[kPartWaves][kRadix];
+  __shared__ int s_gdelta[kRadix];
+  __shared__ int s_sum[4];
+  __shared__ uint64_t s_buf[kTile];
+  __shared__ uint8_t s_dig[kTile];
+  VT* s_val = reinterpret_cast<VT*>(s_buf);
+  const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
+  const int tile = xcd_contiguous_block_id();
+  int begin, end, ntiles, i0;
+  int64_t base = 0;
+  if (LEVEL2) {
+    if (tile >= T.seg_tile[nseg]) return;
+    const int seg = T.tile_seg[tile];
+    const int t0 = T.seg_tile[seg];
+    ntiles = T.seg_tile[seg + 1] - t0;
+    i0 = tile - t0;
+    begin = T.seg_start[seg] + i0 * kTile;
+    end = T.seg_start[seg + 1];
+    base = static_cast<int64_t>(t0) * kRadix;
+  } else {
+    ntiles = tiles_in(n);
+    i0 = tile;
+    begin = tile * kTile;
+    end = n;
+  }
+  for (int q = tid; q < kPartWaves * kRadix; q += kPart) (&s_cnt[0][0])[q] = 0;
+  __syncthreads();
+  const int tile_n = min(kTile, end - begin);
+  const int wave_base = begin + w * (kWave * kPartIPT);
+  volatile int* cnt = s_cnt[w];
+
+  uint64_t key[kPartIPT];
+  VT val[kPartIPT];
+  int lpos[kPartIPT];  // digit << 16 | rank inside (wave, digit), later the slot in the sorted tile
+#pragma unroll
+  for (int k = 0; k < kPartIPT; ++k) {
+    const int p = min(wave_base + k * kWave + lane, end - 1);
+    lpos[k] = dig[p];
+    key[k] = src.key_stream(p, f);
+    val[k] = __builtin_nontemporal_load(val_in + p);
+  }
+#pragma unroll
+  for (int k = 0; k < kPartIPT; ++k) {
+    const bool valid = wave_base + k * kWave + lane < end;
+    const int d = lpos[k];
+    uint64_t same = __ballot(valid);
+#pragma unroll
+    for (int b = 0; b < kRadixBits; ++b) {
+      const bool bit = (d >> b) & 1;
+      const uint64_t vote = __ballot(bit);
+      same &= bit ? vote : ~vote;
+    }
+    const int before = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(same >> 32),
+                                                 __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(same), 0));
+    int basecnt = 0;
+    if (valid) basecnt = cnt[d];
+    __builtin_amdgcn_wave_barrier();
+    if (valid && before == 0) cnt[d] = basecnt + __popcll(same);
+    __builtin_amdgcn_wave_barrier();
+    lpos[k] = (d << 16) | (basecnt + before);
+  }
+  __syncthreads();
+  {  // thread d: where digit d starts inside the sorted tile and in global memory
+    const int d = tid & (kRadix - 1);
+    int c[kPartWaves], tot = 0;
+#pragma unroll
+    for (int u = 0; u < kPartWaves; ++u) {
+      c[u] = s_cnt[u][d];
+      tot += c[u];
+    }
+    int start = wave_inclusive_sum(tot);
+    if (lane == kWave - 1) s_sum[w & 3] = start;
+    __syncthreads();
+    for (int u = 0; u < (w & 3); ++u) start += s_sum[u];
+    start -= tot;
+    if (tid < kRadix) {
+      s_gdelta[d] = off[base + static_cast<int64_t>(d) * ntiles + i0] - start;
+#pragma unroll
+      for (int u = 0; u < kPartWaves; ++u) {
+        s_cnt[u][d] = start;
+        start += c[u];
+      }
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kPartIPT; ++k) {
+    if (wave_base + k * kWave + lane < end) {
+      const int d = lpos[k] >> 16;
+      lpos[k] = (lpos[k] & 0xFFFF) + s_cnt[w][d];
+      s_buf[lpos[k]] = key[k];
+      s_dig[lpos[k]] = static_cast<uint8_t>(d);
+    }
+  }
+  __syncthreads();
+  int dst[kPartIPT];
+#pragma unroll
+  for (int k = 0; k < kPartIPT; ++k) {
+    const int j = k * kPart + tid;
+    if (j < tile_n) {
+      dst[k] = j + s_gdelta[s_dig[j]];
+      key_out[dst[k]] = s_buf[j];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kPartIPT; ++k)
+    if (wave_base + k * kWave + lane < end) s_val[lpos[k]] = val[k];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kPartIPT; ++k) {
+    const int j = k * kPart + tid;
+    if (j < tile_n) val_out[dst[k]] = s_val[j];
+  }
+}
+
+// ---- finish ---------------------------------------------------------------------------------
+// Columns and pos of the bucket's entries in order; the record's value is left to the caller.
+template <int NT, int E, class KA, class PUT>
+__device__ __forceinline__ void store_entries(const uint16_t* ord, int n, int first, int lo_row, int hi_row,
+                                              const KeyForm& f, const KA& key_at, int32_t* __restrict__ pos,
+                                              int32_t* __restrict__ crd_out, const PUT& put) {
+  const int tid = threadIdx.x;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int j = e * NT + tid;
+    const bool live = j < n;
+    if (!__any(live)) break;
+    int row = 0, prev = 0;
+    if (live) {
+      const int li = ord[j];
+      const uint64_t K = key_at(li);
+      row = static_cast<int>(K >> f.cb);
+      crd_out[first + j] = f.col_of(K);
+      put(j, li);
+    }
+    prev = __shfl_up(row, 1);
+    if (lane_id() == 0 && live) prev = j > 0 ? static_cast<int>(key_at(ord[j - 1]) >> f.cb) : lo_row;
+    store_pos_range(pos, live ? prev : 0, row, first + j);
+    const bool last = j == n - 1;
+    if (__any(last)) store_pos_range(pos, last ? row : 0, last ? hi_row : 0, first + n);
+  }
+}
+
+// A bucket with more records than fit: every record's rank is counted. `in` tells whether the
+// record at a position belongs to the bucket.
+template <int NT, typename VT, class SRC, class IN>
+__device__ void rank_and_store(const SRC& src, int begin, int end, const IN& in, int n, int first, int lo_row,
+                               int hi_row, const KeyForm& f, const VT* __restrict__ val_in,
+                               int32_t* __restrict__ pos, int32_t* __restrict__ crd_out,
+                               VT* __restrict__ val_out) {
+  for (int p0 = begin; p0 < end; p0 += NT) {
+    const int p = p0 + threadIdx.x;
+    bool live = p < end;
+    uint64_t K = 0, key = 0;
+    if (live) {
+      K = src.key(p, f);
+      key = K >> f.kshift;
+      live = in(key, p);
+    }
+    if (!__any(live)) continue;
+    int rank = 0, prev = lo_row;
+    for (int q = begin; q < end; ++q) {
+      const uint64_t k = src.key(q, f) >> f.kshift;
+      if (in(k, q) && (k < key || (k == key && q < p))) {
+        ++rank;
+        prev = max(prev, f.row_of(k));
+      }
+    }
+    const int row = static_cast<int>(K >> f.cb);
+    if (live) {
+      crd_out[first + rank] = static_cast<int>(K & ((uint64_t{1} << f.cb) - 1));
+      val_out[first + rank] = val_in[p];
+    }
+    store_pos_range(pos, live ? prev : 0, live ? row : 0, first + rank);
+    const bool last = live && rank == n - 1;
+    if (__any(last)) store_pos_range(pos, last ? row : 0, last ? hi_row : 0, first + n);
+  }
+}
+
+// One workgroup per bucket of the second partition.
+template <typename VT>
+__global__ __launch_bounds__(kFin) void finish_kernel(const KSource src, const VT* __restrict__ val_in,
+                                                      const KeyForm f, int nseg, int nrows, const Tables T,
+                                                      const int32_t* __restrict__ off2,
+                                                      const uint64_t* __restrict__ skey1,
+                                                      const uint64_t* __restrict__ skey2,
+                                                      int32_t* __restrict__ pos, int32_t* __restrict__ crd_out,
+                                                      VT* __restrict__ val_out) {
+  // up to kStaged records: keys, later values, then words and order; beyond: words and order
+  __shared__ __attribute__((aligned(16))) char s_mem[kStaged * 8 + kStaged * 4 + kStaged * 2];
+  static_assert(kCap * 4 + kCap * 2 <= sizeof(s_mem), "");
+  const int g = blockIdx.x;
+  if (g >= T.seg_bucket[nseg]) return;
+  const int seg = T.bucket_seg[g];
+  const int d = g - T.seg_bucket[seg], nb = T.seg_bucket[seg + 1] - T.seg_bucket[seg];
+  const int nt = T.seg_tile[seg + 1] - T.seg_tile[seg];
+  const int64_t base = static_cast<int64_t>(T.seg_tile[seg]) * kRadix;
+  int first = T.seg_start[seg], end = T.seg_start[seg + 1];
+  if (nt > 0) {
+    first = off2[base + static_cast<int64_t>(d) * nt];
+    if (d + 1 < nb) end = off2[base + static_cast<int64_t>(d + 1) * nt];
+  }
+  const int n = end - first;
+  // the bucket's keys lie in [lo, hi], its rows of pos are (row of lo, row of hi]
+  const uint64_t top = static_cast<uint64_t>(nrows) << (f.cb - f.kshift);
+  const uint64_t lo = d > 0 ? skey2[seg * kSegMax + d] : seg > 0 ? skey1[seg] : 0;
+  const uint64_t hi = d + 1 < nb ? skey2[seg * kSegMax + d + 1] : seg + 1 < nseg ? skey1[seg + 1] : top;
+  const int lo_row = d > 0 || seg > 0 ? f.row_of(lo) : -1, hi_row = f.row_of(hi);
+  if (n > kCap) {
+    rank_and_store<kFin, VT>(src, first, end, [](uint64_t, int) { return true; }, n, first, lo_row, hi_row, f, val_in,
+                             pos, crd_out, val_out);
+    return;
+  }
+  if (n == 0) {
+    if (threadIdx.x < kWave) store_pos_range(pos, threadIdx.x == 0 ? lo_row : 0, threadIdx.x == 0 ? hi_row : 0, first);
+    return;
+  }
+  const int shift = coarse_shift(lo, hi);
+  const int tid = threadIdx.x;
+  if (n <= kStaged) {
+    uint64_t* s_key = reinterpret_cast<uint64_t*>(s_mem);
+    VT* s_val = reinterpret_cast<VT*>(s_mem);
+    uint32_t* words = reinterpret_cast<uint32_t*>(s_mem + kStaged * 8);
+    uint16_t* ord = reinterpret_cast<uint16_t*>(s_mem + kStaged * 12);
+    constexpr int E = kStaged / kFin;
+    uint64_t k[E];
+    VT v[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int p = min(first + e * kFin + tid, end - 1);
+      k[e] = src.k[p];
+      v[e] = val_in[p];
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) s_key[e * kFin + tid] = k[e];
+    __syncthreads();
+    const auto key_at = [s_key](int li) { return s_key[li]; };
+    const auto cmp_at = [&](int li) { return s_key[li] >> f.kshift; };
+    if (n <= kStaged / 2) sort_records<kFin, E / 2>(words, ord, n, lo, shift, cmp_at);
+    else sort_records<kFin, E>(words, ord, n, lo, shift, cmp_at);
+    store_entries<kFin, E>(ord, n, first, lo_row, hi_row, f, key_at, pos, crd_out, [](int, int) {});
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < E; ++e) s_val[e * kFin + tid] = v[e];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int j = e * kFin + tid;
+      if (j < n) val_out[first + j] = s_val[ord[j]];
+    }
+  } else {
+    uint32_t* words = reinterpret_cast<uint32_t*>(s_mem);
+    uint16_t* ord = reinterpret_cast<uint16_t*>(s_mem + kCap * 4);
+    constexpr int E = kCap / kFin;
+    const uint64_t* k = src.k + first;
+    const auto key_at = [k](int li) { return k[li]; };
+    const auto cmp_at = [&](int li) { return k[li] >> f.kshift; };
+    sort_records<kFin, E>(words, ord, n, lo, shift, cmp_at);
+    store_entries<kFin, E>(ord, n, first, lo_row, hi_row, f, key_at, pos, crd_out,
+                           [&](int j, int li) { val_out[first + j] = val_in[first + li]; });
+  }
+}
+
+template <int E>
+__device__ __forceinline__ void sort_positions(uint32_t* at, int n) {
+  uint32_t v[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int i = e * kSel + static_cast<int>(threadIdx.x);
+    v[e] = i < n ? at[i] : ~0u;
+  }
+  __syncthreads();
+  block_sort_u32<kSel, E>(v, at);
+}
+
+// One workgroup per `target` records of a segment (the whole input, or a bucket of the first
+// partition). It samples the segment, keeps the two splitters around its share, and picks its
+// records out of the segment.
+template <int E, typename VT, class SRC, bool LEVEL2>
+__global__ __launch_bounds__(kSel) void select_finish_kernel(const SRC src, const VT* __restrict__ val_in,
+                                                             const KeyForm f, int n, int target, int nseg, int nrows,
+                                                             const int32_t* __restrict__ off1, int ntiles1,
+                                                             const uint64_t* __restrict__ skey1,
+                                                             int32_t* __restrict__ pos,
+                                                             int32_t* __restrict__ crd_out,
+                                                             VT* __restrict__ val_out) {
+  constexpr int S = kSel * E;
+  __shared__ uint64_t s_key[S];
+  __shared__ __attribute__((aligned(16))) uint32_t words[kCap];
+  __shared__ __attribute__((aligned(16))) int32_t s_at[kCap];  // positions of the bucket's records
+  __shared__ uint16_t s_ord[kCap];
+  __shared__ int s_cnt, s_less;
+  __shared__ int s_info[4];
+  __shared__ int s_wcnt[kSel / kWave];
+  const int tid = threadIdx.x, lane = lane_id();
+  const int w = __builtin_amdgcn_readfirstlane(wave_id());
+  // ---- which segment, which share of it
+  int seg = 0, begin = 0, end = n, d = blockIdx.x, nb = max(1, (n + target - 1) / target);
+  if (LEVEL2) {
+    if (tid == 0) s_info[0] = -1;
+    int b = 0, e = 0, cnt = 0;
+    if (tid < nseg) {
+      b = off1[static_cast<int64_t>(tid) * ntiles1];
+      e = tid + 1 < kRadix ? off1[static_cast<int64_t>(tid + 1) * ntiles1] : n;
+      cnt = final_buckets(e - b, target);
+    }
+    int incl = cnt;  // running sum over the segments (the first kSegMax threads)
+#pragma unroll
+    for (int q = 1; q < kWave; q <<= 1) {
+      const int u = __shfl_up(incl, q);
+      if (lane >= q) incl += u;
+    }
+    if (lane == kWave - 1) s_wcnt[w] = incl;
+    __syncthreads();
+    for (int u = 0; u < w; ++u) incl += s_wcnt[u];
+    const int g = blockIdx.x;
+    if (cnt > 0 && g < incl && g >= incl - cnt) {
+      s_info[0] = tid;
+      s_info[1] = b;
+      s_info[2] = e;
+      s_info[3] = g - (incl - cnt);
+    }
+    __syncthreads();
+    seg = s_info[0];
+    if (seg < 0) return;  // the grid is an upper bound
+    begin = s_info[1];
+    end = s_info[2];
+    d = s_info[3];
+    nb = final_buckets(end - begin, target);
+  }
+  const int m = end - begin;
+  // ---- splitters
+  Cut lo{0, -1}, hi{static_cast<uint64_t>(nrows) << (f.cb - f.kshift), INT32_MAX};
+  int lo_row = -1, hi_row = nrows;
+  if (seg > 0) {
+    lo.key = skey1[seg];
+    lo_row = f.row_of(lo.key);
+  }
+  if (seg + 1 < nseg) {
+    hi.key = skey1[seg + 1];
+    hi_row = f.row_of(hi.key);
+  }
+  if (nb > 1) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int t = e * kSel + tid;
+      s_key[t] = src.key(begin + sample_pos<S>(t, m), f) >> f.kshift;
+    }
+    __syncthreads();
+    sort_records<kSel, E>(words, s_ord, S, lo.key, coarse_shift(lo.key, hi.key), [&](int t) { return s_key[t]; });
+    if (d > 0) {
+      const int t = s_ord[static_cast<int>((static_cast<int64_t>(d) * S) / nb)];
+      lo = Cut{s_key[t], begin + sample_pos<S>(t, m)};
+      lo_row = f.row_of(lo.key);
+    }
+    if (d + 1 < nb) {
+      const int t = s_ord[static_cast<int>((static_cast<int64_t>(d + 1) * S) / nb)];
+      hi = Cut{s_key[t], begin + sample_pos<S>(t, m)};
+      hi_row = f.row_of(hi.key);
+    }
+    __syncthreads();
+  }
+  const bool cut_below = d > 0, cut_above = d + 1 < nb;
+  const auto in = [&](uint64_t key, int p) {
+    return (!cut_below || lo.at_or_before(key, p)) && (!cut_above || !hi.at_or_before(key, p));
+  };
+  // ---- pick: the positions of the bucket's records, in any order, and how many records precede it.
+  // What decides is the row, except for the rows that the splitters cut; few records qualify.
+  if (tid == 0) s_cnt = s_less = 0;
+  __syncthreads();
+  const int cut_lo = cut_below ? lo_row : -1, cut_hi = cut_above ? hi_row : INT32_MAX;
+  int less = 0;
+  constexpr int U = SRC::kUnroll;
+  for (int p0 = begin + tid; p0 < end; p0 += U * kSel) {
+    typename SRC::Coarse c[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) c[u] = src.coarse(min(p0 + u * kSel, end - 1));
+    uint32_t maybe = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int row = src.coarse_row(c[u], f);
+      const bool ok = p0 + u * kSel < end;
+      less += ok && row < cut_lo ? 1 : 0;
+      maybe |= ok && row >= cut_lo && row <= cut_hi ? 1u << u : 0u;
+    }
+    while (maybe) {
+      const int u = __ffs(static_cast<int>(maybe)) - 1;
+      maybe &= maybe - 1;
+      const int p = p0 + u * kSel;
+      const uint64_t key = src.key(p, f) >> f.kshift;
+      if (cut_below && !lo.at_or_before(key, p)) {
+        ++less;
+      } else if (!cut_above || !hi.at_or_before(key, p)) {
+        const int i = atomicAdd(&s_cnt, 1);
+        if (i < kCap) s_at[i] = p;
+      }
+    }
+  }
+#pragma unroll
+  for (int s = kWave / 2; s > 0; s >>= 1) less += __shfl_xor(less, s);
+  if (lane == 0) atomicAdd(&s_less, less);
+  __syncthreads();
+  const int cnt = s_cnt, first = begin + s_less;
+  if (cnt > kCap) {
+    rank_and_store<kSel, VT>(src, begin, end, in, cnt, first, lo_row, hi_row, f, val_in, pos, crd_out, val_out);
+    return;
+  }
+  if (cnt == 0) {
+    if (w == 0) store_pos_range(pos, lane == 0 ? lo_row : 0, lane == 0 ? hi_row : 0, first);
+    return;
+  }
+  const int shift = coarse_shift(lo.key, hi.key);
+  const auto key_at = [&](int li) { return src.key(s_at[li], f); };
+  const auto cmp_at = [&](int li) { return src.key(s_at[li], f) >> f.kshift; };
+  const auto put = [&](int j, int li) { val_out[first + j] = val_in[s_at[li]]; };
+  // the positions first: records are numbered in input order
+#define SPT_FINISH(E_)                                                                                     \
+  sort_positions<E_>(reinterpret_cast<uint32_t*>(s_at), cnt);                                              \
+  sort_records<kSel, E_>(words, s_ord, cnt, lo.key, shift, cmp_at);                                      \
+  store_entries<kSel, E_>(s_ord, cnt, first, lo_row, hi_row, f, key_at, pos, crd_out, put)
+  if (cnt <= kSel) {
+    SPT_FINISH(1);
+  } else if (cnt <= 2 * kSel) {
+    SPT_FINISH(2);
+  } else {
+    SPT_FINISH(4);
+  }
+#undef SPT_FINISH
+}
+
+// ---- host -----------------------------------------------------------------------------------
+
+bool sample_sort_applies(int64_t n) { return n > 0 && n <= kSampleSortMax; }
+
+static int64_t tiles_bound(int64_t n) { return (n + kTile - 1) / kTile + kSegMax; }
+
+size_t sample_sort_workspace(int dtype, int64_t n) {
+  const size_t vsz = dtype == SPT_F64 ? 8 : 4;
+  if (n <= kSelectMax) return 256;
+  const int levels = n > kTwoLevelMin ? 2 : 1;
+  const size_t hist = align_up(static_cast<size_t>(tiles_bound(n)) * kRadix * 4, 256);
+  size_t b = levels * (align_up(n * 8, 256) + align_up(n * vsz, 256)) + align_up(n, 256);
+  b += levels * hist + scan_workspace(tiles_bound(n) * kRadix);
+  b += 2 * (align_up(kSegMax * 8, 256) + align_up(kSegMax * 4, 256));
+  if (levels == 2) {
+    b += align_up(kSegMax * kSegMax * 8, 256) + align_up(kSegMax * kSegMax * 4, 256);
+    b += 4 * align_up((kSegMax + 1) * 4, 256) + 2 * align_up(tiles_bound(n) * 4, 256) +
+         align_up((n / kDirTarget + kSegMax + 1) * 4, 256);
+  }
+  return b + 256;
+}
+
+template <class SRC, bool LEVEL2>
+static spt_status launch_splitters(int samples, int nseg, const SRC src, const KeyForm f, int n, int nrows, int nb,
+                                   const int32_t* off1, int ntiles1, const Tables& T, const uint64_t* skey1, uint64_t* skey, int32_t* spos,
+                                   hipStream_t s) {
+#define SPT_SPLIT(E_)                                                                                         \
+  hipLaunchKernelGGL((splitters_kernel<E_, SRC, LEVEL2>), dim3(nseg), dim3(1024), 0, s, src, f, n, nrows, nb, \
+                     off1, ntiles1, nseg, T, skey1, skey, spos)
+  if (samples <= 1024) SPT_SPLIT(1);
+  else if (samples <= 2048) SPT_SPLIT(2);
+  else SPT_SPLIT(4);
+#undef SPT_SPLIT
+  SPT_CHECK_LAUNCH("splitters");
+  return SPT_OK;
+}
+
+template <typename VT>
+spt_status sample_sort_convert(int64_t n64, int64_t nrows, int64_t ncols, bool by_col, const int32_t* row,
+                               const int32_t* col, const VT* vals, int32_t* pos_out, int32_t* crd_out,
+                               VT* vals_out, void* ws, size_t ws_bytes, hipStream_t s) {
+  const int n = static_cast<int>(n64);
+  KeyForm f;
+  f.cb = bits_for(ncols);
+  f.kshift = by_col ? 0 : f.cb;
+  const RcSource rc{row, col};
+  if (n64 <= kSelectMax) {
+    const int nb = (n + kSelTarget1 - 1) / kSelTarget1;
+    // four or more samples per share: that a share holds ten times its target has a chance below 1e-11
+#define SPT_SELECT(E_)                                                                                              \
+  hipLaunchKernelGGL((select_finish_kernel<E_, VT, RcSource, false>), dim3(nb), dim3(kSel), 0, s, rc, vals, f, n,   \
+                     kSelTarget1, 1, static_cast<int>(nrows), nullptr, 0, nullptr, pos_out, crd_out, vals_out)
+    if (nb <= 256) SPT_SELECT(1);
+    else SPT_SELECT(2);
+#undef SPT_SELECT
+    SPT_CHECK_LAUNCH("select finish");
+    return SPT_OK;
+  }
+  const bool two = n64 > kTwoLevelMin;
+  if (!ws || ws_bytes < sample_sort_workspace(sizeof(VT) == 8 ? SPT_F64 : SPT_F32, n64))
+    return fail(SPT_ERR_WORKSPACE, "coo_to_csr: workspace of %zu bytes needed, %zu given",
+                sample_sort_workspace(sizeof(VT) == 8 ? SPT_F64 : SPT_F32, n64), ws_bytes);
+  Workspace W(ws, ws_bytes);
+  uint64_t* k1 = W.take<uint64_t>(n);
+  VT* v1 = W.take<VT>(n);
+  uint8_t* dig = W.take<uint8_t>(n);
+  int32_t* hist1 = W.take<int32_t>(tiles_bound(n) * kRadix);
+  int32_t* scan_tmp = reinterpret_cast<int32_t*>(W.take<char>(scan_workspace(tiles_bound(n) * kRadix)));
+  uint64_t* skey1 = W.take<uint64_t>(kSegMax);
+  int32_t* spos1 = W.take<int32_t>(kSegMax);
+  Tables T{};
+
+  // level 1
+  const int nt1 = (n + kTile - 1) / kTile;
+  const int nb1 = two ? kSegMax : static_cast<int>(std::min<int64_t>(kSegMax, (n64 + 16383) / 16384));
+  spt_status st = launch_splitters<RcSource, false>(16 * nb1, 1, rc, f, n, static_cast<int>(nrows), nb1, nullptr, 0, T,
+                                                    nullptr, skey1, spos1, s);
+  if (st != SPT_OK) return st;
+  const int group = nt1 >= 2048 ? kGroup : 1;
+  hipLaunchKernelGGL((classify_kernel<RcSource, false>), dim3((nt1 + group - 1) / group), dim3(kBlock), 0, s, rc, f,
+                     n, group, 1, T, skey1, spos1, dig, hist1);
+  SPT_CHECK_LAUNCH("classify");
+  st = device_scan_i32<false>(hist1, hist1, static_cast<int64_t>(nt1) * kRadix, scan_tmp, s);
+  if (st != SPT_OK) return st;
+  hipLaunchKernelGGL((partition_kernel<VT, RcSource, false>), dim3(nt1), dim3(kPart), 0, s, rc, vals, f, n, 1, T,
+                     dig, hist1, k1, v1);
+  SPT_CHECK_LAUNCH("partition");
+  const KSource s1{k1};
+  if (!two) {
+    const unsigned grid = static_cast<unsigned>(n64 / kSelTarget2 + nb1);
+    hipLaunchKernelGGL((select_finish_kernel<1, VT, KSource, true>), dim3(grid), dim3(kSel), 0, s, s1, v1, f, n,
+                       kSelTarget2, nb1, static_cast<int>(nrows), hist1, nt1, skey1, pos_out, crd_out, vals_out);
+    SPT_CHECK_LAUNCH("select finish");
+    return SPT_OK;
+  }
+
+  // level 2
+  uint64_t* k2 = W.take<uint64_t>(n);
+  VT* v2 = W.take<VT>(n);
+  int32_t* hist2 = W.take<int32_t>(tiles_bound(n) * kRadix);
+  uint64_t* skey2 = W.take<uint64_t>(kSegMax * kSegMax);
+  int32_t* spos2 = W.take<int32_t>(kSegMax * kSegMax);
+  T.seg_start = W.take<int32_t>(kSegMax + 1);
+  T.seg_tile = W.take<int32_t>(kSegMax + 1);
+  T.seg_group = W.take<int32_t>(kSegMax + 1);
+  T.seg_bucket = W.take<int32_t>(kSegMax + 1);
+  T.group_seg = W.take<int32_t>(tiles_bound(n));
+  T.tile_seg = W.take<int32_t>(tiles_bound(n));
+  T.bucket_seg = W.take<int32_t>(n / kDirTarget + kSegMax + 1);
+  st = launch_splitters<KSource, true>(32 * static_cast<int>(std::min<int64_t>(kSegMax, n64 / nb1 * 3 / 2 / kDirTarget + 1)),
+                                       nb1, s1, f, n, static_cast<int>(nrows), 0, hist1, nt1, T, skey1, skey2, spos2, s);
+  if (st != SPT_OK) return st;
+  const unsigned tiles2 = static_cast<unsigned>(tiles_bound(n));
+  hipLaunchKernelGGL((classify_kernel<KSource, true>), dim3(tiles2 / kGroup + kSegMax), dim3(kBlock), 0, s, s1, f,
+                     n, kGroup, nb1, T, skey2, spos2, dig, hist2);
+  SPT_CHECK_LAUNCH("classify 2");
+  st = device_scan_i32<false>(hist2, hist2, static_cast<int64_t>(tiles2) * kRadix, scan_tmp, s);
+  if (st != SPT_OK) return st;
+  hipLaunchKernelGGL((partition_kernel<VT, KSource, true>), dim3(tiles2), dim3(kPart), 0, s, s1, v1, f, n, nb1, T,
+                     dig, hist2, k2, v2);
+  SPT_CHECK_LAUNCH("partition 2");
+  hipLaunchKernelGGL(finish_kernel<VT>, dim3(static_cast<unsigned>(n64 / kDirTarget + nb1)), dim3(kFin), 0, s,
+                     KSource{k2}, v2, f, nb1, static_cast<int>(nrows), T, hist2, skey1, skey2, pos_out, crd_out,
+                     vals_out);
+  SPT_CHECK_LAUNCH("finish");
+  return SPT_OK;
+}
+
+template spt_status sample_sort_convert<uint64_t>(int64_t, int64_t, int64_t, bool, const int32_t*, const int32_t*,
+                                                  const uint64_t*, int32_t*, int32_t*, uint64_t*, void*, size_t,
+                                                  hipStream_t);
+template spt_status sample_sort_convert<uint32_t>(int64_t, int64_t, int64_t, bool, const int32_t*, const int32_t*,
+                                                  const uint32_t*, int32_t*, int32_t*, uint32_t*, void*, size_t,
+                                                  hipStream_t);
+
+}  // namespace spt

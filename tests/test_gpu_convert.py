@@ -151,3 +151,49 @@ def test_one_row_holds_most_entries_and_columns_use_31_bits(order):
     c = rng.integers(0, M, n)
     p = rng.permutation(n)
     _check(5000, M, r[p], c[p], rng.uniform(-1, 1, n), order, what="heavy row, 31-bit columns")
+
+
+# ---- the sample sort's own boundaries ----
+
+@pytest.mark.parametrize("nnz", [384, 385, 1025, 98_305, 131_072, 131_073, 4_194_304, 4_194_305])
+def test_sizes_at_which_the_sample_sort_changes_its_plan(nnz):
+    """One workgroup / several; one launch / one partition / two partitions."""
+    N, M = 50_000, 60_000
+    r, c, v = wl.random_coo_entries(N, M, nnz, seed=500 + nnz % 89, dtype=np.float32, sort=False)
+    _check(N, M, r, c, v, nnz % 2, what=f"nnz={nnz}")
+
+
+def _sampled(m, S):
+    t = np.arange(S, dtype=np.uint64)
+    jitter = ((t * np.uint64(2654435769)) & np.uint64(0xFFFFFFFF)) >> np.uint64(16)
+    return ((((t << np.uint64(16)) | jitter) * np.uint64(m) // np.uint64(S)) >> np.uint64(16)).astype(np.int64)
+
+
+@pytest.mark.parametrize("nnz, S", [(6000, 1024), (4_200_000, 4096)])
+def test_input_that_defeats_the_sampling(nnz, S):
+    """Small keys exactly at the sampled positions: all other records end in one bucket, far more
+    than a workgroup sorts in LDS, and are ranked by counting."""
+    N, M = 100_000, 4000
+    rng = np.random.default_rng(46)
+    r, c = rng.integers(1000, N, nnz), rng.integers(0, M, nnz)
+    at = _sampled(nnz, S)
+    r[at], c[at] = np.arange(S) % 7, np.arange(S) % M
+    _check(N, M, r, c, np.arange(nnz, dtype=np.float64), 0, what="sampling defeated")
+
+
+def test_more_records_than_the_sample_sort_takes():
+    import torch
+    import paper_1804_10112_amd as spt
+    N, M, nnz = 3_000_000, 5_000_000, (1 << 26) + 3
+    g = torch.Generator(device="cuda:0").manual_seed(1)
+    r = torch.randint(0, N, (nnz,), generator=g, device="cuda:0", dtype=torch.int32)
+    c = torch.randint(0, M, (nnz,), generator=g, device="cuda:0", dtype=torch.int32)
+    v = torch.arange(nnz, dtype=torch.int32, device="cuda:0").view(torch.float32)
+    A = spt.DeviceTensor(wl.coo_spec(N, M, [0], [0], np.zeros(1, np.float32), ordered=False))
+    A.c.level[0].crd, A.c.level[1].crd, A.c.vals, A.c.nvals = r.data_ptr(), c.data_ptr(), v.data_ptr(), nnz
+    pos = torch.empty(N + 1, dtype=torch.int32, device="cuda:0")
+    crd, vals = torch.empty_like(c), torch.empty_like(v)
+    spt.spt_coo_to_csr(A, spt.SPT_ORDER_ROW_COL, pos, crd, vals, A.workspace(spt.SPT_OP_COO_TO_CSR))
+    order = torch.sort(r.long() * M + c, stable=True).indices
+    assert torch.equal(crd, c[order]) and torch.equal(vals.view(torch.int32), order.int())
+    assert torch.equal(pos[1:].long(), torch.bincount(r, minlength=N).cumsum(0)) and int(pos[0]) == 0

@@ -8,8 +8,8 @@
 //   up to kSelectMax records          one launch: workgroup j sorts a sample of the keys, picks
 //                                     the records between its two splitters out of the whole
 //                                     input (which stays in L2) and sorts them;
-//   up to kTwoLevelMin                one stable partition into up to 256 buckets, then the same
-//                                     selection inside each bucket;
+//   up to kOneLevelMax                one stable partition into up to 256 buckets, one workgroup
+//                                     per bucket;
 //   beyond                            two stable partitions, then one workgroup per bucket.
 // A partition is count -> exclusive scan -> stable scatter, as a radix pass, with the digit found
 // by bisection among the splitters instead of taken from the key bits. The count kernel notes
@@ -51,11 +51,10 @@ constexpr int kPartIPT = kTile / kPart;
 constexpr int kGroup = 4;           // consecutive tiles that one workgroup classifies
 constexpr int kLiBits = 12;         // bits of a record's number inside its bucket; the rest of a word: its key, coarsely
 constexpr int kMaxSamples = 4096;   // numbered by kLiBits bits, too
-constexpr int kSelTarget1 = 384;    // records per workgroup: selected out of the whole (small) input,
-constexpr int kSelTarget2 = 1024;   // selected out of a bucket,
+constexpr int kSelTarget = 384;     // records per workgroup: selected out of the whole (small) input,
 constexpr int kDirTarget = 1408;    // of a bucket of its own
-constexpr int64_t kSelectMax = 128 * 1024;  // every workgroup reads all rows: 512 KB from L2
-constexpr int64_t kTwoLevelMin = 4 << 20;   // 256 buckets of 16K records, each read by 16 workgroups
+constexpr int64_t kSelectMax = 64 * 1024;                   // every workgroup reads all rows: 256 KB from L2
+constexpr int64_t kOneLevelMax = int64_t(256) * kDirTarget;  // 256 buckets that fit LDS
 constexpr int64_t kSampleSortMax = int64_t(1) << 26;  // 256 x 256 buckets of kDirTarget and the sample's spread
 constexpr int kSegMax = 256;        // buckets of a partition
 
@@ -90,24 +89,11 @@ struct RcSource {
     return (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_nontemporal_load(row + p))) << f.cb) |
            static_cast<uint32_t>(__builtin_nontemporal_load(col + p));
   }
-  // selection reads the row first and the column only where it decides
-  typedef int32_t Coarse;
-  static constexpr int kUnroll = 16;
-  __device__ __forceinline__ Coarse coarse(int p) const { return row[p]; }
-  __device__ __forceinline__ int coarse_row(Coarse c, const KeyForm&) const { return c; }
-  __device__ __forceinline__ uint64_t fine(Coarse c, int p, const KeyForm& f) const {
-    return (static_cast<uint64_t>(static_cast<uint32_t>(c)) << f.cb) | static_cast<uint32_t>(col[p]);
-  }
 };
 struct KSource {
   const uint64_t* __restrict__ k;
   __device__ __forceinline__ uint64_t key(int p, const KeyForm&) const { return k[p]; }
   __device__ __forceinline__ uint64_t key_stream(int p, const KeyForm&) const { return __builtin_nontemporal_load(k + p); }
-  typedef uint64_t Coarse;
-  static constexpr int kUnroll = 8;
-  __device__ __forceinline__ Coarse coarse(int p) const { return k[p]; }
-  __device__ __forceinline__ int coarse_row(Coarse c, const KeyForm& f) const { return static_cast<int>(c >> f.cb); }
-  __device__ __forceinline__ uint64_t fine(Coarse c, int, const KeyForm&) const { return c; }
 };
 
 // A cut of the order: everything from (key, pos) on.
@@ -123,7 +109,7 @@ struct Cut {
 struct Tables {
   int32_t* seg_start;  // [nseg + 1] first record of each bucket of level 1
   int32_t* seg_tile;   // [nseg + 1] tiles before the segment
-  int32_t* seg_group;  // [nseg + 1] groups of kGroup tiles before the segment
+  int32_t* seg_group;  // [nseg + 1] groups of tiles before the segment
   int32_t* seg_bucket; // [nseg + 1] final buckets before the segment
   int32_t* group_seg;  // segment of each group
   int32_t* tile_seg;   // segment of each tile
@@ -194,7 +180,7 @@ __device__ __forceinline__ int coarse_shift(uint64_t lo, uint64_t hi) {
 // LEVEL2: the segment is a bucket of level 1 (bounds from that level's scanned counts `off1`),
 // nb follows from its size, and the workgroup fills in its rows of the segment tables.
 template <int E, class SRC, bool LEVEL2>
-__global__ __launch_bounds__(1024) void splitters_kernel(const SRC src, const KeyForm f, int n, int nrows, int nb_fixed,
+__global__ __launch_bounds__(1024) void splitters_kernel(const SRC src, const KeyForm f, int n, int nrows, int nb_fixed, int group,
                                                          const int32_t* __restrict__ off1, int ntiles1, int nseg,
                                                          const Tables T, const uint64_t* __restrict__ skey1,
                                                          uint64_t* __restrict__ skey,
@@ -217,11 +203,11 @@ __global__ __launch_bounds__(1024) void splitters_kernel(const SRC src, const Ke
       const int b = off1[static_cast<int64_t>(tid) * ntiles1], e = off1[static_cast<int64_t>(tid + 1) * ntiles1];
       const int nt = tiles_in(e - b);
       atomicAdd(&s_sum[0], nt);
-      atomicAdd(&s_sum[1], (nt + kGroup - 1) / kGroup);
+      atomicAdd(&s_sum[1], (nt + group - 1) / group);
       atomicAdd(&s_sum[2], final_buckets(e - b, kDirTarget));
     }
     __syncthreads();
-    const int nt = tiles_in(m), ng = (nt + kGroup - 1) / kGroup;
+    const int nt = tiles_in(m), ng = (nt + group - 1) / group;
     const int t0 = s_sum[0], g0 = s_sum[1], b0 = s_sum[2];
     if (tid == 0) {
       T.seg_start[seg] = begin;
@@ -382,13 +368,16 @@ __global__ __launch_bounds__(kBlock) void classify_kernel(const SRC src, const K
 // Stable scatter of one tile by the noted buckets; ranks as in the radix scatter: a ballot match
 // inside the wave plus per-wave counters, then the tile is put in bucket order in LDS so that
 // consecutive lanes store to consecutive addresses.
-template <typename VT, class SRC, bool LEVEL2>
+// SELF (few tiles): `off` holds the plain counts, and every workgroup adds up those before its own
+// tile itself; the first leaves the start of every bucket in `starts` (one more than buckets).
+template <typename VT, class SRC, bool LEVEL2, bool SELF = false>
 __global__ __launch_bounds__(kPart) void partition_kernel(const SRC src, const VT* __restrict__ val_in,
                                                            const KeyForm f, int n, int nseg, const Tables T,
                                                            const uint8_t* __restrict__ dig,
                                                            const int32_t* __restrict__ off,
                                                            uint64_t* __restrict__ key_out,
-                                                           VT* __restrict__ val_out) {
+                                                           VT* __restrict__ val_out,
+                                                           int32_t* __restrict__ starts) {
   __shared__ int s_cnt[kPartWaves][kRadix];
   __shared__ int s_gdelta[kRadix];
   __shared__ int s_sum[4];
@@ -464,8 +453,28 @@ __global__ __launch_bounds__(kPart) void partition_kernel(const SRC src, const V
     __syncthreads();
     for (int u = 0; u < (w & 3); ++u) start += s_sum[u];
     start -= tot;
+    int global = 0;
+    if (SELF) {
+      int total = 0;  // of this digit over all tiles; `global`: over the tiles before this one
+#pragma unroll 8
+      for (int q = 0; q < ntiles; ++q) {
+        const int x = off[static_cast<int64_t>(d) * ntiles + q];
+        total += x;
+        global += q < i0 ? x : 0;
+      }
+      int incl = wave_inclusive_sum(total);
+      __syncthreads();
+      if (lane == kWave - 1) s_sum[w & 3] = incl;
+      __syncthreads();
+      for (int u = 0; u < (w & 3); ++u) incl += s_sum[u];
+      global += incl - total;
+      if (i0 == 0 && tid < kRadix) {
+        starts[d] = incl - total;
+        if (d == kRadix - 1) starts[kRadix] = incl;
+      }
+    }
     if (tid < kRadix) {
-      s_gdelta[d] = off[base + static_cast<int64_t>(d) * ntiles + i0] - start;
+      s_gdelta[d] = (SELF ? global : off[base + static_cast<int64_t>(d) * ntiles + i0]) - start;
 #pragma unroll
       for (int u = 0; u < kPartWaves; ++u) {
         s_cnt[u][d] = start;
@@ -569,8 +578,9 @@ __device__ void rank_and_store(const SRC& src, int begin, int end, const IN& in,
   }
 }
 
-// One workgroup per bucket of the second partition.
-template <typename VT>
+// One workgroup per bucket of the last partition. LEVELS == 1: of the only one, whose scanned
+// counts are off2 and whose splitters are skey2, with nseg buckets.
+template <typename VT, int LEVELS>
 __global__ __launch_bounds__(kFin) void finish_kernel(const KSource src, const VT* __restrict__ val_in,
                                                       const KeyForm f, int nseg, int nrows, const Tables T,
                                                       const int32_t* __restrict__ off2,
@@ -582,22 +592,32 @@ __global__ __launch_bounds__(kFin) void finish_kernel(const KSource src, const V
   __shared__ __attribute__((aligned(16))) char s_mem[kStaged * 8 + kStaged * 4 + kStaged * 2];
   static_assert(kCap * 4 + kCap * 2 <= sizeof(s_mem), "");
   const int g = blockIdx.x;
-  if (g >= T.seg_bucket[nseg]) return;
-  const int seg = T.bucket_seg[g];
-  const int d = g - T.seg_bucket[seg], nb = T.seg_bucket[seg + 1] - T.seg_bucket[seg];
-  const int nt = T.seg_tile[seg + 1] - T.seg_tile[seg];
-  const int64_t base = static_cast<int64_t>(T.seg_tile[seg]) * kRadix;
-  int first = T.seg_start[seg], end = T.seg_start[seg + 1];
-  if (nt > 0) {
-    first = off2[base + static_cast<int64_t>(d) * nt];
-    if (d + 1 < nb) end = off2[base + static_cast<int64_t>(d + 1) * nt];
-  }
-  const int n = end - first;
+  int first, end;
   // the bucket's keys lie in [lo, hi], its rows of pos are (row of lo, row of hi]
   const uint64_t top = static_cast<uint64_t>(nrows) << (f.cb - f.kshift);
-  const uint64_t lo = d > 0 ? skey2[seg * kSegMax + d] : seg > 0 ? skey1[seg] : 0;
-  const uint64_t hi = d + 1 < nb ? skey2[seg * kSegMax + d + 1] : seg + 1 < nseg ? skey1[seg + 1] : top;
-  const int lo_row = d > 0 || seg > 0 ? f.row_of(lo) : -1, hi_row = f.row_of(hi);
+  uint64_t lo, hi;
+  if (LEVELS == 1) {
+    first = off2[g];
+    end = off2[g + 1];
+    lo = g > 0 ? skey2[g] : 0;
+    hi = g + 1 < nseg ? skey2[g + 1] : top;
+  } else {
+    if (g >= T.seg_bucket[nseg]) return;
+    const int seg = T.bucket_seg[g];
+    const int d = g - T.seg_bucket[seg], nb = T.seg_bucket[seg + 1] - T.seg_bucket[seg];
+    const int nt = T.seg_tile[seg + 1] - T.seg_tile[seg];
+    const int64_t base = static_cast<int64_t>(T.seg_tile[seg]) * kRadix;
+    first = T.seg_start[seg];
+    end = T.seg_start[seg + 1];
+    if (nt > 0) {
+      first = off2[base + static_cast<int64_t>(d) * nt];
+      if (d + 1 < nb) end = off2[base + static_cast<int64_t>(d + 1) * nt];
+    }
+    lo = d > 0 ? skey2[seg * kSegMax + d] : seg > 0 ? skey1[seg] : 0;
+    hi = d + 1 < nb ? skey2[seg * kSegMax + d + 1] : seg + 1 < nseg ? skey1[seg + 1] : top;
+  }
+  const int n = end - first;
+  const int lo_row = g > 0 ? f.row_of(lo) : -1, hi_row = f.row_of(hi);
   if (n > kCap) {
     rank_and_store<kFin, VT>(src, first, end, [](uint64_t, int) { return true; }, n, first, lo_row, hi_row, f, val_in,
                              pos, crd_out, val_out);
@@ -665,14 +685,11 @@ __device__ __forceinline__ void sort_positions(uint32_t* at, int n) {
   block_sort_u32<kSel, E>(v, at);
 }
 
-// One workgroup per `target` records of a segment (the whole input, or a bucket of the first
-// partition). It samples the segment, keeps the two splitters around its share, and picks its
-// records out of the segment.
-template <int E, typename VT, class SRC, bool LEVEL2>
-__global__ __launch_bounds__(kSel) void select_finish_kernel(const SRC src, const VT* __restrict__ val_in,
-                                                             const KeyForm f, int n, int target, int nseg, int nrows,
-                                                             const int32_t* __restrict__ off1, int ntiles1,
-                                                             const uint64_t* __restrict__ skey1,
+// Small inputs: one workgroup per kSelTarget records. It samples the input, keeps the two
+// splitters around its share, and picks its records out of the input.
+template <int E, typename VT>
+__global__ __launch_bounds__(kSel) void select_finish_kernel(const RcSource src, const VT* __restrict__ val_in,
+                                                             const KeyForm f, int n, int nrows,
                                                              int32_t* __restrict__ pos,
                                                              int32_t* __restrict__ crd_out,
                                                              VT* __restrict__ val_out) {
@@ -682,72 +699,28 @@ __global__ __launch_bounds__(kSel) void select_finish_kernel(const SRC src, cons
   __shared__ __attribute__((aligned(16))) int32_t s_at[kCap];  // positions of the bucket's records
   __shared__ uint16_t s_ord[kCap];
   __shared__ int s_cnt, s_less;
-  __shared__ int s_info[4];
-  __shared__ int s_wcnt[kSel / kWave];
   const int tid = threadIdx.x, lane = lane_id();
   const int w = __builtin_amdgcn_readfirstlane(wave_id());
-  // ---- which segment, which share of it
-  int seg = 0, begin = 0, end = n, d = blockIdx.x, nb = max(1, (n + target - 1) / target);
-  if (LEVEL2) {
-    if (tid == 0) s_info[0] = -1;
-    int b = 0, e = 0, cnt = 0;
-    if (tid < nseg) {
-      b = off1[static_cast<int64_t>(tid) * ntiles1];
-      e = tid + 1 < kRadix ? off1[static_cast<int64_t>(tid + 1) * ntiles1] : n;
-      cnt = final_buckets(e - b, target);
-    }
-    int incl = cnt;  // running sum over the segments (the first kSegMax threads)
-#pragma unroll
-    for (int q = 1; q < kWave; q <<= 1) {
-      const int u = __shfl_up(incl, q);
-      if (lane >= q) incl += u;
-    }
-    if (lane == kWave - 1) s_wcnt[w] = incl;
-    __syncthreads();
-    for (int u = 0; u < w; ++u) incl += s_wcnt[u];
-    const int g = blockIdx.x;
-    if (cnt > 0 && g < incl && g >= incl - cnt) {
-      s_info[0] = tid;
-      s_info[1] = b;
-      s_info[2] = e;
-      s_info[3] = g - (incl - cnt);
-    }
-    __syncthreads();
-    seg = s_info[0];
-    if (seg < 0) return;  // the grid is an upper bound
-    begin = s_info[1];
-    end = s_info[2];
-    d = s_info[3];
-    nb = final_buckets(end - begin, target);
-  }
-  const int m = end - begin;
+  const int d = blockIdx.x, nb = gridDim.x;
   // ---- splitters
   Cut lo{0, -1}, hi{static_cast<uint64_t>(nrows) << (f.cb - f.kshift), INT32_MAX};
   int lo_row = -1, hi_row = nrows;
-  if (seg > 0) {
-    lo.key = skey1[seg];
-    lo_row = f.row_of(lo.key);
-  }
-  if (seg + 1 < nseg) {
-    hi.key = skey1[seg + 1];
-    hi_row = f.row_of(hi.key);
-  }
   if (nb > 1) {
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const int t = e * kSel + tid;
-      s_key[t] = src.key(begin + sample_pos<S>(t, m), f) >> f.kshift;
+      s_key[t] = src.key(sample_pos<S>(t, n), f) >> f.kshift;
     }
     __syncthreads();
     sort_records<kSel, E>(words, s_ord, S, lo.key, coarse_shift(lo.key, hi.key), [&](int t) { return s_key[t]; });
     if (d > 0) {
       const int t = s_ord[static_cast<int>((static_cast<int64_t>(d) * S) / nb)];
-      lo = Cut{s_key[t], begin + sample_pos<S>(t, m)};
+      lo = Cut{s_key[t], sample_pos<S>(t, n)};
       lo_row = f.row_of(lo.key);
     }
     if (d + 1 < nb) {
       const int t = s_ord[static_cast<int>((static_cast<int64_t>(d + 1) * S) / nb)];
-      hi = Cut{s_key[t], begin + sample_pos<S>(t, m)};
+      hi = Cut{s_key[t], sample_pos<S>(t, n)};
       hi_row = f.row_of(hi.key);
     }
     __syncthreads();
@@ -762,18 +735,17 @@ __global__ __launch_bounds__(kSel) void select_finish_kernel(const SRC src, cons
   __syncthreads();
   const int cut_lo = cut_below ? lo_row : -1, cut_hi = cut_above ? hi_row : INT32_MAX;
   int less = 0;
-  constexpr int U = SRC::kUnroll;
-  for (int p0 = begin + tid; p0 < end; p0 += U * kSel) {
-    typename SRC::Coarse c[U];
+  constexpr int U = 16;
+  for (int p0 = tid; p0 < n; p0 += U * kSel) {
+    int32_t row[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) c[u] = src.coarse(min(p0 + u * kSel, end - 1));
+    for (int u = 0; u < U; ++u) row[u] = src.row[min(p0 + u * kSel, n - 1)];
     uint32_t maybe = 0;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int row = src.coarse_row(c[u], f);
-      const bool ok = p0 + u * kSel < end;
-      less += ok && row < cut_lo ? 1 : 0;
-      maybe |= ok && row >= cut_lo && row <= cut_hi ? 1u << u : 0u;
+      const bool ok = p0 + u * kSel < n;
+      less += ok && row[u] < cut_lo ? 1 : 0;
+      maybe |= ok && row[u] >= cut_lo && row[u] <= cut_hi ? 1u << u : 0u;
     }
     while (maybe) {
       const int u = __ffs(static_cast<int>(maybe)) - 1;
@@ -792,9 +764,9 @@ __global__ __launch_bounds__(kSel) void select_finish_kernel(const SRC src, cons
   for (int s = kWave / 2; s > 0; s >>= 1) less += __shfl_xor(less, s);
   if (lane == 0) atomicAdd(&s_less, less);
   __syncthreads();
-  const int cnt = s_cnt, first = begin + s_less;
+  const int cnt = s_cnt, first = s_less;
   if (cnt > kCap) {
-    rank_and_store<kSel, VT>(src, begin, end, in, cnt, first, lo_row, hi_row, f, val_in, pos, crd_out, val_out);
+    rank_and_store<kSel, VT>(src, 0, n, in, cnt, first, lo_row, hi_row, f, val_in, pos, crd_out, val_out);
     return;
   }
   if (cnt == 0) {
@@ -829,26 +801,26 @@ static int64_t tiles_bound(int64_t n) { return (n + kTile - 1) / kTile + kSegMax
 size_t sample_sort_workspace(int dtype, int64_t n) {
   const size_t vsz = dtype == SPT_F64 ? 8 : 4;
   if (n <= kSelectMax) return 256;
-  const int levels = n > kTwoLevelMin ? 2 : 1;
+  const int levels = n > kOneLevelMax ? 2 : 1;
   const size_t hist = align_up(static_cast<size_t>(tiles_bound(n)) * kRadix * 4, 256);
   size_t b = levels * (align_up(n * 8, 256) + align_up(n * vsz, 256)) + align_up(n, 256);
   b += levels * hist + scan_workspace(tiles_bound(n) * kRadix);
-  b += 2 * (align_up(kSegMax * 8, 256) + align_up(kSegMax * 4, 256));
+  b += align_up(kSegMax * 8, 256) + align_up(kSegMax * 4, 256);
+  b += 5 * align_up((kSegMax + 1) * 4, 256);
   if (levels == 2) {
     b += align_up(kSegMax * kSegMax * 8, 256) + align_up(kSegMax * kSegMax * 4, 256);
-    b += 4 * align_up((kSegMax + 1) * 4, 256) + 2 * align_up(tiles_bound(n) * 4, 256) +
-         align_up((n / kDirTarget + kSegMax + 1) * 4, 256);
+    b += 2 * align_up(tiles_bound(n) * 4, 256) + align_up((n / kDirTarget + kSegMax + 1) * 4, 256);
   }
   return b + 256;
 }
 
 template <class SRC, bool LEVEL2>
-static spt_status launch_splitters(int samples, int nseg, const SRC src, const KeyForm f, int n, int nrows, int nb,
+static spt_status launch_splitters(int samples, int nseg, const SRC src, const KeyForm f, int n, int nrows, int nb, int group,
                                    const int32_t* off1, int ntiles1, const Tables& T, const uint64_t* skey1, uint64_t* skey, int32_t* spos,
                                    hipStream_t s) {
 #define SPT_SPLIT(E_)                                                                                         \
   hipLaunchKernelGGL((splitters_kernel<E_, SRC, LEVEL2>), dim3(nseg), dim3(1024), 0, s, src, f, n, nrows, nb, \
-                     off1, ntiles1, nseg, T, skey1, skey, spos)
+                     group, off1, ntiles1, nseg, T, skey1, skey, spos)
   if (samples <= 1024) SPT_SPLIT(1);
   else if (samples <= 2048) SPT_SPLIT(2);
   else SPT_SPLIT(4);
@@ -867,18 +839,14 @@ spt_status sample_sort_convert(int64_t n64, int64_t nrows, int64_t ncols, bool b
   f.kshift = by_col ? 0 : f.cb;
   const RcSource rc{row, col};
   if (n64 <= kSelectMax) {
-    const int nb = (n + kSelTarget1 - 1) / kSelTarget1;
-    // four or more samples per share: that a share holds ten times its target has a chance below 1e-11
-#define SPT_SELECT(E_)                                                                                              \
-  hipLaunchKernelGGL((select_finish_kernel<E_, VT, RcSource, false>), dim3(nb), dim3(kSel), 0, s, rc, vals, f, n,   \
-                     kSelTarget1, 1, static_cast<int>(nrows), nullptr, 0, nullptr, pos_out, crd_out, vals_out)
-    if (nb <= 256) SPT_SELECT(1);
-    else SPT_SELECT(2);
-#undef SPT_SELECT
+    const int nb = (n + kSelTarget - 1) / kSelTarget;
+    // six or more samples per share: that a share holds ten times its target has a chance below 1e-17
+    hipLaunchKernelGGL((select_finish_kernel<1, VT>), dim3(nb), dim3(kSel), 0, s, rc, vals, f, n,
+                       static_cast<int>(nrows), pos_out, crd_out, vals_out);
     SPT_CHECK_LAUNCH("select finish");
     return SPT_OK;
   }
-  const bool two = n64 > kTwoLevelMin;
+  const bool two = n64 > kOneLevelMax;
   if (!ws || ws_bytes < sample_sort_workspace(sizeof(VT) == 8 ? SPT_F64 : SPT_F32, n64))
     return fail(SPT_ERR_WORKSPACE, "coo_to_csr: workspace of %zu bytes needed, %zu given",
                 sample_sort_workspace(sizeof(VT) == 8 ? SPT_F64 : SPT_F32, n64), ws_bytes);
@@ -894,27 +862,32 @@ spt_status sample_sort_convert(int64_t n64, int64_t nrows, int64_t ncols, bool b
 
   // level 1
   const int nt1 = (n + kTile - 1) / kTile;
-  const int nb1 = two ? kSegMax : static_cast<int>(std::min<int64_t>(kSegMax, (n64 + 16383) / 16384));
-  spt_status st = launch_splitters<RcSource, false>(16 * nb1, 1, rc, f, n, static_cast<int>(nrows), nb1, nullptr, 0, T,
-                                                    nullptr, skey1, spos1, s);
+  // one level: final buckets; two: up to 256 buckets of sixteen final ones or more
+  const int per = two ? 16 * kDirTarget : kDirTarget;
+  const int nb1 = std::min(kSegMax, (n + per - 1) / per);
+  spt_status st = launch_splitters<RcSource, false>((two ? 16 : 24) * nb1, 1, rc, f, n, static_cast<int>(nrows), nb1,
+                                                    1, nullptr, 0, T, nullptr, skey1, spos1, s);
   if (st != SPT_OK) return st;
-  const int group = nt1 >= 2048 ? kGroup : 1;
+  const int group = nt1 >= 2048 ? kGroup : 1;  // few tiles: a workgroup for each
   hipLaunchKernelGGL((classify_kernel<RcSource, false>), dim3((nt1 + group - 1) / group), dim3(kBlock), 0, s, rc, f,
                      n, group, 1, T, skey1, spos1, dig, hist1);
   SPT_CHECK_LAUNCH("classify");
+  const KSource s1{k1};
+  if (!two) {
+    int32_t* starts = W.take<int32_t>(kSegMax + 1);
+    hipLaunchKernelGGL((partition_kernel<VT, RcSource, false, true>), dim3(nt1), dim3(kPart), 0, s, rc, vals, f, n, 1, T,
+                       dig, hist1, k1, v1, starts);
+    SPT_CHECK_LAUNCH("partition");
+    hipLaunchKernelGGL((finish_kernel<VT, 1>), dim3(nb1), dim3(kFin), 0, s, s1, v1, f, nb1, static_cast<int>(nrows), T,
+                       starts, nullptr, skey1, pos_out, crd_out, vals_out);
+    SPT_CHECK_LAUNCH("finish");
+    return SPT_OK;
+  }
   st = device_scan_i32<false>(hist1, hist1, static_cast<int64_t>(nt1) * kRadix, scan_tmp, s);
   if (st != SPT_OK) return st;
   hipLaunchKernelGGL((partition_kernel<VT, RcSource, false>), dim3(nt1), dim3(kPart), 0, s, rc, vals, f, n, 1, T,
-                     dig, hist1, k1, v1);
+                     dig, hist1, k1, v1, nullptr);
   SPT_CHECK_LAUNCH("partition");
-  const KSource s1{k1};
-  if (!two) {
-    const unsigned grid = static_cast<unsigned>(n64 / kSelTarget2 + nb1);
-    hipLaunchKernelGGL((select_finish_kernel<1, VT, KSource, true>), dim3(grid), dim3(kSel), 0, s, s1, v1, f, n,
-                       kSelTarget2, nb1, static_cast<int>(nrows), hist1, nt1, skey1, pos_out, crd_out, vals_out);
-    SPT_CHECK_LAUNCH("select finish");
-    return SPT_OK;
-  }
 
   // level 2
   uint64_t* k2 = W.take<uint64_t>(n);
@@ -930,18 +903,18 @@ spt_status sample_sort_convert(int64_t n64, int64_t nrows, int64_t ncols, bool b
   T.tile_seg = W.take<int32_t>(tiles_bound(n));
   T.bucket_seg = W.take<int32_t>(n / kDirTarget + kSegMax + 1);
   st = launch_splitters<KSource, true>(32 * static_cast<int>(std::min<int64_t>(kSegMax, n64 / nb1 * 3 / 2 / kDirTarget + 1)),
-                                       nb1, s1, f, n, static_cast<int>(nrows), 0, hist1, nt1, T, skey1, skey2, spos2, s);
+                                       nb1, s1, f, n, static_cast<int>(nrows), 0, group, hist1, nt1, T, skey1, skey2, spos2, s);
   if (st != SPT_OK) return st;
   const unsigned tiles2 = static_cast<unsigned>(tiles_bound(n));
-  hipLaunchKernelGGL((classify_kernel<KSource, true>), dim3(tiles2 / kGroup + kSegMax), dim3(kBlock), 0, s, s1, f,
-                     n, kGroup, nb1, T, skey2, spos2, dig, hist2);
+  hipLaunchKernelGGL((classify_kernel<KSource, true>), dim3(tiles2 / group + kSegMax), dim3(kBlock), 0, s, s1, f,
+                     n, group, nb1, T, skey2, spos2, dig, hist2);
   SPT_CHECK_LAUNCH("classify 2");
   st = device_scan_i32<false>(hist2, hist2, static_cast<int64_t>(tiles2) * kRadix, scan_tmp, s);
   if (st != SPT_OK) return st;
   hipLaunchKernelGGL((partition_kernel<VT, KSource, true>), dim3(tiles2), dim3(kPart), 0, s, s1, v1, f, n, nb1, T,
-                     dig, hist2, k2, v2);
+                     dig, hist2, k2, v2, nullptr);
   SPT_CHECK_LAUNCH("partition 2");
-  hipLaunchKernelGGL(finish_kernel<VT>, dim3(static_cast<unsigned>(n64 / kDirTarget + nb1)), dim3(kFin), 0, s,
+  hipLaunchKernelGGL((finish_kernel<VT, 2>), dim3(static_cast<unsigned>(n64 / kDirTarget + nb1)), dim3(kFin), 0, s,
                      KSource{k2}, v2, f, nb1, static_cast<int>(nrows), T, hist2, skey1, skey2, pos_out, crd_out,
                      vals_out);
   SPT_CHECK_LAUNCH("finish");

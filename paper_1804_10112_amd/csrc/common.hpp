@@ -68,11 +68,12 @@ __device__ __forceinline__ void lds_barrier() {
 // on one contiguous range of logical blocks, so neighbouring blocks (which
 // re-read each other's part of x) share an L2.
 constexpr int kXcds = 8;
-__device__ __forceinline__ int xcd_contiguous_block_id() {
-  const int nb = gridDim.x, q = nb / kXcds, rem = nb % kXcds;
-  const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
+__device__ __forceinline__ int xcd_contiguous_block_id(int block, int nb) {
+  const int q = nb / kXcds, rem = nb % kXcds;
+  const int xcd = block % kXcds, slot = block / kXcds;
   return xcd * q + (xcd < rem ? xcd : rem) + slot;
 }
+__device__ __forceinline__ int xcd_contiguous_block_id() { return xcd_contiguous_block_id(blockIdx.x, gridDim.x); }
 
 // First index in sorted a[0..n) whose value is >= target, found by the whole
 // wave: every step probes 64 evenly spaced entries, so a 4M-entry array needs

@@ -2,8 +2,8 @@
 //
 // All four kernels are bound by HBM bandwidth: the matrix arrays are streamed
 // once with coalesced (non-temporal) loads, x is gathered through the caches.
-//  * CSR and sorted COO share one kernel: a workgroup owns a fixed chunk of
-//    stored entries (balanced in entries, not rows, so power-law rows cost
+//  * CSR: a group of lanes per row. Strongly skewed CSR and sorted COO share one kernel: a
+//    workgroup owns a fixed chunk of stored entries (balanced in entries, not rows, so power-law rows cost
 //    nothing extra), stages the products in LDS and reduces them per row with a
 //    segmented scan; a row cut by a chunk boundary is finished by a tiny carry
 //    kernel. No atomics, results are bit-reproducible.
@@ -11,7 +11,6 @@
 //  * DIA and ELL read the diagonal-major / slot-major arrays with consecutive
 //    rows in consecutive lanes.
 #include <algorithm>
-#include <cstdlib>
 
 #include "common.hpp"
 #include "segreduce.hpp"
@@ -379,210 +378,263 @@ __global__ __launch_bounds__(kBlock) void seg_spmv_kernel(
   }
 }
 
-// ---------------------------------------------------------------- CSR, short rows, streamed
-// A workgroup owns 256 consecutive rows. Their entries are one contiguous range of crd /
-// vals, which the lanes read side by side with 16-byte loads (no lane waits on pos to find
-// its entries), multiply by x and park in LDS in pieces of kStreamCap products; then one
-// lane per row adds, in order, the part of its row that lies in the piece (eight LDS reads
-// per round trip). A row part longer than kStreamCoop products is added up by the whole wave
-// instead (strided partial sums, then a butterfly), so one long row costs its length / 64,
-// not its length. Any row length is handled; the kernel is chosen for short mean rows because
-// there a piece holds many whole rows and nothing has to be searched. Fixed order of
-// additions: bit-reproducible.
-// Measured and left out (banded matrix, 6 entries per row, fp64, 41 us): 2 or 4 rows per lane
-// (43 / 46 us: fewer, longer workgroups leave the last round of workgroups half empty);
-// workgroups that stay resident and walk through their blocks with the next piece's loads
-// issued before the current piece is reduced (43-45 us with 1024 or 2048 products per piece,
-// at 5, 6 or 8 waves per SIMD). The kernel runs at the rate at which the memory system serves
-// this mix of three streams and a gather of 64-byte pieces of x, not at a latency limit.
-constexpr int kStreamRows = kBlock;  // rows per workgroup, one per lane
-constexpr int kStreamCap = 2048;     // products parked per piece
-constexpr int kStreamCoop = 48;      // longer row parts are summed by the whole wave
-constexpr int kStreamLong = 3 * kStreamCap;  // rows from this length on take the register path
+// ---------------------------------------------------------------- CSR
+// G lanes per row, each with 16 bytes of values and the columns that go with them: the lanes of a
+// wave, row after row, read one stretch of the arrays, and nothing is staged, searched or waited
+// for at a barrier: bounds, entries, x, y are the only memory round trips of a row. K entries per
+// lane (2 fp64, 4 fp32) halve or quarter the load instructions against one entry per lane, which
+// is what large short-rowed matrices are bound by (7 entries per row, 12.8M entries: fp64 46 ->
+// 28 us, fp32 43 -> 18 us). Rows beyond 4 K G entries are added up by the whole wave, beyond
+// kRowsWide by the whole workgroup, so that a long row costs its length divided by what those
+// have in flight. Fixed order of additions: bit-reproducible.
+// Against a kernel that streamed 256 rows at a time through LDS and let a lane add up each, in us,
+// three matrices in turn:
+//   entries                800 000      1.6M      6.4M      12.8M      25.6M
+//   7 per row, fp64      8.0 / 5.7  8.6 / 6.8  20 / 18    39 / 35    74 / 67
+//   uniform, mean 10, "   10 / 7.8   16 / 12   55 / 53  158 / 155  393 / 388
+//   power law, mean 15, " 25 / 11    31 / 18   77 / 71  194 / 165  429 / 416
+//   8 to 32, fp32        9.6 / 5.8   14 / 10   39 / 32    68 / 75  170 / 178
+constexpr int kRowsWide = 4096;
+constexpr int kShortRow = 32;    // a declared bound up to here means rows of much the same length
 
-template <typename T>
-__device__ __forceinline__ T wave_sum(T v) {
+// Sum over the G lanes of a group, in every lane of it.
+template <int G, typename T>
+__device__ __forceinline__ T group_sum(T v) {
+  if (G >= 16) v += dpp_move<0x128, 0xf>(T(0), v);                  // row_ror:8
+  if (G >= 16) v += dpp_move<0x124, 0xf>(T(0), v);                  // row_ror:4
+  if (G == 8) v += dpp_move<0x141, 0xf>(T(0), v);                   // row_half_mirror
+  if (G >= 4) v += dpp_move<0x4E, 0xf>(T(0), v);                    // quad_perm 2,3,0,1
+  if (G >= 2) v += dpp_move<0xB1, 0xf>(T(0), v);                    // quad_perm 1,0,3,2
 #pragma unroll
-  for (int d = kWave / 2; d > 0; d >>= 1) v += __shfl_xor(v, d);
+  for (int d = 16; d < G; d <<= 1) v += __shfl_xor(v, d);
   return v;
 }
 
-template <typename T, bool VEC, class XP>
-__global__ __launch_bounds__(kBlock) void csr_stream_kernel(int nrows, int nnz,
-                                                            const int32_t* __restrict__ pos,
-                                                            const int32_t* __restrict__ crd,
-                                                            const T* __restrict__ vals, const XP x,
-                                                            T* __restrict__ y,
-                                                            const int32_t* __restrict__ select, int want) {
-  typedef int32_t i4 __attribute__((ext_vector_type(4)));
-  using V = typename VecOf<T>::type;  // 16 bytes of values
-  constexpr int R = VecOf<T>::R;
-  if (!selected(select, want)) return;  // the other CSR kernel was chosen on the device
-  __shared__ int32_t s_pos[kStreamRows + 1];
-  __shared__ T s_prod[kStreamCap];
-  __shared__ T s_wpart[kBlock / kWave];
-  __shared__ int s_lend;
-  const int tid = threadIdx.x;
-  const int row0 = xcd_contiguous_block_id() * kStreamRows;
-  for (int q = tid; q <= kStreamRows; q += kBlock) s_pos[q] = pos[min(row0 + q, nrows)];
-  __syncthreads();
-  const int e0 = s_pos[0], e1 = s_pos[kStreamRows];
-  const int e0a = e0 & ~3;  // pieces start on a multiple of 4 entries: aligned 16-byte loads
-  const int ra = s_pos[tid], rb = s_pos[tid + 1];
-  T acc = T(0);
-  // can this block hold a row of kStreamLong entries or more? (uniform; rare)
-  const bool has_long = e1 - e0 >= kStreamLong;
-  if (has_long) {
-    if (tid == 0) s_lend = 0;
-    __syncthreads();
+// 16 bytes of values and the columns that go with them, at any entry: vector loads that are only
+// element-aligned.
+template <typename T> struct Entries;
+template <> struct Entries<double> {
+  static constexpr int K = 2;
+  typedef double V __attribute__((ext_vector_type(2), aligned(8)));
+  typedef int32_t I __attribute__((ext_vector_type(2), aligned(4)));
+};
+template <> struct Entries<float> {
+  static constexpr int K = 4;
+  typedef float V __attribute__((ext_vector_type(4), aligned(4)));
+  typedef int32_t I __attribute__((ext_vector_type(4), aligned(4)));
+};
+
+// Block `block` of `nblocks`: NG * R consecutive rows.
+template <typename T, int G, int R, bool NT, class XP>
+__device__ __forceinline__ void csr_rows_block(int block, int nblocks, int nrows, int nnz,
+                                               const int32_t* __restrict__ pos, const int32_t* __restrict__ crd,
+                                               const T* __restrict__ vals, const XP& x, T* __restrict__ y) {
+  constexpr int NG = kBlock / G;
+  constexpr int K = Entries<T>::K;
+  constexpr int KG = K * G;
+  using V = typename Entries<T>::V;
+  using I = typename Entries<T>::I;
+  __shared__ int s_wide[NG * R];  // rows left to the whole workgroup
+  __shared__ int s_nwide;
+  __shared__ T s_part[kBlock / kWave];
+  const int tid = threadIdx.x, lane = lane_id();
+  const int gl = tid % G;
+  // rows of one pass over the groups are neighbours: a wave reads one stretch of entries per pass
+  const int row0 = xcd_contiguous_block_id(block, nblocks) * (NG * R) + tid / G;
+  int a[R], b[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int row = min(row0 + r * NG, nrows - 1);
+    a[r] = pos[row];
+    b[r] = pos[row + 1];
   }
-  constexpr int G = kStreamCap / (4 * kBlock);
-  for (int c0 = e0a; c0 < e1; c0 += kStreamCap) {
-    if (has_long) {
-      // Long stretch of one row ahead: its whole pieces are added up in registers, without
-      // LDS and without a barrier per piece (so the loads of consecutive pieces overlap), and
-      // folded into the row's lane once. Keeps a block with a 100 000-entry row from taking
-      // fifty serial load -> park -> add rounds.
-      const bool mine = ra <= c0 && rb - c0 >= 2 * kStreamCap;  // at most one lane
-      if (mine) s_lend = rb;
-      __syncthreads();
-      const int lend = s_lend;
-      __syncthreads();
-      if (mine) s_lend = 0;
-      if (lend) {
-        T part = T(0);
-        int c = c0;
-#pragma unroll 1
-        for (; c + kStreamCap <= lend; c += kStreamCap) {
+  if (tid == 0) s_nwide = 0;
+  T acc[R];
+  bool wide = false;
+  // K entries from p on, of which those before `end` count; loads stay inside the arrays
+  const auto load = [&](int p, I& c, V& v) {
+    const int q = min(p, nnz - K);
+    c = NT ? __builtin_nontemporal_load(reinterpret_cast<const I*>(crd + q)) : *reinterpret_cast<const I*>(crd + q);
+    v = NT ? __builtin_nontemporal_load(reinterpret_cast<const V*>(vals + q)) : *reinterpret_cast<const V*>(vals + q);
+  };
+  // x at those that count (an idle lane gathers nothing), 0 at the others: all gathers of a step
+  // are on their way before the first is used
+  const auto gather = [&](int p, int end, const I& c, T (&g)[K]) {
+    const int q = min(p, nnz - K);
 #pragma unroll
-          for (int g = 0; g < G; ++g) {
-            const int p = c + 4 * (g * kBlock + tid);
-            if (VEC) {
-              const i4 cc = ld_stream(reinterpret_cast<const i4*>(crd + p));
-              T v[4];
-#pragma unroll
-              for (int h = 0; h < 4 / R; ++h) {
-                const V w = ld_stream(reinterpret_cast<const V*>(vals + p + R * h));
-#pragma unroll
-                for (int r = 0; r < R; ++r) v[R * h + r] = w[r];
-              }
-#pragma unroll
-              for (int r = 0; r < 4; ++r) part += v[r] * x.at(cc[r]);
-            } else {
-#pragma unroll
-              for (int r = 0; r < 4; ++r) part += ld_stream(vals + p + r) * x.at(ld_stream(crd + p + r));
-            }
-          }
-        }
-        part = wave_sum(part);
-        if (lane_id() == 0) s_wpart[wave_id()] = part;
-        __syncthreads();
-        if (mine) {
-#pragma unroll
-          for (int w = 0; w < kBlock / kWave; ++w) acc += s_wpart[w];
-        }
-        __syncthreads();
-        c0 = c - kStreamCap;  // the loop's increment moves on to c
-        continue;
-      }
+    for (int k = 0; k < K; ++k) {
+      g[k] = 0;
+      if (q + k >= p && q + k < end) g[k] = x.at(c[k]);
     }
-    const int c1 = min(c0 + kStreamCap, e1);
-    // a lane holds up to G groups of 4 consecutive entries; all their loads are issued before
-    // the first use, none behind a per-lane branch: a lane without work in this piece re-reads
-    // the piece's first group (one cache line for all such lanes) and parks products nobody adds
-    const bool whole = VEC && c1 + 3 <= nnz;  // uniform: every 16-byte group lies inside the arrays
-    T pr[G][4];
-    if (whole) {
-      i4 c[G];
-      T v[G][4];
+  };
+  const auto dot = [](const V& v, const T (&g)[K]) {
+    T t = 0;
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
-        const int p = c0 + 4 * (g * kBlock + tid);
-        const int pc = p < c1 ? p : c0;
-        c[g] = ld_stream(reinterpret_cast<const i4*>(crd + pc));
+    for (int k = 0; k < K; ++k) t += v[k] * g[k];
+    return t;
+  };
+  {
+    I c[R];
+    V v[R];
+    T g[R][K];
 #pragma unroll
-        for (int h = 0; h < 4 / R; ++h) {
-          const V w = ld_stream(reinterpret_cast<const V*>(vals + pc + R * h));
-#pragma unroll
-          for (int r = 0; r < R; ++r) v[g][R * h + r] = w[r];
-        }
-      }
-#pragma unroll
-      for (int g = 0; g < G; ++g)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) pr[g][r] = v[g][r] * x.at(c[g][r]);
-    } else {
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        const int p = c0 + 4 * (g * kBlock + tid);
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          pr[g][r] = p + r < c1 ? ld_stream(vals + p + r) * x.at(ld_stream(crd + p + r)) : T(0);
-      }
+    for (int r = 0; r < R; ++r) {
+      const int p = a[r] + gl * K;
+      load(p < b[r] ? p : a[r], c[r], v[r]);  // an idle lane reads what its row's first lane reads
     }
 #pragma unroll
-    for (int g = 0; g < G; ++g)
+    for (int r = 0; r < R; ++r) gather(a[r] + gl * K, b[r] - a[r] <= 4 * KG ? b[r] : 0, c[r], g[r]);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) s_prod[4 * (g * kBlock + tid) + r] = pr[g][r];
-    __syncthreads();
-    const int a = max(ra, c0), e = min(rb, c1);
-    const bool big = e - a > kStreamCoop;
-    if (!big && a < e) {
-      for (int q0 = a; q0 < e; q0 += 8) {  // reads at a clamped index, added in order
-        T t[8];
+    for (int r = 0; r < R; ++r) acc[r] = dot(v[r], g[r]);
+  }
 #pragma unroll
-        for (int k = 0; k < 8; ++k) t[k] = s_prod[min(q0 + k, e - 1) - c0];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) acc += q0 + k < e ? t[k] : T(0);
+  for (int r = 0; r < R; ++r) {
+    const int len = b[r] - a[r];
+    if (len > KG && len <= 4 * KG) {
+      for (int p = a[r] + KG + gl * K; p < b[r]; p += KG) {
+        I c;
+        V v;
+        T g[K];
+        load(p, c, v);
+        gather(p, b[r], c, g);
+        acc[r] += dot(v, g);
       }
     }
-    uint64_t todo = __ballot(big);
-    while (todo) {  // uniform: the wave adds up one long row part at a time
+    acc[r] = group_sum<G>(acc[r]);
+    uint64_t todo = __ballot(gl == 0 && len > 4 * KG && len <= kRowsWide);
+    while (todo) {
       const int src = __ffsll(static_cast<long long>(todo)) - 1;
       todo &= todo - 1;
-      const int la = __shfl(a, src), lb = __shfl(e, src);
-      T part = T(0);
-      for (int q = la + lane_id(); q < lb; q += kWave) part += s_prod[q - c0];
-      part = wave_sum(part);
-      if (lane_id() == src) acc += part;
+      const int la = __shfl(a[r], src), lb = __shfl(b[r], src);
+      T part = 0;
+      for (int p = la + lane * K; p < lb; p += 2 * K * kWave) {
+        I c[2];
+        V v[2];
+        T g[2][K];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) load(p + u * K * kWave, c[u], v[u]);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) gather(p + u * K * kWave, lb, c[u], g[u]);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) part += dot(v[u], g[u]);
+      }
+      part = wave_total<T>(part);
+      if (lane == src) acc[r] = part;
+    }
+    const int row = row0 + r * NG;
+    if (row < nrows && gl == 0 && len <= kRowsWide) y[row] = acc[r];
+    wide |= row < nrows && len > kRowsWide;
+  }
+  if (!__syncthreads_or(wide)) return;
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (gl == 0 && row0 + r * NG < nrows && b[r] - a[r] > kRowsWide) s_wide[atomicAdd(&s_nwide, 1)] = row0 + r * NG;
+  __syncthreads();
+  const int nwide = s_nwide;
+  for (int w = 0; w < nwide; ++w) {
+    const int r = s_wide[w];
+    const int la = pos[r], lb = pos[r + 1];
+    T part = 0;
+    for (int p = la + tid; p < lb; p += 8 * kBlock) {
+      int32_t c[8];
+      T v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int q = min(p + u * kBlock, lb - 1);
+        c[u] = crd[q];
+        v[u] = vals[q];
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const T t = v[u] * x.at(c[u]);
+        part += p + u * kBlock < lb ? t : T(0);
+      }
+    }
+    part = wave_total<T>(part);
+    if (lane == 0) s_part[wave_id()] = part;
+    __syncthreads();
+    if (tid == 0) {
+      T sum = 0;
+#pragma unroll
+      for (int u = 0; u < kBlock / kWave; ++u) sum += s_part[u];
+      y[r] = sum;
     }
     __syncthreads();
   }
-  const int r = row0 + tid;
-  if (r < nrows) y[r] = acc;
+}
+
+template <typename T, int G, int R, bool NT, class XP>
+__global__ __launch_bounds__(kBlock) void csr_rows_kernel(int nblocks, int nrows, int nnz,
+                                                          const int32_t* __restrict__ pos,
+                                                          const int32_t* __restrict__ crd,
+                                                          const T* __restrict__ vals, const XP x,
+                                                          T* __restrict__ y) {
+  csr_rows_block<T, G, R, NT>(blockIdx.x, nblocks, nrows, nnz, pos, crd, vals, x, y);
+}
+// One of two candidates (the device has chosen): workgroups take several blocks, since the start of
+// 10^5 workgroups that return at once costs 40 us.
+template <typename T, int G, int R, class XP>
+__global__ __launch_bounds__(kBlock) void csr_rows_if_kernel(int nblocks, int nrows, int nnz,
+                                                             const int32_t* __restrict__ pos,
+                                                             const int32_t* __restrict__ crd,
+                                                             const T* __restrict__ vals, const XP x,
+                                                             T* __restrict__ y, const int32_t* __restrict__ select,
+                                                             int want) {
+  if (!selected(select, want)) return;
+  for (int block = blockIdx.x; block < nblocks; block += gridDim.x) {
+    csr_rows_block<T, G, R, true>(block, nblocks, nrows, nnz, pos, crd, vals, x, y);
+    __syncthreads();
+  }
+}
+constexpr int kIfBlocks = 16384;  // a multiple of the XCDs: a workgroup's blocks stay on one
+
+// Rows are skewed if declared so (max_children above kShortRow): then the entries are dealt
+// out evenly. Fewer than four entries do not fill a vector load.
+static bool csr_use_rows(int64_t nnz, int64_t nrows, int hint) {
+  return nnz >= 4 && nnz < INT32_MAX && nrows + kBlock < INT32_MAX && hint <= kShortRow;
 }
 
 template <typename T, class XP>
-static spt_status launch_csr_stream(int64_t nnz, int64_t nrows, const int32_t* pos,
-                                    const int32_t* crd, const T* vals, const XP x, T* y,
-                                    hipStream_t s, const int32_t* select = nullptr, int want = 0) {
-  const unsigned grid = (unsigned)((nrows + kStreamRows - 1) / kStreamRows);
-  const bool vec = ((reinterpret_cast<uintptr_t>(crd) | reinterpret_cast<uintptr_t>(vals)) & 15) == 0;
-  if (vec)
-    hipLaunchKernelGGL((csr_stream_kernel<T, true, XP>), dim3(grid), dim3(kBlock), 0, s, (int)nrows,
-                       (int)nnz, pos, crd, vals, x, y, select, want);
-  else
-    hipLaunchKernelGGL((csr_stream_kernel<T, false, XP>), dim3(grid), dim3(kBlock), 0, s, (int)nrows,
-                       (int)nnz, pos, crd, vals, x, y, select, want);
-  SPT_CHECK_LAUNCH("csr_stream");
+static spt_status launch_csr_rows(int64_t nnz, int64_t nrows, const int32_t* pos, const int32_t* crd, const T* vals,
+                                  const XP x, T* y, hipStream_t s, const int32_t* select = nullptr, int want = 0) {
+  // Rows per group at once: two where rows are so short that one leaves a lane with a single load
+  // (7 entries per row, 25.6M entries, fp64: 80 -> 70 us), else one. Up to 2^20 entries the chip is
+  // not full and waves that hold fewer rows meet fewer long ones: groups twice as wide.
+#define SPT_ROWS(G_, R_)                                                                                      \
+  do {                                                                                                        \
+    const int nb = (int)((nrows + kBlock / G_ * R_ - 1) / (kBlock / G_ * R_));                                \
+    if (select)                                                                                               \
+      hipLaunchKernelGGL((csr_rows_if_kernel<T, G_, R_, XP>), dim3(std::min(nb, kIfBlocks)), dim3(kBlock), 0, \
+                         s, nb, (int)nrows, (int)nnz, pos, crd, vals, x, y, select, want);                    \
+    else if (large)                                                                                           \
+      hipLaunchKernelGGL((csr_rows_kernel<T, G_, R_, true, XP>), dim3(nb), dim3(kBlock), 0, s, nb, (int)nrows, \
+                         (int)nnz, pos, crd, vals, x, y);                                                     \
+    else                                                                                                      \
+      hipLaunchKernelGGL((csr_rows_kernel<T, G_, R_, false, XP>), dim3(nb), dim3(kBlock), 0, s, nb, (int)nrows, \
+                         (int)nnz, pos, crd, vals, x, y);                                                     \
+  } while (0)
+  // Entries are read past the caches once the matrix would leave no room for x in them (7 per row,
+  // 25.6M entries, fp64: 76 -> 67 us; but 1.6M entries, uniform: 12 -> 14 us).
+  const bool large = nnz * (4 + (int64_t)sizeof(T)) > 96000000;
+  const bool small = nnz <= (1 << 20);
+  const bool two = !small && nnz <= 8 * nrows;
+  const int64_t lanes = nnz / Entries<T>::K * (small ? 2 : 1);
+  if (lanes <= 2 * nrows) {
+    if (two) SPT_ROWS(2, 2);
+    else SPT_ROWS(2, 1);
+  } else if (lanes <= 4 * nrows) {
+    if (two) SPT_ROWS(4, 2);
+    else SPT_ROWS(4, 1);
+  } else if (lanes <= 8 * nrows) {
+    SPT_ROWS(8, 1);
+  } else if (lanes <= 16 * nrows) {
+    SPT_ROWS(16, 1);
+  } else {
+    SPT_ROWS(32, 1);
+  }
+#undef SPT_ROWS
+  SPT_CHECK_LAUNCH("csr_rows");
   return SPT_OK;
-}
-
-// Which CSR kernel runs. The streamed kernel needs no search and no second launch and wins
-// where rows are short (banded matrix, 6 entries per row, fp64: 42 vs 65 us; rows of 8..32
-// entries, fp32: 117 vs 135 us); the entry-balanced kernel does not care how the entries are
-// spread over the rows (power-law rows, mean 15, longest 10^5: 0.97 ms against 1.08 ms
-// streamed). The host knows the mean row length (nvals / rows) and nothing about the spread,
-// so the mean decides, and a declared bound on the longest row (max_children of the column
-// level, 0 = unknown) overrides it either way.
-constexpr int kStreamMeanRow = 32;
-static bool csr_use_stream(int64_t nnz, int64_t nrows, int hint) {
-  if (nnz < 1 || nnz >= INT32_MAX || nrows + kBlock >= INT32_MAX) return false;
-  static const char* force = getenv("SPT_CSR_KERNEL");  // measurement aid: "stream" or "balanced"
-  if (force && force[0] == 's') return true;
-  if (force && force[0] == 'b') return false;
-  if (hint > 0) return hint <= kStreamMeanRow;
-  return nnz <= kStreamMeanRow * nrows;
 }
 
 // ---------------------------------------------------------------- unsorted COO
@@ -802,22 +854,22 @@ static spt_status launch_seg(int64_t nnz, int64_t nrows, const int32_t* pos_or_r
 
 // Large CSR matrices without a declared row bound: which kernel suits is decided on the device.
 // kSelectFlags workgroups look at the entry count of every block of 256 rows; if some block
-// holds more than 1/kSkewShare of all entries, the streamed kernel would end on that block's
-// workgroup alone (a block of 10^5 entries keeps one workgroup busy for about 0.1 ms), and the
-// entry-balanced kernel runs instead. Both kernels are launched; the one not chosen returns at
-// once. That costs some 10 us, which is why only matrices of kDynamicMinEntries entries or
-// more (kernel times from half a millisecond) are looked at; smaller ones go by the mean alone.
+// holds more than 1/kSkewShare of all entries, the row-wise kernel would end on the workgroup of
+// one long row (10^5 entries keep it busy for about 0.1 ms), and the entry-balanced kernel runs
+// instead (60M entries, power law: 0.97 ms against 1.10). Both kernels are launched; the one not
+// chosen returns at once. That costs some 10 us, which is why only matrices of kDynamicMinEntries
+// entries or more (kernel times from 0.4 ms) are looked at.
 constexpr int64_t kDynamicMinEntries = int64_t(1) << 25;
-constexpr int kSkewShare = 1536;
+constexpr int kSkewShare = 1536, kSkewRows = 256;
 __global__ __launch_bounds__(kBlock) void csr_skew_kernel(int nrows, int nnz, const int32_t* __restrict__ pos,
                                                           int32_t* __restrict__ select) {
   __shared__ int s_any;
   if (threadIdx.x == 0) s_any = 0;
   __syncthreads();
-  const int nblocks = (nrows + kStreamRows - 1) / kStreamRows;
+  const int nblocks = (nrows + kSkewRows - 1) / kSkewRows;
   int heavy = 0;
   for (int b = blockIdx.x * kBlock + threadIdx.x; b < nblocks; b += kSelectFlags * kBlock) {
-    const int64_t e = pos[min((b + 1) * kStreamRows, nrows)] - pos[b * kStreamRows];
+    const int64_t e = pos[min((b + 1) * kSkewRows, nrows)] - pos[b * kSkewRows];
     heavy |= e * kSkewShare > nnz;
   }
   if (heavy) s_any = 1;
@@ -834,18 +886,17 @@ static spt_status spmv_sparse_x_typed(const spt_tensor* A, const spt_tensor* X, 
   const int64_t nnz = A->nvals, N = A->level[0].N;
   const T* vals = static_cast<const T*>(A->vals);
   if (X->nvals >= INT32_MAX) return fail(SPT_ERR_UNSUPPORTED, "spmv: x too large");
-  const int hint = A->level[1].max_children;  // declared short rows: the streamed kernel
-  const bool stream = csr_use_stream(nnz, N, hint);
+  const bool rows = csr_use_rows(nnz, N, A->level[1].max_children);
   if (L.kind == SPT_HASHED) {
     if (L.M < 1) return fail(SPT_ERR_INVALID_ARG, "spmv: hashed x needs a table width W >= 1");
-    if (stream)
-      return launch_csr_stream<T, HashX<T>>(nnz, N, A->level[1].pos, A->level[1].crd, vals,
+    if (rows)
+      return launch_csr_rows<T, HashX<T>>(nnz, N, A->level[1].pos, A->level[1].crd, vals,
                                             HashX<T>{L.crd, xv, (int)L.M}, y, s);
     return launch_seg_x<T, true, HashX<T>>(nnz, N, A->level[1].pos, A->level[1].crd, vals,
                                            HashX<T>{L.crd, xv, (int)L.M}, y, ws, ws_bytes, s);
   }
-  if (stream)
-    return launch_csr_stream<T, SparseX<T>>(nnz, N, A->level[1].pos, A->level[1].crd, vals,
+  if (rows)
+    return launch_csr_rows<T, SparseX<T>>(nnz, N, A->level[1].pos, A->level[1].crd, vals,
                                             SparseX<T>{L.crd, xv, (int)X->nvals}, y, s);
   return launch_seg_x<T, true, SparseX<T>>(nnz, N, A->level[1].pos, A->level[1].crd, vals,
                                            SparseX<T>{L.crd, xv, (int)X->nvals}, y, ws, ws_bytes, s);
@@ -898,9 +949,8 @@ static spt_status spmv_typed(Format f, const spt_tensor* A, const T* x, T* y, vo
       T* t = reinterpret_cast<T*>(W.take<double>(stored));
       char* rest = static_cast<char*>(ws) + W.used;
       const int hint = A->level[1].max_children;
-      if (csr_use_stream(A->nvals, stored, hint))
-        st = launch_csr_stream<T, DenseX<T>>(A->nvals, stored, A->level[1].pos, A->level[1].crd, vals,
-                                             DenseX<T>{x}, t, s);
+      if (csr_use_rows(A->nvals, stored, hint))
+        st = launch_csr_rows<T>(A->nvals, stored, A->level[1].pos, A->level[1].crd, vals, DenseX<T>{x}, t, s);
       else
         st = launch_seg<T, true>(A->nvals, stored, A->level[1].pos, A->level[1].crd, vals, x, t, rest,
                                  ws_bytes - W.used, s);
@@ -912,28 +962,20 @@ static spt_status spmv_typed(Format f, const spt_tensor* A, const T* x, T* y, vo
     }
     case Format::CSR: {
       const int hint = A->level[1].max_children;
-      if (csr_use_stream(A->nvals, A->level[0].N, hint)) {
-        static const bool forced = getenv("SPT_CSR_KERNEL") != nullptr;
-        if (hint == 0 && A->nvals >= kDynamicMinEntries && !forced) {
-          if (!ws || ws_bytes < seg_spmv_workspace(A->nvals))
-            return fail(SPT_ERR_WORKSPACE, "spmv: workspace of %zu bytes needed, %zu given",
-                        seg_spmv_workspace(A->nvals), ws_bytes);
-          // the flags live in the last 256 bytes of the workspace, behind the carries
-          int32_t* select = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + seg_spmv_workspace(A->nvals) - 256);
-          hipLaunchKernelGGL(csr_skew_kernel, dim3(kSelectFlags), dim3(kBlock), 0, s, (int)A->level[0].N, (int)A->nvals,
-                             A->level[1].pos, select);
-          SPT_CHECK_LAUNCH("csr skew");
-          spt_status st = launch_csr_stream<T, DenseX<T>>(A->nvals, A->level[0].N, A->level[1].pos,
-                                                          A->level[1].crd, vals, DenseX<T>{x}, y, s, select, 0);
-          if (st != SPT_OK) return st;
-          return launch_seg<T, true>(A->nvals, A->level[0].N, A->level[1].pos, A->level[1].crd, vals, x, y,
-                                     ws, ws_bytes, s, select, 1);
-        }
-        return launch_csr_stream<T, DenseX<T>>(A->nvals, A->level[0].N, A->level[1].pos,
-                                               A->level[1].crd, vals, DenseX<T>{x}, y, s);
-      }
-      return launch_seg<T, true>(A->nvals, A->level[0].N, A->level[1].pos, A->level[1].crd, vals,
-                                 x, y, ws, ws_bytes, s);
+      const int64_t nnz = A->nvals, N = A->level[0].N;
+      const int32_t *pos = A->level[1].pos, *crd = A->level[1].crd;
+      if (!csr_use_rows(nnz, N, hint)) return launch_seg<T, true>(nnz, N, pos, crd, vals, x, y, ws, ws_bytes, s);
+      if (hint > 0 || nnz < kDynamicMinEntries) return launch_csr_rows<T>(nnz, N, pos, crd, vals, DenseX<T>{x}, y, s);
+      if (!ws || ws_bytes < seg_spmv_workspace(nnz))
+        return fail(SPT_ERR_WORKSPACE, "spmv: workspace of %zu bytes needed, %zu given", seg_spmv_workspace(nnz),
+                    ws_bytes);
+      // the flags live in the last 256 bytes of the workspace, behind the carries
+      int32_t* select = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + seg_spmv_workspace(nnz) - 256);
+      hipLaunchKernelGGL(csr_skew_kernel, dim3(kSelectFlags), dim3(kBlock), 0, s, (int)N, (int)nnz, pos, select);
+      SPT_CHECK_LAUNCH("csr skew");
+      spt_status st = launch_csr_rows<T>(nnz, N, pos, crd, vals, DenseX<T>{x}, y, s, select, 0);
+      if (st != SPT_OK) return st;
+      return launch_seg<T, true>(nnz, N, pos, crd, vals, x, y, ws, ws_bytes, s, select, 1);
     }
     case Format::CSC: {
       // (dense columns, compressed rows): the entries lie in column order, which makes the

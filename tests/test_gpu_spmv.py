@@ -326,3 +326,30 @@ def test_unsupported_and_invalid_descriptors_report_errors():
     with pytest.raises(spt.SptError) as e:
         spt.spt_spmv(A, None, y, A.workspace(spt.SPT_OP_SPMV))
     assert e.value.status == 1
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("lengths", [
+    [4], [0, 0, 4, 0], [1, 3], [3, 1, 0],                       # the fewest entries a vector load needs
+    [7] * 1000, [0, 1, 2, 3, 4, 5] * 300, [33, 31] * 500,        # groups of every width
+    [40] * 70 + [64, 65, 127, 128, 129, 255, 256, 257] * 3,      # lane group / wave boundary
+    [2] * 50 + [4095, 4096, 4097, 9001] + [1] * 50 + [20_000],   # wave / workgroup boundary
+], ids=lambda l: f"{len(l)}rows{sum(l)}")
+def test_csr_row_lengths_at_the_edges_of_the_row_kernel(lengths, dtype):
+    rng = np.random.default_rng(len(lengths))
+    M = 30_000
+    pos = np.concatenate([[0], np.cumsum(lengths)])
+    crd = np.concatenate([np.sort(rng.choice(M, n, replace=False)) for n in lengths]).astype(np.int32)
+    vals = rng.uniform(-1, 1, len(crd)).astype(dtype)
+    x = rng.uniform(-1, 1, M).astype(dtype)
+    spec = wl.csr_spec(len(lengths), M, pos, crd, vals)
+    _check(spec, x, "csr rows")
+    ref, mag = oracle.spmv(spec, x)
+    assert_close(gpu_spmv(spec, x, misalign=True), ref, mag, spec.vals.dtype, "csr rows, unaligned arrays")
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+def test_csr_two_rows_per_group(dtype):
+    """Above 2^20 entries with short rows a group of lanes takes two rows at once."""
+    c2 = wl.config2(N=180_001, dtype=dtype)
+    _check(c2["csr"], c2["x"], "csr short rows")

@@ -57,32 +57,26 @@ __global__ __launch_bounds__(kBlock) void dia_spmv_kernel(int64_t N, int64_t M, 
   y[i] = acc;
 }
 
-// ---------------------------------------------------------------- ELL
-// Cell (k,i) at k*N+i; a negative column marks padding and is skipped without
-// touching its value or x.
-template <typename T>
-__global__ __launch_bounds__(kBlock) void ell_spmv_kernel(int64_t N, int W,
-                                                          const int32_t* __restrict__ crd,
-                                                          const T* __restrict__ vals,
-                                                          const T* __restrict__ x,
-                                                          T* __restrict__ y) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= N) return;
-  T acc = 0;
-#pragma unroll 8
-  for (int k = 0; k < W; ++k) {
-    const int32_t j = ld_stream(crd + (int64_t)k * N + i);
-    if (j >= 0) acc += ld_stream(vals + (int64_t)k * N + i) * x[j];
-  }
-  y[i] = acc;
-}
-
 // ---------------------------------------------------------------- DIA / ELL, R rows per lane
-// Same computations with 16-byte loads: a lane owns R consecutive rows (R = 2
-// for fp64, 4 for fp32), so every access to the diagonal-major / slot-major
-// arrays is one aligned 16-byte vector. HBM delivers ~7 TB/s to 16-byte lane
-// loads but under 4 TB/s to 4-byte ones, hence the width. Needs N % R == 0 and
-// 16-byte aligned arrays (checked on the host; otherwise the scalar kernels run).
+// 16-byte loads: a lane owns R consecutive rows (R = 2 for fp64, 4 for fp32), and every access to
+// the diagonal-major / slot-major arrays is one 16-byte vector. HBM delivers ~7 TB/s to 16-byte
+// lane loads but under 4 TB/s to 4-byte ones, hence the width. The vectors need element alignment
+// only (the hardware takes them at any dword), so any number of rows will do: the last lane starts
+// at row N - R, and rows that two lanes compute get the same value twice.
+// 16 bytes of values and the columns that go with them, at any entry: vector loads that are only
+// element-aligned.
+template <typename T> struct Entries;
+template <> struct Entries<double> {
+  static constexpr int K = 2;
+  typedef double V __attribute__((ext_vector_type(2), aligned(8)));
+  typedef int32_t I __attribute__((ext_vector_type(2), aligned(4)));
+};
+template <> struct Entries<float> {
+  static constexpr int K = 4;
+  typedef float V __attribute__((ext_vector_type(4), aligned(4)));
+  typedef int32_t I __attribute__((ext_vector_type(4), aligned(4)));
+};
+
 template <typename T> struct VecOf;
 template <> struct VecOf<double> { static constexpr int R = 2; typedef double type __attribute__((ext_vector_type(2))); typedef int32_t itype __attribute__((ext_vector_type(2))); };
 template <> struct VecOf<float> { static constexpr int R = 4; typedef float type __attribute__((ext_vector_type(4))); typedef int32_t itype __attribute__((ext_vector_type(4))); };
@@ -92,92 +86,157 @@ template <> struct VecOf<float> { static constexpr int R = 4; typedef float type
 // round trip per lane). KT == 0: any K, in batches of 8 (the tail batch re-reads
 // the last diagonal and masks it out).
 // A diagonal whose row range [max(0,-off), min(N, M-off)) misses all rows of the
-// wave is skipped by the whole wave (a scalar branch): far diagonals are empty
+// wave is skipped by the whole wave (a scalar branch: far diagonals are empty
 // over half the matrix, and loading their cells would move bytes that are never
-// used. Inside a live wave no load sits behind a per-lane branch: cells outside the
-// range are loaded (they are inside the array) and masked, x is read at a clamped
-// index. XV: x is 16-byte aligned and M a multiple of R, so a diagonal whose offset
-// is a multiple of R reads its R values of x as one aligned 16-byte load.
-template <typename T, int KT, bool XV>
+// used). Where the range covers the wave's rows, x is one vector per lane as well; only
+// the waves at a diagonal's ends read x element by element, at a clamped index.
+// 7 diagonals, against x gathered element by element and a lane per row where no vector divides the
+// rows: 3.66M rows fp32 38 -> 23 us, 1.83M rows fp64 30 -> 24 us, 1.5M rows (odd) fp64 24 -> 20 us.
+template <typename T, int KT>
 __global__ __launch_bounds__(kBlock) void dia_spmv_vec_kernel(int64_t N, int64_t M, int K,
                                                               const int32_t* __restrict__ offset,
                                                               const T* __restrict__ vals,
                                                               const T* __restrict__ x,
                                                               T* __restrict__ y) {
-  constexpr int R = VecOf<T>::R;
+  constexpr int R = Entries<T>::K;
   constexpr int B = KT > 0 ? KT : 8;
-  using V = typename VecOf<T>::type;
+  using V = typename Entries<T>::V;
   const int64_t blk0 = (int64_t)xcd_contiguous_block_id() * kBlock;
-  const int64_t i0 = (blk0 + threadIdx.x) * R;
   // rows [w0, w1) belong to this wave (uniform: kept in scalar registers)
   const int64_t w0 = (blk0 + __builtin_amdgcn_readfirstlane(threadIdx.x & ~(kWave - 1))) * R;
-  const int64_t w1 = w0 + kWave * R;
-  if (i0 >= N) return;
-  V acc = 0;
+  if (w0 >= N) return;
+  const int64_t w1 = w0 + kWave * R < N ? w0 + kWave * R : N;
+  int64_t i0 = (blk0 + threadIdx.x) * R;
+  if (i0 > N - R) i0 = N - R;
+  T acc[R] = {};
   const int kend = KT > 0 ? KT : K;
   for (int d0 = 0; d0 < kend; d0 += B) {
     V v[B];
     V xv[B];
-    int64_t j0[B];
 #pragma unroll
     for (int u = 0; u < B; ++u) {
       const int d = min(d0 + u, kend - 1);
       const int64_t off = offset[d];  // uniform address: a scalar load
-      j0[u] = i0 + off;
       v[u] = 0;
       xv[u] = 0;
       const int64_t lo = off < 0 ? -off : 0, hi = (M - off) < N ? (M - off) : N;
-      if (w0 < hi && w1 > lo) {  // uniform
-        v[u] = ld_stream(reinterpret_cast<const V*>(vals + (int64_t)d * N + i0));
-        if (XV && (off % R) == 0) {  // uniform; j0 is a multiple of R
-          const int64_t jc = j0[u] < 0 ? 0 : (j0[u] > M - R ? M - R : j0[u]);
-          xv[u] = *reinterpret_cast<const V*>(x + jc);
+      if (w0 < hi && w1 > lo && d0 + u < kend) {  // uniform
+        v[u] = __builtin_nontemporal_load(reinterpret_cast<const V*>(vals + (int64_t)d * N + i0));
+        if (w0 - R >= lo && w1 <= hi) {  // uniform (the last lane may start before w0)
+          xv[u] = *reinterpret_cast<const V*>(x + i0 + off);
         } else {
 #pragma unroll
           for (int r = 0; r < R; ++r) {
-            const int64_t j = j0[u] + r;
-            xv[u][r] = x[j < 0 ? 0 : (j >= M ? M - 1 : j)];
+            const int64_t j = i0 + off + r;
+            const bool in = j >= 0 && j < M;
+            xv[u][r] = x[in ? j : 0];
+            if (!in) v[u][r] = xv[u][r] = 0;
           }
         }
       }
     }
 #pragma unroll
-    for (int u = 0; u < B; ++u) {
-      if (d0 + u < kend) {
+    for (int u = 0; u < B; ++u)
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const int64_t j = j0[u] + r;
-          acc[r] += (j >= 0 && j < M) ? v[u][r] * xv[u][r] : T(0);
-        }
-      }
-    }
+      for (int r = 0; r < R; ++r) acc[r] += v[u][r] * xv[u][r];
   }
-  *reinterpret_cast<V*>(y + i0) = acc;
+  V out;
+#pragma unroll
+  for (int r = 0; r < R; ++r) out[r] = acc[r];
+  *reinterpret_cast<V*>(y + i0) = out;
 }
 
-// Bound by the gathers of x (one cache line per stored entry), so the loop is
-// kept simple: padding neither gathers nor multiplies.
+// Fewer rows than a vector holds.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void ell_spmv_vec_kernel(int64_t N, int W,
-                                                              const int32_t* __restrict__ crd,
-                                                              const T* __restrict__ vals,
-                                                              const T* __restrict__ x,
-                                                              T* __restrict__ y) {
-  constexpr int R = VecOf<T>::R;
-  using V = typename VecOf<T>::type;
-  using IV = typename VecOf<T>::itype;
-  const int64_t i0 = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * R;
-  if (i0 >= N) return;
-  V acc = 0;
-#pragma unroll 4
+__global__ __launch_bounds__(kBlock) void ell_spmv_kernel(int64_t N, int W, const int32_t* __restrict__ crd,
+                                                          const T* __restrict__ vals, const T* __restrict__ x,
+                                                          T* __restrict__ y) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i >= N) return;
+  T acc = 0;
   for (int k = 0; k < W; ++k) {
-    const IV j = ld_stream(reinterpret_cast<const IV*>(crd + (int64_t)k * N + i0));
-    const V v = ld_stream(reinterpret_cast<const V*>(vals + (int64_t)k * N + i0));
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-      if (j[r] >= 0) acc[r] += v[r] * x[j[r]];
+    const int32_t j = crd[(int64_t)k * N + i];
+    if (j >= 0) acc += vals[(int64_t)k * N + i] * x[j];
   }
-  *reinterpret_cast<V*>(y + i0) = acc;
+  y[i] = acc;
+}
+
+// ELL: cell (k,i) at k*N+i; a negative column marks padding and is skipped without touching its
+// value or x. S waves share the slots of 64 * R rows and add up their parts in LDS: a matrix of few
+// rows would otherwise keep a wave for every 128 or 256 rows walking through all slots, one batch
+// of memory round trips after the other (42 000 rows of 32 slots: fp64 27 -> 9 us, fp32 25 -> 6.5 us;
+// 16 waves with two slots each gain nothing more). From kEllWaves waves on the chip is full without
+// that, and the plain loop over the slots reaches the rate of the x gathers (1M rows, fp32: 111 us;
+// split, or with batches of 4 or 8 slots, 117 to 135).
+constexpr int kEllWaves = 2800;
+
+template <typename T, int S>
+__global__ __launch_bounds__(kBlock) void ell_spmv_vec_kernel(
+    int64_t N, int W, const int32_t* __restrict__ crd, const T* __restrict__ vals, const T* __restrict__ x,
+    T* __restrict__ y) {
+  constexpr int R = Entries<T>::K;
+  constexpr int NR = kBlock / S;  // a workgroup takes NR * R rows
+  constexpr int kBatch = 8;  // slots whose loads are in flight together
+  using V = typename Entries<T>::V;
+  using I = typename Entries<T>::I;
+  __shared__ T s_part[S > 1 ? S : 1][S > 1 ? NR * R : 1];
+  const int lr = threadIdx.x % NR, part = S > 1 ? threadIdx.x / NR : 0;
+  int64_t i0 = ((int64_t)blockIdx.x * NR + lr) * R;
+  const bool live = i0 < N;
+  if (i0 > N - R) i0 = N - R;
+  const int per = (W + S - 1) / S;
+  const int k0 = part * per, k1 = min(k0 + per, W);
+  T acc[R] = {};
+  if (live && S == 1) {
+#pragma unroll 4
+    for (int k = 0; k < W; ++k) {
+      const int64_t c = (int64_t)k * N + i0;
+      const I j = __builtin_nontemporal_load(reinterpret_cast<const I*>(crd + c));
+      const V v = __builtin_nontemporal_load(reinterpret_cast<const V*>(vals + c));
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (j[r] >= 0) acc[r] += v[r] * x[j[r]];
+    }
+  } else if (live) {
+    for (int k = k0; k < k1; k += kBatch) {
+      I j[kBatch];
+      V v[kBatch];
+      T g[kBatch][R];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        const int64_t c = (int64_t)min(k + u, k1 - 1) * N + i0;
+        j[u] = __builtin_nontemporal_load(reinterpret_cast<const I*>(crd + c));
+        v[u] = __builtin_nontemporal_load(reinterpret_cast<const V*>(vals + c));
+      }
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          g[u][r] = 0;
+          if (k + u < k1 && j[u][r] >= 0) g[u][r] = x[j[u][r]];
+          else v[u][r] = 0;
+        }
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u)
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r] += v[u][r] * g[u][r];
+    }
+  }
+  if (S > 1) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) s_part[part][r * NR + lr] = acc[r];
+    __syncthreads();
+    if (part > 0) return;
+#pragma unroll
+    for (int q = 1; q < S; ++q)
+#pragma unroll
+      for (int r = 0; r < R; ++r) acc[r] += s_part[q][r * NR + lr];
+  }
+  if (!live) return;
+  V out;
+#pragma unroll
+  for (int r = 0; r < R; ++r) out[r] = acc[r];
+  *reinterpret_cast<V*>(y + i0) = out;
 }
 
 static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
@@ -409,20 +468,6 @@ __device__ __forceinline__ T group_sum(T v) {
   for (int d = 16; d < G; d <<= 1) v += __shfl_xor(v, d);
   return v;
 }
-
-// 16 bytes of values and the columns that go with them, at any entry: vector loads that are only
-// element-aligned.
-template <typename T> struct Entries;
-template <> struct Entries<double> {
-  static constexpr int K = 2;
-  typedef double V __attribute__((ext_vector_type(2), aligned(8)));
-  typedef int32_t I __attribute__((ext_vector_type(2), aligned(4)));
-};
-template <> struct Entries<float> {
-  static constexpr int K = 4;
-  typedef float V __attribute__((ext_vector_type(4), aligned(4)));
-  typedef int32_t I __attribute__((ext_vector_type(4), aligned(4)));
-};
 
 // Block `block` of `nblocks`: NG * R consecutive rows.
 template <typename T, int G, int R, bool NT, class XP>
@@ -1031,21 +1076,15 @@ static spt_status spmv_typed(Format f, const spt_tensor* A, const T* x, T* y, vo
       if (N == 0) return SPT_OK;
       if (K >= INT32_MAX) return fail(SPT_ERR_UNSUPPORTED, "spmv: too many diagonals");
       if (K == 0) return launch_fill<T>(y, N, T(0), s);
-      constexpr int R = VecOf<T>::R;
+      constexpr int R = Entries<T>::K;
       if (M == 0) return launch_fill<T>(y, N, T(0), s);
-      if (N % R == 0 && aligned16(vals) && aligned16(y)) {
-        const int64_t lanes = N / R;
+      if (N >= R) {
+        const int64_t lanes = (N + R - 1) / R;
         const dim3 grid((unsigned)((lanes + kBlock - 1) / kBlock));
         const int32_t* off = A->level[1].offset;
-        const bool xvec = aligned16(x) && M % R == 0 && M >= R;
-#define SPT_DIA_CASE(KT)                                                                       \
-  case KT:                                                                                     \
-    if (xvec)                                                                                  \
-      hipLaunchKernelGGL((dia_spmv_vec_kernel<T, KT, true>), grid, dim3(kBlock), 0, s, N, M,   \
-                         (int)K, off, vals, x, y);                                             \
-    else                                                                                       \
-      hipLaunchKernelGGL((dia_spmv_vec_kernel<T, KT, false>), grid, dim3(kBlock), 0, s, N, M,  \
-                         (int)K, off, vals, x, y);                                             \
+#define SPT_DIA_CASE(KT)                                                                                       \
+  case KT:                                                                                                     \
+    hipLaunchKernelGGL((dia_spmv_vec_kernel<T, KT>), grid, dim3(kBlock), 0, s, N, M, (int)K, off, vals, x, y); \
     break;
         switch (K <= 16 ? (int)K : 0) {
           SPT_DIA_CASE(1) SPT_DIA_CASE(2) SPT_DIA_CASE(3) SPT_DIA_CASE(4) SPT_DIA_CASE(5)
@@ -1053,8 +1092,7 @@ static spt_status spmv_typed(Format f, const spt_tensor* A, const T* x, T* y, vo
           SPT_DIA_CASE(11) SPT_DIA_CASE(12) SPT_DIA_CASE(13) SPT_DIA_CASE(14) SPT_DIA_CASE(15)
           SPT_DIA_CASE(16)
           default:
-            hipLaunchKernelGGL((dia_spmv_vec_kernel<T, 0, false>), grid, dim3(kBlock), 0, s, N, M,
-                               (int)K, off, vals, x, y);
+            hipLaunchKernelGGL((dia_spmv_vec_kernel<T, 0>), grid, dim3(kBlock), 0, s, N, M, (int)K, off, vals, x, y);
         }
 #undef SPT_DIA_CASE
       } else {
@@ -1068,12 +1106,16 @@ static spt_status spmv_typed(Format f, const spt_tensor* A, const T* x, T* y, vo
       const int64_t Wd = A->level[0].N, N = A->level[1].N;
       if (N == 0) return SPT_OK;
       if (Wd >= INT32_MAX) return fail(SPT_ERR_UNSUPPORTED, "spmv: ELL width too large");
-      constexpr int R = VecOf<T>::R;
+      constexpr int R = Entries<T>::K;
       if (Wd == 0 || A->level[2].N == 0) return launch_fill<T>(y, N, T(0), s);
-      if (N % R == 0 && aligned16(vals) && aligned16(y) && aligned16(A->level[2].crd)) {
-        const int64_t lanes = N / R;
-        hipLaunchKernelGGL(ell_spmv_vec_kernel<T>, dim3((unsigned)((lanes + kBlock - 1) / kBlock)),
-                           dim3(kBlock), 0, s, N, (int)Wd, A->level[2].crd, vals, x, y);
+      if (N >= R) {
+        const int64_t waves = (N + kWave * R - 1) / (kWave * R);
+        if (waves >= kEllWaves || Wd <= 8)
+          hipLaunchKernelGGL((ell_spmv_vec_kernel<T, 1>), dim3((unsigned)((waves + 3) / 4)), dim3(kBlock), 0, s, N,
+                             (int)Wd, A->level[2].crd, vals, x, y);
+        else
+          hipLaunchKernelGGL((ell_spmv_vec_kernel<T, 4>), dim3((unsigned)waves), dim3(kBlock), 0, s, N, (int)Wd,
+                             A->level[2].crd, vals, x, y);
       } else {
         hipLaunchKernelGGL(ell_spmv_kernel<T>, dim3((unsigned)((N + kBlock - 1) / kBlock)),
                            dim3(kBlock), 0, s, N, (int)Wd, A->level[2].crd, vals, x, y);

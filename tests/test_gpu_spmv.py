@@ -353,3 +353,19 @@ def test_csr_two_rows_per_group(dtype):
     """Above 2^20 entries with short rows a group of lanes takes two rows at once."""
     c2 = wl.config2(N=180_001, dtype=dtype)
     _check(c2["csr"], c2["x"], "csr short rows")
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("N", [1, 2, 3, 4, 5, 7, 127, 129, 255, 257, 511, 513, 1027])
+def test_dia_and_ell_at_any_row_count(N, dtype):
+    """Row counts around the vectors, waves and workgroups; fewer and more slots than one batch."""
+    c2 = wl.config2(N=N, poison=True, dtype=dtype) if N >= 127 else None
+    if c2:
+        _check(c2["dia"], c2["x"], f"dia N={N}")
+    for lo, hi in ((0, 3), (2, 9), (1, min(33, N + 1))):
+        c3 = wl.config3(N=N, lo=min(lo, N), hi=min(hi, N), dtype=dtype, seed=N + hi)
+        _check(c3["ell"], c3["x"], f"ell N={N} W={c3['W']}")
+    M = 3 * N + 5                                   # rectangular, diagonals that leave the matrix early
+    off = np.array([-(N - 1), -1, 0, 2, N, M - 1]) if N > 1 else np.array([0, M - 1])
+    vals = np.random.default_rng(N).uniform(-1, 1, (len(off), N)).astype(dtype)
+    _check(wl.dia_spec(N, M, off, vals), wl.dense_vector(M, 5, dtype), f"dia N={N} M={M}")

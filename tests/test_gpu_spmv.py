@@ -369,3 +369,15 @@ def test_dia_and_ell_at_any_row_count(N, dtype):
     off = np.array([-(N - 1), -1, 0, 2, N, M - 1]) if N > 1 else np.array([0, M - 1])
     vals = np.random.default_rng(N).uniform(-1, 1, (len(off), N)).astype(dtype)
     _check(wl.dia_spec(N, M, off, vals), wl.dense_vector(M, 5, dtype), f"dia N={N} M={M}")
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("nnz", [786_431, 786_432, 786_433, 1_100_003])
+def test_unordered_coo_where_binning_begins(nnz, dtype):
+    rng = np.random.default_rng(nnz)
+    for N, M, heavy in ((30_000, 20_000, 0), (5, 7000, 0), (100_000, 9000, 400_000)):
+        r, c = rng.integers(0, N, nnz), rng.integers(0, M, nnz)
+        r[:heavy] = N // 3                              # one row: its bin has several slices
+        p = rng.permutation(nnz)
+        _check(wl.coo_spec(N, M, r[p], c[p], rng.uniform(-1, 1, nnz).astype(dtype), ordered=False),
+               wl.dense_vector(M, 5, dtype), f"unordered nnz={nnz} N={N} heavy={heavy}")

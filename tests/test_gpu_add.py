@@ -63,6 +63,28 @@ def test_add_skewed_rows_empty_rows_and_misaligned(fmt):
     _check_matrix(c, b, fmt, np.float64, f"add {fmt} skewed swapped")
 
 
+@pytest.mark.parametrize("fmt", ["coo", "csr"])
+@pytest.mark.parametrize("N,M,nb,shared", [
+    (1, 5000, 1023, 1023), (1, 5000, 1024, 1024), (3, 4000, 2048, 2047),  # twins where a tile ends
+    (2046, 9, 1, 1), (2047, 9, 1, 0), (5_000_000, 64, 5000, 2500),        # tiles of nothing but row starts
+    (3000, 4000, 3_000_000, 1_500_000)])                                  # more tiles than are resident at once
+def test_add_and_mul_at_the_edges_of_tiles(fmt, N, M, nb, shared):
+    r, c, v = wl.random_coo_entries(N, M, nb, seed=nb, dtype=np.float64)
+    r2, c2, v2 = wl.random_coo_entries(N, M, max(nb // 2, 1), seed=nb + 1, dtype=np.float64)
+    keep = np.sort(np.random.default_rng(nb).permutation(len(v))[:shared])
+    key = np.concatenate([r[keep].astype(np.int64) * M + c[keep], r2.astype(np.int64) * M + c2])
+    key, first = np.unique(key, return_index=True)
+    w = np.concatenate([v[keep] * 0.5, v2])[first]
+    mk = wl.csr_from_sorted_coo if fmt == "csr" else wl.coo_spec
+    b, d = mk(N, M, r, c, v), mk(N, M, (key // M).astype(np.int32), (key % M).astype(np.int32), w)
+    _check_matrix(b, d, fmt, np.float64, "add")
+    (ri, ci), rv, rm = oracle.mul(b, d)
+    idx, gv = gpu_add(d, b, fmt, op="mul")
+    rows = np.concatenate([[0], np.cumsum(np.bincount(ri, minlength=N))]) if fmt == "csr" else ri
+    assert np.array_equal(idx[0], rows) and np.array_equal(idx[1], ci)
+    assert_close(gv, rv, rm, np.float64, "mul")
+
+
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
 @pytest.mark.parametrize("nb,nc", [(100, 90), (20_000, 30_000), (5_000, 450_000)])
 def test_plus_third_order(dtype, nb, nc):

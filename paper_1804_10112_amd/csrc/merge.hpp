@@ -1,5 +1,5 @@
-// Merge-path machinery shared by the co-iteration kernels (INNERPROD: intersection,
-// sparse addition: union) over two ordered, unique COO coordinate lists (Section 4.4).
+// Coordinate keys of ordered, unique COO lists (Section 4.4), shared by INNERPROD and the sparse
+// addition, and the merge-path partition of INNERPROD.
 #pragma once
 #include "common.hpp"
 

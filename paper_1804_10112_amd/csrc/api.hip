@@ -41,7 +41,8 @@ spt_status ttv_dispatch(Format f, const spt_tensor* B, const void* c, int32_t* o
 size_t ttv_workspace(Format f, const spt_tensor* B);
 spt_status mttkrp_dispatch(Format f, const spt_tensor* B, const void* C, const void* D, int32_t J,
                            void* A_out, void* ws, size_t ws_bytes, hipStream_t s);
-size_t mttkrp_workspace(Format f, const spt_tensor* B, int32_t J);
+size_t spdm_workspace(const spt_tensor* B, int32_t J);
+size_t mttkrp3_workspace(const spt_tensor* B, int32_t J);
 spt_status spdm_dispatch(const spt_tensor* B, const void* C, int32_t J, void* A_out, void* ws,
                          size_t ws_bytes, hipStream_t s);
 
@@ -704,7 +705,7 @@ size_t spt_workspace_bytes(int32_t op, const spt_tensor* T, int32_t J) {
       n = f == Format::CSR ? seg_spmv_workspace(T->nvals) : 0;
       break;
     case SPT_OP_SPDM:
-      n = f == Format::COO2 ? mttkrp_workspace(f, T, J) : 0;
+      n = f == Format::COO2 ? spdm_workspace(T, J) : 0;
       break;
     case SPT_OP_SPMV:
       if (f == Format::CSR || (f == Format::COO2 && (T->level[0].flags & SPT_ORDERED)))
@@ -725,7 +726,7 @@ size_t spt_workspace_bytes(int32_t op, const spt_tensor* T, int32_t J) {
       n = ttv_workspace(f, T);
       break;
     case SPT_OP_MTTKRP:
-      n = mttkrp_workspace(f, T, J);
+      n = mttkrp3_workspace(T, J);
       break;
     case SPT_OP_TTM:
       n = (f == Format::COO3 || f == Format::CSF3) ? ttm_workspace(f, T, J) : 0;

@@ -1,0 +1,559 @@
+// MTTKRP A_ij = sum_kl B_ikl C_kj D_lj on ordered COO and on CSF (Section 5.3), gfx950.
+//
+// A run of consecutive entries with the same i is one row of A (deduplication, Section 4.3). Entries
+// are split evenly: a workgroup has a chunk, a group of L lanes `epg` consecutive entries of it, and a
+// lane one 16-byte vector of the J columns, so that a load instruction of a wave fetches the factor
+// rows of 64 / L entries. A lane holds the coordinates of four entries at a time; they are handed
+// around its group, and the eight factor rows of four entries are in flight together.
+//   - A row that begins and ends inside a group is stored by the group; rows across groups are added
+//     up by a segmented scan over the groups; the part of a chunk that continues a row begun before it
+//     leaves as a carry (row, J values), which the carry kernels add in a fixed order (no atomics).
+//   - CSF: i and k are the last slice and fibre that start at or before an entry. The starts inside a
+//     chunk are marked in a bit set in LDS; C[k, :] is multiplied once per fibre (factored form).
+// Bound by the gathers of factor rows, large tensors by those that miss L2 (50M entries, J = 32, fp32:
+// 970 us, 68M lines of 128 bytes from L2, of them 37M from beyond; more or fewer waves, the next rows
+// loaded ahead, or C[k, :] kept while k stays change nothing). With 32 lanes of one column per entry,
+// which issue four times as many loads and hand-arounds, and longer walks per group: 1080 us, and for
+// 738 000 entries in CSF, J = 16, fp64, 96 us instead of 47.
+#include <algorithm>
+
+#include "common.hpp"
+#include "search.hpp"
+
+namespace spt {
+
+template <typename T>
+constexpr int kVec = 16 / sizeof(T);
+
+template <typename T, int V>
+struct ColVec {
+  typedef T type __attribute__((ext_vector_type(V), aligned(sizeof(T))));
+};
+template <typename T>
+struct ColVec<T, 1> {
+  typedef T type;
+};
+template <typename T, int V>
+__device__ __forceinline__ void load_cols(const T* p, T (&x)[V]) {
+  const typename ColVec<T, V>::type v = *reinterpret_cast<const typename ColVec<T, V>::type*>(p);
+  if constexpr (V == 1) {
+    x[0] = v;
+  } else {
+#pragma unroll
+    for (int q = 0; q < V; ++q) x[q] = v[q];
+  }
+}
+template <typename T, int V>
+__device__ __forceinline__ void store_cols(T* p, const T (&x)[V]) {
+  typename ColVec<T, V>::type v;
+  if constexpr (V == 1) {
+    v = x[0];
+  } else {
+#pragma unroll
+    for (int q = 0; q < V; ++q) v[q] = x[q];
+  }
+  *reinterpret_cast<typename ColVec<T, V>::type*>(p) = v;
+}
+
+// Four consecutive values from p + e on, those at `end` and beyond as zero.
+template <typename E>
+__device__ __forceinline__ void load_four(const E* __restrict__ p, int e, int end, E (&x)[4]) {
+  typedef E V4 __attribute__((ext_vector_type(4), aligned(sizeof(E))));
+  if (e + 4 <= end) {
+    const V4 v = __builtin_nontemporal_load(reinterpret_cast<const V4*>(p + e));
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[r] = v[r];
+  } else {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[r] = e + r < end ? p[e + r] : E(0);
+  }
+}
+
+// Value of lane addr / 4, through the LDS crossbar.
+__device__ __forceinline__ int32_t from_lane(int addr, int32_t v) { return __builtin_amdgcn_ds_bpermute(addr, v); }
+__device__ __forceinline__ float from_lane(int addr, float v) {
+  return __int_as_float(__builtin_amdgcn_ds_bpermute(addr, __float_as_int(v)));
+}
+__device__ __forceinline__ double from_lane(int addr, double v) {
+  const int lo = __builtin_amdgcn_ds_bpermute(addr, __double2loint(v));
+  const int hi = __builtin_amdgcn_ds_bpermute(addr, __double2hiint(v));
+  return __hiloint2double(hi, lo);
+}
+
+// The upper levels of a CSF tensor; bounds as made by mttkrp_prepare_kernel.
+struct CsfLevels {
+  const int32_t *crd0, *pos1, *crd1, *pos2, *bounds;
+};
+
+// Zeroes A (rows without entries stay zero). CSF: for chunk boundary c (entries from c * chunk on),
+// bounds[3c] = first fibre that starts at or after it, bounds[3c+1] = first slice that starts at or
+// after that fibre, bounds[3c+2] = the same as the end of the chunk before (all slices once the fibres
+// are used up). Boundary nchunks is the end. Eight lanes search a boundary.
+constexpr int kBoundLanes = 8;
+template <typename T>
+__global__ __launch_bounds__(kBlock) void mttkrp_prepare_kernel(T* __restrict__ A, int64_t size, int fill_blocks,
+                                                                int nchunks, int chunk, int nslices, int nfibres,
+                                                                const int32_t* __restrict__ pos1,
+                                                                const int32_t* __restrict__ pos2,
+                                                                int32_t* __restrict__ bounds) {
+  if (static_cast<int>(blockIdx.x) < fill_blocks) {
+    typedef T V __attribute__((ext_vector_type(kVec<T>), aligned(sizeof(T))));
+    const int64_t e = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) * kVec<T>;
+    if (e + kVec<T> <= size) *reinterpret_cast<V*>(A + e) = V(T(0));
+    else
+      for (int64_t q = e; q < size; ++q) A[q] = T(0);
+    return;
+  }
+  const int c = ((blockIdx.x - fill_blocks) * kBlock + threadIdx.x) / kBoundLanes;
+  if (c > nchunks) return;
+  int f = nfibres;
+  if (c < nchunks) {
+    const int target = c * chunk;
+    f = group_last_true<kBoundLanes>(0, static_cast<int64_t>(nfibres) + 2, [&](int q) { return q == 0 || pos2[q - 1] < target; });
+  }
+  const int sl = group_last_true<kBoundLanes>(0, static_cast<int64_t>(nslices) + 2, [&](int q) { return q == 0 || pos1[q - 1] < f; });
+  if (threadIdx.x % kBoundLanes == 0) {
+    bounds[3 * c] = f;
+    bounds[3 * c + 1] = sl;
+    bounds[3 * c + 2] = f >= nfibres ? nslices : sl;
+  }
+}
+
+// Position of the last marked entry at or before entry e; before[w] = last marked entry before word w.
+__device__ __forceinline__ int last_mark(const uint32_t* marks, const int16_t* before, int e) {
+  const int w = e >> 5;
+  const uint32_t m = marks[w] & ((2u << (e & 31)) - 1);
+  return m ? w * 32 + 31 - __clz(m) : before[w];
+}
+
+// before[] of `words` words, by one wave. Entry 0 is marked.
+__device__ __forceinline__ void marks_before(const uint32_t* marks, int16_t* before, int words) {
+  int from = 0;
+  for (int w0 = 0; w0 < words; w0 += kWave) {
+    const int w = w0 + lane_id();
+    const uint32_t m = w < words ? marks[w] : 0;
+    const uint64_t any = __ballot(m != 0), below = any & ((uint64_t{1} << lane_id()) - 1);
+    const int at = m ? w * 32 + 31 - __clz(m) : 0;
+    const int prev = __shfl(at, below ? 63 - __clzll(static_cast<long long>(below)) : 0);
+    if (w < words) before[w] = static_cast<int16_t>(below ? prev : from);
+    if (any) from = __shfl(at, 63 - __clzll(static_cast<long long>(any)));
+  }
+}
+
+template <typename T, int L, int V, bool CSF>
+__global__ __launch_bounds__(kBlock) void mttkrp_rows_kernel(int n, int J, int epg, const int32_t* __restrict__ ci,
+                                                             const int32_t* __restrict__ ck,
+                                                             const int32_t* __restrict__ cl,
+                                                             const T* __restrict__ vals, const T* __restrict__ Cm,
+                                                             const T* __restrict__ Dm, const CsfLevels csf,
+                                                             T* __restrict__ A, int32_t* __restrict__ carry_key,
+                                                             T* __restrict__ carry_vec) {
+  constexpr int NG = kBlock / L, kGroupsOfWave = kWave / L;
+  extern __shared__ __attribute__((aligned(16))) int32_t s_csf[];
+  __shared__ T s_v[kBlock / kWave][L][V];
+  __shared__ int s_f[kBlock / kWave];
+  __shared__ int s_slice_first;  // the chunk starts with a slice
+  const int tid = threadIdx.x, lane = lane_id();
+  const int g = tid / L, gl = tid % L;
+  const int chunk = xcd_contiguous_block_id(), size = NG * epg;
+  const int base = chunk * size, end = min(base + size, n);
+  // the last vector of a row ends with the row (it repeats columns of the one before if J is no multiple of V)
+  const bool jok = (static_cast<int>(blockIdx.y) * L + gl) * V < J;
+  const int col = min((static_cast<int>(blockIdx.y) * L + gl) * V, J - V);
+
+  int32_t *s_k = s_csf, *s_i = s_csf + size;
+  uint32_t *s_fibre = reinterpret_cast<uint32_t*>(s_i + size), *s_slice = s_fibre + (size + 31) / 32;
+  int16_t *s_fibre_before = reinterpret_cast<int16_t*>(s_slice + (size + 31) / 32), *s_slice_before = s_fibre_before + (size + 31) / 32;
+  if (CSF) {
+    const int f_lo = csf.bounds[3 * chunk], f_hi = csf.bounds[3 * chunk + 3];
+    const int s_lo = csf.bounds[3 * chunk + 1], s_hi = csf.bounds[3 * chunk + 5];
+    int32_t cut_k = -1, cut_i = -1;  // of the fibre and the slice that the chunk's start cuts
+    if (tid == 0) {
+      if (f_lo > 0) cut_k = csf.crd1[f_lo - 1];
+      if (s_lo > 0) cut_i = csf.crd0[s_lo - 1];
+    }
+    for (int w = tid; w < 2 * ((size + 31) / 32); w += kBlock) s_fibre[w] = 0;
+    __syncthreads();
+    for (int f = f_lo + tid; f < f_hi; f += kBlock) {
+      const int a = csf.pos2[f], b = csf.pos2[f + 1], k = csf.crd1[f];
+      if (b > a) {
+        s_k[a - base] = k;
+        atomicOr(&s_fibre[(a - base) >> 5], 1u << ((a - base) & 31));
+      }
+    }
+    // a slice is marked at its first stored entry, whichever of its fibres holds it (a
+    // compressed level may hold empty segments: leading fibres of a slice can be empty)
+    for (int sl = s_lo + tid; sl < s_hi; sl += kBlock) {
+      const int a = csf.pos2[csf.pos1[sl]], b = csf.pos2[csf.pos1[sl + 1]];
+      if (b > a && a < end) {
+        s_i[a - base] = csf.crd0[sl];
+        atomicOr(&s_slice[(a - base) >> 5], 1u << ((a - base) & 31));
+      }
+    }
+    __syncthreads();
+    if (tid == 0) {
+      s_slice_first = s_slice[0] & 1;
+      if (!(s_fibre[0] & 1)) {
+        s_k[0] = cut_k;
+        s_fibre[0] |= 1;
+      }
+      if (!(s_slice[0] & 1)) {
+        s_i[0] = cut_i;
+        s_slice[0] |= 1;
+      }
+    }
+    __syncthreads();
+    if (wave_id() == 0) marks_before(s_fibre, s_fibre_before, (size + 31) / 32);
+    if (wave_id() == 1) marks_before(s_slice, s_slice_before, (size + 31) / 32);
+    __syncthreads();
+  }
+
+  const int g0 = base + g * epg, g1 = min(g0 + epg, end);
+  T acc[V], lead[V], t[V], c_cur[V];
+#pragma unroll
+  for (int q = 0; q < V; ++q) acc[q] = lead[q] = t[q] = c_cur[q] = T(0);
+  bool has_head = false;
+  int first_close = -1, cur_k = -1;
+  // the row of the entry before this group's first (-1: there is none; -2: a different one)
+  int cur;
+  if (!CSF) cur = g0 >= end ? ci[end - 1] : g0 > 0 ? ci[g0 - 1] : -1;
+  else if (g0 >= end) cur = s_i[last_mark(s_slice, s_slice_before, end - 1 - base)];
+  else if (g0 > base) cur = s_i[last_mark(s_slice, s_slice_before, g0 - 1 - base)];
+  else cur = base == 0 ? -1 : s_slice_first ? -2 : s_i[0];
+
+  for (int b0 = g0; b0 < g1; b0 += 4 * L) {
+    int32_t ri[4], rk[4], rl[4];
+    T rv[4];
+    const int p = b0 + 4 * gl;
+    load_four(cl, p, g1, rl);
+    load_four(vals, p, g1, rv);
+    if (!CSF) {
+      load_four(ci, p, g1, ri);
+      load_four(ck, p, g1, rk);
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int e = min(p + r, end - 1) - base;
+        ri[r] = s_i[last_mark(s_slice, s_slice_before, e)];
+        rk[r] = s_k[last_mark(s_fibre, s_fibre_before, e)];
+      }
+    }
+    const int batch = min(4 * L, g1 - b0);
+    for (int q = 0; 4 * q < batch; ++q) {
+      const int addr = 4 * ((lane & ~(L - 1)) + q);
+      int i[4], k[4];
+      T v[4], c[4][V], d[4][V];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        i[r] = from_lane(addr, ri[r]);
+        k[r] = from_lane(addr, rk[r]);
+        const int l = from_lane(addr, rl[r]);
+        v[r] = from_lane(addr, rv[r]);
+        load_cols<T, V>(Cm + static_cast<int64_t>(k[r]) * J + col, c[r]);
+        load_cols<T, V>(Dm + static_cast<int64_t>(l) * J + col, d[r]);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if (4 * q + r < batch) {
+          if (CSF && (i[r] != cur || k[r] != cur_k)) {  // close the fibre
+#pragma unroll
+            for (int x = 0; x < V; ++x) {
+              acc[x] += c_cur[x] * t[x];
+              t[x] = T(0);
+              c_cur[x] = c[r][x];
+            }
+            cur_k = k[r];
+          }
+          if (i[r] != cur) {  // close the row
+            if (!has_head) {
+              has_head = true;
+              first_close = cur;
+#pragma unroll
+              for (int x = 0; x < V; ++x) lead[x] = acc[x];
+            } else if (jok) {
+              store_cols<T, V>(A + static_cast<int64_t>(cur) * J + col, acc);
+            }
+            cur = i[r];
+#pragma unroll
+            for (int x = 0; x < V; ++x) acc[x] = T(0);
+          }
+#pragma unroll
+          for (int x = 0; x < V; ++x) {
+            if (CSF) t[x] += v[r] * d[r][x];
+            else acc[x] += v[r] * c[r][x] * d[r][x];
+          }
+        }
+      }
+    }
+  }
+  if (CSF)
+#pragma unroll
+    for (int x = 0; x < V; ++x) acc[x] += c_cur[x] * t[x];
+
+  // sums of open rows over the groups: (a row ends here, what is open after it)
+  bool f = has_head;
+#pragma unroll
+  for (int s = 1; s < kGroupsOfWave; s <<= 1) {
+    const bool uf = __shfl_up(static_cast<int>(f), s * L);
+    const bool in = lane >= s * L;
+#pragma unroll
+    for (int x = 0; x < V; ++x) {
+      const T up = __shfl_up(acc[x], s * L);
+      if (in && !f) acc[x] = up + acc[x];
+    }
+    f = f || (in && uf);
+  }
+  if (lane / L == kGroupsOfWave - 1) {
+#pragma unroll
+    for (int x = 0; x < V; ++x) s_v[wave_id()][gl][x] = acc[x];
+    if (gl == 0) s_f[wave_id()] = f;
+  }
+  __syncthreads();
+  T pre[V];
+  bool pre_f = false;
+#pragma unroll
+  for (int x = 0; x < V; ++x) pre[x] = T(0);
+  for (int w = 0; w < wave_id(); ++w) {
+    const bool wf = s_f[w];
+#pragma unroll
+    for (int x = 0; x < V; ++x) pre[x] = wf ? s_v[w][gl][x] : pre[x] + s_v[w][gl][x];
+    pre_f = pre_f || wf;
+  }
+  T before[V];  // open before this group
+  bool before_f = __shfl_up(static_cast<int>(f), L);
+  if (lane < L) before_f = false;
+#pragma unroll
+  for (int x = 0; x < V; ++x) {
+    const T up = __shfl_up(acc[x], L);
+    before[x] = before_f ? up : (lane < L ? pre[x] : pre[x] + up);
+  }
+  before_f = before_f || pre_f;
+  if (has_head) {
+#pragma unroll
+    for (int x = 0; x < V; ++x) before[x] += lead[x];
+    if (before_f) {
+      if (jok && first_close >= 0) store_cols<T, V>(A + static_cast<int64_t>(first_close) * J + col, before);
+    } else {  // precedes the first row that starts in the chunk
+      if (jok) store_cols<T, V>(carry_vec + static_cast<int64_t>(chunk) * J + col, before);
+      if (gl == 0 && blockIdx.y == 0) carry_key[chunk] = max(first_close, -1);
+    }
+  }
+  if (g == NG - 1) {
+    if (!f)
+#pragma unroll
+      for (int x = 0; x < V; ++x) acc[x] = pre[x] + acc[x];
+    if (f || pre_f) {
+      if (jok) store_cols<T, V>(A + static_cast<int64_t>(cur) * J + col, acc);
+    } else {  // no row starts in the chunk
+      if (jok) store_cols<T, V>(carry_vec + static_cast<int64_t>(chunk) * J + col, acc);
+      if (gl == 0 && blockIdx.y == 0) carry_key[chunk] = cur;
+    }
+  }
+}
+
+// One level of carries: the same sums over 64 carries per workgroup and 32 columns, a thread adding
+// eight of them, into A; what continues a row begun in an earlier workgroup leaves as a carry again.
+// (Bound by latency: a longer walk per thread only takes longer. 48 800 carries with 32 per thread: 20 us.)
+constexpr int kCarryCols = 32, kCarryRows = 8, kCarrySpan = kBlock / kCarryCols * kCarryRows;
+template <typename T>
+__global__ __launch_bounds__(kBlock) void mttkrp_carry_kernel(int n, int J, const int32_t* __restrict__ key,
+                                                              const T* __restrict__ vec, T* __restrict__ A,
+                                                              int32_t* __restrict__ out_key, T* __restrict__ out_vec) {
+  constexpr int NG = kBlock / kCarryCols;
+  __shared__ T s_lead[NG][kCarryCols], s_tail[NG][kCarryCols];
+  __shared__ int s_first[NG], s_last[NG];
+  __shared__ bool s_head[NG];
+  const int g = threadIdx.x / kCarryCols, c = threadIdx.x % kCarryCols;
+  const int j = blockIdx.y * kCarryCols + c, jc = min(j, J - 1);
+  const int g0 = blockIdx.x * kCarrySpan + g * kCarryRows;
+  int32_t k[kCarryRows];
+  T v[kCarryRows];
+#pragma unroll
+  for (int r = 0; r < kCarryRows; ++r) {
+    const int w = min(g0 + r, n - 1);
+    k[r] = key[w];
+    v[r] = vec[static_cast<int64_t>(w) * J + jc];
+  }
+  int cur = g0 > 0 ? key[min(g0, n) - 1] : -1, first = -1;
+  bool head = false;
+  T acc = 0, lead = 0;
+#pragma unroll
+  for (int r = 0; r < kCarryRows; ++r) {
+    if (g0 + r >= n) break;
+    if (k[r] != cur) {
+      if (!head) {
+        head = true;
+        first = cur;
+        lead = acc;
+      } else if (cur >= 0 && j < J) {
+        A[static_cast<int64_t>(cur) * J + j] += acc;
+      }
+      cur = k[r];
+      acc = 0;
+    }
+    acc += v[r];
+  }
+  s_lead[g][c] = lead;
+  s_tail[g][c] = acc;
+  if (c == 0) {
+    s_head[g] = head;
+    s_first[g] = first;
+    s_last[g] = cur;
+  }
+  __syncthreads();
+  if (g > 0) return;
+  T run = 0;
+  bool seen = false;
+  for (int q = 0; q < NG; ++q) {
+    if (!s_head[q]) {
+      run += s_tail[q][c];
+      continue;
+    }
+    const T total = run + s_lead[q][c];
+    if (seen) {
+      if (s_first[q] >= 0 && j < J) A[static_cast<int64_t>(s_first[q]) * J + j] += total;
+    } else {
+      if (j < J) out_vec[static_cast<int64_t>(blockIdx.x) * J + j] = total;
+      if (j == 0) out_key[blockIdx.x] = s_first[q];
+    }
+    seen = true;
+    run = s_tail[q][c];
+  }
+  const int last = s_last[NG - 1];
+  if (seen) {
+    if (last >= 0 && j < J) A[static_cast<int64_t>(last) * J + j] += run;
+  } else {
+    if (j < J) out_vec[static_cast<int64_t>(blockIdx.x) * J + j] = run;
+    if (j == 0) out_key[blockIdx.x] = last;
+  }
+}
+
+// Adds the remaining carries to A: eight lanes for the first carry of a row and one column add up
+// all carries of the row, in double also for float data.
+constexpr int kFixLanes = 8;
+template <typename T>
+__global__ __launch_bounds__(kBlock) void mttkrp_fixup_kernel(int n, int J, const int32_t* __restrict__ key,
+                                                              const T* __restrict__ vec, T* __restrict__ A) {
+  const int64_t idx = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) / kFixLanes;
+  if (idx >= static_cast<int64_t>(n) * J) return;
+  const int w = static_cast<int>(idx / J), j = static_cast<int>(idx % J);
+  const int32_t k = key[w];
+  if (k < 0 || (w > 0 && key[w - 1] == k)) return;  // the same for all eight lanes
+  double s = 0;
+  for (int u = w + threadIdx.x % kFixLanes; u < n && key[u] == k; u += kFixLanes)
+    s += static_cast<double>(vec[static_cast<int64_t>(u) * J + j]);
+#pragma unroll
+  for (int d = 1; d < kFixLanes; d <<= 1) s += __shfl_xor(s, d);
+  if (threadIdx.x % kFixLanes == 0) {
+    T* a = A + static_cast<int64_t>(k) * J + j;
+    *a = static_cast<T>(static_cast<double>(*a) + s);
+  }
+}
+
+// ---- host ------------------------------------------------------------------
+
+struct MttkrpPlan {
+  int lanes, vec, epg, chunk;
+  int64_t n1, n2;  // chunks, workgroups of the first level of carries
+};
+
+// Lanes: the vectors of a row, up to 32 (longer rows take several passes over the entries, side by
+// side). Entries of a group: enough workgroups for six on every compute unit while a group keeps at least
+// 16 entries, which its fixed work (bounds, scan, carry) is worth, and at most 2048 entries per workgroup
+// (measured with 512 to 4096: more entries keep fewer rows of C in cache, fewer leave more carries;
+// up to 10 % apart) and 128 per group.
+static MttkrpPlan mttkrp_plan(int64_t nnz, int64_t J, int dtype) {
+  MttkrpPlan P;
+  P.vec = dtype == SPT_F64 ? kVec<double> : kVec<float>;
+  if (J < P.vec) P.vec = 1;
+  const int64_t nv = (J + P.vec - 1) / P.vec;
+  P.lanes = P.vec == 1 ? 4 : nv <= 2 ? 2 : nv <= 4 ? 4 : nv <= 8 ? 8 : nv <= 16 ? 16 : 32;
+  const int groups = kBlock / P.lanes;
+  const int64_t want = nnz / (6 * 256) / groups;
+  P.epg = static_cast<int>(std::min<int64_t>(std::max<int64_t>(want / 16 * 16, 16), std::min(128, 2048 / groups)));
+  P.chunk = P.epg * groups;
+  P.n1 = (nnz + P.chunk - 1) / P.chunk;
+  P.n2 = (P.n1 + kCarrySpan - 1) / kCarrySpan;
+  return P;
+}
+
+size_t mttkrp3_workspace(const spt_tensor* B, int32_t J) {
+  const MttkrpPlan P = mttkrp_plan(B->nvals, std::max(J, 1), B->dtype);
+  const size_t row = static_cast<size_t>(std::max(J, 1)) * (B->dtype == SPT_F64 ? 8 : 4);
+  return align_up(static_cast<size_t>(P.n1) * 4, 256) + align_up(P.n1 * row, 256) +
+         align_up(static_cast<size_t>(P.n2) * 4, 256) + align_up(P.n2 * row, 256) +
+         align_up(static_cast<size_t>(P.n1 + 1) * 12, 256) + 256;
+}
+
+template <typename T>
+static spt_status mttkrp3_typed(Format f, const spt_tensor* B, const T* Cm, const T* Dm, int J, T* A, void* ws,
+                                size_t ws_bytes, hipStream_t s) {
+  const int64_t I = B->level[0].N, nnz64 = B->nvals, size = I * J;
+  const bool csf = f == Format::CSF3;
+  const int64_t nsl = csf ? B->level[1].M : 0, nfib = csf ? B->level[2].M : 0;
+  const MttkrpPlan P = mttkrp_plan(nnz64, J, B->dtype);
+  if (nnz64 + P.chunk >= INT32_MAX || size >= ((int64_t)1 << 38) || nsl + 1 >= INT32_MAX || nfib + 1 >= INT32_MAX)
+    return fail(SPT_ERR_UNSUPPORTED, "mttkrp: tensor too large");
+  if (nnz64 > 0 && (!ws || ws_bytes < mttkrp3_workspace(B, J)))
+    return fail(SPT_ERR_WORKSPACE, "mttkrp: workspace of %zu bytes needed, %zu given", mttkrp3_workspace(B, J), ws_bytes);
+  const int nnz = (int)nnz64, n1 = (int)P.n1, n2 = (int)P.n2;
+  Workspace W(ws, ws_bytes);
+  int32_t *key1 = nullptr, *key2 = nullptr, *bounds = nullptr;
+  T *vec1 = nullptr, *vec2 = nullptr;
+  if (nnz > 0) {
+    key1 = W.take<int32_t>(n1);
+    vec1 = W.take<T>((size_t)n1 * J);
+    key2 = W.take<int32_t>(n2);
+    vec2 = W.take<T>((size_t)n2 * J);
+    bounds = W.take<int32_t>(3 * ((size_t)n1 + 1));
+  }
+  const int fill = (int)((size + kBlock * kVec<T> - 1) / (kBlock * kVec<T>));
+  const int search = csf && nnz > 0 ? ((n1 + 1) * kBoundLanes + kBlock - 1) / kBlock : 0;
+  if (fill + search > 0) {
+    hipLaunchKernelGGL(mttkrp_prepare_kernel<T>, dim3(fill + search), dim3(kBlock), 0, s, A, size, fill, n1, P.chunk,
+                       (int)nsl, (int)nfib, B->level[1].pos, B->level[2].pos, bounds);
+    SPT_CHECK_LAUNCH("mttkrp prepare");
+  }
+  if (nnz == 0 || J == 0) return SPT_OK;
+  const CsfLevels up{B->level[0].crd, B->level[1].pos, B->level[1].crd, B->level[2].pos, bounds};
+  const int tiles = ((J + P.vec - 1) / P.vec + P.lanes - 1) / P.lanes;
+  const size_t lds = csf ? (size_t)P.chunk * 8 + 2 * (size_t)((P.chunk + 31) / 32) * 6 : 0;
+#define SPT_MTTKRP(L_, V_)                                                                                           \
+  if (csf)                                                                                                           \
+    hipLaunchKernelGGL((mttkrp_rows_kernel<T, L_, V_, true>), dim3(n1, tiles), dim3(kBlock), lds, s, nnz, J, P.epg,  \
+                       nullptr, nullptr, B->level[2].crd, static_cast<const T*>(B->vals), Cm, Dm, up, A, key1, vec1); \
+  else                                                                                                               \
+    hipLaunchKernelGGL((mttkrp_rows_kernel<T, L_, V_, false>), dim3(n1, tiles), dim3(kBlock), 0, s, nnz, J, P.epg,   \
+                       B->level[0].crd, B->level[1].crd, B->level[2].crd, static_cast<const T*>(B->vals), Cm, Dm, up, \
+                       A, key1, vec1)
+  if (P.vec == 1) { SPT_MTTKRP(4, 1); }
+  else if (P.lanes == 2) { SPT_MTTKRP(2, kVec<T>); }
+  else if (P.lanes == 4) { SPT_MTTKRP(4, kVec<T>); }
+  else if (P.lanes == 8) { SPT_MTTKRP(8, kVec<T>); }
+  else if (P.lanes == 16) { SPT_MTTKRP(16, kVec<T>); }
+  else { SPT_MTTKRP(32, kVec<T>); }
+#undef SPT_MTTKRP
+  SPT_CHECK_LAUNCH("mttkrp rows");
+  hipLaunchKernelGGL(mttkrp_carry_kernel<T>, dim3(n2, (J + kCarryCols - 1) / kCarryCols), dim3(kBlock), 0, s, n1, J, key1,
+                     vec1, A, key2, vec2);
+  SPT_CHECK_LAUNCH("mttkrp carries");
+  if (n2 == 1) return SPT_OK;  // nothing precedes the only workgroup
+  hipLaunchKernelGGL(mttkrp_fixup_kernel<T>, dim3((unsigned)(((int64_t)n2 * J * kFixLanes + kBlock - 1) / kBlock)),
+                     dim3(kBlock), 0, s, n2, J, key2, vec2, A);
+  SPT_CHECK_LAUNCH("mttkrp fixup");
+  return SPT_OK;
+}
+
+spt_status mttkrp_dispatch(Format f, const spt_tensor* B, const void* C, const void* D, int32_t J,
+                           void* A_out, void* ws, size_t ws_bytes, hipStream_t s) {
+  for (int k = 0; k < 3; ++k)
+    if (!(B->level[k].flags & SPT_ORDERED))
+      return fail(SPT_ERR_UNSUPPORTED, "mttkrp: every level of B must be ordered");
+  if (B->dtype == SPT_F64)
+    return mttkrp3_typed<double>(f, B, static_cast<const double*>(C), static_cast<const double*>(D), J,
+                                 static_cast<double*>(A_out), ws, ws_bytes, s);
+  return mttkrp3_typed<float>(f, B, static_cast<const float*>(C), static_cast<const float*>(D), J,
+                              static_cast<float*>(A_out), ws, ws_bytes, s);
+}
+
+}  // namespace spt

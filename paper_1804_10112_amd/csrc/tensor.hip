@@ -1,10 +1,9 @@
-// 3rd-order kernels (paper Section 5.3): TTV A_ij = sum_k B_ijk c_k and
-// MTTKRP A_ij = sum_kl B_ikl C_kj D_lj on ordered COO and on CSF, gfx950.
+// TTV A_ij = sum_k B_ijk c_k (paper Section 5.3) on ordered COO and on CSF, TTM and SpDM, gfx950.
 //
 // Both reduce runs of consecutive stored entries that share leading
 // coordinates -- the GPU form of the paper's deduplication / iterator chaining
-// over ordered non-unique levels (Section 4.3): (i,j) fibers for TTV, i slices
-// for MTTKRP. Work is split evenly over stored entries; a run cut by a split
+// over ordered non-unique levels (Section 4.3): (i,j) fibers for TTV, rows
+// for SpDM. Work is split evenly over stored entries; a run cut by a split
 // leaves a carry that a follow-up kernel adds in a fixed order (no atomics).
 #include <algorithm>
 
@@ -273,25 +272,22 @@ static spt_status ttv_coo_typed(const spt_tensor* B, const T* c, int32_t* out_i,
   return SPT_OK;
 }
 
-// ================================================================ MTTKRP
+// ================================================================ SpDM
 //
+// A_ij = sum_k B_ik C_kj, B an ordered COO matrix (or the entries of a tensor under fibre numbers, TTM).
 // G lanes (32 or 64) work on one stored entry at a time, lane gl owning output
 // column jt*G + gl; a workgroup has 256/G such groups, each walking kEPG
 // consecutive entries and keeping the running row sum in a register. Entry
 // coordinates are loaded G at a time (coalesced) and broadcast with shuffles;
-// the factor rows C[k,:], D[l,:] are gathered as contiguous G-wide rows.
+// the factor rows C[k,:] are gathered as contiguous G-wide rows.
 // LEVEL2 = the same reduction applied to the (key, vector) carries of level 1.
-// CSF    = i and k come from the upper levels (expanded into LDS per chunk) and
-//          the product with C[k,:] is applied once per fiber piece (factored
-//          form, Section 5.3 / CSF being the more efficient format).
-// entries walked by one group of lanes, per mode: the CSF pre-phase is amortised over a
-// longer walk; the carry level is small and wants parallelism instead
-enum { MT_COO = 0, MT_LEVEL2 = 1, MT_CSF = 2, MT_SPDM = 3 };
-template <int MODE> struct Epg { static constexpr int value = MODE == 2 ? 256 : (MODE == 1 ? 32 : 128); };
+enum { MT_LEVEL2 = 1, MT_SPDM = 3 };
+// entries walked by one group of lanes: the carry level is small and wants parallelism instead
+template <int MODE> struct Epg { static constexpr int value = MODE == MT_LEVEL2 ? 32 : 128; };
 constexpr int kU = 8;  // entries whose factor rows are in flight together
 
 template <typename T, int G>
-struct MttkrpShared {
+struct SpdmShared {
   T lead[kBlock / G][G];
   T tail[kBlock / G][G];
   int has_head[kBlock / G];
@@ -300,31 +296,6 @@ struct MttkrpShared {
   int empty[kBlock / G];
 };
 
-
-// First r in [0, n] with a[r] >= target (a ascending, n entries).
-__device__ __forceinline__ int first_at_or_after(const int32_t* __restrict__ a, int n, int target) {
-  int lo = 0, hi = n;
-  while (lo < hi) {
-    const int mid = lo + ((hi - lo) >> 1);
-    if (a[mid] < target) lo = mid + 1; else hi = mid;
-  }
-  return lo;
-}
-
-// CSF: for chunk boundary c (entries from c * chunk on), out[3c] = first fiber that starts at or
-// after it, out[3c+1] = first slice that starts at or after that fiber, out[3c+2] = the same as
-// the end of the chunk before (all slices once the fibers are used up). Boundary nchunks = the end.
-__global__ __launch_bounds__(kBlock) void csf_chunk_bounds_kernel(
-    int nchunks, int chunk, int nslices, int nfibers, const int32_t* __restrict__ pos1,
-    const int32_t* __restrict__ pos2, int32_t* __restrict__ out) {
-  const int c = blockIdx.x * kBlock + threadIdx.x;
-  if (c > nchunks) return;
-  const int f = c == nchunks ? nfibers : first_at_or_after(pos2, nfibers + 1, c * chunk);
-  const int sl = first_at_or_after(pos1, nslices + 1, f);
-  out[3 * c] = f;
-  out[3 * c + 1] = sl;
-  out[3 * c + 2] = f >= nfibers ? nslices : sl;
-}
 
 // Broadcast of lane (addr / 4)'s value through the LDS crossbar.
 __device__ __forceinline__ int32_t bperm(int addr, int32_t v) { return __builtin_amdgcn_ds_bpermute(addr, v); }
@@ -337,31 +308,24 @@ __device__ __forceinline__ double bperm(int addr, double v) {
   return __hiloint2double(hi, lo);
 }
 
-// FAST: the factor matrices are addressed with 32-bit byte offsets formed by one 24-bit
+// FAST: the factor matrix is addressed with 32-bit byte offsets formed by one 24-bit
 // multiply-add (host-checked: dimensions and J * sizeof(T) below 2^23, matrices below 4 GiB),
 // and no load of the batch sits behind a branch: a batch slot beyond the group's entries
 // repeats the last entry, a lane beyond column J reads column J - 1 (neither is ever stored).
 // The 64-bit multiply-adds and the per-entry branches of the general path cost more vector
 // instructions than the arithmetic itself.
 template <typename T, int G, int MODE, bool FAST>
-__global__ __launch_bounds__(kBlock) void mttkrp_kernel(
+__global__ __launch_bounds__(kBlock) void spdm_rows_kernel(
     int n, int J,
-    // COO: ci/ck/cl; CSF: cl only (crd of level 2) plus the upper levels below
-    const int32_t* __restrict__ ci, const int32_t* __restrict__ ck, const int32_t* __restrict__ cl,
-    const T* __restrict__ vals, const T* __restrict__ Cm, const T* __restrict__ Dm,
-    // CSF upper levels
-    const int32_t* __restrict__ crd0, const int32_t* __restrict__ pos1, const int32_t* __restrict__ crd1,
-    const int32_t* __restrict__ pos2, int nslices, int nfibers,
+    const int32_t* __restrict__ ci, const int32_t* __restrict__ ck, const T* __restrict__ vals,
+    const T* __restrict__ Cm,
     // LEVEL2 input
     const int32_t* __restrict__ in_key, const T* __restrict__ in_vec,
     T* __restrict__ A, int32_t* __restrict__ carry_key, T* __restrict__ carry_vec) {
   constexpr int NG = kBlock / G;
   constexpr int kEPG = Epg<MODE>::value;
   constexpr int CHUNK = NG * kEPG;
-  __shared__ MttkrpShared<T, G> sh;
-  __shared__ int32_t s_i[MODE == MT_CSF ? CHUNK : 1];
-  __shared__ int32_t s_k[MODE == MT_CSF ? CHUNK : 1];
-  __shared__ int s_mark0;
+  __shared__ SpdmShared<T, G> sh;
   // SpDM closes a row every few entries. A store issued between two batches of gathers
   // makes the next batch wait for the store's acknowledgement (loads and stores retire
   // through one counter), so closed rows are parked in LDS and written out in bursts.
@@ -383,91 +347,26 @@ __global__ __launch_bounds__(kBlock) void mttkrp_kernel(
   const int chunk_base = chunk * CHUNK;
   const int chunk_end = min(chunk_base + CHUNK, n);
 
-  if (MODE == MT_CSF) {
-    // Expand the coordinates of levels 0 and 1 for the entries of this chunk:
-    // mark the first entry of every fiber / slice that starts inside the chunk,
-    // then let every entry take the last mark at or before it.
-    // fibers [f_lo, f_hi) and slices [s_lo, s_hi) start inside the chunk; found beforehand, one
-    // bisection per chunk boundary (csf_chunk_bounds_kernel), passed through in_key
-    const int f_lo = in_key[3 * chunk], f_hi = in_key[3 * chunk + 3];
-    for (int e = tid; e < CHUNK; e += kBlock) {
-      s_i[e] = -1;
-      s_k[e] = -1;
-    }
-    __syncthreads();
-    for (int f = f_lo + tid; f < f_hi; f += kBlock) {
-      const int a = pos2[f];
-      if (pos2[f + 1] > a) s_k[a - chunk_base] = crd1[f];
-    }
-    __syncthreads();
-    const int s_lo = in_key[3 * chunk + 1], s_hi = in_key[3 * chunk + 5];
-    // a slice is marked at its first stored entry, whichever of its fibers holds it (a
-    // compressed level may hold empty segments: leading fibers of a slice can be empty)
-    for (int sl = s_lo + tid; sl < s_hi; sl += kBlock) {
-      const int a = pos2[pos1[sl]];
-      if (pos2[pos1[sl + 1]] > a && a < chunk_base + CHUNK) s_i[a - chunk_base] = crd0[sl];
-    }
-    __syncthreads();
-    // propagate marks forward: 256 threads, CHUNK/256 consecutive entries each
-    constexpr int PER = CHUNK / kBlock;
-    int li = -1, lk = -1;
-    if (tid == 0) s_mark0 = s_i[0] >= 0;  // the chunk starts on a slice head
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int e = tid * PER + q;
-      if (s_i[e] >= 0) li = s_i[e];
-      if (s_k[e] >= 0) lk = s_k[e];
-    }
-    // exclusive "last mark" over threads; reuse the segmented scan's key lane
-    __shared__ SegScanStorage<int> s_sc;
-    SegSum<int> a = block_seg_exclusive_scan<int>(SegSum<int>{li >= 0, 0, li}, s_sc);
-    __syncthreads();
-    SegSum<int> b = block_seg_exclusive_scan<int>(SegSum<int>{lk >= 0, 0, lk}, s_sc);
-    // carry-in coordinates of the chunk: the slice / fiber cut by its start
-    int run_i = a.f ? a.k : (s_lo > 0 ? crd0[s_lo - 1] : -1);
-    int run_k = b.f ? b.k : (f_lo > 0 ? crd1[f_lo - 1] : -1);
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int e = tid * PER + q;
-      if (s_i[e] >= 0) run_i = s_i[e];
-      else s_i[e] = run_i;
-      if (s_k[e] >= 0) run_k = s_k[e];
-      else s_k[e] = run_k;
-    }
-    __syncthreads();
-  }
-
   // ---- group walk
   const int g0 = chunk_base + g * kEPG;
   const int g1 = min(g0 + kEPG, chunk_end);
-  T acc = 0, lead = 0, t = 0, c_cur = 0;
+  T acc = 0, lead = 0;
   int has_head = 0, first_close = -1;
-  int cur = -1, cur_k = -1;
-  // cur = slice coordinate of the entry just before this group's first entry
-  // (-1: there is none; -2: unknown but different, the group starts on a head)
+  int cur = -1;
+  // cur = row of the entry just before this group's first entry (-1: there is none)
   if (g0 < g1) {
-    if (MODE == MT_COO || MODE == MT_SPDM) cur = g0 > 0 ? ci[g0 - 1] : -1;
+    if (MODE == MT_SPDM) cur = g0 > 0 ? ci[g0 - 1] : -1;
     if (MODE == MT_LEVEL2) cur = g0 > 0 ? in_key[g0 - 1] : -1;
-    if (MODE == MT_CSF) {
-      if (g0 > chunk_base) cur = s_i[g0 - 1 - chunk_base];
-      else cur = chunk_base == 0 ? -1 : (s_mark0 ? -2 : s_i[0]);
-    }
   }
 
   for (int b0 = g0; b0 < g1; b0 += G) {
     const int p_l = b0 + gl;
-    int32_t ri = 0, rk = 0, rl = 0;
+    int32_t ri = 0, rk = 0;
     T rv = 0;
     if (p_l < g1) {
-      if (MODE == MT_COO || MODE == MT_SPDM) {
+      if (MODE == MT_SPDM) {
         ri = ldg_stream(ci + p_l);
         rk = ldg_stream(ck + p_l);
-        if (MODE == MT_COO) rl = ldg_stream(cl + p_l);
-        rv = ldg_stream(vals + p_l);
-      } else if (MODE == MT_CSF) {
-        ri = s_i[p_l - chunk_base];
-        rk = s_k[p_l - chunk_base];
-        rl = ldg_stream(cl + p_l);
         rv = ldg_stream(vals + p_l);
       } else {
         ri = in_key[p_l];
@@ -479,32 +378,18 @@ __global__ __launch_bounds__(kBlock) void mttkrp_kernel(
     // then run the segment logic over the batch in order.
     for (int s0 = 0; s0 < cntb; s0 += kU) {
       int ii[kU];
-      T fa[kU], fb[kU], vv[kU];
-      bool fh[kU];
-      int pi = cur, pk = cur_k;
+      T fa[kU], vv[kU];
 #pragma unroll
       for (int u = 0; u < kU; ++u) {
         const int sidx = s0 + u;  // < G because kU divides G
         const bool live = sidx < cntb;
-        fh[u] = false;
         vv[u] = T(1);
-        fb[u] = T(1);
         if (FAST && MODE != MT_LEVEL2) {
           const int addr = half_base + 4 * min(sidx, cntb - 1);
           ii[u] = bperm(addr, ri);
           const int k = bperm(addr, rk);
           vv[u] = bperm(addr, rv);
-          const int l = MODE != MT_SPDM ? bperm(addr, rl) : 0;
           fa[u] = *reinterpret_cast<const T*>(reinterpret_cast<const char*>(Cm) + (__umul24(k, jbytes) + joff));
-          if (MODE != MT_SPDM)
-            fb[u] = *reinterpret_cast<const T*>(reinterpret_cast<const char*>(Dm) + (__umul24(l, jbytes) + joff));
-          if (MODE == MT_CSF) {  // C[k,:] is used where a new (i,k) fiber piece starts
-            fh[u] = live && (ii[u] != pi || k != pk);
-            if (live) {
-              pi = ii[u];
-              pk = k;
-            }
-          }
           continue;
         }
         ii[u] = __shfl(ri, sidx, G);
@@ -512,31 +397,14 @@ __global__ __launch_bounds__(kBlock) void mttkrp_kernel(
           fa[u] = (live && jok) ? in_vec[(int64_t)(b0 + sidx) * J + j] : T(0);
         } else {
           const int k = __shfl(rk, sidx, G);
-          const int l = __shfl(rl, sidx, G);
           vv[u] = __shfl(rv, sidx, G);
-          if (MODE != MT_SPDM) fb[u] = (live && jok) ? Dm[(int64_t)l * J + j] : T(0);
-          if (MODE == MT_COO || MODE == MT_SPDM) {
-            fa[u] = (live && jok) ? Cm[(int64_t)k * J + j] : T(0);
-          } else {  // CSF: C[k,:] only where a new (i,k) fiber piece starts
-            fh[u] = live && (ii[u] != pi || k != pk);
-            fa[u] = (fh[u] && jok) ? Cm[(int64_t)k * J + j] : T(0);
-            if (live) {
-              pi = ii[u];
-              pk = k;
-            }
-          }
+          fa[u] = (live && jok) ? Cm[(int64_t)k * J + j] : T(0);
         }
       }
-      cur_k = pk;
 #pragma unroll
       for (int u = 0; u < kU; ++u) {
         if (s0 + u < cntb) {
           const int i = ii[u];
-          if (MODE == MT_CSF && fh[u]) {  // factored form: close the previous fiber piece
-            acc += c_cur * t;
-            t = 0;
-            c_cur = fa[u];
-          }
           if (i != cur) {
             if (!has_head) {
               lead = acc;
@@ -555,9 +423,7 @@ __global__ __launch_bounds__(kBlock) void mttkrp_kernel(
             acc = 0;
             cur = i;
           }
-          if (MODE == MT_CSF) t += vv[u] * fb[u];
-          else if (MODE == MT_COO) acc += vv[u] * fa[u] * fb[u];
-          else if (MODE == MT_SPDM) acc += vv[u] * fa[u];
+          if (MODE == MT_SPDM) acc += vv[u] * fa[u];
           else acc += fa[u];
         }
       }
@@ -572,7 +438,6 @@ __global__ __launch_bounds__(kBlock) void mttkrp_kernel(
     for (int r = 0; r < nbuf; ++r)
       if (jok) __builtin_nontemporal_store(s_rowv[g][r][gl], &A[(int64_t)s_rowk[g][r] * J + j]);
   }
-  if (MODE == MT_CSF) acc += c_cur * t;
 
   sh.lead[g][gl] = lead;
   sh.tail[g][gl] = acc;
@@ -641,47 +506,40 @@ __global__ __launch_bounds__(kBlock) void vec_carry_fixup_kernel(int n, int J,
   A[(int64_t)kk * J + j] = (T)((double)A[(int64_t)kk * J + j] + s);
 }
 
-static int mttkrp_group(int J) { return J <= 32 ? 32 : 64; }
-static int mttkrp_chunk(int J, int mode) {
-  const int epg = mode == MT_CSF ? Epg<MT_CSF>::value : (mode == MT_LEVEL2 ? Epg<MT_LEVEL2>::value : Epg<MT_COO>::value);
-  return (kBlock / mttkrp_group(J)) * epg;
+static int spdm_group(int J) { return J <= 32 ? 32 : 64; }
+static int spdm_chunk(int J, int mode) {
+  return (kBlock / spdm_group(J)) * (mode == MT_LEVEL2 ? Epg<MT_LEVEL2>::value : Epg<MT_SPDM>::value);
 }
 
-size_t mttkrp_workspace(Format, const spt_tensor* B, int32_t J) {
+size_t spdm_workspace(const spt_tensor* B, int32_t J) {
   if (J < 1) J = 1;
-  const int64_t chunk = mttkrp_chunk(J, MT_COO);  // the smaller level-1 chunk of the two formats
-  const int64_t chunk2 = mttkrp_chunk(J, MT_LEVEL2);
+  const int64_t chunk = spdm_chunk(J, MT_SPDM), chunk2 = spdm_chunk(J, MT_LEVEL2);
   const int64_t n1 = (B->nvals + chunk - 1) / chunk;
   const int64_t n2 = (n1 + chunk2 - 1) / chunk2;
   return align_up((size_t)n1 * 4, 256) + align_up((size_t)n1 * J * 8, 256) +
-         align_up((size_t)n2 * 4, 256) + align_up((size_t)n2 * J * 8, 256) +
-         align_up((size_t)(n1 + 1) * 12, 256) + 256;
+         align_up((size_t)n2 * 4, 256) + align_up((size_t)n2 * J * 8, 256) + 256;
 }
 
-// rows_override / cols_override (SpDM mode only): row and column index per stored entry taken
+// rows_override / cols_override: row and column index per stored entry taken
 // from these arrays instead of B's first two levels, and no zero fill of A (every output row
 // then has at least one entry, and rows with entries are stored, not accumulated).
 template <typename T, int G, bool FAST>
-static spt_status mttkrp_launch(Format f, const spt_tensor* B, const T* Cm, const T* Dm, int J,
-                                T* A, void* ws, size_t ws_bytes, hipStream_t s,
-                                const int32_t* rows_override = nullptr,
-                                const int32_t* cols_override = nullptr) {
-  const int CHUNK = mttkrp_chunk(J, f == Format::CSF3 ? MT_CSF : MT_COO);
-  const int CHUNK2 = mttkrp_chunk(J, MT_LEVEL2);
+static spt_status spdm_launch(const spt_tensor* B, const T* Cm, int J, T* A, void* ws, size_t ws_bytes,
+                              hipStream_t s, const int32_t* rows_override, const int32_t* cols_override) {
+  const int CHUNK = spdm_chunk(J, MT_SPDM), CHUNK2 = spdm_chunk(J, MT_LEVEL2);
   const int64_t I = B->level[0].N;
   const int64_t nnz64 = B->nvals;
   if (nnz64 + CHUNK >= INT32_MAX || I * J >= ((int64_t)1 << 38))
-    return fail(SPT_ERR_UNSUPPORTED, "mttkrp: tensor too large");
+    return fail(SPT_ERR_UNSUPPORTED, "spdm: matrix too large");
   if (I * J > 0 && !rows_override) {
     hipLaunchKernelGGL(fill_t_kernel<T>, dim3((unsigned)((I * J + kBlock - 1) / kBlock)),
                        dim3(kBlock), 0, s, A, I * J, T(0));
-    SPT_CHECK_LAUNCH("mttkrp fill");
+    SPT_CHECK_LAUNCH("spdm fill");
   }
   const int nnz = (int)nnz64;
   if (nnz == 0) return SPT_OK;
-  if (!ws || ws_bytes < mttkrp_workspace(f, B, J))
-    return fail(SPT_ERR_WORKSPACE, "mttkrp: workspace of %zu bytes needed, %zu given",
-                mttkrp_workspace(f, B, J), ws_bytes);
+  if (!ws || ws_bytes < spdm_workspace(B, J))
+    return fail(SPT_ERR_WORKSPACE, "spdm: workspace of %zu bytes needed, %zu given", spdm_workspace(B, J), ws_bytes);
   const int n1 = (nnz + CHUNK - 1) / CHUNK;
   const int n2 = (n1 + CHUNK2 - 1) / CHUNK2;
   Workspace W(ws, ws_bytes);
@@ -691,66 +549,37 @@ static spt_status mttkrp_launch(Format f, const spt_tensor* B, const T* Cm, cons
   T* vec2 = W.take<T>((size_t)n2 * J);
   const unsigned jt = (unsigned)((J + G - 1) / G);
   const spt_level* L = B->level;
-  if (f == Format::COO2) {  // SpDM: the same slice reduction with one dense factor
-    hipLaunchKernelGGL((mttkrp_kernel<T, G, MT_SPDM, FAST>), dim3(n1, jt), dim3(kBlock), 0, s, nnz, J,
-                       rows_override ? rows_override : L[0].crd,
-                       cols_override ? cols_override : L[1].crd, nullptr,
-                       static_cast<const T*>(B->vals), Cm, nullptr, nullptr, nullptr, nullptr, nullptr,
-                       0, 0, nullptr, nullptr, A, key1, vec1);
-  } else if (f == Format::COO3) {
-    hipLaunchKernelGGL((mttkrp_kernel<T, G, MT_COO, FAST>), dim3(n1, jt), dim3(kBlock), 0, s, nnz, J,
-                       L[0].crd, L[1].crd, L[2].crd, static_cast<const T*>(B->vals), Cm, Dm, nullptr,
-                       nullptr, nullptr, nullptr, 0, 0, nullptr, nullptr, A, key1, vec1);
-  } else {
-    const int64_t nsl = L[1].M, nfib = L[2].M;
-    if (nsl + 1 >= INT32_MAX || nfib + 1 >= INT32_MAX)
-      return fail(SPT_ERR_UNSUPPORTED, "mttkrp: tensor too large");
-    int32_t* bounds = W.take<int32_t>(3 * ((size_t)n1 + 1));
-    hipLaunchKernelGGL(csf_chunk_bounds_kernel, dim3((n1 + 1 + kBlock - 1) / kBlock), dim3(kBlock), 0, s,
-                       n1, CHUNK, (int)nsl, (int)nfib, L[1].pos, L[2].pos, bounds);
-    SPT_CHECK_LAUNCH("csf chunk bounds");
-    hipLaunchKernelGGL((mttkrp_kernel<T, G, MT_CSF, FAST>), dim3(n1, jt), dim3(kBlock), 0, s, nnz, J,
-                       nullptr, nullptr, L[2].crd, static_cast<const T*>(B->vals), Cm, Dm, L[0].crd,
-                       L[1].pos, L[1].crd, L[2].pos, (int)nsl, (int)nfib, bounds, nullptr, A, key1,
-                       vec1);
-  }
-  SPT_CHECK_LAUNCH("mttkrp");
-  hipLaunchKernelGGL((mttkrp_kernel<T, G, MT_LEVEL2, false>), dim3(n2, jt), dim3(kBlock), 0, s, n1, J,
-                     nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-                     nullptr, 0, 0, key1, vec1, A, key2, vec2);
-  SPT_CHECK_LAUNCH("mttkrp level 2");
+  hipLaunchKernelGGL((spdm_rows_kernel<T, G, MT_SPDM, FAST>), dim3(n1, jt), dim3(kBlock), 0, s, nnz, J,
+                     rows_override ? rows_override : L[0].crd, cols_override ? cols_override : L[1].crd,
+                     static_cast<const T*>(B->vals), Cm, nullptr, nullptr, A, key1, vec1);
+  SPT_CHECK_LAUNCH("spdm");
+  hipLaunchKernelGGL((spdm_rows_kernel<T, G, MT_LEVEL2, false>), dim3(n2, jt), dim3(kBlock), 0, s, n1, J,
+                     nullptr, nullptr, nullptr, nullptr, key1, vec1, A, key2, vec2);
+  SPT_CHECK_LAUNCH("spdm level 2");
   const int64_t tot = (int64_t)n2 * J;
   hipLaunchKernelGGL(vec_carry_fixup_kernel<T>, dim3((unsigned)((tot + kBlock - 1) / kBlock)),
                      dim3(kBlock), 0, s, n2, J, key2, vec2, A);
-  SPT_CHECK_LAUNCH("mttkrp fixup");
+  SPT_CHECK_LAUNCH("spdm fixup");
   return SPT_OK;
 }
 
 template <typename T>
-static spt_status mttkrp_typed(Format f, const spt_tensor* B, const void* C, const void* D, int J,
-                               void* A, void* ws, size_t ws_bytes, hipStream_t s,
-                               const int32_t* rows_override = nullptr,
-                               const int32_t* cols_override = nullptr) {
+static spt_status spdm_typed(const spt_tensor* B, const void* C, int J, void* A, void* ws, size_t ws_bytes,
+                             hipStream_t s, const int32_t* rows_override = nullptr,
+                             const int32_t* cols_override = nullptr) {
   const T* Cm = static_cast<const T*>(C);
-  const T* Dm = static_cast<const T*>(D);
   // 32-bit factor addressing: every coordinate and the row size below 2^23 (one 24-bit multiply),
-  // every factor matrix below 4 GiB
+  // the factor matrix below 4 GiB
   int64_t big = 0;  // the largest dimension bounds every coordinate that indexes a factor row
   for (int k = 0; k < B->nlevels; ++k) big = std::max(big, B->level[k].N);
   const int64_t rowb = (int64_t)J * (int64_t)sizeof(T);
   const bool fast = big < (1 << 23) && rowb < (1 << 23) && big * rowb < ((int64_t)1 << 32);
-  if (mttkrp_group(J) == 32) {
-    if (fast)
-      return mttkrp_launch<T, 32, true>(f, B, Cm, Dm, J, static_cast<T*>(A), ws, ws_bytes, s, rows_override,
-                                        cols_override);
-    return mttkrp_launch<T, 32, false>(f, B, Cm, Dm, J, static_cast<T*>(A), ws, ws_bytes, s, rows_override,
-                                       cols_override);
-  }
-  if (fast)
-    return mttkrp_launch<T, 64, true>(f, B, Cm, Dm, J, static_cast<T*>(A), ws, ws_bytes, s, rows_override,
-                                      cols_override);
-  return mttkrp_launch<T, 64, false>(f, B, Cm, Dm, J, static_cast<T*>(A), ws, ws_bytes, s, rows_override,
-                                     cols_override);
+  T* out = static_cast<T*>(A);
+  if (spdm_group(J) == 32)
+    return fast ? spdm_launch<T, 32, true>(B, Cm, J, out, ws, ws_bytes, s, rows_override, cols_override)
+                : spdm_launch<T, 32, false>(B, Cm, J, out, ws, ws_bytes, s, rows_override, cols_override);
+  return fast ? spdm_launch<T, 64, true>(B, Cm, J, out, ws, ws_bytes, s, rows_override, cols_override)
+              : spdm_launch<T, 64, false>(B, Cm, J, out, ws, ws_bytes, s, rows_override, cols_override);
 }
 
 // SpDM A = B C (Section 5.2, Figure 11): B an ordered COO matrix, C and A dense row-major.
@@ -758,18 +587,8 @@ spt_status spdm_dispatch(const spt_tensor* B, const void* C, int32_t J, void* A_
                          size_t ws_bytes, hipStream_t s) {
   if (!(B->level[0].flags & SPT_ORDERED))
     return fail(SPT_ERR_UNSUPPORTED, "spdm: the row level of B must be ordered");
-  if (B->dtype == SPT_F64)
-    return mttkrp_typed<double>(Format::COO2, B, C, nullptr, J, A_out, ws, ws_bytes, s);
-  return mttkrp_typed<float>(Format::COO2, B, C, nullptr, J, A_out, ws, ws_bytes, s);
-}
-
-spt_status mttkrp_dispatch(Format f, const spt_tensor* B, const void* C, const void* D, int32_t J,
-                           void* A_out, void* ws, size_t ws_bytes, hipStream_t s) {
-  for (int k = 0; k < 3; ++k)
-    if (!(B->level[k].flags & SPT_ORDERED))
-      return fail(SPT_ERR_UNSUPPORTED, "mttkrp: every level of B must be ordered");
-  if (B->dtype == SPT_F64) return mttkrp_typed<double>(f, B, C, D, J, A_out, ws, ws_bytes, s);
-  return mttkrp_typed<float>(f, B, C, D, J, A_out, ws, ws_bytes, s);
+  if (B->dtype == SPT_F64) return spdm_typed<double>(B, C, J, A_out, ws, ws_bytes, s);
+  return spdm_typed<float>(B, C, J, A_out, ws, ws_bytes, s);
 }
 
 // ================================================================ TTV dispatch
@@ -894,7 +713,7 @@ size_t ttm_workspace(Format f, const spt_tensor* B, int32_t K) {
   if (K < 1) K = 1;
   const int64_t nnz = B->nvals, L = B->level[2].N;
   size_t n = align_up((size_t)nnz * 4, 256) + align_up((size_t)L * K * 8, 256) +
-             mttkrp_workspace(Format::COO2, B, K);
+             spdm_workspace(B, K);
   if (f == Format::COO3) n += ttv_coo_workspace(nnz);
   return n + 256;
 }
@@ -958,7 +777,7 @@ static spt_status ttm_typed(Format f, const spt_tensor* B, const T* C, int K, in
                      dim3(kBlock), 0, s, K, L, C, Ct);
   SPT_CHECK_LAUNCH("ttm transpose");
   void* rest = static_cast<char*>(ws) + W.used;
-  return mttkrp_typed<T>(Format::COO2, B, Ct, nullptr, K, out_v, rest, ws_bytes - W.used, s, fid,
+  return spdm_typed<T>(B, Ct, K, out_v, rest, ws_bytes - W.used, s, fid,
                          B->level[2].crd);
 }
 

@@ -91,6 +91,24 @@ def test_mttkrp_sizes(nnz):
     _check_mttkrp(coo, csf, Cm, Dm, f"mttkrp nnz={nnz}")
 
 
+@pytest.mark.parametrize("dtype,J,nnz", [
+    (np.float32, 3, 70_000), (np.float32, 8, 1_700_000), (np.float32, 37, 400_000), (np.float64, 2, 900_000),
+    (np.float64, 16, 900_001), (np.float64, 65, 200_003)])
+def test_mttkrp_groups_of_lanes_and_rows_across_many_chunks(dtype, J, nnz):
+    """Every number of lanes per entry, groups of more than 16 entries, rows as long as many chunks
+    (two levels of carries) next to rows of one entry, J no multiple of a lane's columns."""
+    dims = (5000, 900, 1100)
+    rng = np.random.default_rng(nnz)
+    rows = np.concatenate([np.full(nnz * 2 // 5, 3), np.full(nnz // 5, 4700), rng.integers(0, 5000, nnz * 2 // 5)])
+    key = np.unique((rows.astype(np.int64) * 900 + rng.integers(0, 900, len(rows))) * 1100
+                    + rng.integers(0, 1100, len(rows)))
+    ci, ck, cl = (key // (900 * 1100)).astype(np.int32), (key // 1100 % 900).astype(np.int32), (key % 1100).astype(np.int32)
+    v = rng.uniform(0, 1, len(key)).astype(dtype)
+    coo, csf = wl.coo3_spec(dims, ci, ck, cl, v), wl.csf3_from_sorted_coo(dims, ci, ck, cl, v)
+    Cm, Dm = rng.uniform(0, 1, (900, J)).astype(dtype), rng.uniform(0, 1, (1100, J)).astype(dtype)
+    _check_mttkrp(coo, csf, Cm, Dm, f"mttkrp J={J} nnz={len(key)}")
+
+
 def test_mttkrp_degenerate_and_exact():
     rng = np.random.default_rng(1)
     # one slice holds everything (crosses many chunks and both carry levels)

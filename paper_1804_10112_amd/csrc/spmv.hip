@@ -12,6 +12,7 @@
 //    rows in consecutive lanes.
 #include <algorithm>
 
+#include "carry.hpp"
 #include "common.hpp"
 #include "segreduce.hpp"
 #include "wavescan.hpp"
@@ -823,6 +824,98 @@ __global__ __launch_bounds__(kWave) void coo_small_spmv_kernel(int nnz, int nrow
   if (lane == 0) y[open_row] = sum;
 }
 
+// Ordered COO: one wave per 256 consecutive entries (four per lane, 16-byte loads). The sum
+// of a row goes to y from the piece that holds its first entry; what precedes a piece's first row
+// start leaves as a carry. ZERO: rows without entries are zeroed by the thread that sees the gap.
+// Bound by launches and latency for few entries (200 000 entries, fp64, with a workgroup per 2048
+// entries, a fill and a serial fixup: 10.1 us), by the gathers of x and the streams for many.
+template <typename T, bool ZERO>
+__global__ __launch_bounds__(kBlock) void coo_pieces_kernel(int nnz, int npieces, int nrows,
+                                                            const int32_t* __restrict__ row,
+                                                            const int32_t* __restrict__ col,
+                                                            const T* __restrict__ vals, const T* __restrict__ x,
+                                                            T* __restrict__ y, int32_t* __restrict__ carry_key,
+                                                            T* __restrict__ carry_val) {
+  typedef T V4 __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+  typedef int32_t I4 __attribute__((ext_vector_type(4), aligned(4)));
+  const int lane = lane_id();
+  const int piece = xcd_contiguous_block_id() * (kBlock / kWave) + wave_id();
+  if (piece >= npieces) return;
+  const int base = piece * kSmallPiece, p0 = base + lane * 4;
+  int32_t r[4], c[4];
+  T v[4];
+  if (base + kSmallPiece <= nnz) {  // uniform
+    const I4 rr = __builtin_nontemporal_load(reinterpret_cast<const I4*>(row + p0));
+    const I4 cc = __builtin_nontemporal_load(reinterpret_cast<const I4*>(col + p0));
+    const V4 vv = __builtin_nontemporal_load(reinterpret_cast<const V4*>(vals + p0));
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      r[q] = rr[q];
+      c[q] = cc[q];
+      v[q] = vv[q];
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int p = min(p0 + q, nnz - 1);  // beyond the end: the last entry's row again, value 0
+      r[q] = row[p];
+      c[q] = col[p];
+      v[q] = p0 + q < nnz ? vals[p] : T(0);
+    }
+  }
+  int32_t before = -1;
+  if (lane == 0 && base > 0) before = row[base - 1];
+  T prod[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) prod[q] = x[c[q]];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) prod[q] = p0 + q < nnz ? v[q] * prod[q] : T(0);
+  const int32_t prev = dpp_move<0x138, 0xf>(-1, r[3]);  // wave_shr:1
+  if (lane > 0) before = prev;
+
+  T acc = 0, lead = 0;
+  bool has_head = false, head_first = false;
+  int last_row = -1, a = before;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const bool head = r[q] != a;
+    if (ZERO) zero_rows<T>(y, head ? a + 1 : 0, head ? r[q] : 0);
+    if (head) {
+      if (has_head) y[last_row] = acc;  // a row that starts and ends inside this lane
+      else lead = acc;
+      head_first = head_first || q == 0;
+      has_head = true;
+      last_row = r[q];
+      acc = 0;
+    }
+    acc += prod[q];
+    a = r[q];
+  }
+  if (ZERO && piece == npieces - 1) zero_rows<T>(y, lane == kWave - 1 ? r[3] + 1 : 0, lane == kWave - 1 ? nrows : 0);
+  const uint64_t heads = __ballot(has_head);
+  const int from = last_lane(heads, false), prev_head = last_lane(heads, true);
+  const T sum = wave_marked_sum<T>(acc, from >= 0 ? lane - from : kWave);
+  T open = dpp_move<0x138, 0xf>(T(0), sum);  // what is open before this lane
+  if (lane == 0) open = T(0);
+  const int open_row = __shfl(last_row, max(prev_head, 0));
+  if (has_head) {
+    if (prev_head >= 0) {
+      y[open_row] = open + lead;
+    } else {  // what precedes the piece's first row start
+      carry_key[piece] = lane == 0 && head_first ? -1 : before;
+      carry_val[piece] = open + lead;
+    }
+  }
+  if (lane == kWave - 1) {  // the row still open at the end of the piece
+    if (from >= 0) {
+      y[has_head ? last_row : open_row] = sum;
+    } else {
+      carry_key[piece] = r[0];
+      carry_val[piece] = sum;
+    }
+  }
+}
+
 // ---------------------------------------------------------------- launchers
 
 // binned scatter for large unordered COO (coo_bin.hip)
@@ -841,6 +934,15 @@ size_t coo_unordered_workspace(int dtype, int64_t nnz, int64_t nrows) {
 
 constexpr int kSegIPT = 8;
 
+// Ordered COO of more entries: waves that hold 256 each gain nothing over workgroups of 2048 (40M
+// entries, fp64, uniform rows 709 against 705 us, power law 664 against 645), and leave more carries.
+constexpr int64_t kPiecesMaxEntries = int64_t(1) << 24;
+size_t seg_spmv_workspace(int64_t nnz);
+size_t ordered_coo_workspace(int64_t nnz) {
+  if (nnz > kPiecesMaxEntries) return seg_spmv_workspace(nnz);
+  const int64_t np = (nnz + kSmallPiece - 1) / kSmallPiece;
+  return align_up((size_t)np * 4, 256) + align_up((size_t)np * 8, 256) + 256;
+}
 size_t seg_spmv_workspace(int64_t nnz) {
   const int64_t chunk = (int64_t)kSegIPT * kBlock;
   const int64_t nwg = (nnz + chunk - 1) / chunk;
@@ -886,6 +988,38 @@ static spt_status launch_seg_x(int64_t nnz, int64_t nrows, const int32_t* pos_or
   SPT_CHECK_LAUNCH("seg_spmv");
   hipLaunchKernelGGL(carry_fixup_kernel<T>, dim3((nwg + kBlock - 1) / kBlock), dim3(kBlock), 0, s,
                      nwg, ckey, cval, y, select, want);
+  SPT_CHECK_LAUNCH("carry_fixup");
+  return SPT_OK;
+}
+
+// Up to kZeroRows rows the pieces zero the rows without entries (worst case, one gap of all rows: one
+// wave zeroes them in 4096 rounds), which saves the launch that zeroes all.
+constexpr int64_t kZeroRows = 1 << 18;
+template <typename T>
+static spt_status launch_coo_pieces(int64_t nnz, int64_t nrows, const int32_t* row, const int32_t* col, const T* vals,
+                                    const T* x, T* y, void* ws, size_t ws_bytes, hipStream_t s) {
+  if (nnz == 0) return launch_fill<T>(y, nrows, T(0), s);
+  if (nnz + kSmallPiece >= INT32_MAX || nrows + 1 >= INT32_MAX)
+    return fail(SPT_ERR_UNSUPPORTED, "spmv: more than 2^31 entries or rows");
+  const int np = (int)((nnz + kSmallPiece - 1) / kSmallPiece);
+  if (!ws || ws_bytes < ordered_coo_workspace(nnz))
+    return fail(SPT_ERR_WORKSPACE, "spmv: workspace of %zu bytes needed, %zu given", ordered_coo_workspace(nnz), ws_bytes);
+  Workspace W(ws, ws_bytes);
+  int32_t* ckey = W.take<int32_t>(np);
+  T* cval = W.take<T>(np);
+  const dim3 grid((np + kBlock / kWave - 1) / (kBlock / kWave));
+  if (nrows <= kZeroRows) {
+    hipLaunchKernelGGL((coo_pieces_kernel<T, true>), grid, dim3(kBlock), 0, s, (int)nnz, np, (int)nrows, row, col, vals, x,
+                       y, ckey, cval);
+  } else {
+    spt_status st = launch_fill<T>(y, nrows, T(0), s);
+    if (st != SPT_OK) return st;
+    hipLaunchKernelGGL((coo_pieces_kernel<T, false>), grid, dim3(kBlock), 0, s, (int)nnz, np, (int)nrows, row, col, vals, x,
+                       y, ckey, cval);
+  }
+  SPT_CHECK_LAUNCH("coo pieces");
+  hipLaunchKernelGGL(carry_fixup_kernel<T>, dim3((np + kBlock - 1) / kBlock), dim3(kBlock), 0, s, np, ckey, cval, y,
+                     nullptr, 0);
   SPT_CHECK_LAUNCH("carry_fixup");
   return SPT_OK;
 }
@@ -1058,9 +1192,10 @@ static spt_status spmv_typed(Format f, const spt_tensor* A, const T* x, T* y, vo
         SPT_CHECK_LAUNCH("coo_small_spmv");
         return SPT_OK;
       }
+      if ((A->level[0].flags & SPT_ORDERED) && nnz <= kPiecesMaxEntries)
+        return launch_coo_pieces<T>(nnz, N, A->level[0].crd, A->level[1].crd, vals, x, y, ws, ws_bytes, s);
       if (A->level[0].flags & SPT_ORDERED)
-        return launch_seg<T, false>(nnz, N, A->level[0].crd, A->level[1].crd, vals, x, y, ws,
-                                    ws_bytes, s);
+        return launch_seg<T, false>(nnz, N, A->level[0].crd, A->level[1].crd, vals, x, y, ws, ws_bytes, s);
       if (nnz >= INT32_MAX) return fail(SPT_ERR_UNSUPPORTED, "spmv: more than 2^31 entries");
       if (nnz >= kBinnedMinEntries)
         return coo_binned_spmv<T>(nnz, N, A->level[0].crd, A->level[1].crd, vals, x, y, ws, ws_bytes,
@@ -1159,7 +1294,7 @@ __global__ __launch_bounds__(kBlock) void split_pairs_kernel(int64_t n, const in
 }
 
 static size_t coo_matrix_spmv_workspace(const spt_tensor* A) {
-  return (A->level[0].flags & SPT_ORDERED) ? seg_spmv_workspace(A->nvals)
+  return (A->level[0].flags & SPT_ORDERED) ? ordered_coo_workspace(A->nvals)
                                            : coo_unordered_workspace(A->dtype, A->nvals, A->level[0].N);
 }
 

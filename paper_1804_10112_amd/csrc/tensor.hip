@@ -7,6 +7,7 @@
 // leaves a carry that a follow-up kernel adds in a fixed order (no atomics).
 #include <algorithm>
 
+#include "carry.hpp"
 #include "common.hpp"
 #include "scan.hpp"
 #include "segreduce.hpp"

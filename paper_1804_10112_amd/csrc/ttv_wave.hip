@@ -23,6 +23,7 @@
 // 263 / 174 us), four pieces in flight instead of two (no change). What remains is the serial
 // instruction stream of a wave: sixteen waves per compute unit is all that one workgroup, which
 // the single copy of c forces, can provide.
+#include "carry.hpp"
 #include "common.hpp"
 #include "scan.hpp"
 #include "segreduce.hpp"

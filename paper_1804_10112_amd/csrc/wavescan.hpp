@@ -50,6 +50,34 @@ __device__ __forceinline__ int wave_inclusive_sum(int v) {
   return v;
 }
 
+// Inclusive segmented sum over the wave: v of the lanes from the last marked one up to this. `back`
+// is the distance to it (0: this lane is marked; above 63: no lane up to here is). Where the
+// distance is known, a step is a move, an add and a select, a third of what carrying the marks along
+// takes.
+template <int CTRL, int ROWS, typename T>
+__device__ __forceinline__ void wave_marked_step(T& v, bool open) {
+  const T up = dpp_move<CTRL, ROWS>(T(0), v);
+  v = open ? up + v : v;
+}
+template <typename T>
+__device__ __forceinline__ T wave_marked_sum(T v, int back) {
+  const int lane = lane_id();
+  wave_marked_step<0x111, 0xf>(v, back >= 1);  // row_shr:1, 2, 4, 8: inside each row of 16 lanes
+  wave_marked_step<0x112, 0xf>(v, back >= 2);
+  wave_marked_step<0x114, 0xf>(v, back >= 4);
+  wave_marked_step<0x118, 0xf>(v, back >= 8);
+  wave_marked_step<0x142, 0xa>(v, back > (lane & 15));  // row_bcast:15 into rows 1 and 3
+  wave_marked_step<0x143, 0xc>(v, back > (lane & 31));  // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
+// Last lane before this one (before: true) or up to this one whose bit is set in m, or -1.
+__device__ __forceinline__ int last_lane(uint64_t m, bool before) {
+  const uint64_t self = uint64_t{1} << lane_id();
+  m &= (self - 1) | (before ? 0 : self);
+  return 63 - __clzll(static_cast<long long>(m));
+}
+
 // Sum over the wave's lanes, the same value in every lane.
 template <typename T>
 __device__ __forceinline__ T wave_total(T v) {

@@ -381,3 +381,29 @@ def test_unordered_coo_where_binning_begins(nnz, dtype):
         p = rng.permutation(nnz)
         _check(wl.coo_spec(N, M, r[p], c[p], rng.uniform(-1, 1, nnz).astype(dtype), ordered=False),
                wl.dense_vector(M, 5, dtype), f"unordered nnz={nnz} N={N} heavy={heavy}")
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("nnz", [65_537, 65_792, 200_001, 1_000_000])
+def test_ordered_coo_in_pieces(nnz, dtype):
+    """Pieces of 256 entries: long gaps of rows without entries (zeroed by the pieces up to 2^18 rows, by
+    a fill beyond), a row of many pieces, rows that start and end with a piece."""
+    rng = np.random.default_rng(nnz)
+    for N in (262_144, 262_145, 3):
+        r = rng.integers(0, N, nnz)
+        if N > 3:
+            r[r < N // 3] = N // 3                      # one row of a third of the entries after a gap
+            r[(r > N // 2) & (r < N - 20_000)] = N // 2
+        r = np.sort(r)
+        r[: 1024] = np.repeat(r[0], 1024)
+        c = rng.integers(0, 5000, nnz)
+        _check(wl.coo_spec(N, 5000, r, c, rng.uniform(-1, 1, nnz).astype(dtype)), wl.dense_vector(5000, 5, dtype),
+               f"ordered coo nnz={nnz} N={N}")
+
+
+def test_ordered_coo_on_both_sides_of_the_largest_in_pieces():
+    rng = np.random.default_rng(3)
+    n = (1 << 24) + 1
+    r, c, v = np.sort(rng.integers(0, 400_000, n)), rng.integers(0, 9000, n), rng.uniform(-1, 1, n)
+    for m in (n, n - 1):
+        _check(wl.coo_spec(400_000, 9000, r[:m], c[:m], v[:m]), wl.dense_vector(9000, 5, np.float64), f"nnz={m}")

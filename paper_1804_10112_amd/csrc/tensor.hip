@@ -30,12 +30,10 @@ __global__ __launch_bounds__(kBlock) void fill_t_kernel(T* __restrict__ out, int
   if (i < n) out[i] = value;
 }
 
-// ================================================================ TTV on COO
+// ================================================================ fibres of a COO tensor (TTM)
 
 constexpr int kTtvIPT = 8;
 constexpr int kTtvChunk = kTtvIPT * kBlock;
-
-__device__ __forceinline__ int ttv_slot(int e) { return e + e / kTtvIPT; }
 
 // heads[w] = number of (i,j) fiber starts among the entries of chunk w.
 // VEC: 16-byte coordinate loads (needs 16-byte aligned ci, cj).
@@ -85,192 +83,6 @@ __global__ void ttv_total_kernel(int nchunks, const int32_t* __restrict__ heads,
                                  const int32_t* __restrict__ off, int64_t* __restrict__ out_nnz) {
   if (threadIdx.x == 0 && blockIdx.x == 0)
     *out_nnz = nchunks > 0 ? (int64_t)off[nchunks - 1] + heads[nchunks - 1] : 0;
-}
-
-// One output entry per fiber, at index off[chunk] + rank of the fiber's head
-// inside the chunk (append order = ascending (i,j), Section 3.4). The thread
-// holding a head appends the coordinates; the thread holding the fiber's end
-// stores the value. Carry protocol as in the SpMV kernel, keyed by output index.
-template <typename T> struct TtvVec;
-template <> struct TtvVec<double> { static constexpr int R = 2; typedef double type __attribute__((ext_vector_type(2))); typedef int32_t itype __attribute__((ext_vector_type(2))); };
-template <> struct TtvVec<float> { static constexpr int R = 4; typedef float type __attribute__((ext_vector_type(4))); typedef int32_t itype __attribute__((ext_vector_type(4))); };
-
-template <typename T, bool VEC>
-__global__ __launch_bounds__(kBlock) void ttv_coo_kernel(
-    int nnz, const int32_t* __restrict__ ci, const int32_t* __restrict__ cj,
-    const int32_t* __restrict__ ck, const T* __restrict__ vals, const T* __restrict__ c,
-    const int32_t* __restrict__ chunk_off, int32_t* __restrict__ out_i, int32_t* __restrict__ out_j,
-    T* __restrict__ out_v, int32_t* __restrict__ carry_key, T* __restrict__ carry_val) {
-  __shared__ T s_val[kTtvChunk + kBlock];
-  __shared__ int32_t s_i[kTtvChunk + kBlock];
-  __shared__ int32_t s_j[kTtvChunk + kBlock];
-  __shared__ SegScanStorage<T> s_scan;
-
-  const int tid = threadIdx.x;
-  const int chunk = blockIdx.x;  // plain order: one sequential stream per array reads fastest
-  const int base = chunk * kTtvChunk;
-  const int end = min(base + kTtvChunk, nnz);
-  const int32_t fill_i = ci[end - 1], fill_j = cj[end - 1];
-  constexpr int R = TtvVec<T>::R;
-  using V = typename TtvVec<T>::type;
-  using IV = typename TtvVec<T>::itype;
-#pragma unroll
-  for (int q = 0; q < kTtvIPT / R; ++q) {
-    const int e0 = (q * kBlock + tid) * R;
-    const int p0 = base + e0;
-    int32_t i[R], j[R], k[R];
-    T v[R];
-    bool ok[R];
-    if (VEC && p0 + R <= end) {
-      const IV iv = ldg_stream(reinterpret_cast<const IV*>(ci + p0));
-      const IV jv = ldg_stream(reinterpret_cast<const IV*>(cj + p0));
-      const IV kv = ldg_stream(reinterpret_cast<const IV*>(ck + p0));
-      const V vv = ldg_stream(reinterpret_cast<const V*>(vals + p0));
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        i[r] = iv[r];
-        j[r] = jv[r];
-        k[r] = kv[r];
-        v[r] = vv[r];
-        ok[r] = true;
-      }
-    } else {
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        ok[r] = p0 + r < end;
-        i[r] = ok[r] ? ldg_stream(ci + p0 + r) : fill_i;
-        j[r] = ok[r] ? ldg_stream(cj + p0 + r) : fill_j;
-        k[r] = ok[r] ? ldg_stream(ck + p0 + r) : 0;
-        v[r] = ok[r] ? ldg_stream(vals + p0 + r) : T(0);
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      s_val[ttv_slot(e0 + r)] = ok[r] ? v[r] * c[k[r]] : T(0);
-      s_i[ttv_slot(e0 + r)] = i[r];
-      s_j[ttv_slot(e0 + r)] = j[r];
-    }
-  }
-  int32_t pi = -1, pj = -1;  // coordinates of the entry before this thread's items
-  if (tid == 0 && base > 0) {
-    pi = ci[base - 1];
-    pj = cj[base - 1];
-  }
-  __syncthreads();
-  if (tid > 0) {
-    pi = s_i[ttv_slot(tid * kTtvIPT - 1)];
-    pj = s_j[ttv_slot(tid * kTtvIPT - 1)];
-  }
-
-  int32_t li[kTtvIPT], lj[kTtvIPT];
-  unsigned headmask = 0;
-  {
-    int32_t qi = pi, qj = pj;
-#pragma unroll
-    for (int k = 0; k < kTtvIPT; ++k) {
-      li[k] = s_i[ttv_slot(tid * kTtvIPT + k)];
-      lj[k] = s_j[ttv_slot(tid * kTtvIPT + k)];
-      if (li[k] != qi || lj[k] != qj) headmask |= 1u << k;
-      qi = li[k];
-      qj = lj[k];
-    }
-  }
-  const int cnt = __popc(headmask);
-  int wg_heads;
-  int next_idx = chunk_off[chunk] + block_inclusive_sum(cnt, &wg_heads) - cnt;
-
-  T acc = 0, lead = 0;
-  int has_head = 0, last_key = -1;
-#pragma unroll
-  for (int k = 0; k < kTtvIPT; ++k) {
-    if (headmask & (1u << k)) {
-      if (!has_head) {
-        lead = acc;
-        has_head = 1;
-      } else {
-        out_v[last_key] = acc;
-      }
-      last_key = next_idx++;
-      out_i[last_key] = li[k];
-      out_j[last_key] = lj[k];
-      acc = 0;
-    }
-    acc += s_val[ttv_slot(tid * kTtvIPT + k)];
-  }
-
-  SegSum<T> in = block_seg_exclusive_scan<T>(SegSum<T>{has_head, acc, last_key}, s_scan);
-  const int carry_idx = chunk_off[chunk] - 1;  // fiber cut by the chunk start
-  if (has_head) {
-    const T total = in.v + lead;
-    if (in.f) {
-      out_v[in.k] = total;
-    } else {
-      const bool at_start = (tid == 0) && (headmask & 1u);
-      carry_key[chunk] = at_start ? -1 : carry_idx;
-      carry_val[chunk] = total;
-    }
-  }
-  if (tid == kBlock - 1) {
-    if (has_head) {
-      out_v[last_key] = acc;
-    } else if (in.f) {
-      out_v[in.k] = in.v + acc;
-    } else {
-      carry_key[chunk] = carry_idx;
-      carry_val[chunk] = in.v + acc;
-    }
-  }
-}
-
-static size_t ttv_coo_workspace(int64_t nnz) {
-  const int64_t nch = (nnz + kTtvChunk - 1) / kTtvChunk;
-  return 3 * align_up((size_t)nch * 4, 256) + align_up((size_t)nch * 8, 256) + scan_workspace(nch) +
-         256;
-}
-
-template <typename T>
-static spt_status ttv_coo_typed(const spt_tensor* B, const T* c, int32_t* out_i, int32_t* out_j,
-                                T* out_v, int64_t* out_nnz, void* ws, size_t ws_bytes,
-                                hipStream_t s) {
-  const int64_t nnz64 = B->nvals;
-  if (nnz64 + kTtvChunk >= INT32_MAX) return fail(SPT_ERR_UNSUPPORTED, "ttv: more than 2^31 entries");
-  const int nnz = (int)nnz64;
-  const int nch = (nnz + kTtvChunk - 1) / kTtvChunk;
-  if (nnz == 0) {
-    hipLaunchKernelGGL(ttv_total_kernel, dim3(1), dim3(kWave), 0, s, 0, nullptr, nullptr, out_nnz);
-    SPT_CHECK_LAUNCH("ttv_total");
-    return SPT_OK;
-  }
-  if (!ws || ws_bytes < ttv_coo_workspace(nnz))
-    return fail(SPT_ERR_WORKSPACE, "ttv: workspace of %zu bytes needed, %zu given",
-                ttv_coo_workspace(nnz), ws_bytes);
-  Workspace W(ws, ws_bytes);
-  int32_t* heads = W.take<int32_t>(nch);
-  int32_t* off = W.take<int32_t>(nch);
-  int32_t* ckey = W.take<int32_t>(nch);
-  T* cval = W.take<T>(nch);
-  int32_t* scan_tmp = reinterpret_cast<int32_t*>(W.take<char>(scan_workspace(nch)));
-  const int32_t *ci = B->level[0].crd, *cj = B->level[1].crd, *ck = B->level[2].crd;
-  auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-  const bool vec = al(ci) && al(cj) && al(ck) && al(B->vals);
-  if (vec) hipLaunchKernelGGL(ttv_count_kernel<true>, dim3(nch), dim3(kBlock), 0, s, nnz, ci, cj, heads);
-  else hipLaunchKernelGGL(ttv_count_kernel<false>, dim3(nch), dim3(kBlock), 0, s, nnz, ci, cj, heads);
-  SPT_CHECK_LAUNCH("ttv_count");
-  spt_status st = device_scan_i32<false>(heads, off, nch, scan_tmp, s);
-  if (st != SPT_OK) return st;
-  hipLaunchKernelGGL(ttv_total_kernel, dim3(1), dim3(kWave), 0, s, nch, heads, off, out_nnz);
-  SPT_CHECK_LAUNCH("ttv_total");
-  if (vec)
-    hipLaunchKernelGGL((ttv_coo_kernel<T, true>), dim3(nch), dim3(kBlock), 0, s, nnz, ci, cj, ck,
-                       static_cast<const T*>(B->vals), c, off, out_i, out_j, out_v, ckey, cval);
-  else
-    hipLaunchKernelGGL((ttv_coo_kernel<T, false>), dim3(nch), dim3(kBlock), 0, s, nnz, ci, cj, ck,
-                       static_cast<const T*>(B->vals), c, off, out_i, out_j, out_v, ckey, cval);
-  SPT_CHECK_LAUNCH("ttv_coo");
-  hipLaunchKernelGGL(carry_fixup_kernel<T>, dim3((nch + kBlock - 1) / kBlock), dim3(kBlock), 0, s,
-                     nch, ckey, cval, out_v);
-  SPT_CHECK_LAUNCH("ttv carry_fixup");
-  return SPT_OK;
 }
 
 // ================================================================ SpDM
@@ -715,7 +527,10 @@ size_t ttm_workspace(Format f, const spt_tensor* B, int32_t K) {
   const int64_t nnz = B->nvals, L = B->level[2].N;
   size_t n = align_up((size_t)nnz * 4, 256) + align_up((size_t)L * K * 8, 256) +
              spdm_workspace(B, K);
-  if (f == Format::COO3) n += ttv_coo_workspace(nnz);
+  if (f == Format::COO3) {
+    const int64_t nch = (nnz + kTtvChunk - 1) / kTtvChunk;
+    n += 2 * align_up((size_t)nch * 4, 256) + scan_workspace(nch);
+  }
   return n + 256;
 }
 
@@ -795,23 +610,23 @@ spt_status ttm_dispatch(Format f, const spt_tensor* B, const void* C, int32_t K,
                           static_cast<float*>(out_vals), out_nfib_dev, ws, ws_bytes, s);
 }
 
-// c held in LDS, one resident workgroup per compute unit (ttv_wave.hip)
+// ttv_wave.hip
 bool ttv_wave_applies(int64_t nnz, int64_t K, int dtype);
-size_t ttv_coo_wave_workspace(int64_t nnz);
+size_t ttv_coo_workspace(int64_t nnz);
 size_t ttv_csf_wave_workspace(int64_t nnz);
 template <typename T>
-spt_status ttv_coo_wave(int64_t nnz, int64_t K, const int32_t* ci, const int32_t* cj, const int32_t* ck,
-                        const T* vals, const T* c, int32_t* out_i, int32_t* out_j, T* out_v, int64_t* out_nnz,
-                        void* ws, size_t ws_bytes, hipStream_t s);
+spt_status ttv_coo(int64_t nnz, int64_t K, const int32_t* ci, const int32_t* cj, const int32_t* ck,
+                   const T* vals, const T* c, int32_t* out_i, int32_t* out_j, T* out_v, int64_t* out_nnz,
+                   void* ws, size_t ws_bytes, hipStream_t s);
 template <typename T>
 spt_status ttv_csf_wave(int64_t nnz, int64_t nfib, int64_t K, const int32_t* pos, const int32_t* ck,
                         const T* vals, const T* c, T* out_v, int64_t* out_count, void* ws, size_t ws_bytes,
                         hipStream_t s);
 
 size_t ttv_workspace(Format f, const spt_tensor* B) {
-  if (ttv_wave_applies(B->nvals, B->level[2].N, B->dtype))
-    return f == Format::COO3 ? ttv_coo_wave_workspace(B->nvals) : ttv_csf_wave_workspace(B->nvals);
-  return f == Format::COO3 ? ttv_coo_workspace(B->nvals) : seg_spmv_workspace(B->nvals);
+  if (f == Format::COO3) return ttv_coo_workspace(B->nvals);
+  return ttv_wave_applies(B->nvals, B->level[2].N, B->dtype) ? ttv_csf_wave_workspace(B->nvals)
+                                                             : seg_spmv_workspace(B->nvals);
 }
 
 spt_status ttv_dispatch(Format f, const spt_tensor* B, const void* c, int32_t* out_crd0,
@@ -840,21 +655,19 @@ spt_status ttv_dispatch(Format f, const spt_tensor* B, const void* c, int32_t* o
     return csr_rows_reduce(B->dtype, B->nvals, nfib, B->level[2].pos, B->level[2].crd, B->vals, c,
                            out_vals, ws, ws_bytes, s);
   }
-  if (ttv_wave_applies(B->nvals, B->level[2].N, B->dtype)) {
-    const int32_t *ci = B->level[0].crd, *cj = B->level[1].crd, *ck = B->level[2].crd;
-    if (B->dtype == SPT_F64)
-      return ttv_coo_wave<double>(B->nvals, B->level[2].N, ci, cj, ck, static_cast<const double*>(B->vals),
-                                  static_cast<const double*>(c), out_crd0, out_crd1,
-                                  static_cast<double*>(out_vals), out_nnz_dev, ws, ws_bytes, s);
-    return ttv_coo_wave<float>(B->nvals, B->level[2].N, ci, cj, ck, static_cast<const float*>(B->vals),
-                               static_cast<const float*>(c), out_crd0, out_crd1, static_cast<float*>(out_vals),
-                               out_nnz_dev, ws, ws_bytes, s);
+  if (B->nvals == 0) {
+    hipLaunchKernelGGL(set_i64_kernel, dim3(1), dim3(kWave), 0, s, out_nnz_dev, (int64_t)0);
+    SPT_CHECK_LAUNCH("ttv set count");
+    return SPT_OK;
   }
+  const int32_t *ci = B->level[0].crd, *cj = B->level[1].crd, *ck = B->level[2].crd;
   if (B->dtype == SPT_F64)
-    return ttv_coo_typed<double>(B, static_cast<const double*>(c), out_crd0, out_crd1,
-                                 static_cast<double*>(out_vals), out_nnz_dev, ws, ws_bytes, s);
-  return ttv_coo_typed<float>(B, static_cast<const float*>(c), out_crd0, out_crd1,
-                              static_cast<float*>(out_vals), out_nnz_dev, ws, ws_bytes, s);
+    return ttv_coo<double>(B->nvals, B->level[2].N, ci, cj, ck, static_cast<const double*>(B->vals),
+                           static_cast<const double*>(c), out_crd0, out_crd1, static_cast<double*>(out_vals),
+                           out_nnz_dev, ws, ws_bytes, s);
+  return ttv_coo<float>(B->nvals, B->level[2].N, ci, cj, ck, static_cast<const float*>(B->vals),
+                        static_cast<const float*>(c), out_crd0, out_crd1, static_cast<float*>(out_vals),
+                        out_nnz_dev, ws, ws_bytes, s);
 }
 
 }  // namespace spt

@@ -1,4 +1,5 @@
-// TTV A_ij = sum_k B_ijk c_k (Section 5.3) for large tensors: the vector c is held in LDS.
+// TTV A_ij = sum_k B_ijk c_k (Section 5.3): COO, and CSF tensors of many entries. In pieces of 256
+// entries per wave; for large tensors the vector c is held in LDS.
 //
 // Every stored entry gathers one c_k. With c in global memory those gathers, not the
 // streams of coordinates and values, set the pace (they hit L2, but a wave's 64 distinct
@@ -13,14 +14,15 @@
 //   - a segmented sum over the wave in registers (lane movement inside the vector ALU), no
 //     workgroup barrier anywhere in the loop, so a wave waiting for memory never holds up
 //     another.
-// Output protocol as in the chunked kernels: the piece that holds a fibre's first entry
+// Output: the piece that holds a fibre's first entry
 // stores the fibre's (possibly partial) sum; what precedes the first head of a piece leaves
 // as carry number `piece` and is added afterwards (carry_fixup_kernel), in a fixed order:
 // results are bit-reproducible.
 // Measured on 50M entries in 8.1M fibres, fp32, c of 50 000 values (78 % / 61 % of it cached):
-// COO 214 us (chunked kernel with c in global memory: 324 us), CSF 158 us (357 us). Left out
+// COO 214 us (workgroups of 2048 entries with c in global memory: 324 us), CSF 158 us (357 us). Left out
 // after measuring: eight entries per lane (a lane's two 16-byte loads then lie 32 bytes apart:
-// 263 / 174 us), four pieces in flight instead of two (no change). What remains is the serial
+// 263 / 174 us), four pieces in flight instead of two or the next two loaded ahead (no change), results
+// put in order in LDS before they are stored (dense fibres 12 % faster, skewed tensors 2 to 5 % slower). What remains is the serial
 // instruction stream of a wave: sixteen waves per compute unit is all that one workgroup, which
 // the single copy of c forces, can provide.
 #include "carry.hpp"
@@ -59,6 +61,14 @@ __device__ __forceinline__ void load4(const double* p, double (&v)[4]) {
 }
 __device__ __forceinline__ void load4(const int32_t* p, int32_t (&v)[4]) {
   const int4v q = ld_nt(reinterpret_cast<const int4v*>(p));
+  v[0] = q[0], v[1] = q[1], v[2] = q[2], v[3] = q[3];
+}
+
+// Four consecutive values of any alignment.
+template <typename E>
+__device__ __forceinline__ void load_any(const E* p, E (&v)[4]) {
+  typedef E V4 __attribute__((ext_vector_type(4), aligned(sizeof(E))));
+  const V4 q = __builtin_nontemporal_load(reinterpret_cast<const V4*>(p));
   v[0] = q[0], v[1] = q[1], v[2] = q[2], v[3] = q[3];
 }
 
@@ -289,6 +299,89 @@ __global__ __launch_bounds__(kBig) void ttv_coo_wave_kernel(
   }
 }
 
+// The same with c in global memory and a wave per piece. SELF: piece_off holds the pieces' head counts,
+// which every workgroup adds up as far as its pieces.
+template <typename T, bool SELF>
+__global__ __launch_bounds__(kBlock) void ttv_coo_piece_kernel(
+    int nnz, int npieces, const int32_t* __restrict__ ci, const int32_t* __restrict__ cj,
+    const int32_t* __restrict__ ck, const T* __restrict__ vals, const T* __restrict__ c,
+    const int32_t* __restrict__ piece_off, int32_t* __restrict__ out_i, int32_t* __restrict__ out_j,
+    T* __restrict__ out_v, int64_t* __restrict__ out_nnz, int32_t* __restrict__ carry_key,
+    T* __restrict__ carry_val) {
+  constexpr int kWaves = kBlock / kWave;
+  __shared__ int s_before[kWaves];
+  const int lane = lane_id(), piece0 = blockIdx.x * kWaves;
+  const int piece = min(piece0 + wave_id(), npieces - 1);  // beyond the end: the last piece again, not stored
+  const int base = piece * kPiece, p0 = base + lane * kEPL;
+  int32_t i[kEPL], j[kEPL], k[kEPL];
+  T v[kEPL];
+  if (base + kPiece <= nnz) {  // uniform
+    load_any(ci + p0, i);
+    load_any(cj + p0, j);
+    load_any(ck + p0, k);
+    load_any(vals + p0, v);
+  } else {
+#pragma unroll
+    for (int r = 0; r < kEPL; ++r) {
+      const int p = min(p0 + r, nnz - 1);  // beyond the end: the last entry's fibre, value 0
+      i[r] = ci[p];
+      j[r] = cj[p];
+      k[r] = ck[p];
+      v[r] = p0 + r < nnz ? vals[p] : T(0);
+    }
+  }
+  int32_t qi = -1, qj = -1;
+  if (lane == 0 && base > 0) {
+    qi = ci[base - 1];
+    qj = cj[base - 1];
+  }
+  T g[kEPL];
+#pragma unroll
+  for (int r = 0; r < kEPL; ++r) g[r] = c[k[r]];
+  int first;  // results before the piece
+  if (SELF) {
+    int before = 0;
+    for (int t = threadIdx.x; t < piece0; t += kBlock) before += piece_off[t];
+    before = wave_inclusive_sum(before);
+    if (lane == kWave - 1) s_before[wave_id()] = before;
+    __syncthreads();
+    first = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) first += s_before[w];
+    for (int w = piece0; w < piece; ++w) first += piece_off[w];
+  } else {
+    first = piece_off[piece];
+  }
+  if (piece0 + wave_id() >= npieces) return;
+  const int32_t ui = dpp_move<0x138, 0xf>(-1, i[kEPL - 1]), uj = dpp_move<0x138, 0xf>(-1, j[kEPL - 1]);  // wave_shr:1
+  if (lane > 0) {
+    qi = ui;
+    qj = uj;
+  }
+  unsigned headmask = 0;
+#pragma unroll
+  for (int r = 0; r < kEPL; ++r) {
+    if (i[r] != qi || j[r] != qj) headmask |= 1u << r;
+    qi = i[r];
+    qj = j[r];
+  }
+  const int cnt = __popc(headmask), upto = first + wave_inclusive_sum(cnt);
+  if (piece == npieces - 1 && lane == kWave - 1 && out_nnz) *out_nnz = upto;
+  int next = upto - cnt, key[kEPL];
+  T p[kEPL];
+#pragma unroll
+  for (int r = 0; r < kEPL; ++r) {
+    p[r] = v[r] * g[r];
+    key[r] = next;
+    if (headmask & (1u << r)) {
+      out_i[next] = i[r];
+      out_j[next] = j[r];
+      ++next;
+    }
+  }
+  wave_fibre_sums<T>(p, headmask, key, first - 1, piece, out_v, carry_key, carry_val);
+}
+
 // ================================================================ CSF
 // first[piece] = first fibre that starts at or after the piece's first entry (piece ==
 // npieces: the number of fibres, so that the last piece also covers trailing empty fibres).
@@ -400,18 +493,24 @@ static int compute_units() {
   return cached[dev];
 }
 
+// COO tensors of up to 3M entries leave c in global memory, since staging it in every compute unit costs
+// 8 us, and add up the pieces' counts themselves, since a scan is two launches (us, fp32, skewed tensor:
+// 400 000 entries 12 instead of 23, 2M 29 instead of 34, 4M 48 instead of 47).
+constexpr int kSelfPieces = 12288;
+
 static int64_t pieces_of(int64_t nnz) { return (nnz + kPiece - 1) / kPiece; }
 
-// Smaller tensors stay with the chunked kernels: the fixed cost of staging c on every
-// compute unit is not recovered. So do tensors whose last dimension is so long that less
-// than a quarter of c fits the cache: their gathers go to global memory anyway, and the
-// chunked kernels keep more waves in flight for that.
+// Smaller CSF tensors are reduced row by row (one launch): the fixed cost of staging c on every
+// compute unit is not recovered (500 000 entries: 8 to 12 us by rows, 13 to 19 with c staged; 1M skewed
+// ones 16 to 37 and 14 to 23). Tensors whose last dimension is so long that less
+// than a quarter of c fits the cache leave c in global memory: their gathers go there anyway, and
+// without staging more waves are in flight for them.
 bool ttv_wave_applies(int64_t nnz, int64_t K, int dtype) {
   const int64_t vsz = dtype == SPT_F64 ? 8 : 4;
-  return nnz >= (int64_t(1) << 18) && nnz + kPiece < INT32_MAX && K * vsz <= 4 * (int64_t)kCsfCacheBytes;
+  return nnz >= (int64_t(1) << 19) && nnz + kPiece < INT32_MAX && K * vsz <= 4 * (int64_t)kCsfCacheBytes;
 }
 
-size_t ttv_coo_wave_workspace(int64_t nnz) {
+size_t ttv_coo_workspace(int64_t nnz) {
   const int64_t np = pieces_of(nnz);
   return 3 * align_up((size_t)np * 4, 256) + align_up((size_t)np * 8, 256) + scan_workspace(np) + 256;
 }
@@ -423,14 +522,14 @@ size_t ttv_csf_wave_workspace(int64_t nnz) {
 static bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 template <typename T>
-spt_status ttv_coo_wave(int64_t nnz64, int64_t K, const int32_t* ci, const int32_t* cj, const int32_t* ck,
-                        const T* vals, const T* c, int32_t* out_i, int32_t* out_j, T* out_v, int64_t* out_nnz,
-                        void* ws, size_t ws_bytes, hipStream_t s) {
+spt_status ttv_coo(int64_t nnz64, int64_t K, const int32_t* ci, const int32_t* cj, const int32_t* ck,
+                   const T* vals, const T* c, int32_t* out_i, int32_t* out_j, T* out_v, int64_t* out_nnz,
+                   void* ws, size_t ws_bytes, hipStream_t s) {
+  if (nnz64 + kPiece >= INT32_MAX) return fail(SPT_ERR_UNSUPPORTED, "ttv: more than 2^31 entries");
   const int nnz = (int)nnz64;
   const int np = (int)pieces_of(nnz64);
-  if (!ws || ws_bytes < ttv_coo_wave_workspace(nnz64))
-    return fail(SPT_ERR_WORKSPACE, "ttv: workspace of %zu bytes needed, %zu given", ttv_coo_wave_workspace(nnz64),
-                ws_bytes);
+  if (!ws || ws_bytes < ttv_coo_workspace(nnz64))
+    return fail(SPT_ERR_WORKSPACE, "ttv: workspace of %zu bytes needed, %zu given", ttv_coo_workspace(nnz64), ws_bytes);
   Workspace W(ws, ws_bytes);
   int32_t* heads = W.take<int32_t>(np);
   int32_t* off = W.take<int32_t>(np);
@@ -438,24 +537,35 @@ spt_status ttv_coo_wave(int64_t nnz64, int64_t K, const int32_t* ci, const int32
   T* cval = W.take<T>(np);
   int32_t* scan_tmp = reinterpret_cast<int32_t*>(W.take<char>(scan_workspace(np)));
   const bool vec = al16(ci) && al16(cj) && al16(ck) && al16(vals);
-  const unsigned hgrid = (unsigned)((np + kBlock / kWave - 1) / (kBlock / kWave));
-  if (vec) hipLaunchKernelGGL(ttv_piece_heads_kernel<true>, dim3(hgrid), dim3(kBlock), 0, s, nnz, np, ci, cj, heads);
-  else hipLaunchKernelGGL(ttv_piece_heads_kernel<false>, dim3(hgrid), dim3(kBlock), 0, s, nnz, np, ci, cj, heads);
+  const unsigned grid4 = (unsigned)((np + kBlock / kWave - 1) / (kBlock / kWave));
+  if (vec) hipLaunchKernelGGL(ttv_piece_heads_kernel<true>, dim3(grid4), dim3(kBlock), 0, s, nnz, np, ci, cj, heads);
+  else hipLaunchKernelGGL(ttv_piece_heads_kernel<false>, dim3(grid4), dim3(kBlock), 0, s, nnz, np, ci, cj, heads);
   SPT_CHECK_LAUNCH("ttv piece heads");
-  spt_status st = device_scan_i32<false>(heads, off, np, scan_tmp, s);
-  if (st != SPT_OK) return st;
-  const int cached = (int)std::min<int64_t>(K, kCooCacheBytes / sizeof(T));
-  const bool all = cached == K;
-  const unsigned grid = (unsigned)std::min<int64_t>(compute_units(), (np + kBigWaves - 1) / kBigWaves);
-#define SPT_TTV_COO(VEC_, ALL_)                                                                                  \
+  if (np <= kSelfPieces) {
+    hipLaunchKernelGGL((ttv_coo_piece_kernel<T, true>), dim3(grid4), dim3(kBlock), 0, s, nnz, np, ci, cj, ck, vals, c,
+                       heads, out_i, out_j, out_v, out_nnz, ckey, cval);
+    SPT_CHECK_LAUNCH("ttv coo pieces");
+  } else {
+    spt_status st = device_scan_i32<false>(heads, off, np, scan_tmp, s);
+    if (st != SPT_OK) return st;
+    if (ttv_wave_applies(nnz64, K, sizeof(T) == 8 ? SPT_F64 : SPT_F32)) {
+      const int cached = (int)std::min<int64_t>(K, kCooCacheBytes / sizeof(T));
+      const bool all = cached == K;
+      const unsigned grid = (unsigned)std::min<int64_t>(compute_units(), (np + kBigWaves - 1) / kBigWaves);
+#define SPT_TTV_COO(VEC_, ALL_)                                                                                    \
   hipLaunchKernelGGL((ttv_coo_wave_kernel<T, VEC_, ALL_>), dim3(grid), dim3(kBig), 0, s, nnz, np, ci, cj, ck, vals, \
                      c, cached, off, out_i, out_j, out_v, out_nnz, ckey, cval)
-  if (vec && all) SPT_TTV_COO(true, true);
-  else if (vec) SPT_TTV_COO(true, false);
-  else if (all) SPT_TTV_COO(false, true);
-  else SPT_TTV_COO(false, false);
+      if (vec && all) SPT_TTV_COO(true, true);
+      else if (vec) SPT_TTV_COO(true, false);
+      else if (all) SPT_TTV_COO(false, true);
+      else SPT_TTV_COO(false, false);
 #undef SPT_TTV_COO
-  SPT_CHECK_LAUNCH("ttv coo wave");
+    } else {
+      hipLaunchKernelGGL((ttv_coo_piece_kernel<T, false>), dim3(grid4), dim3(kBlock), 0, s, nnz, np, ci, cj, ck, vals,
+                         c, off, out_i, out_j, out_v, out_nnz, ckey, cval);
+    }
+    SPT_CHECK_LAUNCH("ttv coo");
+  }
   hipLaunchKernelGGL(carry_fixup_kernel<T>, dim3((np + kBlock - 1) / kBlock), dim3(kBlock), 0, s, np, ckey, cval,
                      out_v, nullptr, 0);
   SPT_CHECK_LAUNCH("ttv carry_fixup");
@@ -498,10 +608,10 @@ spt_status ttv_csf_wave(int64_t nnz64, int64_t nfib, int64_t K, const int32_t* p
   return SPT_OK;
 }
 
-template spt_status ttv_coo_wave<float>(int64_t, int64_t, const int32_t*, const int32_t*, const int32_t*,
+template spt_status ttv_coo<float>(int64_t, int64_t, const int32_t*, const int32_t*, const int32_t*,
                                         const float*, const float*, int32_t*, int32_t*, float*, int64_t*, void*,
                                         size_t, hipStream_t);
-template spt_status ttv_coo_wave<double>(int64_t, int64_t, const int32_t*, const int32_t*, const int32_t*,
+template spt_status ttv_coo<double>(int64_t, int64_t, const int32_t*, const int32_t*, const int32_t*,
                                          const double*, const double*, int32_t*, int32_t*, double*, int64_t*, void*,
                                          size_t, hipStream_t);
 template spt_status ttv_csf_wave<float>(int64_t, int64_t, int64_t, const int32_t*, const int32_t*, const float*,

@@ -203,6 +203,16 @@ def test_ttv_with_the_vector_in_lds(dtype, K, tail):
     _check_ttv(coo, csf, c, f"ttv in LDS K={K} tail={tail}")
 
 
+@pytest.mark.parametrize("dtype,K", [(np.float32, 50_000), (np.float64, 16_385), (np.float64, 100_000)])
+@pytest.mark.parametrize("nnz", [520_000, 530_001, 3_140_000, 3_160_003])
+def test_ttv_where_the_kernels_change(dtype, K, nnz):
+    """Below and above 2^19 entries (CSF) and 12 288 pieces of 256 (COO); K = 100 000 doubles do not fit LDS."""
+    dims = (3000, 500, K)
+    ci, cj, ck, v = wl.random_coo3_entries(dims, nnz, 31 + K % 7, dtype, "u01", skew=1.5)
+    coo, csf = wl.coo3_spec(dims, ci, cj, ck, v), wl.csf3_from_sorted_coo(dims, ci, cj, ck, v)
+    _check_ttv(coo, csf, wl.dense_vector(K, 7, dtype, "u01"), f"ttv K={K} nnz={len(v)}")
+
+
 def test_large_ttv_with_a_vector_far_beyond_lds_takes_the_chunked_kernels():
     """c of 600 000 values: less than a quarter would fit LDS, the chunked kernels run."""
     dims = (300, 500, 600_000)

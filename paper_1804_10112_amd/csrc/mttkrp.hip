@@ -14,7 +14,7 @@
 // 970 us, 68M lines of 128 bytes from L2, of them 37M from beyond; more or fewer waves, the next rows
 // loaded ahead, or C[k, :] kept while k stays change nothing). With 32 lanes of one column per entry,
 // which issue four times as many loads and hand-arounds, and longer walks per group: 1080 us, and for
-// 738 000 entries in CSF, J = 16, fp64, 96 us instead of 47.
+// 738 000 entries in CSF, J = 16, fp64, 96 us instead of 41.
 #include <algorithm>
 
 #include "common.hpp"
@@ -450,37 +450,37 @@ __global__ __launch_bounds__(kBlock) void mttkrp_fixup_kernel(int n, int J, cons
   }
 }
 
-// Few carries, in one launch: the workgroup of the first carry of a row adds up all of the row.
-// (50 000 entries in COO, J = 16, fp64: 19.2 -> 14.0 us. A row of 400 carries keeps its workgroup for 5 us,
-// as long as two launches take; where a row could have more, 1953 carries in all, it was 6 us slower.)
-constexpr int kCarryRunsMax = 1024;
+// Few carries, in one launch: the workgroup of the first carry of a row adds up all of the row, whose end
+// it looks up first (rows read ahead without knowing cost 5 us where most rows have one carry). 738 000
+// entries in CSF, J = 16, fp64: 4.8 us, 13 in two launches. A row of all 2048 carries takes 16 rounds.
+constexpr int kCarryRunsMax = 2048, kRunBlock = 512;
 template <typename T>
-__global__ __launch_bounds__(kBlock) void mttkrp_carry_runs_kernel(int n, int J, int log_cols,
+__global__ __launch_bounds__(kRunBlock) void mttkrp_carry_runs_kernel(int n, int J, int log_cols,
                                                                    const int32_t* __restrict__ key,
                                                                    const T* __restrict__ vec, T* __restrict__ A) {
-  __shared__ double s_sum[kBlock];
+  __shared__ double s_sum[kRunBlock];
   const int w = blockIdx.x, k = key[w];
   if (k < 0 || (w > 0 && key[w - 1] == k)) return;
-  const int tid = threadIdx.x, cols = 1 << log_cols, rows = kBlock >> log_cols;
+  const int tid = threadIdx.x, cols = 1 << log_cols, rows = kRunBlock >> log_cols;
   const int c = tid & (cols - 1), j = blockIdx.y * cols + c, jc = min(j, J - 1);
-  constexpr int U = 4;
+  int end = w;  // of the row's carries
+  for (;;) {
+    const int more = __syncthreads_count(end + tid < n && key[min(end + tid, n - 1)] == k);
+    end += more;
+    if (more < kRunBlock) break;
+  }
+  constexpr int U = 8;
   double sum = 0;
-  for (int u = w + (tid >> log_cols); u < n; u += U * rows) {
-    int32_t kk[U];
+  for (int u = w + (tid >> log_cols); u < end; u += U * rows) {
     T v[U];
 #pragma unroll
-    for (int q = 0; q < U; ++q) {
-      const int at = min(u + q * rows, n - 1);
-      kk[q] = u + q * rows < n ? key[at] : -1;
-      v[q] = vec[static_cast<int64_t>(at) * J + jc];
-    }
+    for (int q = 0; q < U; ++q) v[q] = vec[static_cast<int64_t>(min(u + q * rows, end - 1)) * J + jc];
 #pragma unroll
-    for (int q = 0; q < U; ++q) sum += kk[q] == k ? static_cast<double>(v[q]) : 0.0;
-    if (kk[U - 1] != k) break;
+    for (int q = 0; q < U; ++q) sum += u + q * rows < end ? static_cast<double>(v[q]) : 0.0;
   }
   s_sum[tid] = sum;
   __syncthreads();
-  for (int d = kBlock / 2; d >= cols; d >>= 1) {
+  for (int d = kRunBlock / 2; d >= cols; d >>= 1) {
     if (tid < d) s_sum[tid] += s_sum[tid + d];
     __syncthreads();
   }
@@ -577,7 +577,7 @@ static spt_status mttkrp3_typed(Format f, const spt_tensor* B, const T* Cm, cons
   if (n1 <= kCarryRunsMax) {
     int log_cols = 2;
     while (log_cols < 5 && (1 << log_cols) < J) ++log_cols;
-    hipLaunchKernelGGL(mttkrp_carry_runs_kernel<T>, dim3(n1, (J + (1 << log_cols) - 1) >> log_cols), dim3(kBlock), 0, s,
+    hipLaunchKernelGGL(mttkrp_carry_runs_kernel<T>, dim3(n1, (J + (1 << log_cols) - 1) >> log_cols), dim3(kRunBlock), 0, s,
                        n1, J, log_cols, key1, vec1, A);
     SPT_CHECK_LAUNCH("mttkrp carry runs");
     return SPT_OK;

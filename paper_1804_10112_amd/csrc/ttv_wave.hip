@@ -171,20 +171,27 @@ __device__ __forceinline__ void wave_fibre_sums(const T (&p)[kEPL], unsigned hea
 }
 
 // ================================================================ COO
-// heads[piece] = number of (i, j) fibre starts among the piece's entries.
+// heads[piece] = number of (i, j) fibre starts among the piece's entries. Bound by reading i and j; i is
+// ordered, so where it is the same before and at the end of a piece it need not be read.
 template <bool VEC>
 __global__ __launch_bounds__(kBlock) void ttv_piece_heads_kernel(int nnz, int npieces,
                                                                  const int32_t* __restrict__ ci,
                                                                  const int32_t* __restrict__ cj,
                                                                  int32_t* __restrict__ heads) {
-  const int piece = blockIdx.x * (kBlock / kWave) + wave_id();
+  const int piece = __builtin_amdgcn_readfirstlane(blockIdx.x * (kBlock / kWave) + wave_id());
   if (piece >= npieces) return;
   const int lane = lane_id();
   const int p0 = piece * kPiece + lane * kEPL;
   int32_t i[kEPL], j[kEPL];
-  if (VEC && p0 + kEPL <= nnz) {
-    load_lane(ci + p0, i);
+  if (VEC && (piece + 1) * kPiece <= nnz) {  // uniform
     load_lane(cj + p0, j);
+    const int32_t slice = ci[max(piece * kPiece - 1, 0)];
+    if (slice == ci[piece * kPiece + kPiece - 1]) {
+#pragma unroll
+      for (int r = 0; r < kEPL; ++r) i[r] = slice;
+    } else {
+      load_lane(ci + p0, i);
+    }
   } else {
 #pragma unroll
     for (int r = 0; r < kEPL; ++r) {

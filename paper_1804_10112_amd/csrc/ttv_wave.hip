@@ -245,11 +245,19 @@ __global__ __launch_bounds__(kBig) void ttv_coo_wave_kernel(
     for (int u = 0; u < kNP; ++u) {
       const int piece = min(piece0 + u * stride, npieces - 1);  // beyond the end: the last piece again, not stored
       const int p0 = piece * kPiece + lane * kEPL;
-      if (VEC && p0 + kEPL <= nnz) {
-        load_lane(ci + p0, i[u]);
+      const int before = max(piece * kPiece - 1, 0);  // only lane 0 uses it
+      pi[u] = ci[before];
+      pj[u] = cj[before];
+      if (VEC && (piece + 1) * kPiece <= nnz) {  // uniform
         load_lane(cj + p0, j[u]);
         load_lane(ck + p0, k[u]);
         load_lane(vals + p0, v[u]);
+        if (pi[u] == ci[piece * kPiece + kPiece - 1]) {
+#pragma unroll
+          for (int r = 0; r < kEPL; ++r) i[u][r] = pi[u];
+        } else {
+          load_lane(ci + p0, i[u]);
+        }
       } else {
 #pragma unroll
         for (int r = 0; r < kEPL; ++r) {
@@ -261,9 +269,6 @@ __global__ __launch_bounds__(kBig) void ttv_coo_wave_kernel(
           v[u][r] = ok ? vals[p] : T(0);
         }
       }
-      const int before = max(piece * kPiece - 1, 0);  // only lane 0 uses it
-      pi[u] = ci[before];
-      pj[u] = cj[before];
       first[u] = piece_off[piece];
     }
 #pragma unroll

@@ -323,15 +323,21 @@ __global__ __launch_bounds__(kBlock) void ttv_coo_piece_kernel(
   constexpr int kWaves = kBlock / kWave;
   __shared__ int s_before[kWaves];
   const int lane = lane_id(), piece0 = blockIdx.x * kWaves;
-  const int piece = min(piece0 + wave_id(), npieces - 1);  // beyond the end: the last piece again, not stored
+  const int piece = __builtin_amdgcn_readfirstlane(min(piece0 + wave_id(), npieces - 1));  // beyond the end: the last piece again, not stored
   const int base = piece * kPiece, p0 = base + lane * kEPL;
   int32_t i[kEPL], j[kEPL], k[kEPL];
   T v[kEPL];
   if (base + kPiece <= nnz) {  // uniform
-    load_any(ci + p0, i);
-    load_any(cj + p0, j);
     load_any(ck + p0, k);
     load_any(vals + p0, v);
+    load_any(cj + p0, j);
+    const int32_t slice = ci[max(base - 1, 0)];
+    if (slice == ci[base + kPiece - 1]) {
+#pragma unroll
+      for (int r = 0; r < kEPL; ++r) i[r] = slice;
+    } else {
+      load_any(ci + p0, i);
+    }
   } else {
 #pragma unroll
     for (int r = 0; r < kEPL; ++r) {

@@ -35,6 +35,10 @@ constexpr int kAddIPT = kAddPlaces / kBlock;
 // Up to here the workgroups of the merge are all resident at once and search their tiles' ends
 // themselves. Beyond, the searches would delay each of a workgroup's tiles.
 constexpr int kAddSelfTiles = 2048;
+// COO operands are searched over their whole length, by a wave for few tiles (fewest steps), by 16 lanes
+// for more (a fourth of the probes, which miss the caches: 1.6M + 800 000 entries, fp64, 38 -> 28 us;
+// 20 000 + 10 000 entries 11.0 us by waves, 12.0 by 16 lanes).
+constexpr int kAddWaveTiles = 128;
 constexpr int kAddResident = 6, kFillResident = 5;  // workgroups on a compute unit, as registers allow
 constexpr int kCus = 256;
 
@@ -210,7 +214,8 @@ __global__ __launch_bounds__(kBlock, kAddResident) void add_merge_kernel(const A
   AddTile<KL> t, next;
   if (SELF) {
     if (wave_id() < 2) {
-      const AddCut c = add_cut<KL, ROWS, kWave>(o, (static_cast<int64_t>(tile) + wave_id()) * kAddStep);
+      const int64_t d = (static_cast<int64_t>(tile) + wave_id()) * kAddStep;
+      const AddCut c = ROWS || ntiles <= kAddWaveTiles ? add_cut<KL, ROWS, kWave>(o, d) : add_cut<KL, ROWS, 16>(o, d);
       if (lane == 0) {
         s_cut[wave_id()] = c;
         if (wave_id() == 0 || tile == ntiles - 1) cuts[tile + wave_id()] = c;
@@ -518,7 +523,7 @@ static spt_status launch_add_merge(const AddOperands<KL>& o, int ntiles, AddCut*
     hipLaunchKernelGGL((add_cut_kernel<KL, ROWS>), dim3((ntiles * kCutLanes + kBlock) / kBlock), dim3(kBlock),
                        0, s, o, ntiles, cuts);
     SPT_CHECK_LAUNCH("add cut");
-    hipLaunchKernelGGL((add_merge_kernel<KL, ROWS, UNION, false>), dim3(kAddResident * kCus), dim3(kBlock), 0, s,
+    hipLaunchKernelGGL((add_merge_kernel<KL, ROWS, UNION, false>), dim3(std::min(ntiles, kAddResident * kCus)), dim3(kBlock), 0, s,
                        o, ntiles, cuts, bits, counts);
   } else {
     hipLaunchKernelGGL((add_merge_kernel<KL, ROWS, UNION, true>), dim3(ntiles), dim3(kBlock), 0, s, o, ntiles, cuts,

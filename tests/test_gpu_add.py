@@ -67,6 +67,7 @@ def test_add_skewed_rows_empty_rows_and_misaligned(fmt):
 @pytest.mark.parametrize("N,M,nb,shared", [
     (1, 5000, 1023, 1023), (1, 5000, 1024, 1024), (3, 4000, 2048, 2047),  # twins where a tile ends
     (2046, 9, 1, 1), (2047, 9, 1, 0), (5_000_000, 64, 5000, 2500),        # tiles of nothing but row starts
+    (3000, 4000, 524_000, 262_000), (3000, 4000, 600_000, 300_000),       # ends searched by waves, or by 16 lanes
     (3000, 4000, 3_000_000, 1_500_000)])                                  # more tiles than are resident at once
 def test_add_and_mul_at_the_edges_of_tiles(fmt, N, M, nb, shared):
     r, c, v = wl.random_coo_entries(N, M, nb, seed=nb, dtype=np.float64)

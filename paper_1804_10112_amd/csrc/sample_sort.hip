@@ -44,10 +44,10 @@ constexpr int kFin = 256;           // threads of a workgroup that finishes a bu
 constexpr int kSel = 1024;          // threads of a workgroup that selects its records first
 constexpr int kCap = 4096;          // records either can sort in LDS
 constexpr int kStaged = 2048;       // records whose keys and values also pass through LDS (own bucket)
-constexpr int kTile = 4096;         // records per tile of a partition
+constexpr int kTile = 4096;         // records per tile of a partition of many,
+constexpr int kSmallTile = 1024;    // and of few records (see tile_of)
 constexpr int kPart = 256;          // threads that scatter a tile
 constexpr int kPartWaves = kPart / kWave;
-constexpr int kPartIPT = kTile / kPart;
 constexpr int kGroup = 4;           // consecutive tiles that one workgroup classifies
 constexpr int kLiBits = 12;         // bits of a record's number inside its bucket; the rest of a word: its key, coarsely
 constexpr int kMaxSamples = 4096;   // numbered by kLiBits bits, too
@@ -116,7 +116,7 @@ struct Tables {
   int32_t* bucket_seg; // segment of each final bucket
 };
 
-__device__ __forceinline__ int tiles_in(int m) { return (m + kTile - 1) / kTile; }
+__device__ __forceinline__ int tiles_in(int m, int tile) { return (m + tile - 1) / tile; }
 __device__ __forceinline__ int final_buckets(int m, int target) {
   return max(1, min(kSegMax, (m + target - 1) / target));
 }
@@ -180,7 +180,7 @@ __device__ __forceinline__ int coarse_shift(uint64_t lo, uint64_t hi) {
 // LEVEL2: the segment is a bucket of level 1 (bounds from that level's scanned counts `off1`),
 // nb follows from its size, and the workgroup fills in its rows of the segment tables.
 template <int E, class SRC, bool LEVEL2>
-__global__ __launch_bounds__(1024) void splitters_kernel(const SRC src, const KeyForm f, int n, int nrows, int nb_fixed, int group,
+__global__ __launch_bounds__(1024) void splitters_kernel(const SRC src, const KeyForm f, int n, int nrows, int nb_fixed, int group, int tile,
                                                          const int32_t* __restrict__ off1, int ntiles1, int nseg,
                                                          const Tables T, const uint64_t* __restrict__ skey1,
                                                          uint64_t* __restrict__ skey,
@@ -201,13 +201,13 @@ __global__ __launch_bounds__(1024) void splitters_kernel(const SRC src, const Ke
     nb = final_buckets(m, kDirTarget);
     if (tid < seg) {  // what the segments before this one take of each table
       const int b = off1[static_cast<int64_t>(tid) * ntiles1], e = off1[static_cast<int64_t>(tid + 1) * ntiles1];
-      const int nt = tiles_in(e - b);
+      const int nt = tiles_in(e - b, tile);
       atomicAdd(&s_sum[0], nt);
       atomicAdd(&s_sum[1], (nt + group - 1) / group);
       atomicAdd(&s_sum[2], final_buckets(e - b, kDirTarget));
     }
     __syncthreads();
-    const int nt = tiles_in(m), ng = (nt + group - 1) / group;
+    const int nt = tiles_in(m, tile), ng = (nt + group - 1) / group;
     const int t0 = s_sum[0], g0 = s_sum[1], b0 = s_sum[2];
     if (tid == 0) {
       T.seg_start[seg] = begin;
@@ -288,7 +288,7 @@ __device__ __forceinline__ int bucket_of(const SplitterTable& t, uint64_t k, int
 // hist[base + d * nt + i] = records of tile i of the segment whose bucket is d, and each record's
 // bucket as one byte in dig. A workgroup takes up to `group` consecutive tiles of one segment
 // and stores each bucket's counts of them side by side (digit-major for the scan).
-template <class SRC, bool LEVEL2>
+template <class SRC, bool LEVEL2, int TILE>
 __global__ __launch_bounds__(kBlock) void classify_kernel(const SRC src, const KeyForm f, int n, int group,
                                                           int nseg, const Tables T,
                                                           const uint64_t* __restrict__ skey,
@@ -309,7 +309,7 @@ __global__ __launch_bounds__(kBlock) void classify_kernel(const SRC src, const K
     tile0 = (g - T.seg_group[seg]) * group;
     base = static_cast<int64_t>(T.seg_tile[seg]) * kRadix;
   } else {
-    ntiles = tiles_in(n);
+    ntiles = tiles_in(n, TILE);
     tile0 = g * group;
   }
   t.key[tid] = skey[seg * kSegMax + tid];
@@ -332,16 +332,16 @@ __global__ __launch_bounds__(kBlock) void classify_kernel(const SRC src, const K
   }
   __syncthreads();
   const int nt = min(group, ntiles - tile0);
-  constexpr int kAhead = 8;  // keys in flight per thread, across tiles
+  constexpr int kAhead = TILE / kBlock < 8 ? TILE / kBlock : 8;  // keys in flight per thread, across tiles
   uint64_t ahead[kAhead];
 #pragma unroll
   for (int k = 0; k < kAhead; ++k)
-    ahead[k] = src.key_stream(min(begin + tile0 * kTile + k * kBlock + tid, end - 1), f) >> f.kshift;
+    ahead[k] = src.key_stream(min(begin + tile0 * TILE + k * kBlock + tid, end - 1), f) >> f.kshift;
   for (int q = 0; q < nt; ++q) {
-    const int first = begin + (tile0 + q) * kTile;
+    const int first = begin + (tile0 + q) * TILE;
     int* cnt = s_cnt[q];
 #pragma unroll
-    for (int k = 0; k < (kTile / kBlock); ++k) {
+    for (int k = 0; k < (TILE / kBlock); ++k) {
       const int p = first + k * kBlock + tid;
       const uint64_t key = ahead[k % kAhead];
       ahead[k % kAhead] = src.key_stream(min(p + kAhead * kBlock, end - 1), f) >> f.kshift;
@@ -370,7 +370,7 @@ __global__ __launch_bounds__(kBlock) void classify_kernel(const SRC src, const K
 // consecutive lanes store to consecutive addresses.
 // SELF (few tiles): `off` holds the plain counts, and every workgroup adds up those before its own
 // tile itself; the first leaves the start of every bucket in `starts` (one more than buckets).
-template <typename VT, class SRC, bool LEVEL2, bool SELF = false>
+template <typename VT, class SRC, bool LEVEL2, int TILE, bool SELF = false>
 __global__ __launch_bounds__(kPart) void partition_kernel(const SRC src, const VT* __restrict__ val_in,
                                                            const KeyForm f, int n, int nseg, const Tables T,
                                                            const uint8_t* __restrict__ dig,
@@ -378,11 +378,12 @@ __global__ __launch_bounds__(kPart) void partition_kernel(const SRC src, const V
                                                            uint64_t* __restrict__ key_out,
                                                            VT* __restrict__ val_out,
                                                            int32_t* __restrict__ starts) {
+  constexpr int IPT = TILE / kPart;
   __shared__ int s_cnt[kPartWaves][kRadix];
   __shared__ int s_gdelta[kRadix];
   __shared__ int s_sum[4];
-  __shared__ uint64_t s_buf[kTile];
-  __shared__ uint8_t s_dig[kTile];
+  __shared__ uint64_t s_buf[TILE];
+  __shared__ uint8_t s_dig[TILE];
   VT* s_val = reinterpret_cast<VT*>(s_buf);
   const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
   const int tile = xcd_contiguous_block_id();
@@ -394,33 +395,33 @@ __global__ __launch_bounds__(kPart) void partition_kernel(const SRC src, const V
     const int t0 = T.seg_tile[seg];
     ntiles = T.seg_tile[seg + 1] - t0;
     i0 = tile - t0;
-    begin = T.seg_start[seg] + i0 * kTile;
+    begin = T.seg_start[seg] + i0 * TILE;
     end = T.seg_start[seg + 1];
     base = static_cast<int64_t>(t0) * kRadix;
   } else {
-    ntiles = tiles_in(n);
+    ntiles = tiles_in(n, TILE);
     i0 = tile;
-    begin = tile * kTile;
+    begin = tile * TILE;
     end = n;
   }
   for (int q = tid; q < kPartWaves * kRadix; q += kPart) (&s_cnt[0][0])[q] = 0;
   __syncthreads();
-  const int tile_n = min(kTile, end - begin);
-  const int wave_base = begin + w * (kWave * kPartIPT);
+  const int tile_n = min(TILE, end - begin);
+  const int wave_base = begin + w * (kWave * IPT);
   volatile int* cnt = s_cnt[w];
 
-  uint64_t key[kPartIPT];
-  VT val[kPartIPT];
-  int lpos[kPartIPT];  // digit << 16 | rank inside (wave, digit), later the slot in the sorted tile
+  uint64_t key[IPT];
+  VT val[IPT];
+  int lpos[IPT];  // digit << 16 | rank inside (wave, digit), later the slot in the sorted tile
 #pragma unroll
-  for (int k = 0; k < kPartIPT; ++k) {
+  for (int k = 0; k < IPT; ++k) {
     const int p = min(wave_base + k * kWave + lane, end - 1);
     lpos[k] = dig[p];
     key[k] = src.key_stream(p, f);
     val[k] = __builtin_nontemporal_load(val_in + p);
   }
 #pragma unroll
-  for (int k = 0; k < kPartIPT; ++k) {
+  for (int k = 0; k < IPT; ++k) {
     const bool valid = wave_base + k * kWave + lane < end;
     const int d = lpos[k];
     uint64_t same = __ballot(valid);
@@ -456,11 +457,21 @@ __global__ __launch_bounds__(kPart) void partition_kernel(const SRC src, const V
     int global = 0;
     if (SELF) {
       int total = 0;  // of this digit over all tiles; `global`: over the tiles before this one
+      typedef int32_t I4 __attribute__((ext_vector_type(4), aligned(4)));
+      const int32_t* counts = off + static_cast<int64_t>(d) * ntiles;
+      int q = 0;
 #pragma unroll 8
-      for (int q = 0; q < ntiles; ++q) {
-        const int x = off[static_cast<int64_t>(d) * ntiles + q];
-        total += x;
-        global += q < i0 ? x : 0;
+      for (; q + 4 <= ntiles; q += 4) {
+        const I4 x = *reinterpret_cast<const I4*>(counts + q);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          total += x[r];
+          global += q + r < i0 ? x[r] : 0;
+        }
+      }
+      for (; q < ntiles; ++q) {
+        total += counts[q];
+        global += q < i0 ? counts[q] : 0;
       }
       int incl = wave_inclusive_sum(total);
       __syncthreads();
@@ -484,7 +495,7 @@ __global__ __launch_bounds__(kPart) void partition_kernel(const SRC src, const V
   }
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < kPartIPT; ++k) {
+  for (int k = 0; k < IPT; ++k) {
     if (wave_base + k * kWave + lane < end) {
       const int d = lpos[k] >> 16;
       lpos[k] = (lpos[k] & 0xFFFF) + s_cnt[w][d];
@@ -493,9 +504,9 @@ __global__ __launch_bounds__(kPart) void partition_kernel(const SRC src, const V
     }
   }
   __syncthreads();
-  int dst[kPartIPT];
+  int dst[IPT];
 #pragma unroll
-  for (int k = 0; k < kPartIPT; ++k) {
+  for (int k = 0; k < IPT; ++k) {
     const int j = k * kPart + tid;
     if (j < tile_n) {
       dst[k] = j + s_gdelta[s_dig[j]];
@@ -504,11 +515,11 @@ __global__ __launch_bounds__(kPart) void partition_kernel(const SRC src, const V
   }
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < kPartIPT; ++k)
+  for (int k = 0; k < IPT; ++k)
     if (wave_base + k * kWave + lane < end) s_val[lpos[k]] = val[k];
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < kPartIPT; ++k) {
+  for (int k = 0; k < IPT; ++k) {
     const int j = k * kPart + tid;
     if (j < tile_n) val_out[dst[k]] = s_val[j];
   }
@@ -796,7 +807,16 @@ __global__ __launch_bounds__(kSel) void select_finish_kernel(const RcSource src,
 
 bool sample_sort_applies(int64_t n) { return n > 0 && n <= kSampleSortMax; }
 
-static int64_t tiles_bound(int64_t n) { return (n + kTile - 1) / kTile + kSegMax; }
+// Few records: a workgroup of 256 threads takes 16 of a large tile one after the other (14 us to
+// classify them and 15 to 20 to scatter them, whatever n), which tiles of 1024 cut to 8 and 9 to 12 (800 000
+// records: 115 -> 90 us; 3.2M: 204 -> 190; 6M: 257 -> 276, whose counts no longer fit the caches). A single partition's
+// workgroups each add up the counts of all tiles, so it has at most 176 of them.
+constexpr int64_t kSmallTileMax = int64_t(1) << 22;
+static int tile_of(int64_t n) {
+  if (n <= kOneLevelMax) return n <= 128 * kSmallTile ? kSmallTile : 2 * kSmallTile;
+  return n <= kSmallTileMax ? kSmallTile : kTile;
+}
+static int64_t tiles_bound(int64_t n) { return (n + tile_of(n) - 1) / tile_of(n) + kSegMax; }
 
 size_t sample_sort_workspace(int dtype, int64_t n) {
   const size_t vsz = dtype == SPT_F64 ? 8 : 4;
@@ -815,12 +835,12 @@ size_t sample_sort_workspace(int dtype, int64_t n) {
 }
 
 template <class SRC, bool LEVEL2>
-static spt_status launch_splitters(int samples, int nseg, const SRC src, const KeyForm f, int n, int nrows, int nb, int group,
+static spt_status launch_splitters(int samples, int nseg, const SRC src, const KeyForm f, int n, int nrows, int nb, int group, int tile,
                                    const int32_t* off1, int ntiles1, const Tables& T, const uint64_t* skey1, uint64_t* skey, int32_t* spos,
                                    hipStream_t s) {
 #define SPT_SPLIT(E_)                                                                                         \
   hipLaunchKernelGGL((splitters_kernel<E_, SRC, LEVEL2>), dim3(nseg), dim3(1024), 0, s, src, f, n, nrows, nb, \
-                     group, off1, ntiles1, nseg, T, skey1, skey, spos)
+                     group, tile, off1, ntiles1, nseg, T, skey1, skey, spos)
   if (samples <= 1024) SPT_SPLIT(1);
   else if (samples <= 2048) SPT_SPLIT(2);
   else SPT_SPLIT(4);
@@ -861,22 +881,31 @@ spt_status sample_sort_convert(int64_t n64, int64_t nrows, int64_t ncols, bool b
   Tables T{};
 
   // level 1
-  const int nt1 = (n + kTile - 1) / kTile;
+  const int tile = tile_of(n), nt1 = (n + tile - 1) / tile;
   // one level: final buckets; two: up to 256 buckets of sixteen final ones or more
   const int per = two ? 16 * kDirTarget : kDirTarget;
   const int nb1 = std::min(kSegMax, (n + per - 1) / per);
-  spt_status st = launch_splitters<RcSource, false>((two ? 16 : 24) * nb1, 1, rc, f, n, static_cast<int>(nrows), nb1,
-                                                    1, nullptr, 0, T, nullptr, skey1, spos1, s);
+  spt_status st = launch_splitters<RcSource, false>((two ? 16 : 14) * nb1, 1, rc, f, n, static_cast<int>(nrows), nb1,
+                                                    1, tile, nullptr, 0, T, nullptr, skey1, spos1, s);
   if (st != SPT_OK) return st;
-  const int group = nt1 >= 2048 ? kGroup : 1;  // few tiles: a workgroup for each
-  hipLaunchKernelGGL((classify_kernel<RcSource, false>), dim3((nt1 + group - 1) / group), dim3(kBlock), 0, s, rc, f,
-                     n, group, 1, T, skey1, spos1, dig, hist1);
+  const int group = nt1 >= 2048 && tile == kTile ? kGroup : 1;  // few tiles: a workgroup for each
+#define SPT_CLASSIFY(TILE_)                                                                                          \
+  hipLaunchKernelGGL((classify_kernel<RcSource, false, TILE_>), dim3((nt1 + group - 1) / group), dim3(kBlock), 0, s, \
+                     rc, f, n, group, 1, T, skey1, spos1, dig, hist1)
+  if (tile == kSmallTile) SPT_CLASSIFY(kSmallTile);
+  else if (tile == 2 * kSmallTile) SPT_CLASSIFY(2 * kSmallTile);
+  else SPT_CLASSIFY(kTile);
+#undef SPT_CLASSIFY
   SPT_CHECK_LAUNCH("classify");
   const KSource s1{k1};
   if (!two) {
     int32_t* starts = W.take<int32_t>(kSegMax + 1);
-    hipLaunchKernelGGL((partition_kernel<VT, RcSource, false, true>), dim3(nt1), dim3(kPart), 0, s, rc, vals, f, n, 1, T,
-                       dig, hist1, k1, v1, starts);
+    if (tile == kSmallTile)
+      hipLaunchKernelGGL((partition_kernel<VT, RcSource, false, kSmallTile, true>), dim3(nt1), dim3(kPart), 0, s, rc,
+                         vals, f, n, 1, T, dig, hist1, k1, v1, starts);
+    else
+      hipLaunchKernelGGL((partition_kernel<VT, RcSource, false, 2 * kSmallTile, true>), dim3(nt1), dim3(kPart), 0, s, rc,
+                         vals, f, n, 1, T, dig, hist1, k1, v1, starts);
     SPT_CHECK_LAUNCH("partition");
     hipLaunchKernelGGL((finish_kernel<VT, 1>), dim3(nb1), dim3(kFin), 0, s, s1, v1, f, nb1, static_cast<int>(nrows), T,
                        starts, nullptr, skey1, pos_out, crd_out, vals_out);
@@ -885,8 +914,12 @@ spt_status sample_sort_convert(int64_t n64, int64_t nrows, int64_t ncols, bool b
   }
   st = device_scan_i32<false>(hist1, hist1, static_cast<int64_t>(nt1) * kRadix, scan_tmp, s);
   if (st != SPT_OK) return st;
-  hipLaunchKernelGGL((partition_kernel<VT, RcSource, false>), dim3(nt1), dim3(kPart), 0, s, rc, vals, f, n, 1, T,
-                     dig, hist1, k1, v1, nullptr);
+  if (tile == kSmallTile)
+    hipLaunchKernelGGL((partition_kernel<VT, RcSource, false, kSmallTile>), dim3(nt1), dim3(kPart), 0, s, rc, vals, f, n,
+                       1, T, dig, hist1, k1, v1, nullptr);
+  else
+    hipLaunchKernelGGL((partition_kernel<VT, RcSource, false, kTile>), dim3(nt1), dim3(kPart), 0, s, rc, vals, f, n, 1, T,
+                       dig, hist1, k1, v1, nullptr);
   SPT_CHECK_LAUNCH("partition");
 
   // level 2
@@ -903,16 +936,24 @@ spt_status sample_sort_convert(int64_t n64, int64_t nrows, int64_t ncols, bool b
   T.tile_seg = W.take<int32_t>(tiles_bound(n));
   T.bucket_seg = W.take<int32_t>(n / kDirTarget + kSegMax + 1);
   st = launch_splitters<KSource, true>(32 * static_cast<int>(std::min<int64_t>(kSegMax, n64 / nb1 * 3 / 2 / kDirTarget + 1)),
-                                       nb1, s1, f, n, static_cast<int>(nrows), 0, group, hist1, nt1, T, skey1, skey2, spos2, s);
+                                       nb1, s1, f, n, static_cast<int>(nrows), 0, group, tile, hist1, nt1, T, skey1, skey2, spos2, s);
   if (st != SPT_OK) return st;
   const unsigned tiles2 = static_cast<unsigned>(tiles_bound(n));
-  hipLaunchKernelGGL((classify_kernel<KSource, true>), dim3(tiles2 / group + kSegMax), dim3(kBlock), 0, s, s1, f,
-                     n, group, nb1, T, skey2, spos2, dig, hist2);
+  if (tile == kSmallTile)
+    hipLaunchKernelGGL((classify_kernel<KSource, true, kSmallTile>), dim3(tiles2 / group + kSegMax), dim3(kBlock), 0, s, s1,
+                       f, n, group, nb1, T, skey2, spos2, dig, hist2);
+  else
+    hipLaunchKernelGGL((classify_kernel<KSource, true, kTile>), dim3(tiles2 / group + kSegMax), dim3(kBlock), 0, s, s1, f,
+                       n, group, nb1, T, skey2, spos2, dig, hist2);
   SPT_CHECK_LAUNCH("classify 2");
   st = device_scan_i32<false>(hist2, hist2, static_cast<int64_t>(tiles2) * kRadix, scan_tmp, s);
   if (st != SPT_OK) return st;
-  hipLaunchKernelGGL((partition_kernel<VT, KSource, true>), dim3(tiles2), dim3(kPart), 0, s, s1, v1, f, n, nb1, T,
-                     dig, hist2, k2, v2, nullptr);
+  if (tile == kSmallTile)
+    hipLaunchKernelGGL((partition_kernel<VT, KSource, true, kSmallTile>), dim3(tiles2), dim3(kPart), 0, s, s1, v1, f, n,
+                       nb1, T, dig, hist2, k2, v2, nullptr);
+  else
+    hipLaunchKernelGGL((partition_kernel<VT, KSource, true, kTile>), dim3(tiles2), dim3(kPart), 0, s, s1, v1, f, n, nb1, T,
+                       dig, hist2, k2, v2, nullptr);
   SPT_CHECK_LAUNCH("partition 2");
   hipLaunchKernelGGL((finish_kernel<VT, 2>), dim3(static_cast<unsigned>(n64 / kDirTarget + nb1)), dim3(kFin), 0, s,
                      KSource{k2}, v2, f, nb1, static_cast<int>(nrows), T, hist2, skey1, skey2, pos_out, crd_out,

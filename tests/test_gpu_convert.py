@@ -155,7 +155,7 @@ def test_one_row_holds_most_entries_and_columns_use_31_bits(order):
 
 # ---- the sample sort's own boundaries ----
 
-@pytest.mark.parametrize("nnz", [384, 385, 1025, 65_536, 65_537, 360_448, 360_449, 4_194_305])
+@pytest.mark.parametrize("nnz", [384, 385, 1025, 65_536, 65_537, 131_072, 131_073, 360_448, 360_449, 4_194_304, 4_194_305])
 def test_sizes_at_which_the_sample_sort_changes_its_plan(nnz):
     """One workgroup / several; one launch / one partition / two partitions."""
     N, M = 50_000, 60_000

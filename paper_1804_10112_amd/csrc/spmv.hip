@@ -505,18 +505,27 @@ __device__ __forceinline__ void csr_rows_block(int block, int nblocks, int nrows
   };
   // x at those that count (an idle lane gathers nothing), 0 at the others: all gathers of a step
   // are on their way before the first is used
-  const auto gather = [&](int p, int end, const I& c, T (&g)[K]) {
+  const auto counts = [&](int p, int end, int k) {
     const int q = min(p, nnz - K);
+    return q + k >= p && q + k < end;
+  };
+  const auto gather = [&](int p, int end, const I& c, T (&g)[K]) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       g[k] = 0;
-      if (q + k >= p && q + k < end) g[k] = x.at(c[k]);
+      if (counts(p, end, k)) g[k] = x.at(c[k]);
     }
   };
-  const auto dot = [](const V& v, const T (&g)[K]) {
+  // What does not count is not added: its value may be another row's infinity. The sum is selected, not
+  // the value, whose load a selection ahead of the gathers would wait for (7 per row, 14M entries, fp32:
+  // 19.3 against 23.3 us).
+  const auto dot = [&](int p, int end, const V& v, const T (&g)[K]) {
     T t = 0;
 #pragma unroll
-    for (int k = 0; k < K; ++k) t += v[k] * g[k];
+    for (int k = 0; k < K; ++k) {
+      const T sum = t + v[k] * g[k];
+      t = counts(p, end, k) ? sum : t;
+    }
     return t;
   };
   {
@@ -531,7 +540,7 @@ __device__ __forceinline__ void csr_rows_block(int block, int nblocks, int nrows
 #pragma unroll
     for (int r = 0; r < R; ++r) gather(a[r] + gl * K, b[r] - a[r] <= 4 * KG ? b[r] : 0, c[r], g[r]);
 #pragma unroll
-    for (int r = 0; r < R; ++r) acc[r] = dot(v[r], g[r]);
+    for (int r = 0; r < R; ++r) acc[r] = dot(a[r] + gl * K, b[r] - a[r] <= 4 * KG ? b[r] : 0, v[r], g[r]);
   }
 #pragma unroll
   for (int r = 0; r < R; ++r) {
@@ -543,7 +552,7 @@ __device__ __forceinline__ void csr_rows_block(int block, int nblocks, int nrows
         T g[K];
         load(p, c, v);
         gather(p, b[r], c, g);
-        acc[r] += dot(v, g);
+        acc[r] += dot(p, b[r], v, g);
       }
     }
     acc[r] = group_sum<G>(acc[r]);
@@ -562,7 +571,7 @@ __device__ __forceinline__ void csr_rows_block(int block, int nblocks, int nrows
 #pragma unroll
         for (int u = 0; u < 2; ++u) gather(p + u * K * kWave, lb, c[u], g[u]);
 #pragma unroll
-        for (int u = 0; u < 2; ++u) part += dot(v[u], g[u]);
+        for (int u = 0; u < 2; ++u) part += dot(p + u * K * kWave, lb, v[u], g[u]);
       }
       part = wave_total<T>(part);
       if (lane == src) acc[r] = part;

@@ -18,6 +18,13 @@ def assert_close(got, ref, mag, dtype, what=""):
                            f"mag {np.asarray(mag).ravel()[bad[:5]]}")
 
 
+def assert_close_where_finite(got, ref, mag, dtype, what=""):
+    """The infinities (with their signs) and NaNs of ref in the same places, the others as assert_close."""
+    got, ok = np.asarray(got, np.float64), np.isfinite(ref)
+    assert np.array_equal(got[~ok], ref[~ok], equal_nan=True), f"{what}: infinities or NaNs differ"
+    assert_close(got[ok], ref[ok], mag[ok], dtype, what)
+
+
 def gpu_spmv(spec, x, repeat=1, misalign=False):
     import torch
     import paper_1804_10112_amd as spt

@@ -4,7 +4,7 @@ import pytest
 
 import oracle
 import workloads as wl
-from gpu_util import assert_close, gpu_spmv
+from gpu_util import assert_close, assert_close_where_finite, gpu_spmv, gpu_spmv_sparse_x
 
 pytestmark = pytest.mark.gpu
 
@@ -346,6 +346,38 @@ def test_csr_row_lengths_at_the_edges_of_the_row_kernel(lengths, dtype):
     _check(spec, x, "csr rows")
     ref, mag = oracle.spmv(spec, x)
     assert_close(gpu_spmv(spec, x, misalign=True), ref, mag, spec.vals.dtype, "csr rows, unaligned arrays")
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("lengths", [
+    [2, 0, 2, 2], [0, 1, 2, 3, 4, 5] * 50, [7, 0, 9] * 200, [31, 0, 33, 1] * 50,
+    [16, 17, 32, 33, 64, 65, 127, 0, 128, 129, 255, 256, 257, 0] * 2 + [1] * 400,
+    [4095, 0, 4096, 4097, 1, 9001, 0] + [3] * 1500,
+], ids=lambda l: f"{len(l)}rows{sum(l)}")
+def test_csr_infinities_and_nans_stay_in_their_rows(lengths, dtype):
+    """A vector load reaches into the rows before and after: what it finds there is not multiplied.
+    Every third row with entries holds one Inf or NaN, at its start, its end or its middle."""
+    rng = np.random.default_rng(len(lengths))
+    M = 12_000
+    pos = np.concatenate([[0], np.cumsum(lengths)])
+    crd = np.concatenate([np.sort(rng.choice(M, n, replace=False)) for n in lengths]).astype(np.int32)
+    vals = rng.uniform(0.5, 1, len(crd)).astype(dtype)
+    for q, r in enumerate(np.flatnonzero(lengths)[1::3]):
+        at = (pos[r], pos[r + 1] - 1, (pos[r] + pos[r + 1]) // 2)[q % 3]
+        vals[at] = (np.inf, np.nan, -np.inf, np.inf)[q % 4]
+    x = rng.uniform(0.5, 1, M).astype(dtype)
+    rows = np.repeat(np.arange(len(lengths)), lengths)
+    plain = wl.csr_spec(len(lengths), M, pos, crd, vals)
+    ref, mag = oracle.spmv(plain, x)
+    assert np.isfinite(ref).any() and not np.isfinite(ref).all()
+    dcsr = wl.dcsr_from_sorted_coo(len(lengths), M, rows, crd, vals)
+    for spec, what in ((plain, "csr"), (_with_hint(plain, 32), "csr by rows"),
+                       (_with_hint(plain, 100_000), "csr by entries"), (dcsr, "dcsr")):
+        assert_close_where_finite(gpu_spmv(spec, x), ref, mag, dtype, what)
+    every = np.arange(M)
+    for xs in (wl.sparse_vector_spec(M, every, x), wl.hash_vector_spec(M, every, x, 2 * M)):
+        for spec in (plain, _with_hint(plain, 32)):
+            assert_close_where_finite(gpu_spmv_sparse_x(spec, xs), ref, mag, dtype, xs.name)
 
 
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])

@@ -113,6 +113,14 @@ __device__ __forceinline__ void gather_lane(const T* s_c, const T* __restrict__ 
   }
 }
 
+// The last piece: nothing is added for lanes beyond the last entry, whose c may be infinite (their value is 0).
+template <typename T>
+__device__ __forceinline__ void drop_beyond(int p0, int nnz, T (&g)[kEPL]) {
+#pragma unroll
+  for (int r = 0; r < kEPL; ++r)
+    if (p0 + r >= nnz) g[r] = T(0);
+}
+
 // A lane holds the products p[0 .. kEPL) of its consecutive entries; bit r of headmask says
 // that a fibre starts at entry r, key[r] is then that fibre's index in the output.
 // Stores the sums of the fibres that start in this piece, and the piece's carry.
@@ -282,6 +290,7 @@ __global__ __launch_bounds__(kBig) void ttv_coo_wave_kernel(
       }
       T g[kEPL];
       gather_lane<T, ALL>(s_c, c, cached, k[u], g);
+      if ((piece + 1) * kPiece > nnz) drop_beyond(piece * kPiece + lane * kEPL, nnz, g);  // uniform
       unsigned headmask = 0;
 #pragma unroll
       for (int r = 0; r < kEPL; ++r) {
@@ -356,6 +365,7 @@ __global__ __launch_bounds__(kBlock) void ttv_coo_piece_kernel(
   T g[kEPL];
 #pragma unroll
   for (int r = 0; r < kEPL; ++r) g[r] = c[k[r]];
+  if (base + kPiece > nnz) drop_beyond(p0, nnz, g);  // uniform
   int first;  // results before the piece
   if (SELF) {
     int before = 0;
@@ -479,6 +489,7 @@ __global__ __launch_bounds__(kBig) void ttv_csf_wave_kernel(
       volatile int32_t* mark = s_mark[wave_id()][u];
       T g[kEPL];
       gather_lane<T, ALL>(s_c, c, cached, k[u], g);
+      if ((piece + 1) * kPiece > nnz) drop_beyond(piece * kPiece + lane * kEPL, nnz, g);  // uniform
       __builtin_amdgcn_wave_barrier();
       int key[kEPL];
       unsigned headmask = 0;

@@ -4,7 +4,7 @@ import pytest
 
 import oracle
 import workloads as wl
-from gpu_util import assert_close, gpu_mttkrp, gpu_ttv
+from gpu_util import assert_close, assert_close_where_finite, gpu_mttkrp, gpu_ttv
 
 pytestmark = pytest.mark.gpu
 
@@ -211,6 +211,25 @@ def test_ttv_where_the_kernels_change(dtype, K, nnz):
     ci, cj, ck, v = wl.random_coo3_entries(dims, nnz, 31 + K % 7, dtype, "u01", skew=1.5)
     coo, csf = wl.coo3_spec(dims, ci, cj, ck, v), wl.csf3_from_sorted_coo(dims, ci, cj, ck, v)
     _check_ttv(coo, csf, wl.dense_vector(K, 7, dtype, "u01"), f"ttv K={K} nnz={len(v)}")
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("nnz", [3, 300, 530_001, 3_160_003])
+def test_ttv_infinities_beyond_the_last_entry_are_not_added(dtype, nnz):
+    """The last piece is partial: its idle lanes hold c of the last entry or of index 0, which is infinite."""
+    dims = (3000, 500, 4000)
+    ci, cj, ck, v = wl.random_coo3_entries(dims, nnz, 5 + nnz, dtype, "u01", skew=1.5)
+    n = len(v) - (len(v) % 256 == 0)
+    ci, cj, ck, v = ci[:n], cj[:n], ck[:n], v[:n]
+    coo, csf = wl.coo3_spec(dims, ci, cj, ck, v), wl.csf3_from_sorted_coo(dims, ci, cj, ck, v)
+    for at in (0, ck[-1]):
+        c = wl.dense_vector(dims[2], 3, dtype, "u01")
+        c[at] = np.inf
+        _, _, rv, rm = oracle.ttv(coo, c)
+        for spec in (coo, csf):
+            got = gpu_ttv(spec, c)
+            assert got[3] == len(rv)
+            assert_close_where_finite(got[2], rv, rm, dtype, f"ttv {spec.name}")
 
 
 def test_large_ttv_with_a_vector_far_beyond_lds_takes_the_chunked_kernels():

@@ -74,23 +74,25 @@ def test_recognised_compositions_have_workspace_sizes():
 
 
 def test_ttv_workspace_follows_the_kernel_choice():
-    """The query depends on the descriptor's sizes alone: below 2^18 stored entries (and for a
-    last dimension of which less than a quarter would fit LDS) the chunked kernels' carries per
-    2048 entries, from 2^18 on the carries and offsets per 256-entry piece."""
+    """The query depends on the descriptor's sizes alone. COO: head counts, offsets and carries of
+    256-entry pieces at any size. CSF: below 2^19 stored entries, and for a last dimension of which
+    less than a quarter would fit LDS, the carries per 2048 entries; else those of 256-entry pieces."""
     c5 = wl.config5(dims=(20, 16, 12), nnz=300, rank=4)
-    sizes = {}
-    for fmt in ("coo", "csf"):
+
+    def need(fmt, nvals, K=12):
         t = _host_desc(c5[fmt])
-        for nvals in ((1 << 18) - 1, 1 << 18, 1 << 24):
-            t.nvals = nvals
-            if fmt == "csf":
-                t.level[2].M = 1000          # fibres
-            sizes[fmt, nvals] = spt.spt_workspace_bytes(B.SPT_OP_TTV, t)
-        assert sizes[fmt, 1 << 18] > 4 * sizes[fmt, (1 << 18) - 1]      # 8x the carries per entry
-        assert sizes[fmt, 1 << 24] > 32 * sizes[fmt, 1 << 18]
-        t.level[2].N = 10_000_000                                       # c far beyond LDS: chunked again
-        t.nvals = 1 << 18
-        assert spt.spt_workspace_bytes(B.SPT_OP_TTV, t) < sizes[fmt, 1 << 18]
+        t.nvals, t.level[2].N = nvals, K
+        if fmt == "csf":
+            t.level[2].M = 1000                                         # fibres
+        return spt.spt_workspace_bytes(B.SPT_OP_TTV, t)
+
+    for nvals in (1 << 18, (1 << 19) - 1, 1 << 19, 1 << 24):
+        pieces, chunks = -(-nvals // 256), -(-nvals // 2048)
+        assert 20 * pieces <= need("coo", nvals) <= 24 * pieces + 8192
+        assert need("coo", nvals, 10_000_000) == need("coo", nvals)     # the same pieces with c in global memory
+        per_piece, per_chunk = range(16 * pieces, 16 * pieces + 2048), range(12 * chunks, 12 * chunks + 2048)
+        assert need("csf", nvals) in (per_piece if nvals >= 1 << 19 else per_chunk)
+        assert need("csf", nvals, 10_000_000) in per_chunk              # c far beyond LDS
 
 
 def _status(fn, *args):

@@ -106,12 +106,12 @@ typedef enum {
  *          unknown. Like the level properties of Section 3.3 it is a declared
  *          invariant that only selects between loops. CSR SpMV has two: one that gives
  *          a group of lanes to each row, and one that deals the entries out evenly
- *          whatever their rows (best for strongly skewed row lengths). The first runs
- *          without the hint or with a declared bound <= 32, the second with a larger
- *          bound; without the hint and from 2^25 stored entries on, a kernel first looks
- *          at the entry counts of the 256-row blocks and the entry-balanced loop runs if
- *          one block holds more than 1/1536 of all entries. A bound that the data
- *          violates costs time, not correctness.
+ *          whatever their rows (best for long or strongly skewed rows). The first runs
+ *          with a declared bound <= 32, the second with a larger one. Without the hint the
+ *          mean row decides: the first up to 32 entries (64 for up to 2^17 entries in all);
+ *          from 2^25 stored entries on, a kernel then looks at the entry counts of the
+ *          256-row blocks, and the entry-balanced loop runs if one block holds more than
+ *          1/1536 of all entries. A bound that the data violates costs time, not correctness.
  *   crd_stride  elements of crd between the coordinates of consecutive positions: 0 or 1 =
  *          contiguous (struct of arrays). A larger stride describes the array-of-structs
  *          variant of Section 5.2, where one interleaved array holds the coordinates of each

@@ -643,10 +643,24 @@ __global__ __launch_bounds__(kBlock) void csr_rows_if_kernel(int nblocks, int nr
 }
 constexpr int kIfBlocks = 16384;  // a multiple of the XCDs: a workgroup's blocks stay on one
 
-// Rows are skewed if declared so (max_children above kShortRow): then the entries are dealt
-// out evenly. Fewer than four entries do not fill a vector load.
-static bool csr_use_rows(int64_t nnz, int64_t nrows, int hint) {
-  return nnz >= 4 && nnz < INT32_MAX && nrows + kBlock < INT32_MAX && hint <= kShortRow;
+// By rows, or dealt out evenly in entries? A bound declared on the rows (max_children) decides; else
+// the mean row, since a row beyond kRowsWide entries keeps one workgroup busy (0.1 ms per 10^5 entries)
+// and few long rows leave the chip idle. In us, by rows / by entries, fp64, even rows and power-law rows:
+//   entries   mean 16                mean 64                mean 1024      131 072
+//   100 000   4.5 / 8.8, 6.2 / 8.8   4.8 / 8.7, 9.7 / 8.4   9.5 / 9.6
+//   1M        13 / 18, 27 / 18       14 / 17, 34 / 18       19 / 17        1277 / 17
+//   10M       102 / 115, 159 / 114   107 / 113, 221 / 112   114 / 112      1600 / 110
+// (20M entries in one row: 20 ms / 0.17 ms.) Even rows beyond a mean of 32 would gain little by rows,
+// skewed ones lose much; up to 2^17 entries, where a launch saved is half the time, twice that mean.
+// Fewer than four entries do not fill a vector load. By entries takes a workspace: a caller who was not told
+// to need one (no bound declared) and brings none has its rows walked.
+constexpr int64_t kRowsMean = kShortRow, kRowsFew = int64_t(1) << 17;
+size_t seg_spmv_workspace(int64_t nnz);
+static bool csr_use_rows(int64_t nnz, int64_t nrows, int hint, const void* ws, size_t ws_bytes) {
+  if (nnz < 4 || nnz >= INT32_MAX || nrows + kBlock >= INT32_MAX) return false;
+  if (hint > 0) return hint <= kShortRow;
+  if (nnz <= nrows * kRowsMean * (nnz <= kRowsFew ? 2 : 1)) return true;
+  return !ws || ws_bytes < seg_spmv_workspace(nnz);
 }
 
 template <typename T, class XP>
@@ -946,7 +960,6 @@ constexpr int kSegIPT = 8;
 // Ordered COO of more entries: waves that hold 256 each gain nothing over workgroups of 2048 (40M
 // entries, fp64, uniform rows 709 against 705 us, power law 664 against 645), and leave more carries.
 constexpr int64_t kPiecesMaxEntries = int64_t(1) << 24;
-size_t seg_spmv_workspace(int64_t nnz);
 size_t ordered_coo_workspace(int64_t nnz) {
   if (nnz > kPiecesMaxEntries) return seg_spmv_workspace(nnz);
   const int64_t np = (nnz + kSmallPiece - 1) / kSmallPiece;
@@ -1076,7 +1089,7 @@ static spt_status spmv_sparse_x_typed(const spt_tensor* A, const spt_tensor* X, 
   const int64_t nnz = A->nvals, N = A->level[0].N;
   const T* vals = static_cast<const T*>(A->vals);
   if (X->nvals >= INT32_MAX) return fail(SPT_ERR_UNSUPPORTED, "spmv: x too large");
-  const bool rows = csr_use_rows(nnz, N, A->level[1].max_children);
+  const bool rows = csr_use_rows(nnz, N, A->level[1].max_children, ws, ws_bytes);
   if (L.kind == SPT_HASHED) {
     if (L.M < 1) return fail(SPT_ERR_INVALID_ARG, "spmv: hashed x needs a table width W >= 1");
     if (rows)
@@ -1139,7 +1152,7 @@ static spt_status spmv_typed(Format f, const spt_tensor* A, const T* x, T* y, vo
       T* t = reinterpret_cast<T*>(W.take<double>(stored));
       char* rest = static_cast<char*>(ws) + W.used;
       const int hint = A->level[1].max_children;
-      if (csr_use_rows(A->nvals, stored, hint))
+      if (csr_use_rows(A->nvals, stored, hint, rest, ws_bytes - W.used))
         st = launch_csr_rows<T>(A->nvals, stored, A->level[1].pos, A->level[1].crd, vals, DenseX<T>{x}, t, s);
       else
         st = launch_seg<T, true>(A->nvals, stored, A->level[1].pos, A->level[1].crd, vals, x, t, rest,
@@ -1154,7 +1167,7 @@ static spt_status spmv_typed(Format f, const spt_tensor* A, const T* x, T* y, vo
       const int hint = A->level[1].max_children;
       const int64_t nnz = A->nvals, N = A->level[0].N;
       const int32_t *pos = A->level[1].pos, *crd = A->level[1].crd;
-      if (!csr_use_rows(nnz, N, hint)) return launch_seg<T, true>(nnz, N, pos, crd, vals, x, y, ws, ws_bytes, s);
+      if (!csr_use_rows(nnz, N, hint, ws, ws_bytes)) return launch_seg<T, true>(nnz, N, pos, crd, vals, x, y, ws, ws_bytes, s);
       if (hint > 0 || nnz < kDynamicMinEntries) return launch_csr_rows<T>(nnz, N, pos, crd, vals, DenseX<T>{x}, y, s);
       if (!ws || ws_bytes < seg_spmv_workspace(nnz))
         return fail(SPT_ERR_WORKSPACE, "spmv: workspace of %zu bytes needed, %zu given", seg_spmv_workspace(nnz),
@@ -1283,7 +1296,7 @@ spt_status csr_rows_reduce(int dtype, int64_t nnz, int64_t nrows, const int32_t*
   // (the head slices hold fibres of hundreds of entries, the rest single entries: 0.37 ms
   // against 1.24 ms with the streamed kernel on 50M entries in 8.1M fibres); few entries, where
   // one launch is what counts, by rows (50 000 entries, fp64: 7.4 instead of 11 us; 1M skewed ones take longer)
-  if (nnz < (1 << 19) && csr_use_rows(nnz, nrows, 0)) {
+  if (nnz < (1 << 19) && csr_use_rows(nnz, nrows, 0, ws, ws_bytes)) {
     if (dtype == SPT_F64)
       return launch_csr_rows<double>(nnz, nrows, pos, crd, static_cast<const double*>(vals),
                                      DenseX<double>{static_cast<const double*>(x)}, static_cast<double*>(out), s);

@@ -342,10 +342,12 @@ def test_csr_row_lengths_at_the_edges_of_the_row_kernel(lengths, dtype):
     crd = np.concatenate([np.sort(rng.choice(M, n, replace=False)) for n in lengths]).astype(np.int32)
     vals = rng.uniform(-1, 1, len(crd)).astype(dtype)
     x = rng.uniform(-1, 1, M).astype(dtype)
-    spec = wl.csr_spec(len(lengths), M, pos, crd, vals)
+    # a declared bound of 32 (violated here and there) takes the matrix by rows whatever its mean row
+    spec = _with_hint(wl.csr_spec(len(lengths), M, pos, crd, vals), 32)
     _check(spec, x, "csr rows")
     ref, mag = oracle.spmv(spec, x)
     assert_close(gpu_spmv(spec, x, misalign=True), ref, mag, spec.vals.dtype, "csr rows, unaligned arrays")
+    assert_close(gpu_spmv(_with_hint(spec, 0), x), ref, mag, spec.vals.dtype, "csr by the mean row")
 
 
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])
@@ -378,6 +380,84 @@ def test_csr_infinities_and_nans_stay_in_their_rows(lengths, dtype):
     for xs in (wl.sparse_vector_spec(M, every, x), wl.hash_vector_spec(M, every, x, 2 * M)):
         for spec in (plain, _with_hint(plain, 32)):
             assert_close_where_finite(gpu_spmv_sparse_x(spec, xs), ref, mag, dtype, xs.name)
+
+
+def _device_matrix(rows, nnz, dcsr):
+    """nnz entries dealt out evenly to the rows, anywhere in 10^6 columns; arrays on the GPU."""
+    import torch
+    import paper_1804_10112_amd as spt
+    M = 1_000_000
+    A = spt.DeviceTensor((wl.dcsr_from_sorted_coo if dcsr else wl.csr_from_sorted_coo)(
+        rows, M, np.arange(rows), np.zeros(rows, np.int64), np.ones(rows, np.float32)))
+    pos = (torch.arange(rows + 1, device="cuda") * nnz // rows).int()
+    crd = torch.randint(0, M, (nnz,), device="cuda", dtype=torch.int32)
+    vals = torch.rand(nnz, device="cuda")
+    A.c.level[1].pos, A.c.level[1].crd, A.c.vals, A.c.nvals = pos.data_ptr(), crd.data_ptr(), vals.data_ptr(), nnz
+    return A, (pos, crd, vals)
+
+
+@pytest.mark.parametrize("nnz,rows", [(20_000_000, 1), (10_000_000, 100), (500_000, 3)])
+@pytest.mark.parametrize("form", ["csr", "dcsr", "sparse x", "hashed x", "ttv csf"])
+def test_few_long_rows_do_not_wait_for_one_workgroup(nnz, rows, form):
+    """The same entries in few rows and in rows of 16 take about the same time: by rows, a workgroup
+    per long row, they took 10 to 100 times as long. And the sums are right."""
+    import torch
+    import paper_1804_10112_amd as spt
+    M = 1_000_000
+    xd = torch.rand(M, device="cuda")
+    X = {"sparse x": wl.sparse_vector_spec(M, np.arange(64) * 15_000, np.ones(64, np.float32)),
+         "hashed x": wl.hash_vector_spec(M, np.arange(64) * 15_000, np.ones(64, np.float32), 128)}.get(form)
+    if X is not None:
+        xd = torch.zeros(M, device="cuda")
+        xd[torch.arange(64, device="cuda") * 15_000] = 1
+        X = spt.DeviceTensor(X)
+    if form == "ttv csf":
+        nnz = min(nnz, (1 << 19) - 1)   # above, TTV walks over entries anyway
+
+    def best(n_rows):
+        A, keep = _device_matrix(n_rows, nnz, form == "dcsr")
+        y = torch.empty(n_rows, device="cuda")
+        ws = A.workspace(spt.SPT_OP_SPMV)
+        if form == "ttv csf":
+            B = spt.DeviceTensor(wl.csf3_from_sorted_coo((1, n_rows, M), np.zeros(n_rows, np.int64), np.arange(n_rows),
+                                                         np.zeros(n_rows, np.int64), np.ones(n_rows, np.float32)))
+            B.c.level[2].pos, B.c.level[2].crd, B.c.vals, B.c.nvals = A.c.level[1].pos, A.c.level[1].crd, A.c.vals, nnz
+            count = torch.zeros(1, dtype=torch.int64, device="cuda")
+            ws = B.workspace(spt.SPT_OP_TTV)
+        times = []
+        for _ in range(4):
+            start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            start.record()
+            if form == "ttv csf":
+                spt.spt_ttv(B, xd, None, None, y, count, ws)
+            elif X is not None:
+                spt.spt_spmv_sparse_x(A, X, y, ws)
+            else:
+                spt.spt_spmv(A, xd, y, ws)
+            end.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(end))
+        pos, crd, vals = keep
+        terms = vals.double() * xd[crd.long()].double()
+        before = torch.cat([torch.zeros(1, device="cuda", dtype=torch.float64), terms.cumsum(0)])
+        ref = (before[pos[1:].long()] - before[pos[:-1].long()]).cpu().numpy()
+        # no term is negative; ref itself, a difference of running sums up to 10^7, is right to 1e-8
+        assert_close(y.cpu().numpy(), ref, ref + 1e-3, np.float32, f"{form} {n_rows} rows")
+        return min(times)
+
+    long, short = best(rows), best(nnz // 16)
+    assert long < 3 * short + 0.05, f"{form}: {long:.3f} ms in {rows} rows, {short:.3f} ms in rows of 16"
+
+
+@pytest.mark.parametrize("nnz,rows", [(1000, 2), (40_000, 5)])
+def test_csr_long_rows_without_a_workspace_are_walked(nnz, rows):
+    import torch
+    import paper_1804_10112_amd as spt
+    A, (pos, crd, vals) = _device_matrix(rows, nnz, False)
+    x, y = torch.rand(1_000_000, device="cuda"), torch.empty(rows, device="cuda")
+    spt.spt_spmv(A, x, y, None)
+    ref = (vals.double() * x[crd.long()].double()).reshape(rows, -1).sum(1).cpu().numpy()
+    assert_close(y.cpu().numpy(), ref, ref, np.float32, "no workspace")
 
 
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])

@@ -210,7 +210,11 @@ __global__ __launch_bounds__(kAccBlock) void bin_accumulate_kernel(
   const int k = item - t.first[b];
   const bool whole_bin = t.first[b + 1] - t.first[b] == 1;
   const int begin = t.start[b] + k * cut.slice;
-  const int end = whole_bin ? t.start[b + 1] : min(begin + cut.slice, t.start[b + 1]);
+  const int len = whole_bin ? t.start[b + 1] - begin : min(cut.slice, t.start[b + 1] - begin);
+  // from here on entries are counted from the slice's first: the pipeline looks up to 23 551 entries past its
+  // end, and the last slice may end that close to 2^31
+  brow += begin;
+  bprod += begin;
   const int64_t r0 = digit.first(b) + (int64_t)sub * RB;  // first row of this sub-range
   const int nr = (int)max<int64_t>(0, min<int64_t>(RB, digit.first(b + 1) - r0));
 
@@ -224,7 +228,7 @@ __global__ __launch_bounds__(kAccBlock) void bin_accumulate_kernel(
   const auto load = [&](int p0, int32_t (&rr)[U], T (&vv)[U]) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int p = min(p0 + u * kAccBlock, end - 1);
+      const int p = min(p0 + u * kAccBlock, len - 1);
       rr[u] = ld_nt(brow + p);
       vv[u] = ld_nt(bprod + p);
     }
@@ -233,12 +237,12 @@ __global__ __launch_bounds__(kAccBlock) void bin_accumulate_kernel(
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint32_t q = static_cast<uint32_t>(rr[u] - static_cast<int>(r0));
-      if (p0 + u * kAccBlock < end && q < static_cast<uint32_t>(nr)) atomicAdd(&s_acc[q], vv[u]);
+      if (p0 + u * kAccBlock < len && q < static_cast<uint32_t>(nr)) atomicAdd(&s_acc[q], vv[u]);
     }
   };
   constexpr int kStep = U * kAccBlock;
-  if (begin < end) load(begin + tid, r[0], v[0]);
-  for (int p0 = begin + tid; p0 - tid < end; p0 += 2 * kStep) {
+  if (len > 0) load(tid, r[0], v[0]);
+  for (int p0 = tid; p0 - tid < len; p0 += 2 * kStep) {
     load(p0 + kStep, r[1], v[1]);
     add(p0, r[0], v[0]);
     load(p0 + 2 * kStep, r[0], v[0]);

@@ -497,34 +497,36 @@ __device__ __forceinline__ void csr_rows_block(int block, int nblocks, int nrows
   if (tid == 0) s_nwide = 0;
   T acc[R];
   bool wide = false;
-  // K entries from p on, of which those before `end` count; loads stay inside the arrays
-  const auto load = [&](int p, I& c, V& v) {
-    const int q = min(p, nnz - K);
+  // K entries from `off` on in the row that begins at `base`; loads stay inside the arrays, and no index
+  // passes nnz, which may be 2^31 - 2
+  const int lastv = nnz - K;
+  const auto load = [&](int base, int off, I& c, V& v) {
+    const int q = base + min(off, lastv - base);
     c = NT ? __builtin_nontemporal_load(reinterpret_cast<const I*>(crd + q)) : *reinterpret_cast<const I*>(crd + q);
     v = NT ? __builtin_nontemporal_load(reinterpret_cast<const V*>(vals + q)) : *reinterpret_cast<const V*>(vals + q);
   };
-  // x at those that count (an idle lane gathers nothing), 0 at the others: all gathers of a step
-  // are on their way before the first is used
-  const auto counts = [&](int p, int end, int k) {
-    const int q = min(p, nnz - K);
-    return q + k >= p && q + k < end;
+  // x at those that count (they belong to the row, of `len` entries; an idle lane gathers nothing), 0 at the
+  // others: all gathers of a step are on their way before the first is used
+  const auto counts = [&](int base, int off, int len, int k) {
+    const int q = min(off, lastv - base);
+    return q + k >= off && q + k < len;
   };
-  const auto gather = [&](int p, int end, const I& c, T (&g)[K]) {
+  const auto gather = [&](int base, int off, int len, const I& c, T (&g)[K]) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       g[k] = 0;
-      if (counts(p, end, k)) g[k] = x.at(c[k]);
+      if (counts(base, off, len, k)) g[k] = x.at(c[k]);
     }
   };
   // What does not count is not added: its value may be another row's infinity. The sum is selected, not
   // the value, whose load a selection ahead of the gathers would wait for (7 per row, 14M entries, fp32:
   // 19.3 against 23.3 us).
-  const auto dot = [&](int p, int end, const V& v, const T (&g)[K]) {
+  const auto dot = [&](int base, int off, int len, const V& v, const T (&g)[K]) {
     T t = 0;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       const T sum = t + v[k] * g[k];
-      t = counts(p, end, k) ? sum : t;
+      t = counts(base, off, len, k) ? sum : t;
     }
     return t;
   };
@@ -532,27 +534,29 @@ __device__ __forceinline__ void csr_rows_block(int block, int nblocks, int nrows
     I c[R];
     V v[R];
     T g[R][K];
+    int len[R];  // a row for the whole wave or workgroup is left out
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int p = a[r] + gl * K;
-      load(p < b[r] ? p : a[r], c[r], v[r]);  // an idle lane reads what its row's first lane reads
+      len[r] = b[r] - a[r];
+      load(a[r], gl * K < len[r] ? gl * K : 0, c[r], v[r]);  // an idle lane reads what its row's first lane reads
+      if (len[r] > 4 * KG) len[r] = 0;
     }
 #pragma unroll
-    for (int r = 0; r < R; ++r) gather(a[r] + gl * K, b[r] - a[r] <= 4 * KG ? b[r] : 0, c[r], g[r]);
+    for (int r = 0; r < R; ++r) gather(a[r], gl * K, len[r], c[r], g[r]);
 #pragma unroll
-    for (int r = 0; r < R; ++r) acc[r] = dot(a[r] + gl * K, b[r] - a[r] <= 4 * KG ? b[r] : 0, v[r], g[r]);
+    for (int r = 0; r < R; ++r) acc[r] = dot(a[r], gl * K, len[r], v[r], g[r]);
   }
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int len = b[r] - a[r];
     if (len > KG && len <= 4 * KG) {
-      for (int p = a[r] + KG + gl * K; p < b[r]; p += KG) {
+      for (int off = KG + gl * K; off < len; off += KG) {
         I c;
         V v;
         T g[K];
-        load(p, c, v);
-        gather(p, b[r], c, g);
-        acc[r] += dot(p, b[r], v, g);
+        load(a[r], off, c, v);
+        gather(a[r], off, len, c, g);
+        acc[r] += dot(a[r], off, len, v, g);
       }
     }
     acc[r] = group_sum<G>(acc[r]);
@@ -560,18 +564,18 @@ __device__ __forceinline__ void csr_rows_block(int block, int nblocks, int nrows
     while (todo) {
       const int src = __ffsll(static_cast<long long>(todo)) - 1;
       todo &= todo - 1;
-      const int la = __shfl(a[r], src), lb = __shfl(b[r], src);
+      const int base = __builtin_amdgcn_readlane(a[r], src), wlen = __builtin_amdgcn_readlane(len, src);
       T part = 0;
-      for (int p = la + lane * K; p < lb; p += 2 * K * kWave) {
+      for (int off = lane * K; off < wlen; off += 2 * K * kWave) {
         I c[2];
         V v[2];
         T g[2][K];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) load(p + u * K * kWave, c[u], v[u]);
+        for (int u = 0; u < 2; ++u) load(base, off + u * K * kWave, c[u], v[u]);
 #pragma unroll
-        for (int u = 0; u < 2; ++u) gather(p + u * K * kWave, lb, c[u], g[u]);
+        for (int u = 0; u < 2; ++u) gather(base, off + u * K * kWave, wlen, c[u], g[u]);
 #pragma unroll
-        for (int u = 0; u < 2; ++u) part += dot(p + u * K * kWave, lb, v[u], g[u]);
+        for (int u = 0; u < 2; ++u) part += dot(base, off + u * K * kWave, wlen, v[u], g[u]);
       }
       part = wave_total<T>(part);
       if (lane == src) acc[r] = part;
@@ -588,23 +592,40 @@ __device__ __forceinline__ void csr_rows_block(int block, int nblocks, int nrows
   const int nwide = s_nwide;
   for (int w = 0; w < nwide; ++w) {
     const int r = s_wide[w];
-    const int la = pos[r], lb = pos[r + 1];
+    const int la = pos[r], len = pos[r + 1] - la;
+    constexpr int U = 8;  // entries of a thread in flight
+    const int whole = len / (U * kBlock);
+    const int32_t* rc = crd + la + tid;
+    const T* rv = vals + la + tid;
     T part = 0;
-    for (int p = la + tid; p < lb; p += 8 * kBlock) {
-      int32_t c[8];
-      T v[8];
+    for (int round = 0; round < whole; ++round) {
+      int32_t c[U];
+      T v[U];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int q = min(p + u * kBlock, lb - 1);
-        c[u] = crd[q];
-        v[u] = vals[q];
+      for (int u = 0; u < U; ++u) {
+        c[u] = rc[u * kBlock];
+        v[u] = rv[u * kBlock];
       }
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const T t = v[u] * x.at(c[u]);
-        part += p + u * kBlock < lb ? t : T(0);
+      for (int u = 0; u < U; ++u) part += v[u] * x.at(c[u]);
+      rc += U * kBlock;
+      rv += U * kBlock;
+    }
+    const int left = len - whole * (U * kBlock) - tid;  // of the row, from this thread's next entry on
+    int32_t c[U];
+    T v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      c[u] = 0;  // left unset, they take the whole kernel from 58 registers to 90 (fp64; 36.8 -> 43.6 us)
+      v[u] = 0;
+      if (u * kBlock < left) {
+        c[u] = rc[u * kBlock];
+        v[u] = rv[u * kBlock];
       }
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (u * kBlock < left) part += v[u] * x.at(c[u]);
     part = wave_total<T>(part);
     if (lane == 0) s_part[wave_id()] = part;
     __syncthreads();

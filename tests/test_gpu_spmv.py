@@ -519,3 +519,37 @@ def test_ordered_coo_on_both_sides_of_the_largest_in_pieces():
     r, c, v = np.sort(rng.integers(0, 400_000, n)), rng.integers(0, 9000, n), rng.uniform(-1, 1, n)
     for m in (n, n - 1):
         _check(wl.coo_spec(400_000, 9000, r[:m], c[:m], v[:m]), wl.dense_vector(9000, 5, np.float64), f"nnz={m}")
+
+
+@pytest.mark.parametrize("form", ["unordered coo", "csr", "csr, long rows"])
+def test_entries_up_to_the_largest_index(form):
+    """As many entries as each path takes: what its loops look ahead passes 2^31. All values and x are
+    one, so that every sum is the (exact) length of its row."""
+    import torch
+    import paper_1804_10112_amd as spt
+    if torch.cuda.mem_get_info()[0] < 100 << 30:
+        pytest.skip("needs 100 GB of device memory")
+    N, M = 700_001, 1000
+    n = (1 << 31) - 4098 if form == "unordered coo" else (1 << 31) - 2
+    i32 = dict(dtype=torch.int32, device="cuda")
+    col = torch.arange(n, **i32).remainder_(M)
+    vals, x = torch.ones(n, device="cuda"), torch.ones(M, device="cuda")
+    if form == "unordered coo":
+        row = torch.arange(n, **i32).remainder_(N)
+        A = spt.DeviceTensor(wl.coo_spec(N, M, [0], [0], np.ones(1, np.float32), ordered=False))
+        A.c.level[0].crd, A.c.level[1].crd = row.data_ptr(), col.data_ptr()
+        length = n // N + (torch.arange(N, device="cuda") < n % N)
+    else:
+        N = n // 16 if form == "csr" else 400_000
+        length = torch.full((N,), n // N, device="cuda")
+        length[-1] += n % N                                # the last row is the longest, and ends the arrays
+        pos = torch.cat([torch.zeros(1, dtype=torch.int64, device="cuda"), length.cumsum(0)]).int()
+        A = spt.DeviceTensor(wl.csr_spec(1, M, [0, 1], [0], np.ones(1, np.float32), max_row=16))
+        A.c.level[0].N = A.c.level[1].M = N
+        A.c.level[1].pos, A.c.level[1].crd = pos.data_ptr(), col.data_ptr()
+    A.c.vals, A.c.nvals = vals.data_ptr(), n
+    y = torch.full((N,), -1.0, device="cuda")
+    spt.spt_spmv(A, x, y, A.workspace(spt.SPT_OP_SPMV))
+    assert torch.equal(y, length.float())
+    del col, vals, y, length
+    torch.cuda.empty_cache()

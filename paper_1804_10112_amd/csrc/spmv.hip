@@ -728,16 +728,52 @@ static spt_status launch_csr_rows(int64_t nnz, int64_t nrows, const int32_t* pos
 }
 
 // ---------------------------------------------------------------- unsorted COO
-// The fused single loop over all entries of the paper's COO kernel: a scatter
-// into y (Section 4.5, fusing iterators), one atomic add per entry.
+// The fused single loop over all entries of the paper's COO kernel: a scatter into y (Section 4.5, fusing
+// iterators). Bound by the atomics in global memory, which one address takes at 12 ns each, the whole of it at
+// 20 G a second. A workgroup therefore adds up its 1024 entries in a table of rows in LDS first (the first row
+// that meets a slot has it, the others of that slot go straight to y) and then adds each slot to y. In us,
+// fp64, against one atomic an entry:
+//   entries                        20 000       100 000      400 000      786 000
+//   uniform rows                   7.1 / 6.7    8.3 / 8.5     22 / 22      41 / 41
+//   power law                       19 / 7.2     24 / 9.7     39 / 23      70 / 48
+//   half of them in one row        124 / 6.9    607 / 7.0   2402 / 20    4723 / 30
+// (512 entries and 1024 slots: 55 us for the last power law; 2048 and 2048: 43, but 7.5 to 9 us for few entries.)
+constexpr int kScatterPerLane = 4, kScatterEntries = kScatterPerLane * kBlock;
+constexpr int kScatterSlotBits = 10;
 template <typename T>
 __global__ __launch_bounds__(kBlock) void coo_atomic_spmv_kernel(
     int nnz, const int32_t* __restrict__ row, const int32_t* __restrict__ col,
     const T* __restrict__ vals, const T* __restrict__ x, T* __restrict__ y) {
-  const int p = blockIdx.x * kBlock + threadIdx.x;
-  if (p >= nnz) return;
-  const T prod = ld_stream(vals + p) * x[ld_stream(col + p)];
-  unsafeAtomicAdd(y + ld_stream(row + p), prod);
+  constexpr int kSlots = 1 << kScatterSlotBits;
+  __shared__ int32_t s_row[kSlots];
+  __shared__ T s_sum[kSlots];
+  const int tid = threadIdx.x;
+  const int base = blockIdx.x * kScatterEntries;
+  int32_t r[kScatterPerLane];
+  T prod[kScatterPerLane];
+#pragma unroll
+  for (int e = 0; e < kScatterPerLane; ++e) {
+    const int p = min(base + e * kBlock + tid, nnz - 1);
+    r[e] = ld_stream(row + p);
+    prod[e] = ld_stream(vals + p) * x[ld_stream(col + p)];
+  }
+  for (int q = tid; q < kSlots; q += kBlock) {
+    s_row[q] = -1;
+    s_sum[q] = T(0);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < kScatterPerLane; ++e) {
+    if (base + e * kBlock + tid < nnz) {
+      const int slot = static_cast<uint32_t>(r[e]) * 2654435769u >> (32 - kScatterSlotBits);
+      const int owner = atomicCAS(&s_row[slot], -1, r[e]);
+      if (owner == -1 || owner == r[e]) atomicAdd(&s_sum[slot], prod[e]);
+      else unsafeAtomicAdd(y + r[e], prod[e]);
+    }
+  }
+  __syncthreads();
+  for (int q = tid; q < kSlots; q += kBlock)
+    if (s_row[q] >= 0) unsafeAtomicAdd(y + s_row[q], s_sum[q]);
 }
 
 // ---------------------------------------------------------------- sorted COO, small
@@ -968,8 +1004,12 @@ spt_status coo_binned_spmv(int64_t nnz, int64_t nrows, const int32_t* row, const
                            const T* vals, const T* x, T* y, void* ws, size_t ws_bytes,
                            hipStream_t s);
 size_t coo_binned_workspace(int dtype, int64_t nnz, int64_t nrows);
-// Below this one atomic per entry is cheaper than the six launches of the binned scatter (us, fp64 and
-// uniform rows: 50 000 entries 6.4 against 55, 400 000: 23 against 68, 1.6M: 77 against 62).
+// Below this the scatter with atomics is cheaper than the six launches of the binned one. In us, scatter /
+// binned, fp64 (fp32 alike; CSC the same and 3 to 7 for its columns):
+//   entries                   100 000     400 000    786 000      1.6M
+//   uniform rows              8.5 / 40    22 / 44    41 / 51    77 / 58
+//   power law                 9.7 / 40    23 / 44    48 / 54    91 / 70
+//   half of them in one row   7.0 / 49    20 / 54    30 / 63    60 / 78
 constexpr int64_t kBinnedMinEntries = 3 << 18;
 
 size_t coo_unordered_workspace(int dtype, int64_t nnz, int64_t nrows) {
@@ -1222,7 +1262,7 @@ static spt_status spmv_typed(Format f, const spt_tensor* A, const T* x, T* y, vo
                                   static_cast<char*>(ws) + W.used, ws_bytes - W.used, s);
       st = launch_fill<T>(y, N, T(0), s);
       if (st != SPT_OK) return st;
-      hipLaunchKernelGGL(coo_atomic_spmv_kernel<T>, dim3((unsigned)((nnz + kBlock - 1) / kBlock)),
+      hipLaunchKernelGGL(coo_atomic_spmv_kernel<T>, dim3((unsigned)((nnz + kScatterEntries - 1) / kScatterEntries)),
                          dim3(kBlock), 0, s, (int)nnz, A->level[1].crd, cols, vals, x, y);
       SPT_CHECK_LAUNCH("coo_atomic_spmv");
       return SPT_OK;
@@ -1245,7 +1285,7 @@ static spt_status spmv_typed(Format f, const spt_tensor* A, const T* x, T* y, vo
                                   s);
       spt_status st = launch_fill<T>(y, N, T(0), s);
       if (st != SPT_OK || nnz == 0) return st;
-      hipLaunchKernelGGL(coo_atomic_spmv_kernel<T>, dim3((unsigned)((nnz + kBlock - 1) / kBlock)),
+      hipLaunchKernelGGL(coo_atomic_spmv_kernel<T>, dim3((unsigned)((nnz + kScatterEntries - 1) / kScatterEntries)),
                          dim3(kBlock), 0, s, (int)nnz, A->level[0].crd, A->level[1].crd, vals, x,
                          y);
       SPT_CHECK_LAUNCH("coo_atomic_spmv");

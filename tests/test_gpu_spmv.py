@@ -484,6 +484,48 @@ def test_dia_and_ell_at_any_row_count(N, dtype):
 
 
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("nnz", [1, 255, 256, 1023, 1024, 1025, 30_001])
+def test_unordered_coo_and_csc_by_atomics(nnz, dtype):
+    """Around the 1024 entries of a workgroup; one row, few rows, and more rows than the table has slots."""
+    rng = np.random.default_rng(nnz)
+    M = 700
+    for N in (1, 3, 900, 5000, 3_000_000):
+        r, c = rng.integers(0, N, nnz), rng.integers(0, M, nnz)
+        v = rng.uniform(-1, 1, nnz).astype(dtype)
+        v[nnz // 2] = np.inf
+        x = rng.uniform(0.5, 1, M).astype(dtype)
+        ref, mag = oracle.spmv(wl.coo_spec(N, M, r, c, v, ordered=False), x)
+        for spec in (wl.coo_spec(N, M, r, c, v, ordered=False), wl.csc_from_coo(N, M, r, c, v)):
+            assert_close_where_finite(gpu_spmv(spec, x), ref, mag, dtype, f"{spec.name} nnz={nnz} N={N}")
+
+
+def test_unordered_coo_with_a_heavy_row_takes_no_longer():
+    """Half of 400 000 entries in one row: with an atomic for each, 2.4 ms instead of 0.02."""
+    import torch
+    import paper_1804_10112_amd as spt
+    n, N, M = 400_000, 25_000, 25_000
+    rng = np.random.default_rng(2)
+    times = []
+    for heavy in (0, n // 2):
+        r = rng.integers(0, N, n)
+        r[:heavy] = N // 3
+        A = spt.DeviceTensor(wl.coo_spec(N, M, rng.permutation(r), rng.integers(0, M, n), np.ones(n), ordered=False))
+        x, y = torch.ones(M, dtype=torch.float64, device="cuda"), torch.empty(N, dtype=torch.float64, device="cuda")
+        ws = A.workspace(spt.SPT_OP_SPMV)
+        best = 1e9
+        for _ in range(5):
+            start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            start.record()
+            spt.spt_spmv(A, x, y, ws)
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, start.elapsed_time(end))
+        times.append(best)
+        assert np.array_equal(y.cpu().numpy(), np.bincount(r, minlength=N))
+    assert times[1] < 3 * times[0] + 0.05, f"{times[1]:.3f} ms with a heavy row, {times[0]:.3f} without"
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
 @pytest.mark.parametrize("nnz", [786_431, 786_432, 786_433, 1_100_003])
 def test_unordered_coo_where_binning_begins(nnz, dtype):
     rng = np.random.default_rng(nnz)

@@ -19,9 +19,11 @@
 // order: the result is that of a stable sort.
 // pos (Table 3: running sum of the row counts) falls out of the last step: the workgroup of the
 // keys between splitters of rows a and b stores pos[a+1 .. b].
-// A bucket that the sample got wrong (more records than fit LDS; its chance is below 1e-4 per
-// call for any input that does not know the sampling positions) is ranked by counting, slowly
-// but correctly.
+// A bucket that the sample got wrong (more records than fit LDS) is split once more by its workgroup,
+// at splitters of a sample of its own. In random order that happens in none of 300 calls up to 50M
+// records, but in some 2 to 5 of 100 at 60M and 15 of 100 at 2^26, where 256 buckets of a segment are
+// not enough for the larger segments; the call takes no longer for it (60M records, two such inputs of
+// 60: 1.80 ms; with the ranks of the bucket's records counted, 10.4 ms).
 //
 // Measured against the six radix passes it replaces (fp64): 60M records with power-law rows
 // 3.09 -> 1.80 ms (splitters 35 + 87 us, classify 2 x 150, scans 4 x 9, partitions 427 + 441,
@@ -553,7 +555,7 @@ __device__ __forceinline__ void store_entries(const uint16_t* ord, int n, int fi
   }
 }
 
-// A bucket with more records than fit: every record's rank is counted. `in` tells whether the
+// The last resort for more records than fit: every record's rank is counted. `in` tells whether the
 // record at a position belongs to the bucket.
 template <int NT, typename VT, class SRC, class IN>
 __device__ void rank_and_store(const SRC& src, int begin, int end, const IN& in, int n, int first, int lo_row,
@@ -589,6 +591,87 @@ __device__ void rank_and_store(const SRC& src, int begin, int end, const IN& in,
   }
 }
 
+// Puts n positions in order.
+template <int NT, int E>
+__device__ __forceinline__ void sort_positions(uint32_t* at, int n) {
+  uint32_t v[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int i = e * NT + static_cast<int>(threadIdx.x);
+    v[e] = i < n ? at[i] : ~0u;
+  }
+  __syncthreads();
+  block_sort_u32<NT, E>(v, at);
+}
+
+// A bucket with more records than fit is split once more: at splitters of a sample of its own, as in the
+// selection from a small input, one part after the other. (A part that is too large again has its records'
+// ranks counted.)
+constexpr int kSplitSamples = 512;
+constexpr int kSplitBytes = kSplitSamples * 10 + kStaged * 10 + 16;
+template <int NT, typename VT>
+__device__ __forceinline__ void split_and_store(char* mem, const KSource& src, int begin, int end, uint64_t lo_key,
+                                                uint64_t hi_key, int lo_row, int hi_row, const KeyForm& f,
+                                                const VT* __restrict__ val_in, int32_t* __restrict__ pos,
+                                                int32_t* __restrict__ crd_out, VT* __restrict__ val_out) {
+  constexpr int S = kSplitSamples, E = kStaged / NT;
+  uint64_t* s_key = reinterpret_cast<uint64_t*>(mem);
+  uint32_t* words = reinterpret_cast<uint32_t*>(mem + S * 8);
+  uint32_t* at = words + kStaged;
+  uint16_t* ord = reinterpret_cast<uint16_t*>(at + kStaged);
+  uint16_t* s_ord = ord + kStaged;
+  int* s_cnt = reinterpret_cast<int*>(s_ord + S);
+  const int tid = threadIdx.x, lane = lane_id(), n = end - begin;
+  for (int t = tid; t < S; t += NT) s_key[t] = src.key(begin + sample_pos<S>(t, n), f) >> f.kshift;
+  __syncthreads();
+  sort_records<NT, S / NT>(words, s_ord, S, lo_key, coarse_shift(lo_key, hi_key), [s_key](int t) { return s_key[t]; });
+  const int nb = min(S, (n + kStaged / 2 - 1) / (kStaged / 2));
+  const auto cut_at = [&](int d) {
+    const int t = s_ord[d * S / nb];
+    return Cut{s_key[t], begin + sample_pos<S>(t, n)};
+  };
+  int first = begin;
+  for (int d = 0; d < nb; ++d) {
+    const Cut lo = d > 0 ? cut_at(d) : Cut{lo_key, -1}, hi = d + 1 < nb ? cut_at(d + 1) : Cut{hi_key, INT32_MAX};
+    const int a_row = d > 0 ? f.row_of(lo.key) : lo_row, b_row = d + 1 < nb ? f.row_of(hi.key) : hi_row;
+    const auto in = [&](uint64_t key, int p) {
+      return (d == 0 || lo.at_or_before(key, p)) && (d + 1 == nb || !hi.at_or_before(key, p));
+    };
+    if (tid == 0) *s_cnt = 0;
+    __syncthreads();
+    constexpr int U = 8;
+    for (int p0 = begin + tid; p0 < end; p0 += U * NT) {
+      uint64_t key[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) key[u] = src.key(min(p0 + u * NT, end - 1), f) >> f.kshift;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int p = p0 + u * NT;
+        if (p < end && in(key[u], p)) {
+          const int i = atomicAdd(s_cnt, 1);
+          if (i < kStaged) at[i] = p;
+        }
+      }
+    }
+    __syncthreads();
+    const int cnt = *s_cnt;
+    if (cnt > kStaged) {
+      rank_and_store<NT, VT>(src, begin, end, in, cnt, first, a_row, b_row, f, val_in, pos, crd_out, val_out);
+    } else if (cnt == 0) {
+      if (tid < kWave) store_pos_range(pos, lane == 0 ? a_row : 0, lane == 0 ? b_row : 0, first);
+    } else {
+      const auto key_at = [&](int li) { return src.key(at[li], f); };
+      sort_positions<NT, E>(at, cnt);  // records are numbered in input order
+      sort_records<NT, E>(words, ord, cnt, lo.key, coarse_shift(lo.key, hi.key),
+                          [&](int li) { return src.key(at[li], f) >> f.kshift; });
+      store_entries<NT, E>(ord, cnt, first, a_row, b_row, f, key_at, pos, crd_out,
+                           [&](int j, int li) { val_out[first + j] = val_in[at[li]]; });
+    }
+    first += cnt;
+    __syncthreads();
+  }
+}
+
 // One workgroup per bucket of the last partition. LEVELS == 1: of the only one, whose scanned
 // counts are off2 and whose splitters are skey2, with nseg buckets.
 template <typename VT, int LEVELS>
@@ -601,7 +684,7 @@ __global__ __launch_bounds__(kFin) void finish_kernel(const KSource src, const V
                                                       VT* __restrict__ val_out) {
   // up to kStaged records: keys, later values, then words and order; beyond: words and order
   __shared__ __attribute__((aligned(16))) char s_mem[kStaged * 8 + kStaged * 4 + kStaged * 2];
-  static_assert(kCap * 4 + kCap * 2 <= sizeof(s_mem), "");
+  static_assert(kCap * 4 + kCap * 2 <= sizeof(s_mem) && kSplitBytes <= sizeof(s_mem), "");
   const int g = blockIdx.x;
   int first, end;
   // the bucket's keys lie in [lo, hi], its rows of pos are (row of lo, row of hi]
@@ -630,8 +713,7 @@ __global__ __launch_bounds__(kFin) void finish_kernel(const KSource src, const V
   const int n = end - first;
   const int lo_row = g > 0 ? f.row_of(lo) : -1, hi_row = f.row_of(hi);
   if (n > kCap) {
-    rank_and_store<kFin, VT>(src, first, end, [](uint64_t, int) { return true; }, n, first, lo_row, hi_row, f, val_in,
-                             pos, crd_out, val_out);
+    split_and_store<kFin, VT>(s_mem, src, first, end, lo, hi, lo_row, hi_row, f, val_in, pos, crd_out, val_out);
     return;
   }
   if (n == 0) {
@@ -682,18 +764,6 @@ __global__ __launch_bounds__(kFin) void finish_kernel(const KSource src, const V
     store_entries<kFin, E>(ord, n, first, lo_row, hi_row, f, key_at, pos, crd_out,
                            [&](int j, int li) { val_out[first + j] = val_in[first + li]; });
   }
-}
-
-template <int E>
-__device__ __forceinline__ void sort_positions(uint32_t* at, int n) {
-  uint32_t v[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int i = e * kSel + static_cast<int>(threadIdx.x);
-    v[e] = i < n ? at[i] : ~0u;
-  }
-  __syncthreads();
-  block_sort_u32<kSel, E>(v, at);
 }
 
 // Small inputs: one workgroup per kSelTarget records. It samples the input, keeps the two
@@ -790,7 +860,7 @@ __global__ __launch_bounds__(kSel) void select_finish_kernel(const RcSource src,
   const auto put = [&](int j, int li) { val_out[first + j] = val_in[s_at[li]]; };
   // the positions first: records are numbered in input order
 #define SPT_FINISH(E_)                                                                                     \
-  sort_positions<E_>(reinterpret_cast<uint32_t*>(s_at), cnt);                                              \
+  sort_positions<kSel, E_>(reinterpret_cast<uint32_t*>(s_at), cnt);                                        \
   sort_records<kSel, E_>(words, s_ord, cnt, lo.key, shift, cmp_at);                                      \
   store_entries<kSel, E_>(s_ord, cnt, first, lo_row, hi_row, f, key_at, pos, crd_out, put)
   if (cnt <= kSel) {

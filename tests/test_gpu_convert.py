@@ -171,14 +171,58 @@ def _sampled(m, S):
 
 @pytest.mark.parametrize("nnz, S", [(6000, 1024), (4_200_000, 4096)])
 def test_input_that_defeats_the_sampling(nnz, S):
-    """Small keys exactly at the sampled positions: all other records end in one bucket, far more
-    than a workgroup sorts in LDS, and are ranked by counting."""
+    """Small keys exactly at the sampled positions: all other records end in one bucket. Of 6000, it is
+    ranked by counting; of 4.2M, the second partition leaves buckets of 16 000, which are split once more."""
     N, M = 100_000, 4000
     rng = np.random.default_rng(46)
     r, c = rng.integers(1000, N, nnz), rng.integers(0, M, nnz)
     at = _sampled(nnz, S)
     r[at], c[at] = np.arange(S) % 7, np.arange(S) % M
     _check(N, M, r, c, np.arange(nnz, dtype=np.float64), 0, what="sampling defeated")
+
+
+@pytest.mark.parametrize("order", [0, 1])
+@pytest.mark.parametrize("many", [4097, 6000, 20_000])
+@pytest.mark.parametrize("same", [False, True])
+def test_a_bucket_that_the_sample_got_wrong(order, many, same):
+    """Among 200 000 records `many` neighbours in the order (or copies of one coordinate) at positions that
+    are not sampled: one bucket of at least that many."""
+    N, M, nnz = 50_000, 60_000, 200_000
+    rng = np.random.default_rng(many)
+    r, c = rng.integers(0, N, nnz), rng.integers(0, M, nnz)
+    free = np.setdiff1d(np.arange(nnz), _sampled(nnz, 2048))        # 14 samples for each of 143 buckets
+    at = rng.choice(free, many, replace=False)
+    r[at], c[at] = (30_000, 7) if same else (rng.integers(30_000, 30_003, many), rng.integers(0, M, many))
+    _check(N, M, r, c, np.arange(nnz, dtype=np.float64), order, what=f"bucket of {many}")
+
+
+def test_a_bucket_that_the_sample_got_wrong_costs_little():
+    """4.2M records of which all but the sampled ones share a bucket of the first partition, so that all buckets
+    of the second hold four times what fits: counting their ranks took 1.1 s, split once more they take 2 ms (0.2 otherwise)."""
+    import torch
+    import paper_1804_10112_amd as spt
+    N, M, nnz = 100_000, 4000, 4_200_000
+    rng = np.random.default_rng(46)
+    times = []
+    for defeat in (False, True):
+        r, c = rng.integers(1000, N, nnz), rng.integers(0, M, nnz)
+        if defeat:
+            at = _sampled(nnz, 4096)
+            r[at], c[at] = np.arange(4096) % 7, np.arange(4096) % M
+        A = spt.DeviceTensor(wl.coo_spec(N, M, r, c, np.zeros(nnz, np.float32), ordered=False))
+        pos = torch.empty(N + 1, dtype=torch.int32, device="cuda")
+        crd, vals = torch.empty(nnz, dtype=torch.int32, device="cuda"), torch.empty(nnz, device="cuda")
+        ws = A.workspace(spt.SPT_OP_COO_TO_CSR)
+        best = 1e9
+        for _ in range(4):
+            start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            start.record()
+            spt.spt_coo_to_csr(A, 0, pos, crd, vals, ws)
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, start.elapsed_time(end))
+        times.append(best)
+    assert times[1] < 40 * times[0], f"{times[1]:.2f} ms with all buckets too large, {times[0]:.2f} otherwise"
 
 
 def test_more_records_than_the_sample_sort_takes():

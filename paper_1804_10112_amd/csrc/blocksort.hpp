@@ -87,13 +87,22 @@ __device__ __forceinline__ void bitonic_phases(uint32_t (&v)[E], uint32_t* buf) 
 // waves go through LDS. (A merge sort of 64-bit keys in LDS took three times as long, a bitonic
 // network on 64-bit keys five times: compare-and-select of two registers.) On return buf[0 .. NT * E) holds the words in order, visible to all
 // threads. buf must be 16-byte aligned.
+// In two steps: the network, after which thread t holds words t * E .. t * E + E - 1, and the store.
 template <int NT, int E>
-__device__ __forceinline__ void block_sort_u32(uint32_t (&v)[E], uint32_t* buf) {
+__device__ __forceinline__ void block_sort_regs(uint32_t (&v)[E], uint32_t* buf) {
   bitonic_phases<NT, E, 2>(v, buf);
   __syncthreads();
+}
+template <int NT, int E>
+__device__ __forceinline__ void block_sort_store(const uint32_t (&v)[E], uint32_t* buf) {
 #pragma unroll
   for (int e = 0; e < E; ++e) buf[threadIdx.x * E + e] = v[e];
   __syncthreads();
+}
+template <int NT, int E>
+__device__ __forceinline__ void block_sort_u32(uint32_t (&v)[E], uint32_t* buf) {
+  block_sort_regs<NT, E>(v, buf);
+  block_sort_store<NT, E>(v, buf);
 }
 
 }  // namespace spt

@@ -225,6 +225,53 @@ def test_a_bucket_that_the_sample_got_wrong_costs_little():
     assert times[1] < 40 * times[0], f"{times[1]:.2f} ms with all buckets too large, {times[0]:.2f} otherwise"
 
 
+def _clustered(nnz, width, M, rng):
+    """Rows of `width` neighbouring columns anywhere in M, in random order."""
+    N = -(-nnz // width)
+    r = np.repeat(np.arange(N), width)[:nnz]
+    c = (rng.integers(0, M - width, N)[:, None] + np.arange(width)).reshape(-1)[:nnz]
+    p = rng.permutation(nnz)
+    return N, r[p], c[p]
+
+
+@pytest.mark.parametrize("order", [0, 1])
+@pytest.mark.parametrize("nnz", [300, 5000, 60_000, 200_000, 700_000])
+@pytest.mark.parametrize("width", [7, 8, 9, 15, 16, 17, 100, 1000])
+def test_clustered_columns(nnz, width, order):
+    """Stretches of records that 20 bits of a bucket's key range do not tell apart, around the length from
+    which all are sorted again by 20 bits at a time."""
+    M = 2**31 - 10
+    rng = np.random.default_rng(nnz + width)
+    N, r, c = _clustered(nnz, width, M, rng)
+    _check(N, M, r, c, np.arange(nnz, dtype=np.float64), order, what=f"rows of {width} neighbours")
+
+
+def test_clustered_columns_take_no_longer():
+    """Rows of 1000 neighbours in 2^31 columns: with every record compared with its whole stretch, the
+    conversion took twelve times as long as with columns anywhere."""
+    import torch
+    import paper_1804_10112_amd as spt
+    nnz, M = 3_000_000, 2**31 - 10
+    rng = np.random.default_rng(5)
+    times = []
+    for clustered in (False, True):
+        N, r, c = _clustered(nnz, 1000, M, rng) if clustered else (200_000, rng.integers(0, 200_000, nnz), rng.integers(0, M, nnz))
+        A = spt.DeviceTensor(wl.coo_spec(N, M, r, c, np.zeros(nnz, np.float32), ordered=False))
+        pos = torch.empty(N + 1, dtype=torch.int32, device="cuda")
+        crd, vals = torch.empty(nnz, dtype=torch.int32, device="cuda"), torch.empty(nnz, device="cuda")
+        ws = A.workspace(spt.SPT_OP_COO_TO_CSR)
+        best = 1e9
+        for _ in range(4):
+            start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            start.record()
+            spt.spt_coo_to_csr(A, 0, pos, crd, vals, ws)
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, start.elapsed_time(end))
+        times.append(best)
+    assert times[1] < 3 * times[0], f"{times[1]:.2f} ms clustered, {times[0]:.2f} with columns anywhere"
+
+
 def test_more_records_than_the_sample_sort_takes():
     import torch
     import paper_1804_10112_amd as spt

@@ -11,6 +11,7 @@
 //  * DIA and ELL read the diagonal-major / slot-major arrays with consecutive
 //    rows in consecutive lanes.
 #include <algorithm>
+#include <type_traits>
 
 #include "carry.hpp"
 #include "common.hpp"
@@ -470,9 +471,9 @@ __device__ __forceinline__ T group_sum(T v) {
   return v;
 }
 
-// Block `block` of `nblocks`: NG * R consecutive rows.
+// Rows block * NG * R and the NG * R - 1 that follow.
 template <typename T, int G, int R, bool NT, class XP>
-__device__ __forceinline__ void csr_rows_block(int block, int nblocks, int nrows, int nnz,
+__device__ __forceinline__ void csr_rows_block(int block, int nrows, int nnz,
                                                const int32_t* __restrict__ pos, const int32_t* __restrict__ crd,
                                                const T* __restrict__ vals, const XP& x, T* __restrict__ y) {
   constexpr int NG = kBlock / G;
@@ -486,7 +487,7 @@ __device__ __forceinline__ void csr_rows_block(int block, int nblocks, int nrows
   const int tid = threadIdx.x, lane = lane_id();
   const int gl = tid % G;
   // rows of one pass over the groups are neighbours: a wave reads one stretch of entries per pass
-  const int row0 = xcd_contiguous_block_id(block, nblocks) * (NG * R) + tid / G;
+  const int row0 = block * (NG * R) + tid / G;
   int a[R], b[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
@@ -640,12 +641,12 @@ __device__ __forceinline__ void csr_rows_block(int block, int nblocks, int nrows
 }
 
 template <typename T, int G, int R, bool NT, class XP>
-__global__ __launch_bounds__(kBlock) void csr_rows_kernel(int nblocks, int nrows, int nnz,
+__global__ __launch_bounds__(kBlock) void csr_rows_kernel(int nrows, int nnz,
                                                           const int32_t* __restrict__ pos,
                                                           const int32_t* __restrict__ crd,
                                                           const T* __restrict__ vals, const XP x,
                                                           T* __restrict__ y) {
-  csr_rows_block<T, G, R, NT>(blockIdx.x, nblocks, nrows, nnz, pos, crd, vals, x, y);
+  csr_rows_block<T, G, R, NT>(xcd_contiguous_block_id(), nrows, nnz, pos, crd, vals, x, y);
 }
 // One of two candidates (the device has chosen): workgroups take several blocks, since the start of
 // 10^5 workgroups that return at once costs 40 us.
@@ -658,11 +659,95 @@ __global__ __launch_bounds__(kBlock) void csr_rows_if_kernel(int nblocks, int nr
                                                              int want) {
   if (!selected(select, want)) return;
   for (int block = blockIdx.x; block < nblocks; block += gridDim.x) {
-    csr_rows_block<T, G, R, true>(block, nblocks, nrows, nnz, pos, crd, vals, x, y);
+    csr_rows_block<T, G, R, true>(xcd_contiguous_block_id(block, nblocks), nrows, nnz, pos, crd, vals, x, y);
     __syncthreads();
   }
 }
 constexpr int kIfBlocks = 16384;  // a multiple of the XCDs: a workgroup's blocks stay on one
+
+// 256 rows through LDS: their entries, one stretch of the arrays, are read side by side whatever their rows,
+// and the products parked in LDS, where a lane adds up its row's. What that saves is accesses to the first-level
+// cache, of which it takes one for every 64 bytes of entries; by rows, a group's vectors straddle its lines and
+// some lanes are idle: 23.4M accesses against 27.3M (19M entries, 8 to 32 per row, fp32), with that unit busy
+// throughout. Worth it for fp32, whose x fits an L2 (the gathers beyond it hide everything else) and whose
+// entries do not (from there the row kernel is faster). In us, caches cleared / not, by rows and this way:
+//   8 to 32 per row     6.4M 42 / 30 and 42 / 36      12.8M 79 / 73 and 71 / 65       25.6M 181 / 175 and 173 / 168
+//                       19M 124 / 118 and 114 / 109   30.4M (x 6.4 MB) 236 / 232 and 236 / 232
+//   uniform, mean 10    12.8M 98 / 93 and 92 / 87     25.6M (x 10 MB) 294 / 290 and 292 / 288
+//   power law, mean 15 to 20   12.8M 106 / 92 and 101 / 94   14M 146 / 130 and 122 / 111   20M 219 / 198 and 214 / 205
+// A block with very long rows (taken from 16 384 entries on instead of 40 960: 115 and 224 us for the power
+// laws), and the last, whose vectors would pass the end, go by rows.
+constexpr int kStreamPiece = 2048;                      // products in LDS
+constexpr int kStreamMost = 160 * kBlock;               // entries of a block
+constexpr int kStreamLane = 48;                         // entries of a row that a lane adds up alone, else its wave
+constexpr int64_t kStreamXBytes = int64_t(6) << 20;     // an L2 of 4 MB keeps most of it
+template <typename T>
+__global__ __launch_bounds__(kBlock) void csr_stream_kernel(int nrows, int nnz, const int32_t* __restrict__ pos,
+                                                            const int32_t* __restrict__ crd,
+                                                            const T* __restrict__ vals, const DenseX<T> x,
+                                                            T* __restrict__ y) {
+  using V = typename Entries<T>::V;
+  using I = typename Entries<T>::I;
+  constexpr int K = Entries<T>::K, U = kStreamPiece / (K * kBlock), kG = 8;
+  __shared__ int32_t s_pos[kBlock + 1];
+  __shared__ T s_prod[kStreamPiece];
+  const int tid = threadIdx.x, block = xcd_contiguous_block_id(), row0 = block * kBlock;
+  for (int q = tid; q <= kBlock; q += kBlock) s_pos[q] = pos[min(row0 + q, nrows)];
+  __syncthreads();
+  const int e0 = s_pos[0], e1 = s_pos[kBlock];
+  if (e1 - e0 > kStreamMost || e1 + K > nnz) {  // uniform
+    for (int q = 0; q < kG; ++q) {
+      csr_rows_block<T, kG, 1, true>(block * kG + q, nrows, nnz, pos, crd, vals, x, y);
+      __syncthreads();
+    }
+    return;
+  }
+  const int ra = s_pos[tid], rb = s_pos[tid + 1];
+  T acc = 0;
+  for (int c0 = e0 / K * K; c0 < e1; c0 += kStreamPiece) {
+    const int c1 = min(c0 + kStreamPiece, e1);
+    I c[U];
+    V v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int p = c0 + K * (u * kBlock + tid);
+      const int q = p < c1 ? p : c0;  // an idle lane reads what the first one reads, and parks what nobody adds
+      c[u] = __builtin_nontemporal_load(reinterpret_cast<const I*>(crd + q));
+      v[u] = __builtin_nontemporal_load(reinterpret_cast<const V*>(vals + q));
+    }
+    T prod[U][K];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int k = 0; k < K; ++k) prod[u][k] = v[u][k] * x.at(c[u][k]);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int k = 0; k < K; ++k) s_prod[K * (u * kBlock + tid) + k] = prod[u][k];
+    __syncthreads();
+    const int a = max(ra, c0), e = min(rb, c1);
+    const bool big = e - a > kStreamLane;
+    for (int q = a; q < (big ? a : e); q += 8) {
+      T t[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) t[k] = s_prod[min(q + k, e - 1) - c0];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) acc += q + k < e ? t[k] : T(0);
+    }
+    uint64_t todo = __ballot(big);
+    while (todo) {
+      const int src = __ffsll(static_cast<long long>(todo)) - 1;
+      todo &= todo - 1;
+      const int la = __shfl(a, src) - c0, lb = __shfl(e, src) - c0;
+      T part = 0;
+      for (int q = la + lane_id(); q < lb; q += kWave) part += s_prod[q];
+      part = wave_total<T>(part);
+      if (lane_id() == src) acc += part;
+    }
+    __syncthreads();
+  }
+  if (row0 + tid < nrows) y[row0 + tid] = acc;
+}
 
 // By rows, or dealt out evenly in entries? A bound declared on the rows (max_children) decides; else
 // the mean row, since a row beyond kRowsWide entries keeps one workgroup busy (0.1 ms per 10^5 entries)
@@ -686,7 +771,8 @@ static bool csr_use_rows(int64_t nnz, int64_t nrows, int hint, const void* ws, s
 
 template <typename T, class XP>
 static spt_status launch_csr_rows(int64_t nnz, int64_t nrows, const int32_t* pos, const int32_t* crd, const T* vals,
-                                  const XP x, T* y, hipStream_t s, const int32_t* select = nullptr, int want = 0) {
+                                  const XP x, T* y, hipStream_t s, int64_t ncols = INT64_MAX,
+                                  const int32_t* select = nullptr, int want = 0) {
   // Rows per group at once: two where rows are so short that one leaves a lane with a single load
   // (7 entries per row, 25.6M entries, fp64: 80 -> 70 us), else one. Up to 2^20 entries the chip is
   // not full and waves that hold fewer rows meet fewer long ones: groups twice as wide.
@@ -697,10 +783,10 @@ static spt_status launch_csr_rows(int64_t nnz, int64_t nrows, const int32_t* pos
       hipLaunchKernelGGL((csr_rows_if_kernel<T, G_, R_, XP>), dim3(std::min(nb, kIfBlocks)), dim3(kBlock), 0, \
                          s, nb, (int)nrows, (int)nnz, pos, crd, vals, x, y, select, want);                    \
     else if (large)                                                                                           \
-      hipLaunchKernelGGL((csr_rows_kernel<T, G_, R_, true, XP>), dim3(nb), dim3(kBlock), 0, s, nb, (int)nrows, \
+      hipLaunchKernelGGL((csr_rows_kernel<T, G_, R_, true, XP>), dim3(nb), dim3(kBlock), 0, s, (int)nrows,     \
                          (int)nnz, pos, crd, vals, x, y);                                                     \
     else                                                                                                      \
-      hipLaunchKernelGGL((csr_rows_kernel<T, G_, R_, false, XP>), dim3(nb), dim3(kBlock), 0, s, nb, (int)nrows, \
+      hipLaunchKernelGGL((csr_rows_kernel<T, G_, R_, false, XP>), dim3(nb), dim3(kBlock), 0, s, (int)nrows,     \
                          (int)nnz, pos, crd, vals, x, y);                                                     \
   } while (0)
   // Entries are read past the caches once the matrix would leave no room for x in them (7 per row,
@@ -708,6 +794,16 @@ static spt_status launch_csr_rows(int64_t nnz, int64_t nrows, const int32_t* pos
   const bool large = nnz * (4 + (int64_t)sizeof(T)) > 96000000;
   const bool small = nnz <= (1 << 20);
   const bool two = !small && nnz <= 8 * nrows;
+  if constexpr (sizeof(T) == 4 && std::is_same<XP, DenseX<T>>::value) {
+    // (its indices pass the end by up to a piece, which must not pass 2^31)
+    if (large && !select && nnz + 2 * kStreamPiece < INT32_MAX && nnz >= 8 * nrows && nnz <= kShortRow * nrows &&
+        ncols <= kStreamXBytes / (int)sizeof(T)) {
+      hipLaunchKernelGGL(csr_stream_kernel<T>, dim3((unsigned)((nrows + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
+                         (int)nrows, (int)nnz, pos, crd, vals, x, y);
+      SPT_CHECK_LAUNCH("csr_stream");
+      return SPT_OK;
+    }
+  }
   const int64_t lanes = nnz / Entries<T>::K * (small ? 2 : 1);
   if (lanes <= 2 * nrows) {
     if (two) SPT_ROWS(2, 2);
@@ -1214,7 +1310,8 @@ static spt_status spmv_typed(Format f, const spt_tensor* A, const T* x, T* y, vo
       char* rest = static_cast<char*>(ws) + W.used;
       const int hint = A->level[1].max_children;
       if (csr_use_rows(A->nvals, stored, hint, rest, ws_bytes - W.used))
-        st = launch_csr_rows<T>(A->nvals, stored, A->level[1].pos, A->level[1].crd, vals, DenseX<T>{x}, t, s);
+        st = launch_csr_rows<T>(A->nvals, stored, A->level[1].pos, A->level[1].crd, vals, DenseX<T>{x}, t, s,
+                                A->level[1].N);
       else
         st = launch_seg<T, true>(A->nvals, stored, A->level[1].pos, A->level[1].crd, vals, x, t, rest,
                                  ws_bytes - W.used, s);
@@ -1229,7 +1326,7 @@ static spt_status spmv_typed(Format f, const spt_tensor* A, const T* x, T* y, vo
       const int64_t nnz = A->nvals, N = A->level[0].N;
       const int32_t *pos = A->level[1].pos, *crd = A->level[1].crd;
       if (!csr_use_rows(nnz, N, hint, ws, ws_bytes)) return launch_seg<T, true>(nnz, N, pos, crd, vals, x, y, ws, ws_bytes, s);
-      if (hint > 0 || nnz < kDynamicMinEntries) return launch_csr_rows<T>(nnz, N, pos, crd, vals, DenseX<T>{x}, y, s);
+      if (hint > 0 || nnz < kDynamicMinEntries) return launch_csr_rows<T>(nnz, N, pos, crd, vals, DenseX<T>{x}, y, s, A->level[1].N);
       if (!ws || ws_bytes < seg_spmv_workspace(nnz))
         return fail(SPT_ERR_WORKSPACE, "spmv: workspace of %zu bytes needed, %zu given", seg_spmv_workspace(nnz),
                     ws_bytes);
@@ -1237,7 +1334,7 @@ static spt_status spmv_typed(Format f, const spt_tensor* A, const T* x, T* y, vo
       int32_t* select = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + seg_spmv_workspace(nnz) - 256);
       hipLaunchKernelGGL(csr_skew_kernel, dim3(kSelectFlags), dim3(kBlock), 0, s, (int)N, (int)nnz, pos, select);
       SPT_CHECK_LAUNCH("csr skew");
-      spt_status st = launch_csr_rows<T>(nnz, N, pos, crd, vals, DenseX<T>{x}, y, s, select, 0);
+      spt_status st = launch_csr_rows<T>(nnz, N, pos, crd, vals, DenseX<T>{x}, y, s, A->level[1].N, select, 0);
       if (st != SPT_OK) return st;
       return launch_seg<T, true>(nnz, N, pos, crd, vals, x, y, ws, ws_bytes, s, select, 1);
     }

@@ -382,6 +382,36 @@ def test_csr_infinities_and_nans_stay_in_their_rows(lengths, dtype):
             assert_close_where_finite(gpu_spmv_sparse_x(spec, xs), ref, mag, dtype, xs.name)
 
 
+@pytest.mark.parametrize("case", ["even", "long rows", "ends on a vector", "x beyond an L2"])
+def test_csr_fp32_streamed_through_lds(case):
+    """fp32 matrices of more than 12M entries, 8 to 32 per row, whose x fits an L2: rows of 0 to 32 entries,
+    some of 49 to 60 000 (a wave's, several pieces', a block that goes by rows), an infinity and a NaN."""
+    rng = np.random.default_rng(11)
+    N = 620_000 if case != "x beyond an L2" else 800_000
+    M = 700_000 if case != "x beyond an L2" else 1_700_000
+    lens = rng.integers(8, 33, N)
+    lens[rng.integers(0, N, 2000)] = 0
+    if case == "long rows":
+        for row, n in ((5, 49), (6, 2048), (300, 5000), (9_999, 12_000), (10_001, 30_000), (40_000, 60_000), (N - 1, 700)):
+            lens[row] = n
+    pos = np.concatenate([[0], np.cumsum(lens)])
+    if case == "ends on a vector":
+        lens[-1] += -pos[-1] % 4
+        pos[-1] = pos[-2] + lens[-1]
+    nnz = int(pos[-1])
+    assert 96e6 < 8 * nnz and 8 * N <= nnz <= 32 * N
+    crd = rng.integers(0, M, nnz, dtype=np.int32)
+    vals = rng.uniform(-1, 1, nnz).astype(np.float32)
+    vals[pos[1000]], vals[pos[5001] - 1] = np.inf, np.nan
+    x = rng.uniform(0.5, 1, M).astype(np.float32)
+    spec = wl.csr_spec(N, M, pos, crd, vals)
+    ref, mag = oracle.spmv(spec, x)
+    a, b = gpu_spmv(spec, x, repeat=2)
+    assert_close_where_finite(a, ref, mag, np.float32, case)
+    assert np.array_equal(a, b, equal_nan=True), "run-to-run bits differ"
+    assert_close_where_finite(gpu_spmv(spec, x, misalign=True), ref, mag, np.float32, f"{case}, unaligned arrays")
+
+
 def _device_matrix(rows, nnz, dcsr):
     """nnz entries dealt out evenly to the rows, anywhere in 10^6 columns; arrays on the GPU."""
     import torch

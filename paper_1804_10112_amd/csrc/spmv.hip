@@ -1,13 +1,18 @@
 // SpMV y = A x on CSR, COO, DIA and ELL (paper Section 5.2), gfx950.
 //
-// All four kernels are bound by HBM bandwidth: the matrix arrays are streamed
-// once with coalesced (non-temporal) loads, x is gathered through the caches.
-//  * CSR: a group of lanes per row. Strongly skewed CSR and sorted COO share one kernel: a
+// The matrix arrays are read once with coalesced, mostly non-temporal loads, x is gathered through the
+// caches. What bounds a kernel: the rate of a large copy where x is read in order (DIA, banded CSR: 5 TB/s);
+// the gathers of x where columns are anywhere (ELL, CSR, COO: 0.95 to 1.05 of what a kernel that only gathers
+// reaches); launches and latency for some ten thousand entries.
+//  * CSR: a group of lanes per row; fp32 rows of 8 to 32 entries, many of them, 256 at a time through LDS.
+//    CSR with long or strongly skewed rows and large sorted COO share one kernel: a
 //    workgroup owns a fixed chunk of stored entries (balanced in entries, not rows, so power-law rows cost
 //    nothing extra), stages the products in LDS and reduces them per row with a
 //    segmented scan; a row cut by a chunk boundary is finished by a tiny carry
 //    kernel. No atomics, results are bit-reproducible.
-//  * Unsorted COO is the paper's scatter loop: atomic adds into y.
+//  * Sorted COO of up to 2^24 entries: a wave per 256 entries, in one launch up to 65 536.
+//  * Unsorted COO is the paper's scatter loop with atomic adds into y, from 786 432 entries on the binned
+//    scatter of coo_bin.hip.
 //  * DIA and ELL read the diagonal-major / slot-major arrays with consecutive
 //    rows in consecutive lanes.
 #include <algorithm>
@@ -1450,10 +1455,9 @@ static spt_status spmv_typed(Format f, const spt_tensor* A, const T* x, T* y, vo
 spt_status csr_rows_reduce(int dtype, int64_t nnz, int64_t nrows, const int32_t* pos,
                            const int32_t* crd, const void* vals, const void* x, void* out,
                            void* ws, size_t ws_bytes, hipStream_t s) {
-  // the entry-balanced kernel: fibre lengths of a skewed tensor are far from their mean
-  // (the head slices hold fibres of hundreds of entries, the rest single entries: 0.37 ms
-  // against 1.24 ms with the streamed kernel on 50M entries in 8.1M fibres); few entries, where
-  // one launch is what counts, by rows (50 000 entries, fp64: 7.4 instead of 11 us; 1M skewed ones take longer)
+  // By entries: fibre lengths of a skewed tensor are far from their mean (hundreds of entries in the first
+  // slices, single ones elsewhere). Few entries, where one launch is what counts, by rows if fibres are short on
+  // average (50 000 entries, fp64: 7.4 instead of 11 us; 1M skewed ones take longer).
   if (nnz < (1 << 19) && csr_use_rows(nnz, nrows, 0, ws, ws_bytes)) {
     if (dtype == SPT_F64)
       return launch_csr_rows<double>(nnz, nrows, pos, crd, static_cast<const double*>(vals),

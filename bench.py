@@ -119,10 +119,8 @@ def build_items(args):
         vout = torch.empty(nnz, dtype=A.torch_dtype, device=dev)
         wsc = A.workspace(spt.SPT_OP_COO_TO_CSR)
         keep.extend([pos, crd, vout, wsc])
-        passes = conversion_passes(N, N, nnz, spt.SPT_ORDER_ROW_COL)
         items.append(Item("c4_coo_to_csr", lambda: spt.spt_coo_to_csr(A, spt.SPT_ORDER_ROW_COL, pos, crd, vout, wsc),
-                          0, conversion_bytes(passes, nnz, N),
-                          f"{passes} passes over the (key, index) pairs + final gather + pos"))
+                          0, conversion_bytes(nnz, N, 8), "bytes: entries read once and written once, pos"))
         items[-1].run()
         torch.cuda.synchronize()
         rows_sorted = torch.repeat_interleave(torch.arange(N, dtype=torch.int32, device=dev),
@@ -211,10 +209,9 @@ def build_items(args):
         wsc = A.workspace(spt.SPT_OP_COO_TO_CSR)
         keep.extend([A, pos, crd, vout, wsc])
         for tag, order in (("row_stable", spt.SPT_ORDER_ROW_STABLE), ("row_col", spt.SPT_ORDER_ROW_COL)):
-            passes = conversion_passes(n4, n4, nnz, order)
             items.append(Item(f"x14_coo_to_csr_{tag}",
                               lambda order=order: spt.spt_coo_to_csr(A, order, pos, crd, vout, wsc), 0,
-                              conversion_bytes(passes, nnz, n4), f"{passes} passes"))
+                              conversion_bytes(nnz, n4, 8)))
         del c4
     # ---- on request (--only x16): CSR SpMV on config 3's matrix with x as dense array,
     #      sparse vector and hash map at three densities (the experiment of Figure 16)
@@ -401,7 +398,7 @@ def build_items(args):
             keep.extend([Ag, wg5])
             items.append(Item(f"n5_spmv_{nm}", lambda Ag=Ag, wg5=wg5: spt.spt_spmv(Ag, xg, yg, wg5), 2 * nnz3,
                               8 * nnz3 + 12 * N3,
-                              "one atomic per stored value" if nm == "csc" else "CSR kernel over the stored rows"))
+                              "columns written out, then as unordered COO" if nm == "csc" else "CSR kernel over the stored rows"))
         # array-of-structs COO of the same matrix (entries in row order): pairs split, then COO kernels
         Aa = spt.DeviceTensor(wl.coo_aos_spec((N3, N3), (rr, cc), vv))
         wa = Aa.workspace(spt.SPT_OP_SPMV)
@@ -461,19 +458,10 @@ def build_items(args):
     return items, cpu_jobs, keep
 
 
-def conversion_passes(N, M, nnz, order):
-    """Global passes over the records that spt_coo_to_csr makes for this input (mirrors the
-    library's plan: 8-bit digits over the significant bits of the column, then of the row)."""
-    bits = lambda d: max(1, int(np.ceil(np.log2(max(d, 2)))))
-    rows = (bits(N) + 7) // 8
-    return rows + ((bits(M) + 7) // 8 if order == 0 else 0)
-
-
-def conversion_bytes(passes, nnz, N):
-    """Algorithmic bytes of COO -> CSR with a P-pass sort: every pass reads and writes a 64-bit
-    key and a 32-bit payload per entry (2 * 12 bytes), the final gather reads and writes column
-    and value once more (2 * 12), the pos assembly reads the sorted rows (4) and writes pos."""
-    return passes * 2 * 12 * nnz + 2 * 12 * nnz + 4 * nnz + 4 * (N + 1)
+def conversion_bytes(nnz, N, vsize):
+    """Bytes that COO -> CSR cannot do without: row, column and value of every entry read once, column
+    and value written once, pos written."""
+    return (8 + vsize) * nnz + (4 + vsize) * nnz + 4 * (N + 1)
 
 
 def oracle_free_coo(csr_spec):

@@ -8,7 +8,7 @@ from gpu_util import gpu_coo_to_csr
 
 pytestmark = pytest.mark.gpu
 
-TILE = 4096  # records per workgroup of the radix sort: sizes below straddle it
+TILE = 4096  # records of a tile of a large partition, and the most that are sorted in LDS
 
 
 def _check(N, M, r, c, v, order, ordered=False, what=""):
@@ -25,7 +25,7 @@ def _check(N, M, r, c, v, order, ordered=False, what=""):
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])
 @pytest.mark.parametrize("nnz", [0, 1, 255, 256, 4095, 4096, 4097, 3 * 4096 + 5, 100_003])
 def test_random_unsorted(order, dtype, nnz):
-    N, M = 1500, 70_000                      # 11 row bits (2 passes), 17 col bits (3 passes)
+    N, M = 1500, 70_000
     r, c, v = wl.random_coo_entries(N, M, nnz, seed=200 + nnz, dtype=dtype, sort=False)
     _check(N, M, r, c, v, order, what=f"nnz={nnz}")
 

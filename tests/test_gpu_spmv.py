@@ -8,7 +8,7 @@ from gpu_util import assert_close, assert_close_where_finite, gpu_spmv, gpu_spmv
 
 pytestmark = pytest.mark.gpu
 
-CHUNK = 2048  # entries per workgroup of the CSR/COO kernel: sizes below straddle it
+CHUNK = 2048  # entries per workgroup of the entry-balanced kernel: sizes below straddle it
 
 
 def _check(spec, x, what):
@@ -48,7 +48,7 @@ def test_csr_coo_degenerate_structures(dtype):
     v4 = np.array([1, 2, 3, 4], dtype)
     _check(wl.csr_from_sorted_coo(100000, 50, r, c4, v4), x, "csr mostly empty")
     _check(wl.coo_spec(100000, 50, r, c4, v4), x, "coo mostly empty")
-    # more than 2^20 rows: few entries still take the chunked kernel (fill + carries)
+    # more than 2^20 rows: few entries still go in pieces (fill + carries)
     _check(wl.coo_spec(3_000_000, 50, np.array([3, 3, 40000, 2_999_999]), c4, v4), x, "coo, 3M rows, 4 entries")
     # row boundaries exactly on chunk boundaries
     r = np.repeat(np.arange(4), CHUNK)
@@ -66,7 +66,7 @@ def test_csr_coo_degenerate_structures(dtype):
 @pytest.mark.parametrize("nnz", [255, 257, 1023, 65_535, 65_536, 65_537, 200_000])
 def test_sorted_coo_on_both_sides_of_the_single_launch_limit(dtype, nnz):
     """Up to 65 536 entries sorted COO runs in one launch (a wave per 256 entries, the owner of
-    a row reads on past its piece); above, the chunked kernel with carries. Rows of 1 to 3000
+    a row reads on past its piece); above, in pieces with carries. Rows of 1 to 3000
     entries, runs of empty rows, the last rows empty, an infinite x value under the last entry."""
     N, M = 9000, 700
     rng = np.random.default_rng(nnz)
@@ -131,11 +131,11 @@ def test_power_law_rows_scaled_config4():
 @pytest.mark.parametrize("dtype,N", [(np.float64, 6_000_000), (np.float32, 20_000_000)])
 def test_unordered_coo_with_more_rows_than_one_lds_window(dtype, N):
     """Row count so large that a bin's rows need several LDS sub-ranges, and a row so long
-    that its bin is cut into several slices (slices combine with atomics)."""
+    that its bin is cut into several slices, which a last kernel adds up."""
     rng = np.random.default_rng(4)
-    n = 700_000
+    n = 900_000                                 # binned from 786 432 entries on
     row = rng.integers(0, N, n)
-    row[: n // 2] = N - 7                       # one heavy row: > 262144 entries in one bin
+    row[: n // 2] = N - 7                       # one heavy row: half of all entries in one bin
     col = rng.integers(0, 1000, n)
     v = rng.uniform(-1, 1, n).astype(dtype)
     p = rng.permutation(n)
@@ -198,8 +198,8 @@ def _with_hint(spec, bound):
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])
 @pytest.mark.parametrize("lo,hi", [(0, 3), (1, 7), (0, 12), (9, 16), (8, 32)])
 def test_csr_kernel_choice_by_mean_row_length_and_by_hint(dtype, lo, hi):
-    """Plain (pos, crd) CSR with a short mean row runs the streamed kernel (256 rows' entries
-    through LDS, one lane per row) with no hint at all; a declared bound <= 32 selects the same
+    """Plain (pos, crd) CSR with a short mean row runs the row kernel (a group of lanes per row)
+    with no hint at all; a declared bound <= 32 selects the same
     kernel (same bits), a larger one the entry-balanced kernel; all match the oracle."""
     c3 = wl.config3(N=5003, lo=lo, hi=hi, dtype=dtype)
     hinted = c3["csr"]
@@ -212,7 +212,7 @@ def test_csr_kernel_choice_by_mean_row_length_and_by_hint(dtype, lo, hi):
     assert np.array_equal(gpu_spmv(hinted, c3["x"]), a), "the hint selects the same kernel"
     assert_close(gpu_spmv(_with_hint(hinted, 100_000), c3["x"]), ref, mag, dtype,
                  f"entry-balanced kernel rows {lo}..{hi}")
-    assert_close(gpu_spmv(plain, c3["x"], misalign=True), ref, mag, dtype, "streamed kernel, unaligned")
+    assert_close(gpu_spmv(plain, c3["x"], misalign=True), ref, mag, dtype, "row kernel, unaligned")
 
 
 @pytest.mark.parametrize("which", ["c2", "c3"])
@@ -228,11 +228,10 @@ def test_unhinted_csr_of_configs_2_and_3_is_bit_reproducible(which):
 
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])
 @pytest.mark.parametrize("nnz_mod", [0, 1, 2, 3])
-def test_streamed_kernel_with_long_rows_among_short_ones(dtype, nnz_mod):
-    """Mean row length 8, so the streamed kernel runs, but single rows hold 60, 3000, 9000 and
-    40 000 entries: parts of a row longer than 48 products are added up by the whole wave, whole
-    LDS pieces inside one row are added up in registers. The entry count takes every remainder
-    modulo 4 (the last 16-byte group of the arrays is partial)."""
+def test_csr_long_rows_among_short_ones(dtype, nnz_mod):
+    """Mean row length 8, so the row kernel runs, but single rows hold 60, 3000, 9000 and
+    40 000 entries: they are added up by a wave, or above 4096 entries by the workgroup. The entry
+    count takes every remainder modulo 4 (the last vector of the arrays is moved back)."""
     N, M = 12_000, 50_000
     r, c, v = wl.random_coo_entries(N, M, 40_000 + nnz_mod, seed=70 + nnz_mod, dtype=dtype)
     rng = np.random.default_rng(71)
@@ -251,16 +250,16 @@ def test_streamed_kernel_with_long_rows_among_short_ones(dtype, nnz_mod):
     x = wl.dense_vector(M, 72, dtype)
     ref, mag = oracle.spmv(spec, x)
     a, b = gpu_spmv(spec, x, repeat=2)
-    assert_close(a, ref, mag, dtype, "long rows, streamed")
+    assert_close(a, ref, mag, dtype, "long rows, by rows")
     assert np.array_equal(a, b)
-    assert_close(gpu_spmv(spec, x, misalign=True), ref, mag, dtype, "long rows, streamed, unaligned")
+    assert_close(gpu_spmv(spec, x, misalign=True), ref, mag, dtype, "long rows, by rows, unaligned")
     assert_close(gpu_spmv(_with_hint(spec, 40_000), x), ref, mag, dtype, "long rows, entry-balanced")
 
 
 @pytest.mark.parametrize("heavy_row", [0, 150_000])
 def test_large_unhinted_csr_picks_its_kernel_on_the_device(heavy_row):
     """From 2^25 entries on, a CSR matrix without a declared row bound has the entry counts of
-    its 256-row blocks inspected on the device: even blocks keep the streamed kernel (same bits
+    its 256-row blocks inspected on the device: even blocks keep the row kernel (same bits
     as with a declared bound of 16), one block holding a 150 000-entry row switches to the
     entry-balanced kernel (same bits as with a declared bound of 150 000)."""
     N = M = 2_100_000
@@ -294,8 +293,8 @@ def test_large_unhinted_csr_picks_its_kernel_on_the_device(heavy_row):
 
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])
 def test_csr_hint_that_the_data_violates_stays_correct(dtype):
-    """A declared bound of 8 on a matrix with one row of 9000 entries: the streamed kernel takes
-    the long row in several LDS pieces; slower, never wrong."""
+    """A declared bound of 8 on a matrix with one row of 9000 entries: the row kernel gives
+    the long row to its workgroup; slower, never wrong."""
     N, M = 3000, 10_000
     r, c, v = wl.random_coo_entries(N, M, 20_000, seed=77, dtype=dtype)
     rng = np.random.default_rng(78)

@@ -206,7 +206,7 @@ def test_later_entry_points_in_a_captured_graph():
             for j, (t, e) in enumerate(zip(v, eager[k])):
                 if k == "mul" and j in (1, 2):
                     t, e = t[:n_mul], e[:n_mul]
-                if k == "y_csc":                              # binned rows are summed with LDS atomics
+                if k == "y_csc":                              # rows are summed with atomics
                     ref = e.cpu().numpy()
                     assert_close(t.cpu().numpy(), ref, np.abs(ref) + 1.0, np.float64, f"replay {rep} csc")
                 else:

@@ -93,10 +93,11 @@ def test_mttkrp_sizes(nnz):
 
 @pytest.mark.parametrize("dtype,J,nnz", [
     (np.float32, 3, 70_000), (np.float32, 8, 1_700_000), (np.float32, 37, 400_000), (np.float64, 2, 900_000),
-    (np.float64, 16, 900_001), (np.float64, 65, 200_003)])
+    (np.float64, 16, 900_001), (np.float64, 65, 200_003),
+    (np.float32, 37, 620_000), (np.float64, 65, 310_003)])   # the last two: more than 2048 carries, two levels
 def test_mttkrp_groups_of_lanes_and_rows_across_many_chunks(dtype, J, nnz):
     """Every number of lanes per entry, groups of more than 16 entries, rows as long as many chunks
-    (two levels of carries) next to rows of one entry, J no multiple of a lane's columns."""
+    next to rows of one entry, J no multiple of a lane's columns; carries in one launch and in two levels."""
     dims = (5000, 900, 1100)
     rng = np.random.default_rng(nnz)
     rows = np.concatenate([np.full(nnz * 2 // 5, 3), np.full(nnz // 5, 4700), rng.integers(0, 5000, nnz * 2 // 5)])
@@ -111,7 +112,7 @@ def test_mttkrp_groups_of_lanes_and_rows_across_many_chunks(dtype, J, nnz):
 
 def test_mttkrp_degenerate_and_exact():
     rng = np.random.default_rng(1)
-    # one slice holds everything (crosses many chunks and both carry levels)
+    # one slice holds everything (crosses many chunks: a row of carries only)
     n = 200_000
     k = rng.integers(0, 300, n)
     l = rng.integers(0, 400, n)
@@ -183,7 +184,7 @@ def test_csf_with_empty_fibres_and_slices(dtype, nnz, extra):
     assert_close(ov[full], rv, rm, dtype, "ttv csf with gaps")
 
 
-WAVE_MIN = 1 << 18  # from this many entries on TTV keeps c in LDS and lets every wave walk on its own
+WAVE_MIN = 12_289 * 256  # from this many entries on TTV keeps c in LDS (CSF: from 2^19) and lets every wave walk on its own
 
 
 @pytest.mark.parametrize("dtype,K", [(np.float32, 900), (np.float32, 32_768), (np.float32, 50_000),
@@ -193,8 +194,8 @@ def test_ttv_with_the_vector_in_lds(dtype, K, tail):
     """Large tensors: c is cached in LDS whole (K up to 128 KiB of values) or in part (the
     rest is gathered from global memory); the entry count takes every remainder modulo 4, so
     the last 16-byte group and the last 256-entry piece of a wave are partial."""
-    dims = (3000, 500, K)
-    ci, cj, ck, v = wl.random_coo3_entries(dims, WAVE_MIN + 40_000, 900 + K % 97 + tail, dtype, "u01", skew=1.5)
+    dims = (3000, 6000, K)
+    ci, cj, ck, v = wl.random_coo3_entries(dims, WAVE_MIN + 250_000, 900 + K % 97 + tail, dtype, "u01", skew=1.5)
     n = len(v) - (len(v) - tail) % 4
     ci, cj, ck, v = ci[:n], cj[:n], ck[:n], v[:n]
     assert n >= WAVE_MIN and n % 4 == tail
@@ -232,8 +233,8 @@ def test_ttv_infinities_beyond_the_last_entry_are_not_added(dtype, nnz):
             assert_close_where_finite(got[2], rv, rm, dtype, f"ttv {spec.name}")
 
 
-def test_large_ttv_with_a_vector_far_beyond_lds_takes_the_chunked_kernels():
-    """c of 600 000 values: less than a quarter would fit LDS, the chunked kernels run."""
+def test_large_ttv_with_a_vector_far_beyond_lds_leaves_it_in_global_memory():
+    """c of 600 000 values: less than a quarter would fit LDS. COO in pieces, CSF by entries in chunks."""
     dims = (300, 500, 600_000)
     coo, csf = _tensor(dims, WAVE_MIN + 30_000, 77, np.float32)
     assert len(coo.vals) >= WAVE_MIN
@@ -246,7 +247,7 @@ def test_ttv_in_lds_with_long_fibres_empty_fibres_and_unaligned_buffers(dtype):
     empty fibres and slices, exact small-integer data (bit-exact sums), unaligned arrays."""
     rng = np.random.default_rng(17)
     dims = (400, 300, 4000)
-    lens = np.minimum(rng.zipf(1.3, 9000), 3000)
+    lens = np.minimum(rng.zipf(1.3, 12_000), 3000)
     fib = np.sort(rng.choice(dims[0] * dims[1], len(lens), replace=False))
     ci, cj = np.repeat(fib // dims[1], lens), np.repeat(fib % dims[1], lens)
     ck = np.concatenate([np.sort(rng.choice(dims[2], l, replace=False)) for l in lens])

@@ -33,7 +33,7 @@ def test_two_calls_in_a_row_second_smaller(fmt):
     import oracle
     from gpu_util import assert_close
     # rows of up to 30 000 entries: the entry-balanced kernel with carries across many chunks
-    # (the binned scatter of an unordered COO needs ~12 bytes per entry: 250 000 entries fit)
+    # (an unordered COO below 786 432 entries needs no scratch, the binned scatter above ~12 bytes per entry)
     sizes = ((60_000, 900_000, 30_000, 11), (5_000, 40_000, 3_000, 12))
     if fmt == "coo_unordered":
         sizes = ((20_000, 250_000, 8_000, 11), (5_000, 40_000, 3_000, 12), (500, 3_000, 100, 13))

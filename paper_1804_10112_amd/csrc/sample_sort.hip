@@ -126,7 +126,7 @@ __device__ __forceinline__ int final_buckets(int m, int target) {
 // ---- sorting a few thousand records in one workgroup ------------------------------------------
 // After the network: do kCrowd neighbours share their coarse bits? (Of a thread's own words, or of lanes of one
 // row of 16: a stretch of twice that many is seen wherever it lies.)
-constexpr int kCrowd = 8;
+constexpr int kCrowd = 16;
 template <int NT, int E>
 __device__ __forceinline__ bool crowded(const uint32_t (&v)[E], int n) {
   const int tid = threadIdx.x;
@@ -150,8 +150,10 @@ __device__ __forceinline__ bool crowded(const uint32_t (&v)[E], int n) {
 // it (`key_at` gives the whole key of a record). Stretches are two or three records long where columns are
 // anywhere, but as long as a row where they are neighbours in a wide matrix: once one of them has kCrowd
 // records, all are sorted again, by 20 bits at a time from the lowest on. (30M records, counted / sorted
-// again: rows of 10 neighbours in 2M columns 1157 / 1097 us, of 30 1597 / 1106, of 1000 in 2^31 columns
-// 16 640 / 1149. Looking for such stretches costs 0.5 of 21 us for 50 000 records, 0.3 % for 60M.)
+// again: rows of 20 neighbours in 2M columns 1374 / 1098 us, of 30 1603 / 1099, of 1000 in 2^31 columns
+// 16 900 / 1151. From eight records on, rows of 10 neighbours would gain 4 %, but power-law rows, whose long ones
+// crowd a few buckets, lose up to 2 %: 6M records 271 us counted, 272 and 276 sorted again from 16 and from 8 on.
+// Looking for such stretches costs 0.5 of 21 us for 50 000 records.)
 // Bound by vector instructions (110 of 225 per record in the finishing kernel are the network).
 // Left out after measuring: dealing the words to 1024 equal bins of the key range and ranking
 // inside the bins (631 instead of 503 us for 60M records with power-law rows: long and short rows

@@ -1,8 +1,8 @@
-// TTV A_ij = sum_k B_ijk c_k (paper Section 5.3) on ordered COO and on CSF, TTM and SpDM, gfx950.
+// SpDM and TTM on ordered COO and on CSF (paper Sections 5.2, 5.3), and which kernels TTV runs, gfx950.
 //
 // Both reduce runs of consecutive stored entries that share leading
 // coordinates -- the GPU form of the paper's deduplication / iterator chaining
-// over ordered non-unique levels (Section 4.3): (i,j) fibers for TTV, rows
+// over ordered non-unique levels (Section 4.3): (i,j) fibres for TTM, rows
 // for SpDM. Work is split evenly over stored entries; a run cut by a split
 // leaves a carry that a follow-up kernel adds in a fixed order (no atomics).
 #include <algorithm>

@@ -529,7 +529,7 @@ constexpr int kSelfPieces = 12288;
 
 static int64_t pieces_of(int64_t nnz) { return (nnz + kPiece - 1) / kPiece; }
 
-// Smaller CSF tensors are reduced row by row (one launch): the fixed cost of staging c on every
+// Smaller CSF tensors are reduced as CSR rows, one launch where fibres are short: the fixed cost of staging c on every
 // compute unit is not recovered (500 000 entries: 8 to 12 us by rows, 13 to 19 with c staged; 1M skewed
 // ones 16 to 37 and 14 to 23). Tensors whose last dimension is so long that less
 // than a quarter of c fits the cache leave c in global memory: their gathers go there anyway, and

@@ -680,16 +680,20 @@ constexpr int kIfBlocks = 16384;  // a multiple of the XCDs: a workgroup's block
 //                       19M 124 / 118 and 114 / 109   30.4M (x 6.4 MB) 236 / 232 and 236 / 232
 //   uniform, mean 10    12.8M 98 / 93 and 92 / 87     25.6M (x 10 MB) 294 / 290 and 292 / 288
 //   power law, mean 15 to 20   12.8M 106 / 92 and 101 / 94   14M 146 / 130 and 122 / 111   20M 219 / 198 and 214 / 205
+// A sparse or hashed x is looked up for every entry, which idle lanes waste: any such matrix whose entries do not
+// stay cached. By rows and this way, 20M entries, a thousandth of x stored: fp64, mean 20, 280 and 214 us sparse,
+// 334 and 227 hashed, mean 4 415 and 359, 247 and 195; fp32, mean 20, 245 and 214, 274 and 220 (half of it stored:
+// equal to within 5 %; 5M entries, not taken: fp32, mean 4, 79 and 103).
 // A block with very long rows (taken from 16 384 entries on instead of 40 960: 115 and 224 us for the power
 // laws), and the last, whose vectors would pass the end, go by rows.
 constexpr int kStreamPiece = 2048;                      // products in LDS
 constexpr int kStreamMost = 160 * kBlock;               // entries of a block
 constexpr int kStreamLane = 48;                         // entries of a row that a lane adds up alone, else its wave
 constexpr int64_t kStreamXBytes = int64_t(6) << 20;     // an L2 of 4 MB keeps most of it
-template <typename T>
+template <typename T, class XP>
 __global__ __launch_bounds__(kBlock) void csr_stream_kernel(int nrows, int nnz, const int32_t* __restrict__ pos,
                                                             const int32_t* __restrict__ crd,
-                                                            const T* __restrict__ vals, const DenseX<T> x,
+                                                            const T* __restrict__ vals, const XP x,
                                                             T* __restrict__ y) {
   using V = typename Entries<T>::V;
   using I = typename Entries<T>::I;
@@ -799,11 +803,13 @@ static spt_status launch_csr_rows(int64_t nnz, int64_t nrows, const int32_t* pos
   const bool large = nnz * (4 + (int64_t)sizeof(T)) > 96000000;
   const bool small = nnz <= (1 << 20);
   const bool two = !small && nnz <= 8 * nrows;
-  if constexpr (sizeof(T) == 4 && std::is_same<XP, DenseX<T>>::value) {
+  constexpr bool dense = std::is_same<XP, DenseX<T>>::value;
+  if constexpr (sizeof(T) == 4 || !dense) {
     // (its indices pass the end by up to a piece, which must not pass 2^31)
-    if (large && !select && nnz + 2 * kStreamPiece < INT32_MAX && nnz >= 8 * nrows && nnz <= kShortRow * nrows &&
-        ncols <= kStreamXBytes / (int)sizeof(T)) {
-      hipLaunchKernelGGL(csr_stream_kernel<T>, dim3((unsigned)((nrows + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
+    if (!select && nnz + 2 * kStreamPiece < INT32_MAX &&
+        (dense ? large && nnz >= 8 * nrows && nnz <= kShortRow * nrows && ncols <= kStreamXBytes / (int)sizeof(T)
+               : large)) {
+      hipLaunchKernelGGL((csr_stream_kernel<T, XP>), dim3((unsigned)((nrows + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
                          (int)nrows, (int)nnz, pos, crd, vals, x, y);
       SPT_CHECK_LAUNCH("csr_stream");
       return SPT_OK;

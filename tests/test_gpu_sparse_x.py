@@ -43,6 +43,22 @@ def test_hash_map_x(dtype, nnzx, W):
     assert np.array_equal(got, dense) and np.array_equal(sparse, dense)
 
 
+@pytest.mark.parametrize("dtype,nnz", [(np.float32, 12_300_000), (np.float64, 8_200_001)])
+def test_entries_that_do_not_stay_cached(dtype, nnz):
+    """More than 96 MB of entries: products through LDS, as for a dense x of fp32."""
+    rng = np.random.default_rng(nnz)
+    N, M = 900_000, 40_000
+    lens = np.diff(np.concatenate([[0], np.sort(rng.integers(0, nnz, N - 1)), [nnz]]))
+    A = wl.csr_spec(N, M, np.concatenate([[0], np.cumsum(lens)]), rng.integers(0, M, nnz, dtype=np.int32),
+                    rng.uniform(-1, 1, nnz).astype(dtype))
+    xc, xv = wl.random_sparse_vector(M, M // 3, seed=5, dtype=dtype)
+    xd = np.zeros(M, dtype)
+    xd[xc] = xv
+    ref, mag = oracle.spmv(A, xd)            # the oracle's lookups of 12M entries would take half a minute
+    for X in (wl.sparse_vector_spec(M, xc, xv), wl.hash_vector_spec(M, xc, xv, M)):
+        assert_close(gpu_spmv_sparse_x(A, X), ref, mag, dtype, X.name)
+
+
 def test_clustered_keys_probe_across_the_wrap():
     """All coordinates collide on the last buckets, so probing wraps to the table start."""
     A = _matrix(np.float64)

@@ -1,8 +1,8 @@
 // COO -> CSR (paper Section 5.4, Figure 14) on gfx950.
 //
 //   1. reorder (Section 4.3 "reordering"): up to 2^26 records by sample sort
-//      (sample_sort.hip, which also assembles pos); beyond, a stable least-significant-digit
-//      radix sort of the (row, col, value) records, 8 bits per pass, over the
+//      (sample_sort.hip, which also assembles pos); beyond, and where few passes do, a stable
+//      least-significant-digit radix sort of the (row, col, value) records, 8 bits per pass, over the
 //      significant bits of the column (ROW_COL order only) and then of the row.
 //      Every pass is histogram -> exclusive scan -> stable scatter; the records
 //      themselves travel, so no gather through a permutation is needed.
@@ -171,11 +171,14 @@ static SortPlan plan(const spt_tensor* A, int32_t order) {
   P.passes_col = order == SPT_ORDER_ROW_COL ? (bits_for(A->level[1].N) + kRadixBits - 1) / kRadixBits : 0;
   P.passes_row = (bits_for(A->level[0].N) + kRadixBits - 1) / kRadixBits;
   P.ntiles = (int)((nnz + kSortTile - 1) / kSortTile);
-  P.rec_bytes = align_up((size_t)nnz * 4, 256) * 2 + align_up((size_t)nnz * vsz, 256);
+  // records between passes: the last one writes columns and values to the caller's arrays
+  const int passes = P.passes_col + P.passes_row;
+  const size_t row = align_up((size_t)nnz * 4, 256), rest = row + align_up((size_t)nnz * vsz, 256);
+  P.rec_bytes = std::min(passes, 2) * row + std::min(passes - 1, 2) * rest;
   P.hist_bytes = align_up((size_t)kRadix * P.ntiles * 4, 256);
   const int64_t scan_n = std::max<int64_t>((int64_t)kRadix * P.ntiles, A->level[0].N + 1);
   P.scan_bytes = scan_workspace(scan_n);
-  P.total = 2 * P.rec_bytes + P.hist_bytes + P.scan_bytes + 256;
+  P.total = P.rec_bytes + P.hist_bytes + P.scan_bytes + 256;
   return P;
 }
 
@@ -187,9 +190,27 @@ spt_status sample_sort_convert(int64_t n, int64_t nrows, int64_t ncols, bool by_
                                const int32_t* col, const VT* vals, int32_t* pos_out, int32_t* crd_out,
                                VT* vals_out, void* ws, size_t ws_bytes, hipStream_t s);
 
+// The sample sort takes one launch, one partition or two and a finish, whatever the key; a radix sort a pass per 8
+// bits of it. Keys of few bits (a stable order of the rows, small matrices) are for the latter from where the
+// sample sort needs its next step (fp64, in us, radix / sample; fp32 alike, power-law rows more for radix):
+//   passes            130 000     400 000     1.6M         6.4M         30M
+//   1 (200 rows)       31 / 37     30 / 84     36 / 124     84 / 301    306 / 1013
+//   2 (60 000 rows)    61 / 38     62 / 81     69 / 120    168 / 285    601 / 973
+//   3 (4M rows)       109 / 87    107 / 96    118 / 121    256 / 279    857 / 920
+//   4                 115 / 36    123 / 82    134 / 120    331 / 273   1164 / 902
+static bool radix_is_faster(const SortPlan& P, const spt_tensor* A) {
+  const int passes = P.passes_col + P.passes_row;
+  const int64_t from = passes == 1 ? 1 << 16 : passes == 2 ? 256 * 1408 : 3 << 19;
+  return !sample_sort_applies(A->nvals) || (passes <= 3 && A->nvals > from);
+}
+
 size_t coo_to_csr_workspace(const spt_tensor* A) {
-  if (sample_sort_applies(A->nvals)) return sample_sort_workspace(A->dtype, A->nvals);
-  return std::max(plan(A, SPT_ORDER_ROW_COL).total, plan(A, SPT_ORDER_ROW_STABLE).total);
+  size_t need = sample_sort_applies(A->nvals) ? sample_sort_workspace(A->dtype, A->nvals) : 0;
+  for (const int32_t order : {SPT_ORDER_ROW_COL, SPT_ORDER_ROW_STABLE}) {
+    const SortPlan P = plan(A, order);
+    if (radix_is_faster(P, A)) need = std::max(need, P.total);
+  }
+  return need;
 }
 
 template <typename VT>
@@ -222,23 +243,22 @@ static spt_status convert_typed(const spt_tensor* A, int32_t order, int32_t* pos
     hipLaunchKernelGGL(copy_entries_kernel<VT>, dim3(egrid), dim3(kBlock), 0, s, nnz, col, vals,
                        crd_out, vals_out);
     SPT_CHECK_LAUNCH("copy_entries");
-  } else if (sample_sort_applies(nnz64)) {
+  } else if (!radix_is_faster(plan(A, order), A)) {
     return sample_sort_convert<VT>(nnz64, N, A->level[1].N, order == SPT_ORDER_ROW_COL, row, col, vals, pos_out,
                                    crd_out, vals_out, ws, ws_bytes, s);
   } else {
     const SortPlan P = plan(A, order);
     Workspace W(ws, ws_bytes);
-    int32_t* srow[2];
-    int32_t* scol[2];
-    VT* sval[2];
-    for (int b = 0; b < 2; ++b) {
-      srow[b] = W.take<int32_t>(nnz);
+    const int npass = P.passes_col + P.passes_row;
+    int32_t *srow[2] = {}, *scol[2] = {};
+    VT* sval[2] = {};
+    for (int b = 0; b < std::min(npass, 2); ++b) srow[b] = W.take<int32_t>(nnz);
+    for (int b = 0; b < std::min(npass - 1, 2); ++b) {
       scol[b] = W.take<int32_t>(nnz);
       sval[b] = W.take<VT>(nnz);
     }
     int32_t* hist = W.take<int32_t>((size_t)kRadix * P.ntiles);
     int32_t* scan_tmp = reinterpret_cast<int32_t*>(W.take<char>(P.scan_bytes));
-    const int npass = P.passes_col + P.passes_row;
     const int32_t *rin = row, *cin = col;
     const VT* vin = vals;
     for (int i = 0; i < npass; ++i) {

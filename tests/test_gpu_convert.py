@@ -272,6 +272,34 @@ def test_clustered_columns_take_no_longer():
     assert times[1] < 3 * times[0], f"{times[1]:.2f} ms clustered, {times[0]:.2f} with columns anywhere"
 
 
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("N,M,order,at", [
+    (200, 4_000_000, 1, 1 << 16),                                       # one pass
+    (60_000, 900, 1, 256 * 1408), (256, 129, 0, 256 * 1408),            # two
+    (3_000_000, 70_000, 1, 3 << 19), (60_000, 250, 0, 3 << 19),         # three
+])
+def test_short_keys_where_radix_passes_take_over(N, M, order, at, dtype):
+    """Both sides of the record counts from which one to three radix passes replace the sample sort, and 8M;
+    every third record in one row. The reference is torch's stable sort."""
+    import torch
+    import paper_1804_10112_amd as spt
+    g = torch.Generator(device="cuda").manual_seed(N + order)
+    np_dt, t_dt = (np.float64, torch.int64) if dtype == "f64" else (np.float32, torch.int32)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    for nnz in (at, at + 1, 8_000_003):
+        r = torch.randint(0, N, (nnz,), generator=g, **i32)
+        r[::3] = N // 2
+        c = torch.randint(0, M, (nnz,), generator=g, **i32)
+        v = torch.arange(nnz, dtype=t_dt, device="cuda")                # bits that tell the position
+        A = spt.DeviceTensor(wl.coo_spec(N, M, [0], [0], np.zeros(1, np_dt), ordered=False))
+        A.c.level[0].crd, A.c.level[1].crd, A.c.vals, A.c.nvals = r.data_ptr(), c.data_ptr(), v.data_ptr(), nnz
+        pos, crd, vals = torch.empty(N + 1, **i32), torch.empty_like(c), torch.empty_like(v)
+        spt.spt_coo_to_csr(A, order, pos, crd, vals, A.workspace(spt.SPT_OP_COO_TO_CSR))
+        perm = torch.sort(r.long() * M + c if order == 0 else r, stable=True).indices
+        assert torch.equal(crd, c[perm]) and torch.equal(vals, perm.to(t_dt))
+        assert torch.equal(pos[1:].long(), torch.bincount(r, minlength=N).cumsum(0)) and int(pos[0]) == 0
+
+
 def test_more_records_than_the_sample_sort_takes():
     import torch
     import paper_1804_10112_amd as spt

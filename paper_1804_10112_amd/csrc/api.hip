@@ -23,7 +23,8 @@ spt_status fail(spt_status code, const char* fmt, ...) {
 spt_status spmv_dispatch(Format f, const spt_tensor* A, const void* x, void* y, void* ws,
                          size_t ws_bytes, hipStream_t s);
 size_t seg_spmv_workspace(int64_t nnz);
-size_t ordered_coo_workspace(int64_t nnz);
+size_t csr_spmv_workspace(const spt_tensor* A);
+size_t ordered_coo_spmv_workspace(const spt_tensor* A);
 size_t dcsr_spmv_workspace(const spt_tensor* A);
 size_t csc_spmv_workspace(const spt_tensor* A);
 spt_status aos_coo_spmv_dispatch(const spt_tensor* A, const void* x, void* y, void* ws,
@@ -710,9 +711,9 @@ size_t spt_workspace_bytes(int32_t op, const spt_tensor* T, int32_t J) {
       break;
     case SPT_OP_SPMV:
       if (f == Format::CSR)
-        n = seg_spmv_workspace(T->nvals);
+        n = csr_spmv_workspace(T);
       else if (f == Format::COO2 && (T->level[0].flags & SPT_ORDERED))
-        n = ordered_coo_workspace(T->nvals);
+        n = ordered_coo_spmv_workspace(T);
       else if (f == Format::COO2)
         n = coo_unordered_workspace(T->dtype, T->nvals, T->level[0].N);
       else if (f == Format::BCSR && bcsr_fast_ok(T))

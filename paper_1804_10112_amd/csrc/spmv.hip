@@ -21,6 +21,7 @@
 #include "carry.hpp"
 #include "common.hpp"
 #include "segreduce.hpp"
+#include "slices.hpp"
 #include "wavescan.hpp"
 
 namespace spt {
@@ -311,7 +312,7 @@ __global__ __launch_bounds__(kBlock) void seg_spmv_kernel(
     int nnz, int nrows, const int32_t* __restrict__ pos_or_row, const int32_t* __restrict__ col,
     const T* __restrict__ vals, const XP x, T* __restrict__ y,
     int32_t* __restrict__ carry_key, T* __restrict__ carry_val,
-    const int32_t* __restrict__ select, int want) {
+    const uint8_t* __restrict__ select, int want) {
   constexpr int CHUNK = IPT * kBlock;
   if (!selected(select, want)) return;  // the other CSR kernel was chosen on the device
   __shared__ T s_val[CHUNK + kBlock];
@@ -660,9 +661,11 @@ __global__ __launch_bounds__(kBlock) void csr_rows_if_kernel(int nblocks, int nr
                                                              const int32_t* __restrict__ pos,
                                                              const int32_t* __restrict__ crd,
                                                              const T* __restrict__ vals, const XP x,
-                                                             T* __restrict__ y, const int32_t* __restrict__ select,
-                                                             int want) {
-  if (!selected(select, want)) return;
+                                                             T* __restrict__ y, const ByRowsIf cond) {
+  if (!selected(cond.flags, false)) {
+    if (cond.seg_row) find_segment_rows(nrows, pos, cond.nseg, cond.seg_row, y);
+    return;
+  }
   for (int block = blockIdx.x; block < nblocks; block += gridDim.x) {
     csr_rows_block<T, G, R, true>(xcd_contiguous_block_id(block, nblocks), nrows, nnz, pos, crd, vals, x, y);
     __syncthreads();
@@ -781,16 +784,16 @@ static bool csr_use_rows(int64_t nnz, int64_t nrows, int hint, const void* ws, s
 template <typename T, class XP>
 static spt_status launch_csr_rows(int64_t nnz, int64_t nrows, const int32_t* pos, const int32_t* crd, const T* vals,
                                   const XP x, T* y, hipStream_t s, int64_t ncols = INT64_MAX,
-                                  const int32_t* select = nullptr, int want = 0) {
+                                  const ByRowsIf* cond = nullptr) {
   // Rows per group at once: two where rows are so short that one leaves a lane with a single load
   // (7 entries per row, 25.6M entries, fp64: 80 -> 70 us), else one. Up to 2^20 entries the chip is
   // not full and waves that hold fewer rows meet fewer long ones: groups twice as wide.
 #define SPT_ROWS(G_, R_)                                                                                      \
   do {                                                                                                        \
     const int nb = (int)((nrows + kBlock / G_ * R_ - 1) / (kBlock / G_ * R_));                                \
-    if (select)                                                                                               \
+    if (cond)                                                                                                 \
       hipLaunchKernelGGL((csr_rows_if_kernel<T, G_, R_, XP>), dim3(std::min(nb, kIfBlocks)), dim3(kBlock), 0, \
-                         s, nb, (int)nrows, (int)nnz, pos, crd, vals, x, y, select, want);                    \
+                         s, nb, (int)nrows, (int)nnz, pos, crd, vals, x, y, *cond);                           \
     else if (large)                                                                                           \
       hipLaunchKernelGGL((csr_rows_kernel<T, G_, R_, true, XP>), dim3(nb), dim3(kBlock), 0, s, (int)nrows,     \
                          (int)nnz, pos, crd, vals, x, y);                                                     \
@@ -806,7 +809,7 @@ static spt_status launch_csr_rows(int64_t nnz, int64_t nrows, const int32_t* pos
   constexpr bool dense = std::is_same<XP, DenseX<T>>::value;
   if constexpr (sizeof(T) == 4 || !dense) {
     // (its indices pass the end by up to a piece, which must not pass 2^31)
-    if (!select && nnz + 2 * kStreamPiece < INT32_MAX &&
+    if (!cond && nnz + 2 * kStreamPiece < INT32_MAX &&
         (dense ? large && nnz >= 8 * nrows && nnz <= kShortRow * nrows && ncols <= kStreamXBytes / (int)sizeof(T)
                : large)) {
       hipLaunchKernelGGL((csr_stream_kernel<T, XP>), dim3((unsigned)((nrows + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
@@ -1151,7 +1154,7 @@ static spt_status launch_fill(T* out, int64_t n, T v, hipStream_t s) {
 template <typename T, bool CSR, class XP>
 static spt_status launch_seg_x(int64_t nnz, int64_t nrows, const int32_t* pos_or_row,
                                const int32_t* col, const T* vals, const XP x, T* y, void* ws,
-                               size_t ws_bytes, hipStream_t s, const int32_t* select = nullptr,
+                               size_t ws_bytes, hipStream_t s, const uint8_t* select = nullptr,
                                int want = 0) {
   constexpr int CHUNK = kSegIPT * kBlock;
   if (nnz == 0) return launch_fill<T>(y, nrows, T(0), s);
@@ -1217,35 +1220,56 @@ static spt_status launch_coo_pieces(int64_t nnz, int64_t nrows, const int32_t* r
 template <typename T, bool CSR>
 static spt_status launch_seg(int64_t nnz, int64_t nrows, const int32_t* pos_or_row,
                              const int32_t* col, const T* vals, const T* x, T* y, void* ws,
-                             size_t ws_bytes, hipStream_t s, const int32_t* select = nullptr,
+                             size_t ws_bytes, hipStream_t s, const uint8_t* select = nullptr,
                              int want = 0) {
   return launch_seg_x<T, CSR, DenseX<T>>(nnz, nrows, pos_or_row, col, vals, DenseX<T>{x}, y, ws,
                                          ws_bytes, s, select, want);
 }
 
-// Large CSR matrices without a declared row bound: which kernel suits is decided on the device.
-// kSelectFlags workgroups look at the entry count of every block of 256 rows; if some block
-// holds more than 1/kSkewShare of all entries, the row-wise kernel would end on the workgroup of
-// one long row (10^5 entries keep it busy for about 0.1 ms), and the entry-balanced kernel runs
-// instead (60M entries, power law: 0.97 ms against 1.10). Both kernels are launched; the one not
-// chosen returns at once. That costs some 10 us, which is why only matrices of kDynamicMinEntries
-// entries or more (kernel times from 0.4 ms) are looked at.
+// Large CSR matrices without a declared row bound: which kernel suits is decided on the device. A few workgroups
+// look at the entry count of every block of 256 rows and, where x is too large for an L2, at samples of the columns;
+// then both candidates are launched, and the one not chosen returns at once (or finds the rows of the other's
+// segments). By entries if a block of rows is heavy (60M entries, power law: 0.97 ms against 1.10 by rows), with x
+// slice by slice if columns lie scattered. Looking and launching cost some 12 us, which is why only matrices of
+// kDynamicMinEntries entries or more (kernel times from 64 us) are looked at.
 constexpr int64_t kDynamicMinEntries = int64_t(1) << 25;
-constexpr int kSkewShare = 1536, kSkewRows = 256;
-__global__ __launch_bounds__(kBlock) void csr_skew_kernel(int nrows, int nnz, const int32_t* __restrict__ pos,
-                                                          int32_t* __restrict__ select) {
-  __shared__ int s_any;
-  if (threadIdx.x == 0) s_any = 0;
-  __syncthreads();
-  const int nblocks = (nrows + kSkewRows - 1) / kSkewRows;
-  int heavy = 0;
-  for (int b = blockIdx.x * kBlock + threadIdx.x; b < nblocks; b += kSelectFlags * kBlock) {
-    const int64_t e = pos[min((b + 1) * kSkewRows, nrows)] - pos[b * kSkewRows];
-    heavy |= e * kSkewShare > nnz;
-  }
-  if (heavy) s_any = 1;
-  __syncthreads();
-  if (threadIdx.x == 0) select[blockIdx.x] = s_any;  // any flag set: the entry-balanced kernel
+
+// x slice by slice (spmv_slices.hip)? Above, where the choice costs little next to the product; and for ordered COO
+// beyond kPiecesMaxEntries, where the one kernel does both (banded, 39M entries, against a kernel of chunks in LDS:
+// fp64 157 / 150 us, fp32 111 / 114). In us, uniform columns, without / with slices, by the size of x:
+//   36M entries, fp64, COO   4 MB 257 / 257    6 MB 312 / 264    12 MB 493 / 281   24 MB 606 / 323   48 MB 701 / 404
+//                            64 MB 712 / 461   96 MB 770 / 581 (some 4 us more per MB: equal at about 150 MB)
+//   36M entries, CSR         fp32 6 MB 272 / 234, 24 MB 593 / 294; fp64 24 MB 597 / 317, 96 MB 795 / 600
+//   17M entries, COO         fp64 8 MB 200 / 138; fp32 6.4 MB 155 / 133
+//   power law, CSR           fp64, 60M entries, 32 MB 970 / 576; fp32, 35M entries, 9.2 MB 378 / 248
+//   local columns, CSR, 36M  skewed rows fp64 177 / 156, fp32 115 / 114; mean row 90 fp64 154 / 123, fp32 96 / 100;
+//                            a declared bound of 16, which spared the choice before, fp64 107 / 121, fp32 63 / 76
+// Takes a larger workspace than the carries of the kernels it replaces; a caller with one of that size has those.
+constexpr int64_t kSlicesMinX = 6000000, kSlicesMaxX = 128000000;
+size_t slices_spmv_workspace(int64_t nnz);
+ByRowsIf slices_by_rows_if(int64_t nnz, void* ws);
+spt_status launch_csr_skew(int64_t nnz, int64_t nrows, const int32_t* pos, uint8_t* flags, hipStream_t s);
+template <typename T, bool CSR>
+spt_status launch_slices_prepare(int64_t nnz, int64_t nrows, int64_t ncols, const int32_t* pos, const int32_t* col, T* y,
+                                 void* ws, hipStream_t s);
+template <typename T, bool CSR>
+spt_status launch_slices_spmv(int64_t nnz, int64_t ncols, bool rows_may, const int32_t* pos_or_row, const int32_t* col,
+                              const T* vals, const T* x, T* y, void* ws, hipStream_t s);
+template <typename T>
+spt_status launch_segment_rows(int64_t nnz, int64_t nrows, const int32_t* pos, T* y, void* ws, hipStream_t s);
+
+static bool slices_may_pay(bool csr, int64_t nnz, int64_t ncols, int value_bytes) {
+  const int64_t x = ncols * value_bytes;
+  return nnz >= (csr ? kDynamicMinEntries : kPiecesMaxEntries + 1) && nnz + (1 << 16) < INT32_MAX && x > kSlicesMinX && x <= kSlicesMaxX;
+}
+// What spt_workspace_bytes answers; the least that a call takes is seg_spmv_workspace and ordered_coo_workspace.
+size_t csr_spmv_workspace(const spt_tensor* A) {
+  const size_t least = seg_spmv_workspace(A->nvals);
+  return slices_may_pay(true, A->nvals, A->level[1].N, A->dtype == SPT_F64 ? 8 : 4) ? std::max(least, slices_spmv_workspace(A->nvals)) : least;
+}
+size_t ordered_coo_spmv_workspace(const spt_tensor* A) {
+  const size_t least = ordered_coo_workspace(A->nvals);
+  return slices_may_pay(false, A->nvals, A->level[1].N, A->dtype == SPT_F64 ? 8 : 4) ? std::max(least, slices_spmv_workspace(A->nvals)) : least;
 }
 
 // y = A x, A in CSR, x a sparse vector (compressed level) or a hash map (hashed level).
@@ -1336,18 +1360,27 @@ static spt_status spmv_typed(Format f, const spt_tensor* A, const T* x, T* y, vo
       const int hint = A->level[1].max_children;
       const int64_t nnz = A->nvals, N = A->level[0].N;
       const int32_t *pos = A->level[1].pos, *crd = A->level[1].crd;
-      if (!csr_use_rows(nnz, N, hint, ws, ws_bytes)) return launch_seg<T, true>(nnz, N, pos, crd, vals, x, y, ws, ws_bytes, s);
-      if (hint > 0 || nnz < kDynamicMinEntries) return launch_csr_rows<T>(nnz, N, pos, crd, vals, DenseX<T>{x}, y, s, A->level[1].N);
+      const int64_t M = A->level[1].N;
+      const bool rows = csr_use_rows(nnz, N, hint, ws, ws_bytes);
+      if (slices_may_pay(true, nnz, M, sizeof(T)) && ws && ws_bytes >= slices_spmv_workspace(nnz) && N + kBlock < INT32_MAX) {
+        const ByRowsIf cond = slices_by_rows_if(nnz, ws);
+        spt_status st = launch_slices_prepare<T, true>(nnz, N, M, pos, crd, y, ws, s);
+        if (st == SPT_OK)
+          st = rows ? launch_csr_rows<T>(nnz, N, pos, crd, vals, DenseX<T>{x}, y, s, M, &cond)
+                    : launch_segment_rows<T>(nnz, N, pos, y, ws, s);
+        return st == SPT_OK ? launch_slices_spmv<T, true>(nnz, M, rows, pos, crd, vals, x, y, ws, s) : st;
+      }
+      if (!rows) return launch_seg<T, true>(nnz, N, pos, crd, vals, x, y, ws, ws_bytes, s);
+      if (hint > 0 || nnz < kDynamicMinEntries) return launch_csr_rows<T>(nnz, N, pos, crd, vals, DenseX<T>{x}, y, s, M);
       if (!ws || ws_bytes < seg_spmv_workspace(nnz))
         return fail(SPT_ERR_WORKSPACE, "spmv: workspace of %zu bytes needed, %zu given", seg_spmv_workspace(nnz),
                     ws_bytes);
       // the flags live in the last 256 bytes of the workspace, behind the carries
-      int32_t* select = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + seg_spmv_workspace(nnz) - 256);
-      hipLaunchKernelGGL(csr_skew_kernel, dim3(kSelectFlags), dim3(kBlock), 0, s, (int)N, (int)nnz, pos, select);
-      SPT_CHECK_LAUNCH("csr skew");
-      spt_status st = launch_csr_rows<T>(nnz, N, pos, crd, vals, DenseX<T>{x}, y, s, A->level[1].N, select, 0);
-      if (st != SPT_OK) return st;
-      return launch_seg<T, true>(nnz, N, pos, crd, vals, x, y, ws, ws_bytes, s, select, 1);
+      uint8_t* select = static_cast<uint8_t*>(ws) + seg_spmv_workspace(nnz) - 256;
+      const ByRowsIf cond{select, nullptr, 0};
+      spt_status st = launch_csr_skew(nnz, N, pos, select, s);
+      if (st == SPT_OK) st = launch_csr_rows<T>(nnz, N, pos, crd, vals, DenseX<T>{x}, y, s, M, &cond);
+      return st == SPT_OK ? launch_seg<T, true>(nnz, N, pos, crd, vals, x, y, ws, ws_bytes, s, select, 1) : st;
     }
     case Format::CSC: {
       // (dense columns, compressed rows): the entries lie in column order, which makes the
@@ -1382,6 +1415,11 @@ static spt_status spmv_typed(Format f, const spt_tensor* A, const T* x, T* y, vo
                            dim3(kWave), 0, s, (int)nnz, (int)N, A->level[0].crd, A->level[1].crd, vals, x, y);
         SPT_CHECK_LAUNCH("coo_small_spmv");
         return SPT_OK;
+      }
+      if ((A->level[0].flags & SPT_ORDERED) && slices_may_pay(false, nnz, A->level[1].N, sizeof(T)) && ws &&
+          ws_bytes >= slices_spmv_workspace(nnz)) {
+        spt_status st = launch_slices_prepare<T, false>(nnz, N, A->level[1].N, nullptr, A->level[1].crd, y, ws, s);
+        return st == SPT_OK ? launch_slices_spmv<T, false>(nnz, A->level[1].N, false, A->level[0].crd, A->level[1].crd, vals, x, y, ws, s) : st;
       }
       if ((A->level[0].flags & SPT_ORDERED) && nnz <= kPiecesMaxEntries)
         return launch_coo_pieces<T>(nnz, N, A->level[0].crd, A->level[1].crd, vals, x, y, ws, ws_bytes, s);
@@ -1491,13 +1529,21 @@ __global__ __launch_bounds__(kBlock) void split_pairs_kernel(int64_t n, const in
   col[p] = rc[2 * p + 1];
 }
 
-static size_t coo_matrix_spmv_workspace(const spt_tensor* A) {
+static size_t aos_pairs_bytes(const spt_tensor* A) { return 2 * align_up(static_cast<size_t>(A->nvals) * 4, 256); }
+static size_t coo_least_workspace(const spt_tensor* A) {
   return (A->level[0].flags & SPT_ORDERED) ? ordered_coo_workspace(A->nvals)
                                            : coo_unordered_workspace(A->dtype, A->nvals, A->level[0].N);
 }
 
 size_t aos_coo_spmv_workspace(const spt_tensor* A) {
-  return 2 * align_up(static_cast<size_t>(A->nvals) * 4, 256) + coo_matrix_spmv_workspace(A);
+  return aos_pairs_bytes(A) + ((A->level[0].flags & SPT_ORDERED) ? ordered_coo_spmv_workspace(A) : coo_least_workspace(A));
+}
+
+// The least that spt_spmv takes where that is less than `query`, what spt_workspace_bytes answers.
+size_t spmv_least_workspace(Format f, const spt_tensor* A, size_t query) {
+  if (f == Format::CSR) return std::min(query, seg_spmv_workspace(A->nvals));
+  if (f == Format::COO2) return std::min(query, coo_least_workspace(A));
+  return query;
 }
 
 spt_status spmv_dispatch(Format f, const spt_tensor* A, const void* x, void* y, void* ws,
@@ -1508,7 +1554,7 @@ spt_status spmv_dispatch(Format f, const spt_tensor* A, const void* x, void* y, 
 spt_status aos_coo_spmv_dispatch(const spt_tensor* A, const void* x, void* y, void* ws,
                                  size_t ws_bytes, hipStream_t s) {
   const int64_t nnz = A->nvals;
-  const size_t need = aos_coo_spmv_workspace(A);
+  const size_t need = aos_pairs_bytes(A) + coo_least_workspace(A);
   if (nnz > 0 && (!ws || ws_bytes < need))
     return fail(SPT_ERR_WORKSPACE, "spmv: workspace of %zu bytes needed, %zu given", need, ws_bytes);
   spt_tensor S = *A;

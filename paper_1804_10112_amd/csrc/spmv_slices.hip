@@ -1,0 +1,341 @@
+// SpMV on CSR and ordered COO whose columns lie anywhere in an x that no L2 holds: x is gathered slice by slice.
+//
+// Entry after entry, such gathers miss L2, and the fabric brings 64 G lines of 128 bytes a second, whatever is
+// used of them (60M entries, 4M columns, fp64: 57M lines, 0.95 ms). Here every compute unit holds 32 768 entries
+// at a time, 32 per lane, in registers, and the chip sweeps over x in slices of 3.2 MB, which an L2 of 4 MB holds:
+// in each, the entries whose column lies in it fetch their x, all others wait. A line of x is then brought to an
+// XCD once per 1M of its entries instead of once per entry: 26M lines, 0.57 ms.
+//  * The waves of a workgroup meet after each slice; the workgroups of an XCD keep together by themselves, since
+//    the first to enter a slice wait for lines that the others then find. (Without the meeting 0.95 ms, the oldest
+//    waves run ahead; with a barrier across the XCD before the sweep 0.71, with one between slices slower still.)
+//  * Segments of 256 entries are dealt out across the matrix: a row of 10^5 entries lies in a few slices, and
+//    workgroups of consecutive entries would drift apart (0.86 ms; 2048 consecutive entries per wave: 0.73).
+//  * The number of workgroups is a multiple of the compute units, one of them to each (128 registers a lane): with
+//    as many as there are full ones, the last round took as long as the others (0.71 against 0.68 ms).
+//  * 3.2 MB: of 2 to 4 MB the time differs by 2 % at 32 MB; smaller slices cost a pass over the entries each
+//    (96 MB: 0.68 ms at 2.5 MB, 0.58 at 3.5). 36 entries per lane: 0.61 ms, with copies through scratch memory.
+// Bound by the address unit (a load with a few lanes takes it some 20 clocks), then the lines.
+#include <algorithm>
+
+#include "carry.hpp"
+#include "common.hpp"
+#include "slices.hpp"
+#include "wavescan.hpp"
+
+namespace spt {
+
+constexpr int kSliceBlock = 1024, kSliceWaves = kSliceBlock / kWave;
+constexpr int64_t kSliceBytes = 3200000;
+constexpr int kSegments = 8;  // of a wave, each a vector of four entries per lane
+constexpr int kCus = 256;
+
+// What precedes the product, kChoiceFlags workgroups.
+// CSR: does a block of kSkewRows rows hold more than 1 / kSkewShare of all entries? By rows, the kernel would end on
+// the workgroup of one long row (10^5 entries keep it busy for about 0.1 ms). COO: y = 0.
+// Both: do columns lie scattered? Each wave looks at a window of 256 entries: they do if they lie in 16 or more of
+// 64 equal parts of x (random columns in about 63, seven diagonals in at most 14). A window without a descending column
+// lies inside a row and tells nothing: a long row's columns ascend slowly, and yet each is another line.
+constexpr int kSkewShare = 1536, kSkewRows = 256, kScattered = 16;
+template <typename T, bool CSR>
+__global__ __launch_bounds__(kSliceBlock) void slices_prepare_kernel(int nnz, int nrows, int ncols,
+                                                                     const int32_t* __restrict__ pos,
+                                                                     const int32_t* __restrict__ col, T* __restrict__ y,
+                                                                     uint8_t* __restrict__ flags) {
+  typedef int32_t I4 __attribute__((ext_vector_type(4), aligned(4)));
+  __shared__ int s_heavy, s_tell, s_scattered;
+  const int tid = threadIdx.x, lane = lane_id(), w = wave_id(), b = blockIdx.x;
+  if (tid == 0) s_heavy = s_tell = s_scattered = 0;
+  __syncthreads();
+  I4 c = 0;
+  const bool look = col && nnz >= kSegment;  // uniform
+  if (look) {
+    const int64_t at = static_cast<int64_t>(nnz - kSegment) * (b * kSliceWaves + w) / (kChoiceFlags * kSliceWaves);
+    c = *reinterpret_cast<const I4*>(col + at + lane * 4);
+  }
+  if (CSR) {
+    const int nblocks = (nrows + kSkewRows - 1) / kSkewRows;
+    bool heavy = false;
+    for (int k = b * kSliceBlock + tid; k < nblocks; k += kChoiceFlags * kSliceBlock) {
+      const int64_t e = pos[min((k + 1) * kSkewRows, nrows)] - pos[k * kSkewRows];
+      heavy |= e * kSkewShare > nnz;
+    }
+    if (heavy) s_heavy = 1;
+  } else {
+    constexpr int R = 16 / sizeof(T);
+    typedef T V __attribute__((ext_vector_type(R), aligned(sizeof(T))));
+    for (int64_t e = (static_cast<int64_t>(b) * kSliceBlock + tid) * R; e < nrows; e += static_cast<int64_t>(kChoiceFlags) * kSliceBlock * R) {
+      if (e + R <= nrows) *reinterpret_cast<V*>(y + e) = V(T(0));
+      else
+        for (int64_t q = e; q < nrows; ++q) y[q] = T(0);
+    }
+  }
+  if (look) {
+    const float parts = 64.0f / ncols;
+    uint64_t in = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) in |= uint64_t{1} << min(static_cast<int>(c[q] * parts), 63);
+    const int32_t left = __shfl_up(c[3], 1);
+    const bool down = c[1] < c[0] || c[2] < c[1] || c[3] < c[2] || (lane > 0 && c[0] < left);
+    const bool tells = __ballot(down) != 0;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) in |= __shfl_xor(in, d);
+    if (lane == 0 && tells) {
+      atomicAdd(&s_tell, 1);
+      if (__popcll(in) >= kScattered) atomicAdd(&s_scattered, 1);
+    }
+  }
+  __syncthreads();
+  if (tid == 0) flags[b] = (s_heavy ? kChoiceHeavy : 0) | (2 * s_scattered > s_tell ? kChoiceScattered : 0) | (s_tell ? kChoiceTells : 0);
+}
+
+// Row starts of the segments where the row kernel is no candidate.
+template <typename T>
+__global__ __launch_bounds__(kBlock) void segment_rows_kernel(int nrows, const int32_t* __restrict__ pos, int nseg,
+                                                              int32_t* __restrict__ seg_row, T* __restrict__ y) {
+  find_segment_rows(nrows, pos, nseg, seg_row, y);
+}
+
+// Columns that do not lie scattered (the device's choice): the same with one slice, segments in order. A wave reduces
+// its segments one after the other in registers; the segment that holds a row's first entry stores the row's sum, what
+// precedes the first row start leaves as carry number `segment`. CSR: the rows that start in a segment are entered at
+// their first entry in LDS. Fixed order of additions: bit-reproducible.
+template <typename T, bool CSR>
+__global__ __launch_bounds__(kSliceBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) void slices_spmv_kernel(
+    int nnz, int nseg, int nslices, int slice, bool rows_may, const int32_t* __restrict__ pos_or_row, const int32_t* __restrict__ col,
+    const T* __restrict__ vals, const T* __restrict__ x, T* __restrict__ y, const int32_t* __restrict__ seg_row,
+    int32_t* __restrict__ carry_key, T* __restrict__ carry_val, const uint8_t* __restrict__ flags) {
+  constexpr int V = kSegments;
+  typedef T V4 __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+  typedef int32_t I4 __attribute__((ext_vector_type(4), aligned(4)));
+  extern __shared__ __attribute__((aligned(16))) int32_t s_rows[];  // CSR: the row that starts at an entry, or -1
+  const int choice = read_choice(flags);
+  if (rows_may && choice == kByRows) return;
+  const bool by_slices = choice == kBySlices;
+  const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  // segment of vector j: first + j * step, none from `limit` on
+  const int per = (nseg + gridDim.x - 1) / gridDim.x, mine = xcd_contiguous_block_id() * per;
+  const int step = by_slices ? kSliceWaves * gridDim.x : kSliceWaves;
+  const int limit = by_slices ? nseg : min(mine + per, nseg);
+  const int first = by_slices ? w * gridDim.x + blockIdx.x : mine + w;
+
+  uint32_t at[4 * V];
+  T got[4 * V];
+  constexpr uint32_t kNowhere = 0xFFFFFFFFu;
+#pragma unroll
+  for (int j = 0; j < V; ++j) {
+    const int seg = first + j * step;
+    const int64_t p = static_cast<int64_t>(seg) * kSegment;
+    if (seg < limit && p + kSegment <= nnz) {  // uniform
+      const I4 c = __builtin_nontemporal_load(reinterpret_cast<const I4*>(col + p + lane * 4));
+#pragma unroll
+      for (int q = 0; q < 4; ++q) at[4 * j + q] = static_cast<uint32_t>(c[q]) * sizeof(T);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int64_t e = p + lane * 4 + q;
+        at[4 * j + q] = seg < limit && e < nnz ? static_cast<uint32_t>(col[e]) * sizeof(T) : kNowhere;
+      }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 4 * V; ++k) got[k] = 0;
+  SliceGather<T, 4 * V>::run(x, by_slices ? nslices : 1, by_slices ? slice : kNowhere, at, got);
+
+  int32_t* heads = s_rows + w * (V * kSegment);
+  int r_first = 0;  // CSR, lane j: the first row that starts in segment j
+  if (CSR) {
+    constexpr int L = V <= 8 ? 8 : 4;  // lanes that enter the rows of a segment
+    const int j = min(lane / L, V - 1), seg = first + j * step, base = seg * kSegment;
+    const bool live = lane / L < V && seg < limit;
+    const int lo = live ? seg_row[seg] : 0, hi = live ? seg_row[seg + 1] : 0;
+#pragma unroll
+    for (int u = 0; u < V; ++u) *reinterpret_cast<I4*>(heads + u * kSegment + lane * 4) = I4(-1);
+    constexpr int kMany = 256;
+    const bool many = hi - lo > kMany;
+    if (!many) {
+      for (int r = lo + lane % L; r < hi; r += L) {
+        const int a = pos_or_row[r], b = pos_or_row[r + 1];
+        if (b > a) heads[j * kSegment + a - base] = r;
+      }
+    }
+    uint64_t todo = __ballot(many && lane % L == 0);
+    while (todo) {  // mostly rows without entries: the row of each entry is looked up instead
+      const int src = __ffsll(static_cast<long long>(todo)) - 1;
+      todo &= todo - 1;
+      const int l = __builtin_amdgcn_readlane(lo, src), h = __builtin_amdgcn_readlane(hi, src);
+      const int slot = __builtin_amdgcn_readlane(j, src) * kSegment, from = __builtin_amdgcn_readlane(base, src);
+      int r[4], end[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        r[q] = l - 1;
+        end[q] = h;
+      }
+      for (int span = h - l + 1; span > 1; span = (span + 1) / 2) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int mid = r[q] + (end[q] - r[q]) / 2;
+          if (mid > r[q]) {
+            if (pos_or_row[mid] - from <= lane * 4 + q) r[q] = mid;
+            else end[q] = mid;
+          }
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (r[q] >= l && lane * 4 + q < nnz - from && pos_or_row[r[q]] - from == lane * 4 + q) heads[slot + lane * 4 + q] = r[q];
+    }
+    r_first = __shfl(lo, min(lane * L, kWave - 1));
+  }
+
+    constexpr int kBatch = sizeof(T) == 8 ? 2 : 4;
+#pragma unroll
+  for (int h = 0; h < V; h += kBatch) {
+    V4 v[kBatch];
+    I4 rows[kBatch];
+    int32_t prior[kBatch];  // COO: row of the entry before the segment
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const int seg = first + (h + j) * step;
+      const int64_t p = static_cast<int64_t>(seg) * kSegment;
+      if (seg < limit && p + kSegment <= nnz) {  // uniform
+        v[j] = __builtin_nontemporal_load(reinterpret_cast<const V4*>(vals + p + lane * 4));
+        if (!CSR) rows[j] = __builtin_nontemporal_load(reinterpret_cast<const I4*>(pos_or_row + p + lane * 4));
+      } else if (seg < limit) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int64_t e = p + lane * 4 + q;
+          v[j][q] = e < nnz ? vals[e] : T(0);
+          if (!CSR) rows[j][q] = pos_or_row[e < nnz ? e : nnz - 1];
+        }
+      }
+      if (!CSR) prior[j] = seg > 0 && seg < limit ? pos_or_row[p - 1] : -1;
+    }
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const int seg = first + (h + j) * step;
+      if (seg >= limit) break;  // uniform
+      const int64_t left_over = nnz - static_cast<int64_t>(seg) * kSegment;
+      if (CSR) rows[j] = *reinterpret_cast<const I4*>(heads + (h + j) * kSegment + lane * 4);
+      const int cut = CSR ? __builtin_amdgcn_readlane(r_first, h + j) - 1 : prior[j];  // the row that the segment's start cuts
+      int32_t before = cut;
+      if (!CSR) {
+        const int32_t left = dpp_move<0x138, 0xf>(-1, rows[j][3]);  // wave_shr:1
+        if (lane > 0) before = left;
+      }
+      T acc = 0, lead = 0;
+      bool has_head = false, head_first = false;
+      int last_row = -1;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int32_t r = rows[j][q];
+        if (CSR ? r >= 0 : r != before) {
+          if (has_head) y[last_row] = acc;  // a row that starts and ends inside this lane
+          else lead = acc;
+          head_first = head_first || q == 0;
+          has_head = true;
+          last_row = r;
+          acc = 0;
+        }
+        acc += lane * 4 + q < left_over ? v[j][q] * got[4 * (h + j) + q] : T(0);
+        before = r;
+      }
+      const uint64_t marks = __ballot(has_head);
+      const int from = last_lane(marks, false), prev_head = last_lane(marks, true);
+      const T sum = wave_marked_sum<T>(acc, from >= 0 ? lane - from : kWave);
+      T open = dpp_move<0x138, 0xf>(T(0), sum);  // what is open before this lane
+      if (lane == 0) open = T(0);
+      const int open_row = __shfl(last_row, max(prev_head, 0));
+      if (has_head) {
+        if (prev_head >= 0) {
+          y[open_row] = open + lead;
+        } else {  // what precedes the segment's first row start
+          carry_key[seg] = lane == 0 && head_first ? -1 : cut;
+          carry_val[seg] = open + lead;
+        }
+      }
+      if (lane == kWave - 1) {  // the row still open at the end of the segment
+        if (from >= 0) {
+          y[has_head ? last_row : open_row] = sum;
+        } else {
+          carry_key[seg] = cut;
+          carry_val[seg] = sum;
+        }
+      }
+    }
+  }
+}
+
+struct SlicesWorkspace {
+  int nseg;
+  uint8_t* flags;
+  int32_t *seg_row, *carry_key;
+  void* carry_val;
+  size_t bytes;
+  SlicesWorkspace(int64_t nnz, void* ws) {
+    nseg = (int)((nnz + kSegment - 1) / kSegment);
+    Workspace W(ws, 0);
+    flags = W.take<uint8_t>(kChoiceFlags);
+    seg_row = W.take<int32_t>((size_t)nseg + 1);
+    carry_key = W.take<int32_t>(nseg);
+    carry_val = W.take<double>(nseg);
+    bytes = W.used;
+  }
+};
+size_t slices_spmv_workspace(int64_t nnz) { return SlicesWorkspace(nnz, nullptr).bytes; }
+ByRowsIf slices_by_rows_if(int64_t nnz, void* ws) {
+  const SlicesWorkspace W(nnz, ws);
+  return {W.flags, W.seg_row, W.nseg};
+}
+template <typename T>
+spt_status launch_segment_rows(int64_t nnz, int64_t nrows, const int32_t* pos, T* y, void* ws, hipStream_t s) {
+  const SlicesWorkspace W(nnz, ws);
+  hipLaunchKernelGGL(segment_rows_kernel<T>, dim3((unsigned)std::min<int64_t>((nrows + kBlock - 1) / kBlock, 4096)),
+                     dim3(kBlock), 0, s, (int)nrows, pos, W.nseg, W.seg_row, y);
+  SPT_CHECK_LAUNCH("segment rows");
+  return SPT_OK;
+}
+
+template <typename T, bool CSR>
+spt_status launch_slices_prepare(int64_t nnz, int64_t nrows, int64_t ncols, const int32_t* pos, const int32_t* col, T* y,
+                                 void* ws, hipStream_t s) {
+  const SlicesWorkspace W(nnz, ws);
+  hipLaunchKernelGGL((slices_prepare_kernel<T, CSR>), dim3(kChoiceFlags), dim3(kSliceBlock), 0, s, (int)nnz, (int)nrows,
+                     (int)ncols, pos, col, y, W.flags);
+  SPT_CHECK_LAUNCH("slices prepare");
+  return SPT_OK;
+}
+// Only whether a block of rows is heavy, CSR.
+spt_status launch_csr_skew(int64_t nnz, int64_t nrows, const int32_t* pos, uint8_t* flags, hipStream_t s) {
+  hipLaunchKernelGGL((slices_prepare_kernel<float, true>), dim3(kChoiceFlags), dim3(kSliceBlock), 0, s, (int)nnz, (int)nrows, 1,
+                     pos, nullptr, nullptr, flags);
+  SPT_CHECK_LAUNCH("csr skew");
+  return SPT_OK;
+}
+template <typename T, bool CSR>
+spt_status launch_slices_spmv(int64_t nnz, int64_t ncols, bool rows_may, const int32_t* pos_or_row, const int32_t* col,
+                              const T* vals, const T* x, T* y, void* ws, hipStream_t s) {
+  const SlicesWorkspace W(nnz, ws);
+  constexpr int V = kSegments, kPer = kSliceWaves * V;
+  const int nslices = (int)((ncols * (int64_t)sizeof(T) + kSliceBytes - 1) / kSliceBytes);
+  const uint32_t slice = (uint32_t)((ncols + nslices - 1) / nslices * sizeof(T));
+  const int grid = ((W.nseg + kPer - 1) / kPer + kCus - 1) / kCus * kCus;
+  T* cval = static_cast<T*>(W.carry_val);
+  hipLaunchKernelGGL((slices_spmv_kernel<T, CSR>), dim3(grid), dim3(kSliceBlock), CSR ? kPer * kSegment * 4 : 0, s, (int)nnz,
+                     W.nseg, nslices, (int)slice, rows_may, pos_or_row, col, vals, x, y, W.seg_row, W.carry_key, cval, W.flags);
+  SPT_CHECK_LAUNCH("slices_spmv");
+  hipLaunchKernelGGL((carry_fixup_kernel<T, 16>), dim3((W.nseg + kBlock - 1) / kBlock), dim3(kBlock), 0, s, W.nseg, W.carry_key, cval,
+                     y, rows_may ? W.flags : nullptr, 1);
+  SPT_CHECK_LAUNCH("carry_fixup");
+  return SPT_OK;
+}
+#define SPT_SLICES(T, C)                                                                                              \
+  template spt_status launch_slices_prepare<T, C>(int64_t, int64_t, int64_t, const int32_t*, const int32_t*, T*,       \
+                                                  void*, hipStream_t);                                                \
+  template spt_status launch_slices_spmv<T, C>(int64_t, int64_t, bool, const int32_t*, const int32_t*, const T*,      \
+                                               const T*, T*, void*, hipStream_t);
+template spt_status launch_segment_rows<double>(int64_t, int64_t, const int32_t*, double*, void*, hipStream_t);
+template spt_status launch_segment_rows<float>(int64_t, int64_t, const int32_t*, float*, void*, hipStream_t);
+SPT_SLICES(double, true) SPT_SLICES(double, false) SPT_SLICES(float, true) SPT_SLICES(float, false)
+#undef SPT_SLICES
+
+}  // namespace spt

@@ -11,6 +11,8 @@
 
 namespace spt {
 
+size_t spmv_least_workspace(Format f, const spt_tensor* A, size_t query);
+
 constexpr size_t kStaticScratchBytes = SPT_STATIC_SCRATCH_BYTES;  // held by every GPU the library runs on
 
 // Every GPU holds its own copy of this array at its own address. In host code the name is
@@ -51,7 +53,8 @@ extern "C" {
 
 spt_status spt_spmv_static(const spt_tensor* A, const void* x, void* y, void* stream) {
   clear_error();
-  const size_t need = spt_workspace_bytes(SPT_OP_SPMV, A, 0);  // 0: invalid descriptor, error set
+  const size_t query = spt_workspace_bytes(SPT_OP_SPMV, A, 0);  // 0: invalid descriptor, error set
+  const size_t need = query ? spmv_least_workspace(recognize(A), A, query) : 0;
   if (need == 0) return spt_spmv(A, x, y, nullptr, 0, stream);  // reports what is wrong with A
   if (need > kStaticScratchBytes)
     return fail(SPT_ERR_WORKSPACE,

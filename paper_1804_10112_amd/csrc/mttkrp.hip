@@ -11,10 +11,13 @@
 //   - CSF: i and k are the last slice and fibre that start at or before an entry. The starts inside a
 //     chunk are marked in a bit set in LDS; C[k, :] is multiplied once per fibre (factored form).
 // Bound by the gathers of factor rows, large tensors by those that miss L2 (50M entries, J = 32, fp32:
-// 970 us, 68M lines of 128 bytes from L2, of them 37M from beyond; more or fewer waves, the next rows
-// loaded ahead, or C[k, :] kept while k stays change nothing). With 32 lanes of one column per entry,
-// which issue four times as many loads and hand-arounds, and longer walks per group: 1080 us, and for
-// 738 000 entries in CSF, J = 16, fp64, 96 us instead of 41.
+// 680 us, 72M lines of 128 bytes from L2, of them 38M from beyond, which the fabric brings in 600). Chunks go to the
+// XCDs in turn: with one contiguous part of a skewed tensor to each, the XCD with its last slices fetched twice as
+// many lines as the others and took 960 us (738 000 entries in CSF, J = 16, fp64: 41 -> 38; 15M entries, J = 32,
+// fp64, 703 -> 555; runs of 4 or 16 chunks the same). C read past the caches: 880 us. Measured before that: more or
+// fewer waves, the next rows loaded ahead, or C[k, :] kept while k stays change nothing; 32 lanes of one column per
+// entry, which issue four times as many loads and hand-arounds, and longer walks per group take 12 % longer, and for
+// 738 000 entries twice as long.
 #include <algorithm>
 
 #include "common.hpp"
@@ -155,7 +158,8 @@ __global__ __launch_bounds__(kBlock) void mttkrp_rows_kernel(int n, int J, int e
   __shared__ int s_slice_first;  // the chunk starts with a slice
   const int tid = threadIdx.x, lane = lane_id();
   const int g = tid / L, gl = tid % L;
-  const int chunk = xcd_contiguous_block_id(), size = NG * epg;
+  // (in turn to the XCDs: in one piece, the last has the slices of few entries, whose rows of C nobody shares)
+  const int chunk = blockIdx.x, size = NG * epg;
   const int base = chunk * size, end = min(base + size, n);
   // the last vector of a row ends with the row (it repeats columns of the one before if J is no multiple of V)
   const bool jok = (static_cast<int>(blockIdx.y) * L + gl) * V < J;

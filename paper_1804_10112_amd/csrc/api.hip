@@ -315,7 +315,7 @@ static bool ws_misaligned(const void* ws) {
 }
 
 // An array-of-structs COO matrix: both levels read one array of (row, col) pairs.
-static bool is_aos_coo_matrix(const spt_tensor* T) {
+bool is_aos_coo_matrix(const spt_tensor* T) {
   const spt_level* L = T->level;
   return T->order == 2 && T->nlevels == 2 && L[0].kind == SPT_COMPRESSED && L[0].M == 1 &&
          L[1].kind == SPT_SINGLETON && L[0].mode == 0 && L[1].mode == 1 && L[0].crd_stride == 2 &&

@@ -268,7 +268,7 @@ static spt_status convert_typed(const spt_tensor* A, int32_t order, int32_t* pos
       int32_t* rout = srow[i & 1];
       int32_t* cout = last ? crd_out : scol[i & 1];
       VT* vout = last ? vals_out : sval[i & 1];
-      spt_status hs = launch_radix_hist(is_row ? rin : cin, nnz, BitDigit{shift}, P.ntiles, hist, s);
+      spt_status hs = launch_radix_hist(is_row ? rin : cin, nnz, shift, P.ntiles, hist, s);
       if (hs != SPT_OK) return hs;
       spt_status st = device_scan_i32<false>(hist, hist, (int64_t)kRadix * P.ntiles, scan_tmp, s);
       if (st != SPT_OK) return st;

@@ -1,5 +1,4 @@
-// Pieces of the radix machinery shared by the COO->CSR sort and the binned
-// COO SpMV: digit extraction and the per-tile digit histogram.
+// Digits of the COO->CSR sort and of the binned COO SpMV, and the sort's histogram of them per tile.
 #pragma once
 #include "common.hpp"
 
@@ -21,12 +20,7 @@ __device__ __forceinline__ int digit_of(int32_t key, int shift) {
   return ((uint32_t)key >> shift) & (kRadix - 1);
 }
 
-// How a key becomes one of 256 digits: eight of its bits (a pass of the radix sort), or its place
-// among equal stretches of a dimension (binning by rows: digit d begins at first(d)).
-struct BitDigit {
-  int shift;
-  __device__ __forceinline__ int of(int32_t key) const { return digit_of(key, shift); }
-};
+// A key's place among 256 equal stretches of a dimension (binning by rows): digit d begins at first(d).
 struct StretchDigit {
   uint32_t mult;  // 2^32 * 256 / extent
   explicit StretchDigit(int64_t extent) {
@@ -65,9 +59,9 @@ __device__ __forceinline__ void count_digit_runs(int* cnt, int d) {
 // one count per tile and digit stored on its own would be a scattered 4-byte write.
 // VEC: 16-byte key loads (needs a 16-byte aligned key array).
 constexpr int kHistGroup = 8;
-template <bool VEC, class DIGIT>
+template <bool VEC>
 __global__ __launch_bounds__(kBlock) void radix_hist_kernel(const int32_t* __restrict__ key, int n,
-                                                            const DIGIT digit, int ntiles, int group,
+                                                            int shift, int ntiles, int group,
                                                             int32_t* __restrict__ hist) {
   __shared__ int s_cnt[kHistGroup][kRadix];
   for (int q = threadIdx.x; q < group * kRadix; q += kBlock) (&s_cnt[0][0])[q] = 0;
@@ -86,21 +80,21 @@ __global__ __launch_bounds__(kBlock) void radix_hist_kernel(const int32_t* __res
         if (base + (q + 1) * kWave * 4 <= n) {  // the whole wave is inside the array
           const i4 k4 = __builtin_nontemporal_load(reinterpret_cast<const i4*>(key + i));
 #pragma unroll
-          for (int r = 0; r < 4; ++r) count_digit_runs(cnt, digit.of(k4[r]));
+          for (int r = 0; r < 4; ++r) count_digit_runs(cnt, digit_of(k4[r], shift));
         } else if (i + 4 <= n) {
           const i4 k4 = __builtin_nontemporal_load(reinterpret_cast<const i4*>(key + i));
 #pragma unroll
-          for (int r = 0; r < 4; ++r) atomicAdd(&cnt[digit.of(k4[r])], 1);
+          for (int r = 0; r < 4; ++r) atomicAdd(&cnt[digit_of(k4[r], shift)], 1);
         } else {
           for (int r = 0; r < 4; ++r)
-            if (i + r < n) atomicAdd(&cnt[digit.of(key[i + r])], 1);
+            if (i + r < n) atomicAdd(&cnt[digit_of(key[i + r], shift)], 1);
         }
       }
     } else {
 #pragma unroll 4
       for (int q = 0; q < kPart / kWave; ++q) {
         const int i = base + q * kWave + lane;
-        if (i < n) atomicAdd(&cnt[digit.of(key[i])], 1);
+        if (i < n) atomicAdd(&cnt[digit_of(key[i], shift)], 1);
       }
     }
   }
@@ -113,17 +107,16 @@ __global__ __launch_bounds__(kBlock) void radix_hist_kernel(const int32_t* __res
 
 #if defined(__HIPCC__)
 // Enqueues the histogram of the digits for every tile of kSortTile keys.
-template <class DIGIT>
-inline spt_status launch_radix_hist(const int32_t* key, int n, const DIGIT digit, int ntiles, int32_t* hist,
+inline spt_status launch_radix_hist(const int32_t* key, int n, int shift, int ntiles, int32_t* hist,
                                     hipStream_t s) {
   // few tiles: more, shorter workgroups (3.2M keys: 26 us with eight tiles each)
   const int group = ntiles >= 8192 ? kHistGroup : ntiles >= 2048 ? 2 : 1;
   if ((reinterpret_cast<uintptr_t>(key) & 15) == 0)
-    hipLaunchKernelGGL((radix_hist_kernel<true, DIGIT>), dim3((ntiles + group - 1) / group),
-                       dim3(kBlock), 0, s, key, n, digit, ntiles, group, hist);
+    hipLaunchKernelGGL((radix_hist_kernel<true>), dim3((ntiles + group - 1) / group),
+                       dim3(kBlock), 0, s, key, n, shift, ntiles, group, hist);
   else
-    hipLaunchKernelGGL((radix_hist_kernel<false, DIGIT>), dim3((ntiles + group - 1) / group),
-                       dim3(kBlock), 0, s, key, n, digit, ntiles, group, hist);
+    hipLaunchKernelGGL((radix_hist_kernel<false>), dim3((ntiles + group - 1) / group),
+                       dim3(kBlock), 0, s, key, n, shift, ntiles, group, hist);
   SPT_CHECK_LAUNCH("radix_hist");
   return SPT_OK;
 }

@@ -4,6 +4,9 @@
 
 namespace spt {
 
+// An x that an L2 holds need not be cut; beyond some 150 MB the passes cost more than the lines.
+constexpr int64_t kSlicesMinX = 6000000, kSlicesMaxX = 128000000, kSliceBytes = 3200000;
+
 constexpr int kSegment = 4 * kWave;  // consecutive entries that a wave reduces at a time
 
 // The row kernel as one of two candidates: where the choice is made, and what it leaves behind for the other if

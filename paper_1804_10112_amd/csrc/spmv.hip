@@ -11,7 +11,7 @@
 //    segmented scan; a row cut by a chunk boundary is finished by a tiny carry
 //    kernel. No atomics, results are bit-reproducible.
 //  * Sorted COO of up to 2^24 entries: a wave per 256 entries, in one launch up to 65 536.
-//  * Unsorted COO is the paper's scatter loop with atomic adds into y, from 786 432 entries on the binned
+//  * Unsorted COO is the paper's scatter loop with atomic adds into y, from 393 216 entries on the binned
 //    scatter of coo_bin.hip.
 //  * DIA and ELL read the diagonal-major / slot-major arrays with consecutive
 //    rows in consecutive lanes.
@@ -1110,20 +1110,27 @@ __global__ __launch_bounds__(kBlock) void coo_pieces_kernel(int nnz, int npieces
 
 // binned scatter for large unordered COO (coo_bin.hip)
 template <typename T>
-spt_status coo_binned_spmv(int64_t nnz, int64_t nrows, const int32_t* row, const int32_t* col,
+spt_status coo_binned_spmv(int64_t nnz, int64_t nrows, int64_t ncols, const int32_t* row, const int32_t* col,
                            const T* vals, const T* x, T* y, void* ws, size_t ws_bytes,
                            hipStream_t s);
 size_t coo_binned_workspace(int dtype, int64_t nnz, int64_t nrows);
-// Below this the scatter with atomics is cheaper than the six launches of the binned one. In us, scatter /
-// binned, fp64 (fp32 alike; CSC the same and 3 to 7 for its columns):
-//   entries                   100 000     400 000    786 000      1.6M
-//   uniform rows              8.5 / 40    22 / 44    41 / 51    77 / 58
-//   power law                 9.7 / 40    23 / 44    48 / 54    91 / 70
-//   half of them in one row   7.0 / 49    20 / 54    30 / 63    60 / 78
-constexpr int64_t kBinnedMinEntries = 3 << 18;
+// Below this the scatter with atomics is cheaper than the four launches of the binned one. In us, scatter /
+// binned, fp64 and fp32 (CSC the same and 3 to 7 for its columns):
+//   entries                   200 000           300 000           400 000           550 000           780 000
+//   uniform rows         14/21  18/20      19/22  23/21      23/23  27/21      32/24  34/22      42/26  44/24
+//   power law            15/21  18/20      21/22  24/21      28/23  31/21      39/24  42/23      52/26  55/25
+// Binning takes a workspace: up to kScatterMost entries a caller without it has the scatter.
+constexpr int64_t kBinnedMinEntries = 3 << 17, kScatterMost = 3 << 18;
 
 size_t coo_unordered_workspace(int dtype, int64_t nnz, int64_t nrows) {
   return nnz >= kBinnedMinEntries ? coo_binned_workspace(dtype, nnz, nrows) : 256;
+}
+// The least that a call takes.
+static size_t coo_unordered_least(int dtype, int64_t nnz, int64_t nrows) {
+  return nnz >= kScatterMost ? coo_binned_workspace(dtype, nnz, nrows) : 0;
+}
+static bool coo_use_bins(int dtype, int64_t nnz, int64_t nrows, const void* ws, size_t ws_bytes) {
+  return nnz >= kScatterMost || (nnz >= kBinnedMinEntries && ws && ws_bytes >= coo_binned_workspace(dtype, nnz, nrows));
 }
 
 constexpr int kSegIPT = 8;
@@ -1245,7 +1252,6 @@ constexpr int64_t kDynamicMinEntries = int64_t(1) << 25;
 //   local columns, CSR, 36M  skewed rows fp64 177 / 156, fp32 115 / 114; mean row 90 fp64 154 / 123, fp32 96 / 100;
 //                            a declared bound of 16, which spared the choice before, fp64 107 / 121, fp32 63 / 76
 // Takes a larger workspace than the carries of the kernels it replaces; a caller with one of that size has those.
-constexpr int64_t kSlicesMinX = 6000000, kSlicesMaxX = 128000000;
 size_t slices_spmv_workspace(int64_t nnz);
 ByRowsIf slices_by_rows_if(int64_t nnz, void* ws);
 spt_status launch_csr_skew(int64_t nnz, int64_t nrows, const int32_t* pos, uint8_t* flags, hipStream_t s);
@@ -1320,6 +1326,10 @@ size_t csc_spmv_workspace(const spt_tensor* A) {
          coo_unordered_workspace(A->dtype, A->nvals, A->level[1].N);
 }
 
+static size_t csc_spmv_least(const spt_tensor* A) {
+  return align_up(static_cast<size_t>(A->nvals) * 4, 256) + coo_unordered_least(A->dtype, A->nvals, A->level[1].N);
+}
+
 size_t dcsr_spmv_workspace(const spt_tensor* A) {
   return align_up(static_cast<size_t>(A->level[1].M) * 8, 256) + seg_spmv_workspace(A->nvals);
 }
@@ -1391,16 +1401,15 @@ static spt_status spmv_typed(Format f, const spt_tensor* A, const T* x, T* y, vo
       if (nnz >= INT32_MAX || M + 1 >= INT32_MAX)
         return fail(SPT_ERR_UNSUPPORTED, "spmv: more than 2^31 entries or columns");
       if (nnz == 0) return launch_fill<T>(y, N, T(0), s);
-      if (!ws || ws_bytes < csc_spmv_workspace(A))
-        return fail(SPT_ERR_WORKSPACE, "spmv: workspace of %zu bytes needed, %zu given",
-                    csc_spmv_workspace(A), ws_bytes);
+      if (!ws || ws_bytes < csc_spmv_least(A))
+        return fail(SPT_ERR_WORKSPACE, "spmv: workspace of %zu bytes needed, %zu given", csc_spmv_least(A), ws_bytes);
       Workspace W(ws, ws_bytes);
       int32_t* cols = W.take<int32_t>(nnz);
       spt_status st = launch_expand_parents((int)nnz, (int)M, A->level[1].pos, cols, s);
       if (st != SPT_OK) return st;
-      if (nnz >= kBinnedMinEntries)
-        return coo_binned_spmv<T>(nnz, N, A->level[1].crd, cols, vals, x, y,
-                                  static_cast<char*>(ws) + W.used, ws_bytes - W.used, s);
+      char* rest = static_cast<char*>(ws) + W.used;
+      if (coo_use_bins(A->dtype, nnz, N, rest, ws_bytes - W.used))  // (no columns to speak of: they ascend)
+        return coo_binned_spmv<T>(nnz, N, 0, A->level[1].crd, cols, vals, x, y, rest, ws_bytes - W.used, s);
       st = launch_fill<T>(y, N, T(0), s);
       if (st != SPT_OK) return st;
       hipLaunchKernelGGL(coo_atomic_spmv_kernel<T>, dim3((unsigned)((nnz + kScatterEntries - 1) / kScatterEntries)),
@@ -1426,8 +1435,8 @@ static spt_status spmv_typed(Format f, const spt_tensor* A, const T* x, T* y, vo
       if (A->level[0].flags & SPT_ORDERED)
         return launch_seg<T, false>(nnz, N, A->level[0].crd, A->level[1].crd, vals, x, y, ws, ws_bytes, s);
       if (nnz >= INT32_MAX) return fail(SPT_ERR_UNSUPPORTED, "spmv: more than 2^31 entries");
-      if (nnz >= kBinnedMinEntries)
-        return coo_binned_spmv<T>(nnz, N, A->level[0].crd, A->level[1].crd, vals, x, y, ws, ws_bytes,
+      if (coo_use_bins(A->dtype, nnz, N, ws, ws_bytes))
+        return coo_binned_spmv<T>(nnz, N, A->level[1].N, A->level[0].crd, A->level[1].crd, vals, x, y, ws, ws_bytes,
                                   s);
       spt_status st = launch_fill<T>(y, N, T(0), s);
       if (st != SPT_OK || nnz == 0) return st;
@@ -1532,17 +1541,21 @@ __global__ __launch_bounds__(kBlock) void split_pairs_kernel(int64_t n, const in
 static size_t aos_pairs_bytes(const spt_tensor* A) { return 2 * align_up(static_cast<size_t>(A->nvals) * 4, 256); }
 static size_t coo_least_workspace(const spt_tensor* A) {
   return (A->level[0].flags & SPT_ORDERED) ? ordered_coo_workspace(A->nvals)
-                                           : coo_unordered_workspace(A->dtype, A->nvals, A->level[0].N);
+                                           : coo_unordered_least(A->dtype, A->nvals, A->level[0].N);
 }
 
 size_t aos_coo_spmv_workspace(const spt_tensor* A) {
-  return aos_pairs_bytes(A) + ((A->level[0].flags & SPT_ORDERED) ? ordered_coo_spmv_workspace(A) : coo_least_workspace(A));
+  return aos_pairs_bytes(A) + ((A->level[0].flags & SPT_ORDERED) ? ordered_coo_spmv_workspace(A)
+                                                                 : coo_unordered_workspace(A->dtype, A->nvals, A->level[0].N));
 }
 
 // The least that spt_spmv takes where that is less than `query`, what spt_workspace_bytes answers.
+bool is_aos_coo_matrix(const spt_tensor* T);
 size_t spmv_least_workspace(Format f, const spt_tensor* A, size_t query) {
+  if (f == Format::Unsupported && is_aos_coo_matrix(A)) return std::min(query, aos_pairs_bytes(A) + coo_least_workspace(A));
   if (f == Format::CSR) return std::min(query, seg_spmv_workspace(A->nvals));
   if (f == Format::COO2) return std::min(query, coo_least_workspace(A));
+  if (f == Format::CSC) return std::min(query, csc_spmv_least(A));
   return query;
 }
 

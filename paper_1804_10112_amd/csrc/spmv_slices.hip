@@ -25,7 +25,6 @@
 namespace spt {
 
 constexpr int kSliceBlock = 1024, kSliceWaves = kSliceBlock / kWave;
-constexpr int64_t kSliceBytes = 3200000;
 constexpr int kSegments = 8;  // of a wave, each a vector of four entries per lane
 constexpr int kCus = 256;
 

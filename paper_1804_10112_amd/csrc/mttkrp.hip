@@ -10,12 +10,15 @@
 //     leaves as a carry (row, J values), which the carry kernels add in a fixed order (no atomics).
 //   - CSF: i and k are the last slice and fibre that start at or before an entry. The starts inside a
 //     chunk are marked in a bit set in LDS; C[k, :] is multiplied once per fibre (factored form).
-// Bound by the gathers of factor rows, large tensors by those that miss L2 (50M entries, J = 32, fp32:
-// 680 us, 72M lines of 128 bytes from L2, of them 38M from beyond, which the fabric brings in 600). Chunks go to the
+// Bound by the gathers of factor rows, large tensors by those that miss L2 (50M entries, J = 32, fp32: 650 us; with
+// all rows in L2, as a probe, 400). A row of C stays in registers while k does (loaded for every entry: 700 us, and 619
+// instead of 521 with a D that fits L2; same sums, bit for bit). Chunks go to the
 // XCDs in turn: with one contiguous part of a skewed tensor to each, the XCD with its last slices fetched twice as
 // many lines as the others and took 960 us (738 000 entries in CSF, J = 16, fp64: 41 -> 38; 15M entries, J = 32,
-// fp64, 703 -> 555; runs of 4 or 16 chunks the same). C read past the caches: 880 us. Measured before that: more or
-// fewer waves, the next rows loaded ahead, or C[k, :] kept while k stays change nothing; 32 lanes of one column per
+// fp64, 703 -> 555; runs of 4 or 16 chunks the same). Left out after measuring: C read past the caches (small tensors
+// take up to a third longer); half of D to every other XCD, each going through all entries (743 us: the streams are
+// read twice); chunks of twice the entries (1 % faster, fp64 CSF 2 % slower); six waves a SIMD (spills, 815). Before that: more or
+// fewer waves and the next rows loaded ahead change nothing; 32 lanes of one column per
 // entry, which issue four times as many loads and hand-arounds, and longer walks per group take 12 % longer, and for
 // 738 000 entries twice as long.
 #include <algorithm>
@@ -247,19 +250,27 @@ __global__ __launch_bounds__(kBlock) void mttkrp_rows_kernel(int n, int J, int e
       const int addr = 4 * ((lane & ~(L - 1)) + q);
       int i[4], k[4];
       T v[4], c[4][V], d[4][V];
+      bool fresh[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         i[r] = from_lane(addr, ri[r]);
         k[r] = from_lane(addr, rk[r]);
         const int l = from_lane(addr, rl[r]);
         v[r] = from_lane(addr, rv[r]);
-        load_cols<T, V>(Cm + static_cast<int64_t>(k[r]) * J + col, c[r]);
+        // a row of C is loaded for the first entry that it belongs to
+        fresh[r] = k[r] != (r ? k[r - 1] : cur_k) || (CSF && i[r] != (r ? i[r - 1] : cur));
+        if (fresh[r]) load_cols<T, V>(Cm + static_cast<int64_t>(k[r]) * J + col, c[r]);
         load_cols<T, V>(Dm + static_cast<int64_t>(l) * J + col, d[r]);
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         if (4 * q + r < batch) {
-          if (CSF && (i[r] != cur || k[r] != cur_k)) {  // close the fibre
+          if (!CSF) {
+#pragma unroll
+            for (int x = 0; x < V; ++x) c_cur[x] = fresh[r] ? c[r][x] : c_cur[x];
+            cur_k = k[r];
+          }
+          if (CSF && fresh[r]) {  // close the fibre
 #pragma unroll
             for (int x = 0; x < V; ++x) {
               acc[x] += c_cur[x] * t[x];
@@ -284,7 +295,7 @@ __global__ __launch_bounds__(kBlock) void mttkrp_rows_kernel(int n, int J, int e
 #pragma unroll
           for (int x = 0; x < V; ++x) {
             if (CSF) t[x] += v[r] * d[r][x];
-            else acc[x] += v[r] * c[r][x] * d[r][x];
+            else acc[x] += v[r] * c_cur[x] * d[r][x];
           }
         }
       }

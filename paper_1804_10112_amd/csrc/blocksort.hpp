@@ -1,5 +1,7 @@
 // Sorting of 32-bit words by one workgroup, in registers.
 #pragma once
+#include <utility>
+
 #include "common.hpp"
 
 namespace spt {
@@ -31,65 +33,112 @@ __device__ __forceinline__ uint32_t med3_u32(uint32_t a, uint32_t b, uint32_t bo
   return r;
 }
 
-// One comparison step of the network below: partner of key i = tid * E + e is i ^ MASK, MASK being
-// either one bit (a stride) or all bits below a power of two (the mirror step that opens a phase).
-template <int NT, int E, int MASK>
-__device__ __forceinline__ void bitonic_step(uint32_t (&v)[E], uint32_t* buf) {
-  constexpr int TOP = MASK & (MASK + 1) ? MASK : (MASK + 1) / 2;  // the bit that tells the pair apart
-  if constexpr (MASK < E) {
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      if (!(e & TOP)) {
-        const uint32_t a = v[e], b = v[e ^ MASK];
-        v[e] = min(a, b);
-        v[e ^ MASK] = max(a, b);
+// Two words of a thread in order.
+template <int A, int B, int E>
+__device__ __forceinline__ void order_pair(uint32_t (&v)[E]) {
+  const uint32_t a = v[A], b = v[B];
+  v[A] = min(a, b);
+  v[B] = max(a, b);
+}
+
+// The comparators of a merge exchange (Batcher's, as in Knuth 5.2.2 M), which orders any number of words.
+template <int N>
+struct MergeExchange {
+  int a[N * 6] = {}, b[N * 6] = {}, count = 0;
+  constexpr MergeExchange() {
+    static_assert(N <= 16, "");
+    int top = 1;
+    while (top < N) top *= 2;
+    for (int p = top / 2; p > 0; p /= 2) {
+      int q = top / 2, r = 0, d = p;
+      for (;;) {
+        for (int i = 0; i + d < N; ++i) {
+          if ((i & p) == r) {
+            a[count] = i;
+            b[count++] = i + d;
+          }
+        }
+        if (q == p) break;
+        d = q - p;
+        q /= 2;
+        r = p;
       }
     }
-  } else {
-    const int tid = threadIdx.x;
-    constexpr int LM = MASK / E;       // partner thread: tid ^ LM
-    constexpr int EM = MASK & (E - 1); // its key: e ^ EM
-    const uint32_t bound = (tid & (TOP / E)) ? ~0u : 0u;
-    uint32_t o[E];
-    if constexpr (LM < kWave) {
-#pragma unroll
-      for (int e = 0; e < E; ++e) o[e] = lane_xor_u32<LM>(v[e ^ EM]);
+  }
+};
+template <int OFF, int N, int E, int... K>
+__device__ __forceinline__ void merge_exchange(uint32_t (&v)[E], std::integer_sequence<int, K...>) {
+  constexpr MergeExchange<N> list;
+  (order_pair<OFF + list.a[K], OFF + list.b[K]>(v), ...);
+}
+
+// Orders words OFF .. OFF + N - 1 of a thread: in any order, or (BITONIC) a bitonic sequence, which takes fewer
+// comparators while its length is even.
+template <bool BITONIC, int OFF, int N, int E, int I = 0>
+__device__ __forceinline__ void order_words(uint32_t (&v)[E]) {
+  if constexpr (N > 1 && BITONIC && N % 2 == 0) {
+    if constexpr (I < N / 2) {
+      order_pair<OFF + I, OFF + I + N / 2>(v);
+      order_words<true, OFF, N, E, I + 1>(v);
     } else {
-      __syncthreads();
-#pragma unroll
-      for (int e = 0; e < E; ++e) buf[e * NT + tid] = v[e];
-      __syncthreads();
-#pragma unroll
-      for (int e = 0; e < E; ++e) o[e] = buf[(e ^ EM) * NT + (tid ^ LM)];
+      order_words<true, OFF, N / 2>(v);
+      order_words<true, OFF + N / 2, N / 2>(v);
     }
-#pragma unroll
-    for (int e = 0; e < E; ++e) v[e] = med3_u32(v[e], o[e], bound);
-  }
-}
-template <int NT, int E, int J>
-__device__ __forceinline__ void bitonic_strides(uint32_t (&v)[E], uint32_t* buf) {
-  if constexpr (J >= 1) {
-    bitonic_step<NT, E, J>(v, buf);
-    bitonic_strides<NT, E, J / 2>(v, buf);
-  }
-}
-template <int NT, int E, int K>
-__device__ __forceinline__ void bitonic_phases(uint32_t (&v)[E], uint32_t* buf) {
-  if constexpr (K <= NT * E) {
-    bitonic_step<NT, E, K - 1>(v, buf);
-    bitonic_strides<NT, E, K / 4>(v, buf);
-    bitonic_phases<NT, E, K * 2>(v, buf);
+  } else if constexpr (N > 1) {
+    merge_exchange<OFF, N>(v, std::make_integer_sequence<int, MergeExchange<N>().count>());
   }
 }
 
-// Ascending sort of the NT * E 32-bit words of the workgroup (powers of two): a bitonic network in
-// registers whose steps cost a lane movement and one v_med3 per word; only the few steps between
+// One comparison step of the network below: a thread's words meet those of thread tid ^ LM, LM being one bit (a stride)
+// or, in the MIRROR step that opens a phase, all bits below a power of two; they meet in reverse there.
+template <int NT, int E, int LM, bool MIRROR>
+__device__ __forceinline__ void bitonic_step(uint32_t (&v)[E], uint32_t* buf) {
+  constexpr int TOP = MIRROR ? (LM + 1) / 2 : LM;  // the bit that tells the pair apart
+  const int tid = threadIdx.x;
+  const uint32_t bound = (tid & TOP) ? ~0u : 0u;
+  uint32_t o[E];
+  if constexpr (LM < kWave) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) o[e] = lane_xor_u32<LM>(v[MIRROR ? E - 1 - e : e]);
+  } else {
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < E; ++e) buf[e * NT + tid] = v[e];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < E; ++e) o[e] = buf[(MIRROR ? E - 1 - e : e) * NT + (tid ^ LM)];
+  }
+#pragma unroll
+  for (int e = 0; e < E; ++e) v[e] = med3_u32(v[e], o[e], bound);
+}
+template <int NT, int E, int LM>
+__device__ __forceinline__ void bitonic_strides(uint32_t (&v)[E], uint32_t* buf) {
+  if constexpr (LM >= 1) {
+    bitonic_step<NT, E, LM, false>(v, buf);
+    bitonic_strides<NT, E, LM / 2>(v, buf);
+  }
+}
+template <int NT, int E, int T>
+__device__ __forceinline__ void bitonic_phases(uint32_t (&v)[E], uint32_t* buf) {
+  if constexpr (T <= NT) {
+    bitonic_step<NT, E, T - 1, true>(v, buf);
+    bitonic_strides<NT, E, T / 4>(v, buf);
+    order_words<true, 0, E>(v);
+    bitonic_phases<NT, E, T * 2>(v, buf);
+  }
+}
+
+// Ascending sort of the NT * E 32-bit words of the workgroup (NT a power of two, E up to 16): a bitonic network in
+// registers whose steps between threads cost a lane movement and one v_med3 per word; only the few steps between
 // waves go through LDS. (A merge sort of 64-bit keys in LDS took three times as long, a bitonic
-// network on 64-bit keys five times: compare-and-select of two registers.) On return buf[0 .. NT * E) holds the words in order, visible to all
-// threads. buf must be 16-byte aligned.
-// In two steps: the network, after which thread t holds words t * E .. t * E + E - 1, and the store.
+// network on 64-bit keys five times: compare-and-select of two registers.) Halving works for a bitonic sequence
+// of any even length, so E need be no power of two: an even E costs as much per word as the next power of two, an odd
+// one a little more (instructions per word, NT = 256: E = 4 97, 5 108, 6 104, 7 117, 8 104).
+// In two steps: the network, after which thread t holds words t * E .. t * E + E - 1, and the store, after which
+// buf[0 .. NT * E) holds the words in order, visible to all threads.
 template <int NT, int E>
 __device__ __forceinline__ void block_sort_regs(uint32_t (&v)[E], uint32_t* buf) {
+  order_words<false, 0, E>(v);
   bitonic_phases<NT, E, 2>(v, buf);
   __syncthreads();
 }

@@ -63,6 +63,14 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// Between accesses of a wave's lanes to the same LDS words: a wave's LDS operations are served in order, so only the
+// compiler has to keep theirs. (Not a volatile pointer, which hides from it that the memory is LDS: it then issues flat
+// operations, through the vector memory path.)
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Consecutive workgroup ids are dealt round-robin to the 8 XCDs, each with its
 // own L2. This maps blockIdx.x to a logical block id such that every XCD works
 // on one contiguous range of logical blocks, so neighbouring blocks (which

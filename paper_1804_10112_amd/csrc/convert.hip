@@ -51,7 +51,7 @@ __global__ __launch_bounds__(kBlock) void radix_scatter_kernel(
   const int tile_n = min(kSortTile, n - tile_base);
   const int wave_base = tile_base + w * (kWave * kSortIPT);
   const uint64_t lanes_below = ((uint64_t)1 << lane) - 1;
-  volatile int* cnt = s_cnt[w];
+  int* cnt = s_cnt[w];
 
   int32_t key[kSortIPT], oth[kSortIPT];
   VT val[kSortIPT];
@@ -78,9 +78,9 @@ __global__ __launch_bounds__(kBlock) void radix_scatter_kernel(
     const int before = __popcll(same & lanes_below);
     int basecnt = 0;
     if (valid) basecnt = cnt[d];
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_order();
     if (valid && before == 0) cnt[d] = basecnt + __popcll(same);
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_order();
     lpos[k] = basecnt + before;
   }
   __syncthreads();

@@ -26,18 +26,19 @@
 // 60: 1.80 ms; with the ranks of the bucket's records counted, 10.4 ms).
 //
 // Measured against the six radix passes it replaces (fp64): 60M records with power-law rows
-// 3.09 -> 1.80 ms (splitters 35 + 87 us, classify 2 x 150, scans 4 x 9, partitions 427 + 441,
-// finish 505); 50 000 records 171 -> 21 us. The partitions write 256 x 2 interleaved streams and
-// are bound by how the memory system takes them: with twice the waves per compute unit (512
-// threads, half the registers) they are slower (474 us), with tiles of 8192 too (515 us). The
-// finishing kernel is bound by vector instructions.
+// 3.09 -> 1.67 ms (splitters 17 + 70 us, classify 2 x 135, offsets 8 + 10, partitions 403 + 430,
+// finish 476); 5M records 0.21 ms, 250 000 56 us, 50 000 171 -> 22 us. The partitions write 256 x 2 interleaved streams
+// and are bound by how the memory system takes them: it is the bytes in flight that count. Two workgroups of 512 threads
+// on a compute unit: 60M records fp64 1.70 ms in all (before splitters and offsets were made as now), three 1.83, three
+// of 256 threads 1.87, two 1.68; 20M 0.62, 0.63, 0.64 and 0.65; fp32, 40M 1.01, 1.04, 1.03 and 1.06. Tiles of 6144 and
+// 8192: up to 4 and 8 % longer for fp64, 3 % shorter for fp32 of 40M. The
+// classification and the finishing kernel are bound by vector instructions (80 and 70 % of the time).
 #include <algorithm>
 
 #include "blocksort.hpp"
 #include "common.hpp"
 #include "radix.hpp"
 #include "rows.hpp"
-#include "scan.hpp"
 #include "wavescan.hpp"
 
 namespace spt {
@@ -48,8 +49,8 @@ constexpr int kCap = 4096;          // records either can sort in LDS
 constexpr int kStaged = 2048;       // records whose keys and values also pass through LDS (own bucket)
 constexpr int kTile = 4096;         // records per tile of a partition of many,
 constexpr int kSmallTile = 1024;    // and of few records (see tile_of)
-constexpr int kPart = 256;          // threads that scatter a tile
-constexpr int kPartWaves = kPart / kWave;
+// Threads that scatter a tile (few records: more, smaller workgroups).
+constexpr int part_threads(int tile) { return tile >= kTile ? 512 : 256; }
 constexpr int kGroup = 4;           // consecutive tiles that one workgroup classifies
 constexpr int kLiBits = 12;         // bits of a record's number inside its bucket; the rest of a word: its key, coarsely
 constexpr int kMaxSamples = 4096;   // numbered by kLiBits bits, too
@@ -59,6 +60,16 @@ constexpr int64_t kSelectMax = 64 * 1024;                   // every workgroup r
 constexpr int64_t kOneLevelMax = int64_t(256) * kDirTarget;  // 256 buckets that fit LDS
 constexpr int64_t kSampleSortMax = int64_t(1) << 26;  // 256 x 256 buckets of kDirTarget and the sample's spread
 constexpr int kSegMax = 256;        // buckets of a partition
+
+// p[i] at an offset of 32 bits (fewer instructions than a 64-bit address): for fewer than 2^29 elements.
+template <typename E>
+__device__ __forceinline__ const E& at32(const E* p, int i) {
+  return *reinterpret_cast<const E*>(reinterpret_cast<const char*>(p) + static_cast<uint32_t>(i) * static_cast<uint32_t>(sizeof(E)));
+}
+template <typename E>
+__device__ __forceinline__ E& at32(E* p, int i) {
+  return *reinterpret_cast<E*>(reinterpret_cast<char*>(p) + static_cast<uint32_t>(i) * static_cast<uint32_t>(sizeof(E)));
+}
 
 // Position of sample t of S out of m records: one in every m / S, at a place of the stretch that
 // differs from stretch to stretch.
@@ -91,11 +102,18 @@ struct RcSource {
     return (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_nontemporal_load(row + p))) << f.cb) |
            static_cast<uint32_t>(__builtin_nontemporal_load(col + p));
   }
+  __device__ __forceinline__ RcSource from(int p) const { return {row + p, col + p}; }
+  __device__ __forceinline__ uint64_t key_near(int p, const KeyForm& f) const {
+    return (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_nontemporal_load(&at32(row, p)))) << f.cb) |
+           static_cast<uint32_t>(__builtin_nontemporal_load(&at32(col, p)));
+  }
 };
 struct KSource {
   const uint64_t* __restrict__ k;
   __device__ __forceinline__ uint64_t key(int p, const KeyForm&) const { return k[p]; }
   __device__ __forceinline__ uint64_t key_stream(int p, const KeyForm&) const { return __builtin_nontemporal_load(k + p); }
+  __device__ __forceinline__ KSource from(int p) const { return {k + p}; }
+  __device__ __forceinline__ uint64_t key_near(int p, const KeyForm&) const { return __builtin_nontemporal_load(&at32(k, p)); }
 };
 
 // A cut of the order: everything from (key, pos) on.
@@ -137,7 +155,7 @@ __device__ __forceinline__ bool crowded(const uint32_t (&v)[E], int n) {
       c = c || (tid * E + e + kCrowd <= n && v[e] >> kLiBits == v[e + kCrowd - 1] >> kLiBits);
     return c;
   } else {
-    constexpr int D = kCrowd / E - 1;  // lanes further on
+    constexpr int D = (kCrowd + E - 1) / E - 1;  // lanes further on
     const uint32_t last = dpp_u32<0x100 | D>(v[E - 1]);  // row_shl:D
     return (tid & 15) + D < 16 && (tid + D + 1) * E <= n && v[0] >> kLiBits == last >> kLiBits;
   }
@@ -154,7 +172,7 @@ __device__ __forceinline__ bool crowded(const uint32_t (&v)[E], int n) {
 // 16 900 / 1151. From eight records on, rows of 10 neighbours would gain 4 %, but power-law rows, whose long ones
 // crowd a few buckets, lose up to 2 %: 6M records 271 us counted, 272 and 276 sorted again from 16 and from 8 on.
 // Looking for such stretches costs 0.5 of 21 us for 50 000 records.)
-// Bound by vector instructions (110 of 225 per record in the finishing kernel are the network).
+// Bound by vector instructions (half of them in the finishing kernel are the network).
 // Left out after measuring: dealing the words to 1024 equal bins of the key range and ranking
 // inside the bins (631 instead of 503 us for 60M records with power-law rows: long and short rows
 // in one bucket crowd the bins).
@@ -233,12 +251,56 @@ __device__ __forceinline__ int coarse_shift(uint64_t lo, uint64_t hi) {
 }
 
 // ---- splitters ------------------------------------------------------------------------------
-// Sorts S = 1024 * E sampled keys of segment blockIdx.x and takes every (S / nb)th as a splitter.
-// LEVEL2: the segment is a bucket of level 1 (bounds from that level's scanned counts `off1`),
-// nb follows from its size, and the workgroup fills in its rows of the segment tables.
-template <int E, class SRC, bool LEVEL2>
-__global__ __launch_bounds__(1024) void splitters_kernel(const SRC src, const KeyForm f, int n, int nrows, int nb_fixed, int group, int tile,
-                                                         const int32_t* __restrict__ off1, int ntiles1, int nseg,
+// Level 1: S = 1024 * E sampled keys; every (S / nb)th in order is a splitter. A workgroup counts how many of the
+// samples come before each of kRankSamples of them (4096 samples: 17 us, 35 sorted by one workgroup; 1024 samples 4 and 6).
+constexpr int kRankSamples = 16, kRankBlock = 512;
+template <int E>
+__global__ __launch_bounds__(kRankBlock) void rank_splitters_kernel(const RcSource src, const KeyForm f, int n, int nb,
+                                                                uint64_t* __restrict__ skey, int32_t* __restrict__ spos) {
+  constexpr int S = 1024 * E, kLanes = kRankBlock / kRankSamples, kOwn = S / kRankBlock;
+  __shared__ uint64_t s_key[S];
+  const int tid = threadIdx.x;
+  uint64_t own[kOwn];
+#pragma unroll
+  for (int e = 0; e < kOwn; ++e) own[e] = src.key(sample_pos<S>(e * kRankBlock + tid, n), f) >> f.kshift;
+#pragma unroll
+  for (int e = 0; e < kOwn; ++e) s_key[e * kRankBlock + tid] = own[e];
+  if (blockIdx.x == 0 && (tid == 0 || tid >= nb) && tid < kSegMax) {  // unused splitters lie beyond every key
+    skey[tid] = ~uint64_t{0};
+    spos[tid] = INT32_MAX;
+  }
+  __syncthreads();
+  const int t = blockIdx.x * kRankSamples + tid / kLanes;
+  const uint64_t key = s_key[t];
+  int rank = 0;
+#pragma unroll 8
+  for (int q = tid % kLanes; q < S; q += kLanes) rank += s_key[q] < key + (q < t ? 1 : 0) ? 1 : 0;
+#pragma unroll
+  for (int d = 1; d < kLanes; d <<= 1) rank += __shfl_xor(rank, d);
+  const int b = static_cast<int>((static_cast<int64_t>(rank) * nb + S - 1) / S);
+  if (tid % kLanes == 0 && b > 0 && b < nb && static_cast<int>(static_cast<int64_t>(b) * S / nb) == rank) {
+    skey[b] = key;
+    spos[b] = sample_pos<S>(t, n);
+  }
+}
+
+// Records before each bucket of level 1, in the first four waves of the workgroup. Every thread calls.
+__device__ __forceinline__ int bucket_start(int count, int* s_sum) {
+  const int w = wave_id(), lane = lane_id();
+  const int incl = wave_inclusive_sum(count);
+  if (w < 4 && lane == kWave - 1) s_sum[w] = incl;
+  __syncthreads();
+  int start = incl - count;
+  for (int u = 0; u < (w & 3); ++u) start += s_sum[u];
+  return start;
+}
+
+// Level 2: sorts S = 1024 * E sampled keys of segment blockIdx.x, a bucket of level 1 (of total1[] records each), and
+// takes every (S / nb)th as a splitter; nb follows from the segment's size. The workgroup also fills in its rows of the
+// segment tables.
+template <int E>
+__global__ __launch_bounds__(1024) void splitters_kernel(const KSource src, const KeyForm f, int nrows, int group, int tile,
+                                                         const int32_t* __restrict__ total1, int nseg,
                                                          const Tables T, const uint64_t* __restrict__ skey1,
                                                          uint64_t* __restrict__ skey,
                                                          int32_t* __restrict__ spos) {
@@ -246,42 +308,40 @@ __global__ __launch_bounds__(1024) void splitters_kernel(const SRC src, const Ke
   __shared__ uint64_t s_key[S];
   __shared__ __attribute__((aligned(16))) uint32_t words[S];
   __shared__ uint16_t ord[S];
-  __shared__ int s_sum[4];
+  __shared__ int s_sum[4], s_begin;
   const int tid = threadIdx.x;
   const int seg = blockIdx.x;
-  int begin = 0, m = n, nb = nb_fixed;
-  if (LEVEL2) {
-    if (tid < 4) s_sum[tid] = 0;
-    __syncthreads();
-    begin = off1[static_cast<int64_t>(seg) * ntiles1];
-    m = (seg + 1 < kRadix ? off1[static_cast<int64_t>(seg + 1) * ntiles1] : n) - begin;
-    nb = final_buckets(m, kDirTarget);
-    if (tid < seg) {  // what the segments before this one take of each table
-      const int b = off1[static_cast<int64_t>(tid) * ntiles1], e = off1[static_cast<int64_t>(tid + 1) * ntiles1];
-      const int nt = tiles_in(e - b, tile);
-      atomicAdd(&s_sum[0], nt);
-      atomicAdd(&s_sum[1], (nt + group - 1) / group);
-      atomicAdd(&s_sum[2], final_buckets(e - b, kDirTarget));
-    }
-    __syncthreads();
-    const int nt = tiles_in(m, tile), ng = (nt + group - 1) / group;
-    const int t0 = s_sum[0], g0 = s_sum[1], b0 = s_sum[2];
-    if (tid == 0) {
-      T.seg_start[seg] = begin;
-      T.seg_tile[seg] = t0;
-      T.seg_group[seg] = g0;
-      T.seg_bucket[seg] = b0;
-      if (seg == nseg - 1) {
-        T.seg_start[nseg] = begin + m;
-        T.seg_tile[nseg] = t0 + nt;
-        T.seg_group[nseg] = g0 + ng;
-        T.seg_bucket[nseg] = b0 + nb;
-      }
-    }
-    for (int q = tid; q < nt; q += 1024) T.tile_seg[t0 + q] = seg;
-    for (int q = tid; q < ng; q += 1024) T.group_seg[g0 + q] = seg;
-    for (int q = tid; q < nb; q += 1024) T.bucket_seg[b0 + q] = seg;
+  if (tid < 3) s_sum[tid] = 0;
+  if (tid == 0) s_begin = 0;
+  __syncthreads();
+  const int m = total1[seg], nb = final_buckets(m, kDirTarget);
+  if (tid < seg) {  // what the segments before this one take of each table
+    const int before = total1[tid];
+    const int nt = tiles_in(before, tile);
+    atomicAdd(&s_sum[0], nt);
+    atomicAdd(&s_sum[1], (nt + group - 1) / group);
+    atomicAdd(&s_sum[2], final_buckets(before, kDirTarget));
+    atomicAdd(&s_begin, before);
   }
+  __syncthreads();
+  const int begin = s_begin;
+  const int nt = tiles_in(m, tile), ng = (nt + group - 1) / group;
+  const int t0 = s_sum[0], g0 = s_sum[1], b0 = s_sum[2];
+  if (tid == 0) {
+    T.seg_start[seg] = begin;
+    T.seg_tile[seg] = t0;
+    T.seg_group[seg] = g0;
+    T.seg_bucket[seg] = b0;
+    if (seg == nseg - 1) {
+      T.seg_start[nseg] = begin + m;
+      T.seg_tile[nseg] = t0 + nt;
+      T.seg_group[nseg] = g0 + ng;
+      T.seg_bucket[nseg] = b0 + nb;
+    }
+  }
+  for (int q = tid; q < nt; q += 1024) T.tile_seg[t0 + q] = seg;
+  for (int q = tid; q < ng; q += 1024) T.group_seg[g0 + q] = seg;
+  for (int q = tid; q < nb; q += 1024) T.bucket_seg[b0 + q] = seg;
   if (m == 0) return;  // uniform; one empty bucket, no splitter
 #pragma unroll
   for (int e = 0; e < E; ++e) {
@@ -289,8 +349,8 @@ __global__ __launch_bounds__(1024) void splitters_kernel(const SRC src, const Ke
     s_key[t] = src.key(begin + sample_pos<S>(t, m), f) >> f.kshift;
   }
   __syncthreads();
-  const uint64_t lo = LEVEL2 && seg > 0 ? skey1[seg] : 0;
-  const uint64_t hi = LEVEL2 && seg + 1 < nseg ? skey1[seg + 1] : static_cast<uint64_t>(nrows) << (f.cb - f.kshift);
+  const uint64_t lo = seg > 0 ? skey1[seg] : 0;
+  const uint64_t hi = seg + 1 < nseg ? skey1[seg + 1] : static_cast<uint64_t>(nrows) << (f.cb - f.kshift);
   sort_records<1024, E>(words, ord, S, lo, coarse_shift(lo, hi), [&](int t) { return s_key[t]; });
   if (tid < kSegMax) {
     uint64_t key = ~uint64_t{0};  // unused splitters lie beyond every key
@@ -318,18 +378,13 @@ struct SplitterTable {
   uint32_t coarse[kSegMax];
   uint32_t tree[kSegMax];
 };
-__device__ __forceinline__ uint32_t coarse_key(uint64_t k, uint64_t base, int shift) {
-  const uint64_t r = k < base ? 0 : ((k - base) >> shift) + 1;  // monotone, whatever the range
-  return r > 0xFFFFFFFEu ? 0xFFFFFFFEu : static_cast<uint32_t>(r);
-}
-// Bucket of a record: the number of splitters at or before it.
-__device__ __forceinline__ int bucket_of(const SplitterTable& t, uint64_t k, int p, uint64_t base, int shift) {
-  const uint32_t c = coarse_key(k, base, shift);
-  int node = 1;
+// Bucket of a record: the number of splitters at or before it. c: its key's place in the segment's range, coarsely.
+__device__ __forceinline__ int bucket_of(const SplitterTable& t, uint64_t k, int p, uint32_t c) {
+  uint32_t at = 4;  // four times the node
 #pragma unroll
-  for (int level = 0; level < kRadixBits; ++level) node = 2 * node + (t.tree[node] <= c ? 1 : 0);
-  int d = node - kSegMax;
-  if (__any(t.coarse[d] == c && d > 0)) {
+  for (int level = 0; level < kRadixBits; ++level) at = 2 * at + (*reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(t.tree) + at) <= c ? 4 : 0);
+  int d = static_cast<int>(at / 4) - kSegMax;
+  if (__any(t.coarse[d] == c)) {
     d = 0;
 #pragma unroll
     for (int step = kSegMax / 2; step > 0; step >>= 1) {
@@ -346,14 +401,15 @@ __device__ __forceinline__ int bucket_of(const SplitterTable& t, uint64_t k, int
 // bucket as one byte in dig. A workgroup takes up to `group` consecutive tiles of one segment
 // and stores each bucket's counts of them side by side (digit-major for the scan).
 template <class SRC, bool LEVEL2, int TILE>
-__global__ __launch_bounds__(kBlock) void classify_kernel(const SRC src, const KeyForm f, int n, int group,
+__global__ __launch_bounds__(kBlock) void classify_kernel(const SRC src, const KeyForm f, int n, int nrows, int group,
                                                           int nseg, const Tables T,
+                                                          const uint64_t* __restrict__ skey1,
                                                           const uint64_t* __restrict__ skey,
                                                           const int32_t* __restrict__ spos,
                                                           uint8_t* __restrict__ dig, int32_t* __restrict__ hist) {
   __shared__ SplitterTable t;
   __shared__ int s_cnt[kGroup][kRadix];
-  const int tid = threadIdx.x, lane = lane_id();
+  const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
   int seg = 0, begin = 0, end = n, tile0, ntiles;
   int64_t base = 0;
   const int g = xcd_contiguous_block_id();
@@ -373,15 +429,12 @@ __global__ __launch_bounds__(kBlock) void classify_kernel(const SRC src, const K
   t.pos[tid] = spos[seg * kSegMax + tid];
   for (int q = tid; q < group * kRadix; q += kBlock) (&s_cnt[0][0])[q] = 0;
   __syncthreads();
-  // range of the splitters: key[1] .. the last that is not unused
-  const uint64_t kbase = t.key[1];
-  uint64_t klast = kbase;
-#pragma unroll
-  for (int step = kSegMax / 2, d = 0; step > 0; step >>= 1)
-    if (t.key[d + step] != ~uint64_t{0}) d += step, klast = t.key[d];
-  const uint64_t range = klast - kbase;
-  const int shift = range >> 31 ? 33 - __clzll(static_cast<long long>(range)) : 0;
-  t.coarse[tid] = tid == 0 ? 0 : t.key[tid] == ~uint64_t{0} ? ~0u : coarse_key(t.key[tid], kbase, shift);
+  // the segment's keys lie in [lo, hi]
+  const uint64_t lo = LEVEL2 && seg > 0 ? skey1[seg] : 0;
+  const uint64_t hi = LEVEL2 && seg + 1 < nseg ? skey1[seg + 1] : static_cast<uint64_t>(nrows) << (f.cb - f.kshift);
+  const int shift = max(0, 33 - __clzll(static_cast<long long>((hi - lo) | 1)));
+  const auto coarse_key = [&](uint64_t k) { return static_cast<uint32_t>((k - lo) >> shift); };
+  t.coarse[tid] = tid == 0 || t.key[tid] == ~uint64_t{0} ? ~0u : coarse_key(t.key[tid]);  // ~0: no record's
   __syncthreads();
   if (tid > 0) {  // node tid of the tree: which splitter
     const int level = 31 - __clz(tid);
@@ -389,31 +442,35 @@ __global__ __launch_bounds__(kBlock) void classify_kernel(const SRC src, const K
   }
   __syncthreads();
   const int nt = min(group, ntiles - tile0);
+  // a wave's 64 records from p on: the address is the same for all lanes but for the lane
+  const auto load = [&](int p) {
+    const int from = min(p, end - 1);  // (beyond the end: the last record, not used)
+    return src.from(from).key_near(min(lane, end - 1 - from), f) >> f.kshift;
+  };
+  const int first = begin + tile0 * TILE + w * kWave;
   constexpr int kAhead = TILE / kBlock < 8 ? TILE / kBlock : 8;  // keys in flight per thread, across tiles
   uint64_t ahead[kAhead];
 #pragma unroll
-  for (int k = 0; k < kAhead; ++k)
-    ahead[k] = src.key_stream(min(begin + tile0 * TILE + k * kBlock + tid, end - 1), f) >> f.kshift;
+  for (int k = 0; k < kAhead; ++k) ahead[k] = load(first + k * kBlock);
   for (int q = 0; q < nt; ++q) {
-    const int first = begin + (tile0 + q) * TILE;
     int* cnt = s_cnt[q];
 #pragma unroll
     for (int k = 0; k < (TILE / kBlock); ++k) {
-      const int p = first + k * kBlock + tid;
+      const int p = first + q * TILE + k * kBlock;  // uniform
       const uint64_t key = ahead[k % kAhead];
-      ahead[k % kAhead] = src.key_stream(min(p + kAhead * kBlock, end - 1), f) >> f.kshift;
-      const int d = bucket_of(t, key, p, kbase, shift);
-      if (p - lane + kWave <= end) {  // the whole wave
+      ahead[k % kAhead] = load(p + kAhead * kBlock);
+      const int d = bucket_of(t, key, p + lane, coarse_key(key));
+      if (p + kWave <= end) {  // the whole wave
         // ordered input: a wave's records share a bucket, and adds to one counter are serialised
         if (__all(d == __builtin_amdgcn_readfirstlane(d))) {
           if (lane == 0) atomicAdd(&cnt[d], kWave);
         } else {
           atomicAdd(&cnt[d], 1);
         }
-        dig[p] = static_cast<uint8_t>(d);
-      } else if (p < end) {
+        (dig + p)[lane] = static_cast<uint8_t>(d);
+      } else if (p + lane < end) {
         atomicAdd(&cnt[d], 1);
-        dig[p] = static_cast<uint8_t>(d);
+        dig[p + lane] = static_cast<uint8_t>(d);
       }
     }
   }
@@ -422,20 +479,73 @@ __global__ __launch_bounds__(kBlock) void classify_kernel(const SRC src, const K
   for (int q = 0; q < nt; ++q) out[q] = s_cnt[q][tid];
 }
 
+// The counts become offsets, in place. Level 1: a workgroup has the counts of one bucket, which become the records of the
+// bucket in the tiles before; total: of all tiles. Level 2: it has a segment's, which become positions in the array.
+// (A scan of all counts at once takes two launches and three passes over them: 60M records 2 x 18 us instead of 8 and 10, 3.2M 2 x 11.)
+constexpr int kOffBlock = 1024;
+template <bool LEVEL2>
+__global__ __launch_bounds__(kOffBlock) void offsets_kernel(int ntiles1, const Tables T, int32_t* __restrict__ hist,
+                                                            int32_t* __restrict__ total) {
+  typedef int32_t I4 __attribute__((ext_vector_type(4), aligned(4)));
+  __shared__ int s_sum[2][kOffBlock / kWave];
+  const int tid = threadIdx.x, g = blockIdx.x;
+  int run = 0;
+  int64_t len = ntiles1;
+  if (LEVEL2) {
+    len = static_cast<int64_t>(T.seg_tile[g + 1] - T.seg_tile[g]) * kRadix;
+    hist += static_cast<int64_t>(T.seg_tile[g]) * kRadix;
+    run = T.seg_start[g];
+  } else {
+    hist += static_cast<int64_t>(g) * ntiles1;
+  }
+  const auto load = [&](int64_t p) {
+    I4 v = {0, 0, 0, 0};
+    if (p + 4 <= len) v = *reinterpret_cast<const I4*>(hist + p);
+    else
+      for (int r = 0; r < 4; ++r)
+        if (p + r < len) v[r] = hist[p + r];
+    return v;
+  };
+  I4 next = load(4 * tid);
+  for (int64_t p0 = 0, turn = 0; p0 < len; p0 += 4 * kOffBlock, turn ^= 1) {
+    const int64_t p = p0 + 4 * tid;
+    const I4 v = next;
+    next = load(p + 4 * kOffBlock);
+    const int mine = v[0] + v[1] + v[2] + v[3], incl = wave_inclusive_sum(mine);
+    if (lane_id() == kWave - 1) s_sum[turn][wave_id()] = incl;
+    lds_barrier();
+    int all = 0, before = run + incl - mine;
+    for (int u = 0; u < kOffBlock / kWave; ++u) {
+      const int q = s_sum[turn][u];
+      if (u < wave_id()) before += q;
+      all += q;
+    }
+    const I4 o = {before, before + v[0], before + v[0] + v[1], before + v[0] + v[1] + v[2]};
+    if (p + 4 <= len) *reinterpret_cast<I4*>(hist + p) = o;
+    else
+      for (int r = 0; r < 4; ++r)
+        if (p + r < len) hist[p + r] = o[r];
+    run += all;
+  }
+  if (!LEVEL2 && tid == 0) total[g] = run;
+}
+
 // Stable scatter of one tile by the noted buckets; ranks as in the radix scatter: a ballot match
 // inside the wave plus per-wave counters, then the tile is put in bucket order in LDS so that
 // consecutive lanes store to consecutive addresses.
+// Level 1: `off` holds the records of a bucket in the tiles before, total1 those of the buckets.
 // SELF (few tiles): `off` holds the plain counts, and every workgroup adds up those before its own
 // tile itself; the first leaves the start of every bucket in `starts` (one more than buckets).
 template <typename VT, class SRC, bool LEVEL2, int TILE, bool SELF = false>
-__global__ __launch_bounds__(kPart) void partition_kernel(const SRC src, const VT* __restrict__ val_in,
+__global__ __launch_bounds__(part_threads(TILE)) void partition_kernel(const SRC src, const VT* __restrict__ val_in,
                                                            const KeyForm f, int n, int nseg, const Tables T,
                                                            const uint8_t* __restrict__ dig,
                                                            const int32_t* __restrict__ off,
                                                            uint64_t* __restrict__ key_out,
                                                            VT* __restrict__ val_out,
-                                                           int32_t* __restrict__ starts) {
-  constexpr int IPT = TILE / kPart;
+                                                           int32_t* __restrict__ starts,
+                                                           const int32_t* __restrict__ total1) {
+  constexpr int kPart = part_threads(TILE), kPartWaves = kPart / kWave, IPT = TILE / kPart;
   __shared__ int s_cnt[kPartWaves][kRadix];
   __shared__ int s_gdelta[kRadix];
   __shared__ int s_sum[4];
@@ -465,7 +575,7 @@ __global__ __launch_bounds__(kPart) void partition_kernel(const SRC src, const V
   __syncthreads();
   const int tile_n = min(TILE, end - begin);
   const int wave_base = begin + w * (kWave * IPT);
-  volatile int* cnt = s_cnt[w];
+  int* cnt = s_cnt[w];
 
   uint64_t key[IPT];
   VT val[IPT];
@@ -492,9 +602,9 @@ __global__ __launch_bounds__(kPart) void partition_kernel(const SRC src, const V
                                                  __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(same), 0));
     int basecnt = 0;
     if (valid) basecnt = cnt[d];
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_order();
     if (valid && before == 0) cnt[d] = basecnt + __popcll(same);
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_order();
     lpos[k] = (d << 16) | (basecnt + before);
   }
   __syncthreads();
@@ -512,6 +622,11 @@ __global__ __launch_bounds__(kPart) void partition_kernel(const SRC src, const V
     for (int u = 0; u < (w & 3); ++u) start += s_sum[u];
     start -= tot;
     int global = 0;
+    if (!SELF) global = off[base + static_cast<int64_t>(d) * ntiles + i0];
+    if (!SELF && !LEVEL2) {
+      __syncthreads();
+      global += bucket_start(total1[d], s_sum);
+    }
     if (SELF) {
       int total = 0;  // of this digit over all tiles; `global`: over the tiles before this one
       typedef int32_t I4 __attribute__((ext_vector_type(4), aligned(4)));
@@ -542,7 +657,7 @@ __global__ __launch_bounds__(kPart) void partition_kernel(const SRC src, const V
       }
     }
     if (tid < kRadix) {
-      s_gdelta[d] = (SELF ? global : off[base + static_cast<int64_t>(d) * ntiles + i0]) - start;
+      s_gdelta[d] = global - start;
 #pragma unroll
       for (int u = 0; u < kPartWaves; ++u) {
         s_cnt[u][d] = start;
@@ -727,10 +842,51 @@ __device__ __forceinline__ void split_and_store(char* mem, const KSource& src, i
   }
 }
 
+// Up to kFin * E records, whose keys and values pass through LDS.
+template <typename VT, int E>
+__device__ __forceinline__ void finish_staged(char* mem, const KSource& src, int first, int n, uint64_t lo, int shift,
+                                              int lo_row, int hi_row, const KeyForm& f, const VT* __restrict__ val_in,
+                                              int32_t* __restrict__ pos, int32_t* __restrict__ crd_out,
+                                              VT* __restrict__ val_out) {
+  static_assert(kFin * E <= kStaged, "");
+  uint64_t* s_key = reinterpret_cast<uint64_t*>(mem);
+  VT* s_val = reinterpret_cast<VT*>(mem);
+  uint32_t* words = reinterpret_cast<uint32_t*>(mem + kStaged * 8);
+  uint16_t* ord = reinterpret_cast<uint16_t*>(mem + kStaged * 12);
+  const int tid = threadIdx.x;
+  const uint64_t* key_in = src.k + first;
+  val_in += first;
+  val_out += first;
+  uint64_t k[E];
+  VT v[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int p = min(e * kFin + tid, n - 1);
+    k[e] = at32(key_in, p);
+    v[e] = at32(val_in, p);
+  }
+#pragma unroll
+  for (int e = 0; e < E; ++e) s_key[e * kFin + tid] = k[e];
+  __syncthreads();
+  const auto key_at = [s_key](int li) { return s_key[li]; };
+  const auto cmp_at = [&](int li) { return s_key[li] >> f.kshift; };
+  sort_records<kFin, E>(words, ord, n, lo, shift, cmp_at);
+  store_entries<kFin, E>(ord, n, first, lo_row, hi_row, f, key_at, pos, crd_out, [](int, int) {});
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < E; ++e) s_val[e * kFin + tid] = v[e];
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int j = e * kFin + tid;
+    if (j < n) at32(val_out, j) = s_val[ord[j]];
+  }
+}
+
 // One workgroup per bucket of the last partition. LEVELS == 1: of the only one, whose scanned
 // counts are off2 and whose splitters are skey2, with nseg buckets.
 template <typename VT, int LEVELS>
-__global__ __launch_bounds__(kFin) void finish_kernel(const KSource src, const VT* __restrict__ val_in,
+__global__ __launch_bounds__(kFin, 5) void finish_kernel(const KSource src, const VT* __restrict__ val_in,
                                                       const KeyForm f, int nseg, int nrows, const Tables T,
                                                       const int32_t* __restrict__ off2,
                                                       const uint64_t* __restrict__ skey1,
@@ -776,38 +932,14 @@ __global__ __launch_bounds__(kFin) void finish_kernel(const KSource src, const V
     return;
   }
   const int shift = coarse_shift(lo, hi);
-  const int tid = threadIdx.x;
   if (n <= kStaged) {
-    uint64_t* s_key = reinterpret_cast<uint64_t*>(s_mem);
-    VT* s_val = reinterpret_cast<VT*>(s_mem);
-    uint32_t* words = reinterpret_cast<uint32_t*>(s_mem + kStaged * 8);
-    uint16_t* ord = reinterpret_cast<uint16_t*>(s_mem + kStaged * 12);
-    constexpr int E = kStaged / kFin;
-    uint64_t k[E];
-    VT v[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int p = min(first + e * kFin + tid, end - 1);
-      k[e] = src.k[p];
-      v[e] = val_in[p];
-    }
-#pragma unroll
-    for (int e = 0; e < E; ++e) s_key[e * kFin + tid] = k[e];
-    __syncthreads();
-    const auto key_at = [s_key](int li) { return s_key[li]; };
-    const auto cmp_at = [&](int li) { return s_key[li] >> f.kshift; };
-    if (n <= kStaged / 2) sort_records<kFin, E / 2>(words, ord, n, lo, shift, cmp_at);
-    else sort_records<kFin, E>(words, ord, n, lo, shift, cmp_at);
-    store_entries<kFin, E>(ord, n, first, lo_row, hi_row, f, key_at, pos, crd_out, [](int, int) {});
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < E; ++e) s_val[e * kFin + tid] = v[e];
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int j = e * kFin + tid;
-      if (j < n) val_out[first + j] = s_val[ord[j]];
-    }
+    // as many words of a thread as the records need (six for most; with eight for all of them: 30 us longer for 60M)
+#define SPT_STAGED(E_) \
+  finish_staged<VT, E_>(s_mem, src, first, n, lo, shift, lo_row, hi_row, f, val_in, pos, crd_out, val_out)
+    if (n <= 4 * kFin) SPT_STAGED(4);
+    else if (n <= 6 * kFin) SPT_STAGED(6);
+    else SPT_STAGED(8);
+#undef SPT_STAGED
   } else {
     uint32_t* words = reinterpret_cast<uint32_t*>(s_mem);
     uint16_t* ord = reinterpret_cast<uint16_t*>(s_mem + kCap * 4);
@@ -941,6 +1073,9 @@ static int tile_of(int64_t n) {
   if (n <= kOneLevelMax) return n <= 128 * kSmallTile ? kSmallTile : 2 * kSmallTile;
   return n <= kSmallTileMax ? kSmallTile : kTile;
 }
+// LDS that the scatter of a large tile asks for beyond what it uses (46 KB), so that two of its workgroups share a compute
+// unit, not three (see above).
+constexpr size_t kPartPad = 10 * 1024;
 static int64_t tiles_bound(int64_t n) { return (n + tile_of(n) - 1) / tile_of(n) + kSegMax; }
 
 size_t sample_sort_workspace(int dtype, int64_t n) {
@@ -949,7 +1084,7 @@ size_t sample_sort_workspace(int dtype, int64_t n) {
   const int levels = n > kOneLevelMax ? 2 : 1;
   const size_t hist = align_up(static_cast<size_t>(tiles_bound(n)) * kRadix * 4, 256);
   size_t b = levels * (align_up(n * 8, 256) + align_up(n * vsz, 256)) + align_up(n, 256);
-  b += levels * hist + scan_workspace(tiles_bound(n) * kRadix);
+  b += levels * hist;
   b += align_up(kSegMax * 8, 256) + align_up(kSegMax * 4, 256);
   b += 5 * align_up((kSegMax + 1) * 4, 256);
   if (levels == 2) {
@@ -957,21 +1092,6 @@ size_t sample_sort_workspace(int dtype, int64_t n) {
     b += 2 * align_up(tiles_bound(n) * 4, 256) + align_up((n / kDirTarget + kSegMax + 1) * 4, 256);
   }
   return b + 256;
-}
-
-template <class SRC, bool LEVEL2>
-static spt_status launch_splitters(int samples, int nseg, const SRC src, const KeyForm f, int n, int nrows, int nb, int group, int tile,
-                                   const int32_t* off1, int ntiles1, const Tables& T, const uint64_t* skey1, uint64_t* skey, int32_t* spos,
-                                   hipStream_t s) {
-#define SPT_SPLIT(E_)                                                                                         \
-  hipLaunchKernelGGL((splitters_kernel<E_, SRC, LEVEL2>), dim3(nseg), dim3(1024), 0, s, src, f, n, nrows, nb, \
-                     group, tile, off1, ntiles1, nseg, T, skey1, skey, spos)
-  if (samples <= 1024) SPT_SPLIT(1);
-  else if (samples <= 2048) SPT_SPLIT(2);
-  else SPT_SPLIT(4);
-#undef SPT_SPLIT
-  SPT_CHECK_LAUNCH("splitters");
-  return SPT_OK;
 }
 
 template <typename VT>
@@ -1000,7 +1120,6 @@ spt_status sample_sort_convert(int64_t n64, int64_t nrows, int64_t ncols, bool b
   VT* v1 = W.take<VT>(n);
   uint8_t* dig = W.take<uint8_t>(n);
   int32_t* hist1 = W.take<int32_t>(tiles_bound(n) * kRadix);
-  int32_t* scan_tmp = reinterpret_cast<int32_t*>(W.take<char>(scan_workspace(tiles_bound(n) * kRadix)));
   uint64_t* skey1 = W.take<uint64_t>(kSegMax);
   int32_t* spos1 = W.take<int32_t>(kSegMax);
   Tables T{};
@@ -1010,13 +1129,19 @@ spt_status sample_sort_convert(int64_t n64, int64_t nrows, int64_t ncols, bool b
   // one level: final buckets; two: up to 256 buckets of sixteen final ones or more
   const int per = two ? 16 * kDirTarget : kDirTarget;
   const int nb1 = std::min(kSegMax, (n + per - 1) / per);
-  spt_status st = launch_splitters<RcSource, false>((two ? 16 : 14) * nb1, 1, rc, f, n, static_cast<int>(nrows), nb1,
-                                                    1, tile, nullptr, 0, T, nullptr, skey1, spos1, s);
-  if (st != SPT_OK) return st;
+  const int samples = (two ? 16 : 14) * nb1;
+#define SPT_RANK(E_)                                                                                                    \
+  hipLaunchKernelGGL((rank_splitters_kernel<E_>), dim3(1024 * E_ / kRankSamples), dim3(kRankBlock), 0, s, rc, f, n, nb1, \
+                     skey1, spos1)
+  if (samples <= 1024) SPT_RANK(1);
+  else if (samples <= 2048) SPT_RANK(2);
+  else SPT_RANK(4);
+#undef SPT_RANK
+  SPT_CHECK_LAUNCH("splitters");
   const int group = nt1 >= 2048 && tile == kTile ? kGroup : 1;  // few tiles: a workgroup for each
 #define SPT_CLASSIFY(TILE_)                                                                                          \
   hipLaunchKernelGGL((classify_kernel<RcSource, false, TILE_>), dim3((nt1 + group - 1) / group), dim3(kBlock), 0, s, \
-                     rc, f, n, group, 1, T, skey1, spos1, dig, hist1)
+                     rc, f, n, static_cast<int>(nrows), group, 1, T, nullptr, skey1, spos1, dig, hist1)
   if (tile == kSmallTile) SPT_CLASSIFY(kSmallTile);
   else if (tile == 2 * kSmallTile) SPT_CLASSIFY(2 * kSmallTile);
   else SPT_CLASSIFY(kTile);
@@ -1026,31 +1151,33 @@ spt_status sample_sort_convert(int64_t n64, int64_t nrows, int64_t ncols, bool b
   if (!two) {
     int32_t* starts = W.take<int32_t>(kSegMax + 1);
     if (tile == kSmallTile)
-      hipLaunchKernelGGL((partition_kernel<VT, RcSource, false, kSmallTile, true>), dim3(nt1), dim3(kPart), 0, s, rc,
-                         vals, f, n, 1, T, dig, hist1, k1, v1, starts);
+      hipLaunchKernelGGL((partition_kernel<VT, RcSource, false, kSmallTile, true>), dim3(nt1), dim3(part_threads(kSmallTile)), 0, s, rc,
+                         vals, f, n, 1, T, dig, hist1, k1, v1, starts, nullptr);
     else
-      hipLaunchKernelGGL((partition_kernel<VT, RcSource, false, 2 * kSmallTile, true>), dim3(nt1), dim3(kPart), 0, s, rc,
-                         vals, f, n, 1, T, dig, hist1, k1, v1, starts);
+      hipLaunchKernelGGL((partition_kernel<VT, RcSource, false, 2 * kSmallTile, true>), dim3(nt1), dim3(part_threads(kSmallTile)), 0, s, rc,
+                         vals, f, n, 1, T, dig, hist1, k1, v1, starts, nullptr);
     SPT_CHECK_LAUNCH("partition");
     hipLaunchKernelGGL((finish_kernel<VT, 1>), dim3(nb1), dim3(kFin), 0, s, s1, v1, f, nb1, static_cast<int>(nrows), T,
                        starts, nullptr, skey1, pos_out, crd_out, vals_out);
     SPT_CHECK_LAUNCH("finish");
     return SPT_OK;
   }
-  st = device_scan_i32<false>(hist1, hist1, static_cast<int64_t>(nt1) * kRadix, scan_tmp, s);
-  if (st != SPT_OK) return st;
+  // level 2's counts are made later: until then their place holds the sizes of level 1's buckets
+  int32_t* hist2 = W.take<int32_t>(tiles_bound(n) * kRadix);
+  int32_t* total1 = hist2;
+  hipLaunchKernelGGL(offsets_kernel<false>, dim3(kRadix), dim3(kOffBlock), 0, s, nt1, T, hist1, total1);
+  SPT_CHECK_LAUNCH("offsets");
   if (tile == kSmallTile)
-    hipLaunchKernelGGL((partition_kernel<VT, RcSource, false, kSmallTile>), dim3(nt1), dim3(kPart), 0, s, rc, vals, f, n,
-                       1, T, dig, hist1, k1, v1, nullptr);
+    hipLaunchKernelGGL((partition_kernel<VT, RcSource, false, kSmallTile>), dim3(nt1), dim3(part_threads(kSmallTile)), 0, s, rc, vals, f, n,
+                       1, T, dig, hist1, k1, v1, nullptr, total1);
   else
-    hipLaunchKernelGGL((partition_kernel<VT, RcSource, false, kTile>), dim3(nt1), dim3(kPart), 0, s, rc, vals, f, n, 1, T,
-                       dig, hist1, k1, v1, nullptr);
+    hipLaunchKernelGGL((partition_kernel<VT, RcSource, false, kTile>), dim3(nt1), dim3(part_threads(kTile)), kPartPad, s, rc, vals, f, n, 1, T,
+                       dig, hist1, k1, v1, nullptr, total1);
   SPT_CHECK_LAUNCH("partition");
 
   // level 2
   uint64_t* k2 = W.take<uint64_t>(n);
   VT* v2 = W.take<VT>(n);
-  int32_t* hist2 = W.take<int32_t>(tiles_bound(n) * kRadix);
   uint64_t* skey2 = W.take<uint64_t>(kSegMax * kSegMax);
   int32_t* spos2 = W.take<int32_t>(kSegMax * kSegMax);
   T.seg_start = W.take<int32_t>(kSegMax + 1);
@@ -1060,25 +1187,31 @@ spt_status sample_sort_convert(int64_t n64, int64_t nrows, int64_t ncols, bool b
   T.group_seg = W.take<int32_t>(tiles_bound(n));
   T.tile_seg = W.take<int32_t>(tiles_bound(n));
   T.bucket_seg = W.take<int32_t>(n / kDirTarget + kSegMax + 1);
-  st = launch_splitters<KSource, true>(32 * static_cast<int>(std::min<int64_t>(kSegMax, n64 / nb1 * 3 / 2 / kDirTarget + 1)),
-                                       nb1, s1, f, n, static_cast<int>(nrows), 0, group, tile, hist1, nt1, T, skey1, skey2, spos2, s);
-  if (st != SPT_OK) return st;
+  const int samples2 = 32 * static_cast<int>(std::min<int64_t>(kSegMax, n64 / nb1 * 3 / 2 / kDirTarget + 1));
+#define SPT_SPLIT(E_)                                                                                                  \
+  hipLaunchKernelGGL((splitters_kernel<E_>), dim3(nb1), dim3(1024), 0, s, s1, f, static_cast<int>(nrows), group, tile, \
+                     total1, nb1, T, skey1, skey2, spos2)
+  if (samples2 <= 1024) SPT_SPLIT(1);
+  else if (samples2 <= 2048) SPT_SPLIT(2);
+  else SPT_SPLIT(4);
+#undef SPT_SPLIT
+  SPT_CHECK_LAUNCH("splitters 2");
   const unsigned tiles2 = static_cast<unsigned>(tiles_bound(n));
   if (tile == kSmallTile)
     hipLaunchKernelGGL((classify_kernel<KSource, true, kSmallTile>), dim3(tiles2 / group + kSegMax), dim3(kBlock), 0, s, s1,
-                       f, n, group, nb1, T, skey2, spos2, dig, hist2);
+                       f, n, static_cast<int>(nrows), group, nb1, T, skey1, skey2, spos2, dig, hist2);
   else
     hipLaunchKernelGGL((classify_kernel<KSource, true, kTile>), dim3(tiles2 / group + kSegMax), dim3(kBlock), 0, s, s1, f,
-                       n, group, nb1, T, skey2, spos2, dig, hist2);
+                       n, static_cast<int>(nrows), group, nb1, T, skey1, skey2, spos2, dig, hist2);
   SPT_CHECK_LAUNCH("classify 2");
-  st = device_scan_i32<false>(hist2, hist2, static_cast<int64_t>(tiles2) * kRadix, scan_tmp, s);
-  if (st != SPT_OK) return st;
+  hipLaunchKernelGGL(offsets_kernel<true>, dim3(nb1), dim3(kOffBlock), 0, s, 0, T, hist2, nullptr);
+  SPT_CHECK_LAUNCH("offsets 2");
   if (tile == kSmallTile)
-    hipLaunchKernelGGL((partition_kernel<VT, KSource, true, kSmallTile>), dim3(tiles2), dim3(kPart), 0, s, s1, v1, f, n,
-                       nb1, T, dig, hist2, k2, v2, nullptr);
+    hipLaunchKernelGGL((partition_kernel<VT, KSource, true, kSmallTile>), dim3(tiles2), dim3(part_threads(kSmallTile)), 0, s, s1, v1, f, n,
+                       nb1, T, dig, hist2, k2, v2, nullptr, nullptr);
   else
-    hipLaunchKernelGGL((partition_kernel<VT, KSource, true, kTile>), dim3(tiles2), dim3(kPart), 0, s, s1, v1, f, n, nb1, T,
-                       dig, hist2, k2, v2, nullptr);
+    hipLaunchKernelGGL((partition_kernel<VT, KSource, true, kTile>), dim3(tiles2), dim3(part_threads(kTile)), kPartPad, s, s1, v1, f, n, nb1, T,
+                       dig, hist2, k2, v2, nullptr, nullptr);
   SPT_CHECK_LAUNCH("partition 2");
   hipLaunchKernelGGL((finish_kernel<VT, 2>), dim3(static_cast<unsigned>(n64 / kDirTarget + nb1)), dim3(kFin), 0, s,
                      KSource{k2}, v2, f, nb1, static_cast<int>(nrows), T, hist2, skey1, skey2, pos_out, crd_out,

@@ -449,6 +449,7 @@ __global__ __launch_bounds__(kBig) void ttv_csf_wave_kernel(
   const int stride = gridDim.x * kBigWaves;
   for (int piece0 = __builtin_amdgcn_readfirstlane(blockIdx.x * kBigWaves + wave_id()); piece0 < npieces;
        piece0 += kNP * stride) {
+    wave_lds_order();  // the marks are cleared
     int32_t k[kNP][kEPL], f_lo[kNP], f_hi[kNP];
     T v[kNP][kEPL];
 #pragma unroll
@@ -474,7 +475,7 @@ __global__ __launch_bounds__(kBig) void ttv_csf_wave_kernel(
     for (int u = 0; u < kNP; ++u) {
       const int piece = piece0 + u * stride;
       if (piece >= npieces) break;
-      volatile int32_t* mark = s_mark[wave_id()][u];
+      int32_t* mark = s_mark[wave_id()][u];
       const int base = piece * kPiece;
       for (int f = f_lo[u] + lane; f < f_hi[u]; f += kWave) {
         const int a = pos[f], b = pos[f + 1];
@@ -486,11 +487,11 @@ __global__ __launch_bounds__(kBig) void ttv_csf_wave_kernel(
     for (int u = 0; u < kNP; ++u) {
       const int piece = piece0 + u * stride;
       if (piece >= npieces) break;
-      volatile int32_t* mark = s_mark[wave_id()][u];
+      int32_t* mark = s_mark[wave_id()][u];
       T g[kEPL];
       gather_lane<T, ALL>(s_c, c, cached, k[u], g);
       if ((piece + 1) * kPiece > nnz) drop_beyond(piece * kPiece + lane * kEPL, nnz, g);  // uniform
-      __builtin_amdgcn_wave_barrier();
+      wave_lds_order();
       int key[kEPL];
       unsigned headmask = 0;
       T p[kEPL];
@@ -500,7 +501,7 @@ __global__ __launch_bounds__(kBig) void ttv_csf_wave_kernel(
         if (key[r] >= 0) headmask |= 1u << r;
         p[r] = v[u][r] * g[r];
       }
-      __builtin_amdgcn_wave_barrier();
+      wave_lds_order();
 #pragma unroll
       for (int r = 0; r < kEPL; ++r)
         if (key[r] >= 0) mark[lane * kEPL + r] = -1;

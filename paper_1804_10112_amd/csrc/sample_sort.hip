@@ -27,7 +27,7 @@
 //
 // Measured against the six radix passes it replaces (fp64): 60M records with power-law rows
 // 3.09 -> 1.67 ms (splitters 17 + 70 us, classify 2 x 135, offsets 8 + 10, partitions 403 + 430,
-// finish 476); 5M records 0.21 ms, 250 000 56 us, 50 000 171 -> 22 us. The partitions write 256 x 2 interleaved streams
+// finish 476); 5M records 0.21 ms, 250 000 54 us, 50 000 171 -> 20 us. The partitions write 256 x 2 interleaved streams
 // and are bound by how the memory system takes them: it is the bytes in flight that count. Two workgroups of 512 threads
 // on a compute unit: 60M records fp64 1.70 ms in all (before splitters and offsets were made as now), three 1.83, three
 // of 256 threads 1.87, two 1.68; 20M 0.62, 0.63, 0.64 and 0.65; fp32, 40M 1.01, 1.04, 1.03 and 1.06. Tiles of 6144 and
@@ -955,6 +955,9 @@ __global__ __launch_bounds__(kFin, 5) void finish_kernel(const KSource src, cons
 
 // Small inputs: one workgroup per kSelTarget records. It samples the input, keeps the two
 // splitters around its share, and picks its records out of the input.
+// Bound by latency: four round trips to memory and two networks (50 000 records: 20 us; 22 with the picked positions
+// put in order by a third, and keys and values fetched where they are used; all rows loaded ahead of the sample's sort
+// 22, rows between the splitters picked without a look at their keys 20.5).
 template <int E, typename VT>
 __global__ __launch_bounds__(kSel) void select_finish_kernel(const RcSource src, const VT* __restrict__ val_in,
                                                              const KeyForm f, int n, int nrows,
@@ -966,7 +969,8 @@ __global__ __launch_bounds__(kSel) void select_finish_kernel(const RcSource src,
   __shared__ __attribute__((aligned(16))) uint32_t words[kCap];
   __shared__ __attribute__((aligned(16))) int32_t s_at[kCap];  // positions of the bucket's records
   __shared__ uint16_t s_ord[kCap];
-  __shared__ int s_cnt, s_less;
+  __shared__ uint32_t s_picked[kSelectMax / 32];  // bit per record
+  __shared__ int s_sum[kSel / kWave], s_less;
   const int tid = threadIdx.x, lane = lane_id();
   const int w = __builtin_amdgcn_readfirstlane(wave_id());
   const int d = blockIdx.x, nb = gridDim.x;
@@ -997,9 +1001,12 @@ __global__ __launch_bounds__(kSel) void select_finish_kernel(const RcSource src,
   const auto in = [&](uint64_t key, int p) {
     return (!cut_below || lo.at_or_before(key, p)) && (!cut_above || !hi.at_or_before(key, p));
   };
-  // ---- pick: the positions of the bucket's records, in any order, and how many records precede it.
+  // ---- pick: the positions of the bucket's records, and how many records precede it.
   // What decides is the row, except for the rows that the splitters cut; few records qualify.
-  if (tid == 0) s_cnt = s_less = 0;
+  constexpr int kWords = kSelectMax / 32 / kSel;  // of a thread
+#pragma unroll
+  for (int q = 0; q < kWords; ++q) s_picked[q * kSel + tid] = 0;
+  if (tid == 0) s_less = 0;
   __syncthreads();
   const int cut_lo = cut_below ? lo_row : -1, cut_hi = cut_above ? hi_row : INT32_MAX;
   int less = 0;
@@ -1023,8 +1030,7 @@ __global__ __launch_bounds__(kSel) void select_finish_kernel(const RcSource src,
       if (cut_below && !lo.at_or_before(key, p)) {
         ++less;
       } else if (!cut_above || !hi.at_or_before(key, p)) {
-        const int i = atomicAdd(&s_cnt, 1);
-        if (i < kCap) s_at[i] = p;
+        atomicOr(&s_picked[p >> 5], 1u << (p & 31));
       }
     }
   }
@@ -1032,7 +1038,28 @@ __global__ __launch_bounds__(kSel) void select_finish_kernel(const RcSource src,
   for (int s = kWave / 2; s > 0; s >>= 1) less += __shfl_xor(less, s);
   if (lane == 0) atomicAdd(&s_less, less);
   __syncthreads();
-  const int cnt = s_cnt, first = s_less;
+  // the positions in order, so that records are numbered in input order (sorting them takes another network)
+  uint32_t picked[kWords];
+  int own = 0;
+#pragma unroll
+  for (int q = 0; q < kWords; ++q) {
+    picked[q] = s_picked[tid * kWords + q];
+    own += __popc(picked[q]);
+  }
+  int at = wave_inclusive_sum(own) - own, cnt = 0;
+  if (lane == kWave - 1) s_sum[w] = at + own;
+  __syncthreads();
+  for (int u = 0; u < kSel / kWave; ++u) {
+    if (u < w) at += s_sum[u];
+    cnt += s_sum[u];
+  }
+#pragma unroll
+  for (int q = 0; q < kWords; ++q) {
+    for (uint32_t m = picked[q]; m; m &= m - 1, ++at)
+      if (at < kCap) s_at[at] = (tid * kWords + q) * 32 + __ffs(static_cast<int>(m)) - 1;
+  }
+  __syncthreads();
+  const int first = s_less;
   if (cnt > kCap) {
     rank_and_store<kSel, VT>(src, 0, n, in, cnt, first, lo_row, hi_row, f, val_in, pos, crd_out, val_out);
     return;
@@ -1045,13 +1072,22 @@ __global__ __launch_bounds__(kSel) void select_finish_kernel(const RcSource src,
   const auto key_at = [&](int li) { return src.key(s_at[li], f); };
   const auto cmp_at = [&](int li) { return src.key(s_at[li], f) >> f.kshift; };
   const auto put = [&](int j, int li) { val_out[first + j] = val_in[s_at[li]]; };
-  // the positions first: records are numbered in input order
 #define SPT_FINISH(E_)                                                                                     \
-  sort_positions<kSel, E_>(reinterpret_cast<uint32_t*>(s_at), cnt);                                        \
   sort_records<kSel, E_>(words, s_ord, cnt, lo.key, shift, cmp_at);                                      \
   store_entries<kSel, E_>(s_ord, cnt, first, lo_row, hi_row, f, key_at, pos, crd_out, put)
   if (cnt <= kSel) {
-    SPT_FINISH(1);
+    // a record of each thread: keys and values are fetched together, once
+    VT* s_val = reinterpret_cast<VT*>(words);
+    static_assert(kSel * sizeof(VT) <= sizeof(words), "");
+    const int p = s_at[min(tid, cnt - 1)];
+    const VT v = val_in[p];
+    s_key[tid] = src.key(p, f);
+    __syncthreads();
+    sort_records<kSel, 1>(words, s_ord, cnt, lo.key, shift, [&](int li) { return s_key[li] >> f.kshift; });
+    s_val[tid] = v;
+    __syncthreads();
+    store_entries<kSel, 1>(s_ord, cnt, first, lo_row, hi_row, f, [&](int li) { return s_key[li]; }, pos, crd_out,
+                           [&](int j, int li) { val_out[first + j] = s_val[li]; });
   } else if (cnt <= 2 * kSel) {
     SPT_FINISH(2);
   } else {

@@ -39,6 +39,7 @@
 #include "common.hpp"
 #include "radix.hpp"
 #include "rows.hpp"
+#include "scan.hpp"
 #include "wavescan.hpp"
 
 namespace spt {
@@ -486,9 +487,7 @@ constexpr int kOffBlock = 1024;
 template <bool LEVEL2>
 __global__ __launch_bounds__(kOffBlock) void offsets_kernel(int ntiles1, const Tables T, int32_t* __restrict__ hist,
                                                             int32_t* __restrict__ total) {
-  typedef int32_t I4 __attribute__((ext_vector_type(4), aligned(4)));
-  __shared__ int s_sum[2][kOffBlock / kWave];
-  const int tid = threadIdx.x, g = blockIdx.x;
+  const int g = blockIdx.x;
   int run = 0;
   int64_t len = ntiles1;
   if (LEVEL2) {
@@ -498,36 +497,8 @@ __global__ __launch_bounds__(kOffBlock) void offsets_kernel(int ntiles1, const T
   } else {
     hist += static_cast<int64_t>(g) * ntiles1;
   }
-  const auto load = [&](int64_t p) {
-    I4 v = {0, 0, 0, 0};
-    if (p + 4 <= len) v = *reinterpret_cast<const I4*>(hist + p);
-    else
-      for (int r = 0; r < 4; ++r)
-        if (p + r < len) v[r] = hist[p + r];
-    return v;
-  };
-  I4 next = load(4 * tid);
-  for (int64_t p0 = 0, turn = 0; p0 < len; p0 += 4 * kOffBlock, turn ^= 1) {
-    const int64_t p = p0 + 4 * tid;
-    const I4 v = next;
-    next = load(p + 4 * kOffBlock);
-    const int mine = v[0] + v[1] + v[2] + v[3], incl = wave_inclusive_sum(mine);
-    if (lane_id() == kWave - 1) s_sum[turn][wave_id()] = incl;
-    lds_barrier();
-    int all = 0, before = run + incl - mine;
-    for (int u = 0; u < kOffBlock / kWave; ++u) {
-      const int q = s_sum[turn][u];
-      if (u < wave_id()) before += q;
-      all += q;
-    }
-    const I4 o = {before, before + v[0], before + v[0] + v[1], before + v[0] + v[1] + v[2]};
-    if (p + 4 <= len) *reinterpret_cast<I4*>(hist + p) = o;
-    else
-      for (int r = 0; r < 4; ++r)
-        if (p + r < len) hist[p + r] = o[r];
-    run += all;
-  }
-  if (!LEVEL2 && tid == 0) total[g] = run;
+  run = block_exclusive_scan<kOffBlock>(hist, len, run);
+  if (!LEVEL2 && threadIdx.x == 0) total[g] = run;
 }
 
 // Stable scatter of one tile by the noted buckets; ranks as in the radix scatter: a ballot match

@@ -4,6 +4,7 @@
 // per-parent counts) and of the digit offsets of every radix-sort pass.
 #pragma once
 #include "common.hpp"
+#include "wavescan.hpp"
 
 namespace spt {
 
@@ -38,6 +39,43 @@ __device__ __forceinline__ int block_inclusive_sum(int v, int* total) {
   }
   *total = tot;
   return v + pre;
+}
+
+// One workgroup of NT threads: exclusive scan of p[0 .. len) in place, from `run` on; returns the end of it.
+template <int NT>
+__device__ __forceinline__ int block_exclusive_scan(int32_t* __restrict__ p, int64_t len, int run) {
+  typedef int32_t I4 __attribute__((ext_vector_type(4), aligned(4)));
+  __shared__ int s_sum[2][NT / kWave];
+  const auto load = [&](int64_t at) {
+    I4 v = {0, 0, 0, 0};
+    if (at + 4 <= len) v = *reinterpret_cast<const I4*>(p + at);
+    else
+      for (int r = 0; r < 4; ++r)
+        if (at + r < len) v[r] = p[at + r];
+    return v;
+  };
+  I4 next = load(4 * static_cast<int>(threadIdx.x));
+  for (int64_t at0 = 0, turn = 0; at0 < len; at0 += 4 * NT, turn ^= 1) {
+    const int64_t at = at0 + 4 * threadIdx.x;
+    const I4 v = next;
+    next = load(at + 4 * NT);
+    const int mine = v[0] + v[1] + v[2] + v[3], incl = wave_inclusive_sum(mine);
+    if (lane_id() == kWave - 1) s_sum[turn][wave_id()] = incl;
+    lds_barrier();
+    int all = 0, before = run + incl - mine;
+    for (int u = 0; u < NT / kWave; ++u) {
+      const int q = s_sum[turn][u];
+      if (u < wave_id()) before += q;
+      all += q;
+    }
+    const I4 o = {before, before + v[0], before + v[0] + v[1], before + v[0] + v[1] + v[2]};
+    if (at + 4 <= len) *reinterpret_cast<I4*>(p + at) = o;
+    else
+      for (int r = 0; r < 4; ++r)
+        if (at + r < len) p[at + r] = o[r];
+    run += all;
+  }
+  return run;
 }
 
 static __global__ __launch_bounds__(kBlock) void scan_tile_sums_kernel(const int32_t* __restrict__ in,

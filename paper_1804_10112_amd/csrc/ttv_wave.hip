@@ -179,61 +179,89 @@ __device__ __forceinline__ void wave_fibre_sums(const T (&p)[kEPL], unsigned hea
 }
 
 // ================================================================ COO
-// heads[piece] = number of (i, j) fibre starts among the piece's entries. Bound by reading i and j; i is
-// ordered, so where it is the same before and at the end of a piece it need not be read.
-template <bool VEC>
+// piece_off[piece] = (i, j) fibre starts in the pieces before among the workgroup's, group_off[workgroup] = in all of
+// them. Bound by reading i and j; i is ordered, so where it is the same before and at the end of a piece
+// it need not be read. A wave has the loads of four pieces in flight together.
+// SELF (few pieces): one piece for a wave, piece_off[piece] = the starts in it.
+constexpr int kGroupPieces = 16;
+template <bool VEC, bool SELF>
 __global__ __launch_bounds__(kBlock) void ttv_piece_heads_kernel(int nnz, int npieces,
                                                                  const int32_t* __restrict__ ci,
                                                                  const int32_t* __restrict__ cj,
-                                                                 int32_t* __restrict__ heads) {
-  const int piece = __builtin_amdgcn_readfirstlane(blockIdx.x * (kBlock / kWave) + wave_id());
-  if (piece >= npieces) return;
-  const int lane = lane_id();
-  const int p0 = piece * kPiece + lane * kEPL;
-  int32_t i[kEPL], j[kEPL];
-  if (VEC && (piece + 1) * kPiece <= nnz) {  // uniform
-    load_lane(cj + p0, j);
-    const int32_t slice = ci[max(piece * kPiece - 1, 0)];
-    if (slice == ci[piece * kPiece + kPiece - 1]) {
+                                                                 int32_t* __restrict__ piece_off,
+                                                                 int32_t* __restrict__ group_off) {
+  constexpr int kPieces = SELF ? kBlock / kWave : kGroupPieces, OWN = kPieces / (kBlock / kWave);
+  __shared__ int s_heads[kPieces];
+  const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  int32_t i[OWN][kEPL], j[OWN][kEPL], bi[OWN], bj[OWN], ei[OWN];
+  int base[OWN];
 #pragma unroll
-      for (int r = 0; r < kEPL; ++r) i[r] = slice;
+  for (int u = 0; u < OWN; ++u) {
+    base[u] = min(static_cast<int>(blockIdx.x) * kPieces + w * OWN + u, npieces - 1) * kPiece;
+    const int p0 = base[u] + lane * kEPL, before = max(base[u] - 1, 0);
+    if (VEC && base[u] + kPiece <= nnz) {  // uniform
+      load_lane(cj + p0, j[u]);
     } else {
-      load_lane(ci + p0, i);
+#pragma unroll
+      for (int r = 0; r < kEPL; ++r) j[u][r] = cj[min(p0 + r, nnz - 1)];  // beyond the end: the last entry again, never a head
     }
-  } else {
+    bi[u] = ci[before];
+    bj[u] = cj[before];
+    ei[u] = ci[min(base[u] + kPiece, nnz) - 1];
+  }
+#pragma unroll
+  for (int u = 0; u < OWN; ++u) {
+    const int p0 = base[u] + lane * kEPL;
+    if (bi[u] == ei[u]) {  // uniform
+#pragma unroll
+      for (int r = 0; r < kEPL; ++r) i[u][r] = bi[u];
+    } else if (VEC && base[u] + kPiece <= nnz) {
+      load_lane(ci + p0, i[u]);
+    } else {
+#pragma unroll
+      for (int r = 0; r < kEPL; ++r) i[u][r] = ci[min(p0 + r, nnz - 1)];
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < OWN; ++u) {
+    int32_t pi = dpp_move<0x138, 0xf>(bi[u], i[u][kEPL - 1]), pj = dpp_move<0x138, 0xf>(bj[u], j[u][kEPL - 1]);  // wave_shr:1
+    if (base[u] == 0 && lane == 0) pi = pj = -1;
+    int cnt = 0;
 #pragma unroll
     for (int r = 0; r < kEPL; ++r) {
-      const int p = min(p0 + r, nnz - 1);  // beyond the end: the last entry again, never a head
-      i[r] = ci[p];
-      j[r] = cj[p];
+      cnt += __popcll(__ballot(i[u][r] != pi || j[u][r] != pj));
+      pi = i[u][r];
+      pj = j[u][r];
     }
-  }
-  int32_t pi = __shfl_up(i[kEPL - 1], 1), pj = __shfl_up(j[kEPL - 1], 1);
-  if (lane == 0) {
-    pi = pj = -1;
-    if (p0 > 0) {
-      pi = ci[p0 - 1];
-      pj = cj[p0 - 1];
+    const int piece = blockIdx.x * kPieces + w * OWN + u;
+    if (SELF) {
+      if (lane == 0 && piece < npieces) piece_off[piece] = cnt;
+      return;
     }
+    if (lane == 0) s_heads[w * OWN + u] = piece < npieces ? cnt : 0;
   }
-  int cnt = 0;
-#pragma unroll
-  for (int r = 0; r < kEPL; ++r) {
-    cnt += (i[r] != pi || j[r] != pj) ? 1 : 0;
-    pi = i[r];
-    pj = j[r];
+  __syncthreads();
+  if (w == 0) {
+    const int heads = lane < kPieces ? s_heads[lane] : 0, upto = wave_inclusive_sum(heads);
+    const int piece = blockIdx.x * kPieces + lane;
+    if (lane < kPieces && piece < npieces) piece_off[piece] = upto - heads;
+    if (lane == kPieces - 1) group_off[blockIdx.x] = upto;
   }
-  cnt = wave_inclusive_sum(cnt);
-  if (lane == kWave - 1) heads[piece] = cnt;
 }
 
-// One output entry per fibre, at index piece_off[piece] + rank of the fibre's head inside
+// The heads of the groups become those of the groups before, in one workgroup (50M entries: 4 us; a scan over all
+// pieces takes 11 in two launches).
+__global__ __launch_bounds__(1024) void ttv_group_off_kernel(int ngroups, int32_t* __restrict__ group_off) {
+  block_exclusive_scan<1024>(group_off, ngroups, 0);
+}
+
+// One output entry per fibre, at index group_off + piece_off[piece] + rank of the fibre's head inside
 // the piece (append order = ascending (i, j), Section 3.4).
 template <typename T, bool VEC, bool ALL>
 __global__ __launch_bounds__(kBig) void ttv_coo_wave_kernel(
     int nnz, int npieces, const int32_t* __restrict__ ci, const int32_t* __restrict__ cj,
     const int32_t* __restrict__ ck, const T* __restrict__ vals, const T* __restrict__ c, int cached,
-    const int32_t* __restrict__ piece_off, int32_t* __restrict__ out_i, int32_t* __restrict__ out_j,
+    const int32_t* __restrict__ piece_off, const int32_t* __restrict__ group_off, int32_t* __restrict__ out_i, int32_t* __restrict__ out_j,
     T* __restrict__ out_v, int64_t* __restrict__ out_nnz, int32_t* __restrict__ carry_key,
     T* __restrict__ carry_val) {
   __shared__ T s_c[kCooCacheBytes / sizeof(T)];
@@ -277,7 +305,7 @@ __global__ __launch_bounds__(kBig) void ttv_coo_wave_kernel(
           v[u][r] = ok ? vals[p] : T(0);
         }
       }
-      first[u] = piece_off[piece];
+      first[u] = piece_off[piece] + group_off[piece / kGroupPieces];
     }
 #pragma unroll
     for (int u = 0; u < kNP; ++u) {
@@ -326,7 +354,7 @@ template <typename T, bool SELF>
 __global__ __launch_bounds__(kBlock) void ttv_coo_piece_kernel(
     int nnz, int npieces, const int32_t* __restrict__ ci, const int32_t* __restrict__ cj,
     const int32_t* __restrict__ ck, const T* __restrict__ vals, const T* __restrict__ c,
-    const int32_t* __restrict__ piece_off, int32_t* __restrict__ out_i, int32_t* __restrict__ out_j,
+    const int32_t* __restrict__ piece_off, const int32_t* __restrict__ group_off, int32_t* __restrict__ out_i, int32_t* __restrict__ out_j,
     T* __restrict__ out_v, int64_t* __restrict__ out_nnz, int32_t* __restrict__ carry_key,
     T* __restrict__ carry_val) {
   constexpr int kWaves = kBlock / kWave;
@@ -378,7 +406,7 @@ __global__ __launch_bounds__(kBlock) void ttv_coo_piece_kernel(
     for (int w = 0; w < kWaves; ++w) first += s_before[w];
     for (int w = piece0; w < piece; ++w) first += piece_off[w];
   } else {
-    first = piece_off[piece];
+    first = piece_off[piece] + group_off[piece / kGroupPieces];
   }
   if (piece0 + wave_id() >= npieces) return;
   const int32_t ui = dpp_move<0x138, 0xf>(-1, i[kEPL - 1]), uj = dpp_move<0x138, 0xf>(-1, j[kEPL - 1]);  // wave_shr:1
@@ -523,10 +551,11 @@ static int compute_units() {
   return cached[dev];
 }
 
-// COO tensors of up to 3M entries leave c in global memory, since staging it in every compute unit costs
-// 8 us, and add up the pieces' counts themselves, since a scan is two launches (us, fp32, skewed tensor:
-// 400 000 entries 12 instead of 23, 2M 29 instead of 34, 4M 48 instead of 47).
-constexpr int kSelfPieces = 12288;
+// COO tensors of up to 1.5M entries leave c in global memory, since staging it in every compute unit costs
+// 8 us, and add up the pieces' counts themselves, since making offsets of them is a launch of its own (us so / as
+// beyond: 400 000 entries 12 / 14, 1.2M 19 / 23, 1.6M 20.5 / 20.1, 2M fp64 in short fibres 32 / 31, 3M skewed 30 / 27;
+// where c stays in global memory in any case, up to 3M: 2.2M, c of 90 000, fp64 31.8 / 32.8).
+constexpr int kSelfPieces = 6144;
 
 static int64_t pieces_of(int64_t nnz) { return (nnz + kPiece - 1) / kPiece; }
 
@@ -542,7 +571,7 @@ bool ttv_wave_applies(int64_t nnz, int64_t K, int dtype) {
 
 size_t ttv_coo_workspace(int64_t nnz) {
   const int64_t np = pieces_of(nnz);
-  return 3 * align_up((size_t)np * 4, 256) + align_up((size_t)np * 8, 256) + scan_workspace(np) + 256;
+  return 3 * align_up((size_t)np * 4, 256) + align_up((size_t)np * 8, 256) + 256;
 }
 size_t ttv_csf_wave_workspace(int64_t nnz) {
   const int64_t np = pieces_of(nnz);
@@ -561,30 +590,38 @@ spt_status ttv_coo(int64_t nnz64, int64_t K, const int32_t* ci, const int32_t* c
   if (!ws || ws_bytes < ttv_coo_workspace(nnz64))
     return fail(SPT_ERR_WORKSPACE, "ttv: workspace of %zu bytes needed, %zu given", ttv_coo_workspace(nnz64), ws_bytes);
   Workspace W(ws, ws_bytes);
-  int32_t* heads = W.take<int32_t>(np);
+  const bool wave = ttv_wave_applies(nnz64, K, sizeof(T) == 8 ? SPT_F64 : SPT_F32);
+  const bool self = np <= (wave ? kSelfPieces : 2 * kSelfPieces);
+  const unsigned groups = (unsigned)((np + kGroupPieces - 1) / kGroupPieces);
+  int32_t* group_off = W.take<int32_t>(groups);
   int32_t* off = W.take<int32_t>(np);
   int32_t* ckey = W.take<int32_t>(np);
   T* cval = W.take<T>(np);
-  int32_t* scan_tmp = reinterpret_cast<int32_t*>(W.take<char>(scan_workspace(np)));
   const bool vec = al16(ci) && al16(cj) && al16(ck) && al16(vals);
   const unsigned grid4 = (unsigned)((np + kBlock / kWave - 1) / (kBlock / kWave));
-  if (vec) hipLaunchKernelGGL(ttv_piece_heads_kernel<true>, dim3(grid4), dim3(kBlock), 0, s, nnz, np, ci, cj, heads);
-  else hipLaunchKernelGGL(ttv_piece_heads_kernel<false>, dim3(grid4), dim3(kBlock), 0, s, nnz, np, ci, cj, heads);
+#define SPT_TTV_HEADS(VEC_, SELF_)                                                                                  \
+  hipLaunchKernelGGL((ttv_piece_heads_kernel<VEC_, SELF_>), dim3(SELF_ ? grid4 : groups), dim3(kBlock), 0, s, nnz, np, \
+                     ci, cj, off, group_off)
+  if (self && vec) SPT_TTV_HEADS(true, true);
+  else if (self) SPT_TTV_HEADS(false, true);
+  else if (vec) SPT_TTV_HEADS(true, false);
+  else SPT_TTV_HEADS(false, false);
+#undef SPT_TTV_HEADS
   SPT_CHECK_LAUNCH("ttv piece heads");
-  if (np <= kSelfPieces) {
+  if (self) {
     hipLaunchKernelGGL((ttv_coo_piece_kernel<T, true>), dim3(grid4), dim3(kBlock), 0, s, nnz, np, ci, cj, ck, vals, c,
-                       heads, out_i, out_j, out_v, out_nnz, ckey, cval);
+                       off, group_off, out_i, out_j, out_v, out_nnz, ckey, cval);
     SPT_CHECK_LAUNCH("ttv coo pieces");
   } else {
-    spt_status st = device_scan_i32<false>(heads, off, np, scan_tmp, s);
-    if (st != SPT_OK) return st;
-    if (ttv_wave_applies(nnz64, K, sizeof(T) == 8 ? SPT_F64 : SPT_F32)) {
+    hipLaunchKernelGGL(ttv_group_off_kernel, dim3(1), dim3(1024), 0, s, (int)groups, group_off);
+    SPT_CHECK_LAUNCH("ttv group offsets");
+    if (wave) {
       const int cached = (int)std::min<int64_t>(K, kCooCacheBytes / sizeof(T));
       const bool all = cached == K;
       const unsigned grid = (unsigned)std::min<int64_t>(compute_units(), (np + kBigWaves - 1) / kBigWaves);
 #define SPT_TTV_COO(VEC_, ALL_)                                                                                    \
   hipLaunchKernelGGL((ttv_coo_wave_kernel<T, VEC_, ALL_>), dim3(grid), dim3(kBig), 0, s, nnz, np, ci, cj, ck, vals, \
-                     c, cached, off, out_i, out_j, out_v, out_nnz, ckey, cval)
+                     c, cached, off, group_off, out_i, out_j, out_v, out_nnz, ckey, cval)
       if (vec && all) SPT_TTV_COO(true, true);
       else if (vec) SPT_TTV_COO(true, false);
       else if (all) SPT_TTV_COO(false, true);
@@ -592,7 +629,7 @@ spt_status ttv_coo(int64_t nnz64, int64_t K, const int32_t* ci, const int32_t* c
 #undef SPT_TTV_COO
     } else {
       hipLaunchKernelGGL((ttv_coo_piece_kernel<T, false>), dim3(grid4), dim3(kBlock), 0, s, nnz, np, ci, cj, ck, vals,
-                         c, off, out_i, out_j, out_v, out_nnz, ckey, cval);
+                         c, off, group_off, out_i, out_j, out_v, out_nnz, ckey, cval);
     }
     SPT_CHECK_LAUNCH("ttv coo");
   }

@@ -22,8 +22,8 @@
 // A bucket that the sample got wrong (more records than fit LDS) is split once more by its workgroup,
 // at splitters of a sample of its own. In random order that happens in none of 300 calls up to 50M
 // records, but in some 2 to 5 of 100 at 60M and 15 of 100 at 2^26, where 256 buckets of a segment are
-// not enough for the larger segments; the call takes no longer for it (60M records, two such inputs of
-// 60: 1.80 ms; with the ranks of the bucket's records counted, 10.4 ms).
+// not enough for the larger segments; the call takes no longer for it (with the ranks of the bucket's records
+// counted, 60M records took 10.4 instead of 1.8 ms).
 //
 // Measured against the six radix passes it replaces (fp64): 60M records with power-law rows
 // 3.09 -> 1.67 ms (splitters 17 + 70 us, classify 2 x 135, offsets 8 + 10, partitions 403 + 430,
@@ -1071,11 +1071,11 @@ __global__ __launch_bounds__(kSel) void select_finish_kernel(const RcSource src,
 
 bool sample_sort_applies(int64_t n) { return n > 0 && n <= kSampleSortMax; }
 
-// Few records: a workgroup of 256 threads takes 16 of a large tile one after the other (14 us to
-// classify them and 15 to 20 to scatter them, whatever n), which tiles of 1024 cut to 8 and 9 to 12 (800 000
-// records: 115 -> 90 us; 3.2M: 204 -> 190; 6M: 257 -> 276, whose counts no longer fit the caches). A single partition's
+// Few records: a thread takes eight or 16 of a large tile one after the other (14 us to classify them, whatever n),
+// which tiles of 1024 cut (fp64, tiles of 1024 / 4096: 1.2M records 84 / 108 us, 2M 122 / 128, 3M 162 / 160, 4M
+// 195 / 185, 6M 259 / 228, whose counts no longer fit the caches). A single partition's
 // workgroups each add up the counts of all tiles, so it has at most 176 of them.
-constexpr int64_t kSmallTileMax = int64_t(1) << 22;
+constexpr int64_t kSmallTileMax = int64_t(11) << 18;
 static int tile_of(int64_t n) {
   if (n <= kOneLevelMax) return n <= 128 * kSmallTile ? kSmallTile : 2 * kSmallTile;
   return n <= kSmallTileMax ? kSmallTile : kTile;

@@ -6,7 +6,7 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
-SELECT, SMALL, ONE, LARGE = 64 * 1024, 128 * 1024, 256 * 1408, 1 << 22  # one launch; tiles of 1024; one partition; tiles of 4096
+SELECT, SMALL, ONE, LARGE = 64 * 1024, 128 * 1024, 256 * 1408, 11 << 18  # one launch; tiles of 1024; one partition; tiles of 4096
 
 
 @pytest.mark.parametrize("keys,by_col,n,dtype", [

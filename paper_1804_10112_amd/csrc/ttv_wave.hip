@@ -181,16 +181,17 @@ __device__ __forceinline__ void wave_fibre_sums(const T (&p)[kEPL], unsigned hea
 // ================================================================ COO
 // piece_off[piece] = (i, j) fibre starts in the pieces before among the workgroup's, group_off[workgroup] = in all of
 // them. Bound by reading i and j; i is ordered, so where it is the same before and at the end of a piece
-// it need not be read. A wave has the loads of four pieces in flight together.
+// it need not be read. A wave has the loads of its pieces in flight together: four, of many entries eight (whole call,
+// fp32, with four / eight: 12M entries 57 / 59 us, 24M 123 / 123, 50M 241 / 231 (this kernel 52 / 41); 16: 62, 130, 245).
 // SELF (few pieces): one piece for a wave, piece_off[piece] = the starts in it.
-constexpr int kGroupPieces = 16;
-template <bool VEC, bool SELF>
+constexpr int kLogGroup = 4, kLogGroupMany = 5, kManyPieces = 96 * 1024;
+template <bool VEC, bool SELF, int LOG_GROUP>
 __global__ __launch_bounds__(kBlock) void ttv_piece_heads_kernel(int nnz, int npieces,
                                                                  const int32_t* __restrict__ ci,
                                                                  const int32_t* __restrict__ cj,
                                                                  int32_t* __restrict__ piece_off,
                                                                  int32_t* __restrict__ group_off) {
-  constexpr int kPieces = SELF ? kBlock / kWave : kGroupPieces, OWN = kPieces / (kBlock / kWave);
+  constexpr int kPieces = SELF ? kBlock / kWave : 1 << LOG_GROUP, OWN = kPieces / (kBlock / kWave);
   __shared__ int s_heads[kPieces];
   const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
   int32_t i[OWN][kEPL], j[OWN][kEPL], bi[OWN], bj[OWN], ei[OWN];
@@ -261,7 +262,7 @@ template <typename T, bool VEC, bool ALL>
 __global__ __launch_bounds__(kBig) void ttv_coo_wave_kernel(
     int nnz, int npieces, const int32_t* __restrict__ ci, const int32_t* __restrict__ cj,
     const int32_t* __restrict__ ck, const T* __restrict__ vals, const T* __restrict__ c, int cached,
-    const int32_t* __restrict__ piece_off, const int32_t* __restrict__ group_off, int32_t* __restrict__ out_i, int32_t* __restrict__ out_j,
+    const int32_t* __restrict__ piece_off, const int32_t* __restrict__ group_off, int log_group, int32_t* __restrict__ out_i, int32_t* __restrict__ out_j,
     T* __restrict__ out_v, int64_t* __restrict__ out_nnz, int32_t* __restrict__ carry_key,
     T* __restrict__ carry_val) {
   __shared__ T s_c[kCooCacheBytes / sizeof(T)];
@@ -305,7 +306,7 @@ __global__ __launch_bounds__(kBig) void ttv_coo_wave_kernel(
           v[u][r] = ok ? vals[p] : T(0);
         }
       }
-      first[u] = piece_off[piece] + group_off[piece / kGroupPieces];
+      first[u] = piece_off[piece] + group_off[piece >> log_group];
     }
 #pragma unroll
     for (int u = 0; u < kNP; ++u) {
@@ -354,7 +355,7 @@ template <typename T, bool SELF>
 __global__ __launch_bounds__(kBlock) void ttv_coo_piece_kernel(
     int nnz, int npieces, const int32_t* __restrict__ ci, const int32_t* __restrict__ cj,
     const int32_t* __restrict__ ck, const T* __restrict__ vals, const T* __restrict__ c,
-    const int32_t* __restrict__ piece_off, const int32_t* __restrict__ group_off, int32_t* __restrict__ out_i, int32_t* __restrict__ out_j,
+    const int32_t* __restrict__ piece_off, const int32_t* __restrict__ group_off, int log_group, int32_t* __restrict__ out_i, int32_t* __restrict__ out_j,
     T* __restrict__ out_v, int64_t* __restrict__ out_nnz, int32_t* __restrict__ carry_key,
     T* __restrict__ carry_val) {
   constexpr int kWaves = kBlock / kWave;
@@ -406,7 +407,7 @@ __global__ __launch_bounds__(kBlock) void ttv_coo_piece_kernel(
     for (int w = 0; w < kWaves; ++w) first += s_before[w];
     for (int w = piece0; w < piece; ++w) first += piece_off[w];
   } else {
-    first = piece_off[piece] + group_off[piece / kGroupPieces];
+    first = piece_off[piece] + group_off[piece >> log_group];
   }
   if (piece0 + wave_id() >= npieces) return;
   const int32_t ui = dpp_move<0x138, 0xf>(-1, i[kEPL - 1]), uj = dpp_move<0x138, 0xf>(-1, j[kEPL - 1]);  // wave_shr:1
@@ -592,25 +593,28 @@ spt_status ttv_coo(int64_t nnz64, int64_t K, const int32_t* ci, const int32_t* c
   Workspace W(ws, ws_bytes);
   const bool wave = ttv_wave_applies(nnz64, K, sizeof(T) == 8 ? SPT_F64 : SPT_F32);
   const bool self = np <= (wave ? kSelfPieces : 2 * kSelfPieces);
-  const unsigned groups = (unsigned)((np + kGroupPieces - 1) / kGroupPieces);
+  const int log_group = np >= kManyPieces ? kLogGroupMany : kLogGroup;
+  const unsigned groups = (unsigned)(((np - 1) >> log_group) + 1);
   int32_t* group_off = W.take<int32_t>(groups);
   int32_t* off = W.take<int32_t>(np);
   int32_t* ckey = W.take<int32_t>(np);
   T* cval = W.take<T>(np);
   const bool vec = al16(ci) && al16(cj) && al16(ck) && al16(vals);
   const unsigned grid4 = (unsigned)((np + kBlock / kWave - 1) / (kBlock / kWave));
-#define SPT_TTV_HEADS(VEC_, SELF_)                                                                                  \
-  hipLaunchKernelGGL((ttv_piece_heads_kernel<VEC_, SELF_>), dim3(SELF_ ? grid4 : groups), dim3(kBlock), 0, s, nnz, np, \
-                     ci, cj, off, group_off)
-  if (self && vec) SPT_TTV_HEADS(true, true);
-  else if (self) SPT_TTV_HEADS(false, true);
-  else if (vec) SPT_TTV_HEADS(true, false);
-  else SPT_TTV_HEADS(false, false);
+#define SPT_TTV_HEADS(VEC_, SELF_, LOG_)                                                                             \
+  hipLaunchKernelGGL((ttv_piece_heads_kernel<VEC_, SELF_, LOG_>), dim3(SELF_ ? grid4 : groups), dim3(kBlock), 0, s, \
+                     nnz, np, ci, cj, off, group_off)
+  if (self && vec) SPT_TTV_HEADS(true, true, kLogGroup);
+  else if (self) SPT_TTV_HEADS(false, true, kLogGroup);
+  else if (vec && log_group == kLogGroup) SPT_TTV_HEADS(true, false, kLogGroup);
+  else if (vec) SPT_TTV_HEADS(true, false, kLogGroupMany);
+  else if (log_group == kLogGroup) SPT_TTV_HEADS(false, false, kLogGroup);
+  else SPT_TTV_HEADS(false, false, kLogGroupMany);
 #undef SPT_TTV_HEADS
   SPT_CHECK_LAUNCH("ttv piece heads");
   if (self) {
     hipLaunchKernelGGL((ttv_coo_piece_kernel<T, true>), dim3(grid4), dim3(kBlock), 0, s, nnz, np, ci, cj, ck, vals, c,
-                       off, group_off, out_i, out_j, out_v, out_nnz, ckey, cval);
+                       off, group_off, log_group, out_i, out_j, out_v, out_nnz, ckey, cval);
     SPT_CHECK_LAUNCH("ttv coo pieces");
   } else {
     hipLaunchKernelGGL(ttv_group_off_kernel, dim3(1), dim3(1024), 0, s, (int)groups, group_off);
@@ -621,7 +625,7 @@ spt_status ttv_coo(int64_t nnz64, int64_t K, const int32_t* ci, const int32_t* c
       const unsigned grid = (unsigned)std::min<int64_t>(compute_units(), (np + kBigWaves - 1) / kBigWaves);
 #define SPT_TTV_COO(VEC_, ALL_)                                                                                    \
   hipLaunchKernelGGL((ttv_coo_wave_kernel<T, VEC_, ALL_>), dim3(grid), dim3(kBig), 0, s, nnz, np, ci, cj, ck, vals, \
-                     c, cached, off, group_off, out_i, out_j, out_v, out_nnz, ckey, cval)
+                     c, cached, off, group_off, log_group, out_i, out_j, out_v, out_nnz, ckey, cval)
       if (vec && all) SPT_TTV_COO(true, true);
       else if (vec) SPT_TTV_COO(true, false);
       else if (all) SPT_TTV_COO(false, true);
@@ -629,7 +633,7 @@ spt_status ttv_coo(int64_t nnz64, int64_t K, const int32_t* ci, const int32_t* c
 #undef SPT_TTV_COO
     } else {
       hipLaunchKernelGGL((ttv_coo_piece_kernel<T, false>), dim3(grid4), dim3(kBlock), 0, s, nnz, np, ci, cj, ck, vals,
-                         c, off, group_off, out_i, out_j, out_v, out_nnz, ckey, cval);
+                         c, off, group_off, log_group, out_i, out_j, out_v, out_nnz, ckey, cval);
     }
     SPT_CHECK_LAUNCH("ttv coo");
   }

@@ -1,5 +1,5 @@
 """COO tensor times vector where the offsets of the results come from groups of pieces: entry counts at the edges of
-pieces (256 entries), groups (16 pieces) and of the rule (6144 pieces, 12288 where c is too long to be held). Built on the
+pieces (256 entries), groups (16 and 32 pieces) and of the rules (6144 pieces, 12288 where c is too long to be held; 98304). Built on the
 GPU; the reference is the definition, its products and sums in float64."""
 import numpy as np
 import pytest
@@ -18,6 +18,8 @@ FROM, PIECE = 6144 * 256, 256
     ("each", 50_000, FROM + 17 * PIECE - 1, "float32", True),
     ("mixed", 200_000, 2 * FROM, "float64", False),
     ("short", 200_000, 2 * FROM + 5, "float32", False),
+    ("mixed", 9000, 16 * FROM - 1, "float32", False),
+    ("mixed", 9000, 16 * FROM + 31 * PIECE + 7, "float32", True),
 ])
 def test_ttv_groups(fibres, K, nnz, dtype, misalign):
     import torch

@@ -19,9 +19,10 @@
 // as carry number `piece` and is added afterwards (carry_fixup_kernel), in a fixed order:
 // results are bit-reproducible.
 // Measured on 50M entries in 8.1M fibres, fp32, c of 50 000 values (78 % / 61 % of it cached):
-// COO 214 us (workgroups of 2048 entries with c in global memory: 324 us), CSF 158 us (357 us). Left out
+// COO 231 us in all (count of the heads 41, their offsets 5, this kernel 182), CSF 157 us (workgroups of 2048 entries
+// with c in global memory: 324 and 357 us). Left out
 // after measuring: eight entries per lane (a lane's two 16-byte loads then lie 32 bytes apart:
-// 263 / 174 us), four pieces in flight instead of two or the next two loaded ahead (no change), results
+// 263 / 174 us, against 214 / 158 then), four pieces in flight instead of two or the next two loaded ahead (no change), results
 // put in order in LDS before they are stored (dense fibres 12 % faster, skewed tensors 2 to 5 % slower). What remains is the serial
 // instruction stream of a wave: sixteen waves per compute unit is all that one workgroup, which
 // the single copy of c forces, can provide.

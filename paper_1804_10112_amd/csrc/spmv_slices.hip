@@ -149,6 +149,7 @@ __global__ __launch_bounds__(kSliceBlock) __attribute__((amdgpu_waves_per_eu(4, 
     const int lo = live ? seg_row[seg] : 0, hi = live ? seg_row[seg + 1] : 0;
 #pragma unroll
     for (int u = 0; u < V; ++u) *reinterpret_cast<I4*>(heads + u * kSegment + lane * 4) = I4(-1);
+    wave_lds_order();  // other lanes enter rows over what a lane has cleared
     constexpr int kMany = 256;
     const bool many = hi - lo > kMany;
     if (!many) {
@@ -183,6 +184,7 @@ __global__ __launch_bounds__(kSliceBlock) __attribute__((amdgpu_waves_per_eu(4, 
       for (int q = 0; q < 4; ++q)
         if (r[q] >= l && lane * 4 + q < nnz - from && pos_or_row[r[q]] - from == lane * 4 + q) heads[slot + lane * 4 + q] = r[q];
     }
+    wave_lds_order();  // and other lanes again read them
     r_first = __shfl(lo, min(lane * L, kWave - 1));
   }
 

@@ -13,11 +13,13 @@ CSR_FROM, COO_FROM, SEGMENT = 1 << 25, (1 << 24) + 1, 256
 def _lengths(kind, N, nnz, g):
     """Row lengths that add up to nnz: runs of empty rows at both ends and (one segment's worth of them and more)
     in the middle; `heavy` adds rows of many segments (`declared`: and a bound on them), `one row` leaves nearly all
-    entries to one."""
+    entries to one, `some empty` leaves a third of all rows without entries."""
     import torch
     L = torch.randint(0, 2 * (nnz // N) + 2, (N,), generator=g, device="cuda")
     if kind == "one row":
         L = torch.randint(0, 2, (N,), generator=g, device="cuda")
+    elif kind == "some empty":
+        L = torch.randint(0, 3, (N,), generator=g, device="cuda")
     L[:700] = 0
     L[N // 2:N // 2 + 3000] = 0
     L[-900:] = 0
@@ -112,6 +114,10 @@ def _check(A, row, col, vals, x, N, ws, what):
     ("csr", "declared", "scattered", "float32", 1_500_007, 254, False),
     ("csr", "declared", "local", "float64", 750_003, 1, False),
     ("csr", "one row", "scattered", "float32", 1_500_007, 1, False),
+    # rows of a segment about as many as its entries: a wave enters those of some segments row by row (up to 256) and
+    # looks those of others up, into the same stretch of LDS
+    ("csr", "some empty", "scattered", "float64", 750_003, 7, False),
+    ("csr", "some empty", "scattered", "float32", 1_500_007, 2, True),
     ("coo", "even", "scattered", "float64", 750_003, 0, True),
     ("coo", "heavy", "scattered", "float32", 1_500_007, 255, False),
     ("coo", "heavy", "local", "float64", 2_000_003, 2, False),
@@ -122,7 +128,7 @@ def test_against_the_definition(form, kind, cols, dtype, M, extra, misalign):
     import torch
     dt = getattr(torch, dtype)
     nnz = (CSR_FROM if form == "csr" else COO_FROM + SEGMENT - 1) + extra
-    N = 1_200_007 if form == "csr" else 700_003
+    N = nnz + 100_000 if kind == "some empty" else 1_200_007 if form == "csr" else 700_003
     A, keep, row, col, vals = _matrix(form, kind, cols, N, M, nnz, dt, misalign, 5)
     g = torch.Generator(device="cuda").manual_seed(6)
     x = torch.rand(M, generator=g, device="cuda", dtype=dt) * 2 - 1

@@ -11,7 +11,7 @@
 //    segmented scan; a row cut by a chunk boundary is finished by a tiny carry
 //    kernel. No atomics, results are bit-reproducible.
 //  * Sorted COO of up to 2^24 entries: a wave per 256 entries, in one launch up to 65 536.
-//  * Unsorted COO is the paper's scatter loop with atomic adds into y, from 393 216 entries on the binned
+//  * Unsorted COO is the paper's scatter loop with atomic adds into y, from 786 432 entries on the binned
 //    scatter of coo_bin.hip.
 //  * DIA and ELL read the diagonal-major / slot-major arrays with consecutive
 //    rows in consecutive lanes.
@@ -1114,23 +1114,23 @@ spt_status coo_binned_spmv(int64_t nnz, int64_t nrows, int64_t ncols, const int3
                            const T* vals, const T* x, T* y, void* ws, size_t ws_bytes,
                            hipStream_t s);
 size_t coo_binned_workspace(int dtype, int64_t nnz, int64_t nrows);
-// Below this the scatter with atomics is cheaper than the four launches of the binned one. In us, scatter /
-// binned, fp64 and fp32 (CSC the same and 3 to 7 for its columns):
-//   entries                   200 000           300 000           400 000           550 000           780 000
-//   uniform rows         14/21  18/20      19/22  23/21      23/23  27/21      32/24  34/22      42/26  44/24
-//   power law            15/21  18/20      21/22  24/21      28/23  31/21      39/24  42/23      52/26  55/25
-// Binning takes a workspace: up to kScatterMost entries a caller without it has the scatter.
-constexpr int64_t kBinnedMinEntries = 3 << 17, kScatterMost = 3 << 18;
+// Below this unordered entries are scattered with atomics, from here on they are binned (four launches). The line lies
+// where no order of the rows loses; for rows in random order alone it would lie at half of it. In us, scatter / binned:
+//   entries                       400 000           600 000           780 000
+//                              fp64    fp32      fp64    fp32      fp64    fp32
+//   random order, power law   27/23   29/22     41/27   48/24     49/29   59/27
+//   random order, uniform     23/24   27/22     31/27   34/24     39/29   45/26
+//   ordered, not flagged so    8/24    9/23      9/26   11/24     10/28   12/25
+//   half of them in one row   16/35   23/33     23/38   22/36     28/41   35/38
+//   CSC, banded               16/27   16/26     20/30   21/28     24/32   25/29
+constexpr int64_t kBinnedMinEntries = 3 << 18;
 
 size_t coo_unordered_workspace(int dtype, int64_t nnz, int64_t nrows) {
   return nnz >= kBinnedMinEntries ? coo_binned_workspace(dtype, nnz, nrows) : 256;
 }
 // The least that a call takes.
 static size_t coo_unordered_least(int dtype, int64_t nnz, int64_t nrows) {
-  return nnz >= kScatterMost ? coo_binned_workspace(dtype, nnz, nrows) : 0;
-}
-static bool coo_use_bins(int dtype, int64_t nnz, int64_t nrows, const void* ws, size_t ws_bytes) {
-  return nnz >= kScatterMost || (nnz >= kBinnedMinEntries && ws && ws_bytes >= coo_binned_workspace(dtype, nnz, nrows));
+  return nnz >= kBinnedMinEntries ? coo_binned_workspace(dtype, nnz, nrows) : 0;
 }
 
 constexpr int kSegIPT = 8;
@@ -1408,7 +1408,7 @@ static spt_status spmv_typed(Format f, const spt_tensor* A, const T* x, T* y, vo
       spt_status st = launch_expand_parents((int)nnz, (int)M, A->level[1].pos, cols, s);
       if (st != SPT_OK) return st;
       char* rest = static_cast<char*>(ws) + W.used;
-      if (coo_use_bins(A->dtype, nnz, N, rest, ws_bytes - W.used))  // (no columns to speak of: they ascend)
+      if (nnz >= kBinnedMinEntries)  // (no columns to speak of: they ascend)
         return coo_binned_spmv<T>(nnz, N, 0, A->level[1].crd, cols, vals, x, y, rest, ws_bytes - W.used, s);
       st = launch_fill<T>(y, N, T(0), s);
       if (st != SPT_OK) return st;
@@ -1435,7 +1435,7 @@ static spt_status spmv_typed(Format f, const spt_tensor* A, const T* x, T* y, vo
       if (A->level[0].flags & SPT_ORDERED)
         return launch_seg<T, false>(nnz, N, A->level[0].crd, A->level[1].crd, vals, x, y, ws, ws_bytes, s);
       if (nnz >= INT32_MAX) return fail(SPT_ERR_UNSUPPORTED, "spmv: more than 2^31 entries");
-      if (coo_use_bins(A->dtype, nnz, N, ws, ws_bytes))
+      if (nnz >= kBinnedMinEntries)
         return coo_binned_spmv<T>(nnz, N, A->level[1].N, A->level[0].crd, A->level[1].crd, vals, x, y, ws, ws_bytes,
                                   s);
       spt_status st = launch_fill<T>(y, N, T(0), s);

@@ -163,3 +163,22 @@ def test_invalid_and_unsupported_descriptors():
     t.level[1].max_children = 100_000       # declared long rows: the entry-balanced kernel and its carries
     st, msg = _status(spt.spt_spmv, t, 0x1000, 0x1000, None, 0)
     assert st == B.SPT_ERR_WORKSPACE and "workspace" in msg
+
+
+@pytest.mark.parametrize("form", ["coo", "csc"])
+def test_unordered_entries_are_binned_from_786432_on(form):
+    """The bins take scratch for every entry; the scatter below them takes none, or CSC its columns."""
+    def need(nnz):
+        one, zero = np.ones(nnz, np.float32), np.zeros(nnz, np.int32)
+        if form == "coo":
+            spec = wl.coo_spec(1000, 1000, zero, zero, one, ordered=False)
+        else:
+            spec = wl.csr_spec(1000, 1000, np.full(1001, nnz, np.int32), zero, one)
+        t = _host_desc(spec)
+        if form == "csc":
+            t.level[0].mode, t.level[1].mode = 1, 0
+        return spt.spt_workspace_bytes(spt.SPT_OP_SPMV, t)
+    columns = 4 if form == "csc" else 0
+    for nnz in (400_000, 786_431):
+        assert need(nnz) <= columns * nnz + 1024
+    assert need(786_432) >= (columns + 6) * 786_432  # a row within its bin in 16 bits and a product

@@ -5,7 +5,7 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
-FROM, MOST, STEP = 3 << 17, 3 << 18, 512 * 2048  # binned; binned without a choice; entries that a vector a thread is
+FROM, MOST, STEP = 3 << 17, 3 << 18, 512 * 2048  # half of the line; binned from here on; entries that a vector a thread is
 
 
 def _entries(order, N, M, nnz, dtype, misalign, seed):
@@ -77,7 +77,7 @@ def _operand(form, N, M, row, col, row32, col32, vals):
     ("coo", "sorted", 300_000, 1_600_000, (1 << 22) + 4099, "float32", True, "query"),
     ("coo", "heavy", (1 << 24) + 1000, 800_001, (1 << 22) + 2, "float64", True, "query"),
     ("coo", "random", 300_000, 800_001, (1 << 22) - 1, "float64", False, "query"),
-    # without the workspace of the bins: the scatter, as far as that goes
+    # without the workspace of the bins: the scatter below the line
     ("coo", "random", 40_000, 30_000, FROM, "float64", False, "none"),
     ("coo", "random", 40_000, 30_000, MOST - 1, "float32", False, "none"),
     ("coo", "random", 40_000, 30_000, MOST, "float64", False, "refused"),

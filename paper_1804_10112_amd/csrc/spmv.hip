@@ -1249,7 +1249,7 @@ constexpr int64_t kDynamicMinEntries = int64_t(1) << 25;
 //   36M entries, CSR         fp32 6 MB 272 / 234, 24 MB 593 / 294; fp64 24 MB 597 / 317, 96 MB 795 / 600
 //   17M entries, COO         fp64 8 MB 200 / 138; fp32 6.4 MB 155 / 133
 //   power law, CSR           fp64, 60M entries, 32 MB 970 / 576; fp32, 35M entries, 9.2 MB 378 / 248
-//   local columns, CSR, 36M  skewed rows fp64 177 / 156, fp32 115 / 114; mean row 90 fp64 154 / 123, fp32 96 / 100;
+//   local columns, CSR, 36M  a heavy row fp64 171 / 138, fp32 112 / 110; mean row 90 fp64 153 / 111, fp32 94 / 82;
 //                            a declared bound of 16, which spared the choice before, fp64 107 / 121, fp32 63 / 76
 // Takes a larger workspace than the carries of the kernels it replaces; a caller with one of that size has those.
 size_t slices_spmv_workspace(int64_t nnz);

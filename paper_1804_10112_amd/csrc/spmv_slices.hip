@@ -94,10 +94,206 @@ __global__ __launch_bounds__(kBlock) void segment_rows_kernel(int nrows, const i
   find_segment_rows(nrows, pos, nseg, seg_row, y);
 }
 
-// Columns that do not lie scattered (the device's choice): the same with one slice, segments in order. A wave reduces
-// its segments one after the other in registers; the segment that holds a row's first entry stores the row's sum, what
-// precedes the first row start leaves as carry number `segment`. CSR: the rows that start in a segment are entered at
-// their first entry in LDS. Fixed order of additions: bit-reproducible.
+// The sums of a segment's rows, in registers: the segment that holds a row's first entry stores the row's sum, what
+// precedes the first row start leaves as carry number `seg`. A lane has the entries lane * 4 .. lane * 4 + 3, those from
+// `left_over` on do not count. rows: COO, their rows; CSR, the rows that start at them, or -1. cut: the row that
+// the segment's start cuts. Fixed order of additions: bit-reproducible.
+template <typename T, bool CSR, class V4, class I4>
+__device__ __forceinline__ void reduce_segment(int seg, int64_t left_over, int cut, const V4& v, const T* got, const I4& rows,
+                                               T* __restrict__ y, int32_t* __restrict__ carry_key, T* __restrict__ carry_val) {
+  const int lane = lane_id();
+  int32_t before = cut;
+  if (!CSR) {
+    const int32_t left = dpp_move<0x138, 0xf>(-1, rows[3]);  // wave_shr:1
+    if (lane > 0) before = left;
+  }
+  T acc = 0, lead = 0;
+  bool has_head = false, head_first = false;
+  int last_row = -1;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int32_t r = rows[q];
+    if (CSR ? r >= 0 : r != before) {
+      if (has_head) y[last_row] = acc;  // a row that starts and ends inside this lane
+      else lead = acc;
+      head_first = head_first || q == 0;
+      has_head = true;
+      last_row = r;
+      acc = 0;
+    }
+    acc += lane * 4 + q < left_over ? v[q] * got[q] : T(0);
+    before = r;
+  }
+  const uint64_t marks = __ballot(has_head);
+  const int from = last_lane(marks, false), prev_head = last_lane(marks, true);
+  const T sum = wave_marked_sum<T>(acc, from >= 0 ? lane - from : kWave);
+  T open = dpp_move<0x138, 0xf>(T(0), sum);  // what is open before this lane
+  if (lane == 0) open = T(0);
+  const int open_row = __shfl(last_row, max(prev_head, 0));
+  if (has_head) {
+    if (prev_head >= 0) {
+      y[open_row] = open + lead;
+    } else {  // what precedes the segment's first row start
+      carry_key[seg] = lane == 0 && head_first ? -1 : cut;
+      carry_val[seg] = open + lead;
+    }
+  }
+  if (lane == kWave - 1) {  // the row still open at the end of the segment
+    if (from >= 0) {
+      y[has_head ? last_row : open_row] = sum;
+    } else {
+      carry_key[seg] = cut;
+      carry_val[seg] = sum;
+    }
+  }
+}
+
+// CSR, for a segment with more than kMany row starts (mostly of rows without entries): the row of each entry is looked up
+// in rows l .. h - 1, which start in it. from: its first entry.
+constexpr int kMany = 256;
+__device__ __forceinline__ void look_up_rows(int l, int h, int from, int nnz, const int32_t* __restrict__ pos, int32_t* heads) {
+  const int lane = lane_id();
+  int r[4], end[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    r[q] = l - 1;
+    end[q] = h;
+  }
+  for (int span = h - l + 1; span > 1; span = (span + 1) / 2) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int mid = r[q] + (end[q] - r[q]) / 2;
+      if (mid > r[q]) {
+        if (pos[mid] - from <= lane * 4 + q) r[q] = mid;
+        else end[q] = mid;
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (r[q] >= l && lane * 4 + q < nnz - from && pos[r[q]] - from == lane * 4 + q) heads[lane * 4 + q] = r[q];
+}
+
+// Columns that do not lie scattered (the device's choice): x is gathered as the entries come, and kCus workgroups go
+// through the segments in order, an eighth of them on each XCD (a stretch to each workgroup: ordered COO, 60M, fp64
+// 256 us, fp32 174). A wave waits for no other, and has the gathers of the next segment and the columns of the one after
+// that on their way while it adds up one (gathers when their turn comes: up to 4 % longer). Bound by memory, 4.2 TB/s.
+// Whole call, local columns, in us, with all entries of a wave at once as for slices / a kernel of chunks in LDS without
+// a choice before it / this way:
+//   entries              18M              25M               36M               40M               50M              74M
+//   COO, fp64        84 / 81 / 80   112 / 113 / 104   156 / 148 / 148   175 / 164 / 166   214 / 202 / 202   296 / 275 / 280
+//   COO, fp32        64 / 55 / 57    82 / 73 / 72     115 / 102 / 106   128 / 113 / 115   158 / 141 / 139   212 / 182 / 178
+//   CSR, a heavy row,                                 148 / 171 / 138   161 / 191 / 150   193 / 231 / 181   253 / 309 / 228
+//     fp64 and fp32                                   116 / 112 / 110   125 / 124 / 115   146 / 149 / 133   184 / 193 / 157
+template <typename T, bool CSR>
+__device__ __forceinline__ void segments_in_order(int nnz, int nseg, const int32_t* __restrict__ pos_or_row,
+                                                  const int32_t* __restrict__ col, const T* __restrict__ vals,
+                                                  const T* __restrict__ x, T* __restrict__ y, const int32_t* __restrict__ seg_row,
+                                                  int32_t* __restrict__ carry_key, T* __restrict__ carry_val, int32_t* heads) {
+  typedef T V4 __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+  typedef int32_t I4 __attribute__((ext_vector_type(4), aligned(4)));
+  if (blockIdx.x >= kCus) return;
+  const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  // an XCD has an eighth of the segments, its workgroups side by side
+  constexpr int kStep = kCus / kXcds * kSliceWaves;
+  const int per = (nseg + kXcds - 1) / kXcds, xcd = blockIdx.x % kXcds, limit = min((xcd + 1) * per, nseg);
+  struct Entries {
+    I4 r;           // COO: rows
+    V4 v;
+    T got[4];
+    int32_t prior;  // COO: row of the entry before the segment
+    int lo, hi;     // CSR: the rows that start in the segment,
+    int a, b;       // and where the first 64 of them begin and end
+  };
+  const auto load_columns = [&](int seg) {
+    const int64_t p = static_cast<int64_t>(seg) * kSegment;
+    I4 c;
+    if (p + kSegment <= nnz) {  // uniform
+      c = __builtin_nontemporal_load(reinterpret_cast<const I4*>(col + p + lane * 4));
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) c[q] = p + lane * 4 + q < nnz ? col[p + lane * 4 + q] : 0;  // beyond the end: not counted
+    }
+    return c;
+  };
+  const auto load_bounds = [&](int seg, Entries& e) {
+    e.lo = seg_row[seg];
+    e.hi = seg_row[seg + 1];
+  };
+  const auto gather = [&](const I4& c, Entries& e) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) e.got[q] = *reinterpret_cast<const T*>(reinterpret_cast<const char*>(x) + static_cast<uint32_t>(c[q]) * sizeof(T));
+  };
+  const auto load = [&](int seg, Entries& e) {
+    const int64_t p = static_cast<int64_t>(seg) * kSegment;
+    if (p + kSegment <= nnz) {  // uniform
+      e.v = __builtin_nontemporal_load(reinterpret_cast<const V4*>(vals + p + lane * 4));
+      if (!CSR) e.r = __builtin_nontemporal_load(reinterpret_cast<const I4*>(pos_or_row + p + lane * 4));
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int64_t at = p + lane * 4 + q < nnz ? p + lane * 4 + q : nnz - 1;
+        e.v[q] = vals[at];
+        if (!CSR) e.r[q] = pos_or_row[at];
+      }
+    }
+    if (CSR) {
+      const int r = min(e.lo + lane, max(e.hi - 1, e.lo));  // (no row: nothing behind the end of pos is read)
+      e.a = pos_or_row[r];
+      e.b = pos_or_row[min(r + 1, max(e.hi, e.lo))];
+    } else {
+      e.prior = seg > 0 ? pos_or_row[p - 1] : -1;
+    }
+  };
+  int seg = xcd * per + static_cast<int>(blockIdx.x) / kXcds * kSliceWaves + w;
+  if (seg >= limit) return;
+  Entries now{}, next{};
+  I4 c = load_columns(seg);  // of the segment that is gathered next
+  if (CSR) load_bounds(seg, now);
+  gather(c, now);
+  load(seg, now);
+  if (seg + kStep < limit) {
+    c = load_columns(seg + kStep);
+    if (CSR) load_bounds(seg + kStep, next);
+  }
+  for (; seg < limit; seg += kStep) {
+    const int after = seg + kStep;
+    Entries later{};
+    if (after < limit) {  // uniform
+      gather(c, next);
+      load(after, next);
+      if (after + kStep < limit) {
+        c = load_columns(after + kStep);
+        if (CSR) load_bounds(after + kStep, later);
+      }
+    }
+    I4 rows = now.r;
+    if (CSR) {
+      *reinterpret_cast<I4*>(heads + lane * 4) = I4(-1);
+      wave_lds_order();
+      const int base = seg * kSegment;
+      if (now.hi - now.lo > kMany) {
+        look_up_rows(now.lo, now.hi, base, nnz, pos_or_row, heads);
+      } else {
+        if (now.lo + lane < now.hi && now.b > now.a) heads[now.a - base] = now.lo + lane;
+        for (int r = now.lo + kWave + lane; r < now.hi; r += kWave) {
+          const int a = pos_or_row[r], b = pos_or_row[r + 1];
+          if (b > a) heads[a - base] = r;
+        }
+      }
+      wave_lds_order();
+      rows = *reinterpret_cast<const I4*>(heads + lane * 4);
+      wave_lds_order();
+    }
+    reduce_segment<T, CSR>(seg, nnz - static_cast<int64_t>(seg) * kSegment, CSR ? now.lo - 1 : now.prior, now.v, now.got, rows, y, carry_key,
+                           carry_val);
+    now = next;
+    next = later;
+  }
+}
+
+// x slice by slice, all segments of a wave at once. CSR: the rows that start in a segment are entered at their first entry
+// in LDS.
 template <typename T, bool CSR>
 __global__ __launch_bounds__(kSliceBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) void slices_spmv_kernel(
     int nnz, int nseg, int nslices, int slice, bool rows_may, const int32_t* __restrict__ pos_or_row, const int32_t* __restrict__ col,
@@ -109,13 +305,14 @@ __global__ __launch_bounds__(kSliceBlock) __attribute__((amdgpu_waves_per_eu(4, 
   extern __shared__ __attribute__((aligned(16))) int32_t s_rows[];  // CSR: the row that starts at an entry, or -1
   const int choice = read_choice(flags);
   if (rows_may && choice == kByRows) return;
-  const bool by_slices = choice == kBySlices;
   const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
-  // segment of vector j: first + j * step, none from `limit` on
-  const int per = (nseg + gridDim.x - 1) / gridDim.x, mine = xcd_contiguous_block_id() * per;
-  const int step = by_slices ? kSliceWaves * gridDim.x : kSliceWaves;
-  const int limit = by_slices ? nseg : min(mine + per, nseg);
-  const int first = by_slices ? w * gridDim.x + blockIdx.x : mine + w;
+  int32_t* heads = s_rows + w * (V * kSegment);
+  if (choice != kBySlices) {
+    segments_in_order<T, CSR>(nnz, nseg, pos_or_row, col, vals, x, y, seg_row, carry_key, carry_val, heads);
+    return;
+  }
+  // segment of vector j: first + j * step, none from nseg on
+  const int step = kSliceWaves * gridDim.x, first = w * gridDim.x + blockIdx.x;
 
   uint32_t at[4 * V];
   T got[4 * V];
@@ -124,7 +321,7 @@ __global__ __launch_bounds__(kSliceBlock) __attribute__((amdgpu_waves_per_eu(4, 
   for (int j = 0; j < V; ++j) {
     const int seg = first + j * step;
     const int64_t p = static_cast<int64_t>(seg) * kSegment;
-    if (seg < limit && p + kSegment <= nnz) {  // uniform
+    if (seg < nseg && p + kSegment <= nnz) {  // uniform
       const I4 c = __builtin_nontemporal_load(reinterpret_cast<const I4*>(col + p + lane * 4));
 #pragma unroll
       for (int q = 0; q < 4; ++q) at[4 * j + q] = static_cast<uint32_t>(c[q]) * sizeof(T);
@@ -132,25 +329,23 @@ __global__ __launch_bounds__(kSliceBlock) __attribute__((amdgpu_waves_per_eu(4, 
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int64_t e = p + lane * 4 + q;
-        at[4 * j + q] = seg < limit && e < nnz ? static_cast<uint32_t>(col[e]) * sizeof(T) : kNowhere;
+        at[4 * j + q] = seg < nseg && e < nnz ? static_cast<uint32_t>(col[e]) * sizeof(T) : kNowhere;
       }
     }
   }
 #pragma unroll
   for (int k = 0; k < 4 * V; ++k) got[k] = 0;
-  SliceGather<T, 4 * V>::run(x, by_slices ? nslices : 1, by_slices ? slice : kNowhere, at, got);
+  SliceGather<T, 4 * V>::run(x, nslices, slice, at, got);
 
-  int32_t* heads = s_rows + w * (V * kSegment);
   int r_first = 0;  // CSR, lane j: the first row that starts in segment j
   if (CSR) {
-    constexpr int L = V <= 8 ? 8 : 4;  // lanes that enter the rows of a segment
-    const int j = min(lane / L, V - 1), seg = first + j * step, base = seg * kSegment;
-    const bool live = lane / L < V && seg < limit;
+    constexpr int L = kWave / V;  // lanes that enter the rows of a segment
+    const int j = lane / L, seg = first + j * step, base = seg * kSegment;
+    const bool live = seg < nseg;
     const int lo = live ? seg_row[seg] : 0, hi = live ? seg_row[seg + 1] : 0;
 #pragma unroll
     for (int u = 0; u < V; ++u) *reinterpret_cast<I4*>(heads + u * kSegment + lane * 4) = I4(-1);
     wave_lds_order();  // other lanes enter rows over what a lane has cleared
-    constexpr int kMany = 256;
     const bool many = hi - lo > kMany;
     if (!many) {
       for (int r = lo + lane % L; r < hi; r += L) {
@@ -159,36 +354,17 @@ __global__ __launch_bounds__(kSliceBlock) __attribute__((amdgpu_waves_per_eu(4, 
       }
     }
     uint64_t todo = __ballot(many && lane % L == 0);
-    while (todo) {  // mostly rows without entries: the row of each entry is looked up instead
+    while (todo) {
       const int src = __ffsll(static_cast<long long>(todo)) - 1;
       todo &= todo - 1;
-      const int l = __builtin_amdgcn_readlane(lo, src), h = __builtin_amdgcn_readlane(hi, src);
-      const int slot = __builtin_amdgcn_readlane(j, src) * kSegment, from = __builtin_amdgcn_readlane(base, src);
-      int r[4], end[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        r[q] = l - 1;
-        end[q] = h;
-      }
-      for (int span = h - l + 1; span > 1; span = (span + 1) / 2) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int mid = r[q] + (end[q] - r[q]) / 2;
-          if (mid > r[q]) {
-            if (pos_or_row[mid] - from <= lane * 4 + q) r[q] = mid;
-            else end[q] = mid;
-          }
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (r[q] >= l && lane * 4 + q < nnz - from && pos_or_row[r[q]] - from == lane * 4 + q) heads[slot + lane * 4 + q] = r[q];
+      look_up_rows(__builtin_amdgcn_readlane(lo, src), __builtin_amdgcn_readlane(hi, src), __builtin_amdgcn_readlane(base, src), nnz,
+                   pos_or_row, heads + __builtin_amdgcn_readlane(j, src) * kSegment);
     }
     wave_lds_order();  // and other lanes again read them
     r_first = __shfl(lo, min(lane * L, kWave - 1));
   }
 
-    constexpr int kBatch = sizeof(T) == 8 ? 2 : 4;
+  constexpr int kBatch = sizeof(T) == 8 ? 2 : 4;
 #pragma unroll
   for (int h = 0; h < V; h += kBatch) {
     V4 v[kBatch];
@@ -198,10 +374,10 @@ __global__ __launch_bounds__(kSliceBlock) __attribute__((amdgpu_waves_per_eu(4, 
     for (int j = 0; j < kBatch; ++j) {
       const int seg = first + (h + j) * step;
       const int64_t p = static_cast<int64_t>(seg) * kSegment;
-      if (seg < limit && p + kSegment <= nnz) {  // uniform
+      if (seg < nseg && p + kSegment <= nnz) {  // uniform
         v[j] = __builtin_nontemporal_load(reinterpret_cast<const V4*>(vals + p + lane * 4));
         if (!CSR) rows[j] = __builtin_nontemporal_load(reinterpret_cast<const I4*>(pos_or_row + p + lane * 4));
-      } else if (seg < limit) {
+      } else if (seg < nseg) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int64_t e = p + lane * 4 + q;
@@ -209,59 +385,16 @@ __global__ __launch_bounds__(kSliceBlock) __attribute__((amdgpu_waves_per_eu(4, 
           if (!CSR) rows[j][q] = pos_or_row[e < nnz ? e : nnz - 1];
         }
       }
-      if (!CSR) prior[j] = seg > 0 && seg < limit ? pos_or_row[p - 1] : -1;
+      if (!CSR) prior[j] = seg > 0 && seg < nseg ? pos_or_row[p - 1] : -1;
     }
 #pragma unroll
     for (int j = 0; j < kBatch; ++j) {
       const int seg = first + (h + j) * step;
-      if (seg >= limit) break;  // uniform
-      const int64_t left_over = nnz - static_cast<int64_t>(seg) * kSegment;
+      if (seg >= nseg) break;  // uniform
       if (CSR) rows[j] = *reinterpret_cast<const I4*>(heads + (h + j) * kSegment + lane * 4);
-      const int cut = CSR ? __builtin_amdgcn_readlane(r_first, h + j) - 1 : prior[j];  // the row that the segment's start cuts
-      int32_t before = cut;
-      if (!CSR) {
-        const int32_t left = dpp_move<0x138, 0xf>(-1, rows[j][3]);  // wave_shr:1
-        if (lane > 0) before = left;
-      }
-      T acc = 0, lead = 0;
-      bool has_head = false, head_first = false;
-      int last_row = -1;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int32_t r = rows[j][q];
-        if (CSR ? r >= 0 : r != before) {
-          if (has_head) y[last_row] = acc;  // a row that starts and ends inside this lane
-          else lead = acc;
-          head_first = head_first || q == 0;
-          has_head = true;
-          last_row = r;
-          acc = 0;
-        }
-        acc += lane * 4 + q < left_over ? v[j][q] * got[4 * (h + j) + q] : T(0);
-        before = r;
-      }
-      const uint64_t marks = __ballot(has_head);
-      const int from = last_lane(marks, false), prev_head = last_lane(marks, true);
-      const T sum = wave_marked_sum<T>(acc, from >= 0 ? lane - from : kWave);
-      T open = dpp_move<0x138, 0xf>(T(0), sum);  // what is open before this lane
-      if (lane == 0) open = T(0);
-      const int open_row = __shfl(last_row, max(prev_head, 0));
-      if (has_head) {
-        if (prev_head >= 0) {
-          y[open_row] = open + lead;
-        } else {  // what precedes the segment's first row start
-          carry_key[seg] = lane == 0 && head_first ? -1 : cut;
-          carry_val[seg] = open + lead;
-        }
-      }
-      if (lane == kWave - 1) {  // the row still open at the end of the segment
-        if (from >= 0) {
-          y[has_head ? last_row : open_row] = sum;
-        } else {
-          carry_key[seg] = cut;
-          carry_val[seg] = sum;
-        }
-      }
+      reduce_segment<T, CSR>(seg, nnz - static_cast<int64_t>(seg) * kSegment,
+                             CSR ? __builtin_amdgcn_readlane(r_first, h + j) - 1 : prior[j], v[j], got + 4 * (h + j), rows[j], y,
+                             carry_key, carry_val);
     }
   }
 }

@@ -118,6 +118,11 @@ def _check(A, row, col, vals, x, N, ws, what):
     # looks those of others up, into the same stretch of LDS
     ("csr", "some empty", "scattered", "float64", 750_003, 7, False),
     ("csr", "some empty", "scattered", "float32", 1_500_007, 2, True),
+    # columns that do not lie scattered, segments in order: rows looked up and entered, a row of most segments
+    ("csr", "one row", "local", "float64", 750_003, 255, True),
+    ("csr", "one row", "local", "float32", 1_500_007, 0, False),
+    ("coo", "one row", "local", "float32", 1_500_007, 255, True),
+    ("coo", "some empty", "local", "float64", 750_003, 0, False),
     ("coo", "even", "scattered", "float64", 750_003, 0, True),
     ("coo", "heavy", "scattered", "float32", 1_500_007, 255, False),
     ("coo", "heavy", "local", "float64", 2_000_003, 2, False),

@@ -32,11 +32,15 @@ constexpr int kCus = 256;
 // CSR: does a block of kSkewRows rows hold more than 1 / kSkewShare of all entries? By rows, the kernel would end on
 // the workgroup of one long row (10^5 entries keep it busy for about 0.1 ms). COO: y = 0.
 // Both: do columns lie scattered? Each wave looks at a window of 256 entries: they do if they lie in 16 or more of
-// 64 equal parts of x (random columns in about 63, seven diagonals in at most 14). A window without a descending column
-// lies inside a row and tells nothing: a long row's columns ascend slowly, and yet each is another line.
+// 64 equal parts of x (random columns in about 63, seven diagonals in at most 14), and in parts of 4.4 MB or more, which no
+// L2 holds. (Columns anywhere in a third of x that moves on with the row, without / with slices, in us: 2.7 MB, fp32, 36M
+// entries, CSR 194 / 232, COO 228 / 260, 100M 557 / 589 and 599 / 696; 4 MB, fp32, 36M, 237 / 248 and 271 / 275; 4.8 MB, fp64,
+// 36M, 294 / 279 and 312 / 292; 5.3 MB, fp32, 60M, 445 / 427 and 487 / 468, fp64, 100M, 811 / 734 and 860 / 776.)
+// A window without a descending column lies inside a row and tells nothing: a long row's columns ascend slowly, and yet each is another line.
 constexpr int kSkewShare = 1536, kSkewRows = 256, kScattered = 16;
+constexpr int64_t kSpread = 4400000;
 template <typename T, bool CSR>
-__global__ __launch_bounds__(kSliceBlock) void slices_prepare_kernel(int nnz, int nrows, int ncols,
+__global__ __launch_bounds__(kSliceBlock) void slices_prepare_kernel(int nnz, int nrows, int ncols, int least_parts,
                                                                      const int32_t* __restrict__ pos,
                                                                      const int32_t* __restrict__ col, T* __restrict__ y,
                                                                      uint8_t* __restrict__ flags) {
@@ -80,7 +84,7 @@ __global__ __launch_bounds__(kSliceBlock) void slices_prepare_kernel(int nnz, in
     for (int d = 1; d < kWave; d <<= 1) in |= __shfl_xor(in, d);
     if (lane == 0 && tells) {
       atomicAdd(&s_tell, 1);
-      if (__popcll(in) >= kScattered) atomicAdd(&s_scattered, 1);
+      if (__popcll(in) >= least_parts) atomicAdd(&s_scattered, 1);
     }
   }
   __syncthreads();
@@ -433,14 +437,16 @@ template <typename T, bool CSR>
 spt_status launch_slices_prepare(int64_t nnz, int64_t nrows, int64_t ncols, const int32_t* pos, const int32_t* col, T* y,
                                  void* ws, hipStream_t s) {
   const SlicesWorkspace W(nnz, ws);
+  const int64_t x = ncols * (int64_t)sizeof(T);
+  const int least_parts = (int)std::max<int64_t>(kScattered, (64 * kSpread + x - 1) / x);
   hipLaunchKernelGGL((slices_prepare_kernel<T, CSR>), dim3(kChoiceFlags), dim3(kSliceBlock), 0, s, (int)nnz, (int)nrows,
-                     (int)ncols, pos, col, y, W.flags);
+                     (int)ncols, least_parts, pos, col, y, W.flags);
   SPT_CHECK_LAUNCH("slices prepare");
   return SPT_OK;
 }
 // Only whether a block of rows is heavy, CSR.
 spt_status launch_csr_skew(int64_t nnz, int64_t nrows, const int32_t* pos, uint8_t* flags, hipStream_t s) {
-  hipLaunchKernelGGL((slices_prepare_kernel<float, true>), dim3(kChoiceFlags), dim3(kSliceBlock), 0, s, (int)nnz, (int)nrows, 1,
+  hipLaunchKernelGGL((slices_prepare_kernel<float, true>), dim3(kChoiceFlags), dim3(kSliceBlock), 0, s, (int)nnz, (int)nrows, 1, 0,
                      pos, nullptr, nullptr, flags);
   SPT_CHECK_LAUNCH("csr skew");
   return SPT_OK;

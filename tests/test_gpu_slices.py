@@ -13,8 +13,10 @@ CSR_FROM, COO_FROM, SEGMENT = 1 << 25, (1 << 24) + 1, 256
 def _lengths(kind, N, nnz, g):
     """Row lengths that add up to nnz: runs of empty rows at both ends and (one segment's worth of them and more)
     in the middle; `heavy` adds rows of many segments (`declared`: and a bound on them), `one row` leaves nearly all
-    entries to one, `some empty` leaves a third of all rows without entries."""
+    entries to one, `some empty` leaves a third of all rows without entries. `level`: all rows alike."""
     import torch
+    if kind == "level":
+        return nnz // N + (torch.arange(N, device="cuda") < nnz % N).long()
     L = torch.randint(0, 2 * (nnz // N) + 2, (N,), generator=g, device="cuda")
     if kind == "one row":
         L = torch.randint(0, 2, (N,), generator=g, device="cuda")
@@ -50,6 +52,9 @@ def _matrix(form, kind, cols, N, M, nnz, dtype, misalign, seed):
     row = torch.repeat_interleave(torch.arange(N, device="cuda"), L)
     if cols == "scattered":
         col = torch.randint(0, M, (nnz,), generator=g, device="cuda")
+        col = (row * M + col).sort().values % M
+    elif cols == "third":  # anywhere in a third of x that moves on with the row
+        col = (row * M // N + torch.randint(0, M // 3, (nnz,), generator=g, device="cuda")) % M
         col = (row * M + col).sort().values % M
     else:
         col = (row * M // N + torch.randint(-60, 61, (nnz,), generator=g, device="cuda")).clamp_(0, M - 1)
@@ -184,3 +189,47 @@ def test_least_workspace_and_replayed_graph(form):
         assert torch.equal(y, eager)
         spt.spt_spmv(A, x, static, ws)
         assert torch.equal(static, eager)
+
+
+BY_ROWS, BY_ENTRIES, BY_SLICES = range(3)
+
+
+def _choice(ws):
+    """What the flags of the device's choice, the first 256 bytes of the workspace, amount to."""
+    f = ws[:256].cpu().numpy()
+    heavy, scattered, tells = ((f & bit) != 0 for bit in (1, 2, 4))
+    return BY_SLICES if 2 * scattered.sum() > tells.sum() else BY_ENTRIES if heavy.any() else BY_ROWS
+
+
+# What is chosen, and that it is done: rows cut by segments leave carries in the workspace, the row kernel does not touch
+# it. x of 8 MB: a third of it stays in an L2; of 24 MB: not. In a row of nearly all entries columns ascend, which tells nothing.
+@pytest.mark.parametrize("form,kind,cols,dtype,M,want", [
+    ("csr", "level", "local", "float64", 1_000_003, BY_ROWS),
+    ("csr", "level", "third", "float64", 1_000_003, BY_ROWS),
+    ("csr", "level", "third", "float32", 2_000_003, BY_ROWS),
+    ("csr", "heavy", "local", "float32", 2_000_003, BY_ENTRIES),
+    ("csr", "heavy", "third", "float32", 2_000_003, BY_ENTRIES),
+    ("csr", "level", "third", "float64", 3_000_001, BY_SLICES),
+    ("csr", "level", "scattered", "float32", 1_500_007, BY_SLICES),
+    ("csr", "heavy", "scattered", "float64", 16_000_000, BY_SLICES),
+    ("coo", "level", "local", "float32", 2_000_003, BY_ROWS),
+    ("coo", "level", "third", "float32", 2_000_003, BY_ROWS),
+    ("coo", "level", "scattered", "float64", 750_003, BY_SLICES),
+])
+def test_device_choice(form, kind, cols, dtype, M, want):
+    import torch
+    import paper_1804_10112_amd as spt
+    nnz, dt = (CSR_FROM if form == "csr" else COO_FROM) + 7, getattr(torch, dtype)
+    N = 1_200_007
+    A, keep, row, col, vals = _matrix(form, kind, cols, N, M, nnz, dt, False, 9)
+    x = torch.rand(M, device="cuda", dtype=dt)
+    y = torch.empty(N, device="cuda", dtype=dt)
+    ws = torch.full((spt.spt_workspace_bytes(spt.SPT_OP_SPMV, A),), 0x7F, dtype=torch.uint8, device="cuda")
+    spt.spt_spmv(A, x, y, ws)
+    assert _choice(ws) == want
+    segments = -(-nnz // SEGMENT)
+    carries = 256 + -(-4 * (segments + 1) // 256) * 256  # their rows, behind the flags and the first row of each segment
+    unused = (ws[carries:carries + 4 * segments].view(torch.int32) == 0x7F7F7F7F).all().item()
+    assert unused == (form == "csr" and want == BY_ROWS)
+    del A, keep, row, col, vals
+    torch.cuda.empty_cache()

@@ -1242,15 +1242,18 @@ static spt_status launch_seg(int64_t nnz, int64_t nrows, const int32_t* pos_or_r
 constexpr int64_t kDynamicMinEntries = int64_t(1) << 25;
 
 // x slice by slice (spmv_slices.hip)? Above, where the choice costs little next to the product; and for ordered COO
-// beyond kPiecesMaxEntries, where the one kernel does both (banded, 39M entries, against a kernel of chunks in LDS:
-// fp64 157 / 150 us, fp32 111 / 114). In us, uniform columns, without / with slices, by the size of x:
+// beyond kPiecesMaxEntries, where the one kernel does both (local columns, against a kernel of chunks in LDS: 25M entries,
+// fp64 113 / 104 us, fp32 73 / 72; 36M 147 / 148 and 101 / 106). In us, uniform columns, without / with slices, by the size of x:
 //   36M entries, fp64, COO   4 MB 257 / 257    6 MB 312 / 264    12 MB 493 / 281   24 MB 606 / 323   48 MB 701 / 404
 //                            64 MB 712 / 461   96 MB 770 / 581 (some 4 us more per MB: equal at about 150 MB)
 //   36M entries, CSR         fp32 6 MB 272 / 234, 24 MB 593 / 294; fp64 24 MB 597 / 317, 96 MB 795 / 600
 //   17M entries, COO         fp64 8 MB 200 / 138; fp32 6.4 MB 155 / 133
 //   power law, CSR           fp64, 60M entries, 32 MB 970 / 576; fp32, 35M entries, 9.2 MB 378 / 248
 //   local columns, CSR, 36M  a heavy row fp64 171 / 138, fp32 112 / 110; mean row 90 fp64 153 / 111, fp32 94 / 82;
-//                            a declared bound of 16, which spared the choice before, fp64 107 / 121, fp32 63 / 76
+// Not for rows whose declared bound sends them to the row kernel: they are spared the choice, which with local columns
+// costs more than it can be made to cost less (by rows at once / chosen; fp64, 36M entries, 12 a row, 117 / 133, 98M 286 / 318;
+// fp32 69 / 81 and 180 / 201; waves that go through the rows by themselves, the next ones on their way, 128, 317, 89 and
+// 224), though scattered columns then take 556 instead of 313 and 430 instead of 251: who has such declares no bound.
 // Takes a larger workspace than the carries of the kernels it replaces; a caller with one of that size has those.
 size_t slices_spmv_workspace(int64_t nnz);
 ByRowsIf slices_by_rows_if(int64_t nnz, void* ws);
@@ -1264,6 +1267,7 @@ spt_status launch_slices_spmv(int64_t nnz, int64_t ncols, bool rows_may, const i
 template <typename T>
 spt_status launch_segment_rows(int64_t nnz, int64_t nrows, const int32_t* pos, T* y, void* ws, hipStream_t s);
 
+static bool declared_short(int hint) { return hint > 0 && hint <= kShortRow; }
 static bool slices_may_pay(bool csr, int64_t nnz, int64_t ncols, int value_bytes) {
   const int64_t x = ncols * value_bytes;
   return nnz >= (csr ? kDynamicMinEntries : kPiecesMaxEntries + 1) && nnz + (1 << 16) < INT32_MAX && x > kSlicesMinX && x <= kSlicesMaxX;
@@ -1271,7 +1275,8 @@ static bool slices_may_pay(bool csr, int64_t nnz, int64_t ncols, int value_bytes
 // What spt_workspace_bytes answers; the least that a call takes is seg_spmv_workspace and ordered_coo_workspace.
 size_t csr_spmv_workspace(const spt_tensor* A) {
   const size_t least = seg_spmv_workspace(A->nvals);
-  return slices_may_pay(true, A->nvals, A->level[1].N, A->dtype == SPT_F64 ? 8 : 4) ? std::max(least, slices_spmv_workspace(A->nvals)) : least;
+  return !declared_short(A->level[1].max_children) && slices_may_pay(true, A->nvals, A->level[1].N, A->dtype == SPT_F64 ? 8 : 4)
+             ? std::max(least, slices_spmv_workspace(A->nvals)) : least;
 }
 size_t ordered_coo_spmv_workspace(const spt_tensor* A) {
   const size_t least = ordered_coo_workspace(A->nvals);
@@ -1372,7 +1377,7 @@ static spt_status spmv_typed(Format f, const spt_tensor* A, const T* x, T* y, vo
       const int32_t *pos = A->level[1].pos, *crd = A->level[1].crd;
       const int64_t M = A->level[1].N;
       const bool rows = csr_use_rows(nnz, N, hint, ws, ws_bytes);
-      if (slices_may_pay(true, nnz, M, sizeof(T)) && ws && ws_bytes >= slices_spmv_workspace(nnz) && N + kBlock < INT32_MAX) {
+      if (!declared_short(hint) && slices_may_pay(true, nnz, M, sizeof(T)) && ws && ws_bytes >= slices_spmv_workspace(nnz) && N + kBlock < INT32_MAX) {
         const ByRowsIf cond = slices_by_rows_if(nnz, ws);
         spt_status st = launch_slices_prepare<T, true>(nnz, N, M, pos, crd, y, ws, s);
         if (st == SPT_OK)

@@ -233,3 +233,25 @@ def test_device_choice(form, kind, cols, dtype, M, want):
     assert unused == (form == "csr" and want == BY_ROWS)
     del A, keep, row, col, vals
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("dtype", ["float64", "float32"])
+def test_declared_short_rows_are_spared_the_choice(dtype):
+    """No look at the columns, no flags or carries, whatever workspace is handed over; the same sums."""
+    import torch
+    import paper_1804_10112_amd as spt
+    nnz, N, M, dt = CSR_FROM + 7, 1_200_007, 2_000_003, getattr(torch, dtype)
+    A, keep, row, col, vals = _matrix("csr", "level", "local", N, M, nnz, dt, False, 9)
+    ws = torch.full((spt.spt_workspace_bytes(spt.SPT_OP_SPMV, A),), 0x7F, dtype=torch.uint8, device="cuda")
+    A.c.level[1].max_children = nnz // N + 1
+    assert spt.spt_workspace_bytes(spt.SPT_OP_SPMV, A) < ws.numel()
+    x = torch.rand(M, device="cuda", dtype=dt)
+    y = torch.full((N,), float("nan"), device="cuda", dtype=dt)
+    spt.spt_spmv(A, x, y, ws)
+    assert (ws == 0x7F).all().item()
+    A.c.level[1].max_children = 0
+    chosen = torch.full_like(y, float("nan"))
+    spt.spt_spmv(A, x, chosen, ws)
+    assert _choice(ws) == BY_ROWS and torch.equal(y, chosen)
+    del A, keep, row, col, vals
+    torch.cuda.empty_cache()

@@ -1024,9 +1024,22 @@ __global__ __launch_bounds__(kSel) void select_finish_kernel(const RcSource src,
     if (u < w) at += s_sum[u];
     cnt += s_sum[u];
   }
+  // a lane puts those of its words in place; the wave together, where few lanes have many: input in order has them in a
+  // few words (20 000 records 13.4 us, 16.6 with a lane for all of its own)
+  constexpr int kFewPicked = 10, kFewLanes = 8;
+  static_assert(kWords * 32 == kWave, "");
+  const uint64_t many = __ballot(own > kFewPicked);
+  const bool together = __popcll(many) <= kFewLanes;
+  for (uint64_t todo = together ? many : 0; todo; todo &= todo - 1) {
+    const int from = __ffsll(static_cast<long long>(todo)) - 1;
+    const uint64_t bits = static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(picked[1]), from))) << 32 |
+                          static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(picked[0]), from));
+    const int place = __builtin_amdgcn_readlane(at, from) + __popcll(bits & ((uint64_t{1} << lane) - 1));
+    if ((bits >> lane & 1) && place < kCap) s_at[place] = (w * kWave + from) * kWave + lane;
+  }
 #pragma unroll
   for (int q = 0; q < kWords; ++q) {
-    for (uint32_t m = picked[q]; m; m &= m - 1, ++at)
+    for (uint32_t m = together && own > kFewPicked ? 0 : picked[q]; m; m &= m - 1, ++at)
       if (at < kCap) s_at[at] = (tid * kWords + q) * 32 + __ffs(static_cast<int>(m)) - 1;
   }
   __syncthreads();

@@ -10,6 +10,15 @@ SELECT, SMALL, ONE, LARGE = 64 * 1024, 128 * 1024, 256 * 1408, 11 << 18  # one l
 
 
 @pytest.mark.parametrize("keys,by_col,n,dtype", [
+    # one launch: the picked records lie in a few words of a bit set (input in order), or in all of them
+    ("sorted", True, 385, "float64"),
+    ("random", True, 769, "float32"),
+    ("random", False, 3000, "float64"),
+    ("sorted", False, 20_000, "float32"),
+    ("equal", True, 33_001, "float64"),
+    ("skewed", True, 50_021, "float32"),
+    ("sorted", True, SELECT, "float64"),
+    ("random", True, SELECT, "float64"),
     ("random", True, SELECT + 1, "float64"),
     ("random", False, SMALL, "float32"),
     ("random", True, SMALL + 1, "float64"),

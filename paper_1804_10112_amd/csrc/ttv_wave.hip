@@ -554,9 +554,18 @@ static int compute_units() {
 }
 
 // COO tensors of up to 1.5M entries leave c in global memory, since staging it in every compute unit costs
-// 8 us, and add up the pieces' counts themselves, since making offsets of them is a launch of its own (us so / as
-// beyond: 400 000 entries 12 / 14, 1.2M 19 / 23, 1.6M 20.5 / 20.1, 2M fp64 in short fibres 32 / 31, 3M skewed 30 / 27;
-// where c stays in global memory in any case, up to 3M: 2.2M, c of 90 000, fp64 31.8 / 32.8).
+// 8 us, and add up the pieces' counts themselves, since making offsets of them is a launch of its own; up to 2.75M where
+// most of the gathers would go past the staged part of c anyway, fp64 with a c of more than 1.5 times that; up to 3M where
+// nothing of c is staged (2.2M, c of 90 000, fp64 31.8 / 32.8). In us, so / as beyond (400 000 entries 12 / 14, 1.2M 19 / 23):
+//   entries, c                        1.6M         2M           2.5M         3M
+//   fp32, 30 000, skewed              20.0 / 18.7  23.0 / 18.8  27.4 / 23.8  31.1 / 24.4
+//   fp32, 60 000, every one a fibre   24.7 / 25.8  29.1 / 28.0  35.7 / 39.1  41.7 / 40.8
+//   fp64, 20 000, skewed              21.1 / 20.6  23.8 / 21.5  28.8 / 27.1  33.0 / 27.8
+//     "           every one a fibre   27.3 / 27.8  30.8 / 29.3  37.1 / 38.4  42.4 / 39.7
+//   fp64, 30 000, skewed              22.5 / 24.4  25.6 / 24.9  30.8 / 31.8  35.4 / 32.5
+//     "           every one a fibre   28.4 / 30.5  32.8 / 33.3  39.5 / 43.1  45.5 / 45.1
+//   fp64, 60 000, skewed              24.5 / 27.3  28.0 / 28.6  33.5 / 37.4  38.6 / 38.9
+//     "           every one a fibre   28.8 / 33.3  33.6 / 35.5  40.9 / 47.3  47.3 / 48.9
 constexpr int kSelfPieces = 6144;
 
 static int64_t pieces_of(int64_t nnz) { return (nnz + kPiece - 1) / kPiece; }
@@ -593,7 +602,8 @@ spt_status ttv_coo(int64_t nnz64, int64_t K, const int32_t* ci, const int32_t* c
     return fail(SPT_ERR_WORKSPACE, "ttv: workspace of %zu bytes needed, %zu given", ttv_coo_workspace(nnz64), ws_bytes);
   Workspace W(ws, ws_bytes);
   const bool wave = ttv_wave_applies(nnz64, K, sizeof(T) == 8 ? SPT_F64 : SPT_F32);
-  const bool self = np <= (wave ? kSelfPieces : 2 * kSelfPieces);
+  const bool past = sizeof(T) == 8 && K * 2 * static_cast<int64_t>(sizeof(T)) > 3 * kCooCacheBytes;
+  const bool self = np <= (!wave ? 2 * kSelfPieces : past ? kSelfPieces / 4 * 7 : kSelfPieces);
   const int log_group = np >= kManyPieces ? kLogGroupMany : kLogGroup;
   const unsigned groups = (unsigned)(((np - 1) >> log_group) + 1);
   int32_t* group_off = W.take<int32_t>(groups);

@@ -1,5 +1,5 @@
 """COO tensor times vector where the offsets of the results come from groups of pieces: entry counts at the edges of
-pieces (256 entries), groups (16 and 32 pieces) and of the rules (6144 pieces, 12288 where c is too long to be held; 98304). Built on the
+pieces (256 entries), groups (16 and 32 pieces) and of the rules (6144 pieces, 10752 and 12288 where little or nothing of c is held; 98304). Built on the
 GPU; the reference is the definition, its products and sums in float64."""
 import numpy as np
 import pytest
@@ -12,7 +12,10 @@ FROM, PIECE = 6144 * 256, 256
 @pytest.mark.parametrize("fibres,K,nnz,dtype,misalign", [
     ("short", 9000, FROM, "float32", False),
     ("short", 9000, FROM + 1, "float32", False),
+    ("mixed", 25_000, FROM + PIECE, "float64", True),
     ("mixed", 40_000, FROM + PIECE, "float64", True),
+    ("short", 40_000, FROM // 4 * 7, "float64", False),
+    ("mixed", 40_000, FROM // 4 * 7 + 1, "float64", True),
     ("mixed", 9000, FROM + 15 * PIECE + 3, "float64", False),
     ("one", 9000, FROM + 16 * PIECE, "float32", False),
     ("each", 50_000, FROM + 17 * PIECE - 1, "float32", True),

@@ -265,7 +265,8 @@ def test_large_unhinted_csr_picks_its_kernel_on_the_device(heavy_row):
     N = M = 2_100_000
     K = 16
     rng = np.random.default_rng(90 + (heavy_row > 0))
-    cols = (rng.integers(0, M, N, dtype=np.int64)[:, None] + np.arange(K, dtype=np.int64)[None, :] * 131_071) % M
+    # near the diagonal: columns anywhere in an x of 8 MB would be gathered slice by slice, whatever the rows
+    cols = (np.arange(N, dtype=np.int64)[:, None] + rng.integers(0, 7, (N, K)) + np.arange(K, dtype=np.int64)[None, :] * 7) % M
     cols.sort(axis=1)
     lens = np.full(N, K, dtype=np.int64)
     crd = cols.reshape(-1)

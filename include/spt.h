@@ -111,7 +111,10 @@ typedef enum {
  *          mean row decides: the first up to 32 entries (64 for up to 2^17 entries in all);
  *          from 2^25 stored entries on, a kernel then looks at the entry counts of the
  *          256-row blocks, and the entry-balanced loop runs if one block holds more than
- *          1/1536 of all entries. A bound that the data violates costs time, not correctness.
+ *          1/1536 of all entries. Where x takes 6 to 128 MB it also looks at samples of the
+ *          columns, and a third loop, which gathers x a few MB at a time, runs if they lie
+ *          scattered; a declared bound <= 32 is taken at its word and spares the look, a
+ *          larger one does not. A bound that the data violates costs time, not correctness.
  *   crd_stride  elements of crd between the coordinates of consecutive positions: 0 or 1 =
  *          contiguous (struct of arrays). A larger stride describes the array-of-structs
  *          variant of Section 5.2, where one interleaved array holds the coordinates of each
@@ -183,7 +186,7 @@ typedef struct {
  * spt_workspace_bytes(SPT_OP_SPMV, ...)). CSC has its columns written out of pos into the
  * workspace and its entries binned by row like an unordered COO; an array-of-structs COO
  * matrix (crd_stride = 2 on both levels) has its pairs split into the workspace and then runs
- * as COO. Both need the workspace the query returns. Any other composition of levels that stores a
+ * as COO. Any other composition of levels that stores a
  * matrix (dense, hashed rows or columns, DCSR with repeated row coordinates, ...) is
  * evaluated by reading the level functions of Table 2 per stored value, again with
  * floating-point atomics; it needs no workspace.
@@ -192,22 +195,32 @@ typedef struct {
  * (deterministic, workspace from spt_workspace_bytes(SPT_OP_SPMV, ...)); BCSR with larger
  * blocks and every other 4-level composition of a blocked matrix (e.g. CSB = dense, dense,
  * compressed non-unique, singleton) are read per stored value like any other composition.
+ * Workspace: what spt_workspace_bytes(SPT_OP_SPMV, ...) returns suits the fastest kernel. Where
+ * x takes 6 to 128 MB, CSR of 2^25 entries or more and ordered COO of more than 2^24 accept
+ * less: from 12 bytes per 2048 entries on (each of 4 and 8 bytes rounded up to 256, and 256
+ * more) another kernel runs, slower if the columns lie scattered and with the sums rounded in
+ * another order. CSC and unordered COO of fewer than 786 432 entries need what CSC writes its
+ * columns to (4 bytes an entry, rounded up to 256) and nothing. CSR without a declared bound
+ * and of fewer than 2^25 entries also runs without any. The same operand and workspace size
+ * always give the same bits, other than with atomics.
  */
 spt_status spt_spmv(const spt_tensor* A, const void* x, void* y, void* ws,
                     size_t ws_bytes, void* stream);
 
 /*
  * spt_spmv for callers that cannot allocate or hand over a workspace: code under HIP graph
- * capture, tight serving loops, harnesses that forbid hipMalloc. Same operands, result and
- * errors as spt_spmv; the scratch memory comes from a fixed array of
- * SPT_STATIC_SCRATCH_BYTES in device memory that belongs to the library's code object (every
- * GPU the library runs on holds its own copy until the process ends). The call allocates
- * nothing and frees nothing. An operand whose spt_workspace_bytes(SPT_OP_SPMV, ...) exceeds
- * SPT_STATIC_SCRATCH_BYTES is refused with SPT_ERR_WORKSPACE (CSR, ordered COO, DIA, ELL of
- * any size fit; the binned scatter of a large unordered COO does not). The array's address
- * is looked up on the first call on each device, so make that first call outside a graph
- * capture. All calls on one GPU share the array: calls that overlap in time on one GPU
- * (different streams, or threads) race; calls on one stream are ordered and safe.
+ * capture, tight serving loops, harnesses that forbid hipMalloc. Same operands and errors as
+ * spt_spmv, and the result of spt_spmv with a workspace of SPT_STATIC_SCRATCH_BYTES; the
+ * scratch memory comes from a fixed array of that size in device memory that belongs to the
+ * library's code object (every GPU the library runs on holds its own copy until the process
+ * ends). The call allocates nothing and frees nothing. An operand is refused with
+ * SPT_ERR_WORKSPACE if the least workspace that spt_spmv accepts for it exceeds the array (CSR,
+ * ordered COO, DIA, ELL of any size fit; the binned scatter of a large unordered COO does not).
+ * Where only the least fits, spt_spmv with the workspace of the query runs another kernel: CSR
+ * and ordered COO with an x of 6 to 128 MB, from some 67M entries on. The array's address is
+ * looked up on the first call on each device, so make that first call outside a graph capture.
+ * All calls on one GPU share the array: calls that overlap in time on one GPU (different
+ * streams, or threads) race; calls on one stream are ordered and safe.
  */
 #define SPT_STATIC_SCRATCH_BYTES ((size_t)4 << 20)
 spt_status spt_spmv_static(const spt_tensor* A, const void* x, void* y, void* stream);

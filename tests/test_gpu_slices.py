@@ -255,3 +255,26 @@ def test_declared_short_rows_are_spared_the_choice(dtype):
     assert _choice(ws) == BY_ROWS and torch.equal(y, chosen)
     del A, keep, row, col, vals
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("form", ["csr", "coo"])
+def test_beyond_the_static_scratch(form):
+    """Where the library's own scratch memory no longer holds what the slices take, the call without a workspace runs
+    the kernel that does with less, as spt_spmv does with a workspace of that size."""
+    import torch
+    import paper_1804_10112_amd as spt
+    nnz = (spt.SPT_STATIC_SCRATCH_BYTES // 16 + 1) * SEGMENT
+    N, M = 2_400_007, 1_000_003
+    A, keep, row, col, vals = _matrix(form, "level", "scattered", N, M, nnz, torch.float64, False, 8)
+    query = spt.spt_workspace_bytes(spt.SPT_OP_SPMV, A)
+    assert query > spt.SPT_STATIC_SCRATCH_BYTES
+    x = torch.rand(M, device="cuda", dtype=torch.float64)
+    y, least = (torch.full((N,), float("nan"), device="cuda", dtype=torch.float64) for _ in range(2))
+    spt.spt_spmv_static(A, x, y)
+    ref, mag = _reference(row, col, vals, x, N)
+    assert_close_where_finite(y.cpu().numpy(), ref, mag, np.float64, f"{form}, static")
+    spt.spt_spmv(A, x, least, torch.empty(spt.SPT_STATIC_SCRATCH_BYTES, dtype=torch.uint8, device="cuda"))
+    assert torch.equal(least, y)
+    _check(A, row, col, vals, x, N, torch.empty(query, dtype=torch.uint8, device="cuda"), f"{form}, workspace of the query")
+    del A, keep, row, col, vals
+    torch.cuda.empty_cache()

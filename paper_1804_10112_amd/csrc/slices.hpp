@@ -56,13 +56,14 @@ __device__ __forceinline__ void find_segment_rows(int nrows, const int32_t* __re
 // Written out because of what the compiler makes of the same loop: a load under a mask into a register that
 // holds something goes through a copy and a wait, and 32 of them spill (1.2 to 1.9 ms for what takes 0.5 here).
 // A load no lane needs is jumped over: it would keep the address unit busy for some 20 clocks.
+// What is written while offsets are still to be read is marked so (&): no operand may share its register.
 template <typename T, int N>
 struct SliceGather;
 
 #define SPT_EACH10(M, A) M(A##0) M(A##1) M(A##2) M(A##3) M(A##4) M(A##5) M(A##6) M(A##7) M(A##8) M(A##9)
 #define SPT_ONE_TO_NINE(M) M(1) M(2) M(3) M(4) M(5) M(6) M(7) M(8) M(9)
 #define SPT_EACH32(M) M(0) SPT_ONE_TO_NINE(M) SPT_EACH10(M, 1) SPT_EACH10(M, 2) M(30) M(31)
-#define SPT_GATHER_RESULT(K) [g##K] "+v"(got[K]),
+#define SPT_GATHER_RESULT(K) [g##K] "+&v"(got[K]),
 #define SPT_GATHER_OFFSET(K) [a##K] "v"(at[K]),
 #define SPT_GATHER_LOAD(WIDTH, K)                  \
   "s_mov_b64 exec, %[all]\n\t"                     \
@@ -90,7 +91,7 @@ struct SliceGather;
                    "s_cmp_lg_u32 %[n], 0\n\t"                                                                     \
                    "s_cbranch_scc1 0b\n\t"                                                                        \
                    "s_waitcnt vmcnt(0)"                                                                           \
-                   : SPT_EACH##N(SPT_GATHER_RESULT)[n] "+s"(n), [lo] "=&s"(lo), [all] "=&s"(all), [rel] "=&v"(rel) \
+                   : SPT_EACH##N(SPT_GATHER_RESULT)[n] "+&s"(n), [lo] "=&s"(lo), [all] "=&s"(all), [rel] "=&v"(rel) \
                    : SPT_EACH##N(SPT_GATHER_OFFSET)[bytes] "s"(bytes), [x] "s"(x)                                 \
                    : "vcc", "scc", "memory");                                                                     \
     }                                                                                                             \

@@ -15,7 +15,7 @@
 // instead of 521 with a D that fits L2; same sums, bit for bit). Chunks go to the
 // XCDs in turn: with one contiguous part of a skewed tensor to each, the XCD with its last slices fetched twice as
 // many lines as the others and took 960 us (738 000 entries in CSF, J = 16, fp64: 41 -> 38; 15M entries, J = 32,
-// fp64, 703 -> 555; runs of 4 or 16 chunks the same). Left out after measuring: C read past the caches (small tensors
+// fp64, 703 -> 555; runs of 4 or 16 chunks the same; even tensors of 0.4 to 0.9M entries lose 3 %, 22.2 -> 22.9). Left out after measuring: C read past the caches (small tensors
 // take up to a third longer); half of D to every other XCD, each going through all entries (743 us: the streams are
 // read twice); chunks of twice the entries (1 % faster, fp64 CSF 2 % slower); six waves a SIMD (spills, 815). Before that: more or
 // fewer waves and the next rows loaded ahead change nothing; 32 lanes of one column per

@@ -19,7 +19,8 @@
 // as carry number `piece` and is added afterwards (carry_fixup_kernel), in a fixed order:
 // results are bit-reproducible.
 // Measured on 50M entries in 8.1M fibres, fp32, c of 50 000 values (78 % / 61 % of it cached):
-// COO 231 us in all (count of the heads 41, their offsets 5, this kernel 182), CSF 157 us (workgroups of 2048 entries
+// COO 229 us in all, call after call on the same operands (count of the heads 40, their offsets 5, this kernel 185, carries
+// 5; 248 us where operands change from call to call), CSF 157 us (workgroups of 2048 entries
 // with c in global memory: 324 and 357 us). Left out
 // after measuring: eight entries per lane (a lane's two 16-byte loads then lie 32 bytes apart:
 // 263 / 174 us, against 214 / 158 then), four pieces in flight instead of two or the next two loaded ahead (no change), results
@@ -183,7 +184,8 @@ __device__ __forceinline__ void wave_fibre_sums(const T (&p)[kEPL], unsigned hea
 // piece_off[piece] = (i, j) fibre starts in the pieces before among the workgroup's, group_off[workgroup] = in all of
 // them. Bound by reading i and j; i is ordered, so where it is the same before and at the end of a piece
 // it need not be read. A wave has the loads of its pieces in flight together: four, of many entries eight (whole call,
-// fp32, with four / eight: 12M entries 57 / 59 us, 24M 123 / 123, 50M 241 / 231 (this kernel 52 / 41); 16: 62, 130, 245).
+// fp32, with four / eight: 12M entries 57 / 59 us, 24M 127 / 127, 26M 133 / 134, 50M 238 / 229 (this kernel 52 / 40), 50M of
+// one entry to a fibre 501 / 494; 16: 62, 130 and, 50M, 245).
 // SELF (few pieces): one piece for a wave, piece_off[piece] = the starts in it.
 constexpr int kLogGroup = 4, kLogGroupMany = 5, kManyPieces = 96 * 1024;
 template <bool VEC, bool SELF, int LOG_GROUP>

@@ -21,7 +21,10 @@ static __device__ __forceinline__ void store_pos_range(int32_t* __restrict__ pos
     const int src = __ffsll(static_cast<long long>(todo)) - 1;
     todo &= todo - 1;
     const int l = __shfl(lo, src), h = __shfl(hi, src), v = __shfl(val, src);
-    for (int r = l + 1 + lane_id(); r <= h; r += kWave) pos[r] = v;
+    typedef int32_t I4 __attribute__((ext_vector_type(4), aligned(4)));
+    int r = l + 1;
+    for (; r + 4 * kWave <= h + 1; r += 4 * kWave) *reinterpret_cast<I4*>(pos + r + lane_id() * 4) = I4(v);
+    for (r += lane_id(); r <= h; r += kWave) pos[r] = v;
   }
 }
 template <bool VEC>

@@ -13,7 +13,9 @@
 //   beyond                            two stable partitions, then one workgroup per bucket.
 // A partition is count -> exclusive scan -> stable scatter, as a radix pass, with the digit found
 // by bisection among the splitters instead of taken from the key bits. The count kernel notes
-// each record's digit in one byte for the scatter.
+// each record's digit in one byte for the scatter. The second partition leaves records, key and value
+// side by side, whose keys count from their bucket's lower bound: 32 bits, except in segments with a bucket
+// that spans more (the segment's splitters tell; its records then keep 64).
 // Equal keys: splitters are (key, position) pairs, so that even a million copies of one
 // coordinate spread over the buckets, and inside a bucket records carry their number in input
 // order: the result is that of a stable sort.
@@ -26,14 +28,19 @@
 // counted, 60M records took 10.4 instead of 1.8 ms).
 //
 // Measured against the six radix passes it replaces (fp64): 60M records with power-law rows
-// 3.09 -> 1.67 ms (splitters 17 + 70 us, classify 2 x 135, offsets 8 + 10, partitions 403 + 430,
-// finish 476); 5M records 0.21 ms, 250 000 54 us, 50 000 171 -> 20 us. The partitions write 256 x 2 interleaved streams
+// 3.09 -> 1.58 ms (splitters 19 + 70 us, classify 2 x 133, offsets 8 + 9, partitions 405 + 352, finish 464; with whole
+// keys and separate arrays in the second partition 418 and 476); 20M 570 -> 546 us by that, 5M 0.19 ms, 250 000 52 us,
+// 50 000 171 -> 19 us. The partitions write 256 interleaved streams for each array
 // and are bound by how the memory system takes them: it is the bytes in flight that count. Two workgroups of 512 threads
-// on a compute unit: 60M records fp64 1.70 ms in all (before splitters and offsets were made as now), three 1.83, three
+// on a compute unit: 60M records fp64 1.70 ms in all (before splitters, offsets and records were made as now), three 1.83, three
 // of 256 threads 1.87, two 1.68; 20M 0.62, 0.63, 0.64 and 0.65; fp32, 40M 1.01, 1.04, 1.03 and 1.06. Tiles of 6144 and
-// 8192: up to 4 and 8 % longer for fp64, 3 % shorter for fp32 of 40M. The
-// classification and the finishing kernel are bound by vector instructions (80 and 70 % of the time).
+// 8192: up to 4 and 8 % longer for fp64, 3 % shorter for fp32 of 40M. Fewer vector instructions for the ranks do not change
+// large partitions (+-1 %) and take 1 to 2 % off all below 6M records. The
+// classification has vector ALU, LDS and memory busy half of the time each (four records to a lane in loads of 16 bytes,
+// two or four bisections side by side: within 1 %; a table of equal cells in place of the upper steps: 14 % longer where
+// long rows crowd the cells), the finishing kernel is bound by vector instructions (70 % of the time).
 #include <algorithm>
+#include <type_traits>
 
 #include "blocksort.hpp"
 #include "common.hpp"
@@ -117,6 +124,78 @@ struct KSource {
   __device__ __forceinline__ uint64_t key_near(int p, const KeyForm&) const { return __builtin_nontemporal_load(&at32(k, p)); }
 };
 
+// Key and value side by side, as the second partition leaves them: KT = uint64_t, the key K; or uint32_t, K - base, where
+// 32 bits hold that for every bucket of a segment (a third of the record and the wide arithmetic of the last sort less).
+template <typename KT, typename VT>
+struct Record {
+  static constexpr int kWords = (sizeof(KT) + sizeof(VT)) / 4;
+  uint32_t w[kWords];
+  __device__ __forceinline__ static Record of(KT k, VT v) {
+    Record r;
+    __builtin_memcpy(r.w, &k, sizeof(KT));
+    __builtin_memcpy(r.w + sizeof(KT) / 4, &v, sizeof(VT));
+    return r;
+  }
+  __device__ __forceinline__ KT key() const {
+    KT k;
+    __builtin_memcpy(&k, w, sizeof(KT));
+    return k;
+  }
+  __device__ __forceinline__ VT val() const {
+    VT v;
+    __builtin_memcpy(&v, w + sizeof(KT) / 4, sizeof(VT));
+    return v;
+  }
+};
+// A bucket's records before the last sort, from its first one on: `rel` is what the sort compares, K - base of the record
+// or its row alone.
+template <typename VT_>
+struct ArraysBucket {
+  typedef VT_ VT;
+  typedef uint64_t KT;
+  const uint64_t* __restrict__ k;
+  const VT* __restrict__ v;
+  uint64_t base;  // of the order's keys
+  int kshift;
+  __device__ __forceinline__ void load(int p, KT& key, VT& val) const {
+    key = at32(k, p);
+    val = at32(v, p);
+  }
+  __device__ __forceinline__ KT key(int p) const { return at32(k, p); }
+  __device__ __forceinline__ VT val(int p) const { return at32(v, p); }
+  __device__ __forceinline__ KT rel(KT key) const { return (key >> kshift) - base; }
+  __device__ __forceinline__ uint64_t whole(KT key) const { return key; }
+};
+template <typename KT_, typename VT_>
+struct RecordBucket {
+  typedef VT_ VT;
+  typedef KT_ KT;
+  const Record<KT, VT>* __restrict__ r;
+  uint64_t base;  // of the order's keys
+  int kshift;
+  __device__ __forceinline__ void load(int p, KT& key, VT& val) const {
+    const Record<KT, VT> x = at32(r, p);
+    key = x.key();
+    val = x.val();
+  }
+  __device__ __forceinline__ KT key(int p) const { return at32(r, p).key(); }
+  __device__ __forceinline__ VT val(int p) const { return at32(r, p).val(); }
+  __device__ __forceinline__ KT rel(KT key) const {
+    return sizeof(KT) == 4 ? key >> kshift : static_cast<KT>((key >> kshift) - base);
+  }
+  __device__ __forceinline__ uint64_t whole(KT key) const { return sizeof(KT) == 4 ? (base << kshift) + key : key; }
+};
+// The records of the segment that begins at record `begin`, in the room of as many of the wide form.
+template <typename VT, typename P>
+__device__ __forceinline__ auto segment_records(P* records, int begin) {
+  typedef std::conditional_t<std::is_const_v<P>, const char, char> C;
+  return static_cast<C*>(records) + static_cast<int64_t>(begin) * (sizeof(uint64_t) + sizeof(VT));
+}
+// Do 32 bits hold K - (lo << kshift) of every record between two cuts?
+__device__ __forceinline__ bool narrow_keys(uint64_t lo, uint64_t hi, const KeyForm& f) {
+  return hi - lo < (uint64_t{1} << 32 >> f.kshift);
+}
+
 // A cut of the order: everything from (key, pos) on.
 struct Cut {
   uint64_t key;
@@ -162,11 +241,10 @@ __device__ __forceinline__ bool crowded(const uint32_t (&v)[E], int n) {
   }
 }
 
-// Orders n records (numbered as in the input) by key.
-// A record travels through the sort as one 32-bit word: 20 bits of its key's place between the
-// bounds `base` and `base` + 2^(20 + shift), 12 bits of its number in input order. Where that many
-// bits do not tell two neighbours apart, a record counts the keys of its stretch that come before
-// it (`key_at` gives the whole key of a record). Stretches are two or three records long where columns are
+// Orders n records (numbered as in the input) by key. rel_at gives a record's key less a lower bound of all, below 2^(20 + shift).
+// A record travels through the sort as one 32-bit word: the upper 20 bits of that and 12 bits of its number in input
+// order. Where that many bits do not tell two neighbours apart, a record counts the keys of its stretch that come before
+// it. Stretches are two or three records long where columns are
 // anywhere, but as long as a row where they are neighbours in a wide matrix: once one of them has kCrowd
 // records, all are sorted again, by 20 bits at a time from the lowest on. (30M records, counted / sorted
 // again: rows of 20 neighbours in 2M columns 1374 / 1098 us, of 30 1603 / 1099, of 1000 in 2^31 columns
@@ -179,8 +257,7 @@ __device__ __forceinline__ bool crowded(const uint32_t (&v)[E], int n) {
 // in one bucket crowd the bins).
 // words: NT * E words of LDS; ord: n half-words, the records in order.
 template <int NT, int E, class KA>
-__device__ __forceinline__ void sort_records(uint32_t* words, uint16_t* ord, int n, uint64_t base, int shift,
-                                             const KA& key_at) {
+__device__ __forceinline__ void sort_records(uint32_t* words, uint16_t* ord, int n, int shift, const KA& rel_at) {
   __shared__ int s_crowded;
   constexpr uint32_t kLi = (1 << kLiBits) - 1;
   constexpr int kKeyBits = 32 - kLiBits;
@@ -190,7 +267,7 @@ __device__ __forceinline__ void sort_records(uint32_t* words, uint16_t* ord, int
   for (int e = 0; e < E; ++e) {
     const int li = e * NT + tid;
     v[e] = ~0u;
-    if (li < n) v[e] = (static_cast<uint32_t>((key_at(li) - base) >> shift) << kLiBits) | li;
+    if (li < n) v[e] = (static_cast<uint32_t>(rel_at(li) >> shift) << kLiBits) | li;
   }
   if (tid == 0) s_crowded = 0;
   block_sort_regs<NT, E>(v, words);
@@ -202,7 +279,7 @@ __device__ __forceinline__ void sort_records(uint32_t* words, uint16_t* ord, int
       for (int e = 0; e < E; ++e) {
         const int i = e * NT + tid;
         v[e] = ~0u;
-        if (i < n) v[e] = static_cast<uint32_t>((key_at(low ? ord[i] : i) - base) >> low) << kLiBits | i;
+        if (i < n) v[e] = static_cast<uint32_t>(rel_at(low ? ord[i] : i) >> low) << kLiBits | i;
       }
       block_sort_regs<NT, E>(v, words);
       block_sort_store<NT, E>(v, words);
@@ -229,13 +306,13 @@ __device__ __forceinline__ void sort_records(uint32_t* words, uint16_t* ord, int
       const int li = w & kLi;
       int at = i;
       if (shift > 0 && ((i > 0 && words[i - 1] >> kLiBits == q) || (i + 1 < n && words[i + 1] >> kLiBits == q))) {
-        const uint64_t key = key_at(li);
+        const auto key = rel_at(li);
         int g = i;
         while (g > 0 && words[g - 1] >> kLiBits == q) --g;
         at = g;
         for (; g < n && words[g] >> kLiBits == q; ++g) {
           const int other = words[g] & kLi;
-          const uint64_t k = key_at(other);
+          const auto k = rel_at(other);
           at += (k < key || (k == key && other < li)) ? 1 : 0;
         }
       }
@@ -298,7 +375,7 @@ __device__ __forceinline__ int bucket_start(int count, int* s_sum) {
 
 // Level 2: sorts S = 1024 * E sampled keys of segment blockIdx.x, a bucket of level 1 (of total1[] records each), and
 // takes every (S / nb)th as a splitter; nb follows from the segment's size. The workgroup also fills in its rows of the
-// segment tables.
+// segment tables, and says in place of a position of splitter 0, which there is none of, whether the segment's records are narrow.
 template <int E>
 __global__ __launch_bounds__(1024) void splitters_kernel(const KSource src, const KeyForm f, int nrows, int group, int tile,
                                                          const int32_t* __restrict__ total1, int nseg,
@@ -309,9 +386,10 @@ __global__ __launch_bounds__(1024) void splitters_kernel(const KSource src, cons
   __shared__ uint64_t s_key[S];
   __shared__ __attribute__((aligned(16))) uint32_t words[S];
   __shared__ uint16_t ord[S];
-  __shared__ int s_sum[4], s_begin;
+  __shared__ int s_sum[4], s_begin, s_wide;
   const int tid = threadIdx.x;
   const int seg = blockIdx.x;
+  if (tid == 0) s_wide = 0;
   if (tid < 3) s_sum[tid] = 0;
   if (tid == 0) s_begin = 0;
   __syncthreads();
@@ -352,7 +430,7 @@ __global__ __launch_bounds__(1024) void splitters_kernel(const KSource src, cons
   __syncthreads();
   const uint64_t lo = seg > 0 ? skey1[seg] : 0;
   const uint64_t hi = seg + 1 < nseg ? skey1[seg + 1] : static_cast<uint64_t>(nrows) << (f.cb - f.kshift);
-  sort_records<1024, E>(words, ord, S, lo, coarse_shift(lo, hi), [&](int t) { return s_key[t]; });
+  sort_records<1024, E>(words, ord, S, coarse_shift(lo, hi), [&](int t) { return s_key[t] - lo; });
   if (tid < kSegMax) {
     uint64_t key = ~uint64_t{0};  // unused splitters lie beyond every key
     int pos = INT32_MAX;
@@ -362,8 +440,14 @@ __global__ __launch_bounds__(1024) void splitters_kernel(const KSource src, cons
       pos = begin + sample_pos<S>(t, m);
     }
     skey[seg * kSegMax + tid] = key;
-    spos[seg * kSegMax + tid] = pos;
+    spos[seg * kSegMax + tid] = pos;  // (of tid 0: written below)
+    const auto bound = [&](int d) {
+      return d == 0 ? lo : d >= nb ? hi : s_key[ord[static_cast<int>((static_cast<int64_t>(d) * S) / nb)]];
+    };
+    if (tid < nb && !narrow_keys(bound(tid), bound(tid + 1), f)) s_wide = 1;
   }
+  __syncthreads();
+  if (tid == 0) spos[seg * kSegMax] = !s_wide;
 }
 
 // ---- partition ------------------------------------------------------------------------------
@@ -413,9 +497,11 @@ __global__ __launch_bounds__(kBlock) void classify_kernel(const SRC src, const K
   const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
   int seg = 0, begin = 0, end = n, tile0, ntiles;
   int64_t base = 0;
-  const int g = xcd_contiguous_block_id();
+  // a contiguous part for each XCD of the groups there are, not of the grid's bound on them, which would leave the last
+  // XCD the idle ones (1M records 74 us instead of 72, 5.7M 192 and 186)
+  if (LEVEL2 && static_cast<int>(blockIdx.x) >= T.seg_group[nseg]) return;
+  const int g = xcd_contiguous_block_id(blockIdx.x, LEVEL2 ? T.seg_group[nseg] : static_cast<int>(gridDim.x));
   if (LEVEL2) {
-    if (g >= T.seg_group[nseg]) return;
     seg = T.group_seg[g];
     begin = T.seg_start[seg];
     end = T.seg_start[seg + 1];
@@ -501,35 +587,57 @@ __global__ __launch_bounds__(kOffBlock) void offsets_kernel(int ntiles1, const T
   if (!LEVEL2 && threadIdx.x == 0) total[g] = run;
 }
 
+// The lanes of `among` whose eight bits are those of this one. What differs is gathered with a bit of d as 0 or ~0, against
+// which both halves of the lanes that have it take one exclusive or each (selecting the lanes or their complement, the
+// compiler needs twice as many instructions).
+__device__ __forceinline__ uint64_t lanes_with(int d, uint64_t among) {
+  uint32_t lo = 0, hi = 0;
+#pragma unroll
+  for (int b = 0; b < kRadixBits; ++b) {
+    const uint32_t bit = static_cast<uint32_t>(__builtin_amdgcn_sbfe(d, b, 1));
+    const uint64_t vote = __ballot(bit != 0);
+    lo |= static_cast<uint32_t>(vote) ^ bit;
+    hi |= static_cast<uint32_t>(vote >> 32) ^ bit;
+  }
+  return among & ~(static_cast<uint64_t>(hi) << 32 | lo);
+}
+
 // Stable scatter of one tile by the noted buckets; ranks as in the radix scatter: a ballot match
 // inside the wave plus per-wave counters, then the tile is put in bucket order in LDS so that
 // consecutive lanes store to consecutive addresses.
 // Level 1: `off` holds the records of a bucket in the tiles before, total1 those of the buckets.
 // SELF (few tiles): `off` holds the plain counts, and every workgroup adds up those before its own
 // tile itself; the first leaves the start of every bucket in `starts` (one more than buckets).
+// Level 2 leaves records in `out` (level 1 keys in it and values in val_out).
 template <typename VT, class SRC, bool LEVEL2, int TILE, bool SELF = false>
 __global__ __launch_bounds__(part_threads(TILE)) void partition_kernel(const SRC src, const VT* __restrict__ val_in,
                                                            const KeyForm f, int n, int nseg, const Tables T,
                                                            const uint8_t* __restrict__ dig,
                                                            const int32_t* __restrict__ off,
-                                                           uint64_t* __restrict__ key_out,
+                                                           void* __restrict__ out,
                                                            VT* __restrict__ val_out,
                                                            int32_t* __restrict__ starts,
-                                                           const int32_t* __restrict__ total1) {
+                                                           const int32_t* __restrict__ total1,
+                                                           const uint64_t* __restrict__ skey1,
+                                                           const uint64_t* __restrict__ skey2,
+                                                           const int32_t* __restrict__ spos2) {
   constexpr int kPart = part_threads(TILE), kPartWaves = kPart / kWave, IPT = TILE / kPart;
   __shared__ int s_cnt[kPartWaves][kRadix];
   __shared__ int s_gdelta[kRadix];
   __shared__ int s_sum[4];
   __shared__ uint64_t s_buf[TILE];
   __shared__ uint8_t s_dig[TILE];
-  VT* s_val = reinterpret_cast<VT*>(s_buf);
+  __shared__ VT s_values[LEVEL2 ? TILE : 1];
+  __shared__ uint32_t s_lo[LEVEL2 ? kRadix : 1];  // lower bounds of the buckets' keys, as far as a narrow record needs them
+  VT* s_val = LEVEL2 ? s_values : reinterpret_cast<VT*>(s_buf);
   const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
-  const int tile = xcd_contiguous_block_id();
-  int begin, end, ntiles, i0;
+  // (as in the classification)
+  if (LEVEL2 && static_cast<int>(blockIdx.x) >= T.seg_tile[nseg]) return;
+  const int tile = xcd_contiguous_block_id(blockIdx.x, LEVEL2 ? T.seg_tile[nseg] : static_cast<int>(gridDim.x));
+  int begin, end, ntiles, i0, seg = 0;
   int64_t base = 0;
   if (LEVEL2) {
-    if (tile >= T.seg_tile[nseg]) return;
-    const int seg = T.tile_seg[tile];
+    seg = T.tile_seg[tile];
     const int t0 = T.seg_tile[seg];
     ntiles = T.seg_tile[seg + 1] - t0;
     i0 = tile - t0;
@@ -562,13 +670,7 @@ __global__ __launch_bounds__(part_threads(TILE)) void partition_kernel(const SRC
   for (int k = 0; k < IPT; ++k) {
     const bool valid = wave_base + k * kWave + lane < end;
     const int d = lpos[k];
-    uint64_t same = __ballot(valid);
-#pragma unroll
-    for (int b = 0; b < kRadixBits; ++b) {
-      const bool bit = (d >> b) & 1;
-      const uint64_t vote = __ballot(bit);
-      same &= bit ? vote : ~vote;
-    }
+    const uint64_t same = lanes_with(d, __ballot(valid));
     const int before = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(same >> 32),
                                                  __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(same), 0));
     int basecnt = 0;
@@ -629,6 +731,10 @@ __global__ __launch_bounds__(part_threads(TILE)) void partition_kernel(const SRC
     }
     if (tid < kRadix) {
       s_gdelta[d] = global - start;
+      if (LEVEL2) {
+        s_gdelta[d] -= T.seg_start[seg];
+        s_lo[d] = static_cast<uint32_t>((d > 0 ? skey2[seg * kSegMax + d] : seg > 0 ? skey1[seg] : 0) << f.kshift);
+      }
 #pragma unroll
       for (int u = 0; u < kPartWaves; ++u) {
         s_cnt[u][d] = start;
@@ -644,9 +750,30 @@ __global__ __launch_bounds__(part_threads(TILE)) void partition_kernel(const SRC
       lpos[k] = (lpos[k] & 0xFFFF) + s_cnt[w][d];
       s_buf[lpos[k]] = key[k];
       s_dig[lpos[k]] = static_cast<uint8_t>(d);
+      if (LEVEL2) s_val[lpos[k]] = val[k];
     }
   }
   __syncthreads();
+  if constexpr (LEVEL2) {
+    char* at = segment_records<VT>(out, T.seg_start[seg]);
+    const bool narrow = spos2[seg * kSegMax] != 0;
+#pragma unroll
+    for (int k = 0; k < IPT; ++k) {
+      const int j = k * kPart + tid;
+      if (j < tile_n) {
+        const int d = s_dig[j], to = j + s_gdelta[d];
+        if (narrow) {
+          typedef Record<uint32_t, VT> R;
+          at32(reinterpret_cast<R*>(at), to) = R::of(static_cast<uint32_t>(s_buf[j]) - s_lo[d], s_val[j]);
+        } else {
+          typedef Record<uint64_t, VT> R;
+          at32(reinterpret_cast<R*>(at), to) = R::of(s_buf[j], s_val[j]);
+        }
+      }
+    }
+    return;
+  }
+  uint64_t* key_out = static_cast<uint64_t*>(out);
   int dst[IPT];
 #pragma unroll
   for (int k = 0; k < IPT; ++k) {
@@ -698,24 +825,23 @@ __device__ __forceinline__ void store_entries(const uint16_t* ord, int n, int fi
 
 // The last resort for more records than fit: every record's rank is counted. `in` tells whether the
 // record at a position belongs to the bucket.
-template <int NT, typename VT, class SRC, class IN>
-__device__ void rank_and_store(const SRC& src, int begin, int end, const IN& in, int n, int first, int lo_row,
-                               int hi_row, const KeyForm& f, const VT* __restrict__ val_in,
-                               int32_t* __restrict__ pos, int32_t* __restrict__ crd_out,
+template <int NT, typename VT, class KA, class VA, class IN>
+__device__ void rank_and_store(const KA& key_at, const VA& val_at, int end, const IN& in, int n, int first, int lo_row, int hi_row,
+                               const KeyForm& f, int32_t* __restrict__ pos, int32_t* __restrict__ crd_out,
                                VT* __restrict__ val_out) {
-  for (int p0 = begin; p0 < end; p0 += NT) {
+  for (int p0 = 0; p0 < end; p0 += NT) {
     const int p = p0 + threadIdx.x;
     bool live = p < end;
     uint64_t K = 0, key = 0;
     if (live) {
-      K = src.key(p, f);
+      K = key_at(p);
       key = K >> f.kshift;
       live = in(key, p);
     }
     if (!__any(live)) continue;
     int rank = 0, prev = lo_row;
-    for (int q = begin; q < end; ++q) {
-      const uint64_t k = src.key(q, f) >> f.kshift;
+    for (int q = 0; q < end; ++q) {
+      const uint64_t k = key_at(q) >> f.kshift;
       if (in(k, q) && (k < key || (k == key && q < p))) {
         ++rank;
         prev = max(prev, f.row_of(k));
@@ -724,7 +850,7 @@ __device__ void rank_and_store(const SRC& src, int begin, int end, const IN& in,
     const int row = static_cast<int>(K >> f.cb);
     if (live) {
       crd_out[first + rank] = static_cast<int>(K & ((uint64_t{1} << f.cb) - 1));
-      val_out[first + rank] = val_in[p];
+      val_out[first + rank] = val_at(p);
     }
     store_pos_range(pos, live ? prev : 0, live ? row : 0, first + rank);
     const bool last = live && rank == n - 1;
@@ -750,11 +876,11 @@ __device__ __forceinline__ void sort_positions(uint32_t* at, int n) {
 // ranks counted.)
 constexpr int kSplitSamples = 512;
 constexpr int kSplitBytes = kSplitSamples * 10 + kStaged * 10 + 16;
-template <int NT, typename VT>
-__device__ __forceinline__ void split_and_store(char* mem, const KSource& src, int begin, int end, uint64_t lo_key,
-                                                uint64_t hi_key, int lo_row, int hi_row, const KeyForm& f,
-                                                const VT* __restrict__ val_in, int32_t* __restrict__ pos,
-                                                int32_t* __restrict__ crd_out, VT* __restrict__ val_out) {
+template <int NT, class SRC>
+__device__ __forceinline__ void split_and_store(char* mem, const SRC& src, int n, int first, uint64_t lo_key, uint64_t hi_key,
+                                                int lo_row, int hi_row, const KeyForm& f, int32_t* __restrict__ pos,
+                                                int32_t* __restrict__ crd_out, typename SRC::VT* __restrict__ val_out) {
+  typedef typename SRC::VT VT;
   constexpr int S = kSplitSamples, E = kStaged / NT;
   uint64_t* s_key = reinterpret_cast<uint64_t*>(mem);
   uint32_t* words = reinterpret_cast<uint32_t*>(mem + S * 8);
@@ -762,16 +888,16 @@ __device__ __forceinline__ void split_and_store(char* mem, const KSource& src, i
   uint16_t* ord = reinterpret_cast<uint16_t*>(at + kStaged);
   uint16_t* s_ord = ord + kStaged;
   int* s_cnt = reinterpret_cast<int*>(s_ord + S);
-  const int tid = threadIdx.x, lane = lane_id(), n = end - begin;
-  for (int t = tid; t < S; t += NT) s_key[t] = src.key(begin + sample_pos<S>(t, n), f) >> f.kshift;
+  const int tid = threadIdx.x, lane = lane_id();
+  const auto whole_at = [&](int p) { return src.whole(src.key(p)); };
+  for (int t = tid; t < S; t += NT) s_key[t] = whole_at(sample_pos<S>(t, n)) >> f.kshift;
   __syncthreads();
-  sort_records<NT, S / NT>(words, s_ord, S, lo_key, coarse_shift(lo_key, hi_key), [s_key](int t) { return s_key[t]; });
+  sort_records<NT, S / NT>(words, s_ord, S, coarse_shift(lo_key, hi_key), [&](int t) { return s_key[t] - lo_key; });
   const int nb = min(S, (n + kStaged / 2 - 1) / (kStaged / 2));
   const auto cut_at = [&](int d) {
     const int t = s_ord[d * S / nb];
-    return Cut{s_key[t], begin + sample_pos<S>(t, n)};
+    return Cut{s_key[t], sample_pos<S>(t, n)};
   };
-  int first = begin;
   for (int d = 0; d < nb; ++d) {
     const Cut lo = d > 0 ? cut_at(d) : Cut{lo_key, -1}, hi = d + 1 < nb ? cut_at(d + 1) : Cut{hi_key, INT32_MAX};
     const int a_row = d > 0 ? f.row_of(lo.key) : lo_row, b_row = d + 1 < nb ? f.row_of(hi.key) : hi_row;
@@ -781,14 +907,14 @@ __device__ __forceinline__ void split_and_store(char* mem, const KSource& src, i
     if (tid == 0) *s_cnt = 0;
     __syncthreads();
     constexpr int U = 8;
-    for (int p0 = begin + tid; p0 < end; p0 += U * NT) {
+    for (int p0 = tid; p0 < n; p0 += U * NT) {
       uint64_t key[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) key[u] = src.key(min(p0 + u * NT, end - 1), f) >> f.kshift;
+      for (int u = 0; u < U; ++u) key[u] = whole_at(min(p0 + u * NT, n - 1)) >> f.kshift;
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int p = p0 + u * NT;
-        if (p < end && in(key[u], p)) {
+        if (p < n && in(key[u], p)) {
           const int i = atomicAdd(s_cnt, 1);
           if (i < kStaged) at[i] = p;
         }
@@ -797,16 +923,15 @@ __device__ __forceinline__ void split_and_store(char* mem, const KSource& src, i
     __syncthreads();
     const int cnt = *s_cnt;
     if (cnt > kStaged) {
-      rank_and_store<NT, VT>(src, begin, end, in, cnt, first, a_row, b_row, f, val_in, pos, crd_out, val_out);
+      rank_and_store<NT, VT>(whole_at, [&](int p) { return src.val(p); }, n, in, cnt, first, a_row, b_row, f, pos, crd_out, val_out);
     } else if (cnt == 0) {
       if (tid < kWave) store_pos_range(pos, lane == 0 ? a_row : 0, lane == 0 ? b_row : 0, first);
     } else {
-      const auto key_at = [&](int li) { return src.key(at[li], f); };
       sort_positions<NT, E>(at, cnt);  // records are numbered in input order
-      sort_records<NT, E>(words, ord, cnt, lo.key, coarse_shift(lo.key, hi.key),
-                          [&](int li) { return src.key(at[li], f) >> f.kshift; });
-      store_entries<NT, E>(ord, cnt, first, a_row, b_row, f, key_at, pos, crd_out,
-                           [&](int j, int li) { val_out[first + j] = val_in[at[li]]; });
+      sort_records<NT, E>(words, ord, cnt, coarse_shift(lo.key, hi.key),
+                          [&](int li) { return (whole_at(at[li]) >> f.kshift) - lo.key; });
+      store_entries<NT, E>(ord, cnt, first, a_row, b_row, f, [&](int li) { return whole_at(at[li]); }, pos, crd_out,
+                           [&](int j, int li) { val_out[first + j] = src.val(at[li]); });
     }
     first += cnt;
     __syncthreads();
@@ -814,39 +939,33 @@ __device__ __forceinline__ void split_and_store(char* mem, const KSource& src, i
 }
 
 // Up to kFin * E records, whose keys and values pass through LDS.
-template <typename VT, int E>
-__device__ __forceinline__ void finish_staged(char* mem, const KSource& src, int first, int n, uint64_t lo, int shift,
-                                              int lo_row, int hi_row, const KeyForm& f, const VT* __restrict__ val_in,
-                                              int32_t* __restrict__ pos, int32_t* __restrict__ crd_out,
-                                              VT* __restrict__ val_out) {
+template <int E, class SRC>
+__device__ __forceinline__ void finish_staged(char* mem, const SRC& src, int n, int first, int shift, int lo_row, int hi_row,
+                                              const KeyForm& f, int32_t* __restrict__ pos, int32_t* __restrict__ crd_out,
+                                              typename SRC::VT* __restrict__ val_out) {
+  typedef typename SRC::VT VT;
+  typedef typename SRC::KT KT;
   static_assert(kFin * E <= kStaged, "");
-  uint64_t* s_key = reinterpret_cast<uint64_t*>(mem);
+  KT* s_key = reinterpret_cast<KT*>(mem);
   VT* s_val = reinterpret_cast<VT*>(mem);
   uint32_t* words = reinterpret_cast<uint32_t*>(mem + kStaged * 8);
   uint16_t* ord = reinterpret_cast<uint16_t*>(mem + kStaged * 12);
   const int tid = threadIdx.x;
-  const uint64_t* key_in = src.k + first;
-  val_in += first;
-  val_out += first;
-  uint64_t k[E];
+  KT k[E];
   VT v[E];
 #pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int p = min(e * kFin + tid, n - 1);
-    k[e] = at32(key_in, p);
-    v[e] = at32(val_in, p);
-  }
+  for (int e = 0; e < E; ++e) src.load(min(e * kFin + tid, n - 1), k[e], v[e]);
 #pragma unroll
   for (int e = 0; e < E; ++e) s_key[e * kFin + tid] = k[e];
   __syncthreads();
-  const auto key_at = [s_key](int li) { return s_key[li]; };
-  const auto cmp_at = [&](int li) { return s_key[li] >> f.kshift; };
-  sort_records<kFin, E>(words, ord, n, lo, shift, cmp_at);
-  store_entries<kFin, E>(ord, n, first, lo_row, hi_row, f, key_at, pos, crd_out, [](int, int) {});
+  sort_records<kFin, E>(words, ord, n, shift, [&](int li) { return src.rel(s_key[li]); });
+  store_entries<kFin, E>(ord, n, first, lo_row, hi_row, f, [&](int li) { return src.whole(s_key[li]); }, pos, crd_out,
+                         [](int, int) {});
   __syncthreads();
 #pragma unroll
   for (int e = 0; e < E; ++e) s_val[e * kFin + tid] = v[e];
   __syncthreads();
+  val_out += first;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const int j = e * kFin + tid;
@@ -854,21 +973,51 @@ __device__ __forceinline__ void finish_staged(char* mem, const KSource& src, int
   }
 }
 
+// A bucket of n records whose keys lie in [lo, hi], its rows of pos in (lo_row, hi_row].
+template <class SRC>
+__device__ __forceinline__ void finish_bucket(char* mem, const SRC& src, int n, int first, uint64_t lo, uint64_t hi, int lo_row,
+                                              int hi_row, const KeyForm& f, int32_t* __restrict__ pos,
+                                              int32_t* __restrict__ crd_out, typename SRC::VT* __restrict__ val_out) {
+  const int shift = coarse_shift(lo, hi);
+  // as many words of a thread as the records need (six for most; with eight for all of them: 30 us longer for 60M)
+#define SPT_STAGED(E_) finish_staged<E_>(mem, src, n, first, shift, lo_row, hi_row, f, pos, crd_out, val_out)
+  if (n > kCap) {
+    split_and_store<kFin>(mem, src, n, first, lo, hi, lo_row, hi_row, f, pos, crd_out, val_out);
+  } else if (n <= 4 * kFin) {
+    SPT_STAGED(4);
+  } else if (n <= 6 * kFin) {
+    SPT_STAGED(6);
+  } else if (n <= kStaged) {
+    SPT_STAGED(8);
+  } else {
+    uint32_t* words = reinterpret_cast<uint32_t*>(mem);
+    uint16_t* ord = reinterpret_cast<uint16_t*>(mem + kCap * 4);
+    constexpr int E = kCap / kFin;
+    sort_records<kFin, E>(words, ord, n, shift, [&](int li) { return src.rel(src.key(li)); });
+    store_entries<kFin, E>(ord, n, first, lo_row, hi_row, f, [&](int li) { return src.whole(src.key(li)); }, pos, crd_out,
+                           [&](int j, int li) { val_out[first + j] = src.val(li); });
+  }
+#undef SPT_STAGED
+}
+
 // One workgroup per bucket of the last partition. LEVELS == 1: of the only one, whose scanned
-// counts are off2 and whose splitters are skey2, with nseg buckets.
+// counts are off2 and whose splitters are skey2, with nseg buckets, keys and values in arrays (in, val_in).
+// LEVELS == 2: records in `in`, those of a segment narrow if spos2 says so.
 template <typename VT, int LEVELS>
-__global__ __launch_bounds__(kFin, 5) void finish_kernel(const KSource src, const VT* __restrict__ val_in,
+__global__ __launch_bounds__(kFin, 5) void finish_kernel(const void* __restrict__ in, const VT* __restrict__ val_in,
                                                       const KeyForm f, int nseg, int nrows, const Tables T,
                                                       const int32_t* __restrict__ off2,
                                                       const uint64_t* __restrict__ skey1,
                                                       const uint64_t* __restrict__ skey2,
+                                                      const int32_t* __restrict__ spos2,
                                                       int32_t* __restrict__ pos, int32_t* __restrict__ crd_out,
                                                       VT* __restrict__ val_out) {
   // up to kStaged records: keys, later values, then words and order; beyond: words and order
   __shared__ __attribute__((aligned(16))) char s_mem[kStaged * 8 + kStaged * 4 + kStaged * 2];
   static_assert(kCap * 4 + kCap * 2 <= sizeof(s_mem) && kSplitBytes <= sizeof(s_mem), "");
   const int g = blockIdx.x;
-  int first, end;
+  int first, end, begin = 0;
+  bool narrow = false;
   // the bucket's keys lie in [lo, hi], its rows of pos are (row of lo, row of hi]
   const uint64_t top = static_cast<uint64_t>(nrows) << (f.cb - f.kshift);
   uint64_t lo, hi;
@@ -883,8 +1032,9 @@ __global__ __launch_bounds__(kFin, 5) void finish_kernel(const KSource src, cons
     const int d = g - T.seg_bucket[seg], nb = T.seg_bucket[seg + 1] - T.seg_bucket[seg];
     const int nt = T.seg_tile[seg + 1] - T.seg_tile[seg];
     const int64_t base = static_cast<int64_t>(T.seg_tile[seg]) * kRadix;
-    first = T.seg_start[seg];
+    first = begin = T.seg_start[seg];
     end = T.seg_start[seg + 1];
+    narrow = spos2[seg * kSegMax] != 0;
     if (nt > 0) {
       first = off2[base + static_cast<int64_t>(d) * nt];
       if (d + 1 < nb) end = off2[base + static_cast<int64_t>(d + 1) * nt];
@@ -894,33 +1044,22 @@ __global__ __launch_bounds__(kFin, 5) void finish_kernel(const KSource src, cons
   }
   const int n = end - first;
   const int lo_row = g > 0 ? f.row_of(lo) : -1, hi_row = f.row_of(hi);
-  if (n > kCap) {
-    split_and_store<kFin, VT>(s_mem, src, first, end, lo, hi, lo_row, hi_row, f, val_in, pos, crd_out, val_out);
-    return;
-  }
   if (n == 0) {
     if (threadIdx.x < kWave) store_pos_range(pos, threadIdx.x == 0 ? lo_row : 0, threadIdx.x == 0 ? hi_row : 0, first);
     return;
   }
-  const int shift = coarse_shift(lo, hi);
-  if (n <= kStaged) {
-    // as many words of a thread as the records need (six for most; with eight for all of them: 30 us longer for 60M)
-#define SPT_STAGED(E_) \
-  finish_staged<VT, E_>(s_mem, src, first, n, lo, shift, lo_row, hi_row, f, val_in, pos, crd_out, val_out)
-    if (n <= 4 * kFin) SPT_STAGED(4);
-    else if (n <= 6 * kFin) SPT_STAGED(6);
-    else SPT_STAGED(8);
-#undef SPT_STAGED
+  if constexpr (LEVELS == 1) {
+    const ArraysBucket<VT> src{static_cast<const uint64_t*>(in) + first, val_in + first, lo, f.kshift};
+    finish_bucket(s_mem, src, n, first, lo, hi, lo_row, hi_row, f, pos, crd_out, val_out);
   } else {
-    uint32_t* words = reinterpret_cast<uint32_t*>(s_mem);
-    uint16_t* ord = reinterpret_cast<uint16_t*>(s_mem + kCap * 4);
-    constexpr int E = kCap / kFin;
-    const uint64_t* k = src.k + first;
-    const auto key_at = [k](int li) { return k[li]; };
-    const auto cmp_at = [&](int li) { return k[li] >> f.kshift; };
-    sort_records<kFin, E>(words, ord, n, lo, shift, cmp_at);
-    store_entries<kFin, E>(ord, n, first, lo_row, hi_row, f, key_at, pos, crd_out,
-                           [&](int j, int li) { val_out[first + j] = val_in[first + li]; });
+    const char* at = segment_records<VT>(in, begin);
+    if (narrow) {
+      const RecordBucket<uint32_t, VT> src{reinterpret_cast<const Record<uint32_t, VT>*>(at) + (first - begin), lo, f.kshift};
+      finish_bucket(s_mem, src, n, first, lo, hi, lo_row, hi_row, f, pos, crd_out, val_out);
+    } else {
+      const RecordBucket<uint64_t, VT> src{reinterpret_cast<const Record<uint64_t, VT>*>(at) + (first - begin), lo, f.kshift};
+      finish_bucket(s_mem, src, n, first, lo, hi, lo_row, hi_row, f, pos, crd_out, val_out);
+    }
   }
 }
 
@@ -955,7 +1094,7 @@ __global__ __launch_bounds__(kSel) void select_finish_kernel(const RcSource src,
       s_key[t] = src.key(sample_pos<S>(t, n), f) >> f.kshift;
     }
     __syncthreads();
-    sort_records<kSel, E>(words, s_ord, S, lo.key, coarse_shift(lo.key, hi.key), [&](int t) { return s_key[t]; });
+    sort_records<kSel, E>(words, s_ord, S, coarse_shift(lo.key, hi.key), [&](int t) { return s_key[t]; });
     if (d > 0) {
       const int t = s_ord[static_cast<int>((static_cast<int64_t>(d) * S) / nb)];
       lo = Cut{s_key[t], sample_pos<S>(t, n)};
@@ -1045,7 +1184,8 @@ __global__ __launch_bounds__(kSel) void select_finish_kernel(const RcSource src,
   __syncthreads();
   const int first = s_less;
   if (cnt > kCap) {
-    rank_and_store<kSel, VT>(src, 0, n, in, cnt, first, lo_row, hi_row, f, val_in, pos, crd_out, val_out);
+    rank_and_store<kSel, VT>([&](int p) { return src.key(p, f); }, [&](int p) { return val_in[p]; }, n, in, cnt, first, lo_row,
+                             hi_row, f, pos, crd_out, val_out);
     return;
   }
   if (cnt == 0) {
@@ -1054,10 +1194,10 @@ __global__ __launch_bounds__(kSel) void select_finish_kernel(const RcSource src,
   }
   const int shift = coarse_shift(lo.key, hi.key);
   const auto key_at = [&](int li) { return src.key(s_at[li], f); };
-  const auto cmp_at = [&](int li) { return src.key(s_at[li], f) >> f.kshift; };
+  const auto rel_at = [&](int li) { return (src.key(s_at[li], f) >> f.kshift) - lo.key; };
   const auto put = [&](int j, int li) { val_out[first + j] = val_in[s_at[li]]; };
 #define SPT_FINISH(E_)                                                                                     \
-  sort_records<kSel, E_>(words, s_ord, cnt, lo.key, shift, cmp_at);                                      \
+  sort_records<kSel, E_>(words, s_ord, cnt, shift, rel_at);                                              \
   store_entries<kSel, E_>(s_ord, cnt, first, lo_row, hi_row, f, key_at, pos, crd_out, put)
   if (cnt <= kSel) {
     // a record of each thread: keys and values are fetched together, once
@@ -1067,7 +1207,7 @@ __global__ __launch_bounds__(kSel) void select_finish_kernel(const RcSource src,
     const VT v = val_in[p];
     s_key[tid] = src.key(p, f);
     __syncthreads();
-    sort_records<kSel, 1>(words, s_ord, cnt, lo.key, shift, [&](int li) { return s_key[li] >> f.kshift; });
+    sort_records<kSel, 1>(words, s_ord, cnt, shift, [&](int li) { return (s_key[li] >> f.kshift) - lo.key; });
     s_val[tid] = v;
     __syncthreads();
     store_entries<kSel, 1>(s_ord, cnt, first, lo_row, hi_row, f, [&](int li) { return s_key[li]; }, pos, crd_out,
@@ -1093,8 +1233,8 @@ static int tile_of(int64_t n) {
   if (n <= kOneLevelMax) return n <= 128 * kSmallTile ? kSmallTile : 2 * kSmallTile;
   return n <= kSmallTileMax ? kSmallTile : kTile;
 }
-// LDS that the scatter of a large tile asks for beyond what it uses (46 KB), so that two of its workgroups share a compute
-// unit, not three (see above).
+// LDS that the first scatter of large tiles asks for beyond what it uses (46 KB), so that two of its workgroups share a compute
+// unit, not three (see above; the second one, which has keys and values in LDS at a time, uses 62 or 78 KB).
 constexpr size_t kPartPad = 10 * 1024;
 static int64_t tiles_bound(int64_t n) { return (n + tile_of(n) - 1) / tile_of(n) + kSegMax; }
 
@@ -1172,13 +1312,13 @@ spt_status sample_sort_convert(int64_t n64, int64_t nrows, int64_t ncols, bool b
     int32_t* starts = W.take<int32_t>(kSegMax + 1);
     if (tile == kSmallTile)
       hipLaunchKernelGGL((partition_kernel<VT, RcSource, false, kSmallTile, true>), dim3(nt1), dim3(part_threads(kSmallTile)), 0, s, rc,
-                         vals, f, n, 1, T, dig, hist1, k1, v1, starts, nullptr);
+                         vals, f, n, 1, T, dig, hist1, k1, v1, starts, nullptr, nullptr, nullptr, nullptr);
     else
       hipLaunchKernelGGL((partition_kernel<VT, RcSource, false, 2 * kSmallTile, true>), dim3(nt1), dim3(part_threads(kSmallTile)), 0, s, rc,
-                         vals, f, n, 1, T, dig, hist1, k1, v1, starts, nullptr);
+                         vals, f, n, 1, T, dig, hist1, k1, v1, starts, nullptr, nullptr, nullptr, nullptr);
     SPT_CHECK_LAUNCH("partition");
-    hipLaunchKernelGGL((finish_kernel<VT, 1>), dim3(nb1), dim3(kFin), 0, s, s1, v1, f, nb1, static_cast<int>(nrows), T,
-                       starts, nullptr, skey1, pos_out, crd_out, vals_out);
+    hipLaunchKernelGGL((finish_kernel<VT, 1>), dim3(nb1), dim3(kFin), 0, s, k1, v1, f, nb1, static_cast<int>(nrows), T,
+                       starts, nullptr, skey1, nullptr, pos_out, crd_out, vals_out);
     SPT_CHECK_LAUNCH("finish");
     return SPT_OK;
   }
@@ -1189,15 +1329,14 @@ spt_status sample_sort_convert(int64_t n64, int64_t nrows, int64_t ncols, bool b
   SPT_CHECK_LAUNCH("offsets");
   if (tile == kSmallTile)
     hipLaunchKernelGGL((partition_kernel<VT, RcSource, false, kSmallTile>), dim3(nt1), dim3(part_threads(kSmallTile)), 0, s, rc, vals, f, n,
-                       1, T, dig, hist1, k1, v1, nullptr, total1);
+                       1, T, dig, hist1, k1, v1, nullptr, total1, nullptr, nullptr, nullptr);
   else
     hipLaunchKernelGGL((partition_kernel<VT, RcSource, false, kTile>), dim3(nt1), dim3(part_threads(kTile)), kPartPad, s, rc, vals, f, n, 1, T,
-                       dig, hist1, k1, v1, nullptr, total1);
+                       dig, hist1, k1, v1, nullptr, total1, nullptr, nullptr, nullptr);
   SPT_CHECK_LAUNCH("partition");
 
   // level 2
-  uint64_t* k2 = W.take<uint64_t>(n);
-  VT* v2 = W.take<VT>(n);
+  char* records = W.take<char>(n64 * (sizeof(uint64_t) + sizeof(VT)));
   uint64_t* skey2 = W.take<uint64_t>(kSegMax * kSegMax);
   int32_t* spos2 = W.take<int32_t>(kSegMax * kSegMax);
   T.seg_start = W.take<int32_t>(kSegMax + 1);
@@ -1228,13 +1367,13 @@ spt_status sample_sort_convert(int64_t n64, int64_t nrows, int64_t ncols, bool b
   SPT_CHECK_LAUNCH("offsets 2");
   if (tile == kSmallTile)
     hipLaunchKernelGGL((partition_kernel<VT, KSource, true, kSmallTile>), dim3(tiles2), dim3(part_threads(kSmallTile)), 0, s, s1, v1, f, n,
-                       nb1, T, dig, hist2, k2, v2, nullptr, nullptr);
+                       nb1, T, dig, hist2, records, nullptr, nullptr, nullptr, skey1, skey2, spos2);
   else
-    hipLaunchKernelGGL((partition_kernel<VT, KSource, true, kTile>), dim3(tiles2), dim3(part_threads(kTile)), kPartPad, s, s1, v1, f, n, nb1, T,
-                       dig, hist2, k2, v2, nullptr, nullptr);
+    hipLaunchKernelGGL((partition_kernel<VT, KSource, true, kTile>), dim3(tiles2), dim3(part_threads(kTile)), 0, s, s1, v1, f, n, nb1, T,
+                       dig, hist2, records, nullptr, nullptr, nullptr, skey1, skey2, spos2);
   SPT_CHECK_LAUNCH("partition 2");
   hipLaunchKernelGGL((finish_kernel<VT, 2>), dim3(static_cast<unsigned>(n64 / kDirTarget + nb1)), dim3(kFin), 0, s,
-                     KSource{k2}, v2, f, nb1, static_cast<int>(nrows), T, hist2, skey1, skey2, pos_out, crd_out,
+                     records, nullptr, f, nb1, static_cast<int>(nrows), T, hist2, skey1, skey2, spos2, pos_out, crd_out,
                      vals_out);
   SPT_CHECK_LAUNCH("finish");
   return SPT_OK;

@@ -28,8 +28,8 @@
 // counted, 60M records took 10.4 instead of 1.8 ms).
 //
 // Measured against the six radix passes it replaces (fp64): 60M records with power-law rows
-// 3.09 -> 1.58 ms (splitters 19 + 70 us, classify 2 x 133, offsets 8 + 9, partitions 405 + 352, finish 464; with whole
-// keys and separate arrays in the second partition 418 and 476); 20M 570 -> 546 us by that, 5M 0.19 ms, 250 000 52 us,
+// 3.09 -> 1.52 ms (splitters 19 + 70 us, classify 2 x 133, offsets 8 + 9, partitions 405 + 352, finish 400; with whole
+// keys and separate arrays the second partition took 418); 20M 0.52 ms, 5M 0.19 ms, 250 000 52 us,
 // 50 000 171 -> 19 us. The partitions write 256 interleaved streams for each array
 // and are bound by how the memory system takes them: it is the bytes in flight that count. Two workgroups of 512 threads
 // on a compute unit: 60M records fp64 1.70 ms in all (before splitters, offsets and records were made as now), three 1.83, three
@@ -874,26 +874,27 @@ __device__ __forceinline__ void sort_positions(uint32_t* at, int n) {
 // A bucket with more records than fit is split once more: at splitters of a sample of its own, as in the
 // selection from a small input, one part after the other. (A part that is too large again has its records'
 // ranks counted.)
-constexpr int kSplitSamples = 512;
-constexpr int kSplitBytes = kSplitSamples * 10 + kStaged * 10 + 16;
+constexpr int kSplitSamples = 512, kSplitPart = 1536;
+constexpr int kSplitBytes = kSplitSamples * 10 + kSplitPart * 10 + 16;
 template <int NT, class SRC>
 __device__ __forceinline__ void split_and_store(char* mem, const SRC& src, int n, int first, uint64_t lo_key, uint64_t hi_key,
                                                 int lo_row, int hi_row, const KeyForm& f, int32_t* __restrict__ pos,
                                                 int32_t* __restrict__ crd_out, typename SRC::VT* __restrict__ val_out) {
   typedef typename SRC::VT VT;
-  constexpr int S = kSplitSamples, E = kStaged / NT;
+  constexpr int S = kSplitSamples, E = kSplitPart / NT;
   uint64_t* s_key = reinterpret_cast<uint64_t*>(mem);
   uint32_t* words = reinterpret_cast<uint32_t*>(mem + S * 8);
-  uint32_t* at = words + kStaged;
-  uint16_t* ord = reinterpret_cast<uint16_t*>(at + kStaged);
-  uint16_t* s_ord = ord + kStaged;
+  uint32_t* at = words + kSplitPart;
+  uint16_t* ord = reinterpret_cast<uint16_t*>(at + kSplitPart);
+  uint16_t* s_ord = ord + kSplitPart;
   int* s_cnt = reinterpret_cast<int*>(s_ord + S);
   const int tid = threadIdx.x, lane = lane_id();
   const auto whole_at = [&](int p) { return src.whole(src.key(p)); };
   for (int t = tid; t < S; t += NT) s_key[t] = whole_at(sample_pos<S>(t, n)) >> f.kshift;
   __syncthreads();
   sort_records<NT, S / NT>(words, s_ord, S, coarse_shift(lo_key, hi_key), [&](int t) { return s_key[t] - lo_key; });
-  const int nb = min(S, (n + kStaged / 2 - 1) / (kStaged / 2));
+  constexpr int kTarget = kSplitPart * 3 / 8;  // (16 samples to a part of 4096: one that does not fit has a chance below 1e-8)
+  const int nb = min(S, (n + kTarget - 1) / kTarget);
   const auto cut_at = [&](int d) {
     const int t = s_ord[d * S / nb];
     return Cut{s_key[t], sample_pos<S>(t, n)};
@@ -916,13 +917,13 @@ __device__ __forceinline__ void split_and_store(char* mem, const SRC& src, int n
         const int p = p0 + u * NT;
         if (p < n && in(key[u], p)) {
           const int i = atomicAdd(s_cnt, 1);
-          if (i < kStaged) at[i] = p;
+          if (i < kSplitPart) at[i] = p;
         }
       }
     }
     __syncthreads();
     const int cnt = *s_cnt;
-    if (cnt > kStaged) {
+    if (cnt > kSplitPart) {
       rank_and_store<NT, VT>(whole_at, [&](int p) { return src.val(p); }, n, in, cnt, first, a_row, b_row, f, pos, crd_out, val_out);
     } else if (cnt == 0) {
       if (tid < kWave) store_pos_range(pos, lane == 0 ? a_row : 0, lane == 0 ? b_row : 0, first);
@@ -945,11 +946,11 @@ __device__ __forceinline__ void finish_staged(char* mem, const SRC& src, int n, 
                                               typename SRC::VT* __restrict__ val_out) {
   typedef typename SRC::VT VT;
   typedef typename SRC::KT KT;
-  static_assert(kFin * E <= kStaged, "");
   KT* s_key = reinterpret_cast<KT*>(mem);
   VT* s_val = reinterpret_cast<VT*>(mem);
-  uint32_t* words = reinterpret_cast<uint32_t*>(mem + kStaged * 8);
-  uint16_t* ord = reinterpret_cast<uint16_t*>(mem + kStaged * 12);
+  uint32_t* words = reinterpret_cast<uint32_t*>(s_key + kFin * E);
+  uint16_t* ord = reinterpret_cast<uint16_t*>(words + kFin * E);
+  static_assert(sizeof(VT) <= sizeof(KT) + 4, "");
   const int tid = threadIdx.x;
   KT k[E];
   VT v[E];
@@ -973,29 +974,40 @@ __device__ __forceinline__ void finish_staged(char* mem, const SRC& src, int n, 
   }
 }
 
-// A bucket of n records whose keys lie in [lo, hi], its rows of pos in (lo_row, hi_row].
-template <class SRC>
+// Up to kFin * E records, whose keys and values are fetched where they are used.
+template <int E, class SRC>
+__device__ __forceinline__ void finish_direct(char* mem, const SRC& src, int n, int first, int shift, int lo_row, int hi_row,
+                                              const KeyForm& f, int32_t* __restrict__ pos, int32_t* __restrict__ crd_out,
+                                              typename SRC::VT* __restrict__ val_out) {
+  uint32_t* words = reinterpret_cast<uint32_t*>(mem);
+  uint16_t* ord = reinterpret_cast<uint16_t*>(words + E * kFin);
+  sort_records<kFin, E>(words, ord, n, shift, [&](int li) { return src.rel(src.key(li)); });
+  store_entries<kFin, E>(ord, n, first, lo_row, hi_row, f, [&](int li) { return src.whole(src.key(li)); }, pos, crd_out,
+                         [&](int j, int li) { val_out[first + j] = src.val(li); });
+}
+
+// A bucket of n records whose keys lie in [lo, hi], its rows of pos in (lo_row, hi_row]. mem: ROOM bytes of LDS. MOST: words of a
+// thread, beyond which the bucket is split.
+template <int ROOM, int MOST, class SRC>
 __device__ __forceinline__ void finish_bucket(char* mem, const SRC& src, int n, int first, uint64_t lo, uint64_t hi, int lo_row,
                                               int hi_row, const KeyForm& f, int32_t* __restrict__ pos,
                                               int32_t* __restrict__ crd_out, typename SRC::VT* __restrict__ val_out) {
   const int shift = coarse_shift(lo, hi);
   // as many words of a thread as the records need (six for most; with eight for all of them: 30 us longer for 60M)
 #define SPT_STAGED(E_) finish_staged<E_>(mem, src, n, first, shift, lo_row, hi_row, f, pos, crd_out, val_out)
-  if (n > kCap) {
+  constexpr int kStagedMost = ROOM / (sizeof(typename SRC::KT) + 6) / kFin;
+  static_assert(kStagedMost >= 6 && MOST * kFin * 6 <= ROOM && MOST * kFin <= kCap && kSplitBytes <= ROOM, "");
+  if (n > MOST * kFin) {
     split_and_store<kFin>(mem, src, n, first, lo, hi, lo_row, hi_row, f, pos, crd_out, val_out);
   } else if (n <= 4 * kFin) {
     SPT_STAGED(4);
   } else if (n <= 6 * kFin) {
     SPT_STAGED(6);
-  } else if (n <= kStaged) {
-    SPT_STAGED(8);
+  } else if (n <= 8 * kFin) {
+    if constexpr (kStagedMost >= 8) SPT_STAGED(8);
+    else finish_direct<8>(mem, src, n, first, shift, lo_row, hi_row, f, pos, crd_out, val_out);
   } else {
-    uint32_t* words = reinterpret_cast<uint32_t*>(mem);
-    uint16_t* ord = reinterpret_cast<uint16_t*>(mem + kCap * 4);
-    constexpr int E = kCap / kFin;
-    sort_records<kFin, E>(words, ord, n, shift, [&](int li) { return src.rel(src.key(li)); });
-    store_entries<kFin, E>(ord, n, first, lo_row, hi_row, f, [&](int li) { return src.whole(src.key(li)); }, pos, crd_out,
-                           [&](int j, int li) { val_out[first + j] = src.val(li); });
+    finish_direct<MOST>(mem, src, n, first, shift, lo_row, hi_row, f, pos, crd_out, val_out);
   }
 #undef SPT_STAGED
 }
@@ -1003,8 +1015,11 @@ __device__ __forceinline__ void finish_bucket(char* mem, const SRC& src, int n, 
 // One workgroup per bucket of the last partition. LEVELS == 1: of the only one, whose scanned
 // counts are off2 and whose splitters are skey2, with nseg buckets, keys and values in arrays (in, val_in).
 // LEVELS == 2: records in `in`, those of a segment narrow if spos2 says so.
+// Seven workgroups to a compute unit after two levels: the steps of the network wait for each other, and the time goes
+// with the number of workgroups that take turns (60M records, fp64: 650 us with three, 534 with four, 468 with five, 419
+// with six, 400 with seven). Hence the room in LDS and the registers of a lane. After one level there are no more than 256.
 template <typename VT, int LEVELS>
-__global__ __launch_bounds__(kFin, 5) void finish_kernel(const void* __restrict__ in, const VT* __restrict__ val_in,
+__global__ __launch_bounds__(kFin, LEVELS == 1 ? 5 : 7) void finish_kernel(const void* __restrict__ in, const VT* __restrict__ val_in,
                                                       const KeyForm f, int nseg, int nrows, const Tables T,
                                                       const int32_t* __restrict__ off2,
                                                       const uint64_t* __restrict__ skey1,
@@ -1012,9 +1027,8 @@ __global__ __launch_bounds__(kFin, 5) void finish_kernel(const void* __restrict_
                                                       const int32_t* __restrict__ spos2,
                                                       int32_t* __restrict__ pos, int32_t* __restrict__ crd_out,
                                                       VT* __restrict__ val_out) {
-  // up to kStaged records: keys, later values, then words and order; beyond: words and order
-  __shared__ __attribute__((aligned(16))) char s_mem[kStaged * 8 + kStaged * 4 + kStaged * 2];
-  static_assert(kCap * 4 + kCap * 2 <= sizeof(s_mem) && kSplitBytes <= sizeof(s_mem), "");
+  constexpr int kRoom = LEVELS == 1 ? kStaged * 14 : 14 * kFin * 6;
+  __shared__ __attribute__((aligned(16))) char s_mem[kRoom];  // keys, later values, words and order; many records: words and order
   const int g = blockIdx.x;
   int first, end, begin = 0;
   bool narrow = false;
@@ -1050,15 +1064,15 @@ __global__ __launch_bounds__(kFin, 5) void finish_kernel(const void* __restrict_
   }
   if constexpr (LEVELS == 1) {
     const ArraysBucket<VT> src{static_cast<const uint64_t*>(in) + first, val_in + first, lo, f.kshift};
-    finish_bucket(s_mem, src, n, first, lo, hi, lo_row, hi_row, f, pos, crd_out, val_out);
+    finish_bucket<kRoom, kCap / kFin>(s_mem, src, n, first, lo, hi, lo_row, hi_row, f, pos, crd_out, val_out);
   } else {
     const char* at = segment_records<VT>(in, begin);
     if (narrow) {
       const RecordBucket<uint32_t, VT> src{reinterpret_cast<const Record<uint32_t, VT>*>(at) + (first - begin), lo, f.kshift};
-      finish_bucket(s_mem, src, n, first, lo, hi, lo_row, hi_row, f, pos, crd_out, val_out);
+      finish_bucket<kRoom, 14>(s_mem, src, n, first, lo, hi, lo_row, hi_row, f, pos, crd_out, val_out);
     } else {
       const RecordBucket<uint64_t, VT> src{reinterpret_cast<const Record<uint64_t, VT>*>(at) + (first - begin), lo, f.kshift};
-      finish_bucket(s_mem, src, n, first, lo, hi, lo_row, hi_row, f, pos, crd_out, val_out);
+      finish_bucket<kRoom, 12>(s_mem, src, n, first, lo, hi, lo_row, hi_row, f, pos, crd_out, val_out);
     }
   }
 }

@@ -10,21 +10,25 @@
 //     leaves as a carry (row, J values), which the carry kernels add in a fixed order (no atomics).
 //   - CSF: i and k are the last slice and fibre that start at or before an entry. The starts inside a
 //     chunk are marked in a bit set in LDS; C[k, :] is multiplied once per fibre (factored form).
-// Bound by the gathers of factor rows, large tensors by those that miss L2 (50M entries, J = 32, fp32: 650 us; with
-// all rows in L2, as a probe, 400). A row of C stays in registers while k does (loaded for every entry: 700 us, and 619
+// Bound by the gathers of factor rows, large tensors by those that miss L2: what is fetched from beyond it takes all the
+// time there (50M entries, J = 32, fp32: 4.7 GB, 632 us; with all rows in L2, as a probe, 400; chunks in the order of their
+// rows of C: 593). A row of C stays in registers while k does (loaded for every entry: 700 us, and 619
 // instead of 521 with a D that fits L2; same sums, bit for bit). Chunks go to the
-// XCDs in turn: with one contiguous part of a skewed tensor to each, the XCD with its last slices fetched twice as
+// XCDs in turn, unless they are ordered: with one contiguous part of a skewed tensor to each, the XCD with its last slices fetched twice as
 // many lines as the others and took 960 us (738 000 entries in CSF, J = 16, fp64: 41 -> 38; 15M entries, J = 32,
 // fp64, 703 -> 555; runs of 4 or 16 chunks the same; even tensors of 0.4 to 0.9M entries lose 3 %, 22.2 -> 22.9). Left out after measuring: C read past the caches (small tensors
 // take up to a third longer); half of D to every other XCD, each going through all entries (743 us: the streams are
-// read twice); chunks of twice the entries (1 % faster, fp64 CSF 2 % slower); six waves a SIMD (spills, 815). Before that: more or
+// read twice), or picking its entries into a list in LDS first (3.0 instead of 4.7 GB, but 684 us: to pick takes 150, to go
+// through a list 230 without any row of a factor); chunks of twice the entries (1 % faster, fp64 CSF 2 % slower); six waves a SIMD (spills, 815). Before that: more or
 // fewer waves and the next rows loaded ahead change nothing; 32 lanes of one column per
 // entry, which issue four times as many loads and hand-arounds, and longer walks per group take 12 % longer, and for
 // 738 000 entries twice as long.
 #include <algorithm>
 
 #include "common.hpp"
+#include "radix.hpp"
 #include "search.hpp"
+#include "wavescan.hpp"
 
 namespace spt {
 
@@ -89,19 +93,112 @@ __device__ __forceinline__ double from_lane(int addr, double v) {
 // The upper levels of a CSF tensor; bounds as made by mttkrp_prepare_kernel.
 struct CsfLevels {
   const int32_t *crd0, *pos1, *crd1, *pos2, *bounds;
+  int nslices, nfibres;
 };
+
+// ---- the order of the chunks -----------------------------------------------------------------
+// Chunks are sorted by the row of C that one of their entries needs, by kRadix equal stretches of the rows, and each XCD
+// has an eighth of them in this order: chunks of different slices that need the same rows of C meet on one XCD, whose L2
+// then has them (C and D 10.2 and 6.4 MB, 50M entries of skewed slices: the rows 632 -> 593 us; 20M of even ones 527 -> 345).
+// The order changes no result: a chunk's sums and carries have their places. bin_chunks notes for each chunk its bin and
+// its place among the chunks of the same bin in its workgroup's share, and the share's counts; mttkrp_order_kernel makes
+// the order of that (4.5 us; by one workgroup 90). Both stable.
+constexpr int kOrderShare = 4 * kBlock;  // chunks of a workgroup
+template <class KEY>
+__device__ __forceinline__ void bin_chunks(int share, int nchunks, const StretchDigit& digit, const KEY& row_of,
+                                           int32_t* __restrict__ noted, int32_t* __restrict__ hist) {
+  __shared__ int s_cnt[kBlock / kWave][kRadix], s_before[kBlock / kWave][kRadix];
+  const int tid = threadIdx.x, w = wave_id(), lane = lane_id();
+  constexpr int kOwn = kOrderShare / kBlock;
+  for (int q = tid; q < kBlock / kWave * kRadix; q += kBlock) (&s_cnt[0][0])[q] = 0;
+  int d[kOwn], rank[kOwn];
+  const int first = share * kOrderShare + w * kOwn * kWave + lane;
+#pragma unroll
+  for (int k = 0; k < kOwn; ++k)
+    d[k] = static_cast<int>(min(static_cast<uint32_t>(digit.of(row_of(min(first + k * kWave, nchunks - 1)))), kRadix - 1u));
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kOwn; ++k) {
+    const bool valid = first + k * kWave < nchunks;
+    const uint64_t same = lanes_with(d[k], __ballot(valid));
+    const int before = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(same >> 32),
+                                                 __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(same), 0));
+    rank[k] = s_cnt[w][d[k]] + before;
+    wave_lds_order();
+    if (valid && before == 0) s_cnt[w][d[k]] = rank[k] + __popcll(same);
+    wave_lds_order();
+  }
+  __syncthreads();
+  int run = 0;
+#pragma unroll
+  for (int u = 0; u < kBlock / kWave; ++u) {
+    s_before[u][tid] = run;
+    run += s_cnt[u][tid];
+  }
+  hist[share * kRadix + tid] = run;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kOwn; ++k)
+    if (first + k * kWave < nchunks) noted[first + k * kWave] = d[k] << 16 | (s_before[w][d[k]] + rank[k]);
+}
+// Of CSF tensors: the row of the first fibre that starts in or after a chunk.
+__global__ __launch_bounds__(kBlock) void mttkrp_bin_kernel(int nchunks, const StretchDigit digit, const CsfLevels csf,
+                                                            int32_t* __restrict__ noted, int32_t* __restrict__ hist) {
+  bin_chunks(blockIdx.x, nchunks, digit, [&](int c) { return csf.crd1[min(csf.bounds[3 * c], csf.nfibres - 1)]; }, noted, hist);
+}
+__global__ __launch_bounds__(kBlock) void mttkrp_order_kernel(int nchunks, const int32_t* __restrict__ noted,
+                                                              const int32_t* __restrict__ hist, int32_t* __restrict__ bounds) {
+  static_assert(kRadix == kBlock, "");
+  __shared__ int s_start[kRadix];
+  __shared__ int s_sum[kBlock / kWave];
+  const int tid = threadIdx.x, share = blockIdx.x, shares = gridDim.x;
+  constexpr int kOwn = kOrderShare / kBlock, kAtOnce = 32;
+  int x[kOwn];
+#pragma unroll
+  for (int k = 0; k < kOwn; ++k) x[k] = noted[min(share * kOrderShare + k * kBlock + tid, nchunks - 1)];
+  int before = 0, total = 0;
+  for (int q0 = 0; q0 < shares; q0 += kAtOnce) {
+    int cnt[kAtOnce];
+#pragma unroll
+    for (int q = 0; q < kAtOnce; ++q) cnt[q] = hist[min(q0 + q, shares - 1) * kRadix + tid];
+#pragma unroll
+    for (int q = 0; q < kAtOnce; ++q) {
+      before += q0 + q < share ? cnt[q] : 0;
+      total += q0 + q < shares ? cnt[q] : 0;
+    }
+  }
+  int start = wave_inclusive_sum(total);
+  if (lane_id() == kWave - 1) s_sum[wave_id()] = start;
+  __syncthreads();
+  for (int u = 0; u < wave_id(); ++u) start += s_sum[u];
+  s_start[tid] = start - total + before;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kOwn; ++k) {
+    const int c = share * kOrderShare + k * kBlock + tid;
+    if (c < nchunks) bounds[3 * (s_start[x[k] >> 16] + (x[k] & 0xFFFF)) + 2] = c;
+  }
+}
 
 // Zeroes A (rows without entries stay zero). CSF: for chunk boundary c (entries from c * chunk on),
 // bounds[3c] = first fibre that starts at or after it, bounds[3c+1] = first slice that starts at or
-// after that fibre, bounds[3c+2] = the same as the end of the chunk before (all slices once the fibres
-// are used up). Boundary nchunks is the end. Eight lanes search a boundary.
+// after that fibre (as the end of a chunk: all slices once the fibres are used up). Boundary nchunks is the end. Eight
+// lanes search a boundary. (bounds[3c+2]: the order of the chunks.) COO: the last workgroups bin the chunks, if asked to.
 constexpr int kBoundLanes = 8;
 template <typename T>
 __global__ __launch_bounds__(kBlock) void mttkrp_prepare_kernel(T* __restrict__ A, int64_t size, int fill_blocks,
                                                                 int nchunks, int chunk, int nslices, int nfibres,
                                                                 const int32_t* __restrict__ pos1,
                                                                 const int32_t* __restrict__ pos2,
-                                                                int32_t* __restrict__ bounds) {
+                                                                int32_t* __restrict__ bounds, int bin_blocks,
+                                                                const StretchDigit digit, const int32_t* __restrict__ ck,
+                                                                int nnz, int32_t* __restrict__ noted, int32_t* __restrict__ hist) {
+  const int binned = static_cast<int>(blockIdx.x) - (static_cast<int>(gridDim.x) - bin_blocks);
+  if (binned >= 0) {
+    bin_chunks(binned, nchunks, digit, [&](int c) { return ck[min(static_cast<int64_t>(c) * chunk + chunk / 2, static_cast<int64_t>(nnz) - 1)]; },
+               noted, hist);
+    return;
+  }
   if (static_cast<int>(blockIdx.x) < fill_blocks) {
     typedef T V __attribute__((ext_vector_type(kVec<T>), aligned(sizeof(T))));
     const int64_t e = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) * kVec<T>;
@@ -121,7 +218,6 @@ __global__ __launch_bounds__(kBlock) void mttkrp_prepare_kernel(T* __restrict__ 
   if (threadIdx.x % kBoundLanes == 0) {
     bounds[3 * c] = f;
     bounds[3 * c + 1] = sl;
-    bounds[3 * c + 2] = f >= nfibres ? nslices : sl;
   }
 }
 
@@ -153,7 +249,7 @@ __global__ __launch_bounds__(kBlock) void mttkrp_rows_kernel(int n, int J, int e
                                                              const T* __restrict__ vals, const T* __restrict__ Cm,
                                                              const T* __restrict__ Dm, const CsfLevels csf,
                                                              T* __restrict__ A, int32_t* __restrict__ carry_key,
-                                                             T* __restrict__ carry_vec) {
+                                                             T* __restrict__ carry_vec, const int32_t* __restrict__ order) {
   constexpr int NG = kBlock / L, kGroupsOfWave = kWave / L;
   extern __shared__ __attribute__((aligned(16))) int32_t s_csf[];
   __shared__ T s_v[kBlock / kWave][L][V];
@@ -162,7 +258,7 @@ __global__ __launch_bounds__(kBlock) void mttkrp_rows_kernel(int n, int J, int e
   const int tid = threadIdx.x, lane = lane_id();
   const int g = tid / L, gl = tid % L;
   // (in turn to the XCDs: in one piece, the last has the slices of few entries, whose rows of C nobody shares)
-  const int chunk = blockIdx.x, size = NG * epg;
+  const int chunk = order ? order[3 * xcd_contiguous_block_id(blockIdx.x, gridDim.x) + 2] : static_cast<int>(blockIdx.x), size = NG * epg;
   const int base = chunk * size, end = min(base + size, n);
   // the last vector of a row ends with the row (it repeats columns of the one before if J is no multiple of V)
   const bool jok = (static_cast<int>(blockIdx.y) * L + gl) * V < J;
@@ -173,7 +269,7 @@ __global__ __launch_bounds__(kBlock) void mttkrp_rows_kernel(int n, int J, int e
   int16_t *s_fibre_before = reinterpret_cast<int16_t*>(s_slice + (size + 31) / 32), *s_slice_before = s_fibre_before + (size + 31) / 32;
   if (CSF) {
     const int f_lo = csf.bounds[3 * chunk], f_hi = csf.bounds[3 * chunk + 3];
-    const int s_lo = csf.bounds[3 * chunk + 1], s_hi = csf.bounds[3 * chunk + 5];
+    const int s_lo = csf.bounds[3 * chunk + 1], s_hi = f_hi >= csf.nfibres ? csf.nslices : csf.bounds[3 * chunk + 4];
     int32_t cut_k = -1, cut_i = -1;  // of the fibre and the slice that the chunk's start cuts
     if (tid == 0) {
       if (f_lo > 0) cut_k = csf.crd1[f_lo - 1];
@@ -532,6 +628,19 @@ static MttkrpPlan mttkrp_plan(int64_t nnz, int64_t J, int dtype) {
   return P;
 }
 
+// Is it worth 7 us (CSF 10) to order the chunks by their rows of C? An L2 has to be too small for the factors, C to be
+// the larger part of an eighth's traffic saved, and the gathers long enough. Given order / ordered, us:
+//   COO, slices of 10 000 entries, C and D 10.2 and 6.4 MB, 20M entries 536 / 361; C and D 7.7 MB, 5M 149 / 131
+//   COO, skewed slices, 10.2 and 6.4 MB, 50M 648 / 617; 12.8 and 12.8, 20M (fp64) 389 / 370; 6.4 and 6.4, 10M 185 / 176;
+//     3.8 and 6.4, 10M 172 / 170; 1.9 and 6.4, 10M 157 / 164; 6.4 and 1.3, 10M 125 / 128; 7.9 and 7.9, 6M 196 / 195
+//   CSF, skewed, 10.2 and 6.4, 40M 578 / 523; 20.5 and 12.8, 20M (fp64) 720 / 690; 1.9 and 3.8, 10M 119 / 128
+//   COO, slices of 200 entries (a chunk needs rows from all of C), 10.2 and 6.4, 20M 559 / 565
+static bool mttkrp_orders(const MttkrpPlan& P, int64_t nnz, int64_t J, int64_t value, int64_t rows_c, int64_t rows_d) {
+  const int64_t c = rows_c * J * value, d = rows_d * J * value;
+  return nnz >= 8000000 && c >= 6000000 && c + d >= 12000000 &&
+         P.n1 * J * value >= (P.n1 / kOrderShare + 1) * kRadix * 4;  // (the counts take the room of the carries)
+}
+
 size_t mttkrp3_workspace(const spt_tensor* B, int32_t J) {
   const MttkrpPlan P = mttkrp_plan(B->nvals, std::max(J, 1), B->dtype);
   const size_t row = static_cast<size_t>(std::max(J, 1)) * (B->dtype == SPT_F64 ? 8 : 4);
@@ -563,24 +672,37 @@ static spt_status mttkrp3_typed(Format f, const spt_tensor* B, const T* Cm, cons
     bounds = W.take<int32_t>(3 * ((size_t)n1 + 1));
   }
   const int fill = (int)((size + kBlock * kVec<T> - 1) / (kBlock * kVec<T>));
+  const bool in_order = mttkrp_orders(P, nnz64, J, sizeof(T), B->level[1].N, B->level[2].N);
+  const StretchDigit digit(B->level[1].N);
+  const int shares = in_order ? (n1 + kOrderShare - 1) / kOrderShare : 0, bin = csf ? 0 : shares;
+  int32_t *noted = key1, *hist = reinterpret_cast<int32_t*>(vec1);  // free until the rows are made
   const int search = csf && nnz > 0 ? ((n1 + 1) * kBoundLanes + kBlock - 1) / kBlock : 0;
-  if (fill + search > 0) {
-    hipLaunchKernelGGL(mttkrp_prepare_kernel<T>, dim3(fill + search), dim3(kBlock), 0, s, A, size, fill, n1, P.chunk,
-                       (int)nsl, (int)nfib, B->level[1].pos, B->level[2].pos, bounds);
+  if (fill + search + bin > 0) {
+    hipLaunchKernelGGL(mttkrp_prepare_kernel<T>, dim3(fill + search + bin), dim3(kBlock), 0, s, A, size, fill, n1, P.chunk,
+                       (int)nsl, (int)nfib, B->level[1].pos, B->level[2].pos, bounds, bin, digit, B->level[1].crd, nnz, noted, hist);
     SPT_CHECK_LAUNCH("mttkrp prepare");
   }
   if (nnz == 0 || J == 0) return SPT_OK;
-  const CsfLevels up{B->level[0].crd, B->level[1].pos, B->level[1].crd, B->level[2].pos, bounds};
+  const CsfLevels up{B->level[0].crd, B->level[1].pos, B->level[1].crd, B->level[2].pos, bounds, (int)nsl, (int)nfib};
+  if (in_order) {
+    if (csf) {
+      hipLaunchKernelGGL(mttkrp_bin_kernel, dim3(shares), dim3(kBlock), 0, s, n1, digit, up, noted, hist);
+      SPT_CHECK_LAUNCH("mttkrp bins");
+    }
+    hipLaunchKernelGGL(mttkrp_order_kernel, dim3(shares), dim3(kBlock), 0, s, n1, noted, hist, bounds);
+    SPT_CHECK_LAUNCH("mttkrp order");
+  }
+  const int32_t* order = in_order ? bounds : nullptr;
   const int tiles = ((J + P.vec - 1) / P.vec + P.lanes - 1) / P.lanes;
   const size_t lds = csf ? (size_t)P.chunk * 8 + 2 * (size_t)((P.chunk + 31) / 32) * 6 : 0;
 #define SPT_MTTKRP(L_, V_)                                                                                           \
   if (csf)                                                                                                           \
     hipLaunchKernelGGL((mttkrp_rows_kernel<T, L_, V_, true>), dim3(n1, tiles), dim3(kBlock), lds, s, nnz, J, P.epg,  \
-                       nullptr, nullptr, B->level[2].crd, static_cast<const T*>(B->vals), Cm, Dm, up, A, key1, vec1); \
+                       nullptr, nullptr, B->level[2].crd, static_cast<const T*>(B->vals), Cm, Dm, up, A, key1, vec1, order); \
   else                                                                                                               \
     hipLaunchKernelGGL((mttkrp_rows_kernel<T, L_, V_, false>), dim3(n1, tiles), dim3(kBlock), 0, s, nnz, J, P.epg,   \
                        B->level[0].crd, B->level[1].crd, B->level[2].crd, static_cast<const T*>(B->vals), Cm, Dm, up, \
-                       A, key1, vec1)
+                       A, key1, vec1, order)
   if (P.vec == 1) { SPT_MTTKRP(4, 1); }
   else if (P.lanes == 2) { SPT_MTTKRP(2, kVec<T>); }
   else if (P.lanes == 4) { SPT_MTTKRP(4, kVec<T>); }

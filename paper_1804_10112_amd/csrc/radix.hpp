@@ -34,6 +34,21 @@ struct StretchDigit {
   __device__ __forceinline__ int of(int32_t key) const { return __umulhi(static_cast<uint32_t>(key), mult); }
 };
 
+// The lanes of `among` whose eight bits are those of this one. What differs is gathered with a bit of d as 0 or ~0, against
+// which both halves of the lanes that have it take one exclusive or each (selecting the lanes or their complement, the
+// compiler needs twice as many instructions).
+__device__ __forceinline__ uint64_t lanes_with(int d, uint64_t among) {
+  uint32_t lo = 0, hi = 0;
+#pragma unroll
+  for (int b = 0; b < kRadixBits; ++b) {
+    const uint32_t bit = static_cast<uint32_t>(__builtin_amdgcn_sbfe(d, b, 1));
+    const uint64_t vote = __ballot(bit != 0);
+    lo |= static_cast<uint32_t>(vote) ^ bit;
+    hi |= static_cast<uint32_t>(vote >> 32) ^ bit;
+  }
+  return among & ~(static_cast<uint64_t>(hi) << 32 | lo);
+}
+
 // One more key with digit d in each of the wave's 64 lanes (all active, lane order =
 // key order up to a fixed stride). Sorted input (a long row, a long fibre) gives
 // neighbouring lanes the same digit, and separate LDS atomics on one counter are

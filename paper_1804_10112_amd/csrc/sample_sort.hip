@@ -587,21 +587,6 @@ __global__ __launch_bounds__(kOffBlock) void offsets_kernel(int ntiles1, const T
   if (!LEVEL2 && threadIdx.x == 0) total[g] = run;
 }
 
-// The lanes of `among` whose eight bits are those of this one. What differs is gathered with a bit of d as 0 or ~0, against
-// which both halves of the lanes that have it take one exclusive or each (selecting the lanes or their complement, the
-// compiler needs twice as many instructions).
-__device__ __forceinline__ uint64_t lanes_with(int d, uint64_t among) {
-  uint32_t lo = 0, hi = 0;
-#pragma unroll
-  for (int b = 0; b < kRadixBits; ++b) {
-    const uint32_t bit = static_cast<uint32_t>(__builtin_amdgcn_sbfe(d, b, 1));
-    const uint64_t vote = __ballot(bit != 0);
-    lo |= static_cast<uint32_t>(vote) ^ bit;
-    hi |= static_cast<uint32_t>(vote >> 32) ^ bit;
-  }
-  return among & ~(static_cast<uint64_t>(hi) << 32 | lo);
-}
-
 // Stable scatter of one tile by the noted buckets; ranks as in the radix scatter: a ballot match
 // inside the wave plus per-wave counters, then the tile is put in bucket order in LDS so that
 // consecutive lanes store to consecutive addresses.

@@ -141,10 +141,15 @@ __device__ __forceinline__ void bin_chunks(int share, int nchunks, const Stretch
   for (int k = 0; k < kOwn; ++k)
     if (first + k * kWave < nchunks) noted[first + k * kWave] = d[k] << 16 | (s_before[w][d[k]] + rank[k]);
 }
-// Of CSF tensors: the row of the first fibre that starts in or after a chunk.
-__global__ __launch_bounds__(kBlock) void mttkrp_bin_kernel(int nchunks, const StretchDigit digit, const CsfLevels csf,
+// COO: the row of a chunk's middle entry; CSF: of the first fibre that starts in or after the chunk.
+template <bool CSF>
+__global__ __launch_bounds__(kBlock) void mttkrp_bin_kernel(int n, int chunk, int nchunks, const StretchDigit digit,
+                                                            const int32_t* __restrict__ ck, const CsfLevels csf,
                                                             int32_t* __restrict__ noted, int32_t* __restrict__ hist) {
-  bin_chunks(blockIdx.x, nchunks, digit, [&](int c) { return csf.crd1[min(csf.bounds[3 * c], csf.nfibres - 1)]; }, noted, hist);
+  bin_chunks(blockIdx.x, nchunks, digit, [&](int c) {
+    if (CSF) return csf.crd1[min(csf.bounds[3 * c], csf.nfibres - 1)];
+    return ck[min(static_cast<int64_t>(c) * chunk + chunk / 2, static_cast<int64_t>(n) - 1)];
+  }, noted, hist);
 }
 __global__ __launch_bounds__(kBlock) void mttkrp_order_kernel(int nchunks, const int32_t* __restrict__ noted,
                                                               const int32_t* __restrict__ hist, int32_t* __restrict__ bounds) {
@@ -183,22 +188,14 @@ __global__ __launch_bounds__(kBlock) void mttkrp_order_kernel(int nchunks, const
 // Zeroes A (rows without entries stay zero). CSF: for chunk boundary c (entries from c * chunk on),
 // bounds[3c] = first fibre that starts at or after it, bounds[3c+1] = first slice that starts at or
 // after that fibre (as the end of a chunk: all slices once the fibres are used up). Boundary nchunks is the end. Eight
-// lanes search a boundary. (bounds[3c+2]: the order of the chunks.) COO: the last workgroups bin the chunks, if asked to.
+// lanes search a boundary. (bounds[3c+2]: the order of the chunks.)
 constexpr int kBoundLanes = 8;
 template <typename T>
 __global__ __launch_bounds__(kBlock) void mttkrp_prepare_kernel(T* __restrict__ A, int64_t size, int fill_blocks,
                                                                 int nchunks, int chunk, int nslices, int nfibres,
                                                                 const int32_t* __restrict__ pos1,
                                                                 const int32_t* __restrict__ pos2,
-                                                                int32_t* __restrict__ bounds, int bin_blocks,
-                                                                const StretchDigit digit, const int32_t* __restrict__ ck,
-                                                                int nnz, int32_t* __restrict__ noted, int32_t* __restrict__ hist) {
-  const int binned = static_cast<int>(blockIdx.x) - (static_cast<int>(gridDim.x) - bin_blocks);
-  if (binned >= 0) {
-    bin_chunks(binned, nchunks, digit, [&](int c) { return ck[min(static_cast<int64_t>(c) * chunk + chunk / 2, static_cast<int64_t>(nnz) - 1)]; },
-               noted, hist);
-    return;
-  }
+                                                                int32_t* __restrict__ bounds) {
   if (static_cast<int>(blockIdx.x) < fill_blocks) {
     typedef T V __attribute__((ext_vector_type(kVec<T>), aligned(sizeof(T))));
     const int64_t e = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) * kVec<T>;
@@ -242,14 +239,14 @@ __device__ __forceinline__ void marks_before(const uint32_t* marks, int16_t* bef
   }
 }
 
-template <typename T, int L, int V, bool CSF>
+template <typename T, int L, int V, bool CSF, bool ORDERED>
 __global__ __launch_bounds__(kBlock) void mttkrp_rows_kernel(int n, int J, int epg, const int32_t* __restrict__ ci,
                                                              const int32_t* __restrict__ ck,
                                                              const int32_t* __restrict__ cl,
                                                              const T* __restrict__ vals, const T* __restrict__ Cm,
                                                              const T* __restrict__ Dm, const CsfLevels csf,
                                                              T* __restrict__ A, int32_t* __restrict__ carry_key,
-                                                             T* __restrict__ carry_vec, const int32_t* __restrict__ order) {
+                                                             T* __restrict__ carry_vec, const int32_t* __restrict__ bounds) {
   constexpr int NG = kBlock / L, kGroupsOfWave = kWave / L;
   extern __shared__ __attribute__((aligned(16))) int32_t s_csf[];
   __shared__ T s_v[kBlock / kWave][L][V];
@@ -258,7 +255,8 @@ __global__ __launch_bounds__(kBlock) void mttkrp_rows_kernel(int n, int J, int e
   const int tid = threadIdx.x, lane = lane_id();
   const int g = tid / L, gl = tid % L;
   // (in turn to the XCDs: in one piece, the last has the slices of few entries, whose rows of C nobody shares)
-  const int chunk = order ? order[3 * xcd_contiguous_block_id(blockIdx.x, gridDim.x) + 2] : static_cast<int>(blockIdx.x), size = NG * epg;
+  const int chunk = ORDERED ? bounds[3 * xcd_contiguous_block_id(blockIdx.x, gridDim.x) + 2] : static_cast<int>(blockIdx.x);
+  const int size = NG * epg;
   const int base = chunk * size, end = min(base + size, n);
   // the last vector of a row ends with the row (it repeats columns of the one before if J is no multiple of V)
   const bool jok = (static_cast<int>(blockIdx.y) * L + gl) * V < J;
@@ -609,26 +607,36 @@ struct MttkrpPlan {
 };
 
 // Lanes: the vectors of a row, up to 32 (longer rows take several passes over the entries, side by
-// side). Entries of a group: enough workgroups for six on every compute unit while a group keeps at least
-// 16 entries, which its fixed work (bounds, scan, carry) is worth, and at most 2048 entries per workgroup
+// side). Entries of a group: 16, which its fixed work (bounds, scan, carry) is worth, while all workgroups then fit the
+// compute units at a time (their registers: five of a COO tensor to each, four of CSF); beyond, as many as leave about six
+// workgroups to each, in whole batches of the coordinates that the group's lanes hold (four each), since a part
+// of one costs as much; at most 2048 entries per workgroup
 // (measured with 512 to 4096: more entries keep fewer rows of C in cache, fewer leave more carries;
-// up to 10 % apart) and 128 per group.
-static MttkrpPlan mttkrp_plan(int64_t nnz, int64_t J, int dtype) {
+// up to 10 % apart) and 128 per group. In multiples of 16 / in batches, J = 32, us:
+//   CSF, fp32: 600 000 entries 36.3 / 32.8; 1.3M 56.6 / 47.1; 3M 77.9 / 75.3; fp64: 600 000 58.7 / 51.0; 2M 111 / 107
+//   COO, fp32: 900 000 entries 33.2 / 31.3; 1.3M 45.2 / 38.4; 3M 71.3 / 70.6; fp64: 600 000 50.5 / 44.2; 2M 106 / 100
+// (32 lanes: batches of 128 entries are too long, 400 000 entries 65.6 in 16, 68.0.)
+static MttkrpPlan mttkrp_plan(int64_t nnz, int64_t J, int dtype, bool csf) {
   MttkrpPlan P;
   P.vec = dtype == SPT_F64 ? kVec<double> : kVec<float>;
   if (J < P.vec) P.vec = 1;
   const int64_t nv = (J + P.vec - 1) / P.vec;
   P.lanes = P.vec == 1 ? 4 : nv <= 2 ? 2 : nv <= 4 ? 4 : nv <= 8 ? 8 : nv <= 16 ? 16 : 32;
   const int groups = kBlock / P.lanes;
+  const int batch = P.lanes <= 16 ? std::max(4 * P.lanes, 16) : 16;
+  const int64_t once = int64_t(csf ? 4 : 5) * 256 * groups * 16;
   const int64_t want = nnz / (6 * 256) / groups;
-  P.epg = static_cast<int>(std::min<int64_t>(std::max<int64_t>(want / 16 * 16, 16), std::min(128, 2048 / groups)));
+  int64_t epg = 16;
+  if (P.lanes > 16) epg = std::max<int64_t>(want / 16 * 16, 16);
+  else if (nnz > once) epg = std::max<int64_t>((want + batch / 2) / batch * batch, batch);
+  P.epg = static_cast<int>(std::min<int64_t>(epg, std::min(128, 2048 / groups)));
   P.chunk = P.epg * groups;
   P.n1 = (nnz + P.chunk - 1) / P.chunk;
   P.n2 = (P.n1 + kCarrySpan - 1) / kCarrySpan;
   return P;
 }
 
-// Is it worth 7 us (CSF 10) to order the chunks by their rows of C? An L2 has to be too small for the factors, C to be
+// Is it worth 10 us to order the chunks by their rows of C? An L2 has to be too small for the factors, C to be
 // the larger part of an eighth's traffic saved, and the gathers long enough. Given order / ordered, us:
 //   COO, slices of 10 000 entries, C and D 10.2 and 6.4 MB, 20M entries 536 / 361; C and D 7.7 MB, 5M 149 / 131
 //   COO, skewed slices, 10.2 and 6.4 MB, 50M 648 / 617; 12.8 and 12.8, 20M (fp64) 389 / 370; 6.4 and 6.4, 10M 185 / 176;
@@ -642,7 +650,7 @@ static bool mttkrp_orders(const MttkrpPlan& P, int64_t nnz, int64_t J, int64_t v
 }
 
 size_t mttkrp3_workspace(const spt_tensor* B, int32_t J) {
-  const MttkrpPlan P = mttkrp_plan(B->nvals, std::max(J, 1), B->dtype);
+  const MttkrpPlan P = mttkrp_plan(B->nvals, std::max(J, 1), B->dtype, B->level[1].kind == SPT_COMPRESSED);
   const size_t row = static_cast<size_t>(std::max(J, 1)) * (B->dtype == SPT_F64 ? 8 : 4);
   return align_up(static_cast<size_t>(P.n1) * 4, 256) + align_up(P.n1 * row, 256) +
          align_up(static_cast<size_t>(P.n2) * 4, 256) + align_up(P.n2 * row, 256) +
@@ -655,7 +663,7 @@ static spt_status mttkrp3_typed(Format f, const spt_tensor* B, const T* Cm, cons
   const int64_t I = B->level[0].N, nnz64 = B->nvals, size = I * J;
   const bool csf = f == Format::CSF3;
   const int64_t nsl = csf ? B->level[1].M : 0, nfib = csf ? B->level[2].M : 0;
-  const MttkrpPlan P = mttkrp_plan(nnz64, J, B->dtype);
+  const MttkrpPlan P = mttkrp_plan(nnz64, J, B->dtype, csf);
   if (nnz64 + P.chunk >= INT32_MAX || size >= ((int64_t)1 << 38) || nsl + 1 >= INT32_MAX || nfib + 1 >= INT32_MAX)
     return fail(SPT_ERR_UNSUPPORTED, "mttkrp: tensor too large");
   if (nnz64 > 0 && (!ws || ws_bytes < mttkrp3_workspace(B, J)))
@@ -672,37 +680,38 @@ static spt_status mttkrp3_typed(Format f, const spt_tensor* B, const T* Cm, cons
     bounds = W.take<int32_t>(3 * ((size_t)n1 + 1));
   }
   const int fill = (int)((size + kBlock * kVec<T> - 1) / (kBlock * kVec<T>));
-  const bool in_order = mttkrp_orders(P, nnz64, J, sizeof(T), B->level[1].N, B->level[2].N);
-  const StretchDigit digit(B->level[1].N);
-  const int shares = in_order ? (n1 + kOrderShare - 1) / kOrderShare : 0, bin = csf ? 0 : shares;
-  int32_t *noted = key1, *hist = reinterpret_cast<int32_t*>(vec1);  // free until the rows are made
   const int search = csf && nnz > 0 ? ((n1 + 1) * kBoundLanes + kBlock - 1) / kBlock : 0;
-  if (fill + search + bin > 0) {
-    hipLaunchKernelGGL(mttkrp_prepare_kernel<T>, dim3(fill + search + bin), dim3(kBlock), 0, s, A, size, fill, n1, P.chunk,
-                       (int)nsl, (int)nfib, B->level[1].pos, B->level[2].pos, bounds, bin, digit, B->level[1].crd, nnz, noted, hist);
+  if (fill + search > 0) {
+    hipLaunchKernelGGL(mttkrp_prepare_kernel<T>, dim3(fill + search), dim3(kBlock), 0, s, A, size, fill, n1, P.chunk,
+                       (int)nsl, (int)nfib, B->level[1].pos, B->level[2].pos, bounds);
     SPT_CHECK_LAUNCH("mttkrp prepare");
   }
   if (nnz == 0 || J == 0) return SPT_OK;
   const CsfLevels up{B->level[0].crd, B->level[1].pos, B->level[1].crd, B->level[2].pos, bounds, (int)nsl, (int)nfib};
+  const bool in_order = mttkrp_orders(P, nnz64, J, sizeof(T), B->level[1].N, B->level[2].N);
   if (in_order) {
-    if (csf) {
-      hipLaunchKernelGGL(mttkrp_bin_kernel, dim3(shares), dim3(kBlock), 0, s, n1, digit, up, noted, hist);
-      SPT_CHECK_LAUNCH("mttkrp bins");
-    }
+    const StretchDigit digit(B->level[1].N);
+    const int shares = (n1 + kOrderShare - 1) / kOrderShare;
+    int32_t *noted = key1, *hist = reinterpret_cast<int32_t*>(vec1);  // free until the rows are made
+    if (csf)
+      hipLaunchKernelGGL(mttkrp_bin_kernel<true>, dim3(shares), dim3(kBlock), 0, s, nnz, P.chunk, n1, digit, nullptr, up, noted, hist);
+    else
+      hipLaunchKernelGGL(mttkrp_bin_kernel<false>, dim3(shares), dim3(kBlock), 0, s, nnz, P.chunk, n1, digit, B->level[1].crd, up, noted, hist);
+    SPT_CHECK_LAUNCH("mttkrp bins");
     hipLaunchKernelGGL(mttkrp_order_kernel, dim3(shares), dim3(kBlock), 0, s, n1, noted, hist, bounds);
     SPT_CHECK_LAUNCH("mttkrp order");
   }
-  const int32_t* order = in_order ? bounds : nullptr;
   const int tiles = ((J + P.vec - 1) / P.vec + P.lanes - 1) / P.lanes;
   const size_t lds = csf ? (size_t)P.chunk * 8 + 2 * (size_t)((P.chunk + 31) / 32) * 6 : 0;
-#define SPT_MTTKRP(L_, V_)                                                                                           \
-  if (csf)                                                                                                           \
-    hipLaunchKernelGGL((mttkrp_rows_kernel<T, L_, V_, true>), dim3(n1, tiles), dim3(kBlock), lds, s, nnz, J, P.epg,  \
-                       nullptr, nullptr, B->level[2].crd, static_cast<const T*>(B->vals), Cm, Dm, up, A, key1, vec1, order); \
-  else                                                                                                               \
-    hipLaunchKernelGGL((mttkrp_rows_kernel<T, L_, V_, false>), dim3(n1, tiles), dim3(kBlock), 0, s, nnz, J, P.epg,   \
-                       B->level[0].crd, B->level[1].crd, B->level[2].crd, static_cast<const T*>(B->vals), Cm, Dm, up, \
-                       A, key1, vec1, order)
+#define SPT_MTTKRP_AS(L_, V_, CSF_, ORDERED_)                                                                           \
+  hipLaunchKernelGGL((mttkrp_rows_kernel<T, L_, V_, CSF_, ORDERED_>), dim3(n1, tiles), dim3(kBlock), lds, s, nnz, J, P.epg, \
+                     csf ? nullptr : B->level[0].crd, csf ? nullptr : B->level[1].crd, B->level[2].crd,                  \
+                     static_cast<const T*>(B->vals), Cm, Dm, up, A, key1, vec1, bounds)
+#define SPT_MTTKRP(L_, V_)                             \
+  if (csf && in_order) SPT_MTTKRP_AS(L_, V_, true, true);   \
+  else if (csf) SPT_MTTKRP_AS(L_, V_, true, false);         \
+  else if (in_order) SPT_MTTKRP_AS(L_, V_, false, true);    \
+  else SPT_MTTKRP_AS(L_, V_, false, false)
   if (P.vec == 1) { SPT_MTTKRP(4, 1); }
   else if (P.lanes == 2) { SPT_MTTKRP(2, kVec<T>); }
   else if (P.lanes == 4) { SPT_MTTKRP(4, kVec<T>); }
@@ -710,6 +719,7 @@ static spt_status mttkrp3_typed(Format f, const spt_tensor* B, const T* Cm, cons
   else if (P.lanes == 16) { SPT_MTTKRP(16, kVec<T>); }
   else { SPT_MTTKRP(32, kVec<T>); }
 #undef SPT_MTTKRP
+#undef SPT_MTTKRP_AS
   SPT_CHECK_LAUNCH("mttkrp rows");
   if (n1 <= kCarryRunsMax) {
     int log_cols = 2;

@@ -376,7 +376,7 @@ __global__ __launch_bounds__(kBlock) void bin_reduce_kernel(const Cut cut, const
 
 // x slice by slice from here on. Unsliced / sliced, uniform columns, us: fp64, 6.4 MB, 1.6M entries 44 / 53, 3.2M 66 / 70,
 // 6.4M 111 / 105; 16 MB, 8M 183 / 134; 32 MB, 16M 389 / 273; fp32, 6.4 MB, 3.2M 60 / 59, 6.4M 96 / 86; shuffled
-// entries of a banded matrix, fp64, 32 MB, 28M 575 / 407.
+// entries of a banded matrix, fp64, 32 MB, 28M 575 / 407. (30M, fp64, 64 MB, in slices of 3.2 MB 714, of 5.6 627.)
 constexpr int64_t kSlicedMinEntries = int64_t(1) << 22;
 
 struct BinPlan {
@@ -423,7 +423,7 @@ static spt_status binned_spmv(int nnz, int64_t nrows, int64_t ncols, const int32
   const StretchDigit digit(nrows);
   const int64_t xbytes = ncols * (int64_t)sizeof(T);
   const bool sliced = nnz >= kSlicedMinEntries && xbytes > kSlicesMinX && xbytes <= kSlicesMaxX;
-  const int nslices = sliced ? (int)((xbytes + kSliceBytes - 1) / kSliceBytes) : 1;
+  const int nslices = sliced ? slices_of(ncols, sizeof(T), int64_t(2) * 256 * kTileMost) : 1;
   const int slice = (int)((ncols + nslices - 1) / nslices * sizeof(T));
 #define SPT_TILE(V_, SLICED_)                                                                                             \
   hipLaunchKernelGGL((bin_tile_kernel<T, R, V_, SLICED_>), dim3(P.ntiles), dim3(kTileBlock), 0, s, nnz, digit, P.tile, row, col, \

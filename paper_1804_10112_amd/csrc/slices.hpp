@@ -1,11 +1,27 @@
 // Gathers from a vector that no L2 holds, slice by slice, in registers.
 #pragma once
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace spt {
 
 // An x that an L2 holds need not be cut; beyond some 150 MB the passes cost more than the lines.
-constexpr int64_t kSlicesMinX = 6000000, kSlicesMaxX = 128000000, kSliceBytes = 3200000;
+constexpr int64_t kSlicesMinX = 6000000, kSlicesMaxX = 128000000;
+
+// Slices of an x, of which an XCD gathers `entries` / kXcds entries at a time (`entries`: of all). A slice that an L2
+// holds next to what streams through it, 3.2 MB, where a line of x serves several of them; where it serves fewer, a miss more
+// or less counts less than one more slice to go through: up to 5.6 MB. Whole product of 60M entries (40M: marked), uniform
+// columns, with slices of 3.2 / 4.2 / 5.4 / 7 MB, us:
+//   x, MB             32 (power law)          48 (40M)               64                     96                    120
+//   fp64      547 / 573 / 627 /  -     432 / 415 / 420 / 474  721 / 671 / 657 / 706  938 / 817 / 778 / 796  1094 / 953 / 877 / 860
+//   fp32                                                       584 / 590 / 632 / 701                        728 / 734 / 736 / 781
+inline int slices_of(int64_t ncols, int64_t value, int64_t entries) {
+  const int64_t x = ncols * value;
+  const double of_a_line = static_cast<double>(entries) / kXcds / (static_cast<double>(x) / 128);
+  const int64_t bytes = static_cast<int64_t>(3200000 * std::min(std::max(4.5 / of_a_line, 1.0), 1.75));
+  return static_cast<int>((x + bytes - 1) / bytes);
+}
 
 constexpr int kSegment = 4 * kWave;  // consecutive entries that a wave reduces at a time
 
@@ -98,5 +114,75 @@ struct SliceGather;
   };
 SPT_SLICE_GATHER(double, 32, SPT_GATHER_LOAD2)
 SPT_SLICE_GATHER(float, 32, SPT_GATHER_LOAD1)
+
+// The same with more entries to a lane: got[k] holds the byte offset of entry k in its first 32 bits, and the value takes
+// its place, in the registers from v48 on, which are named here since an operand's first half has no name. What is still
+// to be gathered is kept as a bit per entry: a register may look like an offset once its load has been issued, or be
+// read while the load is on its way, in lanes whose bit is cleared. An offset beyond every slice is left as it is.
+template <typename T>
+struct SliceGatherInPlace;
+template <typename T>
+constexpr int kInPlace = sizeof(T) == 8 ? 40 : 64;  // entries to a lane
+
+// (entry, its bit, of which register, the registers of its value)
+#define SPT_PLACES_double(M) \
+  M(0, 0x1, 0, 48, 49) M(1, 0x2, 0, 50, 51) M(2, 0x4, 0, 52, 53) M(3, 0x8, 0, 54, 55) M(4, 0x10, 0, 56, 57) M(5, 0x20, 0, 58, 59) \
+   M(6, 0x40, 0, 60, 61) M(7, 0x80, 0, 62, 63) M(8, 0x100, 0, 64, 65) M(9, 0x200, 0, 66, 67) M(10, 0x400, 0, 68, 69) M(11, 0x800, 0, 70, 71) \
+   M(12, 0x1000, 0, 72, 73) M(13, 0x2000, 0, 74, 75) M(14, 0x4000, 0, 76, 77) M(15, 0x8000, 0, 78, 79) M(16, 0x10000, 0, 80, 81) M(17, 0x20000, 0, 82, 83) \
+   M(18, 0x40000, 0, 84, 85) M(19, 0x80000, 0, 86, 87) M(20, 0x100000, 0, 88, 89) M(21, 0x200000, 0, 90, 91) M(22, 0x400000, 0, 92, 93) M(23, 0x800000, 0, 94, 95) \
+   M(24, 0x1000000, 0, 96, 97) M(25, 0x2000000, 0, 98, 99) M(26, 0x4000000, 0, 100, 101) M(27, 0x8000000, 0, 102, 103) M(28, 0x10000000, 0, 104, 105) M(29, 0x20000000, 0, 106, 107) \
+   M(30, 0x40000000, 0, 108, 109) M(31, 0x80000000, 0, 110, 111) M(32, 0x1, 1, 112, 113) M(33, 0x2, 1, 114, 115) M(34, 0x4, 1, 116, 117) M(35, 0x8, 1, 118, 119) \
+   M(36, 0x10, 1, 120, 121) M(37, 0x20, 1, 122, 123) M(38, 0x40, 1, 124, 125) M(39, 0x80, 1, 126, 127)
+#define SPT_PLACES_float(M) \
+  M(0, 0x1, 0, 48, 48) M(1, 0x2, 0, 49, 49) M(2, 0x4, 0, 50, 50) M(3, 0x8, 0, 51, 51) M(4, 0x10, 0, 52, 52) M(5, 0x20, 0, 53, 53) \
+   M(6, 0x40, 0, 54, 54) M(7, 0x80, 0, 55, 55) M(8, 0x100, 0, 56, 56) M(9, 0x200, 0, 57, 57) M(10, 0x400, 0, 58, 58) M(11, 0x800, 0, 59, 59) \
+   M(12, 0x1000, 0, 60, 60) M(13, 0x2000, 0, 61, 61) M(14, 0x4000, 0, 62, 62) M(15, 0x8000, 0, 63, 63) M(16, 0x10000, 0, 64, 64) M(17, 0x20000, 0, 65, 65) \
+   M(18, 0x40000, 0, 66, 66) M(19, 0x80000, 0, 67, 67) M(20, 0x100000, 0, 68, 68) M(21, 0x200000, 0, 69, 69) M(22, 0x400000, 0, 70, 70) M(23, 0x800000, 0, 71, 71) \
+   M(24, 0x1000000, 0, 72, 72) M(25, 0x2000000, 0, 73, 73) M(26, 0x4000000, 0, 74, 74) M(27, 0x8000000, 0, 75, 75) M(28, 0x10000000, 0, 76, 76) M(29, 0x20000000, 0, 77, 77) \
+   M(30, 0x40000000, 0, 78, 78) M(31, 0x80000000, 0, 79, 79) M(32, 0x1, 1, 80, 80) M(33, 0x2, 1, 81, 81) M(34, 0x4, 1, 82, 82) M(35, 0x8, 1, 83, 83) \
+   M(36, 0x10, 1, 84, 84) M(37, 0x20, 1, 85, 85) M(38, 0x40, 1, 86, 86) M(39, 0x80, 1, 87, 87) M(40, 0x100, 1, 88, 88) M(41, 0x200, 1, 89, 89) \
+   M(42, 0x400, 1, 90, 90) M(43, 0x800, 1, 91, 91) M(44, 0x1000, 1, 92, 92) M(45, 0x2000, 1, 93, 93) M(46, 0x4000, 1, 94, 94) M(47, 0x8000, 1, 95, 95) \
+   M(48, 0x10000, 1, 96, 96) M(49, 0x20000, 1, 97, 97) M(50, 0x40000, 1, 98, 98) M(51, 0x80000, 1, 99, 99) M(52, 0x100000, 1, 100, 100) M(53, 0x200000, 1, 101, 101) \
+   M(54, 0x400000, 1, 102, 102) M(55, 0x800000, 1, 103, 103) M(56, 0x1000000, 1, 104, 104) M(57, 0x2000000, 1, 105, 105) M(58, 0x4000000, 1, 106, 106) M(59, 0x8000000, 1, 107, 107) \
+   M(60, 0x10000000, 1, 108, 108) M(61, 0x20000000, 1, 109, 109) M(62, 0x40000000, 1, 110, 110) M(63, 0x80000000, 1, 111, 111)
+#define SPT_PLACE_OPERAND_double(K, BIT, W, LO, HI) "+{v[" #LO ":" #HI "]}"(got[K]),
+#define SPT_PLACE_OPERAND_float(K, BIT, W, LO, HI) "+{v" #LO "}"(got[K]),
+#define SPT_PLACE_LOAD_double(LO, HI) "global_load_dwordx2 v[" #LO ":" #HI "], v" #LO ", %[x]\n"
+#define SPT_PLACE_LOAD_float(LO, HI) "global_load_dword v" #LO ", v" #LO ", %[x]\n"
+#define SPT_PLACE_STEP(T, K, BIT, W, LO, HI)       \
+  "s_mov_b64 exec, %[all]\n\t"                     \
+  "v_and_b32 %[bit], " #BIT ", %[todo" #W "]\n\t"  \
+  "v_subrev_u32 %[rel], %[lo], v" #LO "\n\t"       \
+  "v_cmpx_gt_u32 vcc, %[bytes], %[rel]\n\t"        \
+  "v_cmpx_ne_u32 vcc, 0, %[bit]\n\t"               \
+  "s_cbranch_execz 1f\n\t"                         \
+  "v_xor_b32 %[todo" #W "], " #BIT ", %[todo" #W "]\n\t" SPT_PLACE_LOAD_##T(LO, HI) \
+  "1:\n\t"
+#define SPT_PLACE_STEP_double(K, BIT, W, LO, HI) SPT_PLACE_STEP(double, K, BIT, W, LO, HI)
+#define SPT_PLACE_STEP_float(K, BIT, W, LO, HI) SPT_PLACE_STEP(float, K, BIT, W, LO, HI)
+#define SPT_GATHER_IN_PLACE(T)                                                                                    \
+  template <>                                                                                                     \
+  struct SliceGatherInPlace<T> {                                                                                  \
+    static __device__ __forceinline__ void run(const T* x, int n, uint32_t bytes, T (&got)[kInPlace<T>]) {        \
+      uint32_t lo, rel, bit, todo0 = ~0u, todo1 = ~0u;                                                            \
+      uint64_t all;                                                                                               \
+      asm volatile("s_mov_b64 %[all], exec\n\t"                                                                   \
+                   "s_mov_b32 %[lo], 0\n"                                                                         \
+                   "0:\n\t" SPT_PLACES_##T(SPT_PLACE_STEP_##T)                                                    \
+                   "s_mov_b64 exec, %[all]\n\t"                                                                   \
+                   "s_barrier\n\t"                                                                                \
+                   "s_add_u32 %[lo], %[lo], %[bytes]\n\t"                                                         \
+                   "s_sub_u32 %[n], %[n], 1\n\t"                                                                  \
+                   "s_cmp_lg_u32 %[n], 0\n\t"                                                                     \
+                   "s_cbranch_scc1 0b\n\t"                                                                        \
+                   "s_waitcnt vmcnt(0)"                                                                           \
+                   : SPT_PLACES_##T(SPT_PLACE_OPERAND_##T)[n] "+&s"(n), [lo] "=&s"(lo), [all] "=&s"(all),         \
+                     [rel] "=&v"(rel), [bit] "=&v"(bit), [todo0] "+&v"(todo0), [todo1] "+&v"(todo1)                \
+                   : [bytes] "s"(bytes), [x] "s"(x)                                                               \
+                   : "vcc", "scc", "memory");                                                                     \
+    }                                                                                                             \
+  };
+SPT_GATHER_IN_PLACE(double)
+SPT_GATHER_IN_PLACE(float)
 
 }  // namespace spt

@@ -1,10 +1,10 @@
 // SpMV on CSR and ordered COO whose columns lie anywhere in an x that no L2 holds: x is gathered slice by slice.
 //
 // Entry after entry, such gathers miss L2, and the fabric brings 64 G lines of 128 bytes a second, whatever is
-// used of them (60M entries, 4M columns, fp64: 57M lines, 0.95 ms). Here every compute unit holds 32 768 entries
-// at a time, 32 per lane, in registers, and the chip sweeps over x in slices of 3.2 MB, which an L2 of 4 MB holds:
+// used of them (60M entries, 4M columns, fp64: 57M lines, 0.95 ms). Here every compute unit holds 40 960 entries
+// (fp32: 65 536) at a time, 40 per lane, in registers, and the chip sweeps over x in slices of 3.2 MB, which an L2 of 4 MB holds:
 // in each, the entries whose column lies in it fetch their x, all others wait. A line of x is then brought to an
-// XCD once per 1M of its entries instead of once per entry: 26M lines, 0.57 ms.
+// XCD once per 1.3M of its entries instead of once per entry: 0.55 ms.
 //  * The waves of a workgroup meet after each slice; the workgroups of an XCD keep together by themselves, since
 //    the first to enter a slice wait for lines that the others then find. (Without the meeting 0.95 ms, the oldest
 //    waves run ahead; with a barrier across the XCD before the sweep 0.71, with one between slices slower still.)
@@ -12,8 +12,8 @@
 //    workgroups of consecutive entries would drift apart (0.86 ms; 2048 consecutive entries per wave: 0.73).
 //  * The number of workgroups is a multiple of the compute units, one of them to each (128 registers a lane): with
 //    as many as there are full ones, the last round took as long as the others (0.71 against 0.68 ms).
-//  * 3.2 MB: of 2 to 4 MB the time differs by 2 % at 32 MB; smaller slices cost a pass over the entries each
-//    (96 MB: 0.68 ms at 2.5 MB, 0.58 at 3.5). 36 entries per lane: 0.61 ms, with copies through scratch memory.
+//  * An offset's register becomes half of its value's, so that 40 entries fit where 32 with both did (8 rounds over x
+//    become 6). Small x and fewer entries keep the 32 (slices_of_many); larger x have larger slices (slices_of).
 // Bound by the address unit (a load with a few lanes takes it some 20 clocks), then the lines.
 #include <algorithm>
 
@@ -25,7 +25,12 @@
 namespace spt {
 
 constexpr int kSliceBlock = 1024, kSliceWaves = kSliceBlock / kWave;
-constexpr int kSegments = 8;  // of a wave, each a vector of four entries per lane
+constexpr int kFewSegments = 8;
+// Segments of a wave, each a vector of four entries per lane; and as many of them as have their row starts in LDS at a time (CSR).
+template <typename T, bool MANY>
+constexpr int kSegments = MANY ? kInPlace<T> / 4 : kFewSegments;
+template <typename T, bool MANY>
+constexpr int kRowBatch = MANY && sizeof(T) == 8 ? 6 : 8;
 constexpr int kCus = 256;
 
 // What precedes the product, kChoiceFlags workgroups.
@@ -298,19 +303,19 @@ __device__ __forceinline__ void segments_in_order(int nnz, int nseg, const int32
 
 // x slice by slice, all segments of a wave at once. CSR: the rows that start in a segment are entered at their first entry
 // in LDS.
-template <typename T, bool CSR>
+template <typename T, bool CSR, bool MANY>
 __global__ __launch_bounds__(kSliceBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) void slices_spmv_kernel(
     int nnz, int nseg, int nslices, int slice, bool rows_may, const int32_t* __restrict__ pos_or_row, const int32_t* __restrict__ col,
     const T* __restrict__ vals, const T* __restrict__ x, T* __restrict__ y, const int32_t* __restrict__ seg_row,
     int32_t* __restrict__ carry_key, T* __restrict__ carry_val, const uint8_t* __restrict__ flags) {
-  constexpr int V = kSegments;
+  constexpr int V = kSegments<T, MANY>, B = kRowBatch<T, MANY>;
   typedef T V4 __attribute__((ext_vector_type(4), aligned(sizeof(T))));
   typedef int32_t I4 __attribute__((ext_vector_type(4), aligned(4)));
   extern __shared__ __attribute__((aligned(16))) int32_t s_rows[];  // CSR: the row that starts at an entry, or -1
   const int choice = read_choice(flags);
   if (rows_may && choice == kByRows) return;
   const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
-  int32_t* heads = s_rows + w * (V * kSegment);
+  int32_t* heads = s_rows + w * (B * kSegment);
   if (choice != kBySlices) {
     segments_in_order<T, CSR>(nnz, nseg, pos_or_row, col, vals, x, y, seg_row, carry_key, carry_val, heads);
     return;
@@ -318,8 +323,8 @@ __global__ __launch_bounds__(kSliceBlock) __attribute__((amdgpu_waves_per_eu(4, 
   // segment of vector j: first + j * step, none from nseg on
   const int step = kSliceWaves * gridDim.x, first = w * gridDim.x + blockIdx.x;
 
-  uint32_t at[4 * V];
   T got[4 * V];
+  uint32_t offset[4 * V];
   constexpr uint32_t kNowhere = 0xFFFFFFFFu;
 #pragma unroll
   for (int j = 0; j < V; ++j) {
@@ -328,49 +333,58 @@ __global__ __launch_bounds__(kSliceBlock) __attribute__((amdgpu_waves_per_eu(4, 
     if (seg < nseg && p + kSegment <= nnz) {  // uniform
       const I4 c = __builtin_nontemporal_load(reinterpret_cast<const I4*>(col + p + lane * 4));
 #pragma unroll
-      for (int q = 0; q < 4; ++q) at[4 * j + q] = static_cast<uint32_t>(c[q]) * sizeof(T);
+      for (int q = 0; q < 4; ++q) offset[4 * j + q] = static_cast<uint32_t>(c[q]) * sizeof(T);
     } else {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int64_t e = p + lane * 4 + q;
-        at[4 * j + q] = seg < nseg && e < nnz ? static_cast<uint32_t>(col[e]) * sizeof(T) : kNowhere;
+        offset[4 * j + q] = seg < nseg && e < nnz ? static_cast<uint32_t>(col[e]) * sizeof(T) : kNowhere;
       }
     }
   }
+  if constexpr (MANY) {
 #pragma unroll
-  for (int k = 0; k < 4 * V; ++k) got[k] = 0;
-  SliceGather<T, 4 * V>::run(x, nslices, slice, at, got);
-
-  int r_first = 0;  // CSR, lane j: the first row that starts in segment j
-  if (CSR) {
-    constexpr int L = kWave / V;  // lanes that enter the rows of a segment
-    const int j = lane / L, seg = first + j * step, base = seg * kSegment;
-    const bool live = seg < nseg;
-    const int lo = live ? seg_row[seg] : 0, hi = live ? seg_row[seg + 1] : 0;
+    for (int k = 0; k < 4 * V; ++k) {
+      if constexpr (sizeof(T) == 8) got[k] = __hiloint2double(0, static_cast<int>(offset[k]));
+      else got[k] = __uint_as_float(offset[k]);
+    }
+    SliceGatherInPlace<T>::run(x, nslices, slice, got);
+  } else {
 #pragma unroll
-    for (int u = 0; u < V; ++u) *reinterpret_cast<I4*>(heads + u * kSegment + lane * 4) = I4(-1);
-    wave_lds_order();  // other lanes enter rows over what a lane has cleared
-    const bool many = hi - lo > kMany;
-    if (!many) {
-      for (int r = lo + lane % L; r < hi; r += L) {
-        const int a = pos_or_row[r], b = pos_or_row[r + 1];
-        if (b > a) heads[j * kSegment + a - base] = r;
-      }
-    }
-    uint64_t todo = __ballot(many && lane % L == 0);
-    while (todo) {
-      const int src = __ffsll(static_cast<long long>(todo)) - 1;
-      todo &= todo - 1;
-      look_up_rows(__builtin_amdgcn_readlane(lo, src), __builtin_amdgcn_readlane(hi, src), __builtin_amdgcn_readlane(base, src), nnz,
-                   pos_or_row, heads + __builtin_amdgcn_readlane(j, src) * kSegment);
-    }
-    wave_lds_order();  // and other lanes again read them
-    r_first = __shfl(lo, min(lane * L, kWave - 1));
+    for (int k = 0; k < 4 * V; ++k) got[k] = 0;
+    SliceGather<T, 4 * V>::run(x, nslices, slice, offset, got);
   }
 
   constexpr int kBatch = sizeof(T) == 8 ? 2 : 4;
+  static_assert(B % kBatch == 0 && V % kBatch == 0, "");
+  int r_first = 0;  // CSR, in lane l: the first row that starts in segment l / L of those in LDS
+  constexpr int L = kWave / B;  // lanes that enter the rows of a segment
 #pragma unroll
   for (int h = 0; h < V; h += kBatch) {
+    if (CSR && h % B == 0) {
+      const int j = lane / L, seg = first + (h + j) * step, base = seg * kSegment;
+      const bool live = j < B && h + j < V && seg < nseg;
+      const int lo = live ? seg_row[seg] : 0, hi = live ? seg_row[seg + 1] : 0;
+#pragma unroll
+      for (int u = 0; u < B; ++u) *reinterpret_cast<I4*>(heads + u * kSegment + lane * 4) = I4(-1);
+      wave_lds_order();  // other lanes enter rows over what a lane has cleared
+      const bool many = hi - lo > kMany;
+      if (!many) {
+        for (int r = lo + lane % L; r < hi; r += L) {
+          const int a = pos_or_row[r], b = pos_or_row[r + 1];
+          if (b > a) heads[j * kSegment + a - base] = r;
+        }
+      }
+      uint64_t todo = __ballot(many && lane % L == 0);
+      while (todo) {
+        const int src = __ffsll(static_cast<long long>(todo)) - 1;
+        todo &= todo - 1;
+        look_up_rows(__builtin_amdgcn_readlane(lo, src), __builtin_amdgcn_readlane(hi, src), __builtin_amdgcn_readlane(base, src), nnz,
+                     pos_or_row, heads + __builtin_amdgcn_readlane(j, src) * kSegment);
+      }
+      wave_lds_order();  // and other lanes again read them
+      r_first = lo;
+    }
     V4 v[kBatch];
     I4 rows[kBatch];
     int32_t prior[kBatch];  // COO: row of the entry before the segment
@@ -395,11 +409,12 @@ __global__ __launch_bounds__(kSliceBlock) __attribute__((amdgpu_waves_per_eu(4, 
     for (int j = 0; j < kBatch; ++j) {
       const int seg = first + (h + j) * step;
       if (seg >= nseg) break;  // uniform
-      if (CSR) rows[j] = *reinterpret_cast<const I4*>(heads + (h + j) * kSegment + lane * 4);
+      if (CSR) rows[j] = *reinterpret_cast<const I4*>(heads + (h + j) % B * kSegment + lane * 4);
       reduce_segment<T, CSR>(seg, nnz - static_cast<int64_t>(seg) * kSegment,
-                             CSR ? __builtin_amdgcn_readlane(r_first, h + j) - 1 : prior[j], v[j], got + 4 * (h + j), rows[j], y,
+                             CSR ? __builtin_amdgcn_readlane(r_first, (h + j) % B * L) - 1 : prior[j], v[j], got + 4 * (h + j), rows[j], y,
                              carry_key, carry_val);
     }
+    if (CSR) wave_lds_order();  // the next batch clears what lanes have read
   }
 }
 
@@ -451,17 +466,30 @@ spt_status launch_csr_skew(int64_t nnz, int64_t nrows, const int32_t* pos, uint8
   SPT_CHECK_LAUNCH("csr skew");
   return SPT_OK;
 }
+// Do the lanes hold as many entries as they can? Fewer rounds over x then bring fewer lines, but there are fewer workgroups
+// to take turns. 32 / 40 or 64 entries to a lane, x in MB, us: fp64, 60M, 32 568 / 545, 64 767 / 721; 40M, 28 354 / 354; 30M, 16
+// 246 / 249; 18M, 12 154 / 157; 20M, 64 280 / 275. fp32, 60M, 64 719 / 584; 40M, 16 285 / 276; 36M, 12 277 / 272; 24M, 8 176 / 179.
+static bool slices_of_many(int64_t nnz, int64_t ncols, int64_t value, int64_t entries) {
+  return nnz >= 32000000 || entries / kXcds < 8 * (ncols * value / 128);
+}
+
 template <typename T, bool CSR>
 spt_status launch_slices_spmv(int64_t nnz, int64_t ncols, bool rows_may, const int32_t* pos_or_row, const int32_t* col,
                               const T* vals, const T* x, T* y, void* ws, hipStream_t s) {
   const SlicesWorkspace W(nnz, ws);
-  constexpr int V = kSegments, kPer = kSliceWaves * V;
-  const int nslices = (int)((ncols * (int64_t)sizeof(T) + kSliceBytes - 1) / kSliceBytes);
+  const bool many = slices_of_many(nnz, ncols, sizeof(T), int64_t(kSliceBlock) * kCus * kInPlace<T>);
+  const int per = kSliceWaves * (many ? kSegments<T, true> : kFewSegments);
+  const int nslices = slices_of(ncols, sizeof(T), int64_t(per) * kSegment * kCus);
   const uint32_t slice = (uint32_t)((ncols + nslices - 1) / nslices * sizeof(T));
-  const int grid = ((W.nseg + kPer - 1) / kPer + kCus - 1) / kCus * kCus;
+  const int grid = ((W.nseg + per - 1) / per + kCus - 1) / kCus * kCus;
   T* cval = static_cast<T*>(W.carry_val);
-  hipLaunchKernelGGL((slices_spmv_kernel<T, CSR>), dim3(grid), dim3(kSliceBlock), CSR ? kPer * kSegment * 4 : 0, s, (int)nnz,
-                     W.nseg, nslices, (int)slice, rows_may, pos_or_row, col, vals, x, y, W.seg_row, W.carry_key, cval, W.flags);
+  const int lds = CSR ? kSliceWaves * kSegment * 4 * (many ? kRowBatch<T, true> : kRowBatch<T, false>) : 0;
+#define SPT_SLICES_SPMV(MANY_)                                                                                        \
+  hipLaunchKernelGGL((slices_spmv_kernel<T, CSR, MANY_>), dim3(grid), dim3(kSliceBlock), lds, s, (int)nnz, W.nseg,     \
+                     nslices, (int)slice, rows_may, pos_or_row, col, vals, x, y, W.seg_row, W.carry_key, cval, W.flags)
+  if (many) SPT_SLICES_SPMV(true);
+  else SPT_SLICES_SPMV(false);
+#undef SPT_SLICES_SPMV
   SPT_CHECK_LAUNCH("slices_spmv");
   hipLaunchKernelGGL((carry_fixup_kernel<T, 16>), dim3((W.nseg + kBlock - 1) / kBlock), dim3(kBlock), 0, s, W.nseg, W.carry_key, cval,
                      y, rows_may ? W.flags : nullptr, 1);

@@ -184,7 +184,7 @@ __device__ __forceinline__ void wave_fibre_sums(const T (&p)[kEPL], unsigned hea
 // piece_off[piece] = (i, j) fibre starts in the pieces before among the workgroup's, group_off[workgroup] = in all of
 // them. Bound by reading i and j; i is ordered, so where it is the same before and at the end of a piece
 // it need not be read. A wave has the loads of its pieces in flight together: four, of many entries eight (whole call,
-// fp32, with four / eight: 12M entries 57 / 59 us, 24M 127 / 127, 26M 133 / 134, 50M 238 / 229 (this kernel 52 / 40), 50M of
+// fp32, with four / eight: 12M entries 57 / 59 us, 24M 127 / 127, 26M 133 / 134, 50M 238 / 229 (this kernel 52 / 40, since then 34), 50M of
 // one entry to a fibre 501 / 494; 16: 62, 130 and, 50M, 245).
 // SELF (few pieces): one piece for a wave, piece_off[piece] = the starts in it.
 constexpr int kLogGroup = 4, kLogGroupMany = 5, kManyPieces = 96 * 1024;
@@ -209,13 +209,22 @@ __global__ __launch_bounds__(kBlock) void ttv_piece_heads_kernel(int nnz, int np
 #pragma unroll
       for (int r = 0; r < kEPL; ++r) j[u][r] = cj[min(p0 + r, nnz - 1)];  // beyond the end: the last entry again, never a head
     }
-    bi[u] = ci[before];
-    bj[u] = cj[before];
-    ei[u] = ci[min(base[u] + kPiece, nnz) - 1];
+    if (u == 0) {
+      bi[u] = ci[before];
+      bj[u] = cj[before];
+    }
   }
+  // the pieces of a wave lie in one slice, most of them: one look at i for all (a look at both ends of each piece takes a
+  // line of i per KB: 50M entries 43 us, so 34)
+  const bool one = bi[0] == ci[min(base[OWN - 1] + kPiece, nnz) - 1];
 #pragma unroll
   for (int u = 0; u < OWN; ++u) {
     const int p0 = base[u] + lane * kEPL;
+    if (u > 0) {
+      bj[u] = __builtin_amdgcn_readlane(j[u - 1][kEPL - 1], kWave - 1);  // (the piece before; of pieces beyond the end, not stored)
+      bi[u] = one ? bi[0] : ci[max(base[u] - 1, 0)];
+    }
+    ei[u] = one ? bi[0] : ci[min(base[u] + kPiece, nnz) - 1];
     if (bi[u] == ei[u]) {  // uniform
 #pragma unroll
       for (int r = 0; r < kEPL; ++r) i[u][r] = bi[u];

@@ -50,6 +50,7 @@ struct ColLoader {  // column coordinates of a CSR operand; rows are handled apa
   const int32_t* a1;
   __device__ __forceinline__ Raw raw(int p) const { return a1[p]; }
   __device__ __forceinline__ static Key key(Raw k) { return k; }
+  __device__ __forceinline__ static bool le(const ColLoader& a, int p, const ColLoader& b, int q) { return a.a1[p] <= b.a1[q]; }
   __device__ __forceinline__ ColLoader from(const ColLoader& c, bool other) const { return {other ? c.a1 : a1}; }
 };
 __device__ __forceinline__ bool key_le(int32_t a, int32_t b) { return a <= b; }
@@ -74,6 +75,16 @@ struct CooLoader {  // ND coordinates that fit 63 bits together
     if (ND == 3) k |= static_cast<uint32_t>(r.c[ND - 1]);
     return k;
   }
+  // The last coordinate is fetched only where the others are the same: a search probes lines that miss the caches
+  // (COO, fp64, 18M + 14M entries 317 -> 294 us in all; 3.8M + 2M 71 -> 68; fp32, 2M + 1M 30 -> 27).
+  __device__ __forceinline__ static bool le(const CooLoader& a, int p, const CooLoader& b, int q) {
+    const int32_t i = a.a0[p], k = b.a0[q];
+    if (ND == 3) {
+      const int32_t j = a.a1[p], l = b.a1[q];
+      return i != k ? i < k : j != l ? j < l : a.a2[p] <= b.a2[q];
+    }
+    return i != k ? i < k : a.a1[p] <= b.a1[q];
+  }
   __device__ __forceinline__ CooLoader from(const CooLoader& c, bool o) const {
     return {o ? c.a0 : a0, o ? c.a1 : a1, ND == 3 && o ? c.a2 : a2, s0, s1};
   }
@@ -84,6 +95,9 @@ struct WideLoader {  // any extents
   const int32_t *a0, *a1, *a2;
   __device__ __forceinline__ Raw raw(int p) const { return Key3{a0[p], a1[p], a2 ? a2[p] : 0}; }
   __device__ __forceinline__ static Key key(const Raw& r) { return r; }
+  __device__ __forceinline__ static bool le(const WideLoader& a, int p, const WideLoader& b, int q) {
+    return key_le(a.raw(p), b.raw(q));
+  }
   __device__ __forceinline__ WideLoader from(const WideLoader& c, bool o) const {
     return {o ? c.a0 : a0, o ? c.a1 : a1, o ? c.a2 : a2};
   }
@@ -123,8 +137,7 @@ __device__ __forceinline__ AddCut add_cut(const AddOperands<KL>& o, int64_t d) {
   // B's entry q is among the first e of the row if it is smaller than C's entry e - 1 - q
   const int64_t lo = max<int64_t>(0, e - nc), hi = min<int64_t>(e, nb);
   const int x = group_last_true<W>(lo, hi + 1, [&](int q) {
-    return q == lo ||
-           !key_le(o.kc.key(o.kc.raw(c.y + static_cast<int>(e - q))), o.kb.key(o.kb.raw(c.x + q - 1)));
+    return q == lo || !KL::le(o.kc, c.y + static_cast<int>(e - q), o.kb, c.x + q - 1);
   });
   const int y = static_cast<int>(e - x);
   const bool twins = y > 0 && x < nb && key_eq(o.kc.key(o.kc.raw(c.y + y - 1)), o.kb.key(o.kb.raw(c.x + x)));

@@ -31,6 +31,7 @@
 #include "common.hpp"
 #include "scan.hpp"
 #include "segreduce.hpp"
+#include "search.hpp"
 #include "wavescan.hpp"
 
 namespace spt {
@@ -455,21 +456,30 @@ __global__ __launch_bounds__(kBlock) void ttv_coo_piece_kernel(
 // first[piece] = first fibre that starts at or after the piece's first entry (piece ==
 // npieces: the number of fibres, so that the last piece also covers trailing empty fibres).
 // count (may be null) receives the number of values of the result, one per fibre.
+// W lanes per search: it waits for its probes, and eight lanes need a third of the steps (12 000 pieces: 1.3 us
+// less); with 60 000 pieces and more their number counts.
+constexpr int kFewPieces = 32768;
+template <int W>
 __global__ __launch_bounds__(kBlock) void ttv_piece_fibres_kernel(int npieces, int nfib,
                                                                   const int32_t* __restrict__ pos,
                                                                   int32_t* __restrict__ first,
                                                                   int64_t* __restrict__ count) {
-  const int piece = blockIdx.x * kBlock + threadIdx.x;
-  if (piece == 0 && count) *count = nfib;
+  const int t = blockIdx.x * kBlock + threadIdx.x, piece = t / W;
+  if (t == 0 && count) *count = nfib;
   if (piece > npieces) return;
-  int lo = 0, hi = nfib + 1;
-  if (piece == npieces) lo = hi = nfib;
   const int target = piece * kPiece;
-  while (lo < hi) {
-    const int mid = lo + ((hi - lo) >> 1);
-    if (pos[mid] < target) lo = mid + 1; else hi = mid;
+  int lo = 0, hi = nfib + 1;
+  if (piece == npieces) {
+    lo = nfib;
+  } else if (W > 1) {
+    lo = group_last_true<W>(0, static_cast<int64_t>(hi) + 1, [&](int q) { return q == 0 || pos[q - 1] < target; });
+  } else {
+    while (lo < hi) {
+      const int mid = lo + ((hi - lo) >> 1);
+      if (pos[mid] < target) lo = mid + 1; else hi = mid;
+    }
   }
-  first[piece] = min(lo, nfib);
+  if (t % W == 0) first[piece] = min(lo, nfib);
 }
 
 // out_v[f] = sum over the entries of fibre f (dense over the fibres, zero for empty ones).
@@ -551,6 +561,55 @@ __global__ __launch_bounds__(kBig) void ttv_csf_wave_kernel(
   }
 }
 
+// The same with c in global memory and a wave per piece.
+template <typename T>
+__global__ __launch_bounds__(kBlock) void ttv_csf_piece_kernel(
+    int nnz, int npieces, const int32_t* __restrict__ first, const int32_t* __restrict__ pos,
+    const int32_t* __restrict__ ck, const T* __restrict__ vals, const T* __restrict__ c, T* __restrict__ out_v,
+    int32_t* __restrict__ carry_key, T* __restrict__ carry_val) {
+  __shared__ int32_t s_mark[kBlock / kWave][kPiece];
+  const int lane = lane_id();
+  const int piece = __builtin_amdgcn_readfirstlane(blockIdx.x * (kBlock / kWave) + wave_id());
+  if (piece >= npieces) return;
+  const int base = piece * kPiece, p0 = base + lane * kEPL;
+  int32_t k[kEPL], *mark = s_mark[wave_id()];
+  T v[kEPL], g[kEPL];
+  const int f_lo = first[piece], f_hi = first[piece + 1];
+  if (base + kPiece <= nnz) {  // uniform
+    load_any(ck + p0, k);
+    load_any(vals + p0, v);
+  } else {
+#pragma unroll
+    for (int r = 0; r < kEPL; ++r) {
+      const bool ok = p0 + r < nnz;
+      k[r] = ok ? ck[p0 + r] : 0;
+      v[r] = ok ? vals[p0 + r] : T(0);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < kEPL; ++r) mark[lane * kEPL + r] = -1;
+#pragma unroll
+  for (int r = 0; r < kEPL; ++r) g[r] = c[k[r]];
+  if (base + kPiece > nnz) drop_beyond(p0, nnz, g);  // uniform
+  wave_lds_order();
+  for (int f = f_lo + lane; f < f_hi; f += kWave) {
+    const int a = pos[f], b = pos[f + 1];
+    if (b > a) mark[a - base] = f;
+    else out_v[f] = T(0);
+  }
+  wave_lds_order();
+  int key[kEPL];
+  unsigned headmask = 0;
+  T p[kEPL];
+#pragma unroll
+  for (int r = 0; r < kEPL; ++r) {
+    key[r] = mark[lane * kEPL + r];
+    if (key[r] >= 0) headmask |= 1u << r;
+    p[r] = v[r] * g[r];
+  }
+  wave_fibre_sums<T>(p, headmask, key, f_lo - 1, piece, out_v, carry_key, carry_val);
+}
+
 // ================================================================ host
 static int compute_units() {
   static int cached[64] = {0};
@@ -581,11 +640,19 @@ constexpr int kSelfPieces = 6144;
 
 static int64_t pieces_of(int64_t nnz) { return (nnz + kPiece - 1) / kPiece; }
 
-// Smaller CSF tensors are reduced as CSR rows, one launch where fibres are short: the fixed cost of staging c on every
-// compute unit is not recovered (500 000 entries: 8 to 12 us by rows, 13 to 19 with c staged; 1M skewed
-// ones 16 to 37 and 14 to 23). Tensors whose last dimension is so long that less
-// than a quarter of c fits the cache leave c in global memory: their gathers go there anyway, and
-// without staging more waves are in flight for them.
+// CSF tensors of fewer entries are reduced as CSR rows, in one launch where fibres are short (300 000 entries: 7 to 9 us,
+// as pieces 10 to 11; 700 000: 15 to 16, 12 to 13).
+bool ttv_csf_applies(int64_t nnz, int64_t nfib) {
+  return nnz >= (int64_t(1) << 19) && nnz + kPiece < INT32_MAX && nfib + 1 < INT32_MAX;
+}
+
+// c is staged in LDS from here on. CSF, c of 10 000, as pieces with c in global memory / staged: 700 000 entries, fp32
+// 11.5 / 12.0 us, fp64 12.6 / 12.8; 1.5M 13.5 / 13.0, 16.2 / 15.3; 15M 68 / 43, 98 / 55. (COO: the table below.)
+constexpr int64_t kCsfStagedEntries = int64_t(1) << 20;
+
+// Tensors whose last dimension is so long that less than a quarter of c fits the cache leave c in global memory: their
+// gathers go there anyway, and without staging more waves are in flight for them. (CSF, fp64, c of 90 000, reduced as
+// CSR rows / as pieces: 3M entries, skewed 44 / 28 us, every one a fibre 47 / 37; 15M 143 / 104, 177 / 142.)
 bool ttv_wave_applies(int64_t nnz, int64_t K, int dtype) {
   const int64_t vsz = dtype == SPT_F64 ? 8 : 4;
   return nnz >= (int64_t(1) << 19) && nnz + kPiece < INT32_MAX && K * vsz <= 4 * (int64_t)kCsfCacheBytes;
@@ -679,21 +746,30 @@ spt_status ttv_csf_wave(int64_t nnz64, int64_t nfib, int64_t K, const int32_t* p
   int32_t* first = W.take<int32_t>(np + 1);
   int32_t* ckey = W.take<int32_t>(np);
   T* cval = W.take<T>(np);
-  hipLaunchKernelGGL(ttv_piece_fibres_kernel, dim3((np + 1 + kBlock - 1) / kBlock), dim3(kBlock), 0, s, np, (int)nfib,
-                     pos, first, out_count);
+#define SPT_TTV_FIRST(W_)                                                                                                 \
+  hipLaunchKernelGGL(ttv_piece_fibres_kernel<W_>, dim3((unsigned)(((int64_t)(np + 1) * W_ + kBlock - 1) / kBlock)), dim3(kBlock), \
+                     0, s, np, (int)nfib, pos, first, out_count)
+  if (np <= kFewPieces) SPT_TTV_FIRST(8);
+  else SPT_TTV_FIRST(1);
+#undef SPT_TTV_FIRST
   SPT_CHECK_LAUNCH("ttv piece fibres");
-  const bool vec = al16(ck) && al16(vals);
-  const int cached = (int)std::min<int64_t>(K, kCsfCacheBytes / sizeof(T));
-  const bool all = cached == K;
-  const unsigned grid = (unsigned)std::min<int64_t>(compute_units(), (np + kBigWaves - 1) / kBigWaves);
+  if (nnz64 >= kCsfStagedEntries && ttv_wave_applies(nnz64, K, sizeof(T) == 8 ? SPT_F64 : SPT_F32)) {
+    const bool vec = al16(ck) && al16(vals);
+    const int cached = (int)std::min<int64_t>(K, kCsfCacheBytes / sizeof(T));
+    const bool all = cached == K;
+    const unsigned grid = (unsigned)std::min<int64_t>(compute_units(), (np + kBigWaves - 1) / kBigWaves);
 #define SPT_TTV_CSF(VEC_, ALL_)                                                                                   \
   hipLaunchKernelGGL((ttv_csf_wave_kernel<T, VEC_, ALL_>), dim3(grid), dim3(kBig), 0, s, nnz, np, first, pos, ck, \
                      vals, c, cached, out_v, ckey, cval)
-  if (vec && all) SPT_TTV_CSF(true, true);
-  else if (vec) SPT_TTV_CSF(true, false);
-  else if (all) SPT_TTV_CSF(false, true);
-  else SPT_TTV_CSF(false, false);
+    if (vec && all) SPT_TTV_CSF(true, true);
+    else if (vec) SPT_TTV_CSF(true, false);
+    else if (all) SPT_TTV_CSF(false, true);
+    else SPT_TTV_CSF(false, false);
 #undef SPT_TTV_CSF
+  } else {
+    hipLaunchKernelGGL(ttv_csf_piece_kernel<T>, dim3((np + kBlock / kWave - 1) / (kBlock / kWave)), dim3(kBlock), 0, s, nnz,
+                       np, first, pos, ck, vals, c, out_v, ckey, cval);
+  }
   SPT_CHECK_LAUNCH("ttv csf wave");
   hipLaunchKernelGGL(carry_fixup_kernel<T>, dim3((np + kBlock - 1) / kBlock), dim3(kBlock), 0, s, np, ckey, cval,
                      out_v, nullptr, 0);

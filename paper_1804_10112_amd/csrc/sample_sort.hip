@@ -1235,12 +1235,13 @@ bool sample_sort_applies(int64_t n) { return n > 0 && n <= kSampleSortMax; }
 
 // Few records: a thread takes eight or 16 of a large tile one after the other (14 us to classify them, whatever n),
 // which tiles of 1024 cut (fp64, tiles of 1024 / 4096: 1.2M records 84 / 108 us, 2M 122 / 128, 3M 162 / 160, 4M
-// 195 / 185, 6M 259 / 228, whose counts no longer fit the caches). A single partition's
-// workgroups each add up the counts of all tiles, so it has at most 176 of them.
-constexpr int64_t kSmallTileMax = int64_t(11) << 18;
+// 195 / 185, 6M 259 / 228, whose counts no longer fit the caches). From 2M records on tiles of 2048 (of 1024 / 2048, fp32:
+// 1.75M 95 / 96 us, 1.9M 99 / 99, 2.2M 112 / 107, 2.9M 130 / 122; fp64: 101 / 103, 105 / 105, 121 / 114, 137 / 131).
+// A single partition's workgroups each add up the counts of all tiles, so it has at most 176 of them.
+constexpr int64_t kLeastTileMax = int64_t(15) << 17, kSmallTileMax = int64_t(11) << 18;
 static int tile_of(int64_t n) {
   if (n <= kOneLevelMax) return n <= 128 * kSmallTile ? kSmallTile : 2 * kSmallTile;
-  return n <= kSmallTileMax ? kSmallTile : kTile;
+  return n <= kLeastTileMax ? kSmallTile : n <= kSmallTileMax ? 2 * kSmallTile : kTile;
 }
 // LDS that the first scatter of large tiles asks for beyond what it uses (46 KB), so that two of its workgroups share a compute
 // unit, not three (see above; the second one, which has keys and values in LDS at a time, uses 62 or 78 KB).
@@ -1344,6 +1345,9 @@ spt_status sample_sort_convert(int64_t n64, int64_t nrows, int64_t ncols, bool b
   if (tile == kSmallTile)
     hipLaunchKernelGGL((partition_kernel<VT, RcSource, false, kSmallTile>), dim3(nt1), dim3(part_threads(kSmallTile)), 0, s, rc, vals, f, n,
                        1, T, dig, hist1, k1, v1, nullptr, total1, nullptr, nullptr, nullptr);
+  else if (tile == 2 * kSmallTile)
+    hipLaunchKernelGGL((partition_kernel<VT, RcSource, false, 2 * kSmallTile>), dim3(nt1), dim3(part_threads(2 * kSmallTile)), 0, s, rc, vals, f, n,
+                       1, T, dig, hist1, k1, v1, nullptr, total1, nullptr, nullptr, nullptr);
   else
     hipLaunchKernelGGL((partition_kernel<VT, RcSource, false, kTile>), dim3(nt1), dim3(part_threads(kTile)), kPartPad, s, rc, vals, f, n, 1, T,
                        dig, hist1, k1, v1, nullptr, total1, nullptr, nullptr, nullptr);
@@ -1373,6 +1377,9 @@ spt_status sample_sort_convert(int64_t n64, int64_t nrows, int64_t ncols, bool b
   if (tile == kSmallTile)
     hipLaunchKernelGGL((classify_kernel<KSource, true, kSmallTile>), dim3(tiles2 / group + kSegMax), dim3(kBlock), 0, s, s1,
                        f, n, static_cast<int>(nrows), group, nb1, T, skey1, skey2, spos2, dig, hist2);
+  else if (tile == 2 * kSmallTile)
+    hipLaunchKernelGGL((classify_kernel<KSource, true, 2 * kSmallTile>), dim3(tiles2 / group + kSegMax), dim3(kBlock), 0, s, s1,
+                       f, n, static_cast<int>(nrows), group, nb1, T, skey1, skey2, spos2, dig, hist2);
   else
     hipLaunchKernelGGL((classify_kernel<KSource, true, kTile>), dim3(tiles2 / group + kSegMax), dim3(kBlock), 0, s, s1, f,
                        n, static_cast<int>(nrows), group, nb1, T, skey1, skey2, spos2, dig, hist2);
@@ -1381,6 +1388,9 @@ spt_status sample_sort_convert(int64_t n64, int64_t nrows, int64_t ncols, bool b
   SPT_CHECK_LAUNCH("offsets 2");
   if (tile == kSmallTile)
     hipLaunchKernelGGL((partition_kernel<VT, KSource, true, kSmallTile>), dim3(tiles2), dim3(part_threads(kSmallTile)), 0, s, s1, v1, f, n,
+                       nb1, T, dig, hist2, records, nullptr, nullptr, nullptr, skey1, skey2, spos2);
+  else if (tile == 2 * kSmallTile)
+    hipLaunchKernelGGL((partition_kernel<VT, KSource, true, 2 * kSmallTile>), dim3(tiles2), dim3(part_threads(2 * kSmallTile)), 0, s, s1, v1, f, n,
                        nb1, T, dig, hist2, records, nullptr, nullptr, nullptr, skey1, skey2, spos2);
   else
     hipLaunchKernelGGL((partition_kernel<VT, KSource, true, kTile>), dim3(tiles2), dim3(part_threads(kTile)), 0, s, s1, v1, f, n, nb1, T,

@@ -613,7 +613,7 @@ spt_status ttm_dispatch(Format f, const spt_tensor* B, const void* C, int32_t K,
 }
 
 // ttv_wave.hip
-bool ttv_csf_applies(int64_t nnz, int64_t nfib);
+bool ttv_csf_applies(int64_t nnz, int64_t nfib, int64_t K, int dtype);
 bool ttv_wave_applies(int64_t nnz, int64_t K, int dtype);
 size_t ttv_coo_workspace(int64_t nnz);
 size_t ttv_csf_wave_workspace(int64_t nnz);
@@ -628,7 +628,8 @@ spt_status ttv_csf_wave(int64_t nnz, int64_t nfib, int64_t K, const int32_t* pos
 
 size_t ttv_workspace(Format f, const spt_tensor* B) {
   if (f == Format::COO3) return ttv_coo_workspace(B->nvals);
-  return ttv_csf_applies(B->nvals, B->level[2].M) ? ttv_csf_wave_workspace(B->nvals) : seg_spmv_workspace(B->nvals);
+  return ttv_csf_applies(B->nvals, B->level[2].M, B->level[2].N, B->dtype) ? ttv_csf_wave_workspace(B->nvals)
+                                                                           : seg_spmv_workspace(B->nvals);
 }
 
 spt_status ttv_dispatch(Format f, const spt_tensor* B, const void* c, int32_t* out_crd0,
@@ -642,8 +643,9 @@ spt_status ttv_dispatch(Format f, const spt_tensor* B, const void* c, int32_t* o
     // reduction as CSR SpMV with rows = fibers and x = c.
     const int64_t nfib = B->level[2].M;
     // (with less workspace than pieces take, a tensor of a long c is reduced as rows all the same)
-    if (ttv_csf_applies(B->nvals, nfib) && (ttv_wave_applies(B->nvals, B->level[2].N, B->dtype) ||
-                                            (ws && ws_bytes >= ttv_csf_wave_workspace(B->nvals)))) {  // writes the count itself
+    if (ttv_csf_applies(B->nvals, nfib, B->level[2].N, B->dtype) &&
+        (ttv_wave_applies(B->nvals, B->level[2].N, B->dtype) ||
+         (ws && ws_bytes >= ttv_csf_wave_workspace(B->nvals)))) {  // writes the count itself
       if (B->dtype == SPT_F64)
         return ttv_csf_wave<double>(B->nvals, nfib, B->level[2].N, B->level[2].pos, B->level[2].crd,
                                     static_cast<const double*>(B->vals), static_cast<const double*>(c),

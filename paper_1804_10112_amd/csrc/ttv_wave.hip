@@ -641,9 +641,13 @@ constexpr int kSelfPieces = 6144;
 static int64_t pieces_of(int64_t nnz) { return (nnz + kPiece - 1) / kPiece; }
 
 // CSF tensors of fewer entries are reduced as CSR rows, in one launch where fibres are short (300 000 entries: 7 to 9 us,
-// as pieces 10 to 11; 700 000: 15 to 16, 12 to 13).
-bool ttv_csf_applies(int64_t nnz, int64_t nfib) {
-  return nnz >= (int64_t(1) << 19) && nnz + kPiece < INT32_MAX && nfib + 1 < INT32_MAX;
+// as pieces 10 to 11; 700 000: 15 to 16, 12 to 13), and so are those of a longer c: its gathers go beyond L2, and chunks
+// of 2048 entries have more of them in flight. 15M entries, two to a fibre, as rows / as pieces, fp64: c of 100 000
+// 136 / 126, 300 000 142 / 137, 900 000 190 / 209, 10M 314 / 350; fp32: 100 000 98 / 98, 300 000 113 / 104 (3M entries
+// 27.4 / 29.5), 10M 287 / 302.
+bool ttv_csf_applies(int64_t nnz, int64_t nfib, int64_t K, int dtype) {
+  return nnz >= (int64_t(1) << 19) && nnz + kPiece < INT32_MAX && nfib + 1 < INT32_MAX &&
+         K <= (dtype == SPT_F64 ? 300000 : 1 << 17);
 }
 
 // c is staged in LDS from here on. CSF, c of 10 000, as pieces with c in global memory / staged: 700 000 entries, fp32

@@ -28,8 +28,8 @@
 // counted, 60M records took 10.4 instead of 1.8 ms).
 //
 // Measured against the six radix passes it replaces (fp64): 60M records with power-law rows
-// 3.09 -> 1.52 ms (splitters 19 + 70 us, classify 2 x 133, offsets 8 + 9, partitions 405 + 352, finish 400; with whole
-// keys and separate arrays the second partition took 418); 20M 0.52 ms, 5M 0.19 ms, 250 000 52 us,
+// 3.09 -> 1.52 ms (splitters 10 + 70 us, classify 2 x 133, offsets 8 + 9, partitions 405 + 352, finish 400; with whole
+// keys and separate arrays the second partition took 418); 20M 0.52 ms, 5M 0.19 ms, 250 000 48 us,
 // 50 000 171 -> 19 us. The partitions write 256 interleaved streams for each array
 // and are bound by how the memory system takes them: it is the bytes in flight that count. Two workgroups of 512 threads
 // on a compute unit: 60M records fp64 1.70 ms in all (before splitters, offsets and records were made as now), three 1.83, three

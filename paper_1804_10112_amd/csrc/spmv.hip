@@ -1248,7 +1248,7 @@ constexpr int64_t kDynamicMinEntries = int64_t(1) << 25;
 //                            64 MB 712 / 461   96 MB 770 / 581 (some 4 us more per MB: equal at about 150 MB)
 //   36M entries, CSR         fp32 6 MB 272 / 234, 24 MB 593 / 294; fp64 24 MB 597 / 317, 96 MB 795 / 600
 //   17M entries, COO         fp64 8 MB 200 / 138; fp32 6.4 MB 155 / 133
-//   power law, CSR           fp64, 60M entries, 32 MB 970 / 576; fp32, 35M entries, 9.2 MB 378 / 248
+//   power law, CSR           fp64, 60M entries, 32 MB 970 / 545; fp32, 35M entries, 9.2 MB 378 / 248
 //   local columns, CSR, 36M  a heavy row fp64 171 / 138, fp32 112 / 110; mean row 90 fp64 153 / 111, fp32 94 / 82;
 // Not for rows whose declared bound sends them to the row kernel: they are spared the choice, which with local columns
 // costs more than it can be made to cost less (by rows at once / chosen; fp64, 36M entries, 12 a row, 117 / 133, 98M 286 / 318;

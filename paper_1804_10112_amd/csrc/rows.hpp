@@ -5,6 +5,15 @@
 
 namespace spt {
 
+// The elements of pos in l + 1 .. h that one lane of a wave stores: four(r) those from r on, side by side, one(r) a single
+// one. What is left is compared with a step, never the sum of r and a step with h, which row counts close to 2^31 overflow.
+template <class FOUR, class ONE>
+__host__ __device__ __forceinline__ void wave_range(int l, int h, int lane, const FOUR& four, const ONE& one) {
+  int r = l + 1;
+  for (; h - r >= 4 * kWave - 1; r += 4 * kWave) four(r + lane * 4);
+  for (int left = h - r, k = lane; k <= left; k += kWave) one(r + k);
+}
+
 // pos of the compressed column level from the sorted rows. Table 3 assembles pos as
 // per-parent counts (append_edges) followed by a running sum (append_finalize); on sorted
 // rows that running sum is known directly: pos[r] = position of the first entry whose row
@@ -22,9 +31,7 @@ static __device__ __forceinline__ void store_pos_range(int32_t* __restrict__ pos
     todo &= todo - 1;
     const int l = __shfl(lo, src), h = __shfl(hi, src), v = __shfl(val, src);
     typedef int32_t I4 __attribute__((ext_vector_type(4), aligned(4)));
-    int r = l + 1;
-    for (; r + 4 * kWave <= h + 1; r += 4 * kWave) *reinterpret_cast<I4*>(pos + r + lane_id() * 4) = I4(v);
-    for (r += lane_id(); r <= h; r += kWave) pos[r] = v;
+    wave_range(l, h, lane_id(), [&](int r) { *reinterpret_cast<I4*>(pos + r) = I4(v); }, [&](int r) { pos[r] = v; });
   }
 }
 template <bool VEC>

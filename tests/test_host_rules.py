@@ -1,0 +1,55 @@
+"""Arithmetic and rules of the kernels' headers, compiled for the host and run on the CPU at sizes that no test holds in
+memory."""
+import os
+import subprocess
+
+
+from paper_1804_10112_amd import build as spt_build
+
+INCLUDES = ["-I", spt_build.CSRC]
+
+
+def _run(tmp_path, text):
+    src, exe = tmp_path / "check.hip", tmp_path / "check"
+    src.write_text(text)
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-arch=gfx950", "-O1", "-std=c++17", *INCLUDES,
+                    str(src), "-o", str(exe)], check=True, capture_output=True)
+    return subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=60).stdout
+
+
+RANGES = r"""
+#include <climits>
+#include <vector>
+#include "rows.hpp"
+// Every element of l + 1 .. h once, and none beside them: what lies outside is counted, not stored, and the walk ends.
+static bool whole(int l, int h) {
+  std::vector<int> times(static_cast<size_t>(h - l), 0);
+  long long outside = 0, steps = 0;
+  for (int lane = 0; lane < spt::kWave; ++lane) {
+    const auto one = [&](int r) {
+      if (++steps > 100000) throw 1;
+      const long long at = static_cast<long long>(r) - l - 1;
+      if (at >= 0 && at < h - l) ++times[at]; else ++outside;
+    };
+    spt::wave_range(l, h, lane, [&](int r) { for (int q = 0; q < 4; ++q) one(r + q); }, one);
+  }
+  for (const int t : times) if (t != 1) return false;
+  return outside == 0;
+}
+int main() {
+  const int last[] = {0, 63, 300, INT_MAX - 600, INT_MAX - 257, INT_MAX - 256, INT_MAX - 65, INT_MAX - 64, INT_MAX - 2, INT_MAX - 1};
+  const int length[] = {1, 17, 63, 64, 65, 254, 255, 256, 257, 511, 512, 513, 700, 1024};
+  for (const int h : last)
+    for (const int n : length)
+      if (n <= h + 1) {  // l >= -1
+        bool ok = false;
+        try { ok = whole(h - n, h); } catch (int) {}
+        if (!ok) { std::printf("(%d, %d]\n", h - n, h); return 0; }
+      }
+  std::printf("ok\n");
+}
+"""
+
+
+def test_a_waves_share_of_pos_up_to_the_largest_row_counts(tmp_path):
+    assert _run(tmp_path, RANGES) == "ok\n"

@@ -355,7 +355,10 @@ __global__ __launch_bounds__(kSliceBlock) __attribute__((amdgpu_waves_per_eu(4, 
     SliceGather<T, 4 * V>::run(x, nslices, slice, offset, got);
   }
 
-  constexpr int kBatch = sizeof(T) == 8 ? 2 : 4;
+  // Segments whose values (COO: and rows) are on their way at a time. Next to 40 gathered doubles there is room for those
+  // of one: with two, 2 registers (COO: 6) went through scratch memory (60M entries, x of 8 / 32 / 64 MB, CSR 439 / 529 / 647
+  // us, so 429 / 520 / 629; COO 478 / 560 / 684, so 467 / 556 / 680).
+  constexpr int kBatch = sizeof(T) == 8 ? (MANY ? 1 : 2) : 4;
   static_assert(B % kBatch == 0 && V % kBatch == 0, "");
   int r_first = 0;  // CSR, in lane l: the first row that starts in segment l / L of those in LDS
   constexpr int L = kWave / B;  // lanes that enter the rows of a segment

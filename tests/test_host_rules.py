@@ -1,19 +1,21 @@
-"""Arithmetic and rules of the kernels' headers, compiled for the host and run on the CPU at sizes that no test holds in
-memory."""
+"""What a CPU can check of the kernels' sources: arithmetic and rules of their headers, compiled for the host and run at sizes
+that no test holds in memory, and the registers that the compiler gives a kernel."""
 import os
+import re
 import subprocess
 
 
 from paper_1804_10112_amd import build as spt_build
 
 INCLUDES = ["-I", spt_build.CSRC]
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
 def _run(tmp_path, text):
     src, exe = tmp_path / "check.hip", tmp_path / "check"
     src.write_text(text)
-    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-arch=gfx950", "-O1", "-std=c++17", *INCLUDES,
-                    str(src), "-o", str(exe)], check=True, capture_output=True)
+    subprocess.run([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", *INCLUDES, str(src), "-o", str(exe)], check=True,
+                   capture_output=True)
     return subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=60).stdout
 
 
@@ -53,3 +55,13 @@ int main() {
 
 def test_a_waves_share_of_pos_up_to_the_largest_row_counts(tmp_path):
     assert _run(tmp_path, RANGES) == "ok\n"
+
+
+def test_the_kernel_that_gathers_slice_by_slice_keeps_its_registers(tmp_path):
+    """Entries of a lane take 80 of its 128 registers; what no longer fits beside them would go through scratch memory."""
+    asm = tmp_path / "spmv_slices.s"
+    flags = [f for f in spt_build.HIPCC_FLAGS if f not in ("-fPIC", "-shared")]
+    subprocess.run([HIPCC, *flags, "--offload-device-only", "-S", os.path.join(spt_build.CSRC, "spmv_slices.hip"), "-o", str(asm)],
+                   check=True, capture_output=True)
+    scratch = dict(re.findall(r"\.name:\s+(\S*slices_spmv_kernel\S*)\s+\.private_segment_fixed_size: (\d+)", asm.read_text()))
+    assert len(scratch) == 8 and set(scratch.values()) == {"0"}, scratch

@@ -23,6 +23,36 @@ inline int slices_of(int64_t ncols, int64_t value, int64_t entries) {
   return static_cast<int>((x + bytes - 1) / bytes);
 }
 
+// A workgroup of the sliced product on every compute unit; entries to a lane, of one kernel and of the other.
+constexpr int kSliceBlock = 1024, kCus = 256, kFewEntries = 32;
+template <typename T>
+constexpr int kInPlace = sizeof(T) == 8 ? 40 : 64;
+
+// Do the lanes hold kInPlace entries or 32? The chip goes over x in rounds of what all lanes hold; a round of more entries
+// looks at more registers in every slice, filled or not, and each round brings the lines of x. So what counts is
+// how many registers all rounds look at, and, where the two kernels are about equal in that, whether the lines of fewer
+// rounds are many. 32 entries to a lane / kInPlace, us (rounds):
+//   COO, fp64, x, MB     8          16          32          64         126
+//     21M (3, 3)     169 / 174   180 / 188   208 / 221   256 / 268   319 / 333
+//     26M (4, 3)     212 / 210   227 / 222   264 / 256   328 / 305   404 / 389
+//     33M (4, 4)     263 / 268   279 / 285   315 / 329   386 / 394   481 / 502
+//     38M (5, 4)     294 / 306   314 / 322   359 / 363   457 / 439   559 / 556
+//     51M (7, 5)     396 / 396   424 / 415   493 / 472   644 / 573   760 / 725
+//     56M (7, 6)     432 / 439   459 / 463   529 / 529   687 / 646   823 / 814
+//     75M (9, 8)     570 / 623   606 / 654   700 / 730   919 / 901  1077 / 1132
+//   CSR, fp64: 34M (5, 4) 256 / 261, 276 / 278, 322 / 322, 399 / 385; 47M (6, 5) 345 / 341, 368 / 360, 424 / 415, 528 / 502
+//   COO, fp32 (whose kernel of more entries has no slower looks): 18M (3, 2) 142 / 148, 155 / 158, 180 / 183, 232 / 222; 28M
+//     (4, 2) 212 / 209, 229 / 220, 263 / 241, 345 / 286; 51M (7, 4) 373 / 371, 414 / 394, 483 / 445, 650 / 537
+// (COO, fp64, 18M (3, 2), x of 8 MB 148 / 150: three rounds over little.)
+template <typename T>
+inline bool slices_of_many(int64_t nnz, int64_t ncols, bool csr) {
+  const auto rounds = [&](int entries) { return (nnz - 1) / (int64_t(kSliceBlock) * kCus * entries) + 1; };
+  const int64_t x = ncols * static_cast<int64_t>(sizeof(T)), few = rounds(kFewEntries) * kFewEntries, many = rounds(kInPlace<T>) * kInPlace<T>;
+  if (sizeof(T) == 4) return many * 4 <= few * 5 || x > 36000000;
+  if (many < few) return csr || x > 12000000 || rounds(kFewEntries) > 3;
+  return many * 25 <= few * 27 && x > (csr ? 12000000 : 40000000);
+}
+
 constexpr int kSegment = 4 * kWave;  // consecutive entries that a wave reduces at a time
 
 // The row kernel as one of two candidates: where the choice is made, and what it leaves behind for the other if
@@ -121,8 +151,6 @@ SPT_SLICE_GATHER(float, 32, SPT_GATHER_LOAD1)
 // read while the load is on its way, in lanes whose bit is cleared. An offset beyond every slice is left as it is.
 template <typename T>
 struct SliceGatherInPlace;
-template <typename T>
-constexpr int kInPlace = sizeof(T) == 8 ? 40 : 64;  // entries to a lane
 
 // (entry, its bit, of which register, the registers of its value)
 #define SPT_PLACES_double(M) \

@@ -13,7 +13,7 @@
 //  * The number of workgroups is a multiple of the compute units, one of them to each (128 registers a lane): with
 //    as many as there are full ones, the last round took as long as the others (0.71 against 0.68 ms).
 //  * An offset's register becomes half of its value's, so that 40 entries fit where 32 with both did (8 rounds over x
-//    become 6). Small x and fewer entries keep the 32 (slices_of_many); larger x have larger slices (slices_of).
+//    become 6). Where that saves no rounds, lanes keep the 32 (slices_of_many); larger x have larger slices (slices_of).
 // Bound by the address unit (a load with a few lanes takes it some 20 clocks), then the lines.
 #include <algorithm>
 
@@ -24,14 +24,13 @@
 
 namespace spt {
 
-constexpr int kSliceBlock = 1024, kSliceWaves = kSliceBlock / kWave;
-constexpr int kFewSegments = 8;
+constexpr int kSliceWaves = kSliceBlock / kWave;
+constexpr int kFewSegments = kFewEntries / 4;
 // Segments of a wave, each a vector of four entries per lane; and as many of them as have their row starts in LDS at a time (CSR).
 template <typename T, bool MANY>
 constexpr int kSegments = MANY ? kInPlace<T> / 4 : kFewSegments;
 template <typename T, bool MANY>
 constexpr int kRowBatch = MANY && sizeof(T) == 8 ? 6 : 8;
-constexpr int kCus = 256;
 
 // What precedes the product, kChoiceFlags workgroups.
 // CSR: does a block of kSkewRows rows hold more than 1 / kSkewShare of all entries? By rows, the kernel would end on
@@ -469,18 +468,11 @@ spt_status launch_csr_skew(int64_t nnz, int64_t nrows, const int32_t* pos, uint8
   SPT_CHECK_LAUNCH("csr skew");
   return SPT_OK;
 }
-// Do the lanes hold as many entries as they can? Fewer rounds over x then bring fewer lines, but there are fewer workgroups
-// to take turns. 32 / 40 or 64 entries to a lane, x in MB, us: fp64, 60M, 32 568 / 545, 64 767 / 721; 40M, 28 354 / 354; 30M, 16
-// 246 / 249; 18M, 12 154 / 157; 20M, 64 280 / 275. fp32, 60M, 64 719 / 584; 40M, 16 285 / 276; 36M, 12 277 / 272; 24M, 8 176 / 179.
-static bool slices_of_many(int64_t nnz, int64_t ncols, int64_t value, int64_t entries) {
-  return nnz >= 32000000 || entries / kXcds < 8 * (ncols * value / 128);
-}
-
 template <typename T, bool CSR>
 spt_status launch_slices_spmv(int64_t nnz, int64_t ncols, bool rows_may, const int32_t* pos_or_row, const int32_t* col,
                               const T* vals, const T* x, T* y, void* ws, hipStream_t s) {
   const SlicesWorkspace W(nnz, ws);
-  const bool many = slices_of_many(nnz, ncols, sizeof(T), int64_t(kSliceBlock) * kCus * kInPlace<T>);
+  const bool many = slices_of_many<T>(nnz, ncols, CSR);
   const int per = kSliceWaves * (many ? kSegments<T, true> : kFewSegments);
   const int nslices = slices_of(ncols, sizeof(T), int64_t(per) * kSegment * kCus);
   const uint32_t slice = (uint32_t)((ncols + nslices - 1) / nslices * sizeof(T));

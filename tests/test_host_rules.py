@@ -11,12 +11,12 @@ INCLUDES = ["-I", spt_build.CSRC]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
-def _run(tmp_path, text):
+def _run(tmp_path, text, stdin=""):
     src, exe = tmp_path / "check.hip", tmp_path / "check"
     src.write_text(text)
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", *INCLUDES, str(src), "-o", str(exe)], check=True,
                    capture_output=True)
-    return subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=60).stdout
+    return subprocess.run([str(exe)], check=True, input=stdin, capture_output=True, text=True, timeout=60).stdout
 
 
 RANGES = r"""
@@ -55,6 +55,35 @@ int main() {
 
 def test_a_waves_share_of_pos_up_to_the_largest_row_counts(tmp_path):
     assert _run(tmp_path, RANGES) == "ok\n"
+
+
+RULE = r"""
+#include "slices.hpp"
+int main() {
+  long long nnz, x;
+  int value, csr;
+  while (std::scanf("%lld %lld %d %d", &nnz, &x, &value, &csr) == 4)
+    std::printf("%d\n", value == 8 ? spt::slices_of_many<double>(nnz, x / 8, csr) : spt::slices_of_many<float>(nnz, x / 4, csr));
+}
+"""
+
+
+def test_more_entries_to_a_lane_only_where_they_save_looks(tmp_path):
+    """A round of the chip is 1024 * 256 lanes. With no round saved, the kernel of more entries only looks at more registers;
+    with looks saved, it is the faster one from x of 12 MB on."""
+    cases = [(n, x, v, csr) for n in range(16_800_000, 120_000_000, 100_001) for x in (6_500_000, 20_000_000, 30_000_000, 64_000_000)
+             for v in (4, 8) for csr in (0, 1)]
+    got = _run(tmp_path, RULE, "\n".join("%d %d %d %d" % c for c in cases)).split()
+    assert len(got) == len(cases)
+    for (n, x, v, csr), many in zip(cases, got):
+        entries = 40 if v == 8 else 64
+        few, more = (-(-n // (1024 * 256 * e)) for e in (32, entries))
+        if few == more:
+            assert many == "0", (n, x, v, csr)
+        elif more * entries < few * 32 and x > 12_000_000:
+            assert many == "1", (n, x, v, csr)
+        elif v == 8 and more * entries > few * 32 * 1.1:
+            assert many == "0", (n, x, v, csr)
 
 
 def test_the_kernel_that_gathers_slice_by_slice_keeps_its_registers(tmp_path):

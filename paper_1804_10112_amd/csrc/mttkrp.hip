@@ -627,6 +627,14 @@ struct MttkrpPlan {
 //   CSF, fp32: 600 000 entries 36.3 / 32.8; 1.3M 56.6 / 47.1; 3M 77.9 / 75.3; fp64: 600 000 58.7 / 51.0; 2M 111 / 107
 //   COO, fp32: 900 000 entries 33.2 / 31.3; 1.3M 45.2 / 38.4; 3M 71.3 / 70.6; fp64: 600 000 50.5 / 44.2; 2M 106 / 100
 // (32 lanes: batches of 128 entries are too long, 400 000 entries 65.6 in 16, 68.0.)
+// 16 lanes, whose batches are of 64 entries: groups of 48 as long as two workgroups on each compute unit hold the tensor.
+// With 64 there are hardly more workgroups than compute units, and a skewed tensor ends on one of them. (COO: even slices
+// lose some of what 64 gain, up to 5 %, skewed ones gain as much; with 32, even slices lose 10 %, fp32.) Groups of
+// 16 / 32 / 48 / 64, J = 32, fp64, skewed slices, and even ones:
+//   CSF, 265 000 entries  32.5 / 29.7 / 32.2 / 36.9, 35.3 / 31.8 / 29.9 / 31.3; 360 000  35.6 / 32.2 / 33.6 / 37.5, 39.1 / 34.3 / 34.5 / 34.6
+//     400 000 37.1 / 35.3 / 36.7 / 37.3, 42.0 / 39.2 / 39.9 / 36.8
+//   COO, 330 000 entries  28.3 / 26.7 / 28.4 / 29.5, 30.3 / 28.2 / 28.1 / 27.9; 400 000  32.0 / 31.3 / 32.6 / 31.2, 35.1 / 34.1 / 34.4 / 30.9
+//   fp32, J = 64: CSF, 265 000  36.2 / 33.8 / 34.5 / 38.6, 39.8 / 35.2 / 32.7 / 33.3; COO, 330 000  32.4 / 30.7 / 32.1 / 32.8, 36.9 / 32.7 / 31.3 / 31.3
 static MttkrpPlan mttkrp_plan(int64_t nnz, int64_t J, int dtype, bool csf) {
   MttkrpPlan P;
   P.vec = dtype == SPT_F64 ? kVec<double> : kVec<float>;
@@ -639,6 +647,7 @@ static MttkrpPlan mttkrp_plan(int64_t nnz, int64_t J, int dtype, bool csf) {
   const int64_t want = nnz / (6 * 256) / groups;
   int64_t epg = 16;
   if (P.lanes > 16) epg = std::max<int64_t>(want / 16 * 16, 16);
+  else if (P.lanes == 16 && nnz > once && nnz <= int64_t(2) * 256 * groups * 48) epg = 48;
   else if (nnz > once) epg = std::max<int64_t>((want + batch / 2) / batch * batch, batch);
   P.epg = static_cast<int>(std::min<int64_t>(epg, std::min(128, 2048 / groups)));
   P.chunk = P.epg * groups;

@@ -4,7 +4,9 @@ import os
 import re
 import subprocess
 
+import pytest
 
+import paper_1804_10112_amd as spt
 from paper_1804_10112_amd import build as spt_build
 
 INCLUDES = ["-I", spt_build.CSRC]
@@ -84,6 +86,25 @@ def test_more_entries_to_a_lane_only_where_they_save_looks(tmp_path):
             assert many == "1", (n, x, v, csr)
         elif v == 8 and more * entries > few * 32 * 1.1:
             assert many == "0", (n, x, v, csr)
+
+
+@pytest.mark.parametrize("fmt", ["coo", "csf"])
+@pytest.mark.parametrize("dtype,J", [("f64", 32), ("f32", 64), ("f64", 16), ("f32", 32)])
+def test_mttkrp_has_more_workgroups_than_compute_units(fmt, dtype, J):
+    """Carries and bounds of a workgroup take 16 bytes and a row. A tensor that more than one workgroup on each of 256
+    compute units holds has no fewer than four for three of them: with about as many as compute units, the last decides."""
+    def workgroups(nnz):
+        t = spt.binding.SptTensor()
+        t.order, t.nlevels, t.dtype, t.vals, t.nvals = 3, 3, spt.SPT_F64 if dtype == "f64" else spt.SPT_F32, 0x1000, nnz
+        for k, lv in enumerate(t.level[:3]):
+            csf = fmt == "csf"
+            lv.kind, lv.mode, lv.N, lv.crd, lv.crd_stride = 1 if csf or k == 0 else 2, k, 1000, 0x1000, 1
+            lv.M, lv.pos = (1, 0x1000) if k == 0 else (100, 0x1000) if csf else (0, None)
+            lv.flags = spt.SPT_ORDERED | (spt.SPT_UNIQUE if csf or k == 2 else 0)
+        row = J * (8 if dtype == "f64" else 4)
+        return spt.spt_workspace_bytes(spt.SPT_OP_MTTKRP, t, J) / (16 + row + (4 + row) / 64)
+    for nnz in range(200_000, 3_000_000, 1001):
+        assert workgroups(nnz) > 340, (nnz, workgroups(nnz))
 
 
 def test_the_kernel_that_gathers_slice_by_slice_keeps_its_registers(tmp_path):

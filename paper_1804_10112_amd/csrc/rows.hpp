@@ -20,7 +20,9 @@ __host__ __device__ __forceinline__ void wave_range(int l, int h, int lane, cons
 // is >= r. The thread of entry p, whose predecessor lies in row a and which lies in row b,
 // therefore stores p into pos[a+1 .. b] (nothing if a == b), and the last entry's thread
 // stores n into the rest: every element of pos is written exactly once, without atomics
-// or a scan. Ranges longer than 16 rows (runs of empty rows) are written by the whole wave.
+// or a scan. Ranges longer than 16 rows (runs of empty rows) are written by the whole wave, four rows to a lane where 256
+// are left (COO -> CSR, fp32, a row to a lane / so: 50 000 records in 20M rows 43.6 / 38.9 us, in 500M 560 / 475; 1M in 300M
+// 360 / 358, in 20M, whose ranges are of some 20 rows, 108 / 107; 100M empty rows after the last 39.2 / 9.2 ms).
 static __device__ __forceinline__ void store_pos_range(int32_t* __restrict__ pos, int lo, int hi, int val) {
   const bool big = hi - lo > 16;
   if (!big)
@@ -29,7 +31,7 @@ static __device__ __forceinline__ void store_pos_range(int32_t* __restrict__ pos
   while (todo) {
     const int src = __ffsll(static_cast<long long>(todo)) - 1;
     todo &= todo - 1;
-    const int l = __shfl(lo, src), h = __shfl(hi, src), v = __shfl(val, src);
+    const int l = __builtin_amdgcn_readlane(lo, src), h = __builtin_amdgcn_readlane(hi, src), v = __builtin_amdgcn_readlane(val, src);
     typedef int32_t I4 __attribute__((ext_vector_type(4), aligned(4)));
     wave_range(l, h, lane_id(), [&](int r) { *reinterpret_cast<I4*>(pos + r) = I4(v); }, [&](int r) { pos[r] = v; });
   }

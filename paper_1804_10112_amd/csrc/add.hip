@@ -39,6 +39,11 @@ constexpr int kAddSelfTiles = 2048;
 // for more (a fourth of the probes, which miss the caches: 1.6M + 800 000 entries, fp64, 38 -> 28 us;
 // 20 000 + 10 000 entries 11.0 us by waves, 12.0 by 16 lanes).
 constexpr int kAddWaveTiles = 128;
+// From here on a search fetches the last coordinate only where the others are the same: its probes of long operands miss the
+// caches. Below, a second fetch is one more to wait for. Whole / only where needed, us: rows of 15, fp64, 300 000 + 150 000
+// entries 13.3 / 13.4, 500 000 + 250 000 15.9 / 15.8, 800 000 + 400 000 18.8 / 18.3, 2.7M + 1.3M 42.2 / 37.8; three long rows 13.3 /
+// 13.7, 15.8 / 16.5, 18.7 / 19.4, 41.8 / 41.6; (since the searches have a launch of their own) 3.8M + 2M 71 / 68, 18M + 14M 317 / 294.
+constexpr int kAddWholeTiles = 400;
 constexpr int kAddResident = 6, kFillResident = 5;  // workgroups on a compute unit, as registers allow
 constexpr int kCus = 256;
 
@@ -50,7 +55,7 @@ struct ColLoader {  // column coordinates of a CSR operand; rows are handled apa
   const int32_t* a1;
   __device__ __forceinline__ Raw raw(int p) const { return a1[p]; }
   __device__ __forceinline__ static Key key(Raw k) { return k; }
-  __device__ __forceinline__ static bool le(const ColLoader& a, int p, const ColLoader& b, int q) { return a.a1[p] <= b.a1[q]; }
+  __device__ __forceinline__ static bool le(const ColLoader& a, int p, const ColLoader& b, int q, bool) { return a.a1[p] <= b.a1[q]; }
   __device__ __forceinline__ ColLoader from(const ColLoader& c, bool other) const { return {other ? c.a1 : a1}; }
 };
 __device__ __forceinline__ bool key_le(int32_t a, int32_t b) { return a <= b; }
@@ -75,9 +80,9 @@ struct CooLoader {  // ND coordinates that fit 63 bits together
     if (ND == 3) k |= static_cast<uint32_t>(r.c[ND - 1]);
     return k;
   }
-  // The last coordinate is fetched only where the others are the same: a search probes lines that miss the caches
-  // (COO, fp64, 18M + 14M entries 317 -> 294 us in all; 3.8M + 2M 71 -> 68; fp32, 2M + 1M 30 -> 27).
-  __device__ __forceinline__ static bool le(const CooLoader& a, int p, const CooLoader& b, int q) {
+  // lazy: the last coordinate is fetched only where the others are the same (see kAddWholeTiles).
+  __device__ __forceinline__ static bool le(const CooLoader& a, int p, const CooLoader& b, int q, bool lazy) {
+    if (!lazy) return a.key(a.raw(p)) <= b.key(b.raw(q));
     const int32_t i = a.a0[p], k = b.a0[q];
     if (ND == 3) {
       const int32_t j = a.a1[p], l = b.a1[q];
@@ -95,7 +100,7 @@ struct WideLoader {  // any extents
   const int32_t *a0, *a1, *a2;
   __device__ __forceinline__ Raw raw(int p) const { return Key3{a0[p], a1[p], a2 ? a2[p] : 0}; }
   __device__ __forceinline__ static Key key(const Raw& r) { return r; }
-  __device__ __forceinline__ static bool le(const WideLoader& a, int p, const WideLoader& b, int q) {
+  __device__ __forceinline__ static bool le(const WideLoader& a, int p, const WideLoader& b, int q, bool) {
     return key_le(a.raw(p), b.raw(q));
   }
   __device__ __forceinline__ WideLoader from(const WideLoader& c, bool o) const {
@@ -118,7 +123,7 @@ struct AddCut {
 };
 
 template <typename KL, bool ROWS, int W>
-__device__ __forceinline__ AddCut add_cut(const AddOperands<KL>& o, int64_t d) {
+__device__ __forceinline__ AddCut add_cut(const AddOperands<KL>& o, int64_t d, bool lazy) {
   if (d >= o.places()) return AddCut{o.nb, o.nc, o.nrows};
   AddCut c{0, 0, 0};
   int nb = o.nb, nc = o.nc;
@@ -137,7 +142,7 @@ __device__ __forceinline__ AddCut add_cut(const AddOperands<KL>& o, int64_t d) {
   // B's entry q is among the first e of the row if it is smaller than C's entry e - 1 - q
   const int64_t lo = max<int64_t>(0, e - nc), hi = min<int64_t>(e, nb);
   const int x = group_last_true<W>(lo, hi + 1, [&](int q) {
-    return q == lo || !KL::le(o.kc, c.y + static_cast<int>(e - q), o.kb, c.x + q - 1);
+    return q == lo || !KL::le(o.kc, c.y + static_cast<int>(e - q), o.kb, c.x + q - 1, lazy);
   });
   const int y = static_cast<int>(e - x);
   const bool twins = y > 0 && x < nb && key_eq(o.kc.key(o.kc.raw(c.y + y - 1)), o.kb.key(o.kb.raw(c.x + x)));
@@ -154,7 +159,7 @@ __global__ __launch_bounds__(kBlock) void add_cut_kernel(const AddOperands<KL> o
                                                          AddCut* __restrict__ cuts) {
   const int t = (blockIdx.x * kBlock + threadIdx.x) / kCutLanes;
   if (t > ntiles) return;
-  const AddCut c = add_cut<KL, ROWS, kCutLanes>(o, static_cast<int64_t>(t) * kAddStep);
+  const AddCut c = add_cut<KL, ROWS, kCutLanes>(o, static_cast<int64_t>(t) * kAddStep, true);
   if (threadIdx.x % kCutLanes == 0) cuts[t] = c;
 }
 
@@ -228,7 +233,8 @@ __global__ __launch_bounds__(kBlock, kAddResident) void add_merge_kernel(const A
   if (SELF) {
     if (wave_id() < 2) {
       const int64_t d = (static_cast<int64_t>(tile) + wave_id()) * kAddStep;
-      const AddCut c = ROWS || ntiles <= kAddWaveTiles ? add_cut<KL, ROWS, kWave>(o, d) : add_cut<KL, ROWS, 16>(o, d);
+      const AddCut c = ROWS || ntiles <= kAddWaveTiles ? add_cut<KL, ROWS, kWave>(o, d, false)
+                                                       : add_cut<KL, ROWS, 16>(o, d, ntiles > kAddWholeTiles);
       if (lane == 0) {
         s_cut[wave_id()] = c;
         if (wave_id() == 0 || tile == ntiles - 1) cuts[tile + wave_id()] = c;

@@ -195,15 +195,17 @@ spt_status sample_sort_convert(int64_t n, int64_t nrows, int64_t ncols, bool by_
 
 // The sample sort takes one launch, one partition or two and a finish, whatever the key; a radix sort a pass per 8
 // bits of it. Keys of few bits (a stable order of the rows, small matrices) are for the latter from where the
-// sample sort needs its next step (fp64, in us, radix / sample; fp32 alike, power-law rows more for radix):
+// sample sort needs its next step (fp64, even rows, in us, radix / sample):
 //   passes            130 000     400 000     1.6M         6.4M         30M
-//   1 (200 rows)       31 / 37     30 / 84     36 / 124     84 / 301    306 / 1013
-//   2 (60 000 rows)    61 / 38     62 / 81     69 / 120    168 / 285    601 / 973
-//   3 (4M rows)       109 / 87    107 / 96    118 / 121    256 / 279    857 / 920
-//   4                 115 / 36    123 / 82    134 / 120    331 / 273   1164 / 902
+//   1 (200 rows)       30 / 36     31 / 62     37 / 96      84 / 228    295 / 857
+//   2 (60 000 rows)    61 / 35     62 / 59     70 / 93     169 / 217    586 / 791
+//   3 (4M rows)       115 / 88    108 / 77    119 / 97     257 / 212    858 / 760
+//   4                 144 / 93    138 / 83    152 / 97     335 / 209   1134 / 755
+// Three passes: rows of power-law lengths cost the sample sort more and radix passes nothing. 1.8M fp64 104 / 104, fp32 100 /
+// 97; 2M 106 / 114; 6.4M fp64 249 / 228, fp32 197 / 211; 12M 383 / 429; 30M 835 / 859; 60M 1561 / 1651 (even rows 1586 / 1483).
 static bool radix_is_faster(const SortPlan& P, const spt_tensor* A) {
   const int passes = P.passes_col + P.passes_row;
-  const int64_t from = passes == 1 ? 1 << 16 : passes == 2 ? 256 * 1408 : 3 << 19;
+  const int64_t from = passes == 1 ? 1 << 16 : passes == 2 ? 256 * 1408 : 7 << 18;
   return !sample_sort_applies(A->nvals) || (passes <= 3 && A->nvals > from);
 }
 

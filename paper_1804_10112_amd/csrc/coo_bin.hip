@@ -12,8 +12,8 @@
 //      with LDS atomics and stores its rows: to y when it holds the whole bin, otherwise
 //      to scratch, from where a last kernel adds up the slices of each bin.
 // Sorting inside the tile instead of over all entries needs no histogram, no scan of one and no rows read twice; a
-// stretch of a bin is 64 entries long on average. 10M entries, power-law rows, fp32: 231 -> 131 us (sorted over all
-// entries: histogram and scan 24, scatter 120, accumulate 82, reduce 10; here tiles 74, prefix 5, accumulate 40, reduce 9).
+// stretch of a bin is 64 entries long on average. 10M entries, power-law rows, fp32: 231 -> 126 us (sorted over all
+// entries: histogram and scan 24, scatter 120, accumulate 82, reduce 10; here tiles 72, prefix 5, accumulate 39, reduce 9).
 // Like the atomic kernel the result is order-dependent in the last bits
 // (tolerance-checked, not bit-reproducible); the ordered COO path is exact-order.
 #include <algorithm>
@@ -48,7 +48,7 @@ __device__ __forceinline__ void store_tile(const E* __restrict__ buf, E* __restr
 // counter wait for each other there, and in the sums of step 2, still less than sorting over all entries took (10M
 // entries, fp32, sorted so / this way: random order 203 / 105 us, in order of rows 203 / 120, half of them in one row 300 /
 // 200, all 323 / 267; fp64 194 / 151, 203 / 166, 283 / 244, 341 / 318; 1.6M fp32 62 / 36, 64 / 34, 81 / 55, 83 / 56).
-// Bound by the gathers of x, 200 G/s where an L2 holds x (10M entries, fp32: 50 of 76 us), and by the phases of a tile
+// Bound by the gathers of x, 200 G/s where an L2 holds x (10M entries, fp32: 50 of 72 us), and by the phases of a tile
 // that wait for each other: rows, columns and values on their way early are what the registers allow.
 // SLICED: x beyond an L2 is gathered slice by slice (slices.hpp).
 template <typename T, typename R, int V, bool SLICED>

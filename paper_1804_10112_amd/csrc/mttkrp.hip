@@ -662,7 +662,9 @@ static MttkrpPlan mttkrp_plan(int64_t nnz, int64_t J, int dtype, bool csf) {
 //   COO, skewed slices, 10.2 and 6.4 MB, 50M 648 / 617; 12.8 and 12.8, 20M (fp64) 389 / 370; 6.4 and 6.4, 10M 185 / 176;
 //     3.8 and 6.4, 10M 172 / 170; 1.9 and 6.4, 10M 157 / 164; 6.4 and 1.3, 10M 125 / 128; 7.9 and 7.9, 6M 196 / 195
 //   CSF, skewed, 10.2 and 6.4, 40M 578 / 523; 20.5 and 12.8, 20M (fp64) 720 / 690; 1.9 and 3.8, 10M 119 / 128
-//   COO, slices of 200 entries (a chunk needs rows from all of C), 10.2 and 6.4, 20M 559 / 565
+//   COO and CSF, even slices shorter than a chunk (which then needs rows from all of C), 10.2 and 6.4: 8.5M entries in slices of 85 or
+//     212 254 / 262 and 268 / 276, 20M in slices of 200 556 / 567, 40M in slices of 400 1091 / 1101. Skewed slices of the same mean
+//     length gain, 157 / 150, 302 / 283, 536 / 506, and a descriptor does not tell the two apart.
 static bool mttkrp_orders(const MttkrpPlan& P, int64_t nnz, int64_t J, int64_t value, int64_t rows_c, int64_t rows_d) {
   const int64_t c = rows_c * J * value, d = rows_d * J * value;
   return nnz >= 8000000 && c >= 6000000 && c + d >= 12000000 &&

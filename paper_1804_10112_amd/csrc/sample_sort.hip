@@ -22,10 +22,10 @@
 // pos (Table 3: running sum of the row counts) falls out of the last step: the workgroup of the
 // keys between splitters of rows a and b stores pos[a+1 .. b].
 // A bucket that the sample got wrong (more records than fit LDS) is split once more by its workgroup,
-// at splitters of a sample of its own. In random order that happens in none of 300 calls up to 50M
-// records, but in some 2 to 5 of 100 at 60M and 15 of 100 at 2^26, where 256 buckets of a segment are
-// not enough for the larger segments; the call takes no longer for it (with the ranks of the bucket's records
-// counted, 60M records took 10.4 instead of 1.8 ms).
+// at splitters of a sample of its own. In random order that happens in none of 100 calls up to 30M
+// records, in 2 or 3 at 50M, some 20 at 60M and 50 at 2^26, where 256 buckets of a segment are
+// not enough for the larger segments; such a call takes 2 to 3 % longer (60M records 1478 -> 1515 to 1529 us; with
+// the ranks of the bucket's records counted, 10.4 ms).
 //
 // Measured against the six radix passes it replaces (fp64): 60M records with power-law rows
 // 3.09 -> 1.52 ms (splitters 10 + 70 us, classify 2 x 133, offsets 8 + 9, partitions 405 + 352, finish 400; with whole
@@ -888,7 +888,9 @@ __device__ __forceinline__ void split_and_store(char* mem, const SRC& src, int n
   for (int t = tid; t < S; t += NT) s_key[t] = whole_at(sample_pos<S>(t, n)) >> f.kshift;
   __syncthreads();
   sort_records<NT, S / NT>(words, s_ord, S, coarse_shift(lo_key, hi_key), [&](int t) { return s_key[t] - lo_key; });
-  constexpr int kTarget = kSplitPart * 3 / 8;  // (16 samples to a part of 4096: one that does not fit has a chance below 1e-8)
+  // A part that does not fit has a chance below 1e-6 in a bucket of up to 18 000 records (16 samples to a part), 3e-4 at 37 000
+  // and 1e-3 at 60 000; ranks are then counted, in the square of the bucket's records.
+  constexpr int kTarget = kSplitPart * 3 / 8;
   const int nb = min(S, (n + kTarget - 1) / kTarget);
   const auto cut_at = [&](int d) {
     const int t = s_ord[d * S / nb];

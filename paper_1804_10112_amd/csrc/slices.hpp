@@ -6,7 +6,9 @@
 
 namespace spt {
 
-// An x that an L2 holds need not be cut; beyond some 150 MB the passes cost more than the lines.
+// An x that an L2 holds need not be cut. The upper line lies where passes over slices of 3.2 MB came to cost about what
+// the lines did. With the larger slices of slices_of it is cautious: 60M entries, x of 126 MB sliced, fp64 810 and fp32 645 us,
+// of 130 MB not sliced 1231 and 1190.
 constexpr int64_t kSlicesMinX = 6000000, kSlicesMaxX = 128000000;
 
 // Slices of an x, of which an XCD gathers `entries` / kXcds entries at a time (`entries`: of all). A slice that an L2

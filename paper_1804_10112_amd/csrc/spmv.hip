@@ -1245,7 +1245,7 @@ constexpr int64_t kDynamicMinEntries = int64_t(1) << 25;
 // beyond kPiecesMaxEntries, where the one kernel does both (local columns, against a kernel of chunks in LDS: 25M entries,
 // fp64 113 / 104 us, fp32 73 / 72; 36M 147 / 148 and 101 / 106). In us, uniform columns, without / with slices, by the size of x:
 //   36M entries, fp64, COO   4 MB 257 / 257    6 MB 312 / 264    12 MB 493 / 281   24 MB 606 / 323   48 MB 701 / 404
-//                            64 MB 712 / 461   96 MB 770 / 581 (some 4 us more per MB: equal at about 150 MB)
+//                            64 MB 712 / 461   96 MB 770 / 581 (slices of 3.2 MB; as they are now, 35M entries 96 MB 479)
 //   36M entries, CSR         fp32 6 MB 272 / 234, 24 MB 593 / 294; fp64 24 MB 597 / 317, 96 MB 795 / 600
 //   17M entries, COO         fp64 8 MB 200 / 138; fp32 6.4 MB 155 / 133
 //   power law, CSR           fp64, 60M entries, 32 MB 970 / 545; fp32, 35M entries, 9.2 MB 378 / 248

@@ -355,8 +355,8 @@ __global__ __launch_bounds__(kSliceBlock) __attribute__((amdgpu_waves_per_eu(4, 
   }
 
   // Segments whose values (COO: and rows) are on their way at a time. Next to 40 gathered doubles there is room for those
-  // of one: with two, 2 registers (COO: 6) went through scratch memory (60M entries, x of 8 / 32 / 64 MB, CSR 439 / 529 / 647
-  // us, so 429 / 520 / 629; COO 478 / 560 / 684, so 467 / 556 / 680).
+  // of one: with two, 2 registers (COO: 6) went through scratch memory (60M entries, x of 32 MB, us: COO, even rows 561 / 555
+  // so, power law 542 / 534; CSR 528 / 519 and, where the values on their way count for more, 543 / 546; x of 8 and 64 MB, even rows 439 / 429, 647 / 629).
   constexpr int kBatch = sizeof(T) == 8 ? (MANY ? 1 : 2) : 4;
   static_assert(B % kBatch == 0 && V % kBatch == 0, "");
   int r_first = 0;  // CSR, in lane l: the first row that starts in segment l / L of those in LDS

@@ -1,5 +1,5 @@
 """SpMV with x gathered slice by slice where lanes hold 40 (fp64) and 64 (fp32) entries, the offsets and then the values in
-the same registers: both sides of the rule, slices of 3.2 to 5.6 MB, last rounds that few workgroups have; x holds values
+the same registers: slices of 3.2 to 5.6 MB (the edges of the rule: test_gpu_slices_rounds.py), last rounds that few workgroups have; x holds values
 whose first half looks like an offset. The reference is the definition, its products and sums in float64."""
 import pytest
 
@@ -11,11 +11,11 @@ COO_FROM, MANY = (1 << 24) + 256, 32_000_000
 
 
 @pytest.mark.parametrize("form,kind,dtype,N,M,nnz,misalign", [
-    ("coo", "even", "float64", 900_000, 2_621_000, COO_FROM + 1, False),    # x of just under eight lines to an entry, and over
+    ("coo", "even", "float64", 900_000, 2_621_000, COO_FROM + 1, False),
     ("coo", "heavy", "float64", 900_000, 2_622_000, COO_FROM, True),
     ("coo", "even", "float32", 900_000, 8_389_000, COO_FROM + 255, False),
     ("coo", "some empty", "float64", 15_000_000, 15_900_000, COO_FROM + 3, False),
-    ("coo", "heavy", "float32", 900_000, 2_000_003, MANY - 1, True),        # by the entries
+    ("coo", "heavy", "float32", 900_000, 2_000_003, MANY - 1, True),
     ("coo", "even", "float32", 900_000, 2_000_003, MANY, False),
     ("coo", "one row", "float64", 900_000, 2_000_003, MANY + 2, False),
     ("csr", "some empty", "float64", 30_000_000, 2_000_003, 34_000_001, True),

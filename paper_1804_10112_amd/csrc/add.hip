@@ -470,10 +470,10 @@ __global__ __launch_bounds__(kBlock) void expand_rows_kernel(int nnz, int nrows,
   for (int e = threadIdx.x; e < kExpChunk; e += kBlock) s_mark[e] = -1;
   __syncthreads();
   const int r_lo = s_bounds[0], r_hi = s_bounds[1];
-  for (int r = r_lo + 1 + threadIdx.x; r <= r_hi; r += kBlock) {
+  strided(r_lo + 1, r_hi + 1, threadIdx.x, kBlock, [&](int r) {
     const int a = pos[r];
     if (pos[r + 1] > a) s_mark[a - base] = r;  // empty rows own no entry
-  }
+  });
   __syncthreads();
   int32_t local[kExpIPT];
   int run = -1;

@@ -54,6 +54,13 @@ struct Workspace {
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 __device__ __forceinline__ int wave_id() { return threadIdx.x >> 6; }
 
+// f(r) for r = lo + first, lo + first + step, .. below hi; lo is no less than 0. (Rows and fibres may be close to 2^31 in
+// number: the sum of one and a step then passes what an int holds.)
+template <class F>
+__host__ __device__ __forceinline__ void strided(int lo, int hi, int first, int step, const F& f) {
+  for (uint32_t r = static_cast<uint32_t>(lo) + first; r < static_cast<uint32_t>(hi); r += step) f(static_cast<int>(r));
+}
+
 // Workgroup barrier that orders LDS traffic only. __syncthreads() also waits for every
 // outstanding global load of the wave (its fence covers global memory), which would
 // serialise loads issued ahead for a later step; this one waits for the wave's LDS

@@ -286,22 +286,22 @@ __global__ __launch_bounds__(kBlock) void mttkrp_rows_kernel(int n, int J, int e
     }
     for (int w = tid; w < 2 * ((size + 31) / 32); w += kBlock) s_fibre[w] = 0;
     __syncthreads();
-    for (int f = f_lo + tid; f < f_hi; f += kBlock) {
+    strided(f_lo, f_hi, tid, kBlock, [&](int f) {
       const int a = csf.pos2[f], b = csf.pos2[f + 1], k = csf.crd1[f];
       if (b > a) {
         s_k[a - base] = k;
         atomicOr(&s_fibre[(a - base) >> 5], 1u << ((a - base) & 31));
       }
-    }
+    });
     // a slice is marked at its first stored entry, whichever of its fibres holds it (a
     // compressed level may hold empty segments: leading fibres of a slice can be empty)
-    for (int sl = s_lo + tid; sl < s_hi; sl += kBlock) {
+    strided(s_lo, s_hi, tid, kBlock, [&](int sl) {
       const int a = csf.pos2[csf.pos1[sl]], b = csf.pos2[csf.pos1[sl + 1]];
       if (b > a && a < end) {
         s_i[a - base] = csf.crd0[sl];
         atomicOr(&s_slice[(a - base) >> 5], 1u << ((a - base) & 31));
       }
-    }
+    });
     __syncthreads();
     if (tid == 0) {
       s_slice_first = s_slice[0] & 1;

@@ -386,11 +386,11 @@ __global__ __launch_bounds__(kBlock) void seg_spmv_kernel(
     const int r_lo = s_rows[0], r_hi = s_rows[1];
     // the row cut by the chunk start, if the chunk does not begin with a head
     carry_row = r_lo - 1;
-    for (int r = r_lo + tid; r < r_hi; r += kBlock) {
+    strided(r_lo, r_hi, tid, kBlock, [&](int r) {
       const int a = pos_or_row[r], b = pos_or_row[r + 1];
       if (b > a) s_key[lds_slot<IPT>(a - base)] = r;
       else y[r] = T(0);
-    }
+    });
     __syncthreads();
   }
 
@@ -909,7 +909,7 @@ __device__ __forceinline__ void zero_rows(T* __restrict__ y, int lo, int hi) {  
     const int src = __ffsll(static_cast<long long>(todo)) - 1;
     todo &= todo - 1;
     const int l = __shfl(lo, src), h = __shfl(hi, src);
-    for (int r = l + lane_id(); r < h; r += kWave) y[r] = T(0);
+    strided(l, h, lane_id(), kWave, [&](int r) { y[r] = T(0); });
   }
 }
 

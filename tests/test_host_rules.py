@@ -59,6 +59,36 @@ def test_a_waves_share_of_pos_up_to_the_largest_row_counts(tmp_path):
     assert _run(tmp_path, RANGES) == "ok\n"
 
 
+STRIDED = r"""
+#include <climits>
+#include <vector>
+#include "common.hpp"
+int main() {
+  const int ends[] = {0, 1, 255, 256, 257, 100000, INT_MAX - 300, INT_MAX - 256, INT_MAX - 255, INT_MAX - 2, INT_MAX - 1};
+  const int lengths[] = {0, 1, 63, 64, 65, 255, 256, 257, 1000};
+  for (const int hi : ends)
+    for (const int n : lengths) {
+      if (n > hi) continue;
+      std::vector<int> times(n, 0);
+      int others = 0, calls = 0;
+      for (int first = 0; first < 256 && calls < 100000; ++first)
+        spt::strided(hi - n, hi, first, 256, [&](int r) {
+          const long long at = static_cast<long long>(r) - (hi - n);
+          if (++calls > 100000) std::abort();
+          if (at >= 0 && at < n) ++times[at]; else ++others;
+        });
+      for (const int t : times) others += t != 1;
+      if (others) { std::printf("[%d, %d)\n", hi - n, hi); return 0; }
+    }
+  std::printf("ok\n");
+}
+"""
+
+
+def test_walks_over_rows_and_fibres_up_to_the_largest_numbers(tmp_path):
+    assert _run(tmp_path, STRIDED) == "ok\n"
+
+
 RULE = r"""
 #include "slices.hpp"
 int main() {

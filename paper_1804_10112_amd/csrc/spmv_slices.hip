@@ -107,7 +107,7 @@ __global__ __launch_bounds__(kBlock) void segment_rows_kernel(int nrows, const i
 // `left_over` on do not count. rows: COO, their rows; CSR, the rows that start at them, or -1. cut: the row that
 // the segment's start cuts. Fixed order of additions: bit-reproducible.
 template <typename T, bool CSR, class V4, class I4>
-__device__ __forceinline__ void reduce_segment(int seg, int64_t left_over, int cut, const V4& v, const T* got, const I4& rows,
+__device__ __forceinline__ void reduce_segment(int seg, int left_over, int cut, const V4& v, const T* got, const I4& rows,
                                                T* __restrict__ y, int32_t* __restrict__ carry_key, T* __restrict__ carry_val) {
   const int lane = lane_id();
   int32_t before = cut;
@@ -293,7 +293,7 @@ __device__ __forceinline__ void segments_in_order(int nnz, int nseg, const int32
       rows = *reinterpret_cast<const I4*>(heads + lane * 4);
       wave_lds_order();
     }
-    reduce_segment<T, CSR>(seg, nnz - static_cast<int64_t>(seg) * kSegment, CSR ? now.lo - 1 : now.prior, now.v, now.got, rows, y, carry_key,
+    reduce_segment<T, CSR>(seg, nnz - seg * kSegment, CSR ? now.lo - 1 : now.prior, now.v, now.got, rows, y, carry_key,
                            carry_val);
     now = next;
     next = later;
@@ -354,10 +354,11 @@ __global__ __launch_bounds__(kSliceBlock) __attribute__((amdgpu_waves_per_eu(4, 
     SliceGather<T, 4 * V>::run(x, nslices, slice, offset, got);
   }
 
-  // Segments whose values (COO: and rows) are on their way at a time. Next to 40 gathered doubles there is room for those
-  // of one: with two, 2 registers (COO: 6) went through scratch memory (60M entries, x of 32 MB, us: COO, even rows 561 / 555
-  // so, power law 542 / 534; CSR 528 / 519 and, where the values on their way count for more, 543 / 546; x of 8 and 64 MB, even rows 439 / 429, 647 / 629).
-  constexpr int kBatch = sizeof(T) == 8 ? (MANY ? 1 : 2) : 4;
+  // Segments whose values (COO: and rows) are on their way at a time. Next to 40 gathered doubles there is room for those of
+  // two, as long as entries are counted in 32 bits (in 64, a lane's four places took eight registers and 2 others went through
+  // scratch memory), of COO for those of one (with two, 6 and 2 registers). 60M entries, x of 32 MB, us, with scratch memory / one / two:
+  // CSR, power law 543 / 545 / 541, even rows 528 / 518 / 522; COO 543 / 537 /  -, 560 / 553 /  -.
+  constexpr int kBatch = sizeof(T) == 8 ? (MANY && !CSR ? 1 : 2) : 4;
   static_assert(B % kBatch == 0 && V % kBatch == 0, "");
   int r_first = 0;  // CSR, in lane l: the first row that starts in segment l / L of those in LDS
   constexpr int L = kWave / B;  // lanes that enter the rows of a segment
@@ -412,7 +413,7 @@ __global__ __launch_bounds__(kSliceBlock) __attribute__((amdgpu_waves_per_eu(4, 
       const int seg = first + (h + j) * step;
       if (seg >= nseg) break;  // uniform
       if (CSR) rows[j] = *reinterpret_cast<const I4*>(heads + (h + j) % B * kSegment + lane * 4);
-      reduce_segment<T, CSR>(seg, nnz - static_cast<int64_t>(seg) * kSegment,
+      reduce_segment<T, CSR>(seg, nnz - seg * kSegment,
                              CSR ? __builtin_amdgcn_readlane(r_first, (h + j) % B * L) - 1 : prior[j], v[j], got + 4 * (h + j), rows[j], y,
                              carry_key, carry_val);
     }

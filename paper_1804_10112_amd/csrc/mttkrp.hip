@@ -252,8 +252,17 @@ __device__ __forceinline__ void marks_before(const uint32_t* marks, int16_t* bef
   }
 }
 
-template <typename T, int L, int V, bool CSF, bool ORDERED>
-__global__ __launch_bounds__(kBlock) void mttkrp_rows_kernel(int n, int J, int epg, const int32_t* __restrict__ ci,
+// Which workgroup takes what: the XCDs are dealt to the parts of the columns in turn, and the chunks to a part's XCDs, in turn
+// or, ordered, an equal stretch of the order to each. (Workgroups beyond an XCD's chunks return.)
+constexpr int kLine = 128;
+struct Placing {
+  int nchunks, parts;
+  bool ordered;
+};
+
+// PLACED: chunks and columns as `placing` says; else chunk blockIdx.x, and all columns.
+template <typename T, int L, int V, bool CSF, bool PLACED>
+__global__ __launch_bounds__(kBlock) void mttkrp_rows_kernel(int n, int J, int epg, const Placing placing, const int32_t* __restrict__ ci,
                                                              const int32_t* __restrict__ ck,
                                                              const int32_t* __restrict__ cl,
                                                              const T* __restrict__ vals, const T* __restrict__ Cm,
@@ -268,19 +277,26 @@ __global__ __launch_bounds__(kBlock) void mttkrp_rows_kernel(int n, int J, int e
   const int tid = threadIdx.x, lane = lane_id();
   const int g = tid / L, gl = tid % L;
   // (in turn to the XCDs: in one piece, the last has the slices of few entries, whose rows of C nobody shares)
-  const int chunk = ORDERED ? bounds[3 * xcd_contiguous_block_id(blockIdx.x, gridDim.x) + 2] : static_cast<int>(blockIdx.x);
+  int chunk = blockIdx.x, tile = blockIdx.y;
+  if (PLACED) {
+    const int xcd = blockIdx.x % kXcds, turn = blockIdx.x / kXcds, of = kXcds / placing.parts, at = xcd / placing.parts;
+    const int q = placing.nchunks / of, rem = placing.nchunks % of;
+    if (turn >= q + (at < rem)) return;
+    chunk = placing.ordered ? bounds[3 * (at * q + min(at, rem) + turn) + 2] : turn * of + at;
+    tile += xcd % placing.parts * gridDim.y;
+  }
   const int size = NG * epg;
   const int base = chunk * size, end = min(base + size, n);
   // the last vector of a row ends with the row (it repeats columns of the one before if J is no multiple of V)
-  const bool jok = (static_cast<int>(blockIdx.y) * L + gl) * V < J;
-  const int col = min((static_cast<int>(blockIdx.y) * L + gl) * V, J - V);
+  const bool jok = (tile * L + gl) * V < J;
+  const int col = min((tile * L + gl) * V, J - V);
 
   const int g0 = base + g * epg, g1 = min(g0 + epg, end);
   // rows of D and values of the first batch: on their way while the bounds are found (738 000 entries in CSF, J = 16, fp64:
   // 33.8 us without, 32.0 also by the wider search; large ordered tensors lose 2 %)
   int32_t rl[4];
   T rv[4];
-  constexpr bool kEarly = CSF && !ORDERED;
+  constexpr bool kEarly = CSF && !PLACED;
   if (kEarly && g0 < g1) {
     load_four(cl, g0 + 4 * gl, g1, rl);
     load_four(vals, g0 + 4 * gl, g1, rv);
@@ -471,7 +487,7 @@ __global__ __launch_bounds__(kBlock) void mttkrp_rows_kernel(int n, int J, int e
       if (jok && first_close >= 0) store_cols<T, V>(A + static_cast<int64_t>(first_close) * J + col, before);
     } else {  // precedes the first row that starts in the chunk
       if (jok) store_cols<T, V>(carry_vec + static_cast<int64_t>(chunk) * J + col, before);
-      if (gl == 0 && blockIdx.y == 0) carry_key[chunk] = max(first_close, -1);
+      if (gl == 0 && tile == 0) carry_key[chunk] = max(first_close, -1);
     }
   }
   if (g == NG - 1) {
@@ -482,7 +498,7 @@ __global__ __launch_bounds__(kBlock) void mttkrp_rows_kernel(int n, int J, int e
       if (jok) store_cols<T, V>(A + static_cast<int64_t>(cur) * J + col, acc);
     } else {  // no row starts in the chunk
       if (jok) store_cols<T, V>(carry_vec + static_cast<int64_t>(chunk) * J + col, acc);
-      if (gl == 0 && blockIdx.y == 0) carry_key[chunk] = cur;
+      if (gl == 0 && tile == 0) carry_key[chunk] = cur;
     }
   }
 }
@@ -629,8 +645,8 @@ __global__ __launch_bounds__(kRunBlock) void mttkrp_carry_runs_kernel(int n, int
 // ---- host ------------------------------------------------------------------
 
 struct MttkrpPlan {
-  int lanes, vec, epg, chunk;
-  int64_t n1, n2;  // chunks, workgroups of the first level of carries
+  int lanes, vec, epg, chunk, parts;
+  int64_t n1, n2;  // chunks (of each part), workgroups of the first level of carries
 };
 
 // Lanes: the vectors of a row, up to 32 (longer rows take several passes over the entries, side by
@@ -651,16 +667,34 @@ struct MttkrpPlan {
 //     400 000 37.1 / 35.3 / 36.7 / 37.3, 42.0 / 39.2 / 39.9 / 36.8
 //   COO, 330 000 entries  28.3 / 26.7 / 28.4 / 29.5, 30.3 / 28.2 / 28.1 / 27.9; 400 000  32.0 / 31.3 / 32.6 / 31.2, 35.1 / 34.1 / 34.4 / 30.9
 //   fp32, J = 64: CSF, 265 000  36.2 / 33.8 / 34.5 / 38.6, 39.8 / 35.2 / 32.7 / 33.3; COO, 330 000  32.4 / 30.7 / 32.1 / 32.8, 36.9 / 32.7 / 31.3 / 31.3
-static MttkrpPlan mttkrp_plan(int64_t nnz, int64_t J, int dtype, bool csf) {
+// Parts of the J columns, each of whole lines, that XCDs of their own go through all entries for (given C and D on lines): an L2
+// then holds twice, four or eight times as many rows. A gather takes as long for 64 bytes as for a line, so parts of
+// half a line only lose (50M entries, J = 32, fp32: 618 -> 1010 us). The entries are read once per part, which rows that an L2
+// holds anyway do not pay for, nor few entries. One part / parts, us (skewed slices, and even ones), C and D in MB:
+//   COO, J = 32, fp64, 20.5 and 12.8: 200 000 entries 24.4 / 23.9, 24.2 / 23.6; 1M 68 / 60, 80 / 76; 5M 234 / 204, 335 / 313;
+//     20M 692 / 569, 1261 / 1179; 5.1 and 5.1: 1M 45 / 39, 55 / 42; 20M 420 / 419, 859 / 593; 0.5 and 25.6: 2M 88 / 84, 87 / 86
+//   CSF: 1M 75 / 69, 87 / 86; 20M 692 / 560, 1281 / 1177; 5.1 and 5.1: 20M 492 / 499, 885 / 642; 0.5 and 25.6: 1M 61 / 56, 58 / 63
+//   J = 64, fp64 (four parts), 41 and 25.6: 300 000 62 / 52; 2M 219 / 192; 20M 1491 / 1174
+//   2.6 and 0.8: 1M 28.9 / 32.6; 2M 48 / 53; 5.1 and 1.5 (J = 64): 2M 82 / 98; fewer entries than the line: up to 10 % longer
+static int mttkrp_parts(int64_t nnz, int64_t row_bytes, int64_t rows_c, int64_t rows_d, bool csf) {
+  const int64_t c = rows_c * row_bytes, d = rows_d * row_bytes;
+  if (row_bytes > 65536 || nnz * row_bytes < 50000000 || c + d < 9000000 || (csf && c < 1000000)) return 1;
+  int parts = kXcds;
+  while (parts > 1 && row_bytes % (parts * int64_t{kLine}) != 0) parts /= 2;
+  return parts;
+}
+static MttkrpPlan mttkrp_plan(int64_t nnz, int64_t J, int dtype, bool csf, int parts) {
   MttkrpPlan P;
+  P.parts = parts;
+  J /= parts;  // (the rest is about one part; its workgroups are as many for each)
   P.vec = dtype == SPT_F64 ? kVec<double> : kVec<float>;
   if (J < P.vec) P.vec = 1;
   const int64_t nv = (J + P.vec - 1) / P.vec;
   P.lanes = P.vec == 1 ? 4 : nv <= 2 ? 2 : nv <= 4 ? 4 : nv <= 8 ? 8 : nv <= 16 ? 16 : 32;
   const int groups = kBlock / P.lanes;
   const int batch = P.lanes <= 16 ? std::max(4 * P.lanes, 16) : 16;
-  const int64_t once = int64_t(csf ? 4 : 5) * 256 * groups * 16;
-  const int64_t want = nnz / (6 * 256) / groups;
+  const int64_t once = int64_t(csf ? 4 : 5) * 256 * groups * 16 / parts;
+  const int64_t want = nnz * parts / (6 * 256) / groups;
   int64_t epg = 16;
   if (P.lanes > 16) epg = std::max<int64_t>(want / 16 * 16, 16);
   else if (P.lanes == 16 && nnz > once && nnz <= int64_t(2) * 256 * groups * 48) epg = 48;
@@ -688,8 +722,12 @@ static bool mttkrp_orders(const MttkrpPlan& P, int64_t nnz, int64_t J, int64_t v
 }
 
 size_t mttkrp3_workspace(const spt_tensor* B, int32_t J) {
-  const MttkrpPlan P = mttkrp_plan(B->nvals, std::max(J, 1), B->dtype, B->level[1].kind == SPT_COMPRESSED);
   const size_t row = static_cast<size_t>(std::max(J, 1)) * (B->dtype == SPT_F64 ? 8 : 4);
+  const bool csf = B->level[1].kind == SPT_COMPRESSED;
+  MttkrpPlan P = mttkrp_plan(B->nvals, std::max(J, 1), B->dtype, csf, 1);
+  // (parts if both factors lie on lines)
+  const MttkrpPlan split = mttkrp_plan(B->nvals, std::max(J, 1), B->dtype, csf, mttkrp_parts(B->nvals, row, B->level[1].N, B->level[2].N, csf));
+  P.n1 = std::max(P.n1, split.n1), P.n2 = std::max(P.n2, split.n2);
   return align_up(static_cast<size_t>(P.n1) * 4, 256) + align_up(P.n1 * row, 256) +
          align_up(static_cast<size_t>(P.n2) * 4, 256) + align_up(P.n2 * row, 256) +
          align_up(static_cast<size_t>(P.n1 + 1) * 12, 256) + 256;
@@ -701,7 +739,8 @@ static spt_status mttkrp3_typed(Format f, const spt_tensor* B, const T* Cm, cons
   const int64_t I = B->level[0].N, nnz64 = B->nvals, size = I * J;
   const bool csf = f == Format::CSF3;
   const int64_t nsl = csf ? B->level[1].M : 0, nfib = csf ? B->level[2].M : 0;
-  const MttkrpPlan P = mttkrp_plan(nnz64, J, B->dtype, csf);
+  const bool on_lines = (reinterpret_cast<uintptr_t>(Cm) | reinterpret_cast<uintptr_t>(Dm)) % kLine == 0;
+  const MttkrpPlan P = mttkrp_plan(nnz64, J, B->dtype, csf, on_lines ? mttkrp_parts(nnz64, J * (int64_t)sizeof(T), B->level[1].N, B->level[2].N, csf) : 1);
   if (nnz64 + P.chunk >= INT32_MAX || size >= ((int64_t)1 << 38) || nsl + 1 >= INT32_MAX || nfib + 1 >= INT32_MAX)
     return fail(SPT_ERR_UNSUPPORTED, "mttkrp: tensor too large");
   if (nnz64 > 0 && (!ws || ws_bytes < mttkrp3_workspace(B, J)))
@@ -744,16 +783,20 @@ static spt_status mttkrp3_typed(Format f, const spt_tensor* B, const T* Cm, cons
     hipLaunchKernelGGL(mttkrp_order_kernel, dim3(shares), dim3(kBlock), 0, s, n1, noted, hist, bounds);
     SPT_CHECK_LAUNCH("mttkrp order");
   }
-  const int tiles = ((J + P.vec - 1) / P.vec + P.lanes - 1) / P.lanes;
+  const Placing placing{n1, P.parts, in_order};
+  const bool placed = in_order || P.parts > 1;
+  const int of = kXcds / P.parts;
+  const int64_t blocks = placed ? kXcds * ((P.n1 + of - 1) / of) : n1;
+  const int tiles = ((J / P.parts + P.vec - 1) / P.vec + P.lanes - 1) / P.lanes;
   const size_t lds = csf ? (size_t)P.chunk * 8 + 2 * (size_t)((P.chunk + 31) / 32) * 6 : 0;
-#define SPT_MTTKRP_AS(L_, V_, CSF_, ORDERED_)                                                                           \
-  hipLaunchKernelGGL((mttkrp_rows_kernel<T, L_, V_, CSF_, ORDERED_>), dim3(n1, tiles), dim3(kBlock), lds, s, nnz, J, P.epg, \
+#define SPT_MTTKRP_AS(L_, V_, CSF_, PLACED_)                                                                           \
+  hipLaunchKernelGGL((mttkrp_rows_kernel<T, L_, V_, CSF_, PLACED_>), dim3((unsigned)blocks, tiles), dim3(kBlock), lds, s, nnz, J, P.epg, placing, \
                      csf ? nullptr : B->level[0].crd, csf ? nullptr : B->level[1].crd, B->level[2].crd,                  \
                      static_cast<const T*>(B->vals), Cm, Dm, up, A, key1, vec1, bounds)
 #define SPT_MTTKRP(L_, V_)                             \
-  if (csf && in_order) SPT_MTTKRP_AS(L_, V_, true, true);   \
+  if (csf && placed) SPT_MTTKRP_AS(L_, V_, true, true);   \
   else if (csf) SPT_MTTKRP_AS(L_, V_, true, false);         \
-  else if (in_order) SPT_MTTKRP_AS(L_, V_, false, true);    \
+  else if (placed) SPT_MTTKRP_AS(L_, V_, false, true);    \
   else SPT_MTTKRP_AS(L_, V_, false, false)
   if (P.vec == 1) { SPT_MTTKRP(4, 1); }
   else if (P.lanes == 2) { SPT_MTTKRP(2, kVec<T>); }

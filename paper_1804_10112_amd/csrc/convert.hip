@@ -193,9 +193,17 @@ spt_status sample_sort_convert(int64_t n, int64_t nrows, int64_t ncols, bool by_
                                const int32_t* col, const VT* vals, int32_t* pos_out, int32_t* crd_out,
                                VT* vals_out, void* ws, size_t ws_bytes, hipStream_t s);
 
-// The sample sort takes one launch, one partition or two and a finish, whatever the key; a radix sort a pass per 8
-// bits of it. Keys of few bits (a stable order of the rows, small matrices) are for the latter from where the
-// sample sort needs its next step (fp64, even rows, in us, radix / sample):
+// sort by reserved regions (reserve_sort.hip): a middling number of records
+bool reserve_sort_applies(int64_t n, int64_t nrows, int64_t ncols);
+size_t reserve_sort_workspace(int dtype, int64_t n);
+template <typename VT>
+spt_status reserve_sort_convert(int64_t n, int64_t nrows, int64_t ncols, bool by_col, const int32_t* row,
+                                const int32_t* col, const VT* vals, int32_t* pos_out, int32_t* crd_out,
+                                VT* vals_out, void* ws, size_t ws_bytes, hipStream_t s);
+
+// Where the sort by reserved regions does not apply: the sample sort takes one launch, one partition or two and a finish,
+// whatever the key; a radix sort a pass per 8 bits of it. Keys of few bits (a stable order of the rows, small matrices) are for
+// the latter from where the sample sort needs its next step (fp64, even rows, in us, radix / sample):
 //   passes            130 000     400 000     1.6M         6.4M         30M
 //   1 (200 rows)       30 / 36     31 / 62     37 / 96      84 / 228    295 / 857
 //   2 (60 000 rows)    61 / 35     62 / 59     70 / 93     169 / 217    586 / 791
@@ -209,13 +217,30 @@ static bool radix_is_faster(const SortPlan& P, const spt_tensor* A) {
   return !sample_sort_applies(A->nvals) || (passes <= 3 && A->nvals > from);
 }
 
-size_t coo_to_csr_workspace(const spt_tensor* A) {
+// From 16 384 records on the sort by reserved regions is faster than the sample sort (its plan says by how much), up to 1.8M: rows of
+// power-law lengths of three entries on average take 93 / 102 us at 1.6M (reserved / sample sort), 107 / 105 at 2M and 125 / 121 at
+// 2.4M, of 15 entries 87 / 100 and 104 / 107. Radix passes (fp64, in us, reserved / radix): one pass 30.1 / 30.4 at 400 000, 37 / 31 at
+// 640 000; two 47 / 67 at 1M, 73 / 70 at 1.6M.
+static bool reserve_is_fastest(const SortPlan& P, const spt_tensor* A) {
+  const int passes = P.passes_col + P.passes_row;
+  const int64_t most = passes == 1 ? 3 << 17 : passes == 2 ? 5 << 18 : 7 << 18;
+  return A->nvals <= most && reserve_sort_applies(A->nvals, A->level[0].N, A->level[1].N);
+}
+
+// What a call needs. The query asks for more where the sort by reserved regions is the fastest.
+static size_t least_workspace(const spt_tensor* A) {
   size_t need = sample_sort_applies(A->nvals) ? sample_sort_workspace(A->dtype, A->nvals) : 0;
   for (const int32_t order : {SPT_ORDER_ROW_COL, SPT_ORDER_ROW_STABLE}) {
     const SortPlan P = plan(A, order);
     if (radix_is_faster(P, A)) need = std::max(need, P.total);
   }
   return need;
+}
+
+size_t coo_to_csr_workspace(const spt_tensor* A) {
+  const size_t need = least_workspace(A);
+  const bool reserve = reserve_is_fastest(plan(A, SPT_ORDER_ROW_COL), A) || reserve_is_fastest(plan(A, SPT_ORDER_ROW_STABLE), A);
+  return reserve ? std::max(need, reserve_sort_workspace(A->dtype, A->nvals)) : need;
 }
 
 template <typename VT>
@@ -226,7 +251,7 @@ static spt_status convert_typed(const spt_tensor* A, int32_t order, int32_t* pos
   if (nnz64 + kSortTile >= INT32_MAX || N + 1 >= INT32_MAX)
     return fail(SPT_ERR_UNSUPPORTED, "coo_to_csr: more than 2^31 entries or rows");
   const int nnz = (int)nnz64;
-  const size_t need = coo_to_csr_workspace(A);
+  const size_t need = least_workspace(A);
   if (!ws || ws_bytes < need)
     return fail(SPT_ERR_WORKSPACE, "coo_to_csr: workspace of %zu bytes needed, %zu given", need, ws_bytes);
   const int32_t* row = A->level[0].crd;
@@ -248,6 +273,9 @@ static spt_status convert_typed(const spt_tensor* A, int32_t order, int32_t* pos
     hipLaunchKernelGGL(copy_entries_kernel<VT>, dim3(egrid), dim3(kBlock), 0, s, nnz, col, vals,
                        crd_out, vals_out);
     SPT_CHECK_LAUNCH("copy_entries");
+  } else if (reserve_is_fastest(plan(A, order), A) && ws_bytes >= reserve_sort_workspace(A->dtype, nnz64)) {
+    return reserve_sort_convert<VT>(nnz64, N, A->level[1].N, order == SPT_ORDER_ROW_COL, row, col, vals, pos_out,
+                                    crd_out, vals_out, ws, ws_bytes, s);
   } else if (!radix_is_faster(plan(A, order), A)) {
     return sample_sort_convert<VT>(nnz64, N, A->level[1].N, order == SPT_ORDER_ROW_COL, row, col, vals, pos_out,
                                    crd_out, vals_out, ws, ws_bytes, s);

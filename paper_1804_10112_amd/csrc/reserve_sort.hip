@@ -1,0 +1,432 @@
+// COO -> CSR of a middling number of records in one partition, gfx950.
+//
+// The sample sort (sample_sort.hip) partitions stably: count, scan, scatter, five launches for one level and nine or ten for
+// two, and conversions of less than two million records spend most of their time between dependent loads and launches. Here
+// a record carries its position among the bits of its key, (row, column, position) or (row, position, column): no two
+// keys are alike, so records may move in any order. One launch places them: a workgroup counts its tile's records of
+// each bucket in LDS, takes as much of each bucket's region with an atomic add, and stores them there. One workgroup per
+// bucket then sorts it in LDS. What a bucket's region, or its workgroup, does not hold is picked out again, a part
+// of the key range at a time, by its workgroup. The result is that of a stable sort whatever order the adds come in.
+// Keys of more than 64 bits and workspaces of less than the query are for the sample sort.
+//
+// Measured (fp64, 107 000 records, 34.1 us before: samples' ranks 5, partition 7, finish 7 us; 500 000 63 -> 33;
+// 1M 73 -> 46, of which the finish takes 25; 50 000 19.8 -> 15.3). Up to 100 000 records the launches and the chain of loads in
+// each bound it, beyond the network of the finish (vector instructions and barriers) and the adds (counters
+// each in a line of their own: within 2 %).
+#include <algorithm>
+
+#include "common.hpp"
+#include "radix.hpp"
+#include "sortrecords.hpp"
+#include "wavescan.hpp"
+
+namespace spt {
+
+// Bits of a record's number among n.
+constexpr int number_bits(int n) { return n <= 1024 ? 10 : 1 + number_bits((n + 1) / 2); }
+
+// K = row, column and position side by side (by row alone: row, position, column).
+struct UniqueForm {
+  int row_shift, col_shift, pos_shift;
+  uint32_t col_mask;
+  __device__ __forceinline__ uint64_t key(int row, int col, int p) const {
+    return static_cast<uint64_t>(static_cast<uint32_t>(row)) << row_shift | static_cast<uint64_t>(static_cast<uint32_t>(col)) << col_shift |
+           static_cast<uint64_t>(static_cast<uint32_t>(p)) << pos_shift;
+  }
+  __device__ __forceinline__ int row_in(uint64_t K) const { return static_cast<int>(K >> row_shift); }
+  __device__ __forceinline__ int col_of(uint64_t K) const { return static_cast<int>(static_cast<uint32_t>(K >> col_shift) & col_mask); }
+};
+struct UniqueSource {
+  const int32_t* __restrict__ row;
+  const int32_t* __restrict__ col;
+  UniqueForm f;
+  __device__ __forceinline__ uint64_t key(int p) const { return f.key(row[p], col[p], p); }
+};
+
+// ---- splitters ------------------------------------------------------------------------------
+// Every (S / nb)th of S samples in order; the first bucket has none. The counts are cleared beside.
+template <int S>
+__device__ __forceinline__ void store_splitter(int rank, uint64_t key, int nb, uint64_t* __restrict__ skey) {
+  const int step = S / nb;
+  if (rank % step == 0) skey[rank / step] = rank ? key : ~uint64_t{0};
+}
+template <int S>
+__global__ __launch_bounds__(kWave) void reserve_pick_kernel(const UniqueSource src, int n, uint64_t* __restrict__ picked) {
+  const int t = blockIdx.x * kWave + threadIdx.x;
+  picked[t] = src.key(sample_pos<S>(t, n));
+}
+// S up to 4096: a workgroup counts how many samples come before each of 16 of them. Each has all samples; from 4096 on they are
+// put side by side first, which saves every compute unit the lines of rows and columns that hold them.
+constexpr int kRankThreads = 512, kRankLanes = 32;
+template <int S>
+__global__ __launch_bounds__(kRankThreads) void reserve_rank_kernel(const UniqueSource src, int n, int nb,
+                                                                    const uint64_t* __restrict__ picked, uint64_t* __restrict__ skey,
+                                                                    int32_t* __restrict__ count) {
+  constexpr int kOwn = S / kRankThreads;
+  __shared__ uint64_t s_key[S];
+  const int tid = threadIdx.x;
+  uint64_t own[kOwn];
+#pragma unroll
+  for (int e = 0; e < kOwn; ++e) {
+    const int t = e * kRankThreads + tid;
+    own[e] = S >= 4096 ? picked[t] : src.key(sample_pos<S>(t, n));
+  }
+#pragma unroll
+  for (int e = 0; e < kOwn; ++e) s_key[e * kRankThreads + tid] = own[e];
+  if (blockIdx.x == 0 && tid < nb) count[tid] = 0;
+  __syncthreads();
+  const int t = (blockIdx.x * kRankThreads + tid) / kRankLanes;
+  const uint64_t key = s_key[t];
+  int rank = 0;
+#pragma unroll 8
+  for (int q = tid % kRankLanes; q < S; q += kRankLanes) rank += s_key[q] < key + (q < t ? 1 : 0) ? 1 : 0;  // (the same position may be drawn twice)
+#pragma unroll
+  for (int d = 1; d < kRankLanes; d <<= 1) rank += __shfl_xor(rank, d);
+  if (tid % kRankLanes == 0) store_splitter<S>(rank, key, nb, skey);
+}
+// S = 16384 (the square of which would take 40 us): lists of 1024 in order, then each sample is looked up in the others.
+constexpr int kList = 1024, kListThreads = 256;
+template <int S>
+__global__ __launch_bounds__(kListThreads) void reserve_lists_kernel(const UniqueSource src, int n, int bits, uint64_t* __restrict__ list) {
+  constexpr int E = kList / kListThreads, L = S / kList;
+  __shared__ uint64_t s_key[kList];
+  __shared__ __attribute__((aligned(16))) uint32_t words[kList];
+  __shared__ uint16_t ord[kList];
+  const int tid = threadIdx.x;
+  uint64_t own[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) own[e] = src.key(sample_pos<S>((e * kListThreads + tid) * L + blockIdx.x, n));
+#pragma unroll
+  for (int e = 0; e < E; ++e) s_key[e * kListThreads + tid] = own[e];
+  __syncthreads();
+  sort_records<kListThreads, E>(words, ord, kList, max(0, bits - (32 - kLiBits)), [&](int li) { return s_key[li]; });
+#pragma unroll
+  for (int e = 0; e < E; ++e) list[blockIdx.x * kList + e * kListThreads + tid] = s_key[ord[e * kListThreads + tid]];
+}
+template <int S>
+__global__ __launch_bounds__(kListThreads) void reserve_merge_kernel(const uint64_t* __restrict__ list, int nb,
+                                                                     uint64_t* __restrict__ skey, int32_t* __restrict__ count) {
+  constexpr int L = S / kList;
+  const int t = blockIdx.x * kListThreads + threadIdx.x;
+  if (t < nb) count[t] = 0;
+  const int own = t / kList;
+  const uint64_t key = list[t];
+  int lo[L];
+#pragma unroll
+  for (int l = 0; l < L; ++l) lo[l] = 0;
+#pragma unroll
+  for (int step = kList / 2; step > 0; step >>= 1)
+#pragma unroll
+    for (int l = 0; l < L; ++l) lo[l] += list[l * kList + lo[l] + step - 1] < key + (l < own ? 1 : 0) ? step : 0;
+  int rank = t % kList;
+#pragma unroll
+  for (int l = 0; l < L; ++l)
+    if (l != own) rank += lo[l] + (list[l * kList + lo[l]] < key + (l < own ? 1 : 0) ? 1 : 0);
+  store_splitter<S>(rank, key, nb, skey);
+}
+
+// ---- partition ------------------------------------------------------------------------------
+// Four records to a thread. The bucket is found as in the sample sort's classification: a bisection on the first 31 bits of the
+// key, by the whole keys where those are a splitter's.
+template <typename VT, int NB, int NT>
+__global__ __launch_bounds__(NT) void reserve_partition_kernel(const UniqueSource src, const VT* __restrict__ val_in, int n,
+                                                               int coarse_bits, int room, const uint64_t* __restrict__ skey,
+                                                               int32_t* __restrict__ count, Record<uint64_t, VT>* __restrict__ out) {
+  constexpr int IPT = 4, kLevels = NB == 128 ? 7 : NB == 256 ? 8 : NB == 512 ? 9 : 10;
+  __shared__ uint64_t s_key[NB];
+  __shared__ uint32_t s_coarse[NB], s_tree[NB];
+  __shared__ int s_cnt[NB];
+  const int tid = threadIdx.x;
+  const int begin = blockIdx.x * (NT * IPT);
+  int row[IPT], col[IPT];
+  VT val[IPT];
+#pragma unroll
+  for (int k = 0; k < IPT; ++k) {
+    const int p = min(begin + k * NT + tid, n - 1);
+    row[k] = __builtin_nontemporal_load(src.row + p);
+    col[k] = __builtin_nontemporal_load(src.col + p);
+    val[k] = __builtin_nontemporal_load(val_in + p);
+  }
+  const auto coarse = [&](uint64_t k) { return static_cast<uint32_t>(k >> coarse_bits); };
+  for (int b = tid; b < NB; b += NT) {
+    const int level = 31 - __clz(b | 1);
+    const uint64_t own = skey[b], node = skey[b == 0 ? 1 : ((b - (1 << level)) * 2 + 1) << (kLevels - 1 - level)];
+    s_key[b] = own;
+    s_coarse[b] = b == 0 ? ~0u : coarse(own);  // (~0: no record's)
+    s_tree[b] = coarse(node);
+    s_cnt[b] = 0;
+  }
+  __syncthreads();
+  uint64_t key[IPT];
+  int at[IPT];  // bucket << 16 | number among the tile's of it
+#pragma unroll
+  for (int k = 0; k < IPT; ++k) {
+    const int p = begin + k * NT + tid;
+    const bool live = p < n;
+    const uint64_t K = src.f.key(row[k], col[k], min(p, n - 1));
+    const uint32_t c = static_cast<uint32_t>(K >> coarse_bits);
+    uint32_t node = 4;
+#pragma unroll
+    for (int level = 0; level < kLevels; ++level)
+      node = 2 * node + (*reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(s_tree) + node) <= c ? 4 : 0);
+    int d = static_cast<int>(node / 4) - NB;
+    if (__any(s_coarse[d] == c)) {
+      d = 0;
+#pragma unroll
+      for (int step = NB / 2; step > 0; step >>= 1) d += s_key[d + step] <= K ? step : 0;
+    }
+    key[k] = K;
+    int r = 0;
+    // ordered input: a wave's records share a bucket, and adds to one counter are serialised
+    const int d0 = __builtin_amdgcn_readfirstlane(d);
+    if (__all(live && d == d0)) {
+      if (lane_id() == 0) r = atomicAdd(&s_cnt[d], kWave);
+      r = __builtin_amdgcn_readfirstlane(r) + lane_id();
+    } else if (live) {
+      r = atomicAdd(&s_cnt[d], 1);
+    }
+    at[k] = d << 16 | r;
+  }
+  __syncthreads();
+  for (int b = tid; b < NB; b += NT) {
+    const int c = s_cnt[b];
+    if (c) s_cnt[b] = atomicAdd(&count[b], c);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < IPT; ++k) {
+    const int d = at[k] >> 16, slot = s_cnt[d] + (at[k] & 0xFFFF);
+    if (begin + k * NT + tid < n && slot < room) out[d * room + slot] = Record<uint64_t, VT>::of(key[k], val[k]);
+  }
+}
+
+// ---- finish ---------------------------------------------------------------------------------
+constexpr int kStagedWords = 5, kMostWords = 9;  // words of a thread: whose records pass through LDS, and at most
+// A bucket of more records than a workgroup sorts: they are picked out of its region, or out of the input where that does not
+// hold them, those of a part of the key range at a time that fit. Keys differ, so halving the range ends.
+template <int NT, typename VT, class KA, class VA>
+__device__ __forceinline__ void pick_and_store(char* mem, const KA& key_at, const VA& val_at, const UniqueForm& f, int n, int first,
+                                               uint64_t lo, uint64_t last, int lo_row, int hi_row, int32_t* __restrict__ pos,
+                                               int32_t* __restrict__ crd_out, VT* __restrict__ val_out) {
+  constexpr int E = 4, kMost = NT * E, kLi = number_bits(kMost);
+  uint32_t* words = reinterpret_cast<uint32_t*>(mem);
+  int32_t* at = reinterpret_cast<int32_t*>(words + kMost);
+  uint16_t* ord = reinterpret_cast<uint16_t*>(at + kMost);
+  __shared__ int s_found;
+  const int tid = threadIdx.x;
+  uint64_t from = lo, to = last;
+  int a_row = lo_row;
+  for (;;) {
+    if (tid == 0) s_found = 0;
+    __syncthreads();
+    constexpr int U = 4;
+    for (int p0 = tid; p0 < n; p0 += U * NT) {
+      uint64_t key[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) key[u] = key_at(min(p0 + u * NT, n - 1));
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (p0 + u * NT < n && key[u] >= from && key[u] <= to) {
+          const int i = atomicAdd(&s_found, 1);
+          if (i < kMost) at[i] = p0 + u * NT;
+        }
+      }
+    }
+    __syncthreads();
+    const int cnt = s_found;
+    __syncthreads();
+    if (cnt > kMost) {
+      to = from + (to - from) / 2;
+      continue;
+    }
+    const int b_row = to == last ? hi_row : f.row_in(to + 1);
+    if (cnt == 0) {
+      if (tid < kWave) store_pos_range(pos, tid == 0 ? a_row : 0, tid == 0 ? b_row : 0, first);
+    } else {
+      sort_records<NT, E, kLi>(words, ord, cnt, coarse_shift<kLi>(from, to), [&](int li) { return key_at(at[li]) - from; });
+      store_entries<NT, E>(ord, cnt, first, a_row, b_row, f, [&](int li) { return key_at(at[li]); }, pos, crd_out,
+                           [&](int j, int li) { val_out[first + j] = val_at(at[li]); });
+    }
+    if (to == last) break;
+    const uint64_t width = to - from;
+    first += cnt;
+    a_row = b_row;
+    from = to + 1;
+    to = (last - from) / 2 <= width ? last : from + 2 * width;
+    __syncthreads();
+  }
+}
+
+// Bound by the network, whose steps wait for each other: as many workgroups to a compute unit as registers and LDS allow. A
+// bucket's keys are compared in 32 - LI bits first, LI being no more than its records need (14 for all of them: 1M records with
+// power-law rows 58 us, 49 so).
+template <int NT, int WAVES, typename VT>
+__global__ __launch_bounds__(NT, WAVES) void reserve_finish_kernel(const Record<uint64_t, VT>* __restrict__ in, const UniqueSource src,
+                                                            const VT* __restrict__ val_in, int n, int nrows, int room,
+                                                            const uint64_t* __restrict__ skey, const int32_t* __restrict__ count,
+                                                            int32_t* __restrict__ pos, int32_t* __restrict__ crd_out,
+                                                            VT* __restrict__ val_out) {
+  __shared__ __attribute__((aligned(16))) char s_mem[NT * 14 * kStagedWords];
+  __shared__ int s_before;
+  const int g = blockIdx.x, nb = gridDim.x, tid = threadIdx.x;
+  if (tid == 0) s_before = 0;
+  __syncthreads();
+  for (int b0 = 0; b0 < g; b0 += NT) {
+    const int own = b0 + tid < g ? count[b0 + tid] : 0;
+    const int sum = wave_inclusive_sum(own);
+    if (lane_id() == kWave - 1 && sum) atomicAdd(&s_before, sum);
+  }
+  const int m = count[g];
+  const uint64_t lo = g > 0 ? skey[g] : 0;
+  const uint64_t last = (g + 1 < nb ? skey[g + 1] : static_cast<uint64_t>(nrows) << src.f.row_shift) - 1;
+  const int lo_row = g > 0 ? src.f.row_in(lo) : -1, hi_row = g + 1 < nb ? src.f.row_in(last + 1) : nrows;
+  __syncthreads();
+  const int first = s_before;
+  if (m == 0) {
+    if (tid < kWave) store_pos_range(pos, tid == 0 ? lo_row : 0, tid == 0 ? hi_row : 0, first);
+    return;
+  }
+  if (m > room) {
+    pick_and_store<NT, VT>(s_mem, [&](int p) { return src.key(p); }, [&](int p) { return val_in[p]; }, src.f, n, first, lo, last, lo_row,
+                           hi_row, pos, crd_out, val_out);
+    return;
+  }
+  const RecordBucket<uint64_t, VT> bucket{in + static_cast<int64_t>(g) * room, lo, 0};
+  if (m > kMostWords * NT) {
+    pick_and_store<NT, VT>(s_mem, [&](int p) { return bucket.key(p); }, [&](int p) { return bucket.val(p); }, src.f, m, first, lo, last,
+                           lo_row, hi_row, pos, crd_out, val_out);
+    return;
+  }
+#define SPT_FINISH(HOW_, E_)                                                                                             \
+  do {                                                                                                                   \
+    constexpr int kWords = E_, kLi = number_bits(NT * kWords);                                                           \
+    HOW_<NT, kWords, kLi>(s_mem, bucket, m, first, coarse_shift<kLi>(lo, last), lo_row, hi_row, src.f, pos, crd_out, val_out); \
+  } while (0)
+  if (m <= NT) {
+    SPT_FINISH(finish_staged, 1);
+  } else if (m <= 2 * NT) {
+    SPT_FINISH(finish_staged, 2);
+  } else if (m <= 3 * NT) {
+    SPT_FINISH(finish_staged, 3);
+  } else if (m <= 4 * NT) {
+    SPT_FINISH(finish_staged, 4);
+  } else if (m <= kStagedWords * NT) {
+    SPT_FINISH(finish_staged, kStagedWords);
+  } else if (m <= 6 * NT) {
+    SPT_FINISH(finish_direct, 6);
+  } else {
+    SPT_FINISH(finish_direct, kMostWords);
+  }
+#undef SPT_FINISH
+}
+
+// ---- host -----------------------------------------------------------------------------------
+// How many buckets, samples, records to a tile and threads of a workgroup that finishes a bucket (in us, fp64 uniform, before:
+// by the sample sort). More buckets are sorted faster, but take more room by atomic adds and better splitters:
+//   records    before   128 / 1024   256 / 2048   512 / 4096   1024 / 16384 buckets / samples
+//    12 000     12.5       13.1         14.8
+//    20 000     14.7       13.9         14.8
+//    64 000     20.4       15.6         17.5
+//   150 000     37.3                    21.3         22.8
+//   300 000     44.8                    26.5         26.7
+//   600 000     66.5                                 36.0          46.3
+//   1.0M        73.4                                 45.9          56.2
+//   1.5M        90.2                                 69.5          71.6 (power-law rows: 108.6 and 72.6)
+//   1.7M        96.0                                               76.1
+// Threads: 512 while buckets are small (512 buckets of 500 000 records 32.8, with 1024 threads 35.1), 1024 beyond (850 000 42.1, with 512
+// five samples of a hundred calls split a bucket; 1.7M in 1024 buckets 76.1). Tiles: 300 000 records in tiles of 2048 / 4096 26.5 / 26.6,
+// 1M 65 / 61.
+struct ReservePlan {
+  int nb, samples, tile, threads, room;
+};
+constexpr int64_t kReserveMin = 1 << 14, kReserveMax = 7 << 18;
+static ReservePlan reserve_plan(int64_t n) {
+  ReservePlan P = n <= 5 << 14   ? ReservePlan{128, 1024, 1024, 512, 0}
+                  : n <= 9 << 15 ? ReservePlan{256, 2048, 2048, 512, 0}
+                  : n <= 5 << 17 ? ReservePlan{512, 4096, 4096, 512, 0}
+                  : n <= 5 << 18 ? ReservePlan{512, 4096, 4096, 1024, 0}
+                  : n <= 3 << 19 ? ReservePlan{1024, 16384, 4096, 512, 0}
+                                 : ReservePlan{1024, 16384, 4096, 1024, 0};
+  // In random order, a bucket of eight samples has more than five times the mean with a chance of 2e-10, one of sixteen more
+  // than 3.2 times with 3e-9. (What nine words of a thread hold, 3.6 and 2.9 times the mean at least: 1e-6 and 5e-8.)
+  const int64_t mean = (n + P.nb - 1) / P.nb;
+  P.room = static_cast<int>(P.samples == 8 * P.nb ? 5 * mean : (16 * mean + 4) / 5);
+  return P;
+}
+bool reserve_sort_applies(int64_t n, int64_t nrows, int64_t ncols) {
+  const int low = bits_for(ncols) + bits_for(n);
+  return n > kReserveMin && n <= kReserveMax && low + bits_for(nrows) <= 64;
+}
+size_t reserve_sort_workspace(int dtype, int64_t n) {
+  const ReservePlan P = reserve_plan(n);
+  const size_t record = dtype == SPT_F64 ? sizeof(Record<uint64_t, uint64_t>) : sizeof(Record<uint64_t, uint32_t>);
+  return align_up(static_cast<size_t>(P.nb) * P.room * record, 256) + align_up(P.samples * 8, 256) + align_up(P.nb * 8, 256) +
+         align_up(P.nb * 4, 256);
+}
+
+// The splitters, and counts of nothing.
+static spt_status launch_splitters(const UniqueSource& src, int n, int bits, const ReservePlan& P, uint64_t* picked, uint64_t* skey,
+                                   int32_t* count, hipStream_t s) {
+#define SPT_RANK(S_)                                                                                                          \
+  hipLaunchKernelGGL((reserve_rank_kernel<S_>), dim3(S_ * kRankLanes / kRankThreads), dim3(kRankThreads), 0, s, src, n, P.nb, \
+                     picked, skey, count)
+  if (P.samples == 1024) {
+    SPT_RANK(1024);
+  } else if (P.samples == 2048) {
+    SPT_RANK(2048);
+  } else if (P.samples == 4096) {
+    hipLaunchKernelGGL(reserve_pick_kernel<4096>, dim3(4096 / kWave), dim3(kWave), 0, s, src, n, picked);
+    SPT_CHECK_LAUNCH("samples");
+    SPT_RANK(4096);
+  } else {
+    hipLaunchKernelGGL(reserve_lists_kernel<16384>, dim3(16384 / kList), dim3(kListThreads), 0, s, src, n, bits, picked);
+    SPT_CHECK_LAUNCH("samples");
+    hipLaunchKernelGGL(reserve_merge_kernel<16384>, dim3(16384 / kListThreads), dim3(kListThreads), 0, s, picked, P.nb, skey, count);
+  }
+#undef SPT_RANK
+  SPT_CHECK_LAUNCH("splitters");
+  return SPT_OK;
+}
+
+template <typename VT>
+spt_status reserve_sort_convert(int64_t n64, int64_t nrows, int64_t ncols, bool by_col, const int32_t* row, const int32_t* col,
+                                const VT* vals, int32_t* pos_out, int32_t* crd_out, VT* vals_out, void* ws, size_t ws_bytes,
+                                hipStream_t s) {
+  const int n = static_cast<int>(n64);
+  const ReservePlan P = reserve_plan(n64);
+  const int cb = bits_for(ncols), pb = bits_for(n64), bits = bits_for(nrows) + cb + pb;
+  const UniqueForm f{cb + pb, by_col ? pb : 0, by_col ? 0 : cb, static_cast<uint32_t>((uint64_t{1} << cb) - 1)};
+  const UniqueSource src{row, col, f};
+  Workspace W(ws, ws_bytes);
+  typedef Record<uint64_t, VT> R;
+  R* records = W.take<R>(static_cast<size_t>(P.nb) * P.room);
+  uint64_t* picked = W.take<uint64_t>(P.samples);
+  uint64_t* skey = W.take<uint64_t>(P.nb);
+  int32_t* count = W.take<int32_t>(P.nb);
+  const spt_status st = launch_splitters(src, n, bits, P, picked, skey, count, s);
+  if (st != SPT_OK) return st;
+#define SPT_PART(NB_, NT_)                                                                                                \
+  hipLaunchKernelGGL((reserve_partition_kernel<VT, NB_, NT_>), dim3((n + P.tile - 1) / P.tile), dim3(NT_), 0, s, src, vals, n, \
+                     std::max(0, bits - 31), P.room, skey, count, records)
+  if (P.nb == 128) SPT_PART(128, 256);
+  else if (P.nb == 256) SPT_PART(256, 512);
+  else if (P.nb == 512) SPT_PART(512, 1024);
+  else SPT_PART(1024, 1024);
+#undef SPT_PART
+  SPT_CHECK_LAUNCH("partition");
+#define SPT_FINISH(NT_, WAVES_)                                                                                              \
+  hipLaunchKernelGGL((reserve_finish_kernel<NT_, WAVES_, VT>), dim3(P.nb), dim3(NT_), 0, s, records, src, vals, n,                 \
+                     static_cast<int>(nrows), P.room, skey, count, pos_out, crd_out, vals_out)
+  if (P.threads == 512) SPT_FINISH(512, 4);
+  else SPT_FINISH(1024, 8);
+#undef SPT_FINISH
+  SPT_CHECK_LAUNCH("finish");
+  return SPT_OK;
+}
+
+template spt_status reserve_sort_convert<uint64_t>(int64_t, int64_t, int64_t, bool, const int32_t*, const int32_t*, const uint64_t*,
+                                                   int32_t*, int32_t*, uint64_t*, void*, size_t, hipStream_t);
+template spt_status reserve_sort_convert<uint32_t>(int64_t, int64_t, int64_t, bool, const int32_t*, const int32_t*, const uint32_t*,
+                                                   int32_t*, int32_t*, uint32_t*, void*, size_t, hipStream_t);
+
+}  // namespace spt

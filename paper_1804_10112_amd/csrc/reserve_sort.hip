@@ -22,9 +22,6 @@
 
 namespace spt {
 
-// Bits of a record's number among n.
-constexpr int number_bits(int n) { return n <= 1024 ? 10 : 1 + number_bits((n + 1) / 2); }
-
 // K = row, column and position side by side (by row alone: row, position, column).
 struct UniqueForm {
   int row_shift, col_shift, pos_shift;

@@ -745,24 +745,27 @@ template <int ROOM, int MOST, class SRC>
 __device__ __forceinline__ void finish_bucket(char* mem, const SRC& src, int n, int first, uint64_t lo, uint64_t hi, int lo_row,
                                               int hi_row, const KeyForm& f, int32_t* __restrict__ pos,
                                               int32_t* __restrict__ crd_out, typename SRC::VT* __restrict__ val_out) {
-  const int shift = coarse_shift(lo, hi);
   // as many words of a thread as the records need (six for most; with eight for all of them: 30 us longer for 60M)
-#define SPT_STAGED(E_) finish_staged<kFin, E_>(mem, src, n, first, shift, lo_row, hi_row, f, pos, crd_out, val_out)
+#define SPT_FINISH(HOW_, E_)                                                                                              \
+  do {                                                                                                                    \
+    constexpr int kWords = E_, kLi = number_bits(kFin * kWords);                                                          \
+    HOW_<kFin, kWords, kLi>(mem, src, n, first, coarse_shift<kLi>(lo, hi), lo_row, hi_row, f, pos, crd_out, val_out);     \
+  } while (0)
   constexpr int kStagedMost = ROOM / (sizeof(typename SRC::KT) + 6) / kFin;
   static_assert(kStagedMost >= 6 && MOST * kFin * 6 <= ROOM && MOST * kFin <= kCap && kSplitBytes <= ROOM, "");
   if (n > MOST * kFin) {
     split_and_store<kFin>(mem, src, n, first, lo, hi, lo_row, hi_row, f, pos, crd_out, val_out);
   } else if (n <= 4 * kFin) {
-    SPT_STAGED(4);
+    SPT_FINISH(finish_staged, 4);
   } else if (n <= 6 * kFin) {
-    SPT_STAGED(6);
+    SPT_FINISH(finish_staged, 6);
   } else if (n <= 8 * kFin) {
-    if constexpr (kStagedMost >= 8) SPT_STAGED(8);
-    else finish_direct<kFin, 8>(mem, src, n, first, shift, lo_row, hi_row, f, pos, crd_out, val_out);
+    if constexpr (kStagedMost >= 8) SPT_FINISH(finish_staged, 8);
+    else SPT_FINISH(finish_direct, 8);
   } else {
-    finish_direct<kFin, MOST>(mem, src, n, first, shift, lo_row, hi_row, f, pos, crd_out, val_out);
+    SPT_FINISH(finish_direct, MOST);
   }
-#undef SPT_STAGED
+#undef SPT_FINISH
 }
 
 // One workgroup per bucket of the last partition. LEVELS == 1: of the only one, whose scanned

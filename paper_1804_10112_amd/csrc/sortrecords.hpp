@@ -10,6 +10,9 @@ namespace spt {
 constexpr int kLiBits = 12;         // bits of a record's number inside its bucket; the rest of a word: its key, coarsely
 constexpr int kMaxSamples = 4096;   // of the sample sort's; numbered by kLiBits bits, too
 
+// Bits of a record's number among n.
+constexpr int number_bits(int n) { return n <= 1024 ? 10 : 1 + number_bits((n + 1) / 2); }
+
 // p[i] at an offset of 32 bits (fewer instructions than a 64-bit address): for fewer than 2^29 elements.
 template <typename E>
 __device__ __forceinline__ const E& at32(const E* p, int i) {

@@ -4,7 +4,7 @@
 // are split evenly: a workgroup has a chunk, a group of L lanes `epg` consecutive entries of it, and a
 // lane one 16-byte vector of the J columns, so that a load instruction of a wave fetches the factor
 // rows of 64 / L entries. A lane holds the coordinates of four entries at a time; they are handed
-// around its group, and the eight factor rows of four entries are in flight together.
+// around its group, and the eight factor rows of four entries are in flight together (where there are few workgroups, those of eight).
 //   - A row that begins and ends inside a group is stored by the group; rows across groups are added
 //     up by a segmented scan over the groups; the part of a chunk that continues a row begun before it
 //     leaves as a carry (row, J values), which the carry kernels add in a fixed order (no atomics).
@@ -260,8 +260,9 @@ struct Placing {
   bool ordered;
 };
 
-// PLACED: chunks and columns as `placing` says; else chunk blockIdx.x, and all columns.
-template <typename T, int L, int V, bool CSF, bool PLACED>
+// PLACED: chunks and columns as `placing` says; else chunk blockIdx.x, and all columns. U: the rows of 4 * U entries are in flight
+// together.
+template <typename T, int L, int V, bool CSF, bool PLACED, int U = 1>
 __global__ __launch_bounds__(kBlock) void mttkrp_rows_kernel(int n, int J, int epg, const Placing placing, const int32_t* __restrict__ ci,
                                                              const int32_t* __restrict__ ck,
                                                              const int32_t* __restrict__ cl,
@@ -383,24 +384,25 @@ __global__ __launch_bounds__(kBlock) void mttkrp_rows_kernel(int n, int J, int e
       }
     }
     const int batch = min(4 * L, g1 - b0);
-    for (int q = 0; 4 * q < batch; ++q) {
-      const int addr = 4 * ((lane & ~(L - 1)) + q);
-      int i[4], k[4];
-      T v[4], c[4][V], d[4][V];
-      bool fresh[4];
+    static_assert(L % U == 0, "");
+    for (int q = 0; 4 * q < batch; q += U) {
+      int i[4 * U], k[4 * U];
+      T v[4 * U], c[4 * U][V], d[4 * U][V];
+      bool fresh[4 * U];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        i[r] = from_lane(addr, ri[r]);
-        k[r] = from_lane(addr, rk[r]);
-        const int l = from_lane(addr, rl[r]);
-        v[r] = from_lane(addr, rv[r]);
+      for (int r = 0; r < 4 * U; ++r) {
+        const int addr = 4 * ((lane & ~(L - 1)) + q + r / 4);
+        i[r] = from_lane(addr, ri[r % 4]);
+        k[r] = from_lane(addr, rk[r % 4]);
+        const int l = from_lane(addr, rl[r % 4]);
+        v[r] = from_lane(addr, rv[r % 4]);
         // a row of C is loaded for the first entry that it belongs to
         fresh[r] = k[r] != (r ? k[r - 1] : cur_k) || (CSF && i[r] != (r ? i[r - 1] : cur));
         if (fresh[r]) load_cols<T, V>(Cm + static_cast<int64_t>(k[r]) * J + col, c[r]);
         load_cols<T, V>(Dm + static_cast<int64_t>(l) * J + col, d[r]);
       }
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
+      for (int r = 0; r < 4 * U; ++r) {
         if (4 * q + r < batch) {
           if (!CSF) {
 #pragma unroll
@@ -604,8 +606,12 @@ __global__ __launch_bounds__(kBlock) void mttkrp_fixup_kernel(int n, int J, cons
 
 // Few carries, in one launch: the workgroup of the first carry of a row adds up all of the row, whose end
 // it looks up first (rows read ahead without knowing cost 5 us where most rows have one carry). 738 000
-// entries in CSF, J = 16, fp64: 4.8 us, 13 in two launches. A row of all 2048 carries takes 16 rounds.
-constexpr int kCarryRunsMax = 2048, kRunBlock = 512;
+// entries in CSF, J = 16, fp64: 4.8 us, 13 in two launches. A row of all 2048 carries of 32 columns takes 16 rounds, which
+// two launches take as long for from some 2600 on (6.5M entries in two slices, fp32, J = 32: 73.9 / 76.7 in one); rows of up to 16
+// columns only from 4096 on, where launching them all costs as much (one launch / two: 4.5M entries, J = 8, fp32 53.8 / 59.4; 6.5M, J = 16,
+// 82.2 / 86.9; J = 32, 4.5M 76.8 / 81.8; 9M in 4400 carries, J = 32, the same). Beyond 32 columns, 2048 carries are 4096 workgroups.
+constexpr int kRunBlock = 512;
+static int carry_runs_most(int J) { return J <= 16 ? 4096 : J <= 32 ? 2560 : 2048; }
 template <typename T>
 __global__ __launch_bounds__(kRunBlock) void mttkrp_carry_runs_kernel(int n, int J, int log_cols,
                                                                    const int32_t* __restrict__ key,
@@ -647,26 +653,42 @@ __global__ __launch_bounds__(kRunBlock) void mttkrp_carry_runs_kernel(int n, int
 struct MttkrpPlan {
   int lanes, vec, epg, chunk, parts;
   int64_t n1, n2;  // chunks (of each part), workgroups of the first level of carries
+  int64_t blocks;  // workgroups that have entries
 };
 
 // Lanes: the vectors of a row, up to 32 (longer rows take several passes over the entries, side by
-// side). Entries of a group: 16, which its fixed work (bounds, scan, carry) is worth, while all workgroups then fit the
-// compute units at a time (their registers: five of a COO tensor to each, four of CSF); beyond, as many as leave about six
-// workgroups to each, in whole batches of the coordinates that the group's lanes hold (four each), since a part
-// of one costs as much; at most 2048 entries per workgroup
-// (measured with 512 to 4096: more entries keep fewer rows of C in cache, fewer leave more carries;
-// up to 10 % apart) and 128 per group. In multiples of 16 / in batches, J = 32, us:
-//   CSF, fp32: 600 000 entries 36.3 / 32.8; 1.3M 56.6 / 47.1; 3M 77.9 / 75.3; fp64: 600 000 58.7 / 51.0; 2M 111 / 107
-//   COO, fp32: 900 000 entries 33.2 / 31.3; 1.3M 45.2 / 38.4; 3M 71.3 / 70.6; fp64: 600 000 50.5 / 44.2; 2M 106 / 100
-// (32 lanes: batches of 128 entries are too long, 400 000 entries 65.6 in 16, 68.0.)
-// 16 lanes, whose batches are of 64 entries: groups of 48 as long as two workgroups on each compute unit hold the tensor.
-// With 64 there are hardly more workgroups than compute units, and a skewed tensor ends on one of them. (COO: even slices
-// lose some of what 64 gain, up to 5 %, skewed ones gain as much; with 32, even slices lose 10 %, fp32.) Groups of
-// 16 / 32 / 48 / 64, J = 32, fp64, skewed slices, and even ones:
-//   CSF, 265 000 entries  32.5 / 29.7 / 32.2 / 36.9, 35.3 / 31.8 / 29.9 / 31.3; 360 000  35.6 / 32.2 / 33.6 / 37.5, 39.1 / 34.3 / 34.5 / 34.6
-//     400 000 37.1 / 35.3 / 36.7 / 37.3, 42.0 / 39.2 / 39.9 / 36.8
-//   COO, 330 000 entries  28.3 / 26.7 / 28.4 / 29.5, 30.3 / 28.2 / 28.1 / 27.9; 400 000  32.0 / 31.3 / 32.6 / 31.2, 35.1 / 34.1 / 34.4 / 30.9
-//   fp32, J = 64: CSF, 265 000  36.2 / 33.8 / 34.5 / 38.6, 39.8 / 35.2 / 32.7 / 33.3; COO, 330 000  32.4 / 30.7 / 32.1 / 32.8, 36.9 / 32.7 / 31.3 / 31.3
+// side). Entries of a group, in the order of the rules:
+//   - Small tensors are a chain of loads, four entries after four. 4 entries while that makes no more than two workgroups to a compute
+//     unit, 8 up to three (of 16 / 8 / 4, us, skewed slices; CSF's searches for the bounds gain from short chunks, too):
+//       COO, 50 000 entries, fp32, J = 32 12.4 / 11.3 / 10.9; 110 000 13.6 / 12.8 / 12.9; 220 000 (3.4 workgroups) 16.1 / 15.6 / 19.5, even
+//         15.2 / 16.4 / 20.1; fp64, J = 33, 50 000 15.7 / 15.1 / 19.0; CSF, fp32, J = 8, 110 000 18.7 / 15.1 / 13.6; 400 000 19.6 / 16.8 / 16.7;
+//         740 000 23.0 / 19.7 / 24.2; J = 32, 50 000 16.1 / 13.7 / 13.8; 110 000 17.6 / 16.1 / 16.4
+//   - COO with two or four lanes: what these hold at a time, since a group that comes back for the rest of its lines finds them gone (four
+//     arrays, loaded past the caches: 16 and 32 entries / 8 and 16, us, skewed slices and even ones):
+//       J = 8, fp32, 12M entries 124 / 105, 154 / 137; 30M 277 / 225, 351 / 316; 2.5M 34.7 / 30.4, 41 / 40; J = 4, fp64, 30M 319 / 232, 400 / 323
+//       J = 16, fp32, 12M 137 / 111, 196 / 167; 30M 291 / 236, 452 / 386; 2.5M 41.2 / 35.8, 49.9 / 46.9; J = 8, fp64, 30M 300 / 266; J = 3,
+//       fp32, 20M 196 / 165. (CSF reads two arrays and gains more from long chunks: J = 8, fp32, 12M 113 / 125, J = 16 132 / 147.)
+//   - 16, which a group's fixed work (bounds, scan, carry) is worth, while all workgroups then fit the compute units at a
+//     time (their registers: five of a COO tensor to each, four of CSF; of COO with eight and 16 lanes three, then 32: 400 000
+//     entries, fp64, J = 16 20.8 / 19.4, even 21.5 / 19.2; 210 000, fp32, J = 33 20.8 / 20.7, 23.4 / 20.4).
+//   - Beyond, as many as leave about six workgroups to each, in whole batches of the coordinates that the group's lanes hold (four
+//     each), since a part of one costs as much; at most 2048 entries per workgroup
+//     (measured with 512 to 4096: more entries keep fewer rows of C in cache, fewer leave more carries;
+//     up to 10 % apart) and 128 per group. In multiples of 16 / in batches, J = 32, us:
+//       CSF, fp32: 600 000 entries 36.3 / 32.8; 1.3M 56.6 / 47.1; 3M 77.9 / 75.3; fp64: 600 000 58.7 / 51.0; 2M 111 / 107
+//       COO, fp32: 900 000 entries 33.2 / 31.3; 1.3M 45.2 / 38.4; 3M 71.3 / 70.6; fp64: 600 000 50.5 / 44.2; 2M 106 / 100
+//   - 32 lanes, whose batches of 128 entries are too long (400 000 entries 65.6 in 16, 68.0): multiples of 16, up to 64 of them such that
+//     three workgroups go to a compute unit (six / three, J = 33, fp64: COO 150 000 27.4 / 25.6, even 30.2 / 25.6; 300 000
+//     40.9 / 38.1, 46.4 / 41.2; 500 000 50.1 / 48.3, 60.6 / 54.8; CSF 300 000 47.2 / 41.9, 55.2 / 46.1).
+//   - 16 lanes, whose batches are of 64 entries: groups of 48 as long as two workgroups on each compute unit hold the tensor.
+//     With 64 there are hardly more workgroups than compute units, and a skewed tensor ends on one of them. (COO: even slices
+//     lose some of what 64 gain, up to 5 %, skewed ones gain as much; with 32, even slices lose 10 %, fp32.) Groups of
+//     16 / 32 / 48 / 64, J = 32, fp64, skewed slices, and even ones:
+//       CSF, 265 000 entries  32.5 / 29.7 / 32.2 / 36.9, 35.3 / 31.8 / 29.9 / 31.3; 360 000  35.6 / 32.2 / 33.6 / 37.5, 39.1 / 34.3 / 34.5 / 34.6
+//         400 000 37.1 / 35.3 / 36.7 / 37.3, 42.0 / 39.2 / 39.9 / 36.8
+//       COO, 330 000 entries  28.3 / 26.7 / 28.4 / 29.5, 30.3 / 28.2 / 28.1 / 27.9; 400 000  32.0 / 31.3 / 32.6 / 31.2, 35.1 / 34.1 / 34.4 / 30.9
+//       fp32, J = 64: CSF, 265 000  36.2 / 33.8 / 34.5 / 38.6, 39.8 / 35.2 / 32.7 / 33.3; COO, 330 000  32.4 / 30.7 / 32.1 / 32.8, 36.9 / 32.7 / 31.3 / 31.3
+// (A workspace that holds the carries of 16 entries to a group and more, but not of fewer, gets these.)
 // Parts of the J columns, each of whole lines, that XCDs of their own go through all entries for (given C and D on lines): an L2
 // then holds twice, four or eight times as many rows. A gather takes as long for 64 bytes as for a line, so parts of
 // half a line only lose (50M entries, J = 32, fp32: 618 -> 1010 us). The entries are read once per part, which rows that an L2
@@ -683,7 +705,7 @@ static int mttkrp_parts(int64_t nnz, int64_t row_bytes, int64_t rows_c, int64_t 
   while (parts > 1 && row_bytes % (parts * int64_t{kLine}) != 0) parts /= 2;
   return parts;
 }
-static MttkrpPlan mttkrp_plan(int64_t nnz, int64_t J, int dtype, bool csf, int parts) {
+static MttkrpPlan mttkrp_plan(int64_t nnz, int64_t J, int dtype, bool csf, int parts, bool least_carries = false) {
   MttkrpPlan P;
   P.parts = parts;
   J /= parts;  // (the rest is about one part; its workgroups are as many for each)
@@ -692,18 +714,37 @@ static MttkrpPlan mttkrp_plan(int64_t nnz, int64_t J, int dtype, bool csf, int p
   const int64_t nv = (J + P.vec - 1) / P.vec;
   P.lanes = P.vec == 1 ? 4 : nv <= 2 ? 2 : nv <= 4 ? 4 : nv <= 8 ? 8 : nv <= 16 ? 16 : 32;
   const int groups = kBlock / P.lanes;
+  const int64_t tiles = (nv + P.lanes - 1) / P.lanes;
   const int batch = P.lanes <= 16 ? std::max(4 * P.lanes, 16) : 16;
-  const int64_t once = int64_t(csf ? 4 : 5) * 256 * groups * 16 / parts;
+  const int64_t at_once = int64_t(256) * groups * 16 / parts;  // with 16 entries to a group, a workgroup to each compute unit
   const int64_t want = nnz * parts / (6 * 256) / groups;
+  const auto workgroups = [&](int64_t epg) { return (nnz + groups * epg - 1) / (groups * epg) * tiles * parts; };
   int64_t epg = 16;
   if (P.lanes > 16) epg = std::max<int64_t>(want / 16 * 16, 16);
-  else if (P.lanes == 16 && nnz > once && nnz <= int64_t(2) * 256 * groups * 48) epg = 48;
-  else if (nnz > once) epg = std::max<int64_t>((want + batch / 2) / batch * batch, batch);
+  else if (P.lanes == 16 && nnz > (csf ? 4 : 5) * at_once && nnz <= int64_t(2) * 256 * groups * 48) epg = 48;
+  else if (nnz > (csf ? 4 : 5) * at_once) epg = std::max<int64_t>((want + batch / 2) / batch * batch, batch);
+  if (!least_carries) {
+    if ((csf || P.lanes > 2) && workgroups(4) <= 2 * 256) epg = 4;
+    else if (workgroups(8) <= 3 * 256) epg = 8;
+    else if (!csf && P.lanes <= 4) epg = 4 * P.lanes;
+    else if (!csf && P.lanes <= 16 && nnz > 3 * at_once && epg == 16) epg = 32;
+    else if (P.lanes > 16) epg = std::max(epg, std::min<int64_t>((nnz * tiles * parts / (3 * 256) / groups + 8) / 16 * 16, 64));
+  }
   P.epg = static_cast<int>(std::min<int64_t>(epg, std::min(128, 2048 / groups)));
   P.chunk = P.epg * groups;
   P.n1 = (nnz + P.chunk - 1) / P.chunk;
   P.n2 = (P.n1 + kCarrySpan - 1) / kCarrySpan;
+  P.blocks = workgroups(P.epg);
   return P;
+}
+
+// The rows of eight entries in flight together instead of four, whose registers leave three workgroups to a compute unit: while there are
+// no more (four / eight, us: CSF, 738 000 entries, fp64, J = 16 31.2 / 30.1; COO 25.5 / 24.5; 220 000 16.0 / 15.2, but 400 000
+// in 781 workgroups 20.8 / 22.3; of 16 lanes even slices lose 3 %), and where a group has eight, COO, fp32, J up to 8 (30M 225 / 219, even 316 / 284;
+// fp64, J = 4 232 / 240, 323 / 313).
+static bool mttkrp_eight(const MttkrpPlan& P, int dtype, bool csf) {
+  if (P.lanes == 2) return !csf && dtype == SPT_F32 && P.epg == 8;
+  return P.vec > 1 && (P.lanes == 4 || P.lanes == 8) && P.epg >= 8 && P.blocks <= 3 * 256;
 }
 
 // Is it worth 10 us to order the chunks by their rows of C? An L2 has to be too small for the factors, C to be
@@ -721,16 +762,22 @@ static bool mttkrp_orders(const MttkrpPlan& P, int64_t nnz, int64_t J, int64_t v
          P.n1 * J * value >= (P.n1 / kOrderShare + 1) * kRadix * 4;  // (the counts take the room of the carries)
 }
 
-size_t mttkrp3_workspace(const spt_tensor* B, int32_t J) {
-  const size_t row = static_cast<size_t>(std::max(J, 1)) * (B->dtype == SPT_F64 ? 8 : 4);
-  const bool csf = B->level[1].kind == SPT_COMPRESSED;
-  MttkrpPlan P = mttkrp_plan(B->nvals, std::max(J, 1), B->dtype, csf, 1);
-  // (parts if both factors lie on lines)
-  const MttkrpPlan split = mttkrp_plan(B->nvals, std::max(J, 1), B->dtype, csf, mttkrp_parts(B->nvals, row, B->level[1].N, B->level[2].N, csf));
-  P.n1 = std::max(P.n1, split.n1), P.n2 = std::max(P.n2, split.n2);
+static size_t mttkrp_bytes(const MttkrpPlan& P, size_t row) {
   return align_up(static_cast<size_t>(P.n1) * 4, 256) + align_up(P.n1 * row, 256) +
          align_up(static_cast<size_t>(P.n2) * 4, 256) + align_up(P.n2 * row, 256) +
          align_up(static_cast<size_t>(P.n1 + 1) * 12, 256) + 256;
+}
+static MttkrpPlan mttkrp_least(const spt_tensor* B, int32_t J) {
+  return mttkrp_plan(B->nvals, J, B->dtype, B->level[1].kind == SPT_COMPRESSED, 1, true);
+}
+// What a call makes best use of: of one plan, or of another where both factors lie on lines, or a workgroup's carries are short.
+size_t mttkrp3_workspace(const spt_tensor* B, int32_t J) {
+  J = std::max(J, 1);
+  const size_t row = static_cast<size_t>(J) * (B->dtype == SPT_F64 ? 8 : 4);
+  const bool csf = B->level[1].kind == SPT_COMPRESSED;
+  const int parts = mttkrp_parts(B->nvals, row, B->level[1].N, B->level[2].N, csf);
+  return std::max({mttkrp_bytes(mttkrp_least(B, J), row), mttkrp_bytes(mttkrp_plan(B->nvals, J, B->dtype, csf, 1), row),
+                   mttkrp_bytes(mttkrp_plan(B->nvals, J, B->dtype, csf, parts), row)});
 }
 
 template <typename T>
@@ -740,11 +787,13 @@ static spt_status mttkrp3_typed(Format f, const spt_tensor* B, const T* Cm, cons
   const bool csf = f == Format::CSF3;
   const int64_t nsl = csf ? B->level[1].M : 0, nfib = csf ? B->level[2].M : 0;
   const bool on_lines = (reinterpret_cast<uintptr_t>(Cm) | reinterpret_cast<uintptr_t>(Dm)) % kLine == 0;
-  const MttkrpPlan P = mttkrp_plan(nnz64, J, B->dtype, csf, on_lines ? mttkrp_parts(nnz64, J * (int64_t)sizeof(T), B->level[1].N, B->level[2].N, csf) : 1);
+  MttkrpPlan P = mttkrp_plan(nnz64, J, B->dtype, csf, on_lines ? mttkrp_parts(nnz64, J * (int64_t)sizeof(T), B->level[1].N, B->level[2].N, csf) : 1);
+  const size_t row = std::max(J, 1) * sizeof(T);
+  if (ws_bytes < mttkrp_bytes(P, row)) P = mttkrp_least(B, std::max(J, 1));
   if (nnz64 + P.chunk >= INT32_MAX || size >= ((int64_t)1 << 38) || nsl + 1 >= INT32_MAX || nfib + 1 >= INT32_MAX)
     return fail(SPT_ERR_UNSUPPORTED, "mttkrp: tensor too large");
-  if (nnz64 > 0 && (!ws || ws_bytes < mttkrp3_workspace(B, J)))
-    return fail(SPT_ERR_WORKSPACE, "mttkrp: workspace of %zu bytes needed, %zu given", mttkrp3_workspace(B, J), ws_bytes);
+  if (nnz64 > 0 && (!ws || ws_bytes < mttkrp_bytes(P, row)))
+    return fail(SPT_ERR_WORKSPACE, "mttkrp: workspace of %zu bytes needed, %zu given", mttkrp_bytes(P, row), ws_bytes);
   const int nnz = (int)nnz64, n1 = (int)P.n1, n2 = (int)P.n2;
   Workspace W(ws, ws_bytes);
   int32_t *key1 = nullptr, *key2 = nullptr, *bounds = nullptr;
@@ -789,25 +838,33 @@ static spt_status mttkrp3_typed(Format f, const spt_tensor* B, const T* Cm, cons
   const int64_t blocks = placed ? kXcds * ((P.n1 + of - 1) / of) : n1;
   const int tiles = ((J / P.parts + P.vec - 1) / P.vec + P.lanes - 1) / P.lanes;
   const size_t lds = csf ? (size_t)P.chunk * 8 + 2 * (size_t)((P.chunk + 31) / 32) * 6 : 0;
-#define SPT_MTTKRP_AS(L_, V_, CSF_, PLACED_)                                                                           \
-  hipLaunchKernelGGL((mttkrp_rows_kernel<T, L_, V_, CSF_, PLACED_>), dim3((unsigned)blocks, tiles), dim3(kBlock), lds, s, nnz, J, P.epg, placing, \
+  const bool eight = !placed && mttkrp_eight(P, B->dtype, csf);
+#define SPT_MTTKRP_AS(L_, V_, CSF_, PLACED_, U_)                                                                       \
+  hipLaunchKernelGGL((mttkrp_rows_kernel<T, L_, V_, CSF_, PLACED_, U_>), dim3((unsigned)blocks, tiles), dim3(kBlock), lds, s, nnz, J, P.epg, placing, \
                      csf ? nullptr : B->level[0].crd, csf ? nullptr : B->level[1].crd, B->level[2].crd,                  \
                      static_cast<const T*>(B->vals), Cm, Dm, up, A, key1, vec1, bounds)
-#define SPT_MTTKRP(L_, V_)                             \
-  if (csf && placed) SPT_MTTKRP_AS(L_, V_, true, true);   \
-  else if (csf) SPT_MTTKRP_AS(L_, V_, true, false);         \
-  else if (placed) SPT_MTTKRP_AS(L_, V_, false, true);    \
-  else SPT_MTTKRP_AS(L_, V_, false, false)
+#define SPT_MTTKRP(L_, V_)                                \
+  if (csf && placed) SPT_MTTKRP_AS(L_, V_, true, true, 1);   \
+  else if (csf) SPT_MTTKRP_AS(L_, V_, true, false, 1);         \
+  else if (placed) SPT_MTTKRP_AS(L_, V_, false, true, 1);    \
+  else SPT_MTTKRP_AS(L_, V_, false, false, 1)
+#define SPT_MTTKRP_EIGHT(L_)                                        \
+  if (csf) SPT_MTTKRP_AS(L_, kVec<T>, true, false, 2);                \
+  else SPT_MTTKRP_AS(L_, kVec<T>, false, false, 2)
   if (P.vec == 1) { SPT_MTTKRP(4, 1); }
+  else if (P.lanes == 2 && eight) { SPT_MTTKRP_AS(2, kVec<T>, false, false, 2); }
   else if (P.lanes == 2) { SPT_MTTKRP(2, kVec<T>); }
+  else if (P.lanes == 4 && eight) { SPT_MTTKRP_EIGHT(4); }
   else if (P.lanes == 4) { SPT_MTTKRP(4, kVec<T>); }
+  else if (P.lanes == 8 && eight) { SPT_MTTKRP_EIGHT(8); }
   else if (P.lanes == 8) { SPT_MTTKRP(8, kVec<T>); }
   else if (P.lanes == 16) { SPT_MTTKRP(16, kVec<T>); }
   else { SPT_MTTKRP(32, kVec<T>); }
+#undef SPT_MTTKRP_EIGHT
 #undef SPT_MTTKRP
 #undef SPT_MTTKRP_AS
   SPT_CHECK_LAUNCH("mttkrp rows");
-  if (n1 <= kCarryRunsMax) {
+  if (n1 <= carry_runs_most(J)) {
     int log_cols = 2;
     while (log_cols < 5 && (1 << log_cols) < J) ++log_cols;
     hipLaunchKernelGGL(mttkrp_carry_runs_kernel<T>, dim3(n1, (J + (1 << log_cols) - 1) >> log_cols), dim3(kRunBlock), 0, s,

@@ -9,7 +9,12 @@
 //     up by a segmented scan over the groups; the part of a chunk that continues a row begun before it
 //     leaves as a carry (row, J values), which the carry kernels add in a fixed order (no atomics).
 //   - CSF: i and k are the last slice and fibre that start at or before an entry. The starts inside a
-//     chunk are marked in a bit set in LDS; C[k, :] is multiplied once per fibre (factored form).
+//     chunk are marked in a bit set in LDS, where a group sees which of its entries begin one; only those look up k or i.
+//     C[k, :] is multiplied once per fibre (factored form).
+//   - Rows of factors up to 4 GiB are found at 32-bit offsets, and CSF parks a group's first sum in LDS: with the registers
+//     that are left, five waves share a SIMD instead of four (i, k and 64-bit addresses in registers): 11M entries in CSF, fp32, J = 32,
+//     skewed 158 -> 132 us, even 189 -> 174; fp64 262 -> 215, 386 -> 383; 2.6M, fp32, J = 8 34.2 -> 30.5; factors of 51 MB, whose
+//     rows miss L2 whatever is in flight, 748 -> 755. COO, fp64, has four: with five, 16M even entries, J = 8, take 188 instead of 171.
 // Bound by the gathers of factor rows, large tensors by those that miss L2: what is fetched from beyond it takes all the
 // time there (50M entries, J = 32, fp32: 4.7 GB, 632 us; with all rows in L2, as a probe, 400; chunks in the order of their
 // rows of C: 593). A row of C stays in registers while k does (loaded for every entry: 700 us, and 619
@@ -63,6 +68,15 @@ __device__ __forceinline__ void store_cols(T* p, const T (&x)[V]) {
     for (int q = 0; q < V; ++q) v[q] = x[q];
   }
   *reinterpret_cast<typename ColVec<T, V>::type*>(p) = v;
+}
+
+// Row k from column col on. NEAR: at an offset of 32 bits, which takes one register instead of two.
+template <bool NEAR, typename T>
+__device__ __forceinline__ const T* row_at(const T* p, int k, int J, int col) {
+  if constexpr (NEAR)
+    return reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + (static_cast<uint32_t>(k) * static_cast<uint32_t>(J * sizeof(T)) + static_cast<uint32_t>(col * sizeof(T))));
+  else
+    return p + static_cast<int64_t>(k) * J + col;
 }
 
 // Four consecutive values from p + e on, those at `end` and beyond as zero.
@@ -226,18 +240,6 @@ __device__ __forceinline__ int last_mark(const uint32_t* marks, const int16_t* b
   return m ? w * 32 + 31 - __clz(m) : before[w];
 }
 
-// The same of the four entries from e on, a multiple of four (of which one word holds the marks): 2M entries, J = 16, fp64,
-// 50.2 -> 49.5 us; 20M 276 -> 270.
-__device__ __forceinline__ void last_marks(const uint32_t* marks, const int16_t* before, int e, int (&at)[4]) {
-  const int w = e >> 5, none = before[w];
-  const uint32_t word = marks[w];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const uint32_t m = word & ((2u << ((e & 31) + r)) - 1);
-    at[r] = m ? w * 32 + 31 - __clz(m) : none;
-  }
-}
-
 // before[] of `words` words, by one wave. Entry 0 is marked.
 __device__ __forceinline__ void marks_before(const uint32_t* marks, int16_t* before, int words) {
   int from = 0;
@@ -261,9 +263,9 @@ struct Placing {
 };
 
 // PLACED: chunks and columns as `placing` says; else chunk blockIdx.x, and all columns. U: the rows of 4 * U entries are in flight
-// together.
-template <typename T, int L, int V, bool CSF, bool PLACED, int U = 1>
-__global__ __launch_bounds__(kBlock) void mttkrp_rows_kernel(int n, int J, int epg, const Placing placing, const int32_t* __restrict__ ci,
+// together. NEAR: no factor has more than 4 GiB.
+template <typename T, int L, int V, bool CSF, bool PLACED, int U = 1, bool NEAR = true>
+__global__ __launch_bounds__(kBlock, CSF && U == 1 ? 5 : 1) void mttkrp_rows_kernel(int n, int J, int epg, const Placing placing, const int32_t* __restrict__ ci,
                                                              const int32_t* __restrict__ ck,
                                                              const int32_t* __restrict__ cl,
                                                              const T* __restrict__ vals, const T* __restrict__ Cm,
@@ -274,6 +276,7 @@ __global__ __launch_bounds__(kBlock) void mttkrp_rows_kernel(int n, int J, int e
   extern __shared__ __attribute__((aligned(16))) int32_t s_csf[];
   __shared__ T s_v[kBlock / kWave][L][V];
   __shared__ int s_f[kBlock / kWave];
+  __shared__ T s_lead[CSF ? kBlock : 1][V];  // (CSF: the registers that this takes would leave a wave less)
   __shared__ int s_slice_first;  // the chunk starts with a slice
   const int tid = threadIdx.x, lane = lane_id();
   const int g = tid / L, gl = tid % L;
@@ -361,6 +364,12 @@ __global__ __launch_bounds__(kBlock) void mttkrp_rows_kernel(int n, int J, int e
   else if (g0 > base) cur = s_i[last_mark(s_slice, s_slice_before, g0 - 1 - base)];
   else cur = base == 0 ? -1 : s_slice_first ? -2 : s_i[0];
 
+  // CSF: fibre and row of the group's first entry; of the others, the marks tell where a new one starts
+  int first_k = 0, first_i = 0;
+  if (CSF && g0 < g1) {
+    first_k = s_k[last_mark(s_fibre, s_fibre_before, g0 - base)];
+    first_i = s_i[last_mark(s_slice, s_slice_before, g0 - base)];
+  }
   for (int b0 = g0; b0 < g1; b0 += 4 * L) {
     int32_t ri[4], rk[4];
     const int p = b0 + 4 * gl;
@@ -371,35 +380,38 @@ __global__ __launch_bounds__(kBlock) void mttkrp_rows_kernel(int n, int J, int e
     if (!CSF) {
       load_four(ci, p, g1, ri);
       load_four(ck, p, g1, rk);
-    } else {
-      // (entries at the chunk's end and beyond have the row and the fibre of the last one: they are not marked)
-      int ai[4], ak[4];
-      const int e = min(p - base, size - 4);
-      last_marks(s_slice, s_slice_before, e, ai);
-      last_marks(s_fibre, s_fibre_before, e, ak);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        ri[r] = s_i[ai[r]];
-        rk[r] = s_k[ak[r]];
-      }
     }
     const int batch = min(4 * L, g1 - b0);
     static_assert(L % U == 0, "");
     for (int q = 0; 4 * q < batch; q += U) {
+      const int e = b0 + 4 * q - base;  // (a multiple of 4 * U: one word has the marks)
+      const bool at_first = CSF && e == g0 - base;
+      uint32_t new_fibre = 0, new_row = 0;
       int i[4 * U], k[4 * U];
       T v[4 * U], c[4 * U][V], d[4 * U][V];
       bool fresh[4 * U];
+      if (CSF) {
+        new_fibre = s_fibre[e >> 5] >> (e & 31) | at_first;
+        new_row = s_slice[e >> 5] >> (e & 31) | at_first;
+#pragma unroll
+        for (int r = 0; r < 4 * U; ++r) k[r] = s_k[e + r];
+        if (at_first) k[0] = first_k;
+      }
 #pragma unroll
       for (int r = 0; r < 4 * U; ++r) {
         const int addr = 4 * ((lane & ~(L - 1)) + q + r / 4);
-        i[r] = from_lane(addr, ri[r % 4]);
-        k[r] = from_lane(addr, rk[r % 4]);
         const int l = from_lane(addr, rl[r % 4]);
         v[r] = from_lane(addr, rv[r % 4]);
         // a row of C is loaded for the first entry that it belongs to
-        fresh[r] = k[r] != (r ? k[r - 1] : cur_k) || (CSF && i[r] != (r ? i[r - 1] : cur));
-        if (fresh[r]) load_cols<T, V>(Cm + static_cast<int64_t>(k[r]) * J + col, c[r]);
-        load_cols<T, V>(Dm + static_cast<int64_t>(l) * J + col, d[r]);
+        if (CSF) {
+          fresh[r] = new_fibre >> r & 1;
+        } else {
+          i[r] = from_lane(addr, ri[r % 4]);
+          k[r] = from_lane(addr, rk[r % 4]);
+          fresh[r] = k[r] != (r ? k[r - 1] : cur_k);
+        }
+        if (fresh[r]) load_cols<T, V>(row_at<NEAR>(Cm, k[r], J, col), c[r]);
+        load_cols<T, V>(row_at<NEAR>(Dm, l, J, col), d[r]);
       }
 #pragma unroll
       for (int r = 0; r < 4 * U; ++r) {
@@ -416,14 +428,14 @@ __global__ __launch_bounds__(kBlock) void mttkrp_rows_kernel(int n, int J, int e
               t[x] = T(0);
               c_cur[x] = c[r][x];
             }
-            cur_k = k[r];
           }
+          if (CSF) i[r] = new_row >> r & 1 ? (r == 0 && at_first ? first_i : s_i[e + r]) : cur;
           if (i[r] != cur) {  // close the row
             if (!has_head) {
               has_head = true;
               first_close = cur;
 #pragma unroll
-              for (int x = 0; x < V; ++x) lead[x] = acc[x];
+              for (int x = 0; x < V; ++x) (CSF ? s_lead[tid] : lead)[x] = acc[x];
             } else if (jok) {
               store_cols<T, V>(A + static_cast<int64_t>(cur) * J + col, acc);
             }
@@ -484,7 +496,7 @@ __global__ __launch_bounds__(kBlock) void mttkrp_rows_kernel(int n, int J, int e
   before_f = before_f || pre_f;
   if (has_head) {
 #pragma unroll
-    for (int x = 0; x < V; ++x) before[x] += lead[x];
+    for (int x = 0; x < V; ++x) before[x] += CSF ? s_lead[tid][x] : lead[x];
     if (before_f) {
       if (jok && first_close >= 0) store_cols<T, V>(A + static_cast<int64_t>(first_close) * J + col, before);
     } else {  // precedes the first row that starts in the chunk
@@ -669,7 +681,7 @@ struct MttkrpPlan {
 //       J = 16, fp32, 12M 137 / 111, 196 / 167; 30M 291 / 236, 452 / 386; 2.5M 41.2 / 35.8, 49.9 / 46.9; J = 8, fp64, 30M 300 / 266; J = 3,
 //       fp32, 20M 196 / 165. (CSF reads two arrays and gains more from long chunks: J = 8, fp32, 12M 113 / 125, J = 16 132 / 147.)
 //   - 16, which a group's fixed work (bounds, scan, carry) is worth, while all workgroups then fit the compute units at a
-//     time (their registers: five of a COO tensor to each, four of CSF; of COO with eight and 16 lanes three, then 32: 400 000
+//     time (five of a COO tensor to each, four of CSF; of COO with eight and 16 lanes three, then 32: 400 000
 //     entries, fp64, J = 16 20.8 / 19.4, even 21.5 / 19.2; 210 000, fp32, J = 33 20.8 / 20.7, 23.4 / 20.4).
 //   - Beyond, as many as leave about six workgroups to each, in whole batches of the coordinates that the group's lanes hold (four
 //     each), since a part of one costs as much; at most 2048 entries per workgroup
@@ -833,18 +845,21 @@ static spt_status mttkrp3_typed(Format f, const spt_tensor* B, const T* Cm, cons
     SPT_CHECK_LAUNCH("mttkrp order");
   }
   const Placing placing{n1, P.parts, in_order};
-  const bool placed = in_order || P.parts > 1;
+  const bool near = static_cast<uint64_t>(std::max(B->level[1].N, B->level[2].N)) * J * sizeof(T) <= uint64_t{1} << 32;
+  const bool placed = in_order || P.parts > 1 || !near;
   const int of = kXcds / P.parts;
   const int64_t blocks = placed ? kXcds * ((P.n1 + of - 1) / of) : n1;
   const int tiles = ((J / P.parts + P.vec - 1) / P.vec + P.lanes - 1) / P.lanes;
   const size_t lds = csf ? (size_t)P.chunk * 8 + 2 * (size_t)((P.chunk + 31) / 32) * 6 : 0;
   const bool eight = !placed && mttkrp_eight(P, B->dtype, csf);
-#define SPT_MTTKRP_AS(L_, V_, CSF_, PLACED_, U_)                                                                       \
-  hipLaunchKernelGGL((mttkrp_rows_kernel<T, L_, V_, CSF_, PLACED_, U_>), dim3((unsigned)blocks, tiles), dim3(kBlock), lds, s, nnz, J, P.epg, placing, \
+#define SPT_MTTKRP_AS(L_, V_, CSF_, PLACED_, ...)                                                                      \
+  hipLaunchKernelGGL((mttkrp_rows_kernel<T, L_, V_, CSF_, PLACED_, __VA_ARGS__>), dim3((unsigned)blocks, tiles), dim3(kBlock), lds, s, nnz, J, P.epg, placing, \
                      csf ? nullptr : B->level[0].crd, csf ? nullptr : B->level[1].crd, B->level[2].crd,                  \
                      static_cast<const T*>(B->vals), Cm, Dm, up, A, key1, vec1, bounds)
 #define SPT_MTTKRP(L_, V_)                                \
-  if (csf && placed) SPT_MTTKRP_AS(L_, V_, true, true, 1);   \
+  if (csf && !near) SPT_MTTKRP_AS(L_, V_, true, true, 1, false);   \
+  else if (!near) SPT_MTTKRP_AS(L_, V_, false, true, 1, false);   \
+  else if (csf && placed) SPT_MTTKRP_AS(L_, V_, true, true, 1);   \
   else if (csf) SPT_MTTKRP_AS(L_, V_, true, false, 1);         \
   else if (placed) SPT_MTTKRP_AS(L_, V_, false, true, 1);    \
   else SPT_MTTKRP_AS(L_, V_, false, false, 1)

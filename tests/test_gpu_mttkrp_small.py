@@ -66,3 +66,33 @@ def test_least_workspace(form, J, K, nnz, R, dtype):
     assert bool(got[0].abs().sum() > 0)
     with pytest.raises(Exception):
         spt.spt_mttkrp(B, C, D, R, got[0], torch.empty(least - 1, dtype=torch.uint8, device="cuda"))
+
+
+@pytest.mark.parametrize("form", ["coo", "csf"])
+@pytest.mark.parametrize("more", [0, 1, 20_000])
+def test_offsets_of_rows(form, more):
+    """Factors of 4 GiB, whose rows are found at offsets of 32 bits, and of more."""
+    order.test_ordered_chunks(form, 97, (1 << 23) + more, 503, 30_011, 64, "float64")
+
+
+@pytest.mark.parametrize("R,dtype", [(32, "float32"), (16, "float64"), (8, "float32"), (33, "float64")])
+@pytest.mark.parametrize("nnz", [9_001, 150_001, 700_003])
+def test_empty_segments(R, dtype, nnz):
+    """CSF whose slices and fibres are empty here and there, first fibres of a slice among them, against the same entries in COO."""
+    import numpy as np
+    import torch
+    import paper_1804_10112_amd as spt
+    import workloads as wl
+    I, J, K = 211, 503, 701
+    rng = np.random.default_rng(nnz)
+    key = np.unique(rng.integers(0, I * J * K, nnz))
+    i, j, k = (x.astype(np.int32) for x in (key // (J * K), key // K % J, key % K))
+    v = rng.integers(-1, 2, len(key)).astype(dtype)
+    C, D = (torch.from_numpy(rng.integers(-2, 3, n * R).astype(dtype)).cuda() for n in (J, K))
+    got = []
+    for spec in (wl.coo3_spec((I, J, K), i, j, k, v), wl.csf3_with_empty_segments((I, J, K), i, j, k, v, 7, 400, 40)):
+        B = spt.DeviceTensor(spec)
+        A = torch.full((I, R), float("nan"), dtype=C.dtype, device="cuda")
+        spt.spt_mttkrp(B, C, D, R, A, B.workspace(spt.SPT_OP_MTTKRP, R))
+        got.append(A)
+    assert torch.equal(*got) and bool(got[0].abs().sum() > 0)

@@ -44,7 +44,13 @@ constexpr int kAddWaveTiles = 128;
 // entries 13.3 / 13.4, 500 000 + 250 000 15.9 / 15.8, 800 000 + 400 000 18.8 / 18.3, 2.7M + 1.3M 42.2 / 37.8; three long rows 13.3 /
 // 13.7, 15.8 / 16.5, 18.7 / 19.4, 41.8 / 41.6; (since the searches have a launch of their own) 3.8M + 2M 71 / 68, 18M + 14M 317 / 294.
 constexpr int kAddWholeTiles = 400;
-constexpr int kAddResident = 6, kFillResident = 5;  // workgroups on a compute unit, as registers allow
+// Workgroups on a compute unit, as registers allow without scratch memory (and LDS: 160 KB). Merge, of CSR and COO matrices, with six /
+// seven / eight, 20M + 10M entries, fp64: call 208 / 203 / 212 us. Fill, of CSR, fp32, with five / six / seven (by registers seven): 20M + 4.7M
+// 145 / 142 / 145 us, 2.4M + 2.4M 38.6 / 38.1 / 40.9; COO, fp32, with five / six: 12M + 7.2M 150.8 / 153.3; fp64 has scratch memory with six: 208 / 220.
+template <class KL>
+constexpr int kAddResident = 6;
+template <typename T, int NCRD>
+constexpr int kFillResident = sizeof(T) == 4 && NCRD == 1 ? 6 : 5;
 constexpr int kCus = 256;
 
 // Keys of the entries of a level list in two parts, so that nothing waits for raw() until key() is
@@ -107,6 +113,10 @@ struct WideLoader {  // any extents
     return {o ? c.a0 : a0, o ? c.a1 : a1, o ? c.a2 : a2};
   }
 };
+template <>
+constexpr int kAddResident<ColLoader> = 7;
+template <>
+constexpr int kAddResident<CooLoader<2>> = 7;
 
 template <typename KL>
 struct AddOperands {
@@ -207,10 +217,10 @@ struct AddTile {
 // SELF: few tiles, one for each workgroup, whose ends are searched here and stored in cuts.
 // Otherwise the workgroups that are resident at once go through the tiles and load the next tile's
 // coordinates before they look up this one's. Bound by vector instructions, most of them in the
-// lookups (20M + 10M CSR entries, fp64: 54 us; 115 us as a walk of 7 merge steps per thread, which
+// lookups (20M + 10M CSR entries, fp64: 49 us; 115 us as a walk of 7 merge steps per thread, which
 // also needed the rows expanded to a list, 95 us).
 template <typename KL, bool ROWS, bool UNION, bool SELF>
-__global__ __launch_bounds__(kBlock, kAddResident) void add_merge_kernel(const AddOperands<KL> o, int ntiles,
+__global__ __launch_bounds__(kBlock, kAddResident<KL>) void add_merge_kernel(const AddOperands<KL> o, int ntiles,
                                                            AddCut* __restrict__ cuts, uint64_t* __restrict__ bits,
                                                            int32_t* __restrict__ counts) {
   typedef typename KL::Key Key;
@@ -362,7 +372,7 @@ __device__ __forceinline__ uint64_t lane_value(uint64_t x, int lane) {
 // resident at once go through the tiles, so that only the counts of the tiles between one and the
 // next have to be added up.
 template <typename T, int NCRD, bool UNION>
-__global__ __launch_bounds__(kBlock, kFillResident) void add_fill_kernel(
+__global__ __launch_bounds__(kBlock, (kFillResident<T, NCRD>)) void add_fill_kernel(
     int ntiles, const AddCut* __restrict__ cuts, const uint64_t* __restrict__ bits, const int32_t* __restrict__ counts,
     int nb, int nc, int nrows, const CoordArrays B, const T* __restrict__ bv, const CoordArrays C,
     const T* __restrict__ cv, const CoordOut O, T* __restrict__ ov, int32_t* __restrict__ pos,
@@ -542,7 +552,7 @@ static spt_status launch_add_merge(const AddOperands<KL>& o, int ntiles, AddCut*
     hipLaunchKernelGGL((add_cut_kernel<KL, ROWS>), dim3((ntiles * kCutLanes + kBlock) / kBlock), dim3(kBlock),
                        0, s, o, ntiles, cuts);
     SPT_CHECK_LAUNCH("add cut");
-    hipLaunchKernelGGL((add_merge_kernel<KL, ROWS, UNION, false>), dim3(std::min(ntiles, kAddResident * kCus)), dim3(kBlock), 0, s,
+    hipLaunchKernelGGL((add_merge_kernel<KL, ROWS, UNION, false>), dim3(std::min(ntiles, kAddResident<KL> * kCus)), dim3(kBlock), 0, s,
                        o, ntiles, cuts, bits, counts);
   } else {
     hipLaunchKernelGGL((add_merge_kernel<KL, ROWS, UNION, true>), dim3(ntiles), dim3(kBlock), 0, s, o, ntiles, cuts,
@@ -577,7 +587,7 @@ static spt_status add_typed(Format fb, Format fc, const spt_tensor* B, const spt
   Workspace W(ws, ws_bytes);
   AddCut* cuts = W.take<AddCut>(static_cast<size_t>(ntiles) + 1);
   int32_t* counts = W.take<int32_t>(ntiles);
-  const int grid = std::min(ntiles, kFillResident * kCus);
+  const int grid = std::min(ntiles, (rows ? kFillResident<T, 1> : kFillResident<T, 2>) * kCus);
   uint64_t* bits = W.take<uint64_t>(static_cast<size_t>(ntiles) * (rows ? 3 : 2) * kAddWords);
 
   const T *bv = static_cast<const T*>(B->vals), *cv = static_cast<const T*>(C->vals);

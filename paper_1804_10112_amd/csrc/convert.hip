@@ -193,7 +193,7 @@ spt_status sample_sort_convert(int64_t n, int64_t nrows, int64_t ncols, bool by_
                                const int32_t* col, const VT* vals, int32_t* pos_out, int32_t* crd_out,
                                VT* vals_out, void* ws, size_t ws_bytes, hipStream_t s);
 
-// sort by reserved regions (reserve_sort.hip): a middling number of records
+// sort by reserved regions (reserve_sort.hip): a middling number of records, up to 3M
 bool reserve_sort_applies(int64_t n, int64_t nrows, int64_t ncols);
 size_t reserve_sort_workspace(int dtype, int64_t n);
 template <typename VT>
@@ -217,13 +217,17 @@ static bool radix_is_faster(const SortPlan& P, const spt_tensor* A) {
   return !sample_sort_applies(A->nvals) || (passes <= 3 && A->nvals > from);
 }
 
-// From 16 384 records on the sort by reserved regions is faster than the sample sort (its plan says by how much), up to 1.8M: rows of
-// power-law lengths of three entries on average take 93 / 102 us at 1.6M (reserved / sample sort), 107 / 105 at 2M and 125 / 121 at
-// 2.4M, of 15 entries 87 / 100 and 104 / 107. Radix passes (fp64, in us, reserved / radix): one pass 30.1 / 30.4 at 400 000, 37 / 31 at
+// From 16 384 records on the sort by reserved regions is faster than the sample sort (its plan says by how much), up to 3M: beyond, more
+// and more of its buckets take nine words of a thread, and one that a long row's neighbours crowd is sorted late. Power-law rows, reserved / sample
+// sort, us: of three entries on average 1.7M 93 / 102, 1.9M fp32 99 / 103, 2.2M fp64 108 / 124, fp32 114 / 112, 3M 152 / 143; of four to eight
+// 2M 88 / 108, 2.6M fp32 127 / 115; of 15 2.2M 99 / 112, 3M fp64 118 / 137, fp32 113 / 128, 4M 186 / 162 (uniform ones of
+// five 137 / 153, but the host sees only the mean). Keys of three radix passes: 2.6M rows in a stable order 100 / 119, 3.1M of power-law
+// lengths, fp32, 118 / 114. Radix passes (fp64, in us, reserved / radix): one pass 30.1 / 30.4 at 400 000, 37 / 31 at
 // 640 000; two 47 / 67 at 1M, 73 / 70 at 1.6M.
 static bool reserve_is_fastest(const SortPlan& P, const spt_tensor* A) {
   const int passes = P.passes_col + P.passes_row;
-  const int64_t most = passes == 1 ? 3 << 17 : passes == 2 ? 5 << 18 : 7 << 18;
+  const int64_t mean = A->nvals / std::max<int64_t>(A->level[0].N, 1);
+  const int64_t most = passes == 1 ? 3 << 17 : passes == 2 ? 5 << 18 : mean < 4 ? 7 << 18 : mean < 12 ? 2 << 20 : passes == 3 ? 5 << 19 : 3 << 20;
   return A->nvals <= most && reserve_sort_applies(A->nvals, A->level[0].N, A->level[1].N);
 }
 

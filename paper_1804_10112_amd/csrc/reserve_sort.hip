@@ -100,26 +100,43 @@ __global__ __launch_bounds__(kListThreads) void reserve_lists_kernel(const Uniqu
 #pragma unroll
   for (int e = 0; e < E; ++e) list[blockIdx.x * kList + e * kListThreads + tid] = s_key[ord[e * kListThreads + tid]];
 }
+// (Four lanes to a sample, each with a quarter of the lists, and three keys of a list at a time: five loads in a row. Bisections by one
+// lane, eleven: 16384 samples 8.4 and 11.3 us.)
+constexpr int kMergeLanes = 4;
 template <int S>
 __global__ __launch_bounds__(kListThreads) void reserve_merge_kernel(const uint64_t* __restrict__ list, int nb,
                                                                      uint64_t* __restrict__ skey, int32_t* __restrict__ count) {
-  constexpr int L = S / kList;
-  const int t = blockIdx.x * kListThreads + threadIdx.x;
-  if (t < nb) count[t] = 0;
+  constexpr int L = S / kList, kOwn = L / kMergeLanes;
+  static_assert(kList == 1024 && L % kMergeLanes == 0, "");
+  const int at = blockIdx.x * kListThreads + threadIdx.x, t = at / kMergeLanes, part = at % kMergeLanes;
+  if (at < nb) count[at] = 0;
   const int own = t / kList;
   const uint64_t key = list[t];
-  int lo[L];
+  int lo[kOwn];
 #pragma unroll
-  for (int l = 0; l < L; ++l) lo[l] = 0;
+  for (int i = 0; i < kOwn; ++i) lo[i] = 0;
 #pragma unroll
-  for (int step = kList / 2; step > 0; step >>= 1)
+  for (int step = kList / 4; step > 0; step >>= 2) {
+    uint64_t q[kOwn][3];
 #pragma unroll
-    for (int l = 0; l < L; ++l) lo[l] += list[l * kList + lo[l] + step - 1] < key + (l < own ? 1 : 0) ? step : 0;
-  int rank = t % kList;
+    for (int i = 0; i < kOwn; ++i)
 #pragma unroll
-  for (int l = 0; l < L; ++l)
-    if (l != own) rank += lo[l] + (list[l * kList + lo[l]] < key + (l < own ? 1 : 0) ? 1 : 0);
-  store_splitter<S>(rank, key, nb, skey);
+      for (int r = 0; r < 3; ++r) q[i][r] = list[(i * kMergeLanes + part) * kList + lo[i] + (r + 1) * step - 1];
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) {
+      const uint64_t k = key + (i * kMergeLanes + part < own ? 1 : 0);
+      lo[i] += ((q[i][0] < k ? 1 : 0) + (q[i][1] < k ? 1 : 0) + (q[i][2] < k ? 1 : 0)) * step;
+    }
+  }
+  int rank = part == 0 ? t % kList : 0;
+#pragma unroll
+  for (int i = 0; i < kOwn; ++i) {
+    const int l = i * kMergeLanes + part;
+    if (l != own) rank += lo[i] + (list[l * kList + lo[i]] < key + (l < own ? 1 : 0) ? 1 : 0);
+  }
+#pragma unroll
+  for (int d = 1; d < kMergeLanes; d <<= 1) rank += __shfl_xor(rank, d);
+  if (part == 0) store_splitter<S>(rank, key, nb, skey);
 }
 
 // ---- partition ------------------------------------------------------------------------------
@@ -329,14 +346,16 @@ __global__ __launch_bounds__(NT, WAVES) void reserve_finish_kernel(const Record<
 //   600 000     66.5                                 36.0          46.3
 //   1.0M        73.4                                 45.9          56.2
 //   1.5M        90.2                                 69.5          71.6 (power-law rows: 108.6 and 72.6)
-//   1.7M        96.0                                               76.1
+//   1.7M        96.0                                               73.9 (from here on with the samples' ranks as they are found now)
+//   2.2M       114.8                                               90.3 (in 2048 buckets 101.6)
+//   3.0M       133.1                                              119.9 (117.2)
 // Threads: 512 while buckets are small (512 buckets of 500 000 records 32.8, with 1024 threads 35.1), 1024 beyond (850 000 42.1, with 512
 // five samples of a hundred calls split a bucket; 1.7M in 1024 buckets 76.1). Tiles: 300 000 records in tiles of 2048 / 4096 26.5 / 26.6,
 // 1M 65 / 61.
 struct ReservePlan {
   int nb, samples, tile, threads, room;
 };
-constexpr int64_t kReserveMin = 1 << 14, kReserveMax = 7 << 18;
+constexpr int64_t kReserveMin = 1 << 14, kReserveMax = 3 << 20;
 static ReservePlan reserve_plan(int64_t n) {
   ReservePlan P = n <= 5 << 14   ? ReservePlan{128, 1024, 1024, 512, 0}
                   : n <= 9 << 15 ? ReservePlan{256, 2048, 2048, 512, 0}
@@ -378,7 +397,7 @@ static spt_status launch_splitters(const UniqueSource& src, int n, int bits, con
   } else {
     hipLaunchKernelGGL(reserve_lists_kernel<16384>, dim3(16384 / kList), dim3(kListThreads), 0, s, src, n, bits, picked);
     SPT_CHECK_LAUNCH("samples");
-    hipLaunchKernelGGL(reserve_merge_kernel<16384>, dim3(16384 / kListThreads), dim3(kListThreads), 0, s, picked, P.nb, skey, count);
+    hipLaunchKernelGGL(reserve_merge_kernel<16384>, dim3(16384 * kMergeLanes / kListThreads), dim3(kListThreads), 0, s, picked, P.nb, skey, count);
   }
 #undef SPT_RANK
   SPT_CHECK_LAUNCH("splitters");

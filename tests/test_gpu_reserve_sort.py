@@ -58,7 +58,17 @@ def test_lines_of_the_plan(n, order):
     _check(row, col, rng.random(n).astype(np.float64 if n & 1 else np.float32), N, M, order)
 
 
-@pytest.mark.parametrize("n", [20000, 400003])
+@pytest.mark.parametrize("order", [spt.SPT_ORDER_ROW_COL, spt.SPT_ORDER_ROW_STABLE])
+@pytest.mark.parametrize("n,mean", [(7 << 18, 3), ((7 << 18) + 1, 3), (2 << 20, 4), ((2 << 20) + 1, 4), (2 << 20, 11), (5 << 19, 12), ((5 << 19) + 1, 12),
+                                    (3 << 20, 15), ((3 << 20) + 1, 15)])
+def test_where_the_sample_sort_takes_over(n, mean, order):
+    rng = np.random.default_rng(n)
+    N = n // mean
+    row = np.where(rng.random(n) < 0.9, rng.integers(0, N, n), N // 3).astype(np.int32)
+    _check(row, rng.integers(0, N, n).astype(np.int32), rng.random(n).astype(np.float64 if mean & 1 else np.float32), N, N, order)
+
+
+@pytest.mark.parametrize("n", [20000, 400003, 2_500_003])
 @pytest.mark.parametrize("kind", ["one place", "in order", "backwards", "few rows"])
 def test_orders_and_duplicates(n, kind):
     rng = np.random.default_rng(n)

@@ -325,8 +325,8 @@ __device__ __forceinline__ int bucket_of(const SplitterTable& t, uint64_t k, int
 // hist[base + d * nt + i] = records of tile i of the segment whose bucket is d, and each record's
 // bucket as one byte in dig. A workgroup takes up to `group` consecutive tiles of one segment
 // and stores each bucket's counts of them side by side (digit-major for the scan).
-template <class SRC, bool LEVEL2, int TILE>
-__global__ __launch_bounds__(kBlock) void classify_kernel(const SRC src, const KeyForm f, int n, int nrows, int group,
+template <class SRC, bool LEVEL2, int TILE, int NT = kBlock>
+__global__ __launch_bounds__(NT) void classify_kernel(const SRC src, const KeyForm f, int n, int nrows, int group,
                                                           int nseg, const Tables T,
                                                           const uint64_t* __restrict__ skey1,
                                                           const uint64_t* __restrict__ skey,
@@ -334,7 +334,9 @@ __global__ __launch_bounds__(kBlock) void classify_kernel(const SRC src, const K
                                                           uint8_t* __restrict__ dig, int32_t* __restrict__ hist) {
   __shared__ SplitterTable t;
   __shared__ int s_cnt[kGroup][kRadix];
-  const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  constexpr int kSide = NT / kBlock;  // tiles side by side, a workgroup's part of kBlock threads to each
+  const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(kSide == 1 ? wave_id() : wave_id() % (kBlock / kWave));
+  const int side = kSide == 1 ? 0 : __builtin_amdgcn_readfirstlane(wave_id() / (kBlock / kWave));
   int seg = 0, begin = 0, end = n, tile0, ntiles;
   int64_t base = 0;
   // a contiguous part for each XCD of the groups there are, not of the grid's bound on them, which would leave the last
@@ -352,18 +354,20 @@ __global__ __launch_bounds__(kBlock) void classify_kernel(const SRC src, const K
     ntiles = tiles_in(n, TILE);
     tile0 = g * group;
   }
-  t.key[tid] = skey[seg * kSegMax + tid];
-  t.pos[tid] = spos[seg * kSegMax + tid];
-  for (int q = tid; q < group * kRadix; q += kBlock) (&s_cnt[0][0])[q] = 0;
+  if (kSide == 1 || tid < kSegMax) {
+    t.key[tid] = skey[seg * kSegMax + tid];
+    t.pos[tid] = spos[seg * kSegMax + tid];
+  }
+  for (int q = tid; q < group * kRadix; q += NT) (&s_cnt[0][0])[q] = 0;
   __syncthreads();
   // the segment's keys lie in [lo, hi]
   const uint64_t lo = LEVEL2 && seg > 0 ? skey1[seg] : 0;
   const uint64_t hi = LEVEL2 && seg + 1 < nseg ? skey1[seg + 1] : static_cast<uint64_t>(nrows) << (f.cb - f.kshift);
   const int shift = max(0, 33 - __clzll(static_cast<long long>((hi - lo) | 1)));
   const auto coarse_key = [&](uint64_t k) { return static_cast<uint32_t>((k - lo) >> shift); };
-  t.coarse[tid] = tid == 0 || t.key[tid] == ~uint64_t{0} ? ~0u : coarse_key(t.key[tid]);  // ~0: no record's
+  if (kSide == 1 || tid < kSegMax) t.coarse[tid] = tid == 0 || t.key[tid] == ~uint64_t{0} ? ~0u : coarse_key(t.key[tid]);  // ~0: no record's
   __syncthreads();
-  if (tid > 0) {  // node tid of the tree: which splitter
+  if (tid > 0 && (kSide == 1 || tid < kSegMax)) {  // node tid of the tree: which splitter
     const int level = 31 - __clz(tid);
     t.tree[tid] = t.coarse[((tid - (1 << level)) * 2 + 1) << (kRadixBits - 1 - level)];
   }
@@ -374,18 +378,18 @@ __global__ __launch_bounds__(kBlock) void classify_kernel(const SRC src, const K
     const int from = min(p, end - 1);  // (beyond the end: the last record, not used)
     return src.from(from).key_near(min(lane, end - 1 - from), f) >> f.kshift;
   };
-  const int first = begin + tile0 * TILE + w * kWave;
+  const int first = begin + (tile0 + side) * TILE + w * kWave;
   constexpr int kAhead = TILE / kBlock < 8 ? TILE / kBlock : 8;  // keys in flight per thread, across tiles
   uint64_t ahead[kAhead];
 #pragma unroll
   for (int k = 0; k < kAhead; ++k) ahead[k] = load(first + k * kBlock);
-  for (int q = 0; q < nt; ++q) {
+  for (int q = side; q < nt; q += kSide) {
     int* cnt = s_cnt[q];
 #pragma unroll
     for (int k = 0; k < (TILE / kBlock); ++k) {
-      const int p = first + q * TILE + k * kBlock;  // uniform
+      const int p = first + (q - side) * TILE + k * kBlock;  // uniform
       const uint64_t key = ahead[k % kAhead];
-      ahead[k % kAhead] = load(p + kAhead * kBlock);
+      ahead[k % kAhead] = load(p + (k + kAhead < TILE / kBlock ? 0 : (kSide - 1) * TILE) + kAhead * kBlock);
       const int d = bucket_of(t, key, p + lane, coarse_key(key));
       if (p + kWave <= end) {  // the whole wave
         // ordered input: a wave's records share a bucket, and adds to one counter are serialised
@@ -402,8 +406,9 @@ __global__ __launch_bounds__(kBlock) void classify_kernel(const SRC src, const K
     }
   }
   __syncthreads();
-  int32_t* out = hist + base + static_cast<int64_t>(tid) * ntiles + tile0;
-  for (int q = 0; q < nt; ++q) out[q] = s_cnt[q][tid];
+  const int d = kSide == 1 ? tid : tid % kRadix;
+  int32_t* out = hist + base + static_cast<int64_t>(d) * ntiles + tile0;
+  for (int q = kSide == 1 ? 0 : tid / kRadix; q < nt; q += kSide) out[q] = s_cnt[q][d];
 }
 
 // The counts become offsets, in place. Level 1: a workgroup has the counts of one bucket, which become the records of the
@@ -1074,12 +1079,17 @@ spt_status sample_sort_convert(int64_t n64, int64_t nrows, int64_t ncols, bool b
   }
 #undef SPT_RANK
   SPT_CHECK_LAUNCH("splitters");
-  const int group = nt1 >= 2048 && tile == kTile ? kGroup : 1;  // few tiles: a workgroup for each
-#define SPT_CLASSIFY(TILE_)                                                                                          \
-  hipLaunchKernelGGL((classify_kernel<RcSource, false, TILE_>), dim3((nt1 + group - 1) / group), dim3(kBlock), 0, s, \
+  // Few tiles: a workgroup for each. From 2048 on, one for four, which shares its table; up to 4096 of twice the threads, as there are hardly
+  // enough workgroups (fp64, in us, four tiles by 256 / four by 512 / one by 256: 8.6M 298 / 282 / 284, 12M 354 / 337 / 342, 14.5M
+  // 413 / 399 / 408, 16.5M 462 / 458 / 467; 18M 474 / 484 / 481, 30M 761 / 768 / 780, 60M 1503 / 1514 / 1551; 5.4M 192 / 202 / 191).
+  const int group = nt1 >= 2048 && tile == kTile ? kGroup : 1;
+  const bool wide = group == kGroup && nt1 < 4096;
+#define SPT_CLASSIFY(TILE_, ...)                                                                                          \
+  hipLaunchKernelGGL((classify_kernel<RcSource, false, TILE_, ##__VA_ARGS__>), dim3((nt1 + group - 1) / group), dim3(wide ? 2 * kBlock : kBlock), 0, s, \
                      rc, f, n, static_cast<int>(nrows), group, 1, T, nullptr, skey1, spos1, dig, hist1)
   if (tile == kSmallTile) SPT_CLASSIFY(kSmallTile);
   else if (tile == 2 * kSmallTile) SPT_CLASSIFY(2 * kSmallTile);
+  else if (wide) SPT_CLASSIFY(kTile, 2 * kBlock);
   else SPT_CLASSIFY(kTile);
 #undef SPT_CLASSIFY
   SPT_CHECK_LAUNCH("classify");
@@ -1141,6 +1151,9 @@ spt_status sample_sort_convert(int64_t n64, int64_t nrows, int64_t ncols, bool b
   else if (tile == 2 * kSmallTile)
     hipLaunchKernelGGL((classify_kernel<KSource, true, 2 * kSmallTile>), dim3(tiles2 / group + kSegMax), dim3(kBlock), 0, s, s1,
                        f, n, static_cast<int>(nrows), group, nb1, T, skey1, skey2, spos2, dig, hist2);
+  else if (wide)
+    hipLaunchKernelGGL((classify_kernel<KSource, true, kTile, 2 * kBlock>), dim3(tiles2 / group + kSegMax), dim3(2 * kBlock), 0, s, s1, f,
+                       n, static_cast<int>(nrows), group, nb1, T, skey1, skey2, spos2, dig, hist2);
   else
     hipLaunchKernelGGL((classify_kernel<KSource, true, kTile>), dim3(tiles2 / group + kSegMax), dim3(kBlock), 0, s, s1, f,
                        n, static_cast<int>(nrows), group, nb1, T, skey1, skey2, spos2, dig, hist2);

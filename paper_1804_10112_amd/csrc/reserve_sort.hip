@@ -1,7 +1,7 @@
 // COO -> CSR of a middling number of records in one partition, gfx950.
 //
 // The sample sort (sample_sort.hip) partitions stably: count, scan, scatter, five launches for one level and nine or ten for
-// two, and conversions of less than two million records spend most of their time between dependent loads and launches. Here
+// two, and conversions of less than three million records spend most of their time between dependent loads and launches. Here
 // a record carries its position among the bits of its key, (row, column, position) or (row, position, column): no two
 // keys are alike, so records may move in any order. One launch places them: a workgroup counts its tile's records of
 // each bucket in LDS, takes as much of each bucket's region with an atomic add, and stores them there. One workgroup per
@@ -10,7 +10,7 @@
 // Keys of more than 64 bits and workspaces of less than the query are for the sample sort.
 //
 // Measured (fp64, 107 000 records, 34.1 us before: samples' ranks 5, partition 7, finish 7 us; 500 000 63 -> 33;
-// 1M 73 -> 46, of which the finish takes 25; 50 000 19.8 -> 15.3). Up to 100 000 records the launches and the chain of loads in
+// 1M 73 -> 46, of which the finish takes 25; 2.2M 115 -> 90; 50 000 19.8 -> 15.3). Up to 100 000 records the launches and the chain of loads in
 // each bound it, beyond the network of the finish (vector instructions and barriers) and the adds (counters
 // each in a line of their own: within 2 %).
 #include <algorithm>

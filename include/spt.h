@@ -271,6 +271,10 @@ spt_status spt_ttv(const spt_tensor* B, const void* c, int32_t* out_crd0,
  * dimension of B's first level. C: (dim of level 1) x J, D: (dim of level 2)
  * x J, A_out: (dim of level 0) x J, all dense row-major, A_out OVERWRITTEN
  * (rows without entries get 0). B is COO3 or CSF3, ordered. 1 <= J <= 1024.
+ * The workspace of the query suits the fastest split of the entries; a call also runs,
+ * slower and with its sums in another order, with less, down to the bytes that the
+ * message of SPT_ERR_WORKSPACE names. The same operand and workspace size give the same
+ * result bit for bit.
  */
 spt_status spt_mttkrp(const spt_tensor* B, const void* C, const void* D,
                       int32_t J, void* A_out, void* ws, size_t ws_bytes,

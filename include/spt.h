@@ -273,8 +273,8 @@ spt_status spt_ttv(const spt_tensor* B, const void* c, int32_t* out_crd0,
  * (rows without entries get 0). B is COO3 or CSF3, ordered. 1 <= J <= 1024.
  * The workspace of the query suits the fastest split of the entries; a call also runs,
  * slower and with its sums in another order, with less, down to the bytes that the
- * message of SPT_ERR_WORKSPACE names. The same operand and workspace size give the same
- * result bit for bit.
+ * message of SPT_ERR_WORKSPACE names. The same operands, with factors aligned alike, and the
+ * same workspace size give the same result bit for bit.
  */
 spt_status spt_mttkrp(const spt_tensor* B, const void* C, const void* D,
                       int32_t J, void* A_out, void* ws, size_t ws_bytes,

@@ -1,5 +1,5 @@
 """MTTKRP whose columns are split into parts of whole lines: entry counts on both sides of the rule, two, four and eight parts,
-parts of more than a line, chunks in the order of their rows of C, rows that cannot be split, factors that do not lie on lines."""
+parts of more than a line and of lines that leave lanes idle, chunks in the order of their rows of C, rows that cannot be split, factors that do not lie on lines."""
 import pytest
 
 import test_gpu_mttkrp_order as order
@@ -17,7 +17,17 @@ pytestmark = pytest.mark.gpu
     (97, 9_001, 9_001, 97_657, 128, "float32"),
     (97, 5_003, 5_001, 100_003, 256, "float32"),        # eight
     (97, 3_001, 2_003, 100_003, 512, "float32"),        # eight of two lines
-    (97, 9_001, 9_001, 97_657, 96, "float32"),          # three lines
+    (97, 9_001, 9_001, 97_657, 96, "float32"),          # three lines: one part
+    (97, 9_001, 9_001, 97_657, 96, "float64"),          # two of three lines, lanes idle
+    (97, 4_001, 4_003, 97_657, 192, "float64"),         # (factors too small for that)
+    (97, 9_001, 9_001, 97_657, 192, "float64"),         # four
+    (97, 9_001, 9_001, 97_657, 160, "float64"),         # two would be of five lines: one part
+    (97, 9_001, 9_001, 97_657, 320, "float64"),         # two of ten lines
+    (97, 4_001, 4_003, 50_021, 384, "float64"),         # two of twelve lines
+    (97, 9_001, 9_001, 50_021, 384, "float64"),         # eight of three lines
+    (3, 9_001, 9_001, 50_021, 640, "float64"),          # four of ten lines
+    (97, 9_001, 9_001, 97_657, 384, "float32"),
+    (97, 9_001, 9_001, 50_021, 768, "float32"),
     (97, 20_011, 16_001, 400_003, 33, "float64"),
     (400, 47_000, 47_000, 8_000_005, 32, "float64"),    # ordered
 ])

@@ -137,6 +137,51 @@ def test_mttkrp_has_more_workgroups_than_compute_units(fmt, dtype, J):
         assert workgroups(nnz) > 340, (nnz, workgroups(nnz))
 
 
+PARTS = r"""
+#include <vector>
+#include "mttkrp_plan.hpp"
+int main() {
+  long long nnz, J, rows_c, rows_d;
+  int dtype, csf;
+  while (std::scanf("%lld %lld %lld %lld %d %d", &nnz, &J, &rows_c, &rows_d, &dtype, &csf) == 6) {
+    const int value = dtype == SPT_F64 ? 8 : 4;
+    const int parts = spt::mttkrp_parts(nnz, J * value, rows_c, rows_d, csf);
+    const spt::MttkrpPlan P = spt::mttkrp_plan(nnz, J, dtype, csf, parts);
+    std::vector<int> kept(J, 0), of_part(parts, 0);
+    int outside = 0;
+    for (int part = 0; part < parts; ++part)
+      for (int v = 0; v < P.tiles * P.lanes; ++v) {
+        bool keeps;
+        const int col = spt::column_of(static_cast<int>(J) / parts, P.vec, part, v, &keeps);
+        outside += col < 0 || col + P.vec > J;
+        for (int x = 0; keeps && x < P.vec; ++x)
+          if (col + x < J) of_part[part] += kept[col + x]++ == 0;
+      }
+    int missed = 0, least = of_part[0], most = of_part[0];
+    for (const int k : kept) missed += k == 0;
+    for (const int n : of_part) least = std::min(least, n), most = std::max(most, n);
+    std::printf("%d %d %d %d %d %d\n", parts, outside, missed, least, most, parts * P.tiles * P.lanes * P.vec);
+  }
+}
+"""
+
+
+def test_parts_of_the_columns_are_equal_and_cover_them(tmp_path):
+    """Workgroups of every part have as many columns, of whole lines, and no more than a quarter of their lanes idle."""
+    cases = [(n, J, c, d, dtype, csf) for n in (200_000, 20_000_000) for J in range(1, 1025) for c, d in ((20_000, 10_000), (4000, 4000), (9000, 9000))
+             for dtype in (spt.SPT_F64, spt.SPT_F32) for csf in (0, 1)]
+    got = _run(tmp_path, PARTS, "\n".join("%d %d %d %d %d %d" % c for c in cases)).splitlines()
+    assert len(got) == len(cases)
+    several = set()
+    for (n, J, c, d, dtype, csf), line in zip(cases, got):
+        parts, outside, missed, least, most, lanes = map(int, line.split())
+        assert outside == 0 and missed == 0 and least == most == J // parts, (n, J, c, d, dtype, csf, line)
+        if parts > 1:
+            assert J // parts * (8 if dtype == spt.SPT_F64 else 4) % 128 == 0 and 4 * J >= 3 * lanes, (n, J, c, d, dtype, csf, line)
+            several.add((J, dtype, parts))
+    assert {(96, spt.SPT_F64, 2), (192, spt.SPT_F64, 4), (640, spt.SPT_F64, 4), (768, spt.SPT_F32, 8)} <= several
+
+
 def test_the_kernel_that_gathers_slice_by_slice_keeps_its_registers(tmp_path):
     """Entries of a lane take 80 of its 128 registers; what no longer fits beside them would go through scratch memory."""
     asm = tmp_path / "spmv_slices.s"

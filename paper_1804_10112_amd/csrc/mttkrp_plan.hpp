@@ -53,7 +53,10 @@ struct MttkrpPlan {
 //       COO, fp32: 900 000 entries 33.2 / 31.3; 1.3M 45.2 / 38.4; 3M 71.3 / 70.6; fp64: 600 000 50.5 / 44.2; 2M 106 / 100
 //   - 32 lanes, whose batches of 128 entries are too long (400 000 entries 65.6 in 16, 68.0): multiples of 16, up to 64 of them such that
 //     three workgroups go to a compute unit (six / three, J = 33, fp64: COO 150 000 27.4 / 25.6, even 30.2 / 25.6; 300 000
-//     40.9 / 38.1, 46.4 / 41.2; 500 000 50.1 / 48.3, 60.6 / 54.8; CSF 300 000 47.2 / 41.9, 55.2 / 46.1).
+//     40.9 / 38.1, 46.4 / 41.2; 500 000 50.1 / 48.3, 60.6 / 54.8; CSF 300 000 47.2 / 41.9, 55.2 / 46.1). Where four workgroups and more share the
+//     columns of a chunk, up to 32 such that three go to a compute unit, or up to 64 such that three chunks do (J = 128 to 1024, 222 calls of
+//     any sizes and 396 on a grid: against groups as long as six chunks to a compute unit leave, .96 of the time on average and more than 1.06 of it in 56
+//     calls; with up to 64 counting all workgroups .98 and in 130).
 //   - 16 lanes, whose batches are of 64 entries: groups of 48 as long as two workgroups on each compute unit hold the tensor.
 //     With 64 there are hardly more workgroups than compute units, and a skewed tensor ends on one of them. (COO: even slices
 //     lose some of what 64 gain, up to 5 %, skewed ones gain as much; with 32, even slices lose 10 %, fp32.) Groups of
@@ -79,6 +82,7 @@ struct MttkrpPlan {
 //   24 of 32 lanes: J = 96, fp64 .98 .90, .91 .71, .92 .83; 192 1.15 .90, .87 .72, .85 .83; 384 1.16 .93, .85 .73, .86 .85
 //   80 of 96: J = 320 1.14 .96, .91 .89, .93 .93; 640 1.05 .91, .89 .87, .88 .90
 //   40 of 64: J = 160 1.20 1.07, 1.06 1.03, 1.06 1.03; 320 1.35 1.11, 1.03 .96, 1.02 .98; 640 1.36 1.15, 1.05 .98, 1.03 .99
+//   24 and 80, 20 000 and 10 000, even, one part / parts, us: J = 384 999 / 866, 640 1680 / 1479
 //   56 of 64: J = 448 1.02 .85 (1M); 160 of 160: J = 640 .94 .91, .90 .94, .92 .96; 64 of 64: J = 1024 .95 .83, .83 .91, .88 .96
 // and of 4000 and 4000, 300 000 entries (37 to a row) and 600 000: 24 of 32, J = 192 1.02 .80, 1.18 .93; 384 .98 .73, 1.13 .84; 80 of 96, J = 320 .89
 // .80, 1.05 .94; 640 .85 .75, 1.01 .86.
@@ -110,6 +114,7 @@ inline MttkrpPlan mttkrp_plan(int64_t nnz, int64_t J, int dtype, bool csf, int p
   const int64_t at_once = int64_t(256) * groups * 16 / parts;  // with 16 entries to a group, a workgroup to each compute unit
   const int64_t want = nnz * parts / (6 * 256) / groups;
   const auto workgroups = [&](int64_t epg) { return (nnz + groups * epg - 1) / (groups * epg) * tiles * parts; };
+  const auto three = [&](int64_t times) { return (nnz * times / (3 * 256) / groups + 8) / 16 * 16; };
   int64_t epg = 16;
   if (P.lanes > 16) epg = std::max<int64_t>(want / 16 * 16, 16);
   else if (P.lanes == 16 && nnz > (csf ? 4 : 5) * at_once && nnz <= int64_t(2) * 256 * groups * 48) epg = 48;
@@ -119,7 +124,7 @@ inline MttkrpPlan mttkrp_plan(int64_t nnz, int64_t J, int dtype, bool csf, int p
     else if (workgroups(8) <= 3 * 256) epg = 8;
     else if (!csf && P.lanes <= 4) epg = 4 * P.lanes;
     else if (!csf && P.lanes <= 16 && nnz > 3 * at_once && epg == 16) epg = 32;
-    else if (P.lanes > 16) epg = std::max(epg, std::min<int64_t>((nnz * tiles * parts / (3 * 256) / groups + 8) / 16 * 16, 64));
+    else if (P.lanes > 16) epg = std::max({epg, std::min(three(tiles * parts), int64_t(tiles < 4 ? 64 : 32)), std::min(three(parts), int64_t(64))});
   }
   P.epg = static_cast<int>(std::min<int64_t>(epg, std::min(128, 2048 / groups)));
   P.chunk = P.epg * groups;

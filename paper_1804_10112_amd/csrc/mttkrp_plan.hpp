@@ -42,9 +42,10 @@ struct MttkrpPlan {
 //       J = 8, fp32, 12M entries 124 / 105, 154 / 137; 30M 277 / 225, 351 / 316; 2.5M 34.7 / 30.4, 41 / 40; J = 4, fp64, 30M 319 / 232, 400 / 323
 //       J = 16, fp32, 12M 137 / 111, 196 / 167; 30M 291 / 236, 452 / 386; 2.5M 41.2 / 35.8, 49.9 / 46.9; J = 8, fp64, 30M 300 / 266; J = 3,
 //       fp32, 20M 196 / 165. (CSF reads two arrays and gains more from long chunks: J = 8, fp32, 12M 113 / 125, J = 16 132 / 147.)
-//   - 16, which a group's fixed work (bounds, scan, carry) is worth, while all workgroups then fit the compute units at a
-//     time (five of a COO tensor to each, four of CSF; of COO with eight and 16 lanes three, then 32: 400 000
-//     entries, fp64, J = 16 20.8 / 19.4, even 21.5 / 19.2; 210 000, fp32, J = 33 20.8 / 20.7, 23.4 / 20.4).
+//   - 16, which a group's fixed work (bounds, scan, carry) is worth, while some four (CSF) or five (COO) workgroups go to a compute unit (a line
+//     by measurement; by registers five of either fit, of COO in fp64 with two to 16 lanes four). Of COO with eight lanes three, with
+//     16 four, then 32 (32 / 16, twelve tensors of each: eight lanes, 410 000 entries, even .97, skewed 1.05, 520 000 .93, .99; 16 lanes,
+//     210 000 1.00, 1.11, 255 000 .98, 1.08, 270 000 .92, 1.03, 320 000 .91, 1.03).
 //   - Beyond, as many as leave about six workgroups to each, in whole batches of the coordinates that the group's lanes hold (four
 //     each), since a part of one costs as much; at most 2048 entries per workgroup
 //     (measured with 512 to 4096: more entries keep fewer rows of C in cache, fewer leave more carries;
@@ -123,7 +124,7 @@ inline MttkrpPlan mttkrp_plan(int64_t nnz, int64_t J, int dtype, bool csf, int p
     if ((csf || P.lanes > 2) && workgroups(4) <= 2 * 256) epg = 4;
     else if (workgroups(8) <= 3 * 256) epg = 8;
     else if (!csf && P.lanes <= 4) epg = 4 * P.lanes;
-    else if (!csf && P.lanes <= 16 && nnz > 3 * at_once && epg == 16) epg = 32;
+    else if (!csf && P.lanes <= 16 && nnz > (P.lanes == 16 ? 4 : 3) * at_once && epg == 16) epg = 32;
     else if (P.lanes > 16) epg = std::max({epg, std::min(three(tiles * parts), int64_t(tiles < 4 ? 64 : 32)), std::min(three(parts), int64_t(64))});
   }
   P.epg = static_cast<int>(std::min<int64_t>(epg, std::min(128, 2048 / groups)));

@@ -9,8 +9,8 @@ import test_gpu_mttkrp_order as order
 
 pytestmark = pytest.mark.gpu
 
-# two workgroups to a compute unit with 4 entries to a group, three with 8, three with 16
-EDGES = {lanes: (512 * 4 * (256 // lanes), 768 * 8 * (256 // lanes), 768 * 16 * (256 // lanes)) for lanes in (2, 4, 8, 16, 32)}
+# two workgroups to a compute unit with 4 entries to a group, three with 8, three with 16 (16 lanes: four)
+EDGES = {lanes: (512 * 4 * (256 // lanes), 768 * 8 * (256 // lanes), (1024 if lanes == 16 else 768) * 16 * (256 // lanes)) for lanes in (2, 4, 8, 16, 32)}
 
 
 @pytest.mark.parametrize("form", ["coo", "csf"])

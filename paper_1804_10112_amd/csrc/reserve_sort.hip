@@ -5,8 +5,8 @@
 // a record carries its position among the bits of its key, (row, column, position) or (row, position, column): no two
 // keys are alike, so records may move in any order. One launch places them: a workgroup counts its tile's records of
 // each bucket in LDS, takes as much of each bucket's region with an atomic add, and stores them there. One workgroup per
-// bucket then sorts it in LDS. What a bucket's region, or its workgroup, does not hold is picked out again, a part
-// of the key range at a time, by its workgroup. The result is that of a stable sort whatever order the adds come in.
+// bucket then sorts it in LDS. What its workgroup does not hold is picked out of its region, a part of the key range at
+// a time; what a bucket's region does not hold is picked out of the input by all workgroups, a part each. The result is that of a stable sort whatever order the adds come in.
 // Keys of more than 64 bits and workspaces of less than the query are for the sample sort.
 //
 // Measured (fp64, 107 000 records, 34.1 us before: samples' ranks 5, partition 7, finish 7 us; 500 000 63 -> 33;
@@ -25,13 +25,14 @@ namespace spt {
 // K = row, column and position side by side (by row alone: row, position, column).
 struct UniqueForm {
   int row_shift, col_shift, pos_shift;
-  uint32_t col_mask;
+  uint32_t col_mask, pos_mask;
   __device__ __forceinline__ uint64_t key(int row, int col, int p) const {
     return static_cast<uint64_t>(static_cast<uint32_t>(row)) << row_shift | static_cast<uint64_t>(static_cast<uint32_t>(col)) << col_shift |
            static_cast<uint64_t>(static_cast<uint32_t>(p)) << pos_shift;
   }
   __device__ __forceinline__ int row_in(uint64_t K) const { return static_cast<int>(K >> row_shift); }
   __device__ __forceinline__ int col_of(uint64_t K) const { return static_cast<int>(static_cast<uint32_t>(K >> col_shift) & col_mask); }
+  __device__ __forceinline__ int pos_of(uint64_t K) const { return static_cast<int>(static_cast<uint32_t>(K >> pos_shift) & pos_mask); }
 };
 struct UniqueSource {
   const int32_t* __restrict__ row;
@@ -216,62 +217,268 @@ __global__ __launch_bounds__(NT) void reserve_partition_kernel(const UniqueSourc
 
 // ---- finish ---------------------------------------------------------------------------------
 constexpr int kStagedWords = 5, kMostWords = 9;  // words of a thread: whose records pass through LDS, and at most
-// A bucket of more records than a workgroup sorts: they are picked out of its region, or out of the input where that does not
-// hold them, those of a part of the key range at a time that fit. Keys differ, so halving the range ends.
-template <int NT, typename VT, class KA, class VA>
-__device__ __forceinline__ void pick_and_store(char* mem, const KA& key_at, const VA& val_at, const UniqueForm& f, int n, int first,
-                                               uint64_t lo, uint64_t last, int lo_row, int hi_row, int32_t* __restrict__ pos,
-                                               int32_t* __restrict__ crd_out, VT* __restrict__ val_out) {
-  constexpr int E = 4, kMost = NT * E, kLi = number_bits(kMost);
-  uint32_t* words = reinterpret_cast<uint32_t*>(mem);
-  int32_t* at = reinterpret_cast<int32_t*>(words + kMost);
-  uint16_t* ord = reinterpret_cast<uint16_t*>(at + kMost);
-  __shared__ int s_found;
-  const int tid = threadIdx.x;
-  uint64_t from = lo, to = last;
-  int a_row = lo_row;
-  for (;;) {
-    if (tid == 0) s_found = 0;
-    __syncthreads();
-    constexpr int U = 4;
-    for (int p0 = tid; p0 < n; p0 += U * NT) {
-      uint64_t key[U];
+// Where records are picked from: a region of n records, or the whole input.
+template <typename VT>
+struct PickSource {
+  const Record<uint64_t, VT>* __restrict__ region;  // null: the input
+  UniqueSource input;
+  int n;
+};
+// f(key) for all keys of a source, by a workgroup. Of the input, a thread has eight rows and columns in flight.
+template <int NT, typename VT, class F>
+__device__ __forceinline__ void each_key(const PickSource<VT>& s, const F& f) {
+  if (s.region) {
+    for (int p = threadIdx.x; p < s.n; p += NT) f(at32(s.region, p).key());
+    return;
+  }
+  typedef int32_t I4 __attribute__((ext_vector_type(4), aligned(4)));
+  constexpr int U = 2;
+  for (int p0 = 4 * threadIdx.x; p0 < s.n; p0 += 4 * U * NT) {
+    I4 row[U], col[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) key[u] = key_at(min(p0 + u * NT, n - 1));
+    for (int u = 0; u < U; ++u) {
+      const int from = min(p0 + 4 * u * NT, s.n - 4);
+      row[u] = *reinterpret_cast<const I4*>(s.input.row + from);
+      col[u] = *reinterpret_cast<const I4*>(s.input.col + from);
+    }
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (p0 + u * NT < n && key[u] >= from && key[u] <= to) {
-          const int i = atomicAdd(&s_found, 1);
-          if (i < kMost) at[i] = p0 + u * NT;
-        }
-      }
+    for (int u = 0; u < U; ++u) {
+      const int p = p0 + 4 * u * NT, from = min(p, s.n - 4);  // (the last four once)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (from + q >= p) f(s.input.f.key(row[u][q], col[u][q], from + q));
     }
-    __syncthreads();
-    const int cnt = s_found;
-    __syncthreads();
-    if (cnt > kMost) {
-      to = from + (to - from) / 2;
-      continue;
-    }
-    const int b_row = to == last ? hi_row : f.row_in(to + 1);
-    if (cnt == 0) {
-      if (tid < kWave) store_pos_range(pos, tid == 0 ? a_row : 0, tid == 0 ? b_row : 0, first);
-    } else {
-      sort_records<NT, E, kLi>(words, ord, cnt, coarse_shift<kLi>(from, to), [&](int li) { return key_at(at[li]) - from; });
-      store_entries<NT, E>(ord, cnt, first, a_row, b_row, f, [&](int li) { return key_at(at[li]); }, pos, crd_out,
-                           [&](int j, int li) { val_out[first + j] = val_at(at[li]); });
-    }
-    if (to == last) break;
-    const uint64_t width = to - from;
-    first += cnt;
-    a_row = b_row;
-    from = to + 1;
-    to = (last - from) / 2 <= width ? last : from + 2 * width;
-    __syncthreads();
   }
 }
 
-// Bound by the network, whose steps wait for each other: as many workgroups to a compute unit as registers and LDS allow. A
+// What all threads of a workgroup have, added up.
+__device__ __forceinline__ int block_total(int x) {
+  __shared__ int s_total;
+  if (threadIdx.x == 0) s_total = 0;
+  __syncthreads();
+  const int sum = wave_inclusive_sum(x);
+  if (lane_id() == kWave - 1 && sum) atomicAdd(&s_total, sum);
+  __syncthreads();
+  const int total = s_total;
+  __syncthreads();
+  return total;
+}
+
+// The (rank + 1)th smallest of n keys of LDS, all of them in [lo, last].
+template <int NT>
+__device__ __forceinline__ uint64_t ranked_key(const uint64_t* keys, int n, int rank, uint64_t lo, uint64_t last) {
+  while (lo < last) {
+    const uint64_t mid = lo + (last - lo) / 2;
+    int upto = 0;
+    for (int i = threadIdx.x; i < n; i += NT) upto += keys[i] <= mid ? 1 : 0;
+    if (block_total(upto) > rank) last = mid;
+    else lo = mid + 1;
+  }
+  return lo;
+}
+
+// [from, to] has more than `most` records: it becomes a range of at most that many and of one at least, before which [from, to] has none.
+// Each look counts them in NT parts of the range, so that a range of one part is 2^9 times narrower: eight looks at most, as keys differ.
+template <int NT, typename VT>
+__device__ __forceinline__ void narrow(uint32_t* hist, const PickSource<VT>& source, int most, uint64_t* from_at, uint64_t* to_at) {
+  __shared__ int s_wave[NT / kWave], s_part, s_before;
+  const int tid = threadIdx.x;
+  uint64_t from = *from_at, to = *to_at;
+  for (;;) {
+    const int shift = max(0, 64 - __clzll(static_cast<long long>((to - from) | 1)) - (31 - __clz(NT)));
+    hist[tid] = 0;
+    __syncthreads();
+    each_key<NT>(source, [&](uint64_t key) {
+      if (key >= from && key <= to) atomicAdd(&hist[(key - from) >> shift], 1u);
+    });
+    __syncthreads();
+    const int own = static_cast<int>(hist[tid]), sum = wave_inclusive_sum(own);
+    if (lane_id() == kWave - 1) s_wave[wave_id()] = sum;
+    __syncthreads();
+    int before = sum - own;
+    for (int w = 0; w < wave_id(); ++w) before += s_wave[w];
+    if (before <= most && before + own > most) {  // one thread's
+      s_part = tid;
+      s_before = before;
+    }
+    __syncthreads();
+    const uint64_t start = from + (static_cast<uint64_t>(s_part) << shift);
+    const bool some = s_before > 0;
+    __syncthreads();
+    if (some) {
+      to = start - 1;
+    } else {
+      const uint64_t width = (uint64_t{1} << shift) - 1;
+      from = start;
+      to = to - start < width ? to : start + width;
+    }
+    if (some || shift == 0) break;
+  }
+  *from_at = from;
+  *to_at = to;
+}
+
+template <int NT>
+constexpr int kPickKeys = 8 * NT;  // of LDS, at most
+// n keys of LDS in order, padded to a power of two: a bitonic sort that takes few registers, for what is rarely sorted.
+template <int NT>
+__device__ __forceinline__ void sort_keys(uint64_t* key, int n) {
+  int size = 2 * NT;
+  while (size < n) size *= 2;
+  for (int i = n + threadIdx.x; i < size; i += NT) key[i] = ~uint64_t{0};
+  __syncthreads();
+  for (int k = 2; k <= size; k *= 2)
+    for (int d = k / 2; d > 0; d /= 2) {
+#pragma unroll 1
+      for (int t = threadIdx.x; t < size / 2; t += NT) {
+        const int i = 2 * t - (t & (d - 1)), j = i + d;
+        const uint64_t a = key[i], b = key[j];
+        if ((a > b) == ((i & k) == 0)) {
+          key[i] = b;
+          key[j] = a;
+        }
+      }
+      __syncthreads();
+    }
+}
+
+// The records of a source with keys in [lo, last], stored in order from entry `first` on, which counts from key `below` on: as many at a time as LDS
+// holds keys of. A key tells the position and so the value.
+template <int NT, typename VT>
+__device__ __forceinline__ void pick_and_store(uint64_t* mem, const PickSource<VT>& source, const VT* __restrict__ val_in, int first,
+                                               uint64_t below, uint64_t lo, uint64_t last, int lo_row, int hi_row, int32_t* __restrict__ pos,
+                                               int32_t* __restrict__ crd_out, VT* __restrict__ val_out) {
+  constexpr int kMost = kPickKeys<NT>;
+  const UniqueForm& f = source.input.f;
+  __shared__ int s_found;
+  const int tid = threadIdx.x;
+  uint64_t from = lo, to = last;
+  int a_row = lo_row, left = -1;  // left: how many lie in [from, last], once that is known
+  for (;;) {
+    if (tid == 0) s_found = 0;
+    __syncthreads();
+    int before = 0;
+    each_key<NT>(source, [&](uint64_t key) {
+      if (key >= from && key <= to) {
+        const int i = atomicAdd(&s_found, 1);
+        if (i < kMost) mem[i] = key;
+      }
+      before += key >= below && key < lo ? 1 : 0;
+    });
+    __syncthreads();
+    int cnt = s_found;
+    if (left < 0) {
+      left = cnt;
+      first += block_total(before);
+      below = lo;
+    }
+    __syncthreads();
+    if (cnt > kMost && from < to) {
+      narrow<NT>(reinterpret_cast<uint32_t*>(mem), source, kMost, &from, &to);
+      continue;
+    }
+    cnt = min(cnt, kMost);
+    sort_keys<NT>(mem, cnt);
+    const int b_row = to == last ? hi_row : f.row_in(to + 1);
+    for (int j0 = 0; j0 == 0 || j0 < cnt; j0 += NT) {
+      const int j = j0 + tid;
+      int row = 0, prev = 0;
+      if (j < cnt) {
+        const uint64_t K = mem[j];
+        row = f.row_in(K);
+        prev = j > 0 ? f.row_in(mem[j - 1]) : a_row;
+        crd_out[first + j] = f.col_of(K);
+        val_out[first + j] = val_in[f.pos_of(K)];
+      }
+      store_pos_range(pos, prev, row, first + j);
+      const bool end = j == max(cnt - 1, 0);
+      store_pos_range(pos, end ? (cnt ? row : a_row) : 0, end ? b_row : 0, first + cnt);
+    }
+    if (to == last) break;
+    first += cnt;
+    left -= cnt;
+    a_row = b_row;
+    from = to + 1;
+    to = last;
+    __syncthreads();
+    if (left > kMost) narrow<NT>(reinterpret_cast<uint32_t*>(mem), source, kMost, &from, &to);
+  }
+  __syncthreads();
+}
+
+// What the last sort does not hold: the workgroup's own bucket, if it is in its region, m records; and its share of the buckets whose regions
+// are full. Of these, a part of the key range, cut at samples of a second draw (the first had few of it or none), is picked out of the
+// input. So an order that the first draw misses costs a scan of the input for a part, a part or two to a workgroup; one that both
+// miss, one for each 4096 or 8192 records by one workgroup, and as many to narrow the range. All records but the samples in one bucket, us, by its
+// workgroup alone, which halved the range until 2048 or 4096 were left / so / in even order:
+//   20 011 records 309 / 137 / 17; 100 003 4452 / 222 / 22; 1M 128 000 / 532 / 55; 1.5M - / 2267 / 70; 3M - / 3460 / 115
+// (rows and columns fetched four at a time: 1.5M 6900 without.) A call without such buckets takes as long as before (50 000 records 15.2 / 15.2,
+// 900 000 44.6 / 43.7): few registers are left for what is rare, hence the plain sort of keys.
+template <int NT, typename VT>
+__device__ __forceinline__ void sort_the_rest(uint64_t* mem, const Record<uint64_t, VT>* __restrict__ own_region, int m, int own_first,
+                                              bool overflow, const UniqueSource& src, const VT* __restrict__ val_in, int n, int nrows, int room,
+                                              const uint64_t* __restrict__ skey, const int32_t* __restrict__ count,
+                                              int32_t* __restrict__ pos, int32_t* __restrict__ crd_out, VT* __restrict__ val_out) {
+  constexpr int kSamples = kPickKeys<NT>, kTarget = kPickKeys<NT> / 2;  // kTarget: records of a part
+  __shared__ int s_samples;
+  const int nb = gridDim.x, tid = threadIdx.x;
+  bool mine = m <= room && m > kMostWords * NT;
+  for (int part_of_all = blockIdx.x;;) {
+    int b = blockIdx.x, part = 0, parts = 1, first = own_first;
+    const Record<uint64_t, VT>* region = nullptr;
+    if (mine) {
+      region = own_region;
+    } else if (overflow) {
+      part = part_of_all;
+      part_of_all += nb;
+      first = 0;
+      for (b = 0; b < nb; ++b) {
+        const int c = count[b];
+        if (c > room) {
+          parts = (c + kTarget - 1) / kTarget;
+          if (part < parts) break;
+          part -= parts;
+        }
+        first += c;
+      }
+      if (b == nb) return;
+    } else {
+      return;
+    }
+    mine = false;
+    const uint64_t lo = b > 0 ? skey[b] : 0;
+    const uint64_t last = (b + 1 < nb ? skey[b + 1] : static_cast<uint64_t>(nrows) << src.f.row_shift) - 1;
+    uint64_t from = lo, to = last;
+    if (parts > 1) {
+      if (tid == 0) s_samples = 0;
+      __syncthreads();
+#pragma unroll 1
+      for (int t = tid; t < kSamples; t += NT) {
+        const uint64_t key = src.key(sample_pos<kSamples, 3266489917u>(t, n));
+        if (key >= lo && key <= last) mem[atomicAdd(&s_samples, 1)] = key;
+      }
+      __syncthreads();
+      const int samples = s_samples;
+      __syncthreads();
+      parts = min(parts, max(samples, 1));
+      if (part >= parts) continue;  // fewer samples than parts
+      // (a part begins at a sample after the first of them, and the samples' keys differ)
+#pragma unroll 1
+      for (int q = part; q <= part + 1; ++q) {
+        if (q == 0 || q == parts) continue;
+        const uint64_t cut = ranked_key<NT>(mem, samples, static_cast<int>(static_cast<int64_t>(q) * samples / parts), lo, last);
+        if (q == part) from = cut;
+        else to = cut - 1;
+      }
+    }
+    pick_and_store<NT, VT>(mem, PickSource<VT>{region, src, region ? m : n}, val_in, first, lo, from,
+                           to, b == 0 && part == 0 ? -1 : src.f.row_in(from), b + 1 == nb && part + 1 == parts ? nrows : src.f.row_in(to + 1),
+                           pos, crd_out, val_out);
+  }
+}
+
+// Bound by the network, whose steps wait for each other: as many workgroups to a compute unit as registers and LDS allow (1024 threads, eight
+// waves a SIMD, keep two to eight registers in scratch memory). A
 // bucket's keys are compared in 32 - LI bits first, LI being no more than its records need (14 for all of them: 1M records with
 // power-law rows 58 us, 49 so).
 template <int NT, int WAVES, typename VT>
@@ -281,14 +488,16 @@ __global__ __launch_bounds__(NT, WAVES) void reserve_finish_kernel(const Record<
                                                             int32_t* __restrict__ pos, int32_t* __restrict__ crd_out,
                                                             VT* __restrict__ val_out) {
   __shared__ __attribute__((aligned(16))) char s_mem[NT * 14 * kStagedWords];
-  __shared__ int s_before;
+  static_assert(kPickKeys<NT> * 8 <= sizeof(s_mem), "");
+  __shared__ int s_before, s_overflow;
   const int g = blockIdx.x, nb = gridDim.x, tid = threadIdx.x;
-  if (tid == 0) s_before = 0;
+  if (tid == 0) s_before = s_overflow = 0;
   __syncthreads();
-  for (int b0 = 0; b0 < g; b0 += NT) {
-    const int own = b0 + tid < g ? count[b0 + tid] : 0;
-    const int sum = wave_inclusive_sum(own);
+  for (int b0 = 0; b0 < nb; b0 += NT) {
+    const int c = b0 + tid < nb ? count[b0 + tid] : 0;
+    const int sum = wave_inclusive_sum(b0 + tid < g ? c : 0);
     if (lane_id() == kWave - 1 && sum) atomicAdd(&s_before, sum);
+    if (c > room) s_overflow = 1;
   }
   const int m = count[g];
   const uint64_t lo = g > 0 ? skey[g] : 0;
@@ -296,21 +505,16 @@ __global__ __launch_bounds__(NT, WAVES) void reserve_finish_kernel(const Record<
   const int lo_row = g > 0 ? src.f.row_in(lo) : -1, hi_row = g + 1 < nb ? src.f.row_in(last + 1) : nrows;
   __syncthreads();
   const int first = s_before;
+  if (s_overflow || m > kMostWords * NT) {  // uniform
+    sort_the_rest<NT, VT>(reinterpret_cast<uint64_t*>(s_mem), in + static_cast<int64_t>(g) * room, m, first, s_overflow, src, val_in, n, nrows, room,
+                          skey, count, pos, crd_out, val_out);
+    if (m > kMostWords * NT || m > room) return;
+  }
   if (m == 0) {
     if (tid < kWave) store_pos_range(pos, tid == 0 ? lo_row : 0, tid == 0 ? hi_row : 0, first);
     return;
   }
-  if (m > room) {
-    pick_and_store<NT, VT>(s_mem, [&](int p) { return src.key(p); }, [&](int p) { return val_in[p]; }, src.f, n, first, lo, last, lo_row,
-                           hi_row, pos, crd_out, val_out);
-    return;
-  }
   const RecordBucket<uint64_t, VT> bucket{in + static_cast<int64_t>(g) * room, lo, 0};
-  if (m > kMostWords * NT) {
-    pick_and_store<NT, VT>(s_mem, [&](int p) { return bucket.key(p); }, [&](int p) { return bucket.val(p); }, src.f, m, first, lo, last,
-                           lo_row, hi_row, pos, crd_out, val_out);
-    return;
-  }
 #define SPT_FINISH(HOW_, E_)                                                                                             \
   do {                                                                                                                   \
     constexpr int kWords = E_, kLi = number_bits(NT * kWords);                                                           \
@@ -411,7 +615,7 @@ spt_status reserve_sort_convert(int64_t n64, int64_t nrows, int64_t ncols, bool 
   const int n = static_cast<int>(n64);
   const ReservePlan P = reserve_plan(n64);
   const int cb = bits_for(ncols), pb = bits_for(n64), bits = bits_for(nrows) + cb + pb;
-  const UniqueForm f{cb + pb, by_col ? pb : 0, by_col ? 0 : cb, static_cast<uint32_t>((uint64_t{1} << cb) - 1)};
+  const UniqueForm f{cb + pb, by_col ? pb : 0, by_col ? 0 : cb, static_cast<uint32_t>((uint64_t{1} << cb) - 1), static_cast<uint32_t>((uint64_t{1} << pb) - 1)};
   const UniqueSource src{row, col, f};
   Workspace W(ws, ws_bytes);
   typedef Record<uint64_t, VT> R;

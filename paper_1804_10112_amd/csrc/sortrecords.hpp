@@ -25,9 +25,9 @@ __device__ __forceinline__ E& at32(E* p, int i) {
 
 // Position of sample t of S out of m records: one in every m / S, at a place of the stretch that
 // differs from stretch to stretch.
-template <int S>
+template <int S, uint32_t MIX = 2654435769u>
 __device__ __forceinline__ int sample_pos(int t, int m) {
-  const uint32_t jitter = (static_cast<uint32_t>(t) * 2654435769u) >> 16;
+  const uint32_t jitter = (static_cast<uint32_t>(t) * MIX) >> 16;
   return static_cast<int>((((static_cast<uint64_t>(t) << 16) | jitter) * static_cast<uint64_t>(m) / S) >> 16);
 }
 

@@ -245,8 +245,10 @@ spt_status spt_spmv_sparse_x(const spt_tensor* A, const spt_tensor* x, void* y, 
  * append_edges + append_finalize produce, the running sum of the per-row counts).
  * pos_out[N+1], crd_out[nnz], vals_out[nnz]. If both COO levels are flagged
  * SPT_ORDERED the sort is skipped. Index outputs are exact. The workspace of the
- * query suits the fastest sort; a call also runs, slower and with the same result,
- * with 256 bytes up to 65 536 entries and with 40 bytes per entry beyond.
+ * query suits the fastest sort: for unordered entries, from 16 385 of them to 1.3M
+ * up to 82 bytes per entry (fp32: 62), up to 3M 52 (39). A call also runs, slower and
+ * with the same result, with 256 bytes up to 65 536 entries and with 40 bytes per
+ * entry beyond, which is what the query asks for at most otherwise.
  */
 spt_status spt_coo_to_csr(const spt_tensor* A_coo, int32_t order /*spt_order*/,
                           int32_t* pos_out, int32_t* crd_out, void* vals_out,

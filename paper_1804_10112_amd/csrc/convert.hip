@@ -241,9 +241,15 @@ static size_t least_workspace(const spt_tensor* A) {
   return need;
 }
 
+// Do the flags say that the entries are in this order?
+static bool in_order(const spt_tensor* A, int32_t order) {
+  return (A->level[0].flags & SPT_ORDERED) && (order == SPT_ORDER_ROW_STABLE || (A->level[1].flags & SPT_ORDERED));
+}
+
 size_t coo_to_csr_workspace(const spt_tensor* A) {
   const size_t need = least_workspace(A);
-  const bool reserve = reserve_is_fastest(plan(A, SPT_ORDER_ROW_COL), A) || reserve_is_fastest(plan(A, SPT_ORDER_ROW_STABLE), A);
+  const auto reserves = [&](int32_t order) { return !in_order(A, order) && reserve_is_fastest(plan(A, order), A); };
+  const bool reserve = reserves(SPT_ORDER_ROW_COL) || reserves(SPT_ORDER_ROW_STABLE);
   return reserve ? std::max(need, reserve_sort_workspace(A->dtype, A->nvals)) : need;
 }
 
@@ -269,8 +275,7 @@ static spt_status convert_typed(const spt_tensor* A, int32_t order, int32_t* pos
     return SPT_OK;
   }
 
-  const bool sorted_in = (A->level[0].flags & SPT_ORDERED) &&
-                         (order == SPT_ORDER_ROW_STABLE || (A->level[1].flags & SPT_ORDERED));
+  const bool sorted_in = in_order(A, order);
   const int32_t* sorted_rows = row;
   const unsigned egrid = (unsigned)((nnz + kBlock - 1) / kBlock);
   if (sorted_in) {

@@ -182,3 +182,27 @@ def test_unordered_entries_are_binned_from_786432_on(form):
     for nnz in (400_000, 786_431):
         assert need(nnz) <= columns * nnz + 1024
     assert need(786_432) >= (columns + 6) * 786_432  # a row within its bin in 16 bits and a product
+
+
+@pytest.mark.parametrize("dtype,most,middle", [(np.float64, 82, 52), (np.float32, 62, 39)])
+def test_workspace_of_a_conversion(dtype, most, middle):
+    """What the header says of the query, of calls with less, and of entries that are flagged ordered, which are only copied."""
+    spec = wl.coo_spec(8, 8, [0], [0], np.ones(1, dtype), ordered=False)
+    outs = [C.c_void_p(0x1000)] * 3
+    for n in (1, 1000, 16_384, 16_385, 50_021, 65_536, 65_537, 81_921, 294_913, 360_449, 655_361, 1_310_720, 1_310_721, 2_000_003, 3 << 20, (3 << 20) + 1,
+              20_000_003, (1 << 26) + 1, 2_000_000_003):
+        for N, M in ((200, 100), (60_000, 60_000), (n // 20 + 1, n // 20 + 1), (1 << 20, 1 << 20), ((1 << 31) - 3, 1000)):
+            t = _host_desc(spec)
+            t.nvals, t.level[0].N, t.level[1].N = n, N, M
+            query = spt.spt_workspace_bytes(B.SPT_OP_COO_TO_CSR, t)
+            enough = 256 if n <= 65_536 else 40 * n
+            assert query <= (max(enough, most * n) if 16_384 < n <= 5 << 18 else max(enough, middle * n) if 5 << 18 < n <= 3 << 20 else enough), (n, N, M, query)
+            for order in (spt.SPT_ORDER_ROW_COL, spt.SPT_ORDER_ROW_STABLE):
+                assert spt.lib().spt_coo_to_csr(C.byref(t), order, *outs, C.c_void_p(0x1000), C.c_size_t(8), None) == B.SPT_ERR_WORKSPACE
+                least = int(re.search(r"of (\d+) bytes", spt.lib().spt_last_error().decode()).group(1))
+                assert least <= min(enough, query), (n, N, M, order, least)
+            for flags in ((1, 0), (1, 1)):
+                for k in range(2):
+                    t.level[k].flags = (t.level[k].flags & ~B.SPT_ORDERED) | (B.SPT_ORDERED if flags[k] else 0)
+                ordered = spt.spt_workspace_bytes(B.SPT_OP_COO_TO_CSR, t)
+                assert least <= ordered <= query and (flags == (1, 0) or ordered == least), (n, N, M, flags, ordered)

@@ -14,7 +14,8 @@
 //   - Rows of factors up to 4 GiB are found at 32-bit offsets, and CSF parks a group's first sum in LDS: with the registers
 //     that are left, five waves share a SIMD instead of four (i, k and 64-bit addresses in registers): 11M entries in CSF, fp32, J = 32,
 //     skewed 158 -> 132 us, even 189 -> 174; fp64 262 -> 215, 386 -> 383; 2.6M, fp32, J = 8 34.2 -> 30.5; factors of 51 MB, whose
-//     rows miss L2 whatever is in flight, 748 -> 755. COO, fp64, has four: with five, 16M even entries, J = 8, take 188 instead of 171.
+//     rows miss L2 whatever is in flight, 748 -> 755. COO, fp64, has four: with five, 16M even entries, J = 8, take 188 instead of 171. So has CSF, fp64,
+//     with factors beyond 4 GiB (with five, two to five registers go through scratch memory: 3M entries, J = 64 433 us, 411 with four).
 // Bound by the gathers of factor rows, large tensors by those that miss L2: what is fetched from beyond it takes all the
 // time there (50M entries, J = 32, fp32: 4.7 GB, 632 us; with all rows in L2, as a probe, 400; chunks in the order of their
 // rows of C: 593). A row of C stays in registers while k does (loaded for every entry: 700 us, and 619
@@ -255,7 +256,7 @@ __device__ __forceinline__ void marks_before(const uint32_t* marks, int16_t* bef
 // PLACED: chunks and columns as `placing` says; else chunk blockIdx.x, and all columns. U: the rows of 4 * U entries are in flight
 // together. NEAR: no factor has more than 4 GiB.
 template <typename T, int L, int V, bool CSF, bool PLACED, int U = 1, bool NEAR = true>
-__global__ __launch_bounds__(kBlock, CSF && U == 1 ? 5 : 1) void mttkrp_rows_kernel(int n, int J, int epg, const Placing placing, const int32_t* __restrict__ ci,
+__global__ __launch_bounds__(kBlock, CSF && U == 1 && NEAR ? 5 : 1) void mttkrp_rows_kernel(int n, int J, int epg, const Placing placing, const int32_t* __restrict__ ci,
                                                              const int32_t* __restrict__ ck,
                                                              const int32_t* __restrict__ cl,
                                                              const T* __restrict__ vals, const T* __restrict__ Cm,

@@ -182,11 +182,22 @@ def test_parts_of_the_columns_are_equal_and_cover_them(tmp_path):
     assert {(96, spt.SPT_F64, 2), (192, spt.SPT_F64, 4), (640, spt.SPT_F64, 4), (768, spt.SPT_F32, 8)} <= several
 
 
+def _scratch(tmp_path, source, kernel):
+    """Bytes of scratch memory of the kernels of a name."""
+    asm = tmp_path / "kernels.s"
+    flags = [f for f in spt_build.HIPCC_FLAGS if f not in ("-fPIC", "-shared")]
+    subprocess.run([HIPCC, *flags, "--offload-device-only", "-S", os.path.join(spt_build.CSRC, source), "-o", str(asm)],
+                   check=True, capture_output=True)
+    return dict(re.findall(rf"\.name:\s+(\S*{kernel}\S*)\s+\.private_segment_fixed_size: (\d+)", asm.read_text()))
+
+
 def test_the_kernel_that_gathers_slice_by_slice_keeps_its_registers(tmp_path):
     """Entries of a lane take 80 of its 128 registers; what no longer fits beside them would go through scratch memory."""
-    asm = tmp_path / "spmv_slices.s"
-    flags = [f for f in spt_build.HIPCC_FLAGS if f not in ("-fPIC", "-shared")]
-    subprocess.run([HIPCC, *flags, "--offload-device-only", "-S", os.path.join(spt_build.CSRC, "spmv_slices.hip"), "-o", str(asm)],
-                   check=True, capture_output=True)
-    scratch = dict(re.findall(r"\.name:\s+(\S*slices_spmv_kernel\S*)\s+\.private_segment_fixed_size: (\d+)", asm.read_text()))
+    scratch = _scratch(tmp_path, "spmv_slices.hip", "slices_spmv_kernel")
     assert len(scratch) == 8 and set(scratch.values()) == {"0"}, scratch
+
+
+def test_mttkrp_keeps_its_registers(tmp_path):
+    """Five waves a SIMD are asked for only where what a lane holds fits."""
+    scratch = _scratch(tmp_path, "mttkrp.hip", "mttkrp_rows_kernel")
+    assert len(scratch) > 70 and set(scratch.values()) == {"0"}, {k: v for k, v in scratch.items() if v != "0"}

@@ -76,6 +76,10 @@ struct MttkrpPlan {
 //   CSF: 1M 75 / 69, 87 / 86; 20M 692 / 560, 1281 / 1177; 5.1 and 5.1: 20M 492 / 499, 885 / 642; 0.5 and 25.6: 1M 61 / 56, 58 / 63
 //   J = 64, fp64 (four parts), 41 and 25.6: 300 000 62 / 52; 2M 219 / 192; 20M 1491 / 1174
 //   2.6 and 0.8: 1M 28.9 / 32.6; 2M 48 / 53; 5.1 and 1.5 (J = 64): 2M 82 / 98; fewer entries than the line: up to 10 % longer
+// Factors of which the 256 MB of the Infinity Cache do not hold all rows that the entries may need are not split: no L2 holds a share of their rows worth having, and a row comes from memory in
+// pieces. Parts / one part, COO, even slices: J = 64, fp64, C and D 154 and 15 MB, 1.5M entries .90, 6M .91; 154 and 154 1.06, 1.06; 512 and
+// 2.6 1.03, 1.05; 512 and 512 1.09, 1.09; 2048 and 2.6 1.15, 1.20; J = 128, fp64, 92 and 31 MB .87, .89; 307 and 31 .98, .98; 1024 and 5.1
+// 1.13, 1.15 (skewed 1.16, 1.25; CSF 1.14, 1.42); J = 32, fp64, 77 and 77 1.05, 1.04. Of 300 000 entries, J = 64, fp64, 512 and 2.6 .86, 2048 and 2.6 .83.
 // Where a part's vectors leave lanes idle (8 and 16 lanes, and whole groups of 32, have none), every workgroup issues as much for less. An eighth of
 // them costs nothing, a quarter is worth it where the factors are that large in the 512 bytes of a row that unsplit workgroups go
 // through at a time, or where a row is used by few entries, so that fetching it into every L2 once is what counts. Parts / one part, 1.5M entries, COO,
@@ -88,9 +92,10 @@ struct MttkrpPlan {
 // and of 4000 and 4000, 300 000 entries (37 to a row) and 600 000: 24 of 32, J = 192 1.02 .80, 1.18 .93; 384 .98 .73, 1.13 .84; 80 of 96, J = 320 .89
 // .80, 1.05 .94; 640 .85 .75, 1.01 .86.
 inline int mttkrp_parts(int64_t nnz, int64_t row_bytes, int64_t rows_c, int64_t rows_d, bool csf) {
-  constexpr int64_t kFactors = 9000000;
+  constexpr int64_t kFactors = 9000000, kMostFactors = 250000000;
   const int64_t c = rows_c * row_bytes, d = rows_d * row_bytes;
   if (nnz * row_bytes < 50000000 || c + d < kFactors || (csf && c < 1000000)) return 1;
+  if ((std::min(rows_c, nnz) + std::min(rows_d, nnz)) * row_bytes > kMostFactors) return 1;
   const auto worth_it = [&](int parts) {
     if (row_bytes % (parts * int64_t{kLine}) != 0) return false;
     const int64_t vectors = row_bytes / parts / 16, lanes = (vectors + 31) / 32 * 32;

@@ -769,7 +769,7 @@ static spt_status mttkrp3_typed(Format f, const spt_tensor* B, const T* Cm, cons
   if (csf) SPT_MTTKRP_AS(L_, kVec<T>, true, false, 2);                \
   else SPT_MTTKRP_AS(L_, kVec<T>, false, false, 2)
   if (P.vec == 1) { SPT_MTTKRP(4, 1); }
-  else if (P.lanes == 2 && eight) { SPT_MTTKRP_AS(2, kVec<T>, false, false, 2); }
+  else if (P.lanes == 2 && eight) { if constexpr (sizeof(T) == 4) SPT_MTTKRP_AS(2, kVec<T>, false, false, 2); }
   else if (P.lanes == 2) { SPT_MTTKRP(2, kVec<T>); }
   else if (P.lanes == 4 && eight) { SPT_MTTKRP_EIGHT(4); }
   else if (P.lanes == 4) { SPT_MTTKRP(4, kVec<T>); }

@@ -233,6 +233,7 @@ static bool reserve_is_fastest(const SortPlan& P, const spt_tensor* A) {
 
 // What a call needs. The query asks for more where the sort by reserved regions is the fastest.
 static size_t least_workspace(const spt_tensor* A) {
+  if (A->nvals == 0) return 256;  // pos is cleared
   size_t need = sample_sort_applies(A->nvals) ? sample_sort_workspace(A->dtype, A->nvals) : 0;
   for (const int32_t order : {SPT_ORDER_ROW_COL, SPT_ORDER_ROW_STABLE}) {
     const SortPlan P = plan(A, order);

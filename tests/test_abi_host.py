@@ -189,7 +189,7 @@ def test_workspace_of_a_conversion(dtype, most, middle):
     """What the header says of the query, of calls with less, and of entries that are flagged ordered, which are only copied."""
     spec = wl.coo_spec(8, 8, [0], [0], np.ones(1, dtype), ordered=False)
     outs = [C.c_void_p(0x1000)] * 3
-    for n in (1, 1000, 16_384, 16_385, 50_021, 65_536, 65_537, 81_921, 294_913, 360_449, 655_361, 1_310_720, 1_310_721, 2_000_003, 3 << 20, (3 << 20) + 1,
+    for n in (0, 1, 1000, 16_384, 16_385, 50_021, 65_536, 65_537, 81_921, 294_913, 360_449, 655_361, 1_310_720, 1_310_721, 2_000_003, 3 << 20, (3 << 20) + 1,
               20_000_003, (1 << 26) + 1, 2_000_000_003):
         for N, M in ((200, 100), (60_000, 60_000), (n // 20 + 1, n // 20 + 1), (1 << 20, 1 << 20), ((1 << 31) - 3, 1000)):
             t = _host_desc(spec)

@@ -41,18 +41,32 @@ def gpu_spmv(spec, x, repeat=1, misalign=False):
     return outs[0] if repeat == 1 else outs
 
 
+def conversion_workspaces(A, nnz):
+    """Workspaces for spt_coo_to_csr: the query's and, where that is for the sort by reserved regions, as much as the header says is
+    enough, with which the sample sort or the radix sort runs."""
+    import torch
+    import paper_1804_10112_amd as spt
+    query, enough = spt.spt_workspace_bytes(spt.SPT_OP_COO_TO_CSR, A), 256 if nnz <= 65_536 else 40 * nnz
+    return [torch.empty(n, dtype=torch.uint8, device="cuda") for n in ([query, enough] if enough < query else [query])]
+
+
 def gpu_coo_to_csr(spec, order, misalign=False):
+    """With each workspace; the results are the same, bit for bit."""
     import torch
     import paper_1804_10112_amd as spt
     A = spt.DeviceTensor(spec, misalign=misalign)
     N, nnz = spec.dims[0], len(spec.vals)
-    pos = torch.full((N + 1,), -7, dtype=torch.int32, device="cuda")
-    crd = torch.full((max(nnz, 1),), -7, dtype=torch.int32, device="cuda")
-    vals = torch.zeros(max(nnz, 1), dtype=A.torch_dtype, device="cuda")
-    ws = A.workspace(spt.SPT_OP_COO_TO_CSR)
-    spt.spt_coo_to_csr(A, order, pos, crd, vals, ws)
-    torch.cuda.synchronize()
-    return pos.cpu().numpy(), crd.cpu().numpy()[:nnz], vals.cpu().numpy()[:nnz]
+    got = []
+    for ws in conversion_workspaces(A, nnz):
+        pos = torch.full((N + 1,), -7, dtype=torch.int32, device="cuda")
+        crd = torch.full((max(nnz, 1),), -7, dtype=torch.int32, device="cuda")
+        vals = torch.zeros(max(nnz, 1), dtype=A.torch_dtype, device="cuda")
+        spt.spt_coo_to_csr(A, order, pos, crd, vals, ws)
+        torch.cuda.synchronize()
+        got.append((pos.cpu().numpy(), crd.cpu().numpy()[:nnz], vals.cpu().numpy()[:nnz]))
+    for other in got[1:]:
+        assert all(np.array_equal(a.view(np.uint8), b.view(np.uint8)) for a, b in zip(got[0], other)), f"{ws.numel()} bytes of workspace"
+    return got[0]
 
 
 def gpu_ttv(spec, c, misalign=False):

@@ -1,7 +1,10 @@
 """COO -> CSR by two partitions: buckets whose keys take 32 bits from their lower bound on, and buckets whose keys do not
-(a segment has records of 4 or 8 bytes of key). Built on the GPU; the reference is a stable sort, bit for bit."""
+(a segment has records of 4 or 8 bytes of key). Up to 3M records whose keys and positions take 64 bits that is the sort with less
+workspace than the query's; both run. Built on the GPU; the reference is a stable sort, bit for bit."""
 import numpy as np
 import pytest
+
+from gpu_util import conversion_workspaces
 
 pytestmark = pytest.mark.gpu
 
@@ -18,16 +21,16 @@ def convert_and_check(N, M, row, col, by_col, dtype):
     row32, col32, end = row.int(), col.int(), torch.tensor([0, n], dtype=torch.int32, device="cuda")
     A.c.level[0].pos, A.c.level[0].crd, A.c.level[1].crd = end.data_ptr(), row32.data_ptr(), col32.data_ptr()
     A.c.vals, A.c.nvals = vals.data_ptr(), n
-    pos = torch.full((N + 1,), -1, dtype=torch.int32, device="cuda")
-    crd, out = torch.full((n,), -1, dtype=torch.int32, device="cuda"), torch.full_like(vals, -1)
-    ws = torch.empty(spt.spt_workspace_bytes(spt.SPT_OP_COO_TO_CSR, A), dtype=torch.uint8, device="cuda")
-    spt.spt_coo_to_csr(A, spt.SPT_ORDER_ROW_COL if by_col else spt.SPT_ORDER_ROW_STABLE, pos, crd, out, ws)
     at = torch.sort(row * M + col if by_col else row, stable=True).indices
     want = torch.zeros(N + 1, dtype=torch.int64, device="cuda")
     want[1:] = torch.bincount(row, minlength=N).cumsum(0)
-    assert torch.equal(pos.long(), want)
-    assert torch.equal(crd, col32[at])
-    assert torch.equal(out, vals[at])
+    for ws in conversion_workspaces(A, n):
+        pos = torch.full((N + 1,), -1, dtype=torch.int32, device="cuda")
+        crd, out = torch.full((n,), -1, dtype=torch.int32, device="cuda"), torch.full_like(vals, -1)
+        spt.spt_coo_to_csr(A, spt.SPT_ORDER_ROW_COL if by_col else spt.SPT_ORDER_ROW_STABLE, pos, crd, out, ws)
+        assert torch.equal(pos.long(), want)
+        assert torch.equal(crd, col32[at])
+        assert torch.equal(out, vals[at])
 
 
 @pytest.mark.parametrize("what,by_col,N,M,n", [

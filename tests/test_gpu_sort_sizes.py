@@ -1,8 +1,11 @@
-"""COO -> CSR at the sizes where its plan changes: tiles of 1024, 2048 and 4096 records, one partition or two, samples of
+"""COO -> CSR at the sizes where the sample sort's plan changes (up to 3M records with less workspace than the query's, too, with
+which the sort by reserved regions runs): tiles of 1024, 2048 and 4096 records, one partition or two, samples of
 1024 to 4096, buckets that take four, six, eight and sixteen words of a thread, and counts whose rows end off 16 bytes.
 Built on the GPU; the reference is a stable sort, bit for bit."""
 import numpy as np
 import pytest
+
+from gpu_util import conversion_workspaces
 
 pytestmark = pytest.mark.gpu
 
@@ -54,13 +57,13 @@ def test_sizes(keys, by_col, n, dtype):
     row32, col32, end = row.int(), col.int(), torch.tensor([0, n], dtype=torch.int32, device="cuda")
     A.c.level[0].pos, A.c.level[0].crd, A.c.level[1].crd = end.data_ptr(), row32.data_ptr(), col32.data_ptr()
     A.c.vals, A.c.nvals = vals.data_ptr(), n
-    pos = torch.full((N + 1,), -1, dtype=torch.int32, device="cuda")
-    crd, out = torch.full((n,), -1, dtype=torch.int32, device="cuda"), torch.full_like(vals, -1)
-    ws = torch.empty(spt.spt_workspace_bytes(spt.SPT_OP_COO_TO_CSR, A), dtype=torch.uint8, device="cuda")
-    spt.spt_coo_to_csr(A, spt.SPT_ORDER_ROW_COL if by_col else spt.SPT_ORDER_ROW_STABLE, pos, crd, out, ws)
     at = torch.sort(row * M + col if by_col else row, stable=True).indices
     want = torch.zeros(N + 1, dtype=torch.int64, device="cuda")
     want[1:] = torch.bincount(row, minlength=N).cumsum(0)
-    assert torch.equal(pos.long(), want)
-    assert torch.equal(crd, col32[at])
-    assert torch.equal(out, vals[at])
+    for ws in conversion_workspaces(A, n):
+        pos = torch.full((N + 1,), -1, dtype=torch.int32, device="cuda")
+        crd, out = torch.full((n,), -1, dtype=torch.int32, device="cuda"), torch.full_like(vals, -1)
+        spt.spt_coo_to_csr(A, spt.SPT_ORDER_ROW_COL if by_col else spt.SPT_ORDER_ROW_STABLE, pos, crd, out, ws)
+        assert torch.equal(pos.long(), want)
+        assert torch.equal(crd, col32[at])
+        assert torch.equal(out, vals[at])

@@ -27,6 +27,7 @@
 // not enough for the larger segments; such a call takes 2 to 3 % longer (60M records 1478 -> 1515 to 1529 us; with
 // the ranks of the bucket's records counted, 10.4 ms).
 //
+// (From 16 385 records to 3M most calls are reserve_sort.hip's; here come those with wider keys, or less workspace than the query's.)
 // Measured against the six radix passes it replaces (fp64): 60M records with power-law rows
 // 3.09 -> 1.52 ms (splitters 10 + 70 us, classify 2 x 133, offsets 8 + 9, partitions 405 + 352, finish 400; with whole
 // keys and separate arrays the second partition took 418); 20M 0.52 ms, 5M 0.19 ms, 250 000 48 us,

@@ -569,7 +569,7 @@ static ReservePlan reserve_plan(int64_t n) {
                   : n <= 3 << 19 ? ReservePlan{1024, 16384, 4096, 512, 0}
                                  : ReservePlan{1024, 16384, 4096, 1024, 0};
   // In random order, a bucket of eight samples has more than five times the mean with a chance of 2e-10, one of sixteen more
-  // than 3.2 times with 3e-9. (What nine words of a thread hold, 3.6 and 2.9 times the mean at least: 1e-6 and 5e-8.)
+  // than 3.2 times with 3e-9; what it costs, stands at sort_the_rest. (What nine words of a thread hold, 3.6 and 2.9 times the mean at least: 1e-6 and 5e-8.)
   const int64_t mean = (n + P.nb - 1) / P.nb;
   P.room = static_cast<int>(P.samples == 8 * P.nb ? 5 * mean : (16 * mean + 4) / 5);
   return P;

@@ -10,8 +10,10 @@ from paper_1804_10112_amd.binding import SptTensor
 pytestmark = pytest.mark.gpu
 
 
-def _coo(row, col, vals, N, M):
-    dev = [torch.from_numpy(a).cuda() for a in (np.array([0, len(row)], np.int32), row, col, vals)]
+def _coo(row, col, vals, N, M, shift=0):
+    # shift: rows and columns begin that many elements beyond a boundary of 16 bytes
+    dev = [torch.from_numpy(np.concatenate([np.zeros(s, a.dtype), a])).cuda()[s:]
+           for a, s in ((np.array([0, len(row)], np.int32), 0), (row, shift), (col, shift and 4 - shift), (vals, 0))]
     t = SptTensor()
     t.order, t.nlevels, t.dtype = 2, 2, spt.SPT_F64 if vals.dtype == np.float64 else spt.SPT_F32
     t.vals, t.nvals = dev[3].data_ptr(), len(row)
@@ -23,8 +25,8 @@ def _coo(row, col, vals, N, M):
     return t, dev
 
 
-def _check(row, col, vals, N, M, order=spt.SPT_ORDER_ROW_COL, ws_bytes=None):
-    A, keep = _coo(row, col, vals, N, M)
+def _check(row, col, vals, N, M, order=spt.SPT_ORDER_ROW_COL, ws_bytes=None, shift=0):
+    A, keep = _coo(row, col, vals, N, M, shift)
     n = len(row)
     pos, crd = (torch.empty(k, dtype=torch.int32, device="cuda") for k in (N + 1, n))
     out = torch.empty(n, dtype=keep[3].dtype, device="cuda")
@@ -137,7 +139,7 @@ def test_buckets_beyond_their_regions(n, N, M, rows, order):
         row[at] = rng.integers(0, 10, len(at))
     row, col = row.astype(np.int32), col.astype(np.int32)
     assert np.sort(_buckets(row, col, order))[-2 if rows == "two" else -1] > room
-    _check(row, col, rng.random(n).astype(np.float32 if n & 1 else np.float64), N, M, order)
+    _check(row, col, rng.random(n).astype(np.float32 if n & 1 else np.float64), N, M, order, shift=n % 4)
 
 
 @pytest.mark.parametrize("n,clustered", [(20_011, False), (20_011, True), (100_003, False), (100_003, True), (300_000, True)])
